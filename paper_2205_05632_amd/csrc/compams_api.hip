@@ -49,7 +49,7 @@ void launcher_end(Launcher* L, int slot, hipStream_t stream) {
 namespace {
 
 const char* const kSlotNames[kNumSlots] = {
-    "topk_pass_a", "topk_band", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final", "topk_emit", "topk_offsets",
+    "topk_pass_a", "topk_band", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final", "topk_offsets",
     "bs_pass1", "bs_finalize", "bs_pass2", "bs_amsgrad", "none_amsgrad", "wire_encode", "wire_decode"};
 
 static_assert(kCountersPerRow == COMPAMS_COUNTERS_PER_ROW, "the kernels' stride of the counters is the header's");
@@ -61,7 +61,7 @@ struct Layout {
   // top-k
   size_t rows, flags, counters, hist0, hist1, hist1x, hist2, bhist, xcur, chunk_rec, blk, blk_prefix, sel_off, desc, desc2, bnd, bnd_sel, cand, band,
       idx, val, tau, count_gt, wire_total, wire_tile_off, wire_tile_sum, sel_off_srv, segs, map_first, map_level0, map_sweep,
-      map_count, map_emit, map_final, micro_list;
+      map_count, map_final, micro_list;
   // block-sign
   size_t offsets, chunk_block, acc, special, scales, bits;
   uint32_t acc_replicas;
@@ -98,7 +98,7 @@ bool basic_valid(const compams_config* c) {
 
 // Top-k inside every block: the shape of one block's selection problem and how many workgroups it gets.
 struct BlockShape {
-  uint32_t off, d, k, nc, cap, band_cap, cpw, groups_first, groups_level0, groups_sweep, count_blocks, emit_slots, micro;
+  uint32_t off, d, k, nc, cap, band_cap, cpw, groups_first, groups_level0, groups_sweep, count_blocks, micro;
 };
 
 // Entries of a problem's band list: the window around the expected threshold holds a fraction of k.
@@ -124,7 +124,6 @@ std::vector<BlockShape> block_shapes(const compams_config* c) {
     s.micro = s.d <= kMicroCoords ? 1u : 0u;
     s.band_cap = s.micro ? 0u : band_capacity(s.k, s.cap);
     s.count_blocks = (s.nc + s.cpw - 1) / s.cpw;
-    s.emit_slots = (s.nc + kWaves - 1) / kWaves;
     chunks_per_worker += s.nc;
   }
   // the first pass takes a workgroup per chunk; about 512 workgroups find the threshold buckets and 2048 make the
@@ -170,7 +169,7 @@ Layout make_layout(const compams_config* c) {
     L.chunk_rec = take(n * nc * 16);
     L.blk = take(n * kMaxCountBlocks * 8);
     L.blk_prefix = take(n * kMaxCountBlocks * 8);
-    L.sel_off = take(n * (nc + 1) * 4);
+    L.sel_off = take(n * (nc * kWaves + 1) * 4);
     L.desc = take(n * nc * 8);
     L.desc2 = take(n * nc * 8);
     L.bnd = take(n * kBoundaryCap * 8);
@@ -184,17 +183,17 @@ Layout make_layout(const compams_config* c) {
     L.wire_total = take(n * 4);
     L.wire_tile_off = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
     L.wire_tile_sum = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
-    L.sel_off_srv = take(n * (nc + 1) * 4);
+    L.sel_off_srv = take(n * (nc * kWaves + 1) * 4);
   } else if (c->compressor == COMPAMS_TOPK_BLOCKS) {
     const std::vector<BlockShape> shapes = block_shapes(c);
     const size_t M = shapes.size(), S = n * M;
-    size_t k = 0, chunks = 0, caps = 0, bcaps = 0, wg_first = 0, wg_level0 = 0, wg_sweep = 0, wg_count = 0, wg_emit = 0, micro = 0,
+    size_t k = 0, chunks = 0, caps = 0, bcaps = 0, wg_first = 0, wg_level0 = 0, wg_sweep = 0, wg_count = 0, micro = 0,
            big = 0;
     uint32_t cap_max = 0, band_max = 0;
     for (const BlockShape& b : shapes) {
       k += b.k; chunks += b.nc; caps += b.cap; cap_max = std::max(cap_max, b.cap);
       bcaps += b.band_cap; band_max = std::max(band_max, b.band_cap);
-      wg_first += b.groups_first; wg_level0 += b.groups_level0; wg_sweep += b.groups_sweep; wg_count += b.count_blocks; wg_emit += b.emit_slots;
+      wg_first += b.groups_first; wg_level0 += b.groups_level0; wg_sweep += b.groups_sweep; wg_count += b.count_blocks;
       micro += b.micro;
       big += b.nc >= kSubListMinChunks ? 1 : 0;  // blocks whose candidate lists are kept as several runs
     }
@@ -206,12 +205,11 @@ Layout make_layout(const compams_config* c) {
     L.flat.wg_level0 = static_cast<uint32_t>(n * wg_level0);
     L.flat.wg_sweep = static_cast<uint32_t>(n * wg_sweep);
     L.flat.wg_count = static_cast<uint32_t>(n * wg_count);
-    L.flat.wg_emit = static_cast<uint32_t>(n * wg_emit);
     L.flat.wg_final = static_cast<uint32_t>(chunks);
     L.flat.band_stride = bcaps;
     L.flat.blocks = static_cast<uint32_t>(M);
     L.flat.chunk_stride = static_cast<uint32_t>(chunks);
-    L.flat.seloff_stride = static_cast<uint32_t>(chunks + M);
+    L.flat.seloff_stride = static_cast<uint32_t>(chunks * kWaves + M);
     L.flat.cand_stride = caps;
     L.rows = take(S * sizeof(TopkRow));
     L.flags = take(64);
@@ -225,7 +223,7 @@ Layout make_layout(const compams_config* c) {
     L.chunk_rec = take(n * chunks * 16);
     L.blk = take(S * kMaxCountBlocks * 8);
     L.blk_prefix = take(S * kMaxCountBlocks * 8);
-    L.sel_off = take(n * (chunks + M) * 4);
+    L.sel_off = take(n * (chunks * kWaves + M) * 4);
     L.desc = take(n * chunks * 8);
     L.desc2 = take(n * chunks * 8);
     L.bnd = take(S * kBoundaryCap * 8);
@@ -239,13 +237,12 @@ Layout make_layout(const compams_config* c) {
     L.wire_total = take(n * 4);
     L.wire_tile_off = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
     L.wire_tile_sum = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
-    L.sel_off_srv = take(n * (nc + 1) * 4);
+    L.sel_off_srv = take(n * (nc * kWaves + 1) * 4);
     L.segs = take(S * sizeof(Seg));
     L.map_first = take(L.flat.wg_first * sizeof(WgSlot));
     L.map_level0 = take(L.flat.wg_level0 * sizeof(WgSlot));
     L.map_sweep = take(L.flat.wg_sweep * sizeof(WgSlot));
     L.map_count = take(L.flat.wg_count * sizeof(WgSlot));
-    L.map_emit = take(L.flat.wg_emit * sizeof(WgSlot));
     L.map_final = take(L.flat.wg_final * sizeof(WgSlot));
     L.micro_list = take(L.num_micro * 4);
   } else if (c->compressor == COMPAMS_BLOCKSIGN) {
@@ -388,7 +385,7 @@ static void bind_topk_workspace(compams_ctx* ctx, char* w) {
   t.tau = reinterpret_cast<uint32_t*>(w + lay.tau);
   t.sel_off_srv = reinterpret_cast<uint32_t*>(w + lay.sel_off_srv);
   t.segs = nullptr;
-  t.map_first = t.map_level0 = t.map_sweep = t.map_count = t.map_emit = t.map_final = nullptr;
+  t.map_first = t.map_level0 = t.map_sweep = t.map_count = t.map_final = nullptr;
   t.micro_list = nullptr;
   ctx->tkopt.cap = lay.cap_alloc;
   ctx->tkopt.predict = 1;
@@ -489,7 +486,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
     if (cfg->compressor == COMPAMS_TOPK_BLOCKS) {
       // the segments (worker-major: worker i, block b is segment i * M + b) and the workgroups of the flat launches
       std::vector<Seg> segs;
-      std::vector<WgSlot> m_first, m_level0, m_sweep, m_count, m_emit, m_final;
+      std::vector<WgSlot> m_first, m_level0, m_sweep, m_count, m_final;
       std::vector<uint32_t> micro;
       try {
         const std::vector<BlockShape> shapes = block_shapes(cfg);
@@ -507,7 +504,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
             std::memset(&sg, 0, sizeof sg);
             sg.elem_off = i * cfg->ld + sh.off;
             sg.chunk_base = static_cast<uint64_t>(i) * chunks + c_at;
-            sg.seloff_base = static_cast<uint64_t>(i) * (chunks + M) + c_at + b;
+            sg.seloff_base = static_cast<uint64_t>(i) * (chunks * kWaves + M) + c_at * kWaves + b;
             sg.cand_base = static_cast<uint64_t>(i) * caps + cap_at;
             sg.list_base = static_cast<uint64_t>(i) * lay.k_total + k_at;
             sg.band_base = static_cast<uint64_t>(i) * bcaps + band_at;
@@ -523,7 +520,6 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
             for (uint32_t q = 0; q < sh.groups_level0; ++q) m_level0.push_back(WgSlot{si, q});
             for (uint32_t q = 0; q < sh.groups_sweep; ++q) m_sweep.push_back(WgSlot{si, q});
             for (uint32_t q = 0; q < sh.count_blocks; ++q) m_count.push_back(WgSlot{si, q});
-            for (uint32_t q = 0; q < sh.emit_slots; ++q) m_emit.push_back(WgSlot{si, q * static_cast<uint32_t>(kWaves)});
             if (i == 0)
               for (uint32_t q = 0; q < sh.nc; ++q) m_final.push_back(WgSlot{si, q});
             c_at += sh.nc; cap_at += sh.cap; k_at += sh.k; band_at += sh.band_cap;
@@ -541,18 +537,16 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
         ok(hipMemcpy(w + lay.map_level0, m_level0.data(), m_level0.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       ok(hipMemcpy(w + lay.map_sweep, m_sweep.data(), m_sweep.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       ok(hipMemcpy(w + lay.map_count, m_count.data(), m_count.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
-      ok(hipMemcpy(w + lay.map_emit, m_emit.data(), m_emit.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       ok(hipMemcpy(w + lay.map_final, m_final.data(), m_final.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       if (!micro.empty()) ok(hipMemcpy(w + lay.micro_list, micro.data(), micro.size() * 4, hipMemcpyHostToDevice));
       if (m_first.size() != lay.flat.wg_first || m_level0.size() != lay.flat.wg_level0 || m_sweep.size() != lay.flat.wg_sweep || m_count.size() != lay.flat.wg_count ||
-          m_emit.size() != lay.flat.wg_emit || m_final.size() != lay.flat.wg_final || micro.size() != lay.num_micro)
+          m_final.size() != lay.flat.wg_final || micro.size() != lay.num_micro)
         ok(hipErrorInvalidValue);  // the tables and the launch sizes come from the same shapes
       t.segs = reinterpret_cast<const Seg*>(w + lay.segs);
       t.map_first = reinterpret_cast<const WgSlot*>(w + lay.map_first);
       t.map_level0 = reinterpret_cast<const WgSlot*>(w + lay.map_level0);
       t.map_sweep = reinterpret_cast<const WgSlot*>(w + lay.map_sweep);
       t.map_count = reinterpret_cast<const WgSlot*>(w + lay.map_count);
-      t.map_emit = reinterpret_cast<const WgSlot*>(w + lay.map_emit);
       t.map_final = reinterpret_cast<const WgSlot*>(w + lay.map_final);
       t.micro_list = reinterpret_cast<const uint32_t*>(w + lay.micro_list);
     }

@@ -87,20 +87,21 @@ struct TopkRow {
   uint32_t band_valid;  // the next first pass may also fill the band list and the bucket histogram
   uint32_t band_lo, band_hi;  // keys; band_lo >= b_guess << kL0Shift, band_hi > band_lo
   uint32_t band_mul;    // bucket of a key inside the band: see band_bucket()
+  // (read together by the last kernel, up to tie_last)
   uint32_t fast;        // this step's threshold was found in the band: the general kernels skip the problem
   uint32_t mode;        // kMode*
+  uint32_t tau;         // the k-th largest key
+  uint32_t r;           // how many keys equal to tau are selected
+  uint32_t ties;        // how many keys equal tau
+  uint32_t tie_last;    // fast: ties are taken up to and including this coordinate (of the problem)
   uint32_t n_src;       // entries in the candidate list (kModeCand / kModeNeedB)
   uint32_t bstar;       // level-0 bucket that holds the k-th largest key
   uint32_t need;        // keys still to be taken inside the current prefix
   uint32_t prefix1;     // bits 30..9 of the k-th largest key (after level 1)
-  uint32_t tau;         // the k-th largest key
-  uint32_t r;           // how many keys equal to tau are selected
-  uint32_t ties;        // how many keys equal tau
   uint32_t level1_done;    // bits 30..9 of the threshold key are known (prefix1 / need are valid)
   uint32_t ticket[4];      // "last workgroup of the row" counters of kernels 1..4; zero between launches
   uint32_t n_lists;        // runs of the candidate list: kSubLists (run s from entry s * (capacity / kSubLists) on), or 1
   uint32_t n_sub[kSubLists];  // entries of each run (n_src in all)
-  uint32_t tie_last;       // fast: ties are taken up to and including this coordinate (of the problem)
   uint32_t tau_prev;       // the threshold key of the step before (0: none)
   uint32_t above;          // entries at or above band_hi (a list kept as one run; else in the runs' cursor lines)
   uint32_t bnd_n;          // entries of the threshold's bucket gathered so far (k_topk_band); zero between launches
@@ -126,7 +127,7 @@ __device__ __forceinline__ uint32_t band_bucket(uint32_t rel, uint32_t mul) { re
 struct Seg {
   int64_t elem_off;      // first element, relative to the start of g and of e
   uint64_t chunk_base;   // first entry in the per-chunk tables (segment descriptors, count records)
-  uint64_t seloff_base;  // first entry in sel_off (a segment has one entry more than it has chunks)
+  uint64_t seloff_base;  // first entry in sel_off (a segment has one entry more than it has quarters of chunks)
   uint64_t cand_base;    // first entry of the segment's candidate list
   uint64_t list_base;    // first entry of the segment's slice of the worker's (coordinate, value) list
   uint64_t band_base;    // first entry of the segment's band list
@@ -170,8 +171,10 @@ struct TopkWorkspace {
                         //                  within the chunk's count block
   uint2* blk;           // n * kMaxCountBlocks : the two totals of every count block
   uint2* blk_prefix;    // n * kMaxCountBlocks : for a problem selected by k_topk_band, the totals of the blocks
-                        // before each block (the sums the last kernel would otherwise form per chunk)
-  uint32_t* sel_off;    // n * (num_chunks + 1) : where each chunk's slice of the worker's list starts
+                        // before each block (the sums the last kernel would otherwise form per chunk), and how many
+                        // of the kept entries of the threshold's bucket lie before each block
+  uint32_t* sel_off;    // n * (4 num_chunks + 1) : where the slice of the worker's list starts that belongs to each
+                        //                          quarter of a chunk
   uint32_t* count_gt;   // n : selected entries whose key lies strictly above the threshold key
   uint32_t* wire_total;    // n : words of the gap stream of the message being packed or unpacked
   uint32_t* wire_tile_off; // n * ceil(k / kWireTile) : where each tile of gaps starts in its stream
@@ -195,11 +198,10 @@ struct TopkWorkspace {
   const WgSlot* map_level0;
   const WgSlot* map_sweep;
   const WgSlot* map_count;
-  const WgSlot* map_emit;   // .group = first chunk of the four that the workgroup's wavefronts take
   const uint32_t* micro_list;  // segments that are micro problems; a first-pass workgroup with kMicroFlag takes
                                // .group (<= 4) of them, from entry (.seg without the flag) on, one per wavefront
   const WgSlot* map_final;  // .seg = block (worker 0's segment of it), .group = chunk of the block
-  uint32_t* sel_off_srv;    // n * (chunks of a whole row + 1) : list offsets per chunk of coordinates, for the
+  uint32_t* sel_off_srv;    // n * (4 * chunks of a whole row + 1) : list offsets per quarter of a chunk, for the
                             //                                   server's lines run from lists
 };
 
@@ -258,7 +260,7 @@ struct Geometry {
 
 // Kernel slots for optional timing.
 enum KernelSlot {
-  kSlotPassA = 0, kSlotBand, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal, kSlotTopkEmit, kSlotTopkOffsets,
+  kSlotPassA = 0, kSlotBand, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal, kSlotTopkOffsets,
   kSlotBsPass1, kSlotBsFinal, kSlotBsPass2, kSlotBsAms,
   kSlotNoneAms, kSlotWireEncode, kSlotWireDecode, kNumSlots
 };
@@ -272,7 +274,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
                      Launcher* L);
 // Sizes of the flat launches of top-k inside every block.
 struct TopkFlat {
-  uint32_t wg_first, wg_level0, wg_sweep, wg_count, wg_emit, wg_final;
+  uint32_t wg_first, wg_level0, wg_sweep, wg_count, wg_final;
   // from worker i's segment of a block to worker i + 1's: segment index, chunk tables, list offsets, candidates
   uint32_t blocks, chunk_stride, seloff_stride;
   uint64_t cand_stride, band_stride;

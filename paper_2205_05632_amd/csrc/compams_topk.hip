@@ -303,7 +303,7 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
 // x = e + g with the pending zeros honoured, stored in place of e; the k-th largest key by a bit-by-bit search
 // over the keys, which stay in registers (31 steps of ballots: the largest t with at least k keys >= t); the
 // selected entries in coordinate order into the problem's part of the worker's list (ties as everywhere: in
-// coordinate order until r are in); and the records the last kernel reads (it finds the list written).
+// coordinate order until r are in), which the last kernel reads.
 // bm: 32 words of LDS of this wavefront (PEND only).  No barrier: other wavefronts of the workgroup do other
 // problems.
 constexpr int kMicroRounds = static_cast<int>(kMicroCoords / 256);
@@ -321,7 +321,7 @@ __device__ __forceinline__ void micro_problem(const float* __restrict__ g, float
     if (lane < kMicroCoords / 32) bm[lane] = 0;
     const uint32_t* so = ws.sel_off + sg.seloff_base;
     const uint32_t lo = so[0];
-    const uint32_t hi = so[1] < k ? so[1] : k;
+    const uint32_t hi = so[kWaves] < k ? so[kWaves] : k;  // (one chunk: its end)
     for (uint32_t q = lo + lane; q < hi; q += 64) {
       const uint32_t jl = static_cast<uint32_t>(idx[q]) - sg.coord_base;
       if (jl < kMicroCoords) atomicOr(&bm[jl >> 5], 1u << (jl & 31u));
@@ -406,8 +406,6 @@ __device__ __forceinline__ void micro_problem(const float* __restrict__ g, float
     cn[3] = r_take;
     cn[4] = 0;
     cn[5] = 1;
-    ws.chunk_rec[sg.chunk_base] = make_uint4(gt, ties, 0u, 0u);  // one chunk, nothing before it
-    ws.blk[static_cast<size_t>(seg) * kMaxCountBlocks] = make_uint2(gt, ties);
   }
   // the values come back from where this wavefront has just stored them
   emit_chunk(kModeDense, er, d, 0u, nullptr, make_uint2(0u, 0u), 0u, tau, r_take, r_take == ties, 0u, 0u, idx, val, k,
@@ -466,7 +464,7 @@ __device__ __forceinline__ SegCtx seg_ctx(Geometry& geo, TopkOptions& opt, const
     c.elem_off = static_cast<int64_t>(c.seg) * geo.ld;
     c.coord_base = 0;
     c.chunk_base = static_cast<size_t>(c.seg) * geo.num_chunks;
-    c.seloff_base = static_cast<size_t>(c.seg) * (geo.num_chunks + 1);
+    c.seloff_base = static_cast<size_t>(c.seg) * (geo.num_chunks * kWaves + 1);
     c.cand_base = static_cast<size_t>(c.seg) * opt.cap;
     c.list_base = static_cast<size_t>(c.seg) * geo.k;
     c.band_base = static_cast<size_t>(c.seg) * opt.band_cap;
@@ -588,6 +586,7 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 // another.  The level-0 histogram is taken afterwards, from the candidate list (k_topk_level0).
 // ---------------------------------------------------------------------------------------------
 constexpr int kLeanRounds = kRounds / kWaves;  // rounds of a chunk per wavefront
+constexpr uint32_t kQuarterCoords = kChunk / kWaves;
 constexpr int kStageQ = 512;                   // staged candidates per wavefront (of at most 1024 coordinates)
 
 // UNI: grid (chunks, rows).  Otherwise (top-k inside every block) the launch is flat over map_first: a workgroup
@@ -645,8 +644,8 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   uint32_t prev_lo = 0, prev_hi = 0;
   if constexpr (PEND) {
     const uint32_t* prev_off = ws.sel_off + sc.seloff_base;
-    prev_lo = table_u32(prev_off, c);
-    prev_hi = table_u32(prev_off, c + 1);
+    prev_lo = table_u32(prev_off, c * kWaves + wave);
+    prev_hi = table_u32(prev_off, c * kWaves + wave + 1);
   }
   const bool pred = use_guess && rw[0] != 0;  // workgroup-uniform
   const uint32_t bg = rw[1];
@@ -668,8 +667,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     const int32_t* prev_idx = ws.idx + sc.list_base;
     const uint32_t lo = prev_lo;
     const uint32_t hi = prev_hi < geo.k ? prev_hi : geo.k;
-    // 256 entries of the chunk's slice per trip, requested together (a chunk that holds entries at all holds
-    // 80 to 150 of a worker's: one round trip instead of two or three in a row)
+    // 256 entries of the quarter's slice per trip, requested together (one round trip unless the quarter is crowded)
     for (uint32_t q = lo + lane; q < hi; q += 256) {
       uint32_t jv[4];
 #pragma unroll
@@ -1099,12 +1097,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       if (t < n_boundary) en = make_uint2(load_agent(view, 2 * t), load_agent(view, 2 * t + 1));
       b_en[t] = en;
     }
-    {
-      uint32_t all;
-      const uint32_t before = block_excl_scan<kWG>(my_total, scratch, &all);  // (ends with a barrier of its own)
-      if (t < sc.groups) ws.blk_prefix[static_cast<size_t>(row) * kMaxCountBlocks + t] = make_uint2(before, 0u);
-    }
-    __syncthreads();
+    uint32_t all_totals;
+    const uint32_t blocks_before = block_excl_scan<kWG>(my_total, scratch, &all_totals);  // (barriers of its own)
     // rank by (key descending, coordinate ascending): coordinates are distinct, so ranks are
     bool kept = false;
     uint32_t my_key = 0, my_coord = 0xffffffffu;
@@ -1149,6 +1143,12 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     n_kept = need;
     uint32_t* sel = ws.bnd_sel + static_cast<size_t>(row) * kBoundaryCap;
     if (t < kBoundaryCap) sel[t] = b_rank[t];
+    if (t < sc.groups) {
+      const uint32_t block_lo = t * cpw * kChunk;  // (below d: 32 bits hold it)
+      uint32_t kept_before = 0;
+      for (uint32_t q = 0; q < need; ++q) kept_before += b_rank[q] < block_lo ? 1u : 0u;
+      ws.blk_prefix[static_cast<size_t>(row) * kMaxCountBlocks + t] = make_uint2(blocks_before, kept_before);
+    }
     if (t == 0) {
       // ties kept: those at coordinates <= last_coord; all of them if the last tie is kept
       const uint32_t ties_kept = suf[1], ties_after = n_ties - ties_kept;
@@ -1665,15 +1665,6 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 5: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers.
-//   Phase 1: a wavefront finds where its workers' entries of this chunk go in the workers' lists (entries
-//            above the threshold in earlier chunks, plus the ties taken there: in coordinate order until r
-//            are in) and writes the selected (coordinate, value) pairs there.
-//   Phase 2: the chunk's entries are added into an LDS tile of the summed gradient, one worker after
-//            the other (a barrier between them): the fp32 sum has exactly the order i = 0 .. n-1, and
-//            one worker's coordinates are distinct, so no atomics are needed.
-//   Phase 3: gbar = sum / n and the AMSGrad moment and parameter update (server lines of Algorithm 2).
-// ---------------------------------------------------------------------------------------------
 // One wavefront writes the selected entries of chunk c of one selection problem to their places in the list:
 // `at` is where the chunk's slice starts, eq_seen how many keys equal to tau lie in earlier chunks (ties are
 // taken in coordinate order until r are in).  Coordinates are written relative to the worker's row
@@ -1730,13 +1721,43 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
   });
 }
 
-constexpr int kPerWave = 4;                       // workers per wavefront and tile
-constexpr int kTileWorkers = kWaves * kPerWave;
+// ---------------------------------------------------------------------------------------------
+// Kernel 5: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds what is
+// to be known of worker i of the tile.
+//   Selecting: every wavefront takes a quarter of the tile's workers.  Where a worker's entries of the chunk go in its
+//              list follows from the tables (entries above the threshold in earlier chunks, plus the ties taken there:
+//              in coordinate order until r are in); its candidates of the chunk are gone through 64 to a slot, kSlots
+//              slots requested while the ones before are worked on.  The selected (coordinate, value) pairs are
+//              written to the list and kept in LDS.
+//   Adding:    one barrier later the first wavefront (or, where some worker has many entries, every
+//              wavefront for its own quarter of the chunk's coordinates) adds the workers' entries into an LDS tile of
+//              the summed gradient, one worker after the other: the fp32 sum has exactly the order i = 0 .. n-1, and
+//              one worker's coordinates are distinct and touched by one wavefront only, so there are no atomics and no
+//              barrier per worker.  A worker with more selected entries than its share of the LDS is read back from its
+//              list.
+//   Update:    gbar = sum / n and the AMSGrad moment and parameter lines (server lines of Algorithm 2).
+// The loops are kept as loops: a workgroup of a small problem spends more time fetching instructions than executing
+// them.
+// What bounds it: theta, m, v, vhat read and written in place (the pattern alone takes 75 of the 94 us on the
+// ResNet-18 shape, 16 workers, state from HBM), then the slots' instructions and the lists' stores.  Measured against
+// the same kernel with the lists read back from memory and a barrier per worker: ResNet-18 98 -> 94 us, GPT-2 shape
+// 722 -> 685, 16 x 1 M 28 -> 18.5, 4 x 65536 10.7 -> 8.5, the server's half 87 -> 80.
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kTileWorkers = 16;
+constexpr int kSlots = 8;            // slots of 64 entries requested together
+constexpr uint32_t kSolo = 128;      // up to so many selected entries of every worker one wavefront adds them all
+constexpr uint32_t kKept = 2048;     // selected entries of a tile kept in LDS, shared out evenly among its workers
 
-// ROLE: kWholeStep runs all phases; kWorkerHalf stops after phase 1 (the workers' lines of Algorithm 2: the
-// lists are the messages); kServerHalf starts at phase 2 from lists that were put into the workspace (the
-// server's lines; where a chunk's slice of each list starts was found by k_topk_list_offsets).
-// (eight wavefronts per SIMD: the streaming phase needs the occupancy more than phase 1 needs registers)
+// Wavefronts per chunk.  Grids of many chunks have four, each with a quarter of the workers, then of the coordinates.
+// A grid that leaves a compute unit one or two workgroups has sixteen: its time is the chain of the most crowded
+// chunk's slots, not their number (16 workers x 1 M coordinates, 245 chunks, up to 590 selected entries per worker and
+// chunk: 27.2 us with four, 18.5 with sixteen; 4 x 65536: 9.3 and 8.5).
+constexpr int kFinalMany = 4, kFinalFew = 16;
+inline bool few_chunks(uint32_t workgroups) { return workgroups <= 512; }
+
+// ROLE: kWholeStep does all of it; kWorkerHalf writes the lists and stops (the workers' lines of Algorithm 2: the
+// lists are the messages); kServerHalf adds up lists that were put into the workspace (the server's lines; where a
+// quarter's slice of each list starts was found by k_topk_list_offsets).
 enum : int { kWholeStep = 0, kWorkerHalf = 1, kServerHalf = 2 };
 
 // UNI: one selection problem per worker over its whole row, one workgroup per chunk of the row.  !UNI (whole step
@@ -1764,7 +1785,7 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
     f.micro = false;
     f.row0 = 0; f.row_stride = 1;
     f.chunk0 = 0; f.chunk_stride = geo.num_chunks;
-    f.seloff0 = 0; f.seloff_stride = geo.num_chunks + 1;
+    f.seloff0 = 0; f.seloff_stride = geo.num_chunks * kWaves + 1;
     f.cand0 = 0; f.cand_stride = opt.cap;
     f.list0 = 0; f.list_stride = geo.k;
   } else {
@@ -1788,271 +1809,318 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
 // NC: how many of theta, m, v, vhat (in that order) are read and written with ordinary accesses, the others with
 // streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
-template <int ROLE, bool UNI, int NC>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu((UNI && NC == 4) ? 8 : 7, 8))) void k_topk_final(
+template <int ROLE, bool UNI, int NC, int NW>
+__global__ __launch_bounds__(NW * 64) void k_topk_final(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
     const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
-  static_assert(UNI || ROLE == kWholeStep, "the halves of a step work on whole rows");
-  __shared__ float gs[kChunk];
-  __shared__ uint32_t sh_lo[kTileWorkers], sh_hi[kTileWorkers], sh_eqb[kTileWorkers];
+  static_assert(UNI || ROLE != kServerHalf, "the server's half works on whole rows");
+  constexpr uint32_t kPart = kChunk / NW;  // coordinates of a wavefront's part of the chunk
+  static_assert(kTileWorkers % NW == 0 && NW % kWaves == 0 && NW <= 16, "workers and quarters are shared out evenly");
+  __shared__ float4 gs4[ROLE == kWorkerHalf ? 1 : kChunk / 4];
+  __shared__ float kept_val[ROLE == kWholeStep ? kKept : 1];
+  __shared__ uint16_t kept_at[ROLE == kWholeStep ? kKept : 2];  // coordinates within the chunk
+  __shared__ uint32_t sh_part[kTileWorkers][NW];  // a worker's selected entries in the chunk's parts
+  __shared__ uint32_t sh_at[kTileWorkers];     // where its slice of the list starts
+  float* gs = reinterpret_cast<float*>(gs4);
   const FinalCtx f = final_ctx<UNI>(geo, ws, opt, flat);
   const uint32_t c = f.c;
-  const uint32_t base = f.base;
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();  // the wavefront's number: a scalar
-  if (ROLE != kWorkerHalf)
-    for (int t = threadIdx.x; t < kChunk; t += kWG) gs[t] = 0.0f;
+  const uint32_t c_lo = c * kChunk;                                       // the chunk, in coordinates of the problem
+  const uint32_t c_len = f.d_loc - c_lo < kChunk ? f.d_loc - c_lo : kChunk;
+  const uint32_t q_lo = c_lo + wave * kPart;                              // this wavefront's part of it
   if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = 0;  // the general kernels have run
   if (ROLE != kServerHalf && c == 0)  // the next step's first pass allocates its candidate lists from the start
-    for (uint32_t i = threadIdx.x; i < geo.n; i += kWG) {
+    for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {
       ws.rows[f.row0 + i * f.row_stride].cursor = 0;
       ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
     }
-  const uint32_t my_block = c / f.count_cpw;  // count blocks before this chunk's
-  // State that comes from HBM (not all of it kept in the memory-side cache): the first quarter of the chunk's is
-  // requested here, before the look-ups of phases 1 and 2, and travels while they run (16 more registers: seven
-  // wavefronts per SIMD; measured on the final kernel: GPT-2, nothing cached, 727 -> 650-710 us; ResNet-50, two
-  // arrays cached, 139 -> 137; two quarters, at five wavefronts, are slower again; with all four arrays cached the
-  // request gains nothing and the kernel keeps its eight wavefronts).
-  constexpr int kEarly = (ROLE != kWorkerHalf && UNI && NC < 4) ? 1 : 0;  // (the per-block form has no registers to spare)
-  const uint32_t d_end = f.coord_base + f.d_loc;  // the chunk's coordinates end here at the latest
-  float4 th0[kEarly > 0 ? kEarly : 1], mm0[kEarly > 0 ? kEarly : 1], vv0[kEarly > 0 ? kEarly : 1];
+  if (ROLE != kWorkerHalf) {  // (before the tile's barrier: other wavefronts may add here)
 #pragma unroll
-  for (int r = 0; r < kEarly; ++r) {
-    const uint32_t j = base + r * kWG * 4 + threadIdx.x * 4;
-    th0[r] = mm0[r] = vv0[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (j + 3 < d_end) {
-      th0[r] = load_state4<(NC > 0)>(theta + j); mm0[r] = load_state4<(NC > 1)>(m + j);
-      vv0[r] = load_state4<(NC > 2)>(v + j);  // (vhat follows in phase 3: a fourth early load would be spilled)
-    }
+    for (uint32_t r = 0; r < kPart / 256; ++r)
+      gs4[wave * (kPart / 4) + r * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  const uint32_t my_block = c / f.count_cpw;  // count blocks before this chunk's
+  const uint32_t d_end = f.coord_base + f.d_loc;  // the chunk's coordinates end here at the latest
+  const uint32_t j_lane = f.base + wave * kPart + lane * 4;  // the lane's first coordinate of the worker's row
+  // Entries that are in the lists already: put there by the unpacking, or by the first pass for a micro problem.
+  const bool listed = ROLE == kServerHalf || (!UNI && f.micro);
+  const uint32_t share = kKept / (geo.n < kTileWorkers ? geo.n : kTileWorkers);  // of the LDS, per worker
 
-  for (uint32_t i0 = 0; i0 < geo.n; i0 += kTileWorkers) {
-    if (ROLE == kServerHalf) {
-      if (threadIdx.x < kTileWorkers && i0 + threadIdx.x < geo.n) {
-        const uint32_t* so = ws.sel_off_srv + static_cast<size_t>(i0 + threadIdx.x) * (geo.num_chunks + 1) + c;
-        sh_lo[threadIdx.x] = so[0];
-        sh_hi[threadIdx.x] = so[1];
-      }
-    } else {
-    // ---- phase 1a: positions, for this wavefront's workers of the tile (all loads issued together) ----
-    {
-      uint4 rec[kPerWave];
-      uint2 part[kPerWave];
-      uint32_t r_[kPerWave];
-      uint32_t fast_mask = 0;  // wave-uniform: bit u = worker u of this wavefront was selected by k_topk_band
-      // Nothing is looked at before everything has been asked for (a sum inside the loop that loads, a value moved
-      // to a scalar register where it is loaded, or a branch around a worker's loads makes every worker a round
-      // trip of its own): the chunk's record and the first 128 block totals of each worker as vector loads, r and
-      // the route through the scalar path.  A worker beyond the last reads worker i0's tables and is ignored.
-      uint2 pre[kPerWave];
-      uint32_t fast_[kPerWave];
-#pragma unroll
-      for (int u = 0; u < kPerWave; ++u) {
-        const uint32_t i = i0 + wave + u * kWaves;
-        const uint32_t is = i < geo.n ? i : i0;
-        const uint32_t rowi = f.row0 + is * f.row_stride;
-        rec[u] = ws.chunk_rec[f.chunk0 + is * f.chunk_stride + c];
-        // a problem selected by k_topk_band has the sum over the blocks before the chunk's ready (the same in
-        // every lane); for any other the blocks' totals are added up below
-        pre[u] = make_uint2(0, 0);
-        if (my_block) pre[u] = ws.blk_prefix[static_cast<size_t>(rowi) * kMaxCountBlocks + my_block];
-        const uint32_t* rw = reinterpret_cast<const uint32_t*>(ws.rows + rowi);
-        r_[u] = table_u32(rw, offsetof(TopkRow, r) / 4);
-        fast_[u] = table_u32(rw, offsetof(TopkRow, fast) / 4);
-      }
-      bool sums = false;  // wave-uniform: some worker of this wavefront needs its totals added up
-#pragma unroll
-      for (int u = 0; u < kPerWave; ++u) {
-        const bool there = i0 + wave + u * kWaves < geo.n;  // wave-uniform
-        fast_mask |= (there && fast_[u] ? 1u : 0u) << u;
-        sums = sums || (there && !fast_[u] && my_block != 0);
-        part[u] = pre[u];
-        if (!there) { rec[u] = make_uint4(0, 0, 0, 0); part[u] = make_uint2(0, 0); r_[u] = 0; }
-      }
-      if (sums) {  // the general kernels' problems (the rare route: worker after worker, few registers)
-#pragma unroll
-        for (int u = 0; u < kPerWave; ++u) {
-          const uint32_t i = i0 + wave + u * kWaves;
-          if (i < geo.n && !((fast_mask >> u) & 1u)) {  // wave-uniform
-            const uint2* blk = ws.blk + static_cast<size_t>(f.row0 + i * f.row_stride) * kMaxCountBlocks;
-            uint2 sum = make_uint2(0, 0);
-            for (uint32_t b = lane; b < my_block; b += 64) {
-              const uint2 t = blk[b];
-              sum.x += t.x;
-              sum.y += t.y;
-            }
-            part[u] = make_uint2(wave_sum(sum.x), wave_sum(sum.y));
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kPerWave; ++u) {
-        const uint32_t i = i0 + wave + u * kWaves;
-        if (i >= geo.n) continue;  // wave-uniform
-        const uint32_t gt_before = part[u].x + rec[u].z;
-        const uint32_t eq_before = part[u].y + rec[u].w;
-        const uint32_t r = ((fast_mask >> u) & 1u) ? 0u : r_[u];  // that route does not use the "equal to tau" columns
-        const uint32_t taken_before = eq_before < r ? eq_before : r;  // ties go in coordinate order until r are in
-        const uint32_t quota = r - taken_before;
-        const uint32_t take_here = rec[u].y < quota ? rec[u].y : quota;
-        const uint32_t at = gt_before + taken_before;
-        const uint32_t hi = at + rec[u].x + take_here;
-        if (lane == 0) {
-          sh_lo[i - i0] = at;
-          sh_hi[i - i0] = hi;
-          sh_eqb[i - i0] = eq_before;
-        }
-      }
-      // A row selected by k_topk_band: the kept entries of the threshold's bucket are not in the tables above.
-      // Their coordinates (ascending, 0xffffffff beyond the last) come with one load per lane; those before the
-      // chunk move its slice of the list up, those inside lengthen it.
-      if (fast_mask) {  // wave-uniform
-        static_assert(kBoundaryCap == 64, "one entry per lane");
-        uint32_t a[kPerWave];
-#pragma unroll
-        for (int u = 0; u < kPerWave; ++u) {
-          const uint32_t i = i0 + wave + u * kWaves;
-          a[u] = 0xffffffffu;
-          if ((fast_mask >> u) & 1u)
-            a[u] = ws.bnd_sel[static_cast<size_t>(f.row0 + i * f.row_stride) * kBoundaryCap + lane];
-        }
-        const uint32_t lo_c = c * kChunk, hi_c = lo_c + kChunk;  // coordinates of the problem
-#pragma unroll
-        for (int u = 0; u < kPerWave; ++u) {
-          const uint32_t i = i0 + wave + u * kWaves;
-          if (!((fast_mask >> u) & 1u)) continue;
-          const uint32_t before = popc64(ballot64(a[u] < lo_c));
-          const uint32_t here = popc64(ballot64(a[u] >= lo_c && a[u] < hi_c));
-          if (lane == 0) {
-            sh_lo[i - i0] += before;
-            sh_hi[i - i0] += before + here;
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kPerWave; ++u) {
-        const uint32_t i = i0 + wave + u * kWaves;
-        if (i >= geo.n) continue;  // wave-uniform
-        if (lane == 0) {
-          uint32_t* so = ws.sel_off + f.seloff0 + i * f.seloff_stride;
-          so[c] = sh_lo[i - i0];  // the next step's first pass finds this chunk's slice of the list here
-          if (c + 1 == f.num_chunks) so[c + 1] = sh_hi[i - i0];
-        }
-      }
+  // Entries are gone through worker after worker, 64 to a slot.  `cnt` of lane i: the entries of worker i.
+  struct Walk {
+    uint32_t left;     // workers that follow the present one
+    uint32_t i, t, n;  // the present one (kTileWorkers: none is left), its next entry, its entries
+  };
+  auto next_worker = [](Walk& w, uint32_t cnt) {
+    w.i = kTileWorkers;
+    w.t = w.n = 0;
+    if (w.left) {
+      w.i = static_cast<uint32_t>(__builtin_ctz(w.left));
+      w.left &= w.left - 1u;
+      w.n = __builtin_amdgcn_readlane(cnt, w.i);
     }
-    // ---- phase 1b: write the selected entries (positions come back from LDS: written by this wavefront) ----
-    // What a worker's turn needs of its control block and the chunk's segment descriptor is the same in every lane
-    // and was written by earlier launches: it comes through the scalar path, all of it with one round trip, and the
-    // next worker's is asked for before this worker's entries are (a turn was a chain of three round trips).
-    {
-      struct Turn { uint32_t mode, tau, r, ties, fast, tie_last, off, cnt; };
-      auto fetch = [&](uint32_t i) {
-        Turn w{kModeDense, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-        if (i < geo.n && i < i0 + kTileWorkers) {  // wave-uniform
-          const uint32_t* rw = reinterpret_cast<const uint32_t*>(ws.rows + f.row0 + i * f.row_stride);
-          w.mode = table_u32(rw, offsetof(TopkRow, mode) / 4);
-          w.tau = table_u32(rw, offsetof(TopkRow, tau) / 4);
-          w.r = table_u32(rw, offsetof(TopkRow, r) / 4);
-          w.ties = table_u32(rw, offsetof(TopkRow, ties) / 4);
-          w.fast = table_u32(rw, offsetof(TopkRow, fast) / 4);
-          w.tie_last = table_u32(rw, offsetof(TopkRow, tie_last) / 4);
-          const uint32_t* dw = reinterpret_cast<const uint32_t*>(ws.desc + f.chunk0 + i * f.chunk_stride + c);
-          w.off = table_u32(dw, 0);
-          w.cnt = table_u32(dw, 1);
-        }
-        return w;
-      };
-      Turn next = fetch(i0 + wave);
+  };
+  auto next_slot = [&](Walk& w, uint32_t cnt) {
+    w.t += 64;
+    if (w.t >= w.n) next_worker(w, cnt);
+  };
+  struct Slots { uint2 en[kSlots]; };
+
 #pragma unroll 1
-      for (uint32_t i = i0 + wave; i < geo.n && i < i0 + kTileWorkers; i += kWaves) {
-        const Turn w = next;
-        next = fetch(i + kWaves);
-        const uint32_t at = sh_lo[i - i0];
-        const uint32_t hi = sh_hi[i - i0];
-        if (hi == at || f.micro) continue;  // nothing of this worker in the chunk, or written already (wave-uniform)
-        const float* er = e + static_cast<int64_t>(i) * geo.ld + f.coord_base;
-        const uint2* candr = ws.cand + f.cand0 + i * f.cand_stride;
-        int32_t* idx = ws.idx + f.list0 + i * f.list_stride;
-        float* val = ws.val + f.list0 + i * f.list_stride;
-        emit_chunk(w.mode, er, f.d_loc, c, candr, make_uint2(w.off, w.cnt), f.cap, w.tau, w.r, w.r == w.ties,
-                   sh_eqb[i - i0], at, idx, val, f.k_loc, f.coord_base, w.fast != 0, w.tie_last);
-      }
-    }
-    }  // ROLE != kServerHalf
-    if (ROLE == kWorkerHalf) continue;
-    __syncthreads();  // the chunk's list entries and their positions are visible to the whole workgroup
-
-    // ---- phase 2 ----
-    // Workers are taken in groups of kGroup: every thread first requests its entry of each worker's chunk
-    // segment (independent loads, one round trip for the whole group), then the entries are added one worker
-    // after the other.
-    constexpr int kGroup = 8;
-    const uint32_t i_end = i0 + kTileWorkers < geo.n ? i0 + kTileWorkers : geo.n;
-    for (uint32_t g0 = i0; g0 < i_end; g0 += kGroup) {
-      uint32_t lo[kGroup], hi[kGroup], jl[kGroup];
-      float vl[kGroup];
+  for (uint32_t i0 = 0; i0 < geo.n; i0 += kTileWorkers) {
+    if (!listed) {  // uniform
+      // ---- selecting: this wavefront's workers are those at lanes wave, wave + NW, ... ----
+      const bool have = lane < kTileWorkers && (lane & (NW - 1)) == wave && i0 + lane < geo.n;
+      const uint32_t i_lane = have ? i0 + lane : i0;  // (the other lanes read worker i0's tables and ignore them)
+      const uint32_t rowi = f.row0 + i_lane * f.row_stride;
+      static_assert(offsetof(TopkRow, fast) == 32 && offsetof(TopkRow, mode) == 36 && offsetof(TopkRow, tau) == 40 &&
+                    offsetof(TopkRow, r) == 44 && offsetof(TopkRow, ties) == 48 && offsetof(TopkRow, tie_last) == 52,
+                    "words read below");
+      const uint4 ra = reinterpret_cast<const uint4*>(ws.rows + rowi)[2];
+      const uint2 rb = reinterpret_cast<const uint2*>(ws.rows + rowi)[6];
+      const uint2 ds = ws.desc[f.chunk0 + i_lane * f.chunk_stride + c];
+      const uint4 rec = ws.chunk_rec[f.chunk0 + i_lane * f.chunk_stride + c];
+      uint2 pre = make_uint2(0, 0);
+      if (my_block) pre = ws.blk_prefix[static_cast<size_t>(rowi) * kMaxCountBlocks + my_block];
+      const bool fast = ra.x != 0;
+      const bool dense = !fast && ra.y == kModeDense;
+      const bool partial = have && !fast && ra.w != rb.x;  // some of the row's ties are left out
+      const uint32_t tau = ra.z, r = ra.w, tie = fast ? rb.y : 0xffffffffu;
+      const uint32_t off = ds.x;  // of the chunk's segment in the candidate list
+      uint32_t cnt = ds.y;
+      if (off > f.cap) cnt = 0;  // segments always lie inside the list; never read outside it
+      else if (cnt > f.cap - off) cnt = f.cap - off;
+      if (dense) cnt = c_len;    // no list: the chunk's coordinates themselves
+      if (!have) cnt = 0;
+      const uint32_t dense_mask = static_cast<uint32_t>(ballot64(dense));
+      const uint32_t partial_mask = static_cast<uint32_t>(ballot64(partial));
+      auto request = [&](Walk& w, Slots& to) {  // the next kSlots slots
 #pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const uint32_t i = g0 + u;
-        lo[u] = hi[u] = 0;
-        jl[u] = 0xffffffffu;
-        vl[u] = 0.0f;
-        if (i < i_end) {
-          lo[u] = sh_lo[i - i0];
-          hi[u] = sh_hi[i - i0] < f.k_loc ? sh_hi[i - i0] : f.k_loc;
-          const uint32_t q = lo[u] + threadIdx.x;
-          if (q < hi[u]) {
-            jl[u] = static_cast<uint32_t>(ws.idx[f.list0 + i * f.list_stride + q]) - base;
-            vl[u] = ws.val[f.list0 + i * f.list_stride + q];
+        for (int s = 0; s < kSlots; ++s) {
+          to.en[s] = make_uint2(0u, 0u);
+          if (w.i < kTileWorkers) {  // wave-uniform
+            const uint32_t q = w.t + lane, i = i0 + w.i;
+            if (q < w.n) {
+              if ((dense_mask >> w.i) & 1u)
+                to.en[s] = make_uint2(c_lo + q, __float_as_uint((e + static_cast<int64_t>(i) * geo.ld + f.coord_base + c_lo)[q]));
+              else
+                to.en[s] = (ws.cand + f.cand0 + i * f.cand_stride + __builtin_amdgcn_readlane(off, w.i))[q];
+            }
+            next_slot(w, cnt);
           }
         }
+      };
+      Walk now{static_cast<uint32_t>(ballot64(cnt != 0)), 0, 0, 0};
+      next_worker(now, cnt);
+      Walk ahead = now;
+      Slots cur;
+      request(ahead, cur);
+      // positions
+      uint32_t sums = static_cast<uint32_t>(ballot64(have && !fast && my_block != 0));
+      while (sums) {  // the general kernels' problems: the totals of the count blocks before the chunk's are added up
+        const uint32_t u = static_cast<uint32_t>(__builtin_ctz(sums));
+        sums &= sums - 1u;
+        const uint2* blk = ws.blk + static_cast<size_t>(f.row0 + (i0 + u) * f.row_stride) * kMaxCountBlocks;
+        uint2 sum = make_uint2(0, 0);
+        for (uint32_t b = lane; b < my_block; b += 64) {
+          const uint2 t = blk[b];
+          sum.x += t.x;
+          sum.y += t.y;
+        }
+        const uint32_t sx = wave_sum(sum.x), sy = wave_sum(sum.y);
+        if (lane == u) pre = make_uint2(sx, sy);
       }
+      uint32_t at = pre.x + rec.z;  // where the worker's next entry goes
+      uint32_t eq = 0;              // keys equal to tau so far (rows with ties to leave out)
+      if (fast) {
+        // Selected by k_topk_band: the kept entries of the threshold's bucket are not in the tables; pre.y of them lie
+        // before the chunk's count block, and those between the block's start and the chunk are counted here (their
+        // coordinates are ascending, 0xffffffff beyond the last).
+        const uint32_t* sel = ws.bnd_sel + static_cast<size_t>(rowi) * kBoundaryCap;
+        uint32_t nb = pre.y;
+        while (nb < kBoundaryCap && sel[nb] < c_lo) ++nb;
+        at += nb;
+      } else {
+        eq = pre.y + rec.w;
+        at += eq < r ? eq : r;  // ties go in coordinate order until r are in
+      }
+      const uint32_t at_first = at;
+      if (lane < NW)
 #pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const uint32_t i = g0 + u;
-        if (i < i_end && hi[u] > lo[u]) {  // the same in every thread of the workgroup: a worker without entries in
-                                           // the chunk (every worker, in more than half of the chunks) adds nothing
-                                           // and needs no barrier
-          if (jl[u] < static_cast<uint32_t>(kChunk)) gs[jl[u]] = gs[jl[u]] + vl[u];
-          // segments longer than a workgroup: four entries per thread and trip, loads in flight together
-          for (uint32_t q = lo[u] + kWG + threadIdx.x; q < hi[u]; q += 4 * kWG) {
-            uint32_t jj[4];
-            float vv[4];
+        for (uint32_t i = wave; i < kTileWorkers; i += NW) sh_part[i][lane] = 0;
+#pragma unroll 1
+      while (now.i < kTileWorkers) {
+        Slots nxt;
+        request(ahead, nxt);
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-              const uint32_t qq = q + w * kWG;
-              jj[w] = 0xffffffffu;
-              vv[w] = 0.0f;
-              if (qq < hi[u]) {
-                jj[w] = static_cast<uint32_t>(ws.idx[f.list0 + i * f.list_stride + qq]) - base;
-                vv[w] = ws.val[f.list0 + i * f.list_stride + qq];
+        for (int s = 0; s < kSlots; ++s)
+          if (now.i < kTileWorkers) {  // wave-uniform
+            const uint2 en = cur.en[s];
+            const uint32_t key = key_of_bits(en.y);
+            const uint32_t tau_i = __builtin_amdgcn_readlane(tau, now.i), tie_i = __builtin_amdgcn_readlane(tie, now.i);
+            const bool ok = now.t + lane < now.n;
+            bool is_tie = ok && key == tau_i && en.x <= tie_i;
+            if ((partial_mask >> now.i) & 1u) {  // wave-uniform
+              const uint64_t ties = ballot64(is_tie);
+              const uint32_t eq_i = __builtin_amdgcn_readlane(eq, now.i), r_i = __builtin_amdgcn_readlane(r, now.i);
+              is_tie = is_tie && eq_i + count_below(ties) < r_i;
+              if (lane == now.i) eq += popc64(ties);
+            }
+            const bool sel = is_tie || (ok && key > tau_i);
+            const uint64_t taken = ballot64(sel);
+            // lane u: how many of them lie in part u (the part's number is the coordinate's highest bits in the chunk)
+            uint64_t in_part = taken;
+#pragma unroll
+            for (uint32_t bit = kPart; bit < static_cast<uint32_t>(kChunk); bit *= 2) {
+              const uint64_t set = ballot64((en.x & bit) != 0);
+              in_part &= (lane & (bit / kPart)) ? set : ~set;
+            }
+            if (lane < NW) sh_part[now.i][lane] += popc64(in_part);
+            const uint32_t pos = __builtin_amdgcn_readlane(at, now.i) + count_below(taken);
+            if (sel && pos < f.k_loc) {  // (always, when the counts are consistent)
+              const size_t l = f.list0 + (i0 + now.i) * f.list_stride + pos;
+              ws.idx[l] = static_cast<int32_t>(f.coord_base + en.x);
+              ws.val[l] = __uint_as_float(en.y);
+            }
+            if (ROLE == kWholeStep) {
+              const uint32_t kept = pos - __builtin_amdgcn_readlane(at_first, now.i);
+              if (sel && kept < share) {
+                kept_val[now.i * share + kept] = __uint_as_float(en.y);
+                kept_at[now.i * share + kept] = static_cast<uint16_t>(en.x - c_lo);
               }
             }
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-              if (jj[w] < static_cast<uint32_t>(kChunk)) gs[jj[w]] = gs[jj[w]] + vv[w];
+            if (lane == now.i) at += popc64(taken);
+            next_slot(now, cnt);
           }
-          __syncthreads();
+        cur = nxt;
+      }
+      if (have) {
+        sh_at[lane] = at_first;
+        // the next step's first pass finds the quarters' slices of the list here
+        uint32_t* so = ws.sel_off + f.seloff0 + i_lane * f.seloff_stride + c * kWaves;
+        uint32_t upto = at_first;
+#pragma unroll
+        for (uint32_t u = 0; u < NW; ++u) {
+          if (u % (NW / kWaves) == 0) so[u / (NW / kWaves)] = upto;
+          upto += sh_part[lane][u];
         }
+        if (c + 1 == f.num_chunks) so[kWaves] = at;
+      }
+    } else if (ROLE != kServerHalf && threadIdx.x < kTileWorkers && i0 + threadIdx.x < geo.n) {
+      uint32_t* so = ws.sel_off + f.seloff0 + (i0 + threadIdx.x) * f.seloff_stride;  // a micro problem: one chunk
+      so[0] = 0;
+#pragma unroll
+      for (int w = 1; w <= kWaves; ++w) so[w] = f.k_loc;
+    }
+    if (ROLE == kWorkerHalf) continue;
+    if (!listed) __syncthreads();
+
+    // ---- adding ----
+    uint32_t all = 0, from = 0, part = 0;  // lane i: worker i's selected entries, those before the part, those in it
+    if (ROLE == kWholeStep && !listed && lane < kTileWorkers && i0 + lane < geo.n) {
+#pragma unroll
+      for (uint32_t u = 0; u < NW; ++u) {
+        const uint32_t x = sh_part[lane][u];
+        all += x;
+        from += u < wave ? x : 0u;
+        part = u == wave ? x : part;
       }
     }
+    if (ROLE == kWholeStep && !listed && ballot64(all > (share < kSolo ? share : kSolo)) == 0) {
+      // No worker has more than two slots of selected entries in the chunk: the first wavefront adds them all (a
+      // part each would be many more slots, hardly filled).
+      if (wave == 0) {
+        uint32_t left = static_cast<uint32_t>(ballot64(all != 0));
+#pragma unroll 1
+        while (left) {
+          const uint32_t i = static_cast<uint32_t>(__builtin_ctz(left));
+          left &= left - 1u;
+          const uint32_t n = __builtin_amdgcn_readlane(all, i);
+#pragma unroll
+          for (uint32_t t = 0; t < kSolo; t += 64)
+            if (t + lane < n) {
+              float* g = gs + kept_at[i * share + t + lane];
+              *g = *g + kept_val[i * share + t + lane];
+            }
+          __builtin_amdgcn_wave_barrier();  // the next worker's additions come after this one's
+        }
+      }
+      __syncthreads();
+    } else {
+      // this wavefront's part of the coordinates
+      const bool have = lane < kTileWorkers && i0 + lane < geo.n;
+      const uint32_t i_lane = have ? i0 + lane : i0;
+      uint32_t first = 0, cnt = 0;  // the worker's entries of the part: from entry `first` of its list on
+      if (ROLE == kServerHalf) {
+        // (offsets are known per quarter: with more wavefronts each skips the entries of its quarter that are others')
+        const uint32_t* so = ws.sel_off_srv + static_cast<size_t>(i_lane) * (geo.num_chunks * kWaves + 1) + c * kWaves +
+                             wave / (NW / kWaves);
+        first = so[0];
+        const uint32_t hi = so[1] < f.k_loc ? so[1] : f.k_loc;
+        cnt = have && hi > first ? hi - first : 0u;
+      } else if (listed) {
+        cnt = have && wave < kMicroCoords / kPart ? f.k_loc : 0u;  // a micro problem: the whole list, of one chunk
+      } else if (have) {
+        cnt = part;
+        first = sh_at[lane] + from;
+        if (first > f.k_loc) cnt = 0;  // (never, when the counts are consistent)
+        else if (cnt > f.k_loc - first) cnt = f.k_loc - first;
+      }
+      const uint32_t kept_mask = ROLE == kWholeStep && !listed ? static_cast<uint32_t>(ballot64(all <= share)) : 0u;
+      auto request = [&](Walk& w, Slots& to) {
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+          to.en[s] = make_uint2(0u, 0u);
+          if (w.i < kTileWorkers) {  // wave-uniform
+            const uint32_t e_q = w.t + lane;
+            if (e_q < w.n) {
+              if ((kept_mask >> w.i) & 1u) {
+                const uint32_t l = w.i * share + __builtin_amdgcn_readlane(from, w.i) + e_q;
+                to.en[s] = make_uint2(c_lo + kept_at[l], __float_as_uint(kept_val[l]));
+              } else {
+                const size_t l = f.list0 + (i0 + w.i) * f.list_stride + __builtin_amdgcn_readlane(first, w.i) + e_q;
+                to.en[s] = make_uint2(static_cast<uint32_t>(ws.idx[l]) - f.coord_base, __float_as_uint(ws.val[l]));
+              }
+            }
+            next_slot(w, cnt);
+          }
+        }
+      };
+      Walk now{static_cast<uint32_t>(ballot64(cnt != 0)), 0, 0, 0};
+      next_worker(now, cnt);
+      Walk ahead = now;
+      Slots cur;
+      request(ahead, cur);
+#pragma unroll 1
+      while (now.i < kTileWorkers) {
+        Slots nxt;
+        request(ahead, nxt);
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)
+          if (now.i < kTileWorkers) {  // wave-uniform
+            const uint32_t jl = cur.en[s].x - q_lo;
+            if (now.t + lane < now.n && jl < kPart) {  // (others' coordinates; a malformed message's lie anywhere)
+              float* g = gs + wave * kPart + jl;
+              *g = *g + __uint_as_float(cur.en[s].y);
+            }
+            __builtin_amdgcn_wave_barrier();  // the next worker's additions come after this one's
+            next_slot(now, cnt);
+          }
+        cur = nxt;
+      }
+    }
+    if (!listed && i0 + kTileWorkers < geo.n) __syncthreads();  // the next tile's entries take this one's place in LDS
   }
 
   if (ROLE == kWorkerHalf) return;
-#pragma unroll
-  for (int r = 0; r < kChunk / (kWG * 4); ++r) {
-    const uint32_t t = r * kWG * 4 + threadIdx.x * 4;
-    const uint32_t j = base + t;
+#pragma unroll 1
+  for (int r = 0; r < static_cast<int>(kPart / 256); ++r) {
+    const uint32_t t = wave * (kPart / 4) + r * 64 + lane;
+    const uint32_t j = j_lane + r * 256;
     if (j + 3 < d_end) {
-      float4 th, mm, vv, vh;
-      if (r < kEarly) {
-        th = th0[r]; mm = mm0[r]; vv = vv0[r];
-        vh = load_state4<(NC > 3)>(vhat + j);
-      } else {
-        th = load_state4<(NC > 0)>(theta + j); mm = load_state4<(NC > 1)>(m + j);
-        vv = load_state4<(NC > 2)>(v + j); vh = load_state4<(NC > 3)>(vhat + j);
-      }
-      const float4 s = *reinterpret_cast<const float4*>(gs + t);
+      float4 th = load_state4<(NC > 0)>(theta + j), mm = load_state4<(NC > 1)>(m + j);
+      float4 vv = load_state4<(NC > 2)>(v + j), vh = load_state4<(NC > 3)>(vhat + j);
+      const float4 s = gs4[t];
       ams_update(s.x / p.nf, th.x, mm.x, vv.x, vh.x, p);
       ams_update(s.y / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(s.z / p.nf, th.z, mm.z, vv.z, vh.z, p);
@@ -2064,89 +2132,45 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu((UNI && NC 
     } else {
       for (uint32_t s = 0; s < 4 && j + s < d_end; ++s) {
         float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
-        ams_update(gs[t + s] / p.nf, th, mm, vv, vh, p);
+        ams_update(gs[4 * t + s] / p.nf, th, mm, vv, vh, p);
         theta[j + s] = th; m[j + s] = mm; v[j + s] = vv; vhat[j + s] = vh;
       }
     }
   }
 }
 
-// Top-k inside every block: the workers' last lines on their own.  A wavefront takes one chunk of one segment,
-// finds where its slice of the list starts (as phase 1 of the kernel above does for a worker's row) and writes
-// the selected entries there, with coordinates of the worker's whole row.  Flat launch over map_emit.
-__global__ __launch_bounds__(kWG) void k_topk_emit(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                    TopkOptions opt) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = 0;  // the general kernels have run
-  const WgSlot slot = ws.map_emit[blockIdx.x];
-  const Seg sg = ws.segs[slot.seg];
-  const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
-  const uint32_t c = slot.group + wave;
-  if (c >= sg.num_chunks) return;  // wave-uniform; no barrier in this kernel
-  TopkRow* rowp = ws.rows + slot.seg;
-  if (c == 0 && lane == 0) {  // the next step's first pass allocates its list from the start
-    rowp->cursor = 0;
-    rowp->cursor_band = 0;
-  }
-  const uint32_t cap = opt.cap < sg.cap ? opt.cap : sg.cap;
-  const uint32_t r = rowp->r, tau = rowp->tau, mode = rowp->mode;
-  const uint4 rec = ws.chunk_rec[sg.chunk_base + c];
-  const uint2* blk = ws.blk + static_cast<size_t>(slot.seg) * kMaxCountBlocks;
-  const uint32_t my_block = c / sg.count_cpw;
-  uint2 part = make_uint2(0, 0);
-  for (uint32_t b = lane; b < my_block; b += 64) {
-    const uint2 t = blk[b];
-    part.x += t.x;
-    part.y += t.y;
-  }
-  const bool all_ties = rowp->r == rowp->ties;
-  const bool fast = uniform_u32(rowp->fast) != 0;
-  uint32_t gt_before = wave_sum(part.x) + rec.z;
-  const uint32_t eq_before = wave_sum(part.y) + rec.w;
-  uint32_t gt_here = rec.x;
-  uint32_t r_pos = r;
-  if (fast) {  // selected by k_topk_band: see the last kernel
-    const uint32_t a = ws.bnd_sel[static_cast<size_t>(slot.seg) * kBoundaryCap + lane];
-    const uint32_t lo_c = c * kChunk, hi_c = lo_c + kChunk;
-    gt_before += popc64(ballot64(a < lo_c));
-    gt_here += popc64(ballot64(a >= lo_c && a < hi_c));
-    r_pos = 0;
-  }
-  const uint32_t taken_before = eq_before < r_pos ? eq_before : r_pos;
-  const uint32_t quota = r_pos - taken_before;
-  const uint32_t take_here = rec.y < quota ? rec.y : quota;
-  const uint32_t at = gt_before + taken_before;
-  const uint32_t hi = at + gt_here + take_here;
-  if (lane == 0) {
-    uint32_t* so = ws.sel_off + sg.seloff_base;
-    so[c] = at;
-    if (c + 1 == sg.num_chunks) so[c + 1] = hi;
-  }
-  if (hi == at || sg.micro) return;  // a micro problem's entries were written by the first pass
-  emit_chunk(mode, e + sg.elem_off, sg.d, c, ws.cand + sg.cand_base, ws.desc[sg.chunk_base + c], cap, tau, r, all_ties,
-             eq_before, at, ws.idx + sg.list_base, ws.val + sg.list_base, sg.k, sg.coord_base, fast, rowp->tie_last);
-  (void)geo;
-}
-
-// Where each chunk's slice of a worker's ascending coordinate list starts: sel_off[c] = number of listed
-// coordinates below c * kChunk, for c = 0 .. num_chunks.  The thread of entry q fills the chunks between its
-// predecessor's chunk (exclusive) and its own (inclusive); the last entry also fills the rest up to num_chunks.
+// Where each quarter's slice of a worker's ascending coordinate list starts: sel_off_srv[u] = number of listed
+// coordinates below u * kQuarterCoords, for u = 0 .. 4 num_chunks.  Entry q fills the quarters between its
+// predecessor's (exclusive) and its own (inclusive); beyond the last entry follows one that fills the rest.  A short
+// gap is filled by the entry's own lane, a long one by the whole wavefront: the kept coordinates crowd into a few
+// layers, and one lane that writes the quarters of a layer without any was the kernel's 30 us.
 __global__ __launch_bounds__(kWG) void k_topk_list_offsets(Geometry geo, TopkWorkspace ws) {
-  const uint32_t row = blockIdx.y;
+  const uint32_t row = blockIdx.y, quarters = geo.num_chunks * kWaves, lane = lane_id();
   const int32_t* idx = ws.idx + static_cast<size_t>(row) * geo.k;
-  uint32_t* so = ws.sel_off_srv + static_cast<size_t>(row) * (geo.num_chunks + 1);
+  uint32_t* so = ws.sel_off_srv + static_cast<size_t>(row) * (quarters + 1);
+  auto quarter = [&](uint32_t q) {
+    const uint32_t u = static_cast<uint32_t>(idx[q]) / kQuarterCoords;
+    return u < quarters ? u : quarters - 1;  // a coordinate beyond d (flagged by the unpacking)
+  };
   const uint32_t step = gridDim.x * kWG;
-  for (uint32_t q = blockIdx.x * kWG + threadIdx.x; q < geo.k; q += step) {
-    uint32_t cur = static_cast<uint32_t>(idx[q]) / kChunk;
-    if (cur >= geo.num_chunks) cur = geo.num_chunks - 1;  // a coordinate beyond d (flagged by the unpacking)
-    uint32_t from = 0;
-    if (q) {
-      uint32_t prev = static_cast<uint32_t>(idx[q - 1]) / kChunk;
-      if (prev >= geo.num_chunks) prev = geo.num_chunks - 1;
-      from = prev + 1;
+  for (uint32_t q0 = blockIdx.x * kWG + (threadIdx.x & ~63u); q0 <= geo.k; q0 += step) {  // wave-uniform
+    const uint32_t q = q0 + lane;
+    uint32_t from = 0, to = 0;  // quarters from .. to - 1
+    if (q <= geo.k) {
+      from = q ? quarter(q - 1) + 1 : 0u;
+      to = (q < geo.k ? quarter(q) : quarters) + 1;
     }
-    for (uint32_t c = from; c <= cur; ++c) so[c] = q;
-    if (q + 1 == geo.k)
-      for (uint32_t c = cur + 1; c <= geo.num_chunks; ++c) so[c] = geo.k;
+    constexpr uint32_t kShort = 4;
+    const uint32_t gap = to > from ? to - from : 0u;  // (a malformed list need not ascend)
+    if (gap <= kShort)
+      for (uint32_t u = 0; u < gap; ++u) so[from + u] = q;
+    uint64_t big = ballot64(gap > kShort);
+    while (big) {
+      const int l = __builtin_ctzll(big);
+      big &= big - 1;
+      const uint32_t lo = __builtin_amdgcn_readlane(from, l), hi = __builtin_amdgcn_readlane(to, l);
+      for (uint32_t u = lo + lane; u < hi; u += 64) so[u] = q0 + l;
+    }
   }
 }
 
@@ -2206,13 +2230,23 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   COMPAMS_CHECK_LAUNCH();
   const dim3 grid_f(geo.num_chunks);
   const TopkFlat none{};
-#define COMPAMS_FINAL_WHOLE_ROW(NC) k_topk_final<kWholeStep, true, NC>
-  if (role == kWorkerHalf)
-    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, true, 0>, grid_f, wg, stream, theta, m, v, vhat, e, geo, ws, opt,
-           ap, none);
+  const bool few = few_chunks(geo.num_chunks);
+  const dim3 wg_few(kFinalFew * 64);
+#define COMPAMS_FINAL_WHOLE_ROW(NC) k_topk_final<kWholeStep, true, NC, kFinalMany>
+#define COMPAMS_FINAL_WHOLE_ROW_FEW(NC) k_topk_final<kWholeStep, true, NC, kFinalFew>
+  if (role == kWorkerHalf && few)
+    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, true, 0, kFinalFew>, grid_f, wg_few, stream, theta, m, v, vhat, e,
+           geo, ws, opt, ap, none);
+  else if (role == kWorkerHalf)
+    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, true, 0, kFinalMany>, grid_f, wg, stream, theta, m, v, vhat, e, geo,
+           ws, opt, ap, none);
+  else if (few)
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_WHOLE_ROW_FEW, grid_f, wg_few, stream, theta,
+                             m, v, vhat, e, geo, ws, opt, ap, none);
   else
     COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_WHOLE_ROW, grid_f, wg, stream, theta, m, v,
                              vhat, e, geo, ws, opt, ap, none);
+#undef COMPAMS_FINAL_WHOLE_ROW_FEW
 #undef COMPAMS_FINAL_WHOLE_ROW
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
@@ -2248,13 +2282,21 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
     COMPAMS_CHECK_LAUNCH();
   }
   if (workers_only) {
-    launch(L, kSlotTopkEmit, k_topk_emit, dim3(flat.wg_emit), wg, stream, e, geo, ws, opt);
+    const float* residuals = e;
+    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, false, 0, kFinalMany>, dim3(flat.wg_final), wg, stream, theta, m, v,
+           vhat, residuals, geo, ws, opt, ap, flat);
   } else {
     const float* residuals = e;
-    const dim3 grid_f(flat.wg_final);
-#define COMPAMS_FINAL_BLOCKS(NC) k_topk_final<kWholeStep, false, NC>
-    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_BLOCKS, grid_f, wg, stream, theta, m, v, vhat,
-                             residuals, geo, ws, opt, ap, flat);
+    const dim3 grid_f(flat.wg_final), wg_few(kFinalFew * 64);
+#define COMPAMS_FINAL_BLOCKS(NC) k_topk_final<kWholeStep, false, NC, kFinalMany>
+#define COMPAMS_FINAL_BLOCKS_FEW(NC) k_topk_final<kWholeStep, false, NC, kFinalFew>
+    if (few_chunks(flat.wg_final))
+      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_BLOCKS_FEW, grid_f, wg_few, stream, theta, m,
+                               v, vhat, residuals, geo, ws, opt, ap, flat);
+    else
+      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_BLOCKS, grid_f, wg, stream, theta, m, v,
+                               vhat, residuals, geo, ws, opt, ap, flat);
+#undef COMPAMS_FINAL_BLOCKS_FEW
 #undef COMPAMS_FINAL_BLOCKS
   }
   COMPAMS_CHECK_LAUNCH();
@@ -2264,14 +2306,14 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
 // The server's lines from lists that sit in the workspace (idx, val: n ascending lists of k entries).
 hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
-  uint32_t groups = (geo.k + kWG * 4 - 1) / (kWG * 4);
+  uint32_t groups = (geo.k + 1 + kWG - 1) / kWG;
   if (groups > 256) groups = 256;
   launch(L, kSlotTopkOffsets, k_topk_list_offsets, dim3(groups, geo.n), dim3(kWG), stream, geo, ws);
   COMPAMS_CHECK_LAUNCH();
   const float* no_e = nullptr;
   const dim3 grid_f(geo.num_chunks), wg(kWG);
   const TopkFlat none{};
-#define COMPAMS_FINAL_SERVER(NC) k_topk_final<kServerHalf, true, NC>
+#define COMPAMS_FINAL_SERVER(NC) k_topk_final<kServerHalf, true, NC, kFinalMany>
   COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_SERVER, grid_f, wg, stream, theta, m, v, vhat,
                            no_e, geo, ws, opt, ap, none);
 #undef COMPAMS_FINAL_SERVER
