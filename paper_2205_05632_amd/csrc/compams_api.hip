@@ -49,7 +49,7 @@ void launcher_end(Launcher* L, int slot, hipStream_t stream) {
 namespace {
 
 const char* const kSlotNames[kNumSlots] = {
-    "topk_pass_a", "topk_band", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final", "topk_offsets",
+    "topk_pass_a", "topk_band", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final",
     "bs_pass1", "bs_finalize", "bs_pass2", "bs_amsgrad", "none_amsgrad", "wire_encode", "wire_decode"};
 
 static_assert(kCountersPerRow == COMPAMS_COUNTERS_PER_ROW, "the kernels' stride of the counters is the header's");
@@ -682,7 +682,7 @@ int compams_server_step(compams_ctx* ctx, const uint32_t* messages, int64_t stri
   try {
     if (is_topk(c.compressor)) {
       err = wire_decode_topk(ctx->geo, ctx->tk, messages, stride_words, words, ctx->tk.idx, ctx->tk.val, status_out,
-                             stream, L);
+                             true, stream, L);
       if (err == hipSuccess)
         err = topk_server_step(ctx->geo, ctx->tk, ctx->tkopt, ap, c.theta, c.m, c.v, c.vhat, stream, L);
     } else {
@@ -880,7 +880,7 @@ int compams_decode(compams_ctx* ctx, const uint32_t* messages, int64_t stride_wo
   try {
     err = is_topk(c.compressor)
               ? wire_decode_topk(ctx->geo, ctx->tk, messages, stride_words, words, static_cast<int32_t*>(out_a),
-                                 static_cast<float*>(out_b), status_out, stream, L)
+                                 static_cast<float*>(out_b), status_out, false, stream, L)
               : wire_decode_blocksign(ctx->geo, messages, stride_words, words, static_cast<uint32_t*>(out_a),
                                       static_cast<float*>(out_b), status_out, stream, L);
   } catch (...) {

@@ -260,7 +260,7 @@ struct Geometry {
 
 // Kernel slots for optional timing.
 enum KernelSlot {
-  kSlotPassA = 0, kSlotBand, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal, kSlotTopkOffsets,
+  kSlotPassA = 0, kSlotBand, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal,
   kSlotBsPass1, kSlotBsFinal, kSlotBsPass2, kSlotBsAms,
   kSlotNoneAms, kSlotWireEncode, kSlotWireDecode, kNumSlots
 };
@@ -298,7 +298,7 @@ hipError_t wire_encode_topk(const Geometry& geo, const TopkWorkspace& ws, uint32
                             uint32_t* words_out, hipStream_t stream, Launcher* L);
 hipError_t wire_decode_topk(const Geometry& geo, const TopkWorkspace& ws, const uint32_t* messages, int64_t stride,
                             const uint32_t* words, int32_t* idx_out, float* val_out, uint32_t* status,
-                            hipStream_t stream, Launcher* L);
+                            bool quarter_offsets, hipStream_t stream, Launcher* L);
 hipError_t wire_encode_blocksign(const Geometry& geo, const BlocksignWorkspace& ws, uint32_t* messages, int64_t stride,
                                  uint32_t* words_out, hipStream_t stream, Launcher* L);
 hipError_t wire_decode_blocksign(const Geometry& geo, const uint32_t* messages, int64_t stride, const uint32_t* words,

@@ -1757,7 +1757,7 @@ inline bool few_chunks(uint32_t workgroups) { return workgroups <= 512; }
 
 // ROLE: kWholeStep does all of it; kWorkerHalf writes the lists and stops (the workers' lines of Algorithm 2: the
 // lists are the messages); kServerHalf adds up lists that were put into the workspace (the server's lines; where a
-// quarter's slice of each list starts was found by k_topk_list_offsets).
+// quarter's slice of each list starts was found by the unpacking).
 enum : int { kWholeStep = 0, kWorkerHalf = 1, kServerHalf = 2 };
 
 // UNI: one selection problem per worker over its whole row, one workgroup per chunk of the row.  !UNI (whole step
@@ -2139,41 +2139,6 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
   }
 }
 
-// Where each quarter's slice of a worker's ascending coordinate list starts: sel_off_srv[u] = number of listed
-// coordinates below u * kQuarterCoords, for u = 0 .. 4 num_chunks.  Entry q fills the quarters between its
-// predecessor's (exclusive) and its own (inclusive); beyond the last entry follows one that fills the rest.  A short
-// gap is filled by the entry's own lane, a long one by the whole wavefront: the kept coordinates crowd into a few
-// layers, and one lane that writes the quarters of a layer without any was the kernel's 30 us.
-__global__ __launch_bounds__(kWG) void k_topk_list_offsets(Geometry geo, TopkWorkspace ws) {
-  const uint32_t row = blockIdx.y, quarters = geo.num_chunks * kWaves, lane = lane_id();
-  const int32_t* idx = ws.idx + static_cast<size_t>(row) * geo.k;
-  uint32_t* so = ws.sel_off_srv + static_cast<size_t>(row) * (quarters + 1);
-  auto quarter = [&](uint32_t q) {
-    const uint32_t u = static_cast<uint32_t>(idx[q]) / kQuarterCoords;
-    return u < quarters ? u : quarters - 1;  // a coordinate beyond d (flagged by the unpacking)
-  };
-  const uint32_t step = gridDim.x * kWG;
-  for (uint32_t q0 = blockIdx.x * kWG + (threadIdx.x & ~63u); q0 <= geo.k; q0 += step) {  // wave-uniform
-    const uint32_t q = q0 + lane;
-    uint32_t from = 0, to = 0;  // quarters from .. to - 1
-    if (q <= geo.k) {
-      from = q ? quarter(q - 1) + 1 : 0u;
-      to = (q < geo.k ? quarter(q) : quarters) + 1;
-    }
-    constexpr uint32_t kShort = 4;
-    const uint32_t gap = to > from ? to - from : 0u;  // (a malformed list need not ascend)
-    if (gap <= kShort)
-      for (uint32_t u = 0; u < gap; ++u) so[from + u] = q;
-    uint64_t big = ballot64(gap > kShort);
-    while (big) {
-      const int l = __builtin_ctzll(big);
-      big &= big - 1;
-      const uint32_t lo = __builtin_amdgcn_readlane(from, l), hi = __builtin_amdgcn_readlane(to, l);
-      for (uint32_t u = lo + lane; u < hi; u += 64) so[u] = q0 + l;
-    }
-  }
-}
-
 // The residual at the coordinates selected in the last step becomes zero (the worker's error update of
 // Algorithm 2 for the kept coordinates), applied on request.
 __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e, Geometry geo, TopkWorkspace ws) {
@@ -2303,13 +2268,10 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   return hipSuccess;
 }
 
-// The server's lines from lists that sit in the workspace (idx, val: n ascending lists of k entries).
+// The server's lines from lists that sit in the workspace (idx, val: n ascending lists of k entries), with the offsets
+// of their quarters (sel_off_srv).
 hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
-  uint32_t groups = (geo.k + 1 + kWG - 1) / kWG;
-  if (groups > 256) groups = 256;
-  launch(L, kSlotTopkOffsets, k_topk_list_offsets, dim3(groups, geo.n), dim3(kWG), stream, geo, ws);
-  COMPAMS_CHECK_LAUNCH();
   const float* no_e = nullptr;
   const dim3 grid_f(geo.num_chunks), wg(kWG);
   const TopkFlat none{};

@@ -13,7 +13,8 @@
 // A wavefront owns a tile.  Packing: the tile's gaps are staged in LDS and every stream word is written by one
 // lane, which gathers the (at most 32) gaps that overlap it: no atomics touch the message.  Where a tile starts
 // in the stream, and the coordinate before its first entry when unpacking, come from prefix sums over the
-// tiles of a row (one workgroup per row).  A message that is not well formed never makes a kernel read outside
+// tiles of a row: formed by every workgroup for itself where a row has few tiles, else by a launch of its own (one
+// workgroup per row).  A message that is not well formed never makes a kernel read outside
 // [message, message + stride): counts come from the configuration and widths are clamped to 1 .. 31.
 
 #include "compams_device.h"
@@ -84,6 +85,48 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_width(const int32_t* __restri
     messages[static_cast<int64_t>(row) * stride + 3 + blockIdx.x] = sb[0] | (sb[1] << 8) | (sb[2] << 16) | (sb[3] << 24);
 }
 
+// Up to this many tiles per row (kDirectTiles * 256 entries of a list) every workgroup of the kernels that need the
+// sums over the tiles before its own adds them up itself, four loads per thread at most; the launch between two short
+// kernels that this replaces costs 4.7 us (437 tiles x 16 rows: packing 17.1 -> 13.7 us; unpacking, with the offsets of
+// the quarters no longer found by a launch of their own, 34.3 -> 21.0 us).
+// The work of a row grows with the square of its tiles: longer rows keep the launch.
+constexpr uint32_t kDirectTiles = 1024;
+
+// What lies before tile t0 + (the wavefront's number) of a row's per-tile amounts, and the row's sum.
+struct TileSums {
+  uint32_t before, total;
+};
+__device__ __forceinline__ TileSums tile_sums_direct(const uint32_t* __restrict__ amounts, uint32_t tiles, uint32_t t0) {
+  __shared__ uint32_t part[2][kWaves];
+  const uint32_t wave = threadIdx.x >> 6;
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (uint32_t u = 0; u < kDirectTiles / kWG; ++u) {
+    const uint32_t t = u * kWG + threadIdx.x;
+    const uint32_t a = t < tiles ? amounts[t] : 0u;
+    total += a;
+    before += t < t0 ? a : 0u;
+  }
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) {
+    before += __shfl_xor(before, s, 64);
+    total += __shfl_xor(total, s, 64);
+  }
+  if (lane_id() == 0) {
+    part[0][wave] = before;
+    part[1][wave] = total;
+  }
+  __syncthreads();
+  TileSums r{0, 0};
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    r.before += part[0][w];
+    r.total += part[1][w];
+    if (static_cast<uint32_t>(w) < wave && t0 + w < tiles) r.before += amounts[t0 + w];
+  }
+  return r;
+}
+
 // In place: per-tile amounts -> what lies before each tile; totals[row] (if given) gets the row's sum.
 // One workgroup per row.
 __global__ __launch_bounds__(kWG) void k_wire_tile_scan(uint32_t* __restrict__ tiles, uint32_t tiles_per_row,
@@ -102,6 +145,8 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_scan(uint32_t* __restrict__ t
   if (totals && threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
+// DIRECT: tile_off holds the words of every tile, not yet summed (and totals nothing).
+template <bool DIRECT>
 __global__ __launch_bounds__(kWG) void k_wire_pack_topk(const int32_t* __restrict__ idx_all,
                                                          const float* __restrict__ val_all, uint32_t k,
                                                          uint32_t tiles, const uint32_t* __restrict__ tile_off,
@@ -115,7 +160,11 @@ __global__ __launch_bounds__(kWG) void k_wire_pack_topk(const int32_t* __restric
   const float* val = val_all + static_cast<size_t>(row) * k;
   uint32_t* msg = messages + static_cast<int64_t>(row) * stride;
   const uint32_t width_words = (tiles + 3u) >> 2;
-  const uint32_t stream_total = totals[row];
+  const uint32_t* off_row = tile_off + static_cast<size_t>(row) * tiles;
+  TileSums sums;
+  if constexpr (DIRECT) sums = tile_sums_direct(off_row, tiles, blockIdx.x * kWaves);
+  else sums = TileSums{t < tiles ? off_row[t] : 0u, totals[row]};
+  const uint32_t stream_total = sums.total;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     msg[0] = 1u;
     msg[1] = k;
@@ -132,7 +181,7 @@ __global__ __launch_bounds__(kWG) void k_wire_pack_topk(const int32_t* __restric
   __syncthreads();
   if (live) {
     const uint32_t b = width_byte(msg, t);  // written by the width kernel: 1 .. 31
-    uint32_t* stream = msg + 3 + width_words + tile_off[static_cast<size_t>(row) * tiles + t];
+    uint32_t* stream = msg + 3 + width_words + sums.before;
     const uint32_t nw = tile_words(cnt, b);
     for (uint32_t w = lane; w < nw; w += 64) {
       const uint32_t lo = w * 32u;
@@ -164,25 +213,40 @@ __device__ __forceinline__ uint32_t field_of(const uint32_t* __restrict__ tile, 
 
 // status[row]: 0 well formed; bit 0: not a message of this kind and size, or a width outside 1 .. 31; bit 1 (set
 // while unpacking): length differs; bit 2 (set while unpacking): a coordinate at or beyond d.
-// Also leaves the words each tile takes (from the clamped widths) in tile_off, to be scanned.
+// Also leaves in tile_off where each tile starts in its stream (from the clamped widths), and the stream's length in
+// totals[row].  One workgroup per row.
 __global__ __launch_bounds__(kWG) void k_wire_check_topk(const uint32_t* __restrict__ messages, int64_t stride,
                                                           uint32_t k, uint32_t tiles,
                                                           uint32_t* __restrict__ tile_off,
+                                                          uint32_t* __restrict__ totals,
                                                           uint32_t* __restrict__ status) {
   __shared__ uint32_t st;
+  __shared__ uint32_t scratch[kWG / 64 + 1];
   const uint32_t row = blockIdx.x;
   const uint32_t* msg = messages + static_cast<int64_t>(row) * stride;
   if (threadIdx.x == 0) st = (msg[0] != 1u || msg[1] != k || msg[2] != kWireTile) ? 1u : 0u;
   __syncthreads();
   bool bad = false;
-  for (uint32_t t = threadIdx.x; t < tiles; t += kWG) {
-    const uint32_t b = width_byte(msg, t);
-    bad |= b < 1u || b > 31u;
-    tile_off[static_cast<size_t>(row) * tiles + t] = tile_words(tile_count(k, t), clamp_width(b));
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < tiles; base += kWG) {
+    const uint32_t t = base + threadIdx.x;
+    uint32_t words = 0;
+    if (t < tiles) {
+      const uint32_t b = width_byte(msg, t);
+      bad |= b < 1u || b > 31u;
+      words = tile_words(tile_count(k, t), clamp_width(b));
+    }
+    uint32_t total;
+    const uint32_t before = block_excl_scan<kWG>(words, scratch, &total);
+    if (t < tiles) tile_off[static_cast<size_t>(row) * tiles + t] = carry + before;
+    carry += total;
   }
   if (bad) atomicOr(&st, 1u);
   __syncthreads();
-  if (threadIdx.x == 0) status[row] = st;
+  if (threadIdx.x == 0) {
+    status[row] = st;
+    totals[row] = carry;
+  }
 }
 
 // The gaps of a lane's four consecutive entries of tile t (zero beyond the tile) and their number.
@@ -234,6 +298,13 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_sums(const uint32_t* __restri
   if (lane_id() == 0) tile_sum[static_cast<size_t>(row) * tiles + t] = sum;
 }
 
+// DIRECT: tile_sum holds the coordinates each tile covers, not yet summed.  quarter_off (OFFSETS): where the slice of
+// the list starts that belongs to each quarter (kChunk / kWaves coordinates) of a chunk, `quarters` + 1 words per row
+// = number of listed coordinates below each quarter: entry q fills the quarters between its predecessor's (exclusive)
+// and its own (inclusive), beyond the last entry follows one that fills the rest.  A short gap is filled by the entry's
+// own lane, a long one by the whole wavefront (the kept coordinates crowd into a few layers: one lane that wrote all
+// the quarters of a layer without any took 30 us).
+template <bool DIRECT, bool OFFSETS>
 __global__ __launch_bounds__(kWG) void k_wire_unpack_topk(const uint32_t* __restrict__ messages, int64_t stride,
                                                            const uint32_t* __restrict__ words, uint32_t k,
                                                            uint32_t d, uint32_t tiles,
@@ -241,7 +312,8 @@ __global__ __launch_bounds__(kWG) void k_wire_unpack_topk(const uint32_t* __rest
                                                            const uint32_t* __restrict__ totals,
                                                            const uint32_t* __restrict__ tile_sum,
                                                            int32_t* __restrict__ idx_out, float* __restrict__ val_out,
-                                                           uint32_t* __restrict__ status) {
+                                                           uint32_t* __restrict__ status, uint32_t quarters,
+                                                           uint32_t* __restrict__ quarter_off) {
   const uint32_t row = blockIdx.y, wave = threadIdx.x >> 6, lane = lane_id();
   const uint32_t t = blockIdx.x * kWaves + wave;
   const uint32_t* msg = messages + static_cast<int64_t>(row) * stride;
@@ -249,23 +321,58 @@ __global__ __launch_bounds__(kWG) void k_wire_unpack_topk(const uint32_t* __rest
   const uint32_t stream_total = totals[row];
   if (blockIdx.x == 0 && threadIdx.x == 0 && words && words[row] != 3u + width_words + stream_total + k)
     atomicOr(&status[row], 2u);
+  uint32_t tile_before;
+  if constexpr (DIRECT) tile_before = tile_sums_direct(tile_sum + static_cast<size_t>(row) * tiles, tiles, blockIdx.x * kWaves).before;
+  else tile_before = t < tiles ? tile_sum[static_cast<size_t>(row) * tiles + t] : 0u;
   if (t < tiles) {  // wave-uniform
     const LaneGaps g = lane_gaps(msg, k, tiles, t, tile_off + static_cast<size_t>(row) * tiles);
     uint32_t mine = g.n;
 #pragma unroll
     for (int s = 0; s < 4; ++s) mine += g.gap[s];
     // coordinates before this lane's first entry: those before the tile + those of the lanes below
-    uint32_t pos = tile_sum[static_cast<size_t>(row) * tiles + t] + wave_incl_scan(mine) - mine;
+    uint32_t pos = tile_before + wave_incl_scan(mine) - mine;
     int32_t* idx = idx_out + static_cast<size_t>(row) * k + t * kWireTile + lane * 4u;
     bool beyond = false;
+    constexpr uint32_t kQuarter = kChunk / kWaves, kShort = 4;
+    uint32_t* so = OFFSETS ? quarter_off + static_cast<size_t>(row) * (quarters + 1) : nullptr;
+    auto quarter_of = [&](uint32_t j) {  // (a coordinate beyond d is flagged below)
+      const uint32_t u = j / kQuarter;
+      return u < quarters ? u : quarters - 1;
+    };
+    auto fill = [&](uint32_t from, uint32_t to, uint32_t q) {  // quarters from .. to - 1 start at entry q of the list
+      const uint32_t gap = to > from ? to - from : 0u;         // (a malformed message's coordinates may wrap)
+      if (gap <= kShort)
+        for (uint32_t u = 0; u < gap; ++u) so[from + u] = q;
+      uint64_t big = ballot64(gap > kShort);
+      while (big) {
+        const int l = __builtin_ctzll(big);
+        big &= big - 1;
+        const uint32_t lo = __builtin_amdgcn_readlane(from, l), hi = __builtin_amdgcn_readlane(to, l);
+        const uint32_t at = __builtin_amdgcn_readlane(q, l);
+        for (uint32_t u = lo + lane; u < hi; u += 64) so[u] = at;
+      }
+    };
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-      if (static_cast<uint32_t>(s) < g.n) {
+    for (int s = 0; s < 4; ++s) {
+      const bool there = static_cast<uint32_t>(s) < g.n;
+      const uint32_t q = t * kWireTile + lane * 4u + s;
+      uint32_t from = 0, to = 0;
+      if (there) {
         const uint32_t j = pos + g.gap[s];
         beyond |= j >= d;
         idx[s] = static_cast<int32_t>(j);
+        if (OFFSETS) {
+          from = q ? quarter_of(pos - 1u) + 1u : 0u;  // (pos - 1: the entry before)
+          to = quarter_of(j) + 1u;
+        }
         pos = j + 1u;
       }
+      if (OFFSETS) fill(from, to, q);
+    }
+    if (OFFSETS && t + 1 == tiles) {  // wave-uniform: the quarters after the last entry
+      const bool last = g.n != 0 && t * kWireTile + lane * 4u + g.n == k;
+      fill(last ? quarter_of(pos - 1u) + 1u : 0u, last ? quarters + 1u : 0u, k);
+    }
     if (beyond) atomicOr(&status[row], 4u);
   }
   const uint32_t* values = msg + 3 + width_words + stream_total;
@@ -337,32 +444,45 @@ hipError_t wire_encode_topk(const Geometry& geo, const TopkWorkspace& ws, uint32
   launch(L, kSlotWireEncode, k_wire_tile_width, grid, wg, stream, ws.idx, geo.k, tiles, messages, stride,
          ws.wire_tile_off);
   COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireEncode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_off, tiles, ws.wire_total);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireEncode, k_wire_pack_topk, grid, wg, stream, ws.idx, ws.val, geo.k, tiles, ws.wire_tile_off,
-         ws.wire_total, messages, stride, words_out);
+  if (tiles <= kDirectTiles) {
+    launch(L, kSlotWireEncode, k_wire_pack_topk<true>, grid, wg, stream, ws.idx, ws.val, geo.k, tiles, ws.wire_tile_off,
+           ws.wire_total, messages, stride, words_out);
+  } else {
+    launch(L, kSlotWireEncode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_off, tiles, ws.wire_total);
+    COMPAMS_CHECK_LAUNCH();
+    launch(L, kSlotWireEncode, k_wire_pack_topk<false>, grid, wg, stream, ws.idx, ws.val, geo.k, tiles, ws.wire_tile_off,
+           ws.wire_total, messages, stride, words_out);
+  }
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }
 
 hipError_t wire_decode_topk(const Geometry& geo, const TopkWorkspace& ws, const uint32_t* messages, int64_t stride,
                             const uint32_t* words, int32_t* idx_out, float* val_out, uint32_t* status,
-                            hipStream_t stream, Launcher* L) {
+                            bool quarter_offsets, hipStream_t stream, Launcher* L) {
   const uint32_t tiles = (geo.k + kWireTile - 1) / kWireTile;
   const dim3 grid((tiles + kWaves - 1) / kWaves, geo.n), wg(kWG);
   uint32_t* none = nullptr;
   launch(L, kSlotWireDecode, k_wire_check_topk, dim3(geo.n), wg, stream, messages, stride, geo.k, tiles,
-         ws.wire_tile_off, status);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireDecode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_off, tiles, ws.wire_total);
+         ws.wire_tile_off, ws.wire_total, status);
   COMPAMS_CHECK_LAUNCH();
   launch(L, kSlotWireDecode, k_wire_tile_sums, grid, wg, stream, messages, stride, geo.k, tiles, ws.wire_tile_off,
          ws.wire_tile_sum);
   COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireDecode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_sum, tiles, none);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireDecode, k_wire_unpack_topk, grid, wg, stream, messages, stride, words, geo.k, geo.d, tiles,
-         ws.wire_tile_off, ws.wire_total, ws.wire_tile_sum, idx_out, val_out, status);
+  const bool direct = tiles <= kDirectTiles;
+  if (!direct) {
+    launch(L, kSlotWireDecode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_sum, tiles, none);
+    COMPAMS_CHECK_LAUNCH();
+  }
+  const uint32_t quarters = geo.num_chunks * kWaves;
+#define COMPAMS_UNPACK(D, O)                                                                                         \
+  launch(L, kSlotWireDecode, k_wire_unpack_topk<D, O>, grid, wg, stream, messages, stride, words, geo.k, geo.d, tiles, \
+         ws.wire_tile_off, ws.wire_total, ws.wire_tile_sum, idx_out, val_out, status, quarters, ws.sel_off_srv)
+  if (direct && quarter_offsets) COMPAMS_UNPACK(true, true);
+  else if (direct) COMPAMS_UNPACK(true, false);
+  else if (quarter_offsets) COMPAMS_UNPACK(false, true);
+  else COMPAMS_UNPACK(false, false);
+#undef COMPAMS_UNPACK
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }

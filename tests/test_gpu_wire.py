@@ -127,3 +127,33 @@ def test_encode_needs_a_step_and_a_compressor():
     with pytest.raises(B.CompamsError):
         c.compams_encode(stride_words=8)
     c.close()
+
+
+# Sums over the tiles before a tile: formed by every workgroup up to 1024 tiles (262144 entries), by a launch beyond.
+@pytest.mark.parametrize("k", [1, 256 * 4 - 1, 256 * 4 + 1, 256 * 255 + 7, 256 * 1024, 256 * 1024 + 1])
+def test_tile_sums_with_and_without_a_launch_of_their_own(k):
+    n, d = 2, 600_000
+    rng = np.random.default_rng(k)
+    g = rng.standard_normal((n, d)).astype(np.float32)
+    g[:, 100_000:500_000] *= np.float32(1e-3)      # long gaps: hundreds of quarters of a chunk without an entry
+    theta0 = rng.standard_normal(d).astype(np.float32)
+    a, b = (B.Compams(n, d, torch.from_numpy(theta0), compressor=B.TOPK, k=k) for _ in range(2))
+    for ctx, split in ((a, False), (b, True)):
+        gp = torch.zeros((n, ctx.ld))
+        gp[:, :d] = torch.from_numpy(g)
+        gp = gp.to(ctx.device)
+        if not split:
+            ctx.compams_step(gp, 1e-3)
+            continue
+        ctx.compams_worker_step(gp)
+        messages, words = ctx.compams_encode()
+        idx, val, status = ctx.compams_decode(messages, words)
+        torch.cuda.synchronize()
+        assert not status.any()
+        assert torch.equal(idx, ctx.compams_state("last_idx")) and torch.equal(val, ctx.compams_state("last_val"))
+        assert not ctx.compams_server_step(messages, words, 1e-3).any()
+    torch.cuda.synchronize()
+    for s in ("theta", "m", "v", "vhat"):
+        assert torch.equal(getattr(a, s), getattr(b, s)), s
+    a.close()
+    b.close()
