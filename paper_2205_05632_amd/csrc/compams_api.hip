@@ -49,7 +49,7 @@ void launcher_end(Launcher* L, int slot, hipStream_t stream) {
 namespace {
 
 const char* const kSlotNames[kNumSlots] = {
-    "topk_pass_a", "topk_band", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final",
+    "topk_pass_a", "topk_band", "topk_pick", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final",
     "bs_pass1", "bs_finalize", "bs_pass2", "bs_amsgrad", "none_amsgrad", "wire_encode", "wire_decode"};
 
 static_assert(kCountersPerRow == COMPAMS_COUNTERS_PER_ROW, "the kernels' stride of the counters is the header's");

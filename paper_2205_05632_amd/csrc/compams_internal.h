@@ -78,6 +78,13 @@ constexpr uint32_t kBandMaxEntries = 1u << 20;  // capacity of a band list at mo
 constexpr uint32_t kBoundaryCap = 64;      // entries in the bucket that holds the threshold key; more: general route
 constexpr uint32_t kCursorAboveWord = 2;   // word of a run's cursor line that counts the run's entries above the band
 
+// Which kernel found this step's threshold key.
+enum : uint32_t {
+  kFastNot = 0,   // the general ones
+  kFastBand = 1,  // k_topk_band
+  kFastPick = 2   // k_topk_pick: chunk records hold prefixes over the whole row, there are no further tables
+};
+
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
 struct TopkRow {
   uint32_t pred_valid;  // the next first pass may emit candidates with level-0 bucket >= b_guess
@@ -88,7 +95,7 @@ struct TopkRow {
   uint32_t band_lo, band_hi;  // keys; band_lo >= b_guess << kL0Shift, band_hi > band_lo
   uint32_t band_mul;    // bucket of a key inside the band: see band_bucket()
   // (read together by the last kernel, up to tie_last)
-  uint32_t fast;        // this step's threshold was found in the band: the general kernels skip the problem
+  uint32_t fast;        // kFast*, not 0: the threshold is known, the general kernels skip the problem
   uint32_t mode;        // kMode*
   uint32_t tau;         // the k-th largest key
   uint32_t r;           // how many keys equal to tau are selected
@@ -150,11 +157,17 @@ struct WgSlot {
   uint32_t seg, group;
 };
 
+enum : uint32_t {
+  kBandOff = 0,
+  kBandLists = 1,   // the first pass lists and counts what the window holds (k_topk_band)
+  kBandWindow = 2   // it only leaves out of the candidate list what lies below the window (k_topk_pick)
+};
+
 struct TopkOptions {
   uint32_t cap;            // candidate entries per row
   uint32_t predict;        // 1: carry the threshold bucket over to the next step's first pass
   uint32_t force_dense;    // 1: never build a candidate list (test / ablation)
-  uint32_t band;           // 1: also carry a window for the threshold key itself over (k_topk_band)
+  uint32_t band;           // kBand*: also carry a window for the threshold key itself over
   uint32_t band_cap;       // band entries per row
 };
 
@@ -260,7 +273,7 @@ struct Geometry {
 
 // Kernel slots for optional timing.
 enum KernelSlot {
-  kSlotPassA = 0, kSlotBand, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal,
+  kSlotPassA = 0, kSlotBand, kSlotPick, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal,
   kSlotBsPass1, kSlotBsFinal, kSlotBsPass2, kSlotBsAms,
   kSlotNoneAms, kSlotWireEncode, kSlotWireDecode, kNumSlots
 };

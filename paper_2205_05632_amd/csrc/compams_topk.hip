@@ -650,7 +650,8 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   const bool pred = use_guess && rw[0] != 0;  // workgroup-uniform
   const uint32_t bg = rw[1];
   // the band [blo, bhi) of keys: empty (no key is >= 0xffffffff) unless the row carries one
-  const bool banded = pred && opt.band && rw[4] != 0;
+  const bool windowed = pred && opt.band && rw[4] != 0;
+  const bool banded = windowed && opt.band == kBandLists;
   const uint32_t blo = banded ? rw[5] : 0xffffffffu;
   const uint32_t bhi = banded ? rw[6] : 0xffffffffu;
   const uint32_t bmul = banded ? rw[7] : 0u;
@@ -658,7 +659,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   // above that), the band's first key: the threshold is expected inside the band, so that nothing below it is needed
   // (a list of at least k entries that holds every key from some key upwards holds the k largest, wherever that
   // key lies inside a bucket; a shorter one sends the row to the kernels that read it again).
-  const uint32_t cand_lo = banded ? blo : bg << kL0Shift;
+  const uint32_t cand_lo = windowed ? rw[5] : bg << kL0Shift;
   uint32_t* bh = ws.bhist + static_cast<size_t>(row) * kBandBuckets;
   uint32_t* bm = bm_all + (PEND ? wave * 32 : 0);
   if constexpr (PEND) {
@@ -1153,7 +1154,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       // ties kept: those at coordinates <= last_coord; all of them if the last tie is kept
       const uint32_t ties_kept = suf[1], ties_after = n_ties - ties_kept;
       const uint32_t tau_prev = tau_before;
-      rowp->fast = 1;
+      rowp->fast = kFastBand;
       rowp->level1_done = 1;
       rowp->mode = kModeCand;
       rowp->n_src = cand.total;
@@ -1210,6 +1211,241 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The whole selection of a short row (at most kPickChunks chunks) by one workgroup: it takes the place of the band
+// kernel and of the four general ones, whose launches and row-wide steps cost a short row more than its bytes (4 rows
+// of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass 31.0 -> 23.9).
+//   1. Elements: the candidate list if the guess held, else the row's stored values.  The first kPickHeld of a thread
+//      stay in registers; what goes beyond is read again in every sweep.
+//   2. The bucket that holds the k-th largest key, by histograms of kPickBins buckets in LDS, each over the bucket the
+//      one before found: from a list, buckets of a thousandth of an octave from the list's lower end upwards, so that
+//      the first one usually leaves a handful of entries (key bits from the top, as for a row, would put a list's keys
+//      into a few buckets, on which the LDS atomics queue).
+//   3. At most kPickRank entries left: they are ranked by (key descending, coordinate ascending).  More can only be
+//      equal keys: the last tie to take is found by the same histograms over the coordinates.
+//   4. Per chunk the entries kept, and their prefix over the row, for the last kernel; guess and window for the next
+//      step as the other routes set them.
+// A row's window only narrows what the first pass lists (opt.band = kBandWindow); whether the threshold lay inside is
+// counted as on the band route.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPickThreads = 1024;
+constexpr uint32_t kPickChunks = 16;
+constexpr int kPickBins = 2048;
+constexpr int kPickHeld = 4;
+constexpr uint32_t kPickRank = 1024;
+
+__global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
+                                                             TopkOptions opt, uint32_t use_guess) {
+  __shared__ uint32_t lh[kPickBins];
+  __shared__ uint32_t suf[kPickThreads + 1];
+  __shared__ uint32_t out2[2];
+  __shared__ uint2 rank_en[kPickRank];
+  __shared__ uint32_t chunk_cnt[kPickChunks];
+  __shared__ uint32_t sh_count, sh_ties, sh_ties_in, sh_tau, sh_last, sh_from0, sh_from1, sh_window, sh_bucket;
+  const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
+  const uint32_t row = sc.seg, t = threadIdx.x, lane = lane_id();
+  const uint32_t k = geo.k;
+  TopkRow* rowp = ws.rows + row;
+  const float* er = e + sc.elem_off;
+  const uint2* candr = ws.cand + sc.cand_base;
+  const uint32_t n_cand = rowp->cursor, bg = rowp->b_guess;  // (a short row's list is kept as one run)
+  const uint32_t blo = rowp->band_lo, bhi = rowp->band_hi, bmul = rowp->band_mul;
+  const uint32_t tau_before = rowp->tau, tau_before2 = rowp->tau_prev;
+  const bool pred = use_guess && rowp->pred_valid != 0;
+  const bool windowed = pred && opt.band && rowp->band_valid != 0;
+  const bool listed = pred && !opt.force_dense && n_cand >= k && n_cand <= opt.cap;
+  const uint32_t count = listed ? n_cand : geo.d;
+  auto element = [&](uint32_t q) {  // q < count
+    return listed ? candr[q] : make_uint2(q, __float_as_uint(er[q]));
+  };
+  uint2 held[kPickHeld];
+#pragma unroll
+  for (int u = 0; u < kPickHeld; ++u) {
+    const uint32_t q = u * kPickThreads + t;
+    held[u] = q < count ? element(q) : make_uint2(0u, 0u);
+  }
+  // visit(element, whether it exists) for every element, whole wavefronts at a time
+  auto sweep = [&](auto&& visit) {
+#pragma unroll
+    for (int u = 0; u < kPickHeld; ++u)
+      if (static_cast<uint32_t>(u * kPickThreads) < count) visit(held[u], u * kPickThreads + t < count);  // uniform
+#pragma unroll 1
+    for (uint32_t q0 = kPickHeld * kPickThreads; q0 < count; q0 += kPickHeld * kPickThreads) {
+      uint2 en[kPickHeld];
+#pragma unroll
+      for (int u = 0; u < kPickHeld; ++u) {
+        const uint32_t q = q0 + u * kPickThreads + t;
+        en[u] = q < count ? element(q) : make_uint2(0u, 0u);
+      }
+#pragma unroll
+      for (int u = 0; u < kPickHeld; ++u) visit(en[u], q0 + u * kPickThreads + t < count);
+    }
+  };
+  if (t < kPickChunks) chunk_cnt[t] = 0;
+  if (t == 0) sh_count = sh_ties = sh_ties_in = sh_from0 = sh_from1 = sh_window = sh_bucket = 0;
+  // ---- 2. [lo, hi]: keys among which the k-th largest is the need-th largest ----
+  uint32_t lo = listed ? (windowed ? blo : bg << kL0Shift) : 0u, hi = 0xffffffffu;
+  uint32_t shift = listed ? 13u : 20u;  // (20: the buckets reach from 0 to 2^31)
+  uint32_t need = k, inside = 0;
+#pragma unroll 1
+  for (;;) {
+    for (int b = t; b < kPickBins; b += kPickThreads) lh[b] = 0;
+    __syncthreads();
+    sweep([&](const uint2& en, bool ok) {
+      const uint32_t key = key_of_bits(en.y);
+      if (ok && key >= lo && key <= hi) {
+        const uint32_t b = (key - lo) >> shift;
+        atomicAdd(&lh[b < kPickBins ? b : kPickBins - 1], 1u);  // the last bucket holds everything above it
+      }
+    });
+    __syncthreads();
+    find_crossing<kPickBins, kPickThreads>(lh, need, suf, out2);
+    const uint32_t b = out2[0];
+    need -= out2[1];
+    inside = lh[b];
+    lo += b << shift;
+    if (b + 1 < kPickBins) {
+      const uint32_t top = lo + ((1u << shift) - 1u);
+      hi = top < hi ? top : hi;
+    }
+    __syncthreads();  // everybody has read the histogram and the crossing
+    if (inside <= kPickRank || lo == hi) break;
+    // the next buckets: a 2048th of this one, or (the open last bucket) up to the largest key
+    shift = hi == 0xffffffffu ? 20u : (shift > 11u ? shift - 11u : 0u);
+  }
+  // ---- 3. tau and the last tie to take ----
+  uint32_t tau, tie_last, ties, ties_kept;
+  if (inside <= kPickRank) {
+    sweep([&](const uint2& en, bool ok) {
+      const uint32_t key = key_of_bits(en.y);
+      if (ok && key >= lo && key <= hi) rank_en[atomicAdd(&sh_count, 1u)] = make_uint2(en.x, key);
+    });
+    __syncthreads();
+    uint32_t my_key = 0, my_coord = 0, rank = 0;
+    if (t < inside) {
+      my_coord = rank_en[t].x;
+      my_key = rank_en[t].y;
+      for (uint32_t q = 0; q < inside; ++q) {
+        const uint2 o = rank_en[q];
+        rank += (o.y > my_key || (o.y == my_key && o.x < my_coord)) ? 1u : 0u;
+      }
+      if (rank == need - 1) { sh_tau = my_key; sh_last = my_coord; }  // the last kept one
+    }
+    __syncthreads();
+    tau = sh_tau;
+    if (t < inside && my_key == tau) {
+      atomicAdd(&sh_ties, 1u);
+      if (my_coord <= sh_last) atomicAdd(&sh_ties_in, 1u);
+    }
+    __syncthreads();
+    ties = sh_ties;
+    ties_kept = sh_ties_in;
+    tie_last = ties_kept < ties ? sh_last : 0xffffffffu;
+  } else {
+    tau = lo;
+    ties = inside;
+    ties_kept = need;
+    tie_last = 0xffffffffu;
+    if (need < inside) {  // the need-th smallest coordinate among the entries equal to tau
+      uint32_t c_lo = 0, left = need;
+#pragma unroll 1
+      for (uint32_t c_shift = 20;; c_shift = c_shift > 11u ? c_shift - 11u : 0u) {
+        for (int b = t; b < kPickBins; b += kPickThreads) lh[b] = 0;
+        __syncthreads();
+        sweep([&](const uint2& en, bool ok) {
+          const uint32_t rel = (en.x - c_lo) >> c_shift;
+          if (ok && key_of_bits(en.y) == tau && en.x >= c_lo && rel < kPickBins)
+            atomicAdd(&lh[kPickBins - 1 - rel], 1u);  // mirrored: the smallest coordinates on top
+        });
+        __syncthreads();
+        find_crossing<kPickBins, kPickThreads>(lh, left, suf, out2);
+        c_lo += (kPickBins - 1 - out2[0]) << c_shift;
+        left -= out2[1];
+        __syncthreads();
+        if (c_shift == 0) break;
+      }
+      tie_last = c_lo;
+    }
+  }
+  // ---- 4. kept entries per chunk; what the counters and the next step's guess need ----
+  const uint32_t b0 = tau >> kL0Shift;
+  const uint32_t tau_bucket = windowed && tau >= blo && tau < bhi ? band_bucket(tau - blo, bmul) : 0xffffffffu;
+  sweep([&](const uint2& en, bool ok) {
+    const uint32_t key = key_of_bits(en.y), bucket = key >> kL0Shift;
+    const uint64_t kept = ballot64(ok && (key > tau || (key == tau && en.x <= tie_last)));
+    const uint64_t from0 = ballot64(ok && bucket >= b0), from1 = ballot64(ok && bucket + 1 >= b0);
+    const bool in_window = ok && windowed && key >= blo && key < bhi;
+    const uint64_t window = ballot64(in_window), same = ballot64(in_window && band_bucket(key - blo, bmul) == tau_bucket);
+    if (lane == 0) {
+      if (from0) atomicAdd(&sh_from0, popc64(from0));
+      if (from1) atomicAdd(&sh_from1, popc64(from1));
+      if (window) atomicAdd(&sh_window, popc64(window));
+      if (same) atomicAdd(&sh_bucket, popc64(same));
+    }
+    uint64_t left = kept;
+    const uint32_t c = en.x / kChunk;
+    while (left) {  // (a wavefront's 64 elements lie in a few chunks)
+      const uint32_t c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(left));
+      const uint64_t here = ballot64(c == c0) & left;
+      if (lane == 0) atomicAdd(&chunk_cnt[c0], popc64(here));
+      left &= ~here;
+    }
+  });
+  __syncthreads();
+  if (t < geo.num_chunks) {
+    uint32_t before = 0;
+    for (uint32_t u = 0; u < t; ++u) before += chunk_cnt[u];
+    ws.chunk_rec[sc.chunk_base + t] = make_uint4(chunk_cnt[t], 0u, before, 0u);
+  }
+  if (t != 0) return;
+  const uint32_t total = sh_from0;  // entries from the threshold's bucket upwards (a list holds them all)
+  const bool fits = total <= opt.cap && !opt.force_dense;
+  rowp->fast = kFastPick;
+  rowp->level1_done = 1;
+  rowp->mode = listed ? kModeCand : kModeDense;
+  rowp->n_src = listed ? n_cand : 0u;
+  rowp->tau_prev = tau_before;
+  rowp->tau = tau;
+  rowp->r = ties_kept;
+  rowp->ties = ties;
+  rowp->tie_last = tie_last;
+  rowp->cursor = 0;
+  rowp->cursor_band = 0;
+  ws.tau[row] = tau;
+  ws.count_gt[row] = k - ties_kept;
+  uint32_t* cn = ws.counters + row * kCountersPerRow;
+  cn[0] = listed ? 0u : (fits ? 1u : 4u);
+  cn[1] = listed ? n_cand : (fits ? total : 0u);
+  cn[2] = ties;
+  cn[3] = ties_kept;
+  const uint32_t in_window = sh_window;
+  uint32_t miss = 0;
+  if (!windowed || opt.force_dense) miss = 1;
+  else if (n_cand > opt.cap) miss = 2;
+  else if (in_window > opt.band_cap) miss = 3;
+  else if (tau >= bhi) miss = 4;
+  else if (tau < blo) miss = 5;
+  else if (sh_bucket > kBoundaryCap) miss = 6;
+  cn[4] = miss ? 0u : in_window;
+  cn[5] = miss;
+  // Guess and window for the next step, as the other routes set them; from a list nothing is known below its lower
+  // end, and the bucket below the guess it was made with is taken to hold at most as many entries as all above it.
+  uint32_t valid = 0, guess = 0;
+  if (opt.predict && !opt.force_dense) {
+    const uint32_t at_hand = listed ? n_cand : total;
+    const uint32_t bound = listed ? (b0 > bg ? n_cand : 2u * n_cand) : sh_from1;
+    if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
+    else if (at_hand <= opt.cap / 2) { valid = 1; guess = b0; }
+  }
+  rowp->pred_valid = valid;
+  rowp->b_guess = guess;
+  float noise = default_band_noise(k);
+  if (miss == 0 && in_window && normal_key(tau))
+    noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
+            static_cast<float>(in_window);
+  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, opt);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1883,7 +2119,7 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
       uint2 pre = make_uint2(0, 0);
       if (my_block) pre = ws.blk_prefix[static_cast<size_t>(rowi) * kMaxCountBlocks + my_block];
       const bool fast = ra.x != 0;
-      const bool dense = !fast && ra.y == kModeDense;
+      const bool dense = ra.x != kFastBand && ra.y == kModeDense;
       const bool partial = have && !fast && ra.w != rb.x;  // some of the row's ties are left out
       const uint32_t tau = ra.z, r = ra.w, tie = fast ? rb.y : 0xffffffffu;
       const uint32_t off = ds.x;  // of the chunk's segment in the candidate list
@@ -1932,7 +2168,9 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
       }
       uint32_t at = pre.x + rec.z;  // where the worker's next entry goes
       uint32_t eq = 0;              // keys equal to tau so far (rows with ties to leave out)
-      if (fast) {
+      if (ra.x == kFastPick) {
+        at = rec.z;                 // (the prefix over the whole row)
+      } else if (fast) {
         // Selected by k_topk_band: the kept entries of the threshold's bucket are not in the tables; pre.y of them lie
         // before the chunk's count block, and those between the block's start and the chunk are counted here (their
         // coordinates are ascending, 0xffffffff beyond the last).
@@ -2160,7 +2398,7 @@ __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e,
     if (err__ != hipSuccess) return err__;        \
   } while (0)
 
-hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
+hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& options, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
                      bool first_pass_may_predict, bool clear_pending, bool workers_only, hipStream_t stream,
                      Launcher* L) {
@@ -2169,30 +2407,40 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const dim3 grid_rows(G, geo.n), wg(kWG);
   const uint32_t use_guess = first_pass_may_predict ? 1u : 0u;
   const dim3 grid_chunks(geo.num_chunks, geo.n);
+  // Short rows are selected by a workgroup each.  A longer row's list, and a row that has to be read again, are too
+  // much for one compute unit's share of the bandwidth.
+  const bool pick = geo.num_chunks <= kPickChunks;
+  TopkOptions opt = options;
+  if (pick && opt.band) opt.band = kBandWindow;
   if (clear_pending)
     launch(L, kSlotPassA, k_topk_lean<true, true>, grid_chunks, wg, stream, g, e, geo, ws, opt, use_guess);
   else
     launch(L, kSlotPassA, k_topk_lean<false, true>, grid_chunks, wg, stream, g, e, geo, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
-  // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
-  // otherwise, so it runs in every step (about a microsecond when it has nothing to do)
-  const uint32_t count_blocks = (geo.num_chunks + geo.count_cpw - 1) / geo.count_cpw;  // <= kMaxCountBlocks
-  launch(L, kSlotBand, k_topk_band<true>, dim3(count_blocks, geo.n), wg, stream, geo, ws, opt, use_guess);
-  COMPAMS_CHECK_LAUNCH();
-  {
-    // about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
-    // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
-    uint32_t g0 = (512 + geo.n - 1) / geo.n;
-    g0 = g0 > G ? G : g0;
-    launch(L, kSlotLevel0, k_topk_level0<true>, dim3(g0, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+  if (pick) {
+    launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, e, geo, ws, opt, use_guess);
+    COMPAMS_CHECK_LAUNCH();
+  } else {
+      // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
+    // otherwise, so it runs in every step (about a microsecond when it has nothing to do)
+    const uint32_t count_blocks = (geo.num_chunks + geo.count_cpw - 1) / geo.count_cpw;  // <= kMaxCountBlocks
+    launch(L, kSlotBand, k_topk_band<true>, dim3(count_blocks, geo.n), wg, stream, geo, ws, opt, use_guess);
+    COMPAMS_CHECK_LAUNCH();
+    {
+      // about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
+      // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
+      uint32_t g0 = (512 + geo.n - 1) / geo.n;
+      g0 = g0 > G ? G : g0;
+      launch(L, kSlotLevel0, k_topk_level0<true>, dim3(g0, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+    }
+    COMPAMS_CHECK_LAUNCH();
+    launch(L, kSlotLevel1, k_topk_level1<true>, grid_rows, wg, stream, e, geo, ws, opt);
+    COMPAMS_CHECK_LAUNCH();
+    launch(L, kSlotLevel2, k_topk_level2<true>, grid_rows, wg, stream, e, geo, ws, opt);
+    COMPAMS_CHECK_LAUNCH();
+    launch(L, kSlotCount, k_topk_count<true>, dim3(count_blocks, geo.n), wg, stream, e, geo, ws, opt);
+    COMPAMS_CHECK_LAUNCH();
   }
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotLevel1, k_topk_level1<true>, grid_rows, wg, stream, e, geo, ws, opt);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotLevel2, k_topk_level2<true>, grid_rows, wg, stream, e, geo, ws, opt);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotCount, k_topk_count<true>, dim3(count_blocks, geo.n), wg, stream, e, geo, ws, opt);
-  COMPAMS_CHECK_LAUNCH();
   const dim3 grid_f(geo.num_chunks);
   const TopkFlat none{};
   const bool few = few_chunks(geo.num_chunks);

@@ -1,0 +1,60 @@
+"""Rows short enough for the selection by one workgroup (16 chunks of 4096 coordinates; 17 take the other kernels): the
+candidate list and the row itself as source, one and several histogram levels, up to and beyond 1024 entries left to
+rank, ties cut off at a coordinate, infinities, NaNs and zeros.  Every output equals the oracle's bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2205_05632_amd import binding as B
+
+from parity import Pair
+
+pytestmark = pytest.mark.gpu
+
+
+def values(kind, rng, n, d):
+    g = rng.standard_normal((n, d)).astype(np.float32)
+    if kind == "levels":            # few distinct magnitudes: many ties, some of them cut off
+        g = (rng.integers(-2, 3, size=(n, d)) * 0.5).astype(np.float32)
+    elif kind == "equal":           # one magnitude: everything is a tie
+        g = np.where(g < 0, np.float32(-1.5), np.float32(1.5))
+    elif kind == "narrow":          # all magnitudes within one histogram bucket of the first level
+        g = (np.sign(g) * (1.0 + 1e-4 * np.abs(g))).astype(np.float32)
+    elif kind == "wide":            # sixty binary orders of magnitude
+        g = (g * 2.0 ** rng.integers(-30, 30, size=(n, d))).astype(np.float32)
+    elif kind == "zeros":           # more zeros than there are entries to leave out
+        g[:, rng.random(d) < 0.97] = 0.0
+    elif kind == "special":
+        g[:, ::97] = np.inf
+        g[:, 5::101] = -np.inf
+        g[:, 7::103] = np.nan
+        g[:, 9::107] = np.float32(3.3e38)
+    return g
+
+
+@pytest.mark.parametrize("kind", ["normal", "levels", "equal", "narrow", "wide", "zeros", "special"])
+@pytest.mark.parametrize("n,d,k", [(3, 16 * 4096, 655), (2, 16 * 4096 + 1, 655), (4, 9000, 4000), (1, 4095, 4095), (5, 1025, 1)])
+def test_short_rows(kind, n, d, k):
+    rng = np.random.default_rng(d + k)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    for t in range(6):
+        with np.errstate(all="ignore"):
+            p.step(values(kind, rng, n, d), 1e-3, label=f"{kind} {d} step {t}", with_e=t in (2, 5))
+        if t == 3:
+            p.gpu.set_option(B.OPT_CANDIDATE_CAP, max(1, k // 2))   # from here on no list fits: the row itself
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
+@pytest.mark.parametrize("d", [16 * 4096, 17 * 4096])
+def test_the_two_selections_meet_at_sixteen_chunks(d):
+    """Window and guess are the same bookkeeping on both sides of the line: steady steps are counted alike."""
+    n, k = 3, 500
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    for t in range(12):
+        p.step(rng.standard_normal((n, d)).astype(np.float32), 1e-3, label=f"{d} step {t}", with_e=False)
+    torch.cuda.synchronize()
+    c = p.gpu.compams_state("counters").cpu().numpy()
+    assert (c[:, 0] == 0).all() and (c[:, 4] > 0).all() and (c[:, 5] == 0).all(), c
+    p.close()
