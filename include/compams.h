@@ -315,8 +315,9 @@ int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int 
  * large, that every device the library has run this call on holds until the process ends.
  *   cfg: as for compams_init (same checks, same status codes), with compressor = COMPAMS_TOPK (else
  *        COMPAMS_BAD_STATE: the other compressors need tables copied from the host) and with workspace and
- *        workspace_bytes ignored.  A configuration whose compams_workspace_size() exceeds
- *        COMPAMS_STATIC_SCRATCH_BYTES is rejected with COMPAMS_WORKSPACE_TOO_SMALL before anything is enqueued.
+ *        workspace_bytes ignored.  A configuration whose tables would exceed COMPAMS_STATIC_SCRATCH_BYTES (about
+ *        n * min(d, 8 k + 65536) > 4 million candidate slots) is rejected with COMPAMS_WORKSPACE_TOO_SMALL before
+ *        anything is enqueued.
  *        Without COMPAMS_KEEP_STATE the call first zeroes e, m, v, vhat (a first step); with it, e must hold the
  *        error accumulators in their settled form (as compams_state(COMPAMS_STATE_E) or this call left them).
  *   g, lr: as for compams_step.

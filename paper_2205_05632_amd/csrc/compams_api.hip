@@ -101,9 +101,10 @@ struct BlockShape {
   uint32_t off, d, k, nc, cap, band_cap, cpw, groups_first, groups_level0, groups_sweep, count_blocks, micro;
 };
 
-// Entries of a problem's band list: the window around the expected threshold holds a fraction of k.
+// Entries of a problem's band list: the window around the expected threshold holds a fraction of k, or about k hundreds
+// of steps into a run, when the residuals crowd below the threshold (twice that, because an eighth of it is a run's).
 uint32_t band_capacity(uint64_t k, uint32_t cap) {
-  uint64_t want = k + 4096;
+  uint64_t want = 2 * k + 4096;
   if (want > kBandMaxEntries) want = kBandMaxEntries;
   return want > cap ? cap : static_cast<uint32_t>(want);
 }
@@ -142,7 +143,12 @@ std::vector<BlockShape> block_shapes(const compams_config* c) {
   return v;
 }
 
-Layout make_layout(const compams_config* c) {
+// What a layout is for: a context's workspace, the tables of compams_step_static() (which has no window to carry over
+// and no messages to pack), or the size by which that call decides what it takes.  The last is a measure of its own,
+// so that what the call takes does not change with the tables.
+enum LayoutFor { kForContext, kForStatic, kStaticMeasure };
+
+Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
   Layout L;
   std::memset(&L, 0, sizeof L);
   const size_t n = static_cast<size_t>(c->n), d = static_cast<size_t>(c->d);
@@ -156,7 +162,9 @@ Layout make_layout(const compams_config* c) {
     size_t cap = 8 * k + 65536;
     if (cap > d) cap = d;
     L.cap_alloc = static_cast<uint32_t>(cap);
-    L.band_alloc = band_capacity(k, L.cap_alloc);
+    const bool context = purpose == kForContext, measure = purpose == kStaticMeasure;
+    L.band_alloc = context ? band_capacity(k, L.cap_alloc) : 0;
+    const size_t offsets = measure ? nc + 1 : nc * kWaves + 1;
     L.rows = take(n * sizeof(TopkRow));
     L.flags = take(64);
     L.counters = take(n * COMPAMS_COUNTERS_PER_ROW * 4);
@@ -164,34 +172,39 @@ Layout make_layout(const compams_config* c) {
     L.hist1 = take(n * kNB1 * 4);
     L.hist1x = take(n * kTracked * kNB1 * 4);
     L.hist2 = take(n * kNB2 * 4);
-    L.bhist = take(n * kBandBuckets * 4);
+    L.bhist = take(n * (measure ? kBandBucketsFew : band_buckets(static_cast<uint32_t>(k))) * 4);
     L.xcur = take(n * kSubLists * kCursorPitch * 4);
     L.chunk_rec = take(n * nc * 16);
     L.blk = take(n * kMaxCountBlocks * 8);
     L.blk_prefix = take(n * kMaxCountBlocks * 8);
-    L.sel_off = take(n * (nc * kWaves + 1) * 4);
+    L.sel_off = take(n * offsets * 4);
     L.desc = take(n * nc * 8);
-    L.desc2 = take(n * nc * 8);
+    L.desc2 = take(context || measure ? n * nc * 8 : 0);
     L.bnd = take(n * kBoundaryCap * 8);
     L.bnd_sel = take(n * kBoundaryCap * 4);
     L.cand = take(n * cap * 8);
-    L.band = take(n * static_cast<size_t>(L.band_alloc) * 8);
+    L.band = take(n * (measure ? std::min<size_t>({k + 4096, kBandMaxEntries, cap}) : static_cast<size_t>(L.band_alloc)) * 8);
     L.idx = take(n * k * 4);
     L.val = take(n * k * 4);
     L.tau = take(n * 4);
     L.count_gt = take(n * 4);
+    if (purpose == kForStatic) {
+      L.total = at;
+      return L;
+    }
     L.wire_total = take(n * 4);
     L.wire_tile_off = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
     L.wire_tile_sum = take(n * ((k + kWireTile - 1) / kWireTile) * 4);
-    L.sel_off_srv = take(n * (nc * kWaves + 1) * 4);
+    L.sel_off_srv = take(n * offsets * 4);
   } else if (c->compressor == COMPAMS_TOPK_BLOCKS) {
     const std::vector<BlockShape> shapes = block_shapes(c);
     const size_t M = shapes.size(), S = n * M;
-    size_t k = 0, chunks = 0, caps = 0, bcaps = 0, wg_first = 0, wg_level0 = 0, wg_sweep = 0, wg_count = 0, micro = 0,
+    size_t k = 0, chunks = 0, caps = 0, bcaps = 0, bhists = 0, wg_first = 0, wg_level0 = 0, wg_sweep = 0, wg_count = 0, micro = 0,
            big = 0;
     uint32_t cap_max = 0, band_max = 0;
     for (const BlockShape& b : shapes) {
       k += b.k; chunks += b.nc; caps += b.cap; cap_max = std::max(cap_max, b.cap);
+      bhists += b.micro ? 0 : band_buckets(b.k);
       bcaps += b.band_cap; band_max = std::max(band_max, b.band_cap);
       wg_first += b.groups_first; wg_level0 += b.groups_level0; wg_sweep += b.groups_sweep; wg_count += b.count_blocks;
       micro += b.micro;
@@ -218,7 +231,7 @@ Layout make_layout(const compams_config* c) {
     L.hist1 = take(S * kNB1 * 4);
     L.hist1x = take(S * kTracked * kNB1 * 4);
     L.hist2 = take(S * kNB2 * 4);
-    L.bhist = take(S * kBandBuckets * 4);
+    L.bhist = take(n * bhists * 4);
     L.xcur = take(n * big * kSubLists * kCursorPitch * 4);
     L.chunk_rec = take(n * chunks * 16);
     L.blk = take(S * kMaxCountBlocks * 8);
@@ -491,12 +504,12 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
       try {
         const std::vector<BlockShape> shapes = block_shapes(cfg);
         const size_t M = shapes.size();
-        uint64_t chunks = 0, caps = 0, bcaps = 0;
-        for (const BlockShape& b : shapes) { chunks += b.nc; caps += b.cap; bcaps += b.band_cap; }
+        uint64_t chunks = 0, caps = 0, bcaps = 0, bhists = 0;
+        for (const BlockShape& b : shapes) { chunks += b.nc; caps += b.cap; bcaps += b.band_cap; bhists += b.micro ? 0 : band_buckets(b.k); }
         uint32_t cursor_sets = 0;
         segs.resize(static_cast<size_t>(cfg->n) * M);
         for (int64_t i = 0; i < cfg->n; ++i) {
-          uint64_t c_at = 0, cap_at = 0, k_at = 0, band_at = 0;
+          uint64_t c_at = 0, cap_at = 0, k_at = 0, band_at = 0, bhist_at = 0;
           for (size_t b = 0; b < M; ++b) {
             const BlockShape& sh = shapes[b];
             const uint32_t si = static_cast<uint32_t>(static_cast<size_t>(i) * M + b);
@@ -508,6 +521,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
             sg.cand_base = static_cast<uint64_t>(i) * caps + cap_at;
             sg.list_base = static_cast<uint64_t>(i) * lay.k_total + k_at;
             sg.band_base = static_cast<uint64_t>(i) * bcaps + band_at;
+            sg.bhist_base = static_cast<uint64_t>(i) * bhists + bhist_at;
             sg.d = sh.d; sg.k = sh.k; sg.num_chunks = sh.nc; sg.cap = sh.cap; sg.coord_base = sh.off;
             sg.band_cap = sh.band_cap;
             sg.count_cpw = sh.cpw;
@@ -523,6 +537,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
             if (i == 0)
               for (uint32_t q = 0; q < sh.nc; ++q) m_final.push_back(WgSlot{si, q});
             c_at += sh.nc; cap_at += sh.cap; k_at += sh.k; band_at += sh.band_cap;
+            bhist_at += sh.micro ? 0 : band_buckets(sh.k);
           }
         }
         // and last of all the workgroups whose wavefronts take one micro problem each
@@ -953,12 +968,14 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
       reinterpret_cast<uintptr_t>(val_out) % 4 != 0)
     return COMPAMS_BAD_ALIGNMENT;
   compams_ctx ctx;  // lives for this call only; nothing in it owns memory
+  const size_t most = COMPAMS_STATIC_SCRATCH_BYTES;
   try {
-    ctx.lay = make_layout(cfg);
+    if (make_layout(cfg, kStaticMeasure).total > most) return COMPAMS_WORKSPACE_TOO_SMALL;
+    ctx.lay = make_layout(cfg, kForStatic);
   } catch (...) {
     return COMPAMS_HIP_ERROR;
   }
-  if (ctx.lay.total > static_cast<size_t>(COMPAMS_STATIC_SCRATCH_BYTES)) return COMPAMS_WORKSPACE_TOO_SMALL;
+  if (ctx.lay.total > most) return COMPAMS_WORKSPACE_TOO_SMALL;  // (never: it leaves out more than it adds)
   char* w = nullptr;
   if (scratch_of_current_device(&w) != hipSuccess) return COMPAMS_HIP_ERROR;
   ctx.cfg = *cfg;
@@ -966,6 +983,7 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   ctx.cfg.workspace_bytes = COMPAMS_STATIC_SCRATCH_BYTES;
   set_geometry(&ctx);
   bind_topk_workspace(&ctx, w);
+  ctx.tkopt.band = kBandOff;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Layout& lay = ctx.lay;
   const AmsParams ap = ams_params(ctx.cfg, lr, -1);

@@ -69,11 +69,15 @@ enum : uint32_t {
 };
 
 // The band: a window of magnitude keys [band_lo, band_hi) in which the next step's threshold key is expected,
-// set from the last two thresholds, cut into kBandBuckets buckets of equal width (band_bucket below).  The first pass counts, per
-// chunk, the entries at or above band_hi, copies the entries inside the window to a short list of their own (a
+// set from the last two thresholds, cut into band_buckets(k) buckets of equal width (band_bucket below).  The first pass
+// counts, per chunk, the entries at or above band_hi, copies the entries inside the window to a short list of their own (a
 // segment per chunk) and adds them to the row's bucket histogram.  If the threshold does fall inside (checked
 // exactly), one launch finishes the selection from the short list alone (k_topk_band).
-constexpr uint32_t kBandBuckets = 2048;
+// A window holds up to about k entries, and a bucket may hold kBoundaryCap at most: 70 000 to 240 000 entries (k =
+// 110 000 to 260 000, hundreds of steps into a run) fill 2048 buckets with 35 to 120 each, and one row in five went
+// to the general kernels for that alone; 8192 buckets cost their workgroups nothing measurable.
+constexpr uint32_t kBandBucketsFew = 2048, kBandBucketsMany = 8192;
+__host__ __device__ __forceinline__ uint32_t band_buckets(uint32_t k) { return k < 16384 ? kBandBucketsFew : kBandBucketsMany; }
 constexpr uint32_t kBandMaxEntries = 1u << 20;  // capacity of a band list at most
 constexpr uint32_t kBoundaryCap = 64;      // entries in the bucket that holds the threshold key; more: general route
 constexpr uint32_t kCursorAboveWord = 2;   // word of a run's cursor line that counts the run's entries above the band
@@ -87,8 +91,8 @@ enum : uint32_t {
 
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
 struct TopkRow {
-  uint32_t pred_valid;  // the next first pass may emit candidates with level-0 bucket >= b_guess
-  uint32_t b_guess;
+  uint32_t cand_from;   // 0, or one more than the first key that the next first pass lists as a candidate
+  uint32_t b_guess;     // a level-0 bucket at or below that key's
   uint32_t cursor;      // candidate entries allocated so far in this step (a list kept as one run) ...
   uint32_t cursor_band; // ... and band entries: the two are advanced together as one 64-bit word
   uint32_t band_valid;  // the next first pass may also fill the band list and the bucket histogram
@@ -114,18 +118,17 @@ struct TopkRow {
   uint32_t bnd_n;          // entries of the threshold's bucket gathered so far (k_topk_band); zero between launches
   uint32_t bnd_kept;       // fast: how many of them are kept; their coordinates, ascending, are in bnd_sel
   uint32_t ticket_band;    // "last workgroup" counter of k_topk_band; zero between launches
-  uint32_t pad[27];
+  float noise;             // not taken by k_topk_band: what its window's population says of the threshold's scatter (0:
+                           // there was no window)
+  uint32_t pad[26];
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
 
-// Bucket of a key inside a band of `span` keys starting at lo: floor(rel * kBandBuckets / span) for rel = key - lo,
-// computed as the high word of rel * mul with mul = floor(2^32 * kBandBuckets / span); a band of at most kBandBuckets
-// keys (mul = 0) has a bucket per key.  Non-decreasing in the key and always below kBandBuckets.
-inline uint32_t band_multiplier(uint32_t span) {
-  return span > kBandBuckets ? static_cast<uint32_t>((static_cast<uint64_t>(kBandBuckets) << 32) / span) : 0u;
-}
-__device__ __forceinline__ uint32_t band_multiplier_dev(uint32_t span) {
-  return span > kBandBuckets ? static_cast<uint32_t>((static_cast<uint64_t>(kBandBuckets) << 32) / span) : 0u;
+// Bucket of a key inside a band of `span` keys starting at lo: floor(rel * buckets / span) for rel = key - lo,
+// computed as the high word of rel * mul with mul = floor(2^32 * buckets / span); a band of at most `buckets`
+// keys (mul = 0) has a bucket per key.  Non-decreasing in the key and always below `buckets`.
+__device__ __forceinline__ uint32_t band_multiplier_dev(uint32_t span, uint32_t buckets) {
+  return span > buckets ? static_cast<uint32_t>((static_cast<uint64_t>(buckets) << 32) / span) : 0u;
 }
 __device__ __forceinline__ uint32_t band_bucket(uint32_t rel, uint32_t mul) { return mul ? __umulhi(rel, mul) : rel; }
 
@@ -138,6 +141,7 @@ struct Seg {
   uint64_t cand_base;    // first entry of the segment's candidate list
   uint64_t list_base;    // first entry of the segment's slice of the worker's (coordinate, value) list
   uint64_t band_base;    // first entry of the segment's band list
+  uint64_t bhist_base;   // first bucket of the segment's band histogram
   uint32_t d, k;         // length, and how many coordinates are kept
   uint32_t num_chunks;
   uint32_t cap;          // capacity of the candidate list
@@ -196,7 +200,7 @@ struct TopkWorkspace {
   uint2* desc2;         // n * num_chunks : offset of the chunk's segment in the band list; entries at or above the
                         //                  band | entries in the band << 13 | kBandChunkOverflow
   uint2* band;          // n * band_cap   : (coordinate, fp32 bits) of the entries inside the band
-  uint32_t* bhist;      // n * kBandBuckets : how many band entries fall into each bucket; zero between steps
+  uint32_t* bhist;      // band_buckets(k) per problem : how many band entries fall into each bucket; zero between steps
   uint2* bnd;           // n * kBoundaryCap : the entries of the bucket that holds the threshold key
   uint32_t* bnd_sel;    // n * kBoundaryCap : coordinates of the kept ones among them, ascending
   uint32_t* flags;      // [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared

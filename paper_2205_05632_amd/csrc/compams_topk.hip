@@ -11,9 +11,9 @@
 //                  threshold bucket is carried over as a guess, the same pass writes the candidate list: the
 //                  entries at or above the guessed bucket, a segment per chunk.  When the last two thresholds
 //                  also give a band of keys in which this step's threshold is expected, the candidates are the
-//                  entries from the band's first key upwards (it lies at or above the guessed bucket), and the
+//                  entries from a margin below the band upwards (at or above the guessed bucket), and the
 //                  pass counts per chunk the entries above the band, lists the entries inside it (a segment per
-//                  chunk again) and adds them to the row's histogram of 2048 buckets across the band.
+//                  chunk again) and adds them to the row's histogram of 2048 or 8192 buckets across the band.
 //   band           if the threshold key does lie in the band (decided exactly from the counts): per chunk the
 //                  entries kept for certain, their prefixes inside blocks of chunks and the block totals; the
 //                  few entries of the threshold's bucket are ranked by the last workgroup of the row, which
@@ -389,7 +389,7 @@ __device__ __forceinline__ void micro_problem(const float* __restrict__ g, float
     rowp->n_src = 0;
     rowp->cursor = 0;
     rowp->cursor_band = 0;
-    rowp->pred_valid = 0;
+    rowp->cand_from = 0;
     rowp->band_valid = 0;
     rowp->fast = 0;
     rowp->b_guess = 0;
@@ -428,6 +428,7 @@ struct SegCtx {
   uint32_t coord_base;
   size_t chunk_base, seloff_base, cand_base, list_base, band_base;
   uint32_t cursor_set;  // see Seg
+  size_t bhist_base;
 };
 
 // The context of workgroup `group` of segment `seg` in a flat launch.
@@ -445,6 +446,7 @@ __device__ __forceinline__ SegCtx seg_ctx_of(uint32_t seg, uint32_t group, uint3
   c.list_base = sg.list_base;
   c.band_base = sg.band_base;
   c.cursor_set = sg.cursor_set;
+  c.bhist_base = sg.bhist_base;
   geo.d = sg.d;
   geo.k = sg.k;
   geo.num_chunks = sg.num_chunks;
@@ -468,6 +470,7 @@ __device__ __forceinline__ SegCtx seg_ctx(Geometry& geo, TopkOptions& opt, const
     c.cand_base = static_cast<size_t>(c.seg) * opt.cap;
     c.list_base = static_cast<size_t>(c.seg) * geo.k;
     c.band_base = static_cast<size_t>(c.seg) * opt.band_cap;
+    c.bhist_base = static_cast<size_t>(c.seg) * band_buckets(geo.k);
     c.cursor_set = geo.num_chunks >= kSubListMinChunks ? c.seg : kNoCursorSet;  // short rows keep one run
     return c;
   }
@@ -635,7 +638,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   // queue behind the chunk's loads (vector loads return in order) - the first eight words of the control block
   // with one load, the list offsets with it, and only then is any of it looked at (one round trip, not one per
   // condition).
-  static_assert(offsetof(TopkRow, pred_valid) == 0 && offsetof(TopkRow, b_guess) == 4 &&
+  static_assert(offsetof(TopkRow, cand_from) == 0 && offsetof(TopkRow, b_guess) == 4 &&
                 offsetof(TopkRow, band_valid) == 16 && offsetof(TopkRow, band_lo) == 20 &&
                 offsetof(TopkRow, band_hi) == 24 && offsetof(TopkRow, band_mul) == 28 &&
                 offsetof(TopkRow, cursor) == 8 && offsetof(TopkRow, cursor_band) == 12,
@@ -648,19 +651,17 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     prev_hi = table_u32(prev_off, c * kWaves + wave + 1);
   }
   const bool pred = use_guess && rw[0] != 0;  // workgroup-uniform
-  const uint32_t bg = rw[1];
   // the band [blo, bhi) of keys: empty (no key is >= 0xffffffff) unless the row carries one
-  const bool windowed = pred && opt.band && rw[4] != 0;
-  const bool banded = windowed && opt.band == kBandLists;
+  const bool banded = pred && opt.band == kBandLists && rw[4] != 0;
   const uint32_t blo = banded ? rw[5] : 0xffffffffu;
   const uint32_t bhi = banded ? rw[6] : 0xffffffffu;
   const uint32_t bmul = banded ? rw[7] : 0u;
-  // Candidates: every key at or above cand_lo - the guessed bucket's first key, or, with a band (which starts at or
-  // above that), the band's first key: the threshold is expected inside the band, so that nothing below it is needed
-  // (a list of at least k entries that holds every key from some key upwards holds the k largest, wherever that
-  // key lies inside a bucket; a shorter one sends the row to the kernels that read it again).
-  const uint32_t cand_lo = windowed ? rw[5] : bg << kL0Shift;
-  uint32_t* bh = ws.bhist + static_cast<size_t>(row) * kBandBuckets;
+  // Candidates: every key at or above cand_lo - the guessed bucket's first key, or, with a band, a key somewhat below
+  // the band's first one: the threshold is expected inside the band, so that little below it is needed (a list of at
+  // least k entries that holds every key from some key upwards holds the k largest, wherever that key lies inside a
+  // bucket; a shorter one sends the row to the kernels that read it again).
+  const uint32_t cand_lo = rw[0] - 1u;
+  uint32_t* bh = ws.bhist + sc.bhist_base;
   uint32_t* bm = bm_all + (PEND ? wave * 32 : 0);
   if constexpr (PEND) {
     // the quarter's coordinates that were selected in the previous step: their residual counts as zero
@@ -758,7 +759,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     sh_off = off;
     sh_boff = boff;
     ws.desc[sc.chunk_base + c] = make_uint2(run_base + off, total);
-    ws.desc2[sc.chunk_base + c] = make_uint2(brun_base + boff, atotal | (btotal << 13));
+    if (banded) ws.desc2[sc.chunk_base + c] = make_uint2(brun_base + boff, atotal | (btotal << 13));
     if (atotal) atomicAdd(runs ? cur + kCursorAboveWord : &rowp->above, atotal);  // nobody waits for it
   }
   __syncthreads();
@@ -850,10 +851,16 @@ __device__ __forceinline__ float default_band_noise(uint32_t k) { return 1.5f / 
 
 __device__ __forceinline__ bool normal_key(uint32_t key) { return key >= 0x00800000u && key < 0x7f000000u; }
 
+// Below the band's lower end lies a margin of half its half-width, at most 2 %: the candidate list starts there, so
+// that a threshold just below the band (two steps in a hundred on the ResNet-18 and ResNet-50 shapes) is still in the
+// list and costs the general kernels' sweeps (50 us), not two more reads of every row (470 us).  (Without the limit the
+// wide windows of a run's first steps make lists so long that the next step is given no guess.)
+
 __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint32_t tau_prev, uint32_t tau_prev2,
-                                              uint32_t guess_valid, uint32_t guess, float noise,
+                                              uint32_t guess_valid, uint32_t guess, float noise, uint32_t k,
                                               const TopkOptions& opt) {
   uint32_t valid = 0, lo = 0, hi = 0;
+  uint32_t from = guess << kL0Shift;  // the first key that the next first pass lists
   if (guess_valid && opt.band && opt.band_cap && normal_key(tau)) {
     const float t1 = __uint_as_float(tau);
     float d1 = 0.0f;  // the last relative change of the threshold
@@ -876,11 +883,14 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
     const uint32_t floor_key = guess << kL0Shift;
     if (lo < floor_key) lo = floor_key;
     valid = (hi < 0x7f800000u && hi > lo && lo >= 0x00800000u) ? 1u : 0u;
+    const uint32_t margin = __float_as_uint(centre * (1.0f - delta - fminf(0.5f * delta, 0.02f)));
+    if (valid && margin > from) from = margin;
   }
+  rowp->cand_from = guess_valid ? from + 1u : 0u;
   rowp->band_valid = valid;
   rowp->band_lo = lo;
   rowp->band_hi = hi;
-  rowp->band_mul = valid ? band_multiplier_dev(hi - lo) : 0u;
+  rowp->band_mul = valid ? band_multiplier_dev(hi - lo, band_buckets(k)) : 0u;
 }
 
 // The runs of a problem's band list, from the high halves of the cursors the first pass advanced.
@@ -914,7 +924,7 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
 // ---------------------------------------------------------------------------------------------
 // The selection in one launch, for problems whose threshold key falls inside the band the first pass was given.
 // Same geometry as the counting kernel: a workgroup owns a contiguous block of geo.count_cpw chunks.
-//   1. Every workgroup of a problem reads the problem's bucket histogram of band entries (kBandBuckets counts,
+//   1. Every workgroup of a problem reads the problem's bucket histogram of band entries (band_buckets(k) counts,
 //      added up by the first pass) and the count A of entries at or above the band, and finds by itself the
 //      bucket that holds the k-th largest key: it exists iff A < k <= A + (entries in the band); both lists must
 //      have fitted and the bucket must hold at most kBoundaryCap entries.  Otherwise the problem is left to the
@@ -931,9 +941,8 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
 // ---------------------------------------------------------------------------------------------
 template <bool UNI>
 __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace ws, TopkOptions opt, uint32_t use_guess) {
-  __shared__ uint32_t lh[kBandBuckets];
-  __shared__ uint32_t suf[kWG + 1];
-  __shared__ uint32_t out2[2];
+  __shared__ uint32_t suf[kWG / 64];
+  __shared__ uint32_t out3[3];
   __shared__ uint32_t l_gt[kMaxCountCpw];
   __shared__ uint32_t scratch[kWG / 64 + 1];
   __shared__ uint32_t sh_flag;
@@ -946,7 +955,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   if (start >= nc) return;  // uniform; the grid has exactly the blocks that exist
   const uint32_t end = start + cpw < nc ? start + cpw : nc;
   TopkRow* rowp = ws.rows + row;
-  uint32_t* bh = ws.bhist + static_cast<size_t>(row) * kBandBuckets;
+  const uint32_t buckets = band_buckets(k);
+  uint32_t* bh = ws.bhist + sc.bhist_base;
   const uint32_t wave = uniform_u32(t >> 6), lane = lane_id();
   constexpr int kGroup = 8;  // chunks a wavefront takes at a time: descriptors with one load, entries together
   // Everything that can be asked for before anything is known goes out together (a workgroup's work is a chain
@@ -955,10 +965,14 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   const uint2* d2 = ws.desc2 + sc.chunk_base;
   const uint32_t c_first = start + wave * kGroup;
   uint2 ds = make_uint2(0, 0);
-  if (lane < kGroup && c_first + lane < end) ds = d2[c_first + lane];
-  uint32_t x[kBandBuckets / kWG];
+  if (opt.band && lane < kGroup && c_first + lane < end) ds = d2[c_first + lane];  // (no such table without a band)
+  // (thread t's buckets are consecutive: 8 or 32 of them, four to a load)
+  uint4 x[kBandBucketsMany / kWG / 4];
+  const uint32_t per_quads = buckets / kWG / 4;  // uniform
+  const uint4* bh4 = reinterpret_cast<const uint4*>(bh) + t * per_quads;
 #pragma unroll
-  for (uint32_t i = 0; i < kBandBuckets / kWG; ++i) x[i] = bh[i * kWG + t];
+  for (uint32_t i = 0; i < kBandBucketsMany / kWG / 4; ++i)
+    x[i] = i < per_quads ? bh4[i] : make_uint4(0, 0, 0, 0);
   uint32_t total_above = rowp->above;
   if (sc.cursor_set != kNoCursorSet) {
     total_above = 0;
@@ -972,15 +986,21 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   const ListRuns cand = runs_from_cursors(ws, rowp, sc.cursor_set, opt.cap);
   const ListRuns band = band_runs_from_cursors(ws, rowp, sc.cursor_set, opt.band_cap);
   // all of it was written by earlier launches: the same for every workgroup of the problem
-  const bool banded = use_guess && opt.band && !opt.force_dense && rowp->pred_valid != 0 && rowp->band_valid != 0;
+  const bool banded = use_guess && opt.band && !opt.force_dense && rowp->cand_from != 0 && rowp->band_valid != 0;
+  // What the window's population says of the threshold's scatter, also where this route is not taken.
+  float noise = 0.0f;
+  if (banded && bhi > blo && band.total)
+    noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(blo)) * sqrtf(static_cast<float>(k)) /
+            static_cast<float>(band.total);
   if (!(banded && cand.fits && band.fits && bhi > blo)) {
     // Not this route.  The first pass may still have counted (lists that did not fit): one workgroup clears the
     // problem's histogram and counters; nobody of this launch makes use of them.
     if (sc.group == 0) {
       if (banded)
-        for (uint32_t b = t; b < kBandBuckets; b += kWG) bh[b] = 0;
+        for (uint32_t b = t; b < buckets; b += kWG) bh[b] = 0;
       if (t == 0) {
-        rowp->fast = 0;
+        rowp->fast = kFastNot;
+        rowp->noise = noise;
         rowp->above = 0;
         if (sc.cursor_set != kNoCursorSet)
           for (uint32_t s = 0; s < kSubLists; ++s)
@@ -1009,20 +1029,56 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     }
   };
   request(ds);
-  // ---- 1. the bucket of the threshold key ----
-#pragma unroll
-  for (uint32_t i = 0; i < kBandBuckets / kWG; ++i) lh[i * kWG + t] = x[i];
-  __syncthreads();
+  // ---- 1. the bucket of the threshold key: the thread whose buckets the count from the top crosses finds it ----
   bool inside = total_above < k && k - total_above <= band.total;  // uniform
   const uint32_t miss = total_above >= k ? 4u : (inside ? 6u : 5u);  // the threshold lies above / below the band; or (6) ...
-  uint32_t bstar = 0, need = 0;
+  uint32_t bstar = 0, need = 0, n_boundary = 0;
   if (inside) {
-    find_crossing<kBandBuckets>(lh, k - total_above, suf, out2);
-    bstar = out2[0];
-    need = k - total_above - out2[1];       // how many entries of bucket bstar are kept: 1 <= need <= lh[bstar]
-    inside = lh[bstar] <= kBoundaryCap;
+    const uint32_t want = k - total_above;
+    uint32_t mine = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kBandBucketsMany / kWG / 4; ++i) mine += x[i].x + x[i].y + x[i].z + x[i].w;
+    uint32_t from_here = mine;  // entries in this thread's buckets and those of the threads above it
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t up = __shfl_down(from_here, o, 64);
+      if (lane + o < 64) from_here += up;
+    }
+    if (lane == 0) suf[wave] = from_here;
+    if (t < 3) out3[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w)
+      if (w > wave) from_here += suf[w];
+    uint32_t above = from_here - mine;
+    if (from_here >= want && above < want) {  // exactly one thread
+      bool found = false;
+      auto look = [&](uint32_t count, uint32_t bucket) {
+        if (found) return;
+        if (above + count >= want) {
+          found = true;
+          out3[0] = bucket;
+          out3[1] = above;
+          out3[2] = count;
+        } else {
+          above += count;
+        }
+      };
+#pragma unroll
+      for (int i = static_cast<int>(kBandBucketsMany / kWG / 4) - 1; i >= 0; --i) {
+        const uint32_t first = (t * per_quads + i) * 4;  // (quads beyond the thread's share are empty and never cross)
+        look(x[i].w, first + 3);
+        look(x[i].z, first + 2);
+        look(x[i].y, first + 1);
+        look(x[i].x, first);
+      }
+    }
+    __syncthreads();
+    bstar = out3[0];
+    need = want - out3[1];       // how many entries of bucket bstar are kept: 1 <= need <= out3[2]
+    n_boundary = out3[2];
+    inside = n_boundary <= kBoundaryCap;
   }
-  const uint32_t n_boundary = inside ? lh[bstar] : 0u;
   // ---- 2. per chunk: entries kept for certain; the threshold bucket's entries are gathered ----
   if (inside) {
     uint2* bnd = ws.bnd + static_cast<size_t>(row) * kBoundaryCap;
@@ -1081,7 +1137,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   }
   // ---- 3. the problem-wide part, by whichever of its workgroups finishes last ----
   if (!last_group_of_row(&rowp->ticket_band, sc.groups, &sh_flag)) return;
-  for (uint32_t b = t; b < kBandBuckets; b += kWG) bh[b] = 0;  // every workgroup has read it
+  for (uint32_t b = t; b < buckets; b += kWG) bh[b] = 0;  // every workgroup has read it
   uint32_t n_kept = 0;
   if (inside) {
     // the gathered entries (written by other workgroups with device-scope stores: read at that scope)
@@ -1112,10 +1168,10 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         rank += (kq > my_key || (kq == my_key && cq < my_coord)) ? 1u : 0u;
       }
       kept = rank < need;
-      if (rank == need - 1) { out2[0] = my_key; out2[1] = my_coord; }  // the last kept one: tau and the last tie taken
+      if (rank == need - 1) { out3[0] = my_key; out3[1] = my_coord; }  // the last kept one: tau and the last tie taken
     }
     __syncthreads();
-    const uint32_t tau = out2[0], last_coord = out2[1];
+    const uint32_t tau = out3[0], last_coord = out3[1];
     // ties, and the kept entries' coordinates in ascending order
     if (t < kBoundaryCap) b_rank[t] = 0xffffffffu;
     __syncthreads();
@@ -1183,14 +1239,12 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
         else if (cand.total <= opt.cap / 2) { valid = 1; guess = b0; }
       }
-      rowp->pred_valid = valid;
       rowp->b_guess = guess;
-      const float width = (__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau);  // band keys are normal floats
-      const float noise = 8.0f * width * sqrtf(static_cast<float>(k)) / static_cast<float>(band.total);
-      set_next_band(rowp, tau, tau_prev, tau_before2, valid, guess, noise, opt);
+      set_next_band(rowp, tau, tau_prev, tau_before2, valid, guess, noise, k, opt);
     }
   } else if (t == 0) {
-    rowp->fast = 0;
+    rowp->fast = kFastNot;
+    rowp->noise = noise;
     uint32_t* cn = ws.counters + row * kCountersPerRow;
     cn[4] = 0;
     cn[5] = miss;  // (6): ... its bucket holds more entries than are ranked here
@@ -1251,9 +1305,9 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   const float* er = e + sc.elem_off;
   const uint2* candr = ws.cand + sc.cand_base;
   const uint32_t n_cand = rowp->cursor, bg = rowp->b_guess;  // (a short row's list is kept as one run)
-  const uint32_t blo = rowp->band_lo, bhi = rowp->band_hi, bmul = rowp->band_mul;
+  const uint32_t blo = rowp->band_lo, bhi = rowp->band_hi, bmul = rowp->band_mul, cand_lo = rowp->cand_from - 1u;
   const uint32_t tau_before = rowp->tau, tau_before2 = rowp->tau_prev;
-  const bool pred = use_guess && rowp->pred_valid != 0;
+  const bool pred = use_guess && rowp->cand_from != 0;
   const bool windowed = pred && opt.band && rowp->band_valid != 0;
   const bool listed = pred && !opt.force_dense && n_cand >= k && n_cand <= opt.cap;
   const uint32_t count = listed ? n_cand : geo.d;
@@ -1286,7 +1340,7 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   if (t < kPickChunks) chunk_cnt[t] = 0;
   if (t == 0) sh_count = sh_ties = sh_ties_in = sh_from0 = sh_from1 = sh_window = sh_bucket = 0;
   // ---- 2. [lo, hi]: keys among which the k-th largest is the need-th largest ----
-  uint32_t lo = listed ? (windowed ? blo : bg << kL0Shift) : 0u, hi = 0xffffffffu;
+  uint32_t lo = listed ? cand_lo : 0u, hi = 0xffffffffu;
   uint32_t shift = listed ? 13u : 20u;  // (20: the buckets reach from 0 to 2^31)
   uint32_t need = k, inside = 0;
 #pragma unroll 1
@@ -1439,13 +1493,12 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
     if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
     else if (at_hand <= opt.cap / 2) { valid = 1; guess = b0; }
   }
-  rowp->pred_valid = valid;
   rowp->b_guess = guess;
   float noise = default_band_noise(k);
   if (miss == 0 && in_window && normal_key(tau))
     noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
             static_cast<float>(in_window);
-  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, opt);
+  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, k, opt);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1472,7 +1525,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
   if (rowp->fast) return;  // the threshold was found in the band (k_topk_band); same for the whole row
   const uint32_t bg = rowp->b_guess;
   const ListRuns runs = runs_from_cursors(ws, rowp, sc.cursor_set, opt.cap);  // written by the previous launch
-  const bool listed = use_guess && rowp->pred_valid != 0 && runs.total >= geo.k && runs.fits && !opt.force_dense;
+  const bool listed = use_guess && rowp->cand_from != 0 && runs.total >= geo.k && runs.fits && !opt.force_dense;
   for (int b = threadIdx.x; b < kNB0; b += kWG) lh[b] = 0;
   for (uint32_t b = threadIdx.x; b < kTracked * kNB1; b += kWG) lh1[b] = 0;
   __syncthreads();
@@ -1560,7 +1613,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
       if (bstar && total + below <= opt.cap / 2) { valid = 1; guess = bstar - 1; }
       else if (total <= opt.cap / 2) { valid = 1; guess = bstar; }
     }
-    rowp->pred_valid = valid;
+    rowp->cand_from = valid ? (guess << kL0Shift) + 1u : 0u;
     rowp->b_guess = guess;
     uint32_t* cn = ws.counters + row * kCountersPerRow;
     cn[0] = reads;
@@ -1726,7 +1779,8 @@ __global__ __launch_bounds__(kWG) void k_topk_level2(const float* __restrict__ e
     cn[3] = r;
     cn[4] = 0;
     // the guess was set when the threshold bucket was found (first kernel of this route, an earlier launch)
-    set_next_band(rowp, tau, tau_prev, tau_prev2, rowp->pred_valid, rowp->b_guess, default_band_noise(geo.k), opt);
+    set_next_band(rowp, tau, tau_prev, tau_prev2, rowp->cand_from != 0 ? 1u : 0u, rowp->b_guess,
+                  rowp->noise > 0.0f ? rowp->noise : default_band_noise(geo.k), geo.k, opt);
   }
 }
 
