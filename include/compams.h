@@ -325,8 +325,8 @@ int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int 
  *        COMPAMS_STATE_LAST_VAL).
  * Only enqueues kernels on hip_stream (no copy or memset node, no synchronisation).  When the stream has passed
  * the call, theta, m, v, vhat and e hold the result of one iteration of Algorithm 2 with nothing left pending:
- * bit for bit what the four calls above give.  Nothing is carried from one call to the next (no threshold guess:
- * every call reads the rows of corrected gradients a second time), so it is the slower way to step.
+ * bit for bit what the four calls above give.  Nothing is carried from one call to the next (the threshold guess comes
+ * from a sample of every row), so it is the slower way to step.
  * All calls on one device share that device's array: calls that overlap in time on one device (two streams, two
  * threads) race; calls on one stream, or otherwise ordered, do not. */
 #define COMPAMS_STATIC_SCRATCH_BYTES (32u << 20)

@@ -642,7 +642,7 @@ static int step_impl(compams_ctx* ctx, const float* g, float lr, bool workers_on
       const bool may_predict = ctx->steps > 0 && ctx->tkopt.predict && !ctx->tkopt.force_dense;
       if (c.compressor == COMPAMS_TOPK)
         err = topk_step(ctx->geo, ctx->tk, ctx->tkopt, ap, g, c.e, c.theta, c.m, c.v, c.vhat, may_predict,
-                        ctx->clear_pending, workers_only, stream, L);
+                        ctx->clear_pending, workers_only, false, stream, L);
       else
         err = topk_blocks_step(ctx->geo, ctx->tk, ctx->tkopt, ap, ctx->lay.flat, g, c.e, c.theta, c.m, c.v, c.vhat,
                                may_predict, ctx->clear_pending, workers_only, stream, L);
@@ -989,10 +989,12 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   const AmsParams ap = ams_params(ctx.cfg, lr, -1);
   hipError_t err = hipSuccess;
   auto ok = [&](hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; };
-  // the array keeps what the last call left: control blocks, counters, histograms and chunk tables start at zero
-  // (fill kernels, so that the call can be recorded into a graph); lists need no initial value
-  ok(fill_u32(reinterpret_cast<uint32_t*>(w), lay.cand / 4, 0u, stream));
-  ok(fill_u32(reinterpret_cast<uint32_t*>(w + lay.idx), (lay.total - lay.idx) / 4, 0u, stream));
+  // the array keeps what the last call left: control blocks, counters, cursors and histograms start at zero (a fill
+  // kernel, so that the call can be recorded into a graph); the tables behind them are written before they are read
+  ok(fill_u32(reinterpret_cast<uint32_t*>(w), lay.chunk_rec / 4, 0u, stream));
+  // what the workers send is written where the caller wants it
+  if (idx_out) ctx.tk.idx = idx_out;
+  if (val_out) ctx.tk.val = val_out;
   if (!(cfg->flags & COMPAMS_KEEP_STATE)) {
     ok(fill_rows_f32(cfg->e, ctx.geo.n, ctx.geo.ld, ctx.geo.d, 0.0f, stream));
     ok(fill_rows_f32(cfg->m, 1, 0, ctx.geo.d, 0.0f, stream));
@@ -1001,19 +1003,13 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   }
   if (err == hipSuccess) {
     try {
-      // no guess is carried over and no error line is pending on entry; the one this step leaves is applied at once
+      // no guess is carried over and no error line is pending on entry; the one of this step is applied at once
       err = topk_step(ctx.geo, ctx.tk, ctx.tkopt, ap, g, cfg->e, cfg->theta, cfg->m, cfg->v, cfg->vhat, false, false,
-                      false, stream, nullptr);
+                      false, true, stream, nullptr);
     } catch (...) {
       err = hipErrorUnknown;
     }
   }
-  if (err == hipSuccess) err = topk_apply_clear(ctx.geo, ctx.tk, cfg->e, stream);
-  const size_t nk = static_cast<size_t>(cfg->n) * static_cast<size_t>(cfg->k);
-  if (err == hipSuccess && idx_out)
-    err = copy_u32(reinterpret_cast<uint32_t*>(idx_out), reinterpret_cast<const uint32_t*>(ctx.tk.idx), nk, stream);
-  if (err == hipSuccess && val_out)
-    err = copy_u32(reinterpret_cast<uint32_t*>(val_out), reinterpret_cast<const uint32_t*>(ctx.tk.val), nk, stream);
   return err == hipSuccess ? COMPAMS_OK : COMPAMS_HIP_ERROR;
 }
 

@@ -285,9 +285,11 @@ enum KernelSlot {
 struct Launcher;  // host-side helper that brackets launches with events (compams_api.hip)
 
 // Host-side launch entry points, one per compressor (defined next to their kernels).
+// whole: a step that stands for itself (fresh control blocks, no guess, nothing pending): the residual's zeros are
+// written at once.
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
-                     bool first_pass_may_predict, bool clear_pending, bool workers_only, hipStream_t stream,
+                     bool first_pass_may_predict, bool clear_pending, bool workers_only, bool whole, hipStream_t stream,
                      Launcher* L);
 // Sizes of the flat launches of top-k inside every block.
 struct TopkFlat {
@@ -323,7 +325,6 @@ hipError_t wire_decode_blocksign(const Geometry& geo, const uint32_t* messages, 
                                  Launcher* L);
 hipError_t fill_u32(uint32_t* p, size_t count, uint32_t value, hipStream_t stream);
 hipError_t fill_rows_f32(float* p, uint32_t n, int64_t ld, uint32_t d, float value, hipStream_t stream);
-hipError_t copy_u32(uint32_t* dst, const uint32_t* src, size_t count, hipStream_t stream);
 hipError_t stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 hipError_t inplace_probe(float* const* arrays, int n_arrays, size_t count, int cached_arrays, hipStream_t stream);
 

@@ -1349,10 +1349,11 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
     __syncthreads();
     sweep([&](const uint2& en, bool ok) {
       const uint32_t key = key_of_bits(en.y);
-      if (ok && key >= lo && key <= hi) {
-        const uint32_t b = (key - lo) >> shift;
-        atomicAdd(&lh[b < kPickBins ? b : kPickBins - 1], 1u);  // the last bucket holds everything above it
-      }
+      const bool in = ok && key >= lo && key <= hi;
+      const uint32_t b = (key - lo) >> shift;
+      if (in && b + 1 < kPickBins) atomicAdd(&lh[b], 1u);
+      const uint64_t above = ballot64(in && b + 1 >= kPickBins);  // the last bucket holds everything above it
+      if (above && lane == 0) atomicAdd(&lh[kPickBins - 1], popc64(above));
     });
     __syncthreads();
     find_crossing<kPickBins, kPickThreads>(lh, need, suf, out2);
@@ -1499,6 +1500,61 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
     noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
             static_cast<float>(in_window);
   set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, k, opt);
+}
+
+// ---------------------------------------------------------------------------------------------
+// A guess for the first step of a row from a sample of its corrected gradients: kSample / 4 quads spread evenly over
+// the row, one workgroup per row.  (What bounds it are the cache lines that one compute unit asks for: 8192 single
+// coordinates take 37 us, in quads 12.7, 4096 in quads 7.7.)
+// The guess is the bucket above which one and a half times the share k / d of the sample lies, plus three deviations of
+// that count and a few entries for small counts: the list then holds k entries or more but for one row in hundreds, and
+// less than the capacity of 8 k + 65536.  It decides only whether the row is read again.  No window is known: the
+// general kernels select, and are told so here.
+// ---------------------------------------------------------------------------------------------
+constexpr uint32_t kSample = 4096;
+
+__global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __restrict__ g, const float* __restrict__ e,
+                                                               Geometry geo, TopkWorkspace ws) {
+  __shared__ uint32_t lh[kNB0];
+  __shared__ uint32_t suf[kPickThreads + 1];
+  __shared__ uint32_t out2[2];
+  const uint32_t row = blockIdx.x, t = threadIdx.x;
+  const float* gr = g + static_cast<int64_t>(row) * geo.ld;
+  const float* er = e + static_cast<int64_t>(row) * geo.ld;
+  constexpr uint32_t kQuads = kSample / 4;
+  constexpr int kPer = kQuads / kPickThreads;
+  static_assert(kQuads % kPickThreads == 0 && kSample <= kPickChunks * kChunk, "whole quads, of a row that is longer");
+  const uint32_t whole_quads = geo.d / 4;  // (rows of more than kPickChunks chunks: more than kQuads)
+  const uint32_t taken = kSample;
+  float4 x[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const uint32_t q = u * kPickThreads + t;
+    const uint32_t j = 4u * static_cast<uint32_t>((static_cast<uint64_t>(q) * whole_quads) / kQuads);  // (a shift)
+    const float4 ev = *reinterpret_cast<const float4*>(er + j), gv = *reinterpret_cast<const float4*>(gr + j);
+    x[u] = make_float4(ev.x + gv.x, ev.y + gv.y, ev.z + gv.z, ev.w + gv.w);
+  }
+  for (int b = t; b < kNB0; b += kPickThreads) lh[b] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].x)) >> kL0Shift], 1u);
+    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].y)) >> kL0Shift], 1u);
+    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].z)) >> kL0Shift], 1u);
+    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].w)) >> kL0Shift], 1u);
+  }
+  __syncthreads();
+  const float share = static_cast<float>(taken) * (static_cast<float>(geo.k) / static_cast<float>(geo.d));
+  const float want = 1.5f * share + 3.0f * sqrtf(share) + 8.0f;
+  const bool use = want < static_cast<float>(taken);
+  if (row == 0 && t == 0) ws.flags[0] = 1;
+  if (use) {  // uniform
+    find_crossing<kNB0, kPickThreads>(lh, static_cast<uint32_t>(want), suf, out2);
+    if (t == 0) {
+      ws.rows[row].b_guess = out2[0];
+      ws.rows[row].cand_from = (out2[0] << kL0Shift) + 1u;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1882,7 +1938,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
     // A wavefront takes kGroup consecutive chunks at a time: their descriptors come with one load, the first
     // 128 entries of every segment with independent loads (two round trips for the whole group).
     constexpr int kGroup = 8;
-    for (uint32_t c0 = start + wave * kGroup; c0 < end; c0 += kWaves * kGroup) {
+      for (uint32_t c0 = start + wave * kGroup; c0 < end; c0 += kWaves * kGroup) {
       uint2 ds = make_uint2(0, 0);
       if (lane < kGroup && c0 + lane < end) ds = descr[c0 + lane];
       if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
@@ -2099,7 +2155,8 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
 // NC: how many of theta, m, v, vhat (in that order) are read and written with ordinary accesses, the others with
 // streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
-template <int ROLE, bool UNI, int NC, int NW>
+// CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
+template <int ROLE, bool UNI, int NC, int NW, bool CLEAR = false>
 __global__ __launch_bounds__(NW * 64) void k_topk_final(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
     const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
@@ -2273,6 +2330,8 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
               const size_t l = f.list0 + (i0 + now.i) * f.list_stride + pos;
               ws.idx[l] = static_cast<int32_t>(f.coord_base + en.x);
               ws.val[l] = __uint_as_float(en.y);
+              // (nobody reads it again: a chunk of a row without a list is this wavefront's, slot after slot)
+              if (CLEAR) const_cast<float*>(e)[static_cast<int64_t>(i0 + now.i) * geo.ld + f.coord_base + en.x] = 0.0f;
             }
             if (ROLE == kWholeStep) {
               const uint32_t kept = pos - __builtin_amdgcn_readlane(at_first, now.i);
@@ -2454,18 +2513,22 @@ __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e,
 
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& options, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
-                     bool first_pass_may_predict, bool clear_pending, bool workers_only, hipStream_t stream,
+                     bool first_pass_may_predict, bool clear_pending, bool workers_only, bool whole, hipStream_t stream,
                      Launcher* L) {
   const int role = workers_only ? kWorkerHalf : kWholeStep;
   const uint32_t G = groups_per_row(geo.n, geo.num_chunks);
   const dim3 grid_rows(G, geo.n), wg(kWG);
-  const uint32_t use_guess = first_pass_may_predict ? 1u : 0u;
+  const uint32_t use_guess = first_pass_may_predict || whole ? 1u : 0u;
   const dim3 grid_chunks(geo.num_chunks, geo.n);
   // Short rows are selected by a workgroup each.  A longer row's list, and a row that has to be read again, are too
   // much for one compute unit's share of the bandwidth.
   const bool pick = geo.num_chunks <= kPickChunks;
   TopkOptions opt = options;
   if (pick && opt.band) opt.band = kBandWindow;
+  if (whole && !pick) {  // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample)
+    launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws);
+    COMPAMS_CHECK_LAUNCH();
+  }
   if (clear_pending)
     launch(L, kSlotPassA, k_topk_lean<true, true>, grid_chunks, wg, stream, g, e, geo, ws, opt, use_guess);
   else
@@ -2475,11 +2538,13 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, e, geo, ws, opt, use_guess);
     COMPAMS_CHECK_LAUNCH();
   } else {
-      // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
-    // otherwise, so it runs in every step (about a microsecond when it has nothing to do)
+    // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
+    // otherwise, so it runs in every step (about a microsecond when it has nothing to do) but one that stands for itself
     const uint32_t count_blocks = (geo.num_chunks + geo.count_cpw - 1) / geo.count_cpw;  // <= kMaxCountBlocks
-    launch(L, kSlotBand, k_topk_band<true>, dim3(count_blocks, geo.n), wg, stream, geo, ws, opt, use_guess);
-    COMPAMS_CHECK_LAUNCH();
+    if (!whole) {
+      launch(L, kSlotBand, k_topk_band<true>, dim3(count_blocks, geo.n), wg, stream, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+    }
     {
       // about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
       // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
@@ -2498,6 +2563,18 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const dim3 grid_f(geo.num_chunks);
   const TopkFlat none{};
   const bool few = few_chunks(geo.num_chunks);
+  if (whole) {
+#define COMPAMS_FINAL_CLEAR(NC) k_topk_final<kWholeStep, true, NC, kFinalMany, true>
+    if (few)  // (so short that its whole state stays in the memory-side cache)
+      launch(L, kSlotTopkFinal, k_topk_final<kWholeStep, true, 4, kFinalFew, true>, grid_f, dim3(kFinalFew * 64), stream, theta,
+             m, v, vhat, e, geo, ws, opt, ap, none);
+    else
+      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_CLEAR, grid_f, wg, stream, theta, m, v,
+                               vhat, e, geo, ws, opt, ap, none);
+#undef COMPAMS_FINAL_CLEAR
+    COMPAMS_CHECK_LAUNCH();
+    return hipSuccess;
+  }
   const dim3 wg_few(kFinalFew * 64);
 #define COMPAMS_FINAL_WHOLE_ROW(NC) k_topk_final<kWholeStep, true, NC, kFinalMany>
 #define COMPAMS_FINAL_WHOLE_ROW_FEW(NC) k_topk_final<kWholeStep, true, NC, kFinalFew>

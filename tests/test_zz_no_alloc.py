@@ -144,3 +144,44 @@ def test_sizes_beyond_the_array_and_other_compressors_are_rejected():
     assert L.compams_step_static(ctypes.byref(c), t.data_ptr(), 1e-3, None, None, None) == -2
     torch.cuda.synchronize()
     assert not t.cpu().numpy().any()
+
+
+@pytest.mark.parametrize("kind", ["normal", "zeros", "equal", "crowded", "few large"])
+@pytest.mark.parametrize("n,d,k", [(2, 16 * 4096 + 1, 700), (3, 300_007, 3_000), (1, 512 * 4096 - 5, 2_000),
+                                   (1, 512 * 4096 + 1, 20_000), (2, 90_001, 80_000)])
+def test_sampled_guess_of_every_kind_of_row(kind, n, d, k):
+    """Rows whose sample says the right thing, too little or too much: the list holds, is too short or overflows, and
+    the outcome is the oracle's each time, with and without lists asked for."""
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(d + k)
+    ld = B.padded_ld(d)
+    g = np.zeros((n, ld), np.float32)
+    x = rng.standard_normal((n, d)).astype(np.float32)
+    if kind == "zeros":
+        x[:, rng.random(d) < 0.9999] = 0.0
+    elif kind == "equal":
+        x = np.where(x < 0, np.float32(-2.5), np.float32(2.5))
+    elif kind == "crowded":              # everything large in one stretch
+        x *= np.float32(1e-3)
+        x[:, d // 3: d // 3 + 5000] *= np.float32(1e4)
+    elif kind == "few large":            # between the sampled coordinates
+        x *= np.float32(1e-6)
+        x[:, 1::1009] = 1.0
+    g[:, :d] = x
+    theta0 = rng.standard_normal(d).astype(np.float32)
+    cpu = O.Oracle(n, d, theta0, compressor=O.TOPK, k=k)
+    state = [torch.from_numpy(theta0).to(dev)] + [torch.zeros(d, device=dev) for _ in range(3)]
+    e = torch.zeros((n, ld), device=dev)
+    idx, val = torch.zeros((n, k), dtype=torch.int32, device=dev), torch.zeros((n, k), device=dev)
+    for t in range(2):
+        asked = dict(idx_out=idx, val_out=val) if t == 0 else {}
+        assert B.compams_step_static(n, d, k, *state, e, torch.from_numpy(g).to(dev), 1e-3, **asked) == 0
+        cpu.step(np.ascontiguousarray(g[:, :d]), 1e-3)
+        torch.cuda.synchronize()
+        if t == 0:
+            assert np.array_equal(idx.cpu().numpy(), cpu.get("idx")) and bits_equal(val.cpu().numpy(), cpu.get("val"))
+        for name, s in zip(("theta", "m", "v", "vhat"), state):
+            assert bits_equal(s.cpu().numpy(), cpu.get(name)), (t, name)
+        assert bits_equal(np.ascontiguousarray(e.cpu().numpy()[:, :d]), cpu.get("e")), t
+        assert not e.cpu().numpy()[:, d:].any()
+    cpu.close()
