@@ -36,14 +36,21 @@ constexpr uint32_t kTracked = 3;
 constexpr uint32_t kMicroCoords = 1024;
 constexpr uint32_t kMicroFlag = 0x80000000u;  // WgSlot.seg of a first-pass workgroup that takes micro problems
 
-// The counting kernel splits a row's chunks into at most kMaxCountBlocks contiguous blocks of count_cpw chunks
-// (a multiple of 32: four wavefronts, eight chunks at a time).  d < 2^31 gives at most 2^19 chunks.
+// The band and the counting kernel split a row's chunks into at most kMaxCountBlocks contiguous blocks of count_cpw
+// chunks (four wavefronts, eight chunks at a time: a multiple of 32).  d < 2^31 gives at most 2^19 chunks.  Rows of up
+// to 1024 chunks have blocks of 8, two chunks to a wavefront: their blocks of 32 leave most of the chip idle (4 rows of
+// 300007: the counting kernel 18.1 -> 10.1 us; 16 rows of 1 M: the band kernel 14.6 -> 12.6 us).
 constexpr uint32_t kMaxCountBlocks = 256;
 constexpr uint32_t kMaxCountCpw = 2048;
 inline uint32_t count_chunks_per_block(uint32_t num_chunks) {
   const uint32_t m = (num_chunks + 32 * kMaxCountBlocks - 1) / (32 * kMaxCountBlocks);
   return 32 * (m ? m : 1);
 }
+inline uint32_t count_chunks_per_row_block(uint32_t num_chunks) {
+  return num_chunks <= 4 * kMaxCountBlocks ? 8 : count_chunks_per_block(num_chunks);
+}
+// Chunks that a wavefront takes at a time of a block of cpw: two or eight.
+__host__ __device__ __forceinline__ uint32_t chunks_per_wave(uint32_t cpw) { return cpw < 32 ? cpw / 4 : 8; }
 
 // The candidate list of a selection problem is kept as kSubLists runs, chunk c of the problem appending to run
 // c % kSubLists, each run with a cursor in a 128-byte line of its own.  Atomics to one address are performed one

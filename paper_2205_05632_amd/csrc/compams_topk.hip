@@ -963,9 +963,10 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   // of round trips otherwise): the control block and the cursors, the bucket histogram, the counts above the
   // band, the first descriptors.
   const uint2* d2 = ws.desc2 + sc.chunk_base;
-  const uint32_t c_first = start + wave * kGroup;
+  const uint32_t group = chunks_per_wave(cpw);  // <= kGroup
+  const uint32_t c_first = start + wave * group;
   uint2 ds = make_uint2(0, 0);
-  if (opt.band && lane < kGroup && c_first + lane < end) ds = d2[c_first + lane];  // (no such table without a band)
+  if (opt.band && lane < group && c_first + lane < end) ds = d2[c_first + lane];  // (no such table without a band)
   // (thread t's buckets are consecutive: 8 or 32 of them, four to a load)
   uint4 x[kBandBucketsMany / kWG / 4];
   const uint32_t per_quads = buckets / kWG / 4;  // uniform
@@ -1082,10 +1083,10 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   // ---- 2. per chunk: entries kept for certain; the threshold bucket's entries are gathered ----
   if (inside) {
     uint2* bnd = ws.bnd + static_cast<size_t>(row) * kBoundaryCap;
-    for (uint32_t c0 = c_first; c0 < end; c0 += kWaves * kGroup) {
+    for (uint32_t c0 = c_first; c0 < end; c0 += kWaves * group) {
       if (c0 != c_first) {  // wave-uniform
         ds = make_uint2(0, 0);
-        if (lane < kGroup && c0 + lane < end) ds = d2[c0 + lane];
+        if (lane < group && c0 + lane < end) ds = d2[c0 + lane];
         request(ds);
       }
       uint32_t gt[kGroup];  // wave-uniform
@@ -1110,7 +1111,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 #pragma unroll
       for (int u = 0; u < kGroup; ++u)
         if (lane == static_cast<uint32_t>(u)) mine = gt[u];
-      if (lane < kGroup && c0 + lane < end) l_gt[c0 - start + lane] = (ds.y & 0x1fffu) + mine;
+      if (lane < group && c0 + lane < end) l_gt[c0 - start + lane] = (ds.y & 0x1fffu) + mine;
     }
     __syncthreads();
     // exclusive prefixes within the block: thread t takes `per` consecutive chunks
@@ -1938,9 +1939,10 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
     // A wavefront takes kGroup consecutive chunks at a time: their descriptors come with one load, the first
     // 128 entries of every segment with independent loads (two round trips for the whole group).
     constexpr int kGroup = 8;
-      for (uint32_t c0 = start + wave * kGroup; c0 < end; c0 += kWaves * kGroup) {
+    const uint32_t group = chunks_per_wave(cpw);  // <= kGroup
+    for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
       uint2 ds = make_uint2(0, 0);
-      if (lane < kGroup && c0 + lane < end) ds = descr[c0 + lane];
+      if (lane < group && c0 + lane < end) ds = descr[c0 + lane];
       if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
       else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
       uint32_t off[kGroup], cnt[kGroup];
@@ -1985,7 +1987,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
 #pragma unroll
       for (int u = 0; u < kGroup; ++u)
         if (lane == static_cast<uint32_t>(u)) { my_gt = gt[u]; my_eq = eq[u]; }
-      if (lane < kGroup && c0 + lane < end) { l_gt[c0 - start + lane] = my_gt; l_eq[c0 - start + lane] = my_eq; }
+      if (lane < group && c0 + lane < end) { l_gt[c0 - start + lane] = my_gt; l_eq[c0 - start + lane] = my_eq; }
     }
   }
   __syncthreads();
