@@ -63,7 +63,7 @@ struct Layout {
       idx, val, tau, count_gt, wire_total, wire_tile_off, wire_tile_sum, sel_off_srv, segs, map_first, map_level0, map_sweep,
       map_count, map_final, micro_list;
   // block-sign
-  size_t offsets, chunk_block, acc, special, scales, bits;
+  size_t offsets, chunk_block, acc, special, ticket, scales, bits;
   uint32_t acc_replicas;
   uint32_t cap_alloc, band_alloc, num_chunks, words;
   // top-k inside every block
@@ -267,6 +267,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.acc_replicas = static_cast<uint32_t>(std::min<size_t>(32, std::max<size_t>(1, nc / M)));
     L.acc = take(n * M * L.acc_replicas * kLimbs * 8);
     L.special = take(n * M * 4);
+    L.ticket = take(n * 4);
     L.scales = take(n * M * 4);
     L.bits = take(n * static_cast<size_t>(L.words) * 4);
   }
@@ -572,6 +573,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
     b.acc = reinterpret_cast<uint64_t*>(w + lay.acc);
     b.acc_replicas = lay.acc_replicas;
     b.special = reinterpret_cast<uint32_t*>(w + lay.special);
+    b.ticket = reinterpret_cast<uint32_t*>(w + lay.ticket);
     b.scales = reinterpret_cast<float*>(w + lay.scales);
     b.bits = reinterpret_cast<uint32_t*>(w + lay.bits);
     std::vector<uint32_t> off32, cb;

@@ -287,6 +287,124 @@ __device__ __noinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0,
   }
 }
 
+// A block's scale from the digits of its exact sum (still carried in 64-bit words), its flags and its length: the digits
+// are normalised, the sum rounded to double (nearest, ties to even), divided by the length and rounded to fp32.
+__device__ __forceinline__ float block_scale(const uint64_t (&word)[kLimbs], uint32_t sp, double len) {
+  uint32_t digit[kLimbs + 1];
+  uint64_t carry = 0;
+#pragma unroll
+  for (int i = 0; i < kLimbs; ++i) {
+    const uint64_t v = word[i] + carry;
+    digit[i] = static_cast<uint32_t>(v);
+    carry = v >> 32;
+  }
+  digit[kLimbs] = static_cast<uint32_t>(carry);
+  double sum;
+  if (sp & 2u) sum = __longlong_as_double(0x7ff8000000000000ll);
+  else if (sp & 1u) sum = __longlong_as_double(0x7ff0000000000000ll);
+  else {
+    // the four highest non-zero digits carry every bit a double can hold; the rest is a sticky bit
+    int top = 0;
+#pragma unroll
+    for (int i = 1; i <= kLimbs; ++i)
+      if (digit[i]) top = i;
+    const int low = top >= 3 ? top - 3 : 0;
+    uint32_t q[4] = {0, 0, 0, 0};
+    bool below = false;
+#pragma unroll
+    for (int i = 0; i <= kLimbs; ++i) {
+      if (i >= low && i < low + 4) q[i - low] = digit[i];
+      else if (i < low && digit[i]) below = true;
+    }
+    const uint64_t w0 = (static_cast<uint64_t>(q[1]) << 32) | q[0], w1 = (static_cast<uint64_t>(q[3]) << 32) | q[2];
+    sum = fixed192_to_double(w0, w1, 0, 32 * low - 149, below);
+  }
+  return static_cast<float>(sum / len);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Scales: per (row, block) add up the sets of digits (a thread when there is one set, else a wavefront with a
+// lane per set), and turn the sum into the scale.  Clears the digits for the next step.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kWG) void k_bs_finalize(Geometry geo, BlocksignWorkspace ws) {
+  const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
+  const uint32_t R = ws.acc_replicas;  // sets of digits per (row, block)
+  size_t t;
+  uint64_t word[kLimbs];
+  if (R == 1) {  // a thread per (row, block)
+    t = static_cast<size_t>(blockIdx.x) * kWG + threadIdx.x;
+    if (t >= total) return;
+    uint64_t* dg = ws.acc + t * kLimbs;
+#pragma unroll
+    for (int i = 0; i < kLimbs; ++i) {
+      word[i] = dg[i];
+      dg[i] = 0;
+    }
+  } else {  // a wavefront per (row, block): lane r brings replica r, the sums are taken over the wavefront
+    t = static_cast<size_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6);
+    if (t >= total) return;
+    const uint32_t lane = lane_id();
+    uint64_t* dg = ws.acc + (t * R + lane) * kLimbs;
+#pragma unroll
+    for (int i = 0; i < kLimbs; ++i) {
+      uint64_t mine = 0;
+      if (lane < R) {
+        mine = dg[i];
+        dg[i] = 0;
+      }
+      word[i] = wave_sum_u64(mine);  // every digit word is far below 2^53 (see window_to_digits): no wrap
+    }
+    if (lane != 0) return;
+  }
+  const uint32_t b = static_cast<uint32_t>(t % geo.num_blocks);
+  const uint32_t sp = ws.special[t];
+  ws.special[t] = 0;
+  ws.scales[t] = block_scale(word, sp, static_cast<double>(ws.offsets[b + 1] - ws.offsets[b]));
+}
+
+// Rows whose last workgroup forms the scales: few workgroups to draw a ticket, few blocks for one workgroup.
+constexpr uint32_t kBsScalesChunks = 64, kBsScalesBlocks = 64;
+
+// The scales of a row's blocks by one workgroup, from digits that other workgroups of the same launch have added to (with
+// device-scope atomics): read at that scope, all of them at once, and added up in LDS over the sets of a block.
+__device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, const BlocksignWorkspace& ws) {
+  __shared__ unsigned long long sums[kBsScalesBlocks * kLimbs];
+  const uint32_t t = threadIdx.x, M = geo.num_blocks, R = ws.acc_replicas;
+  const uint32_t words = M * R * kLimbs;  // of 64 bits
+  constexpr uint32_t kMost = (kBsScalesChunks * kLimbs + kWG - 1) / kWG;  // (M sets at least, else one per chunk at most)
+  static_assert(kBsScalesBlocks <= kBsScalesChunks, "M * R <= kBsScalesChunks");
+  uint64_t* dg = ws.acc + static_cast<size_t>(row) * words;
+  const __amdgpu_buffer_rsrc_t view = __builtin_amdgcn_make_buffer_rsrc(dg, 0, words * 8u, 0x00020000);
+  uint64_t mine[kMost];
+#pragma unroll
+  for (uint32_t i = 0; i < kMost; ++i) {  // (reads beyond the view return 0)
+    const uint32_t q = t + kWG * i;
+    const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b32(view, q * 8u, 0, /*device-scope policy*/ 16);
+    const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b32(view, q * 8u + 4u, 0, 16);
+    mine[i] = (static_cast<uint64_t>(hi) << 32) | lo;
+  }
+  uint32_t sp = 0;
+  if (t < M) sp = __hip_atomic_load(ws.special + static_cast<size_t>(row) * M + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (uint32_t q = t; q < M * kLimbs; q += kWG) sums[q] = 0;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kMost; ++i) {
+    const uint32_t q = t + kWG * i;
+    if (q < words) {
+      if (mine[i]) atomicAdd(&sums[q / (R * kLimbs) * kLimbs + q % kLimbs], static_cast<unsigned long long>(mine[i]));
+      dg[q] = 0;  // for the next step (nobody of this launch looks again)
+    }
+  }
+  __syncthreads();
+  if (t < M) {
+    uint64_t word[kLimbs];  // every digit word is far below 2^53 (see window_to_digits): no wrap
+#pragma unroll
+    for (uint32_t d = 0; d < kLimbs; ++d) word[d] = sums[t * kLimbs + d];
+    ws.special[static_cast<size_t>(row) * M + t] = 0;
+    ws.scales[static_cast<size_t>(row) * M + t] = block_scale(word, sp, static_cast<double>(ws.offsets[t + 1] - ws.offsets[t]));
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // First pass for general block layouts as a grid of short workgroups: a workgroup takes ONE chunk and ends,
 // wavefront w takes rounds 4w .. 4w+3 of it (plain streaming kernels of this shape move the same traffic at
@@ -297,9 +415,8 @@ __device__ __noinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0,
 // step is applied to e as it is read.
 // ---------------------------------------------------------------------------------------------
 template <bool PEND>
-__global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
-                                                  BlocksignWorkspace ws) {
-  const uint32_t c = blockIdx.x, row = blockIdx.y;
+__device__ __forceinline__ void bs_lean_chunk(uint32_t c, uint32_t row, const float* __restrict__ g, float* __restrict__ e,
+                                              const Geometry& geo, const BlocksignWorkspace& ws) {
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   float* er = e + static_cast<int64_t>(row) * geo.ld;
@@ -311,7 +428,7 @@ __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, fl
   uint32_t* specr = ws.special + static_cast<size_t>(row) * geo.num_blocks;
   const uint32_t d = geo.d;
   const uint32_t q0 = c * kChunk + wave * (kQuarter * 256);  // first coordinate of this wavefront's quarter
-  if (q0 >= d) return;                                       // wave-uniform; no barrier in this kernel
+  if (q0 >= d) return;                                       // wave-uniform; no barrier in here
   const bool full = (c + 1) * static_cast<uint64_t>(kChunk) <= d;
   BsBatch cur;
   if (full) bs_load_batch_t<true>(cur, gr, er, c, wave * kQuarter, d);
@@ -383,75 +500,26 @@ __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, fl
   window_to_digits(A.sum, A.eh, dg);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Scales: per (row, block) add up the sets of digits (a thread when there is one set, else a wavefront with a
-// lane per set), normalise them, round the sum to double (nearest, ties to even), divide by the block length,
-// round to fp32.  Clears the digits for the next step.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kWG) void k_bs_finalize(Geometry geo, BlocksignWorkspace ws) {
-  const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
-  const uint32_t R = ws.acc_replicas;  // sets of digits per (row, block)
-  size_t t;
-  uint64_t word[kLimbs];
-  if (R == 1) {  // a thread per (row, block)
-    t = static_cast<size_t>(blockIdx.x) * kWG + threadIdx.x;
-    if (t >= total) return;
-    uint64_t* dg = ws.acc + t * kLimbs;
-#pragma unroll
-    for (int i = 0; i < kLimbs; ++i) {
-      word[i] = dg[i];
-      dg[i] = 0;
+// SCALES: the workgroup of a row that finishes last also turns the row's sums into scales.  A short row's few workgroups
+// hardly queue for the ticket, and the launch that this saves is a quarter of a small model's step (4 rows of 65536,
+// blocks of 4096: 13.9 -> 12.6 us a pass); of thousands of workgroups each would wait for its own atomics before it ends.
+template <bool PEND, bool SCALES>
+__global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
+                                                  BlocksignWorkspace ws) {
+  bs_lean_chunk<PEND>(blockIdx.x, blockIdx.y, g, e, geo, ws);
+  if constexpr (SCALES) {
+    __shared__ uint32_t sh_last;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wavefront's atomics have been performed
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t* ticket = ws.ticket + blockIdx.y;
+      const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+      if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+      sh_last = last ? 1u : 0u;
     }
-  } else {  // a wavefront per (row, block): lane r brings replica r, the sums are taken over the wavefront
-    t = static_cast<size_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6);
-    if (t >= total) return;
-    const uint32_t lane = lane_id();
-    uint64_t* dg = ws.acc + (t * R + lane) * kLimbs;
-#pragma unroll
-    for (int i = 0; i < kLimbs; ++i) {
-      uint64_t mine = 0;
-      if (lane < R) {
-        mine = dg[i];
-        dg[i] = 0;
-      }
-      word[i] = wave_sum_u64(mine);  // every digit word is far below 2^53 (see window_to_digits): no wrap
-    }
-    if (lane != 0) return;
+    __syncthreads();
+    if (sh_last) row_scales(blockIdx.y, geo, ws);
   }
-  const uint32_t b = static_cast<uint32_t>(t % geo.num_blocks);
-  uint32_t digit[kLimbs + 1];
-  uint64_t carry = 0;
-#pragma unroll
-  for (int i = 0; i < kLimbs; ++i) {
-    const uint64_t v = word[i] + carry;
-    digit[i] = static_cast<uint32_t>(v);
-    carry = v >> 32;
-  }
-  digit[kLimbs] = static_cast<uint32_t>(carry);
-  const uint32_t sp = ws.special[t];
-  ws.special[t] = 0;
-  const double len = static_cast<double>(ws.offsets[b + 1] - ws.offsets[b]);
-  double sum;
-  if (sp & 2u) sum = __longlong_as_double(0x7ff8000000000000ll);
-  else if (sp & 1u) sum = __longlong_as_double(0x7ff0000000000000ll);
-  else {
-    // the four highest non-zero digits carry every bit a double can hold; the rest is a sticky bit
-    int top = 0;
-#pragma unroll
-    for (int i = 1; i <= kLimbs; ++i)
-      if (digit[i]) top = i;
-    const int low = top >= 3 ? top - 3 : 0;
-    uint32_t q[4] = {0, 0, 0, 0};
-    bool below = false;
-#pragma unroll
-    for (int i = 0; i <= kLimbs; ++i) {
-      if (i >= low && i < low + 4) q[i - low] = digit[i];
-      else if (i < low && digit[i]) below = true;
-    }
-    const uint64_t w0 = (static_cast<uint64_t>(q[1]) << 32) | q[0], w1 = (static_cast<uint64_t>(q[3]) << 32) | q[2];
-    sum = fixed192_to_double(w0, w1, 0, 32 * low - 149, below);
-  }
-  ws.scales[t] = static_cast<float>(sum / len);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -836,14 +904,18 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
                           float* e, float* theta, float* m, float* v, float* vhat, bool residual_pending,
                           bool workers_only, hipStream_t stream, Launcher* L) {
   const dim3 grid_chunks(geo.num_chunks, geo.n), wg(kWG);
-  if (residual_pending) launch(L, kSlotBsPass1, k_bs_lean<true>, grid_chunks, wg, stream, g, e, geo, ws);
-  else launch(L, kSlotBsPass1, k_bs_lean<false>, grid_chunks, wg, stream, g, e, geo, ws);
+  const bool scales = geo.num_chunks <= kBsScalesChunks && geo.num_blocks <= kBsScalesBlocks;
+  auto* first = residual_pending ? (scales ? k_bs_lean<true, true> : k_bs_lean<true, false>)
+                                 : (scales ? k_bs_lean<false, true> : k_bs_lean<false, false>);
+  launch(L, kSlotBsPass1, first, grid_chunks, wg, stream, g, e, geo, ws);
   COMPAMS_CHECK_LAUNCH();
-  const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
-  const size_t per_group = ws.acc_replicas == 1 ? kWG : kWaves;  // (row, block) pairs per workgroup
-  launch(L, kSlotBsFinal, k_bs_finalize, dim3(static_cast<uint32_t>((total + per_group - 1) / per_group)), wg, stream,
-         geo, ws);
-  COMPAMS_CHECK_LAUNCH();
+  if (!scales) {
+    const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
+    const size_t per_group = ws.acc_replicas == 1 ? kWG : kWaves;  // (row, block) pairs per workgroup
+    launch(L, kSlotBsFinal, k_bs_finalize, dim3(static_cast<uint32_t>((total + per_group - 1) / per_group)), wg, stream,
+           geo, ws);
+    COMPAMS_CHECK_LAUNCH();
+  }
   // The residual e = x - sign(x) * mu is left to the next step's first pass (or to blocksign_apply_residual when
   // e is asked for).
   if (workers_only) return hipSuccess;

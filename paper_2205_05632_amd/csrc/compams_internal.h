@@ -236,6 +236,7 @@ struct BlocksignWorkspace {
                         // the sum of a (row, block) is the sum of its replicas
   uint32_t acc_replicas;
   uint32_t* special;    // n * M : bit 0 = an infinity was seen, bit 1 = a NaN was seen
+  uint32_t* ticket;     // n : "last workgroup of the row" counters of the first pass; zero between launches
   float* scales;        // n * M
   uint32_t* bits;       // n * words
 };

@@ -722,3 +722,22 @@ def test_every_count_of_cached_state_arrays_gives_the_same_bytes(case, cached):
     run_pair(p, gs, label=f"{case}, {cached} cached")
     assert all(p.exact[s] for s in ("theta", "m", "v", "vhat"))
     p.close()
+
+
+@pytest.mark.parametrize("n,d,blocks", [(3, 64 * 4096, 64), (2, 64 * 4096 + 4, 64), (2, 64 * 4096, 65), (5, 9001, 1), (1, 37, 37),
+                                        (33, 4096, 3), (2, 250_001, 2)])
+def test_blocksign_scales_of_short_rows(n, d, blocks):
+    """Up to 64 chunks and 64 blocks the row's last workgroup forms the scales, beyond either a launch of its own: the
+    same sums, cleared for the next step, with entries that miss the register windows and a block that is not finite."""
+    rng = np.random.default_rng(d + blocks)
+    cuts = np.sort(rng.choice(np.arange(1, d), size=blocks - 1, replace=False))
+    off = np.concatenate([[0], cuts, [d]]).astype(np.int64)
+    p = Pair(n, d, rng.standard_normal(d), B.BLOCKSIGN, block_offsets=off)
+    for t in range(4):
+        g = (rng.standard_normal((n, d)) * 2.0 ** rng.integers(-40, 3, size=(n, d))).astype(np.float32)
+        if t == 2 and blocks > 2:
+            g[0, off[1]] = np.inf
+        with np.errstate(all="ignore"):
+            p.step(g, 1e-3, label=f"short row {d} x {blocks} step {t}", with_e=t == 3)
+    assert all(p.exact.values()), p.exact
+    p.close()
