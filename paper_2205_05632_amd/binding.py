@@ -104,6 +104,17 @@ def _current_stream_handle() -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
+def _on_stream(device: torch.device, call, *args) -> int:
+    """call(*args, handle of `device`'s current stream) with `device` current.  A step of a small model takes about
+    10 us: the device is switched only if another one is current, and the stream's handle is asked for without the
+    Python object around it (4 us less than a torch.cuda.device block and torch.cuda.current_stream())."""
+    index = device.index
+    if index is None or index == torch._C._cuda_getDevice():
+        return call(*args, torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    with torch.cuda.device(device):
+        return call(*args, _current_stream_handle())
+
+
 def padded_ld(d: int) -> int:
     """Row stride the binding picks by default.  Any multiple of 4 elements >= d is legal (16-byte aligned
     rows); rows that start on a 4 KiB boundary stream measurably faster (whole cache lines and DRAM bursts
@@ -190,8 +201,7 @@ class Compams:
         """g: n x ld fp32 tensor on the context's device (columns >= d ignored)."""
         assert g.dtype == torch.float32 and g.is_cuda and g.is_contiguous()
         assert g.shape == (self.n, self.ld), f"g must be {self.n} x {self.ld}, got {tuple(g.shape)}"
-        with torch.cuda.device(self.device):
-            _check(lib().compams_step(self._h, g.data_ptr(), lr, _current_stream_handle()), "compams_step")
+        _check(_on_stream(self.device, lib().compams_step, self._h, g.data_ptr(), lr), "compams_step")
 
     def compams_state(self, name: str):
         """A torch view (no copy) of a state tensor or of the last step's messages ("pending": a bool)."""
@@ -224,9 +234,8 @@ class Compams:
         stride = self.compams_wire_capacity() if stride_words is None else int(stride_words)
         messages = torch.empty((self.n, stride), dtype=torch.int32, device=self.device)
         words = torch.empty(self.n, dtype=torch.int32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(lib().compams_encode(self._h, messages.data_ptr(), stride, words.data_ptr(),
-                                        _current_stream_handle()), "compams_encode")
+        _check(_on_stream(self.device, lib().compams_encode, self._h, messages.data_ptr(), stride, words.data_ptr()),
+               "compams_encode")
         return messages, words
 
     def compams_decode(self, messages: torch.Tensor, words=None):
@@ -241,10 +250,9 @@ class Compams:
             a = torch.empty((self.n, (self.d + 31) // 32), dtype=torch.int32, device=self.device)
             b = torch.empty((self.n, self.M), dtype=torch.float32, device=self.device)
         status = torch.empty(self.n, dtype=torch.int32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(lib().compams_decode(self._h, messages.data_ptr(), messages.shape[1],
-                                        None if words is None else words.data_ptr(), a.data_ptr(), b.data_ptr(),
-                                        status.data_ptr(), _current_stream_handle()), "compams_decode")
+        _check(_on_stream(self.device, lib().compams_decode, self._h, messages.data_ptr(), messages.shape[1],
+                          None if words is None else words.data_ptr(), a.data_ptr(), b.data_ptr(), status.data_ptr()),
+               "compams_decode")
         return a, b, status
 
     # -- the two halves of a step ----------------------------------------------------------------
@@ -252,18 +260,15 @@ class Compams:
         """The workers' lines only: compresses, updates e, leaves the messages for compams_encode."""
         assert g.dtype == torch.float32 and g.is_cuda and g.is_contiguous()
         assert g.shape == (self.n, self.ld), f"g must be {self.n} x {self.ld}, got {tuple(g.shape)}"
-        with torch.cuda.device(self.device):
-            _check(lib().compams_worker_step(self._h, g.data_ptr(), _current_stream_handle()), "compams_worker_step")
+        _check(_on_stream(self.device, lib().compams_worker_step, self._h, g.data_ptr()), "compams_worker_step")
 
     def compams_server_step(self, messages: torch.Tensor, words, lr: float) -> torch.Tensor:
         """The server's lines from n packed messages; returns the per-message status words."""
         assert messages.dtype == torch.int32 and messages.is_cuda and messages.is_contiguous()
         assert messages.shape[0] == self.n
         status = torch.empty(self.n, dtype=torch.int32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(lib().compams_server_step(self._h, messages.data_ptr(), messages.shape[1],
-                                             None if words is None else words.data_ptr(), lr, status.data_ptr(),
-                                             _current_stream_handle()), "compams_server_step")
+        _check(_on_stream(self.device, lib().compams_server_step, self._h, messages.data_ptr(), messages.shape[1],
+                          None if words is None else words.data_ptr(), lr, status.data_ptr()), "compams_server_step")
         return status
 
     # -- extras ----------------------------------------------------------------------------------
@@ -328,10 +333,8 @@ def compams_step_static(n: int, d: int, k: int, theta, m, v, vhat, e, g, lr: flo
     cfg.flags = KEEP_STATE if keep_state else 0
     cfg.theta, cfg.m, cfg.v, cfg.vhat, cfg.e = theta.data_ptr(), m.data_ptr(), v.data_ptr(), vhat.data_ptr(), e.data_ptr()
     assert g.stride(0) == e.stride(0) and g.is_cuda and g.dtype == torch.float32
-    with torch.cuda.device(e.device):
-        return lib().compams_step_static(ctypes.byref(cfg), g.data_ptr(), lr,
-                                         None if idx_out is None else idx_out.data_ptr(),
-                                         None if val_out is None else val_out.data_ptr(), _current_stream_handle())
+    return _on_stream(e.device, lib().compams_step_static, ctypes.byref(cfg), g.data_ptr(), lr,
+                      None if idx_out is None else idx_out.data_ptr(), None if val_out is None else val_out.data_ptr())
 
 
 def compams_cached_state_arrays(d: int) -> int:
