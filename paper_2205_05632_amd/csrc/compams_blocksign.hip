@@ -523,62 +523,47 @@ __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, fl
 }
 
 // ---------------------------------------------------------------------------------------------
-// The residual  e = x - sign(x) * mu  on its own (and the sign words once more): when the caller asks for e
-// while the update is still pending.  One wavefront per chunk.  Eight lanes (32 coordinates) share one word
-// of the bit map.
+// The residual  e = x - sign(x) * mu  on its own: when the caller asks for e while the update is still pending.  A grid
+// of short workgroups as the first pass (HBM-bound: 8 bytes per worker-coordinate; workgroups that walked many chunks,
+// and wrote the sign words once more: 16 x 11.2 M coordinates took 276 us, this 232).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWG) void k_bs_pass2(float* __restrict__ e, Geometry geo, BlocksignWorkspace ws) {
-  const uint32_t row = blockIdx.y;
+  const uint32_t c = blockIdx.x, row = blockIdx.y;
+  const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   float* er = e + static_cast<int64_t>(row) * geo.ld;
   const uint32_t* __restrict__ off = ws.offsets;
   const float* __restrict__ mur = ws.scales + static_cast<size_t>(row) * geo.num_blocks;
-  uint32_t* bitr = ws.bits + static_cast<size_t>(row) * geo.words;
-  const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
-  const uint32_t stride = gridDim.x * kWaves;
   const uint32_t d = geo.d;
-  for (uint32_t c = blockIdx.x * kWaves + wave; c < geo.num_chunks; c += stride) {
-    uint32_t b = ws.chunk_block[c];
-#pragma unroll 1
-    for (int r0 = 0; r0 < kRounds; r0 += kBsBatch) {
-      if (c * kChunk + r0 * 256 >= d) break;  // wave-uniform
-      float4 xb[kBsBatch];
+  const uint32_t q0 = c * kChunk + wave * (kQuarter * 256);  // first coordinate of this wavefront's quarter
+  if (q0 >= d) return;                                       // wave-uniform; no barrier in this kernel
+  float4 xb[kQuarter];
 #pragma unroll
-      for (int u = 0; u < kBsBatch; ++u) {
-        const uint32_t j = c * kChunk + (r0 + u) * 256 + lane * 4;
-        xb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (j < d) xb[u] = load_stream4(er + j);
-      }
+  for (int u = 0; u < kQuarter; ++u) {
+    const uint32_t j = q0 + u * 256 + lane * 4;
+    xb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < d) xb[u] = load_stream4(er + j);
+  }
+  uint32_t b = table_u32(ws.chunk_block, c);
 #pragma unroll
-      for (int u = 0; u < kBsBatch; ++u) {
-        const uint32_t j0 = c * kChunk + (r0 + u) * 256;
-        if (j0 >= d) break;
-        const uint32_t j = j0 + lane * 4;
-        const bool in = j < d;
-        const bool ok[4] = {in, j + 1 < d, j + 2 < d, j + 3 < d};
-        while (off[b + 1] <= j0) ++b;
-        const uint32_t j_end = (j0 + 256 < d) ? j0 + 256 : d;
-        float mu[4];
-        if (off[b + 1] >= j_end) {
-          const float m0 = mur[b];
-          mu[0] = mu[1] = mu[2] = mu[3] = m0;
-        } else {
+  for (int u = 0; u < kQuarter; ++u) {
+    const uint32_t j0 = q0 + u * 256;
+    if (j0 >= d) break;  // wave-uniform
+    const uint32_t j = j0 + lane * 4;
+    const bool ok[4] = {j < d, j + 1 < d, j + 2 < d, j + 3 < d};
+    while (table_u32(off, b + 1) <= j0) ++b;  // block of the round's first coordinate
+    const uint32_t j_end = j0 + 256 < d ? j0 + 256 : d;
+    float mu[4];
+    if (table_u32(off, b + 1) >= j_end) {
+      mu[0] = mu[1] = mu[2] = mu[3] = table_f32(mur, b);
+    } else {
 #pragma unroll
-          for (int s = 0; s < 4; ++s) mu[s] = ok[s] ? mur[block_of(off, b, j + s)] : 0.0f;
-        }
-        float xv[4] = {xb[u].x, xb[u].y, xb[u].z, xb[u].w};
-        uint32_t nib = 0;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const bool neg = ok[s] && xv[s] < 0.0f;
-          nib |= (neg ? 1u : 0u) << s;
-          if (ok[s]) xv[s] = xv[s] - (neg ? -mu[s] : mu[s]);
-        }
-        if (in) store_stream4(er + j, make_float4(xv[0], xv[1], xv[2], xv[3]));
-        const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
-        const uint32_t widx = (j0 >> 5) + (lane >> 3);
-        if ((lane & 7u) == 0 && widx < geo.words) bitr[widx] = word;
-      }
+      for (int s = 0; s < 4; ++s) mu[s] = ok[s] ? mur[block_of(off, b, j + s)] : 0.0f;
     }
+    float xv[4] = {xb[u].x, xb[u].y, xb[u].z, xb[u].w};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (ok[s]) xv[s] = xv[s] - (xv[s] < 0.0f ? -mu[s] : mu[s]);
+    if (ok[0]) store_stream4(er + j, make_float4(xv[0], xv[1], xv[2], xv[3]));
   }
 }
 
@@ -935,8 +920,7 @@ hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& 
 }
 
 hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspace& ws, float* e, hipStream_t stream) {
-  const uint32_t G = groups_per_row(geo.n, geo.num_chunks);
-  hipLaunchKernelGGL(k_bs_pass2, dim3(G * 2, geo.n), dim3(kWG), 0, stream, e, geo, ws);
+  hipLaunchKernelGGL(k_bs_pass2, dim3(geo.num_chunks, geo.n), dim3(kWG), 0, stream, e, geo, ws);
   return hipGetLastError();
 }
 
