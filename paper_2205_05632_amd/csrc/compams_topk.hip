@@ -18,6 +18,8 @@
 //                  entries kept for certain, their prefixes inside blocks of chunks and the block totals; the
 //                  few entries of the threshold's bucket are ranked by the last workgroup of the row, which
 //                  gives tau, the ties to keep (by coordinate) and the next step's guess and band.
+//   pick           rows of at most 16 chunks: the whole selection by one workgroup per row, in place of the band kernel
+//                  and the general ones.
 //   The general route (12 + 10 + 9 key bits and a zero sign bit), for every other row:
 //   level 0        histogram of the 12-bit threshold buckets, from the candidate list when the guess held (the
 //                  list then holds at least k entries), else from the row itself; for a listed row also the
@@ -37,6 +39,8 @@
 // With top-k inside every block (one selection problem per worker and block) the same launches go over all
 // problems at once through tables of workgroup slots; problems of at most 1024 coordinates are solved by one
 // wavefront inside the first pass.
+// A step without a state of its own (the step whose tables lie in a static array) has no guess to carry over: a kernel
+// before the first pass takes one from a sample of every row.
 // Zeroing the residual at the selected coordinates is not done by scattered stores: the next step's
 // first pass treats the coordinates in the previous lists as zero while it forms x (and a small kernel
 // applies the zeros when the caller asks for e).
@@ -836,8 +840,9 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
 // arithmetic.  Training thresholds drift smoothly while the residuals build up (+34 %, +17 %, +10 %, +7.5 % ... over
 // the first steps of the ResNet-18-shaped workload, +2 % at step ten): with d1 the last relative change and d0 the
 // one before, a drift that is dying down (same sign, |d1| < |d0|) is taken to go on doing so, next = d1 * d1 / d0
-// (not below d1 / 4), and to be off by at most half of what that took away from d1; any other pair of changes is
-// extrapolated flat, next = d1, unsure by 0.4 |d1| + |d1 - d0|.  The centre is tau (1 + next), the half-width
+// (not below d1 / 4), and to be off by at most half of what that took away from d1; changes of opposite signs are
+// scatter about a level, next = 0, unsure by 0.7 of the larger one; a drift that grows is extrapolated flat, next = d1,
+// unsure by 0.4 |d1| + |d1 - d0|.  The centre is tau (1 + next), the half-width
 // 0.4 % + unsure + `noise`, an allowance for the scatter of the k-th largest of a sample from step to step.  With B entries found in a window
 // of relative width w around the threshold, one entry more or fewer above a level moves the k-th largest key by
 // w / B of its value and the count above a level scatters by about sqrt(k): k_topk_band passes 8 w sqrt(k) / B
@@ -871,6 +876,9 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
       if (d0 * d1 > 0.0f && fabsf(d1) < fabsf(d0)) {  // a drift that is dying down: let it go on doing so
         next = d1 * fmaxf(d1 / d0, 0.25f);
         unsure = 0.5f * fabsf(d1 - next);
+      } else if (d0 * d1 <= 0.0f) {  // scatter about a level that stands still
+        next = 0.0f;
+        unsure = 0.7f * fmaxf(fabsf(d1), fabsf(d0));
       } else {
         unsure += fabsf(d1 - d0);
       }
