@@ -51,7 +51,7 @@ enum {
   COMPAMS_BLOCKSIGN = 2, /* Definition 2: per block, sign(x) times the block's mean absolute value */
   COMPAMS_TOPK_BLOCKS = 3 /* Definition 1 applied to every block on its own: block b keeps its block_k[b] coordinates
                              of largest magnitude per worker (the usual per-layer top-k).  Block offsets must be
-                             multiples of 4.  Workspace grows with n * num_blocks (about 35 KB each): meant for
+                             multiples of 4.  Workspace grows with n * num_blocks (40 KB each and more): meant for
                              layer-sized blocks */
 };
 

@@ -76,14 +76,18 @@ enum : uint32_t {
 };
 
 // The band: a window of magnitude keys [band_lo, band_hi) in which the next step's threshold key is expected,
-// set from the last two thresholds, cut into band_buckets(k) buckets of equal width (band_bucket below).  The first pass
+// set from the last two thresholds, cut into 2048 or 8192 buckets of equal width (band_bucket below).  The first pass
 // counts, per chunk, the entries at or above band_hi, copies the entries inside the window to a short list of their own (a
 // segment per chunk) and adds them to the row's bucket histogram.  If the threshold does fall inside (checked
 // exactly), one launch finishes the selection from the short list alone (k_topk_band).
 // A window holds up to about k entries, and a bucket may hold kBoundaryCap at most: 70 000 to 240 000 entries (k =
 // 110 000 to 260 000, hundreds of steps into a run) fill 2048 buckets with 35 to 120 each, and one row in five went
-// to the general kernels for that alone; 8192 buckets cost their workgroups nothing measurable.
+// to the general kernels for that alone.  A window expected to hold no more than 16 entries to each of 2048 buckets
+// keeps those: every workgroup of the band kernel reads the histogram (16 x 11.2 M coordinates, k = 111 816, windows of
+// 14 000 entries: 15.7 us with 2048 buckets, 21.2 with 8192).
 constexpr uint32_t kBandBucketsFew = 2048, kBandBucketsMany = 8192;
+enum : uint32_t { kBandFew = 1, kBandMany = 2 };  // TopkRow::band_valid
+// Room for so many is kept per problem.
 __host__ __device__ __forceinline__ uint32_t band_buckets(uint32_t k) { return k < 16384 ? kBandBucketsFew : kBandBucketsMany; }
 constexpr uint32_t kBandMaxEntries = 1u << 20;  // capacity of a band list at most
 constexpr uint32_t kBoundaryCap = 64;      // entries in the bucket that holds the threshold key; more: general route
@@ -102,7 +106,7 @@ struct TopkRow {
   uint32_t b_guess;     // a level-0 bucket at or below that key's
   uint32_t cursor;      // candidate entries allocated so far in this step (a list kept as one run) ...
   uint32_t cursor_band; // ... and band entries: the two are advanced together as one 64-bit word
-  uint32_t band_valid;  // the next first pass may also fill the band list and the bucket histogram
+  uint32_t band_valid;  // kBandFew / kBandMany: the next first pass may also fill the band list and the bucket histogram
   uint32_t band_lo, band_hi;  // keys; band_lo >= b_guess << kL0Shift, band_hi > band_lo
   uint32_t band_mul;    // bucket of a key inside the band: see band_bucket()
   // (read together by the last kernel, up to tie_last)
@@ -138,6 +142,18 @@ __device__ __forceinline__ uint32_t band_multiplier_dev(uint32_t span, uint32_t 
   return span > buckets ? static_cast<uint32_t>((static_cast<uint64_t>(buckets) << 32) / span) : 0u;
 }
 __device__ __forceinline__ uint32_t band_bucket(uint32_t rel, uint32_t mul) { return mul ? __umulhi(rel, mul) : rel; }
+// Where its count lies: of the many buckets a thread of the band kernel takes 32 consecutive ones, kept in four
+// groups of 8 with a quarter of the table between them, so that its first 8 are found before it is known how many
+// there are.  The few lie in one quarter, which differs from problem to problem: always the first, 32 KB apart, they
+// would meet on a quarter of the memory channels (first pass of the ResNet-18 shape 350.6 us, in different quarters 339.2).
+__device__ __forceinline__ uint32_t band_rotation(uint32_t k, uint32_t problem) {
+  return band_buckets(k) == kBandBucketsMany ? problem & 3u : 0u;
+}
+__device__ __forceinline__ uint32_t band_slot(uint32_t bucket, bool many, uint32_t rotation) {
+  return many ? ((((bucket >> 3) + rotation) & 3u) << 11) | ((bucket >> 5) << 3) | (bucket & 7u)
+              : rotation * kBandBucketsFew + bucket;
+}
+static_assert(kBandBucketsFew == 256 * 8 && kBandBucketsMany == 4 * kBandBucketsFew, "slots above");
 
 // One selection problem: a worker's whole row (top-k over the flattened gradient) or one block of a worker's
 // row (top-k inside every block).  Index fields count entries of the respective workspace tables.

@@ -660,6 +660,8 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   const uint32_t blo = banded ? rw[5] : 0xffffffffu;
   const uint32_t bhi = banded ? rw[6] : 0xffffffffu;
   const uint32_t bmul = banded ? rw[7] : 0u;
+  const bool bmany = rw[4] == kBandMany;
+  const uint32_t brot = band_rotation(geo.k, sc.seg);
   // Candidates: every key at or above cand_lo - the guessed bucket's first key, or, with a band, a key somewhat below
   // the band's first one: the threshold is expected inside the band, so that little below it is needed (a list of at
   // least k entries that holds every key from some key upwards holds the k largest, wherever that key lies inside a
@@ -787,7 +789,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
         const uint64_t bb = ballot64(inb);
         if (inb) {
           bdst[bat + count_below(bb)] = en;
-          atomicAdd(&bh[band_bucket(key - blo, bmul)], 1u);  // the row's bucket histogram; nobody waits for it
+          atomicAdd(&bh[band_slot(band_bucket(key - blo, bmul), bmany, brot)], 1u);  // the row's bucket histogram; nobody waits for it
         }
         bat += popc64(bb);
       }
@@ -824,7 +826,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
           if (inb[s]) {
             if (bpos < band_w) {
               bdst[bpos] = make_uint2(j + s, bits[s]);
-              atomicAdd(&bh[band_bucket(key_of_bits(bits[s]) - blo, bmul)], 1u);
+              atomicAdd(&bh[band_slot(band_bucket(key_of_bits(bits[s]) - blo, bmul), bmany, brot)], 1u);
             }
             ++bpos;
           }
@@ -866,6 +868,7 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
                                               const TopkOptions& opt) {
   uint32_t valid = 0, lo = 0, hi = 0;
   uint32_t from = guess << kL0Shift;  // the first key that the next first pass lists
+  float delta_set = 0.0f;
   if (guess_valid && opt.band && opt.band_cap && normal_key(tau)) {
     const float t1 = __uint_as_float(tau);
     float d1 = 0.0f;  // the last relative change of the threshold
@@ -884,6 +887,7 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
       }
     }
     const float delta = fminf(0.004f + unsure + fminf(fmaxf(noise, 0.0005f), 0.25f), 0.25f);
+    delta_set = delta;
     const float centre = t1 * (1.0f + next);
     const float flo = centre * (1.0f - delta), fhi = centre * (1.0f + delta);
     lo = __float_as_uint(flo);
@@ -895,10 +899,14 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
     if (valid && margin > from) from = margin;
   }
   rowp->cand_from = guess_valid ? from + 1u : 0u;
-  rowp->band_valid = valid;
+  // Buckets of the window's histogram: the population of the last window (noise is 8 w sqrt(k) / B) says how many
+  // entries this one will hold; beyond 16 to a bucket of the few it gets the many.
+  const bool many = band_buckets(k) == kBandBucketsMany &&
+                    16.0f * delta_set * sqrtf(static_cast<float>(k)) > 16.0f * kBandBucketsFew * noise;
+  rowp->band_valid = valid ? (many ? kBandMany : kBandFew) : 0u;
   rowp->band_lo = lo;
   rowp->band_hi = hi;
-  rowp->band_mul = valid ? band_multiplier_dev(hi - lo, band_buckets(k)) : 0u;
+  rowp->band_mul = valid ? band_multiplier_dev(hi - lo, many ? kBandBucketsMany : kBandBucketsFew) : 0u;
 }
 
 // The runs of a problem's band list, from the high halves of the cursors the first pass advanced.
@@ -932,7 +940,7 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
 // ---------------------------------------------------------------------------------------------
 // The selection in one launch, for problems whose threshold key falls inside the band the first pass was given.
 // Same geometry as the counting kernel: a workgroup owns a contiguous block of geo.count_cpw chunks.
-//   1. Every workgroup of a problem reads the problem's bucket histogram of band entries (band_buckets(k) counts,
+//   1. Every workgroup of a problem reads the problem's bucket histogram of band entries (2048 or 8192 counts,
 //      added up by the first pass) and the count A of entries at or above the band, and finds by itself the
 //      bucket that holds the k-th largest key: it exists iff A < k <= A + (entries in the band); both lists must
 //      have fitted and the bucket must hold at most kBoundaryCap entries.  Otherwise the problem is left to the
@@ -963,7 +971,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   if (start >= nc) return;  // uniform; the grid has exactly the blocks that exist
   const uint32_t end = start + cpw < nc ? start + cpw : nc;
   TopkRow* rowp = ws.rows + row;
-  const uint32_t buckets = band_buckets(k);
   uint32_t* bh = ws.bhist + sc.bhist_base;
   const uint32_t wave = uniform_u32(t >> 6), lane = lane_id();
   constexpr int kGroup = 8;  // chunks a wavefront takes at a time: descriptors with one load, entries together
@@ -975,13 +982,15 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   const uint32_t c_first = start + wave * group;
   uint2 ds = make_uint2(0, 0);
   if (opt.band && lane < group && c_first + lane < end) ds = d2[c_first + lane];  // (no such table without a band)
-  // (thread t's buckets are consecutive: 8 or 32 of them, four to a load)
-  uint4 x[kBandBucketsMany / kWG / 4];
-  const uint32_t per_quads = buckets / kWG / 4;  // uniform
-  const uint4* bh4 = reinterpret_cast<const uint4*>(bh) + t * per_quads;
+  // (thread t's buckets are consecutive: 8 of the few, 32 of the many, of which the first 8 lie where the few do and the
+  // others are asked for below, with the band entries)
+  constexpr uint32_t kQuadsFew = kBandBucketsFew / kWG / 4, kQuadsMany = kBandBucketsMany / kWG / 4;
+  uint4 x[kQuadsMany];
+  const uint32_t rot = band_rotation(k, row);
+  const uint4* bh4 = reinterpret_cast<const uint4*>(bh) + t * kQuadsFew;
 #pragma unroll
-  for (uint32_t i = 0; i < kBandBucketsMany / kWG / 4; ++i)
-    x[i] = i < per_quads ? bh4[i] : make_uint4(0, 0, 0, 0);
+  for (uint32_t i = 0; i < kQuadsMany; ++i)
+    x[i] = i < kQuadsFew ? bh4[rot * (kBandBucketsFew / 4) + i] : make_uint4(0, 0, 0, 0);
   uint32_t total_above = rowp->above;
   if (sc.cursor_set != kNoCursorSet) {
     total_above = 0;
@@ -996,6 +1005,10 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   const ListRuns band = band_runs_from_cursors(ws, rowp, sc.cursor_set, opt.band_cap);
   // all of it was written by earlier launches: the same for every workgroup of the problem
   const bool banded = use_guess && opt.band && !opt.force_dense && rowp->cand_from != 0 && rowp->band_valid != 0;
+  const bool many = rowp->band_valid == kBandMany;
+  const uint32_t buckets = many ? kBandBucketsMany : kBandBucketsFew;
+  uint32_t* bh_used = many ? bh : bh + rot * kBandBucketsFew;
+  const uint32_t per_quads = many ? kQuadsMany : kQuadsFew;  // uniform
   // What the window's population says of the threshold's scatter, also where this route is not taken.
   float noise = 0.0f;
   if (banded && bhi > blo && band.total)
@@ -1006,7 +1019,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     // problem's histogram and counters; nobody of this launch makes use of them.
     if (sc.group == 0) {
       if (banded)
-        for (uint32_t b = t; b < buckets; b += kWG) bh[b] = 0;
+        for (uint32_t b = t; b < buckets; b += kWG) bh_used[b] = 0;
       if (t == 0) {
         rowp->fast = kFastNot;
         rowp->noise = noise;
@@ -1037,6 +1050,10 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       a[u] = lane < cnt[u] ? bandr[off[u] + lane] : make_uint2(0, 0);
     }
   };
+  if (many) {  // uniform
+#pragma unroll
+    for (uint32_t i = kQuadsFew; i < kQuadsMany; ++i) x[i] = bh4[((i / kQuadsFew + rot) & 3u) * (kBandBucketsFew / 4) + i % kQuadsFew];
+  }
   request(ds);
   // ---- 1. the bucket of the threshold key: the thread whose buckets the count from the top crosses finds it ----
   bool inside = total_above < k && k - total_above <= band.total;  // uniform
@@ -1046,7 +1063,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     const uint32_t want = k - total_above;
     uint32_t mine = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kBandBucketsMany / kWG / 4; ++i) mine += x[i].x + x[i].y + x[i].z + x[i].w;
+    for (uint32_t i = 0; i < kQuadsMany; ++i) mine += x[i].x + x[i].y + x[i].z + x[i].w;
     uint32_t from_here = mine;  // entries in this thread's buckets and those of the threads above it
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -1074,8 +1091,9 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         }
       };
 #pragma unroll
-      for (int i = static_cast<int>(kBandBucketsMany / kWG / 4) - 1; i >= 0; --i) {
-        const uint32_t first = (t * per_quads + i) * 4;  // (quads beyond the thread's share are empty and never cross)
+      for (int i = static_cast<int>(kQuadsMany) - 1; i >= 0; --i) {
+        if (i >= static_cast<int>(kQuadsFew) && !many) continue;  // uniform
+        const uint32_t first = (t * per_quads + i) * 4;
         look(x[i].w, first + 3);
         look(x[i].z, first + 2);
         look(x[i].y, first + 1);
@@ -1146,7 +1164,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   }
   // ---- 3. the problem-wide part, by whichever of its workgroups finishes last ----
   if (!last_group_of_row(&rowp->ticket_band, sc.groups, &sh_flag)) return;
-  for (uint32_t b = t; b < buckets; b += kWG) bh[b] = 0;  // every workgroup has read it
+  for (uint32_t b = t; b < buckets; b += kWG) bh_used[b] = 0;  // every workgroup has read it
   uint32_t n_kept = 0;
   if (inside) {
     // the gathered entries (written by other workgroups with device-scope stores: read at that scope)

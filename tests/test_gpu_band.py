@@ -192,3 +192,24 @@ def test_worker_half_takes_the_band_route_too():
     assert np.array_equal(np.ascontiguousarray(w.compams_state("e").cpu().numpy()).view(np.uint32),
                           cpu.get("e").view(np.uint32))
     w.close(); cpu.close()
+
+
+@pytest.mark.parametrize("n,d,k", [(2, 1000001, 100000), (1, 63 * 4096 + 4, 90000)])
+def test_windows_of_many_and_of_few_buckets(n, d, k):
+    """The window's histogram has 8192 buckets where it is expected to hold more than 32768 entries (thresholds that
+    scatter), else 2048 (thresholds that settle): both, and the changes from one to the other, on a row of eight runs
+    and on one of a single run whose last chunk is hardly filled."""
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d, np.float32), B.TOPK, k=k)
+    used = []
+    for t in range(40):
+        scale = rng.uniform(0.92, 1.08) if t < 20 else 1.0 if t < 32 else rng.uniform(0.9, 1.1)
+        g = (rng.standard_normal((n, d)) * scale).astype(np.float32)
+        p.step(g, 1e-3, label=f"step {t}", with_e=(t % 10 == 9))
+        used.append(band_counter(p))
+    used = np.array(used)
+    assert (used[29:32] > 0).all() and (used[29:32] < 32768).all(), used
+    if d > 500000:
+        assert (used > 32768).any(), used
+    assert all(p.exact.values()), p.exact
+    p.close()
