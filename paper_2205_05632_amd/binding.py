@@ -107,7 +107,11 @@ def _current_stream_handle() -> int:
 def _on_stream(device: torch.device, call, *args) -> int:
     """call(*args, handle of `device`'s current stream) with `device` current.  A step of a small model takes about
     10 us: the device is switched only if another one is current, and the stream's handle is asked for without the
-    Python object around it (4 us less than a torch.cuda.device block and torch.cuda.current_stream())."""
+    Python object around it (4 us less than a torch.cuda.device block and torch.cuda.current_stream()).  Another
+    device than a GPU is refused as that block refuses it: its index is None too, and the call would be handed pointers
+    into host memory."""
+    if device.type != "cuda":
+        raise ValueError(f"Expected a cuda device, but got: {device}")
     index = device.index
     if index is None or index == torch._C._cuda_getDevice():
         return call(*args, torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))

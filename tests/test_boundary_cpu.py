@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2205_05632_amd import binding as B
 from paper_2205_05632_amd import workloads as W
@@ -191,3 +192,43 @@ def test_gradients_are_a_pure_function_of_seed_and_step():
     zero_rows = (rows == 0).all(dim=2)
     assert zero_rows.any() and not zero_rows.all()
     assert not np.signbit(g.numpy()[g.numpy() == 0]).any()      # dropped rows are +0.0
+
+
+class _Tensor:
+    """Just what compams_step_static asks of a tensor, on any device."""
+    dtype, is_cuda = torch.float32, True
+
+    def __init__(self, device):
+        self.device = torch.device(device)
+
+    def data_ptr(self):
+        return 4096
+
+    def stride(self, dim):
+        return 64
+
+
+@pytest.mark.parametrize("device", ["cpu", "meta"])
+def test_residual_outside_a_gpu_is_refused_before_the_call(monkeypatch, device):
+    """The pointers of such a tensor would reach the kernels: nothing on the C side can tell them from device ones."""
+    called = []
+
+    class Library:
+        @staticmethod
+        def compams_step_static(*args):
+            called.append(args)
+            return 0
+
+    monkeypatch.setattr(B, "lib", lambda: Library)
+    gpu = _Tensor("cuda:0")
+    with pytest.raises(ValueError, match="Expected a cuda device"):
+        B.compams_step_static(1, 60, 3, gpu, gpu, gpu, gpu, _Tensor(device), gpu, 1e-3)
+    with pytest.raises(ValueError, match="Expected a cuda device"):
+        B._on_stream(torch.device(device), lambda *a: called.append(a) or 0, 1, 2)
+    assert not called
+
+
+def test_stream_handle_functions_exist():
+    """The step calls ask torch for the current device and stream without the Python objects around them."""
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        assert callable(getattr(torch._C, name)), name

@@ -91,3 +91,12 @@ def test_messages_packed_on_another_stream_than_the_step():
         want = O.wire_encode_topk(cpu.get("idx")[i], cpu.get("val")[i])
         assert wn[i] == want.size and np.array_equal(m[i, : wn[i]], want), f"message of worker {i}"
     gpu.close(); cpu.close()
+
+
+def test_calls_get_the_handle_of_the_current_stream():
+    """Also on a side stream, and for a device named without an index."""
+    side = torch.cuda.Stream()
+    for device in (torch.device("cuda", torch.cuda.current_device()), torch.device("cuda")):
+        for stream in (torch.cuda.default_stream(), side):
+            with torch.cuda.stream(stream):
+                assert B._on_stream(device, lambda *a: a, 7) == (7, torch.cuda.current_stream().cuda_stream)
