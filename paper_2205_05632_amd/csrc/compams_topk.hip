@@ -18,8 +18,8 @@
 //                  entries kept for certain, their prefixes inside blocks of chunks and the block totals; the
 //                  few entries of the threshold's bucket are ranked by the last workgroup of the row, which
 //                  gives tau, the ties to keep (by coordinate) and the next step's guess and band.
-//   pick           rows of at most 16 chunks: the whole selection by one workgroup per row, in place of the band kernel
-//                  and the general ones.
+//   pick           rows of at most 16 chunks, in every step that may have a guess: the whole selection by one workgroup
+//                  per row, in place of the band kernel and the general ones.
 //   The general route (12 + 10 + 9 key bits and a zero sign bit), for every other row:
 //   level 0        histogram of the 12-bit threshold buckets, from the candidate list when the guess held (the
 //                  list then holds at least k entries), else from the row itself; for a listed row also the
@@ -1297,9 +1297,9 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 // ---------------------------------------------------------------------------------------------
 // The whole selection of a short row (at most kPickChunks chunks) by one workgroup: it takes the place of the band
 // kernel and of the four general ones, whose launches and row-wide steps cost a short row more than its bytes (4 rows
-// of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass 31.0 -> 23.9).
-//   1. Elements: the candidate list if the guess held, else the row's stored values.  The first kPickHeld of a thread
-//      stay in registers; what goes beyond is read again in every sweep.
+// of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass 31.0 -> 24.2).
+//   1. Elements: the candidate list if the guess held, else the row's stored values, chunk after chunk.  The first trip of
+//      four per thread stays in registers; what goes beyond is read again in every sweep, four trips requested together.
 //   2. The bucket that holds the k-th largest key, by histograms of kPickBins buckets in LDS, each over the bucket the
 //      one before found: from a list, buckets of a thousandth of an octave from the list's lower end upwards, so that
 //      the first one usually leaves a handful of entries (key bits from the top, as for a row, would put a list's keys
@@ -1308,85 +1308,135 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 //      equal keys: the last tie to take is found by the same histograms over the coordinates.
 //   4. Per chunk the entries kept, and their prefix over the row, for the last kernel; guess and window for the next
 //      step as the other routes set them.
+// Where the line lies (whole step in us, 4 rows, the general kernels / this one): k = d / 100 16 chunks 30.6 / 24.6, 32
+// chunks 30.8 / 28.6, 48 chunks 31.1 / 33.7; k = d / 10 16 chunks 39.5 / 39.1, 20 chunks 40.1 / 42.9.  What bounds it is one compute
+// unit's instructions, about 20 us for a sweep over 65536 coordinates.  A row whose list did not hold (a selection of half
+// the row, magnitudes that are few and equal) still takes it: 4 x 65536, k = 32768 164 / 101, k = 19660 of three
+// magnitudes 198 / 170.  A step of which it is known beforehand that no row has a guess (the first of a context, prediction
+// off) goes to the general kernels: 4 x 65536, k = 655 56 / 95.
 // A row's window only narrows what the first pass lists (opt.band = kBandWindow); whether the threshold lay inside is
 // counted as on the band route.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPickThreads = 1024;
 constexpr uint32_t kPickChunks = 16;
 constexpr int kPickBins = 2048;
-constexpr int kPickHeld = 4;
-constexpr uint32_t kPickRank = 1024;
+constexpr uint32_t kPickQuad = 4;    // elements of a thread per trip
+constexpr uint32_t kPickRank = 256;  // (ranked by comparing all with all: a thousand of them take 27 us, one more sweep less)
+constexpr uint32_t kPickCrowd = 16;
 
-__global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                             TopkOptions opt, uint32_t use_guess) {
-  __shared__ uint32_t lh[kPickBins];
-  __shared__ uint32_t suf[kPickThreads + 1];
-  __shared__ uint32_t out2[2];
-  __shared__ uint2 rank_en[kPickRank];
-  __shared__ uint32_t chunk_cnt[kPickChunks];
-  __shared__ uint32_t sh_count, sh_ties, sh_ties_in, sh_tau, sh_last, sh_from0, sh_from1, sh_window, sh_bucket;
-  const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
+struct PickShared {
+  uint32_t lh[kPickBins];
+  uint32_t suf[kPickThreads + 1];
+  uint32_t out2[2];
+  uint2 rank_en[kPickRank];
+  uint32_t chunk_cnt[kPickChunks];
+  uint32_t count, ties, ties_in, tau, last, from0, from1, window, bucket;
+};
+
+// What the selection reads of a row's control block, all of it requested together.
+struct PickRow {
+  uint32_t n_cand, cand_from, b_guess, band_valid, band_lo, band_hi, band_mul, tau, tau_prev;
+};
+
+// LISTED: the row's elements are the entries of its candidate list, else the coordinates of the row.
+template <bool LISTED>
+__device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict__ e, const Geometry& geo,
+                                         const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc,
+                                         const PickRow& in_row, bool pred) {
   const uint32_t row = sc.seg, t = threadIdx.x, lane = lane_id();
   const uint32_t k = geo.k;
   TopkRow* rowp = ws.rows + row;
   const float* er = e + sc.elem_off;
   const uint2* candr = ws.cand + sc.cand_base;
-  const uint32_t n_cand = rowp->cursor, bg = rowp->b_guess;  // (a short row's list is kept as one run)
-  const uint32_t blo = rowp->band_lo, bhi = rowp->band_hi, bmul = rowp->band_mul, cand_lo = rowp->cand_from - 1u;
-  const uint32_t tau_before = rowp->tau, tau_before2 = rowp->tau_prev;
-  const bool pred = use_guess && rowp->cand_from != 0;
-  const bool windowed = pred && opt.band && rowp->band_valid != 0;
-  const bool listed = pred && !opt.force_dense && n_cand >= k && n_cand <= opt.cap;
-  const uint32_t count = listed ? n_cand : geo.d;
-  auto element = [&](uint32_t q) {  // q < count
-    return listed ? candr[q] : make_uint2(q, __float_as_uint(er[q]));
-  };
-  uint2 held[kPickHeld];
+  const uint32_t n_cand = in_row.n_cand, bg = in_row.b_guess;
+  const uint32_t blo = in_row.band_lo, bhi = in_row.band_hi, bmul = in_row.band_mul, cand_lo = in_row.cand_from - 1u;
+  const uint32_t tau_before = in_row.tau, tau_before2 = in_row.tau_prev;
+  const bool windowed = pred && opt.band && in_row.band_valid != 0;
+  const uint32_t count = LISTED ? n_cand : geo.d;
+  // A trip takes kPickQuad elements of every thread: entries of the list 1024 apart, or a quad of the row's coordinates (a
+  // trip is then a chunk).
+  struct Trip { uint2 en[kPickQuad]; };
+  constexpr uint32_t kTripElements = kPickQuad * kPickThreads;
+  static_assert(kTripElements == kChunk, "a trip over the row is a chunk");
+  auto number = [&](uint32_t q0, uint32_t u) { return LISTED ? q0 + u * kPickThreads + t : q0 + kPickQuad * t + u; };
+  auto load = [&](uint32_t q0, Trip& to) {
+    if constexpr (LISTED) {
 #pragma unroll
-  for (int u = 0; u < kPickHeld; ++u) {
-    const uint32_t q = u * kPickThreads + t;
-    held[u] = q < count ? element(q) : make_uint2(0u, 0u);
-  }
-  // visit(element, whether it exists) for every element, whole wavefronts at a time
-  auto sweep = [&](auto&& visit) {
-#pragma unroll
-    for (int u = 0; u < kPickHeld; ++u)
-      if (static_cast<uint32_t>(u * kPickThreads) < count) visit(held[u], u * kPickThreads + t < count);  // uniform
-#pragma unroll 1
-    for (uint32_t q0 = kPickHeld * kPickThreads; q0 < count; q0 += kPickHeld * kPickThreads) {
-      uint2 en[kPickHeld];
-#pragma unroll
-      for (int u = 0; u < kPickHeld; ++u) {
-        const uint32_t q = q0 + u * kPickThreads + t;
-        en[u] = q < count ? element(q) : make_uint2(0u, 0u);
-      }
-#pragma unroll
-      for (int u = 0; u < kPickHeld; ++u) visit(en[u], q0 + u * kPickThreads + t < count);
+      for (uint32_t u = 0; u < kPickQuad; ++u) to.en[u] = number(q0, u) < count ? candr[number(q0, u)] : make_uint2(0u, 0u);
+    } else {
+      const uint32_t j = number(q0, 0);
+      const float4 x = j < count ? *reinterpret_cast<const float4*>(er + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+      to.en[0] = make_uint2(j, __float_as_uint(x.x));
+      to.en[1] = make_uint2(j + 1, __float_as_uint(x.y));
+      to.en[2] = make_uint2(j + 2, __float_as_uint(x.z));
+      to.en[3] = make_uint2(j + 3, __float_as_uint(x.w));
     }
   };
-  if (t < kPickChunks) chunk_cnt[t] = 0;
-  if (t == 0) sh_count = sh_ties = sh_ties_in = sh_from0 = sh_from1 = sh_window = sh_bucket = 0;
+  Trip held;  // the first trip stays in registers
+  load(0, held);
+  // visit(element, whether it exists, first element of the trip) for every element, whole wavefronts at a time
+  auto sweep = [&](auto&& visit) {
+    constexpr uint32_t kAhead = 4;  // trips requested together
+#pragma unroll
+    for (uint32_t u = 0; u < kPickQuad; ++u)
+      if (!LISTED || u * kPickThreads < count) visit(held.en[u], number(0, u) < count, 0u);  // uniform
+#pragma unroll 1
+    for (uint32_t q0 = kTripElements; q0 < count; q0 += kAhead * kTripElements) {
+      Trip trip[kAhead];
+#pragma unroll
+      for (uint32_t w = 0; w < kAhead; ++w)
+        if (q0 + w * kTripElements < count) load(q0 + w * kTripElements, trip[w]);  // uniform
+#pragma unroll
+      for (uint32_t w = 0; w < kAhead; ++w)
+        if (q0 + w * kTripElements < count) {
+#pragma unroll
+          for (uint32_t u = 0; u < kPickQuad; ++u)
+            visit(trip[w].en[u], number(q0 + w * kTripElements, u) < count, q0 + w * kTripElements);
+        }
+    }
+  };
+  // One more in lh[b] for every lane with `in`.  Additions to one word are performed one after the other: a word that
+  // kPickCrowd lanes or more share (equal magnitudes, zeros) is counted by a ballot.
+  auto count_in = [&](bool in, uint32_t b) {
+    uint64_t left = ballot64(in);
+    while (left) {
+      const uint32_t b0 = __builtin_amdgcn_readlane(b, __builtin_ctzll(left));
+      const uint64_t same = ballot64(in && b == b0);
+      if (popc64(same) < kPickCrowd) {
+        if (in) atomicAdd(&sh.lh[b], 1u);
+        break;
+      }
+      if (lane == 0) atomicAdd(&sh.lh[b0], popc64(same));
+      in = in && b != b0;
+      left &= ~same;
+    }
+  };
+  if (t < kPickChunks) sh.chunk_cnt[t] = 0;
+  if (t == 0) sh.count = sh.ties = sh.ties_in = sh.from0 = sh.from1 = sh.window = sh.bucket = 0;
   // ---- 2. [lo, hi]: keys among which the k-th largest is the need-th largest ----
-  uint32_t lo = listed ? cand_lo : 0u, hi = 0xffffffffu;
-  uint32_t shift = listed ? 13u : 20u;  // (20: the buckets reach from 0 to 2^31)
+  uint32_t lo = LISTED ? cand_lo : 0u, hi = 0xffffffffu;
+  uint32_t shift = LISTED ? 13u : 20u;  // (20: the buckets reach from 0 to 2^31)
   uint32_t need = k, inside = 0;
 #pragma unroll 1
   for (;;) {
-    for (int b = t; b < kPickBins; b += kPickThreads) lh[b] = 0;
+    for (int b = t; b < kPickBins; b += kPickThreads) sh.lh[b] = 0;
     __syncthreads();
-    sweep([&](const uint2& en, bool ok) {
-      const uint32_t key = key_of_bits(en.y);
+    sweep([&](const uint2& en, bool ok, uint32_t) {
+      const uint32_t key = key_of_bits(en.y), b = (key - lo) >> shift;
       const bool in = ok && key >= lo && key <= hi;
-      const uint32_t b = (key - lo) >> shift;
-      if (in && b + 1 < kPickBins) atomicAdd(&lh[b], 1u);
-      const uint64_t above = ballot64(in && b + 1 >= kPickBins);  // the last bucket holds everything above it
-      if (above && lane == 0) atomicAdd(&lh[kPickBins - 1], popc64(above));
+      if constexpr (LISTED) {  // (a list's keys spread over the buckets; counting the crowded ones apart costs 0.3 us)
+        if (in && b + 1 < kPickBins) atomicAdd(&sh.lh[b], 1u);
+        const uint64_t above = ballot64(in && b + 1 >= kPickBins);  // the last bucket holds everything above it
+        if (above && lane == 0) atomicAdd(&sh.lh[kPickBins - 1], popc64(above));
+      } else {
+        count_in(in, b < kPickBins - 1 ? b : kPickBins - 1);
+      }
     });
     __syncthreads();
-    find_crossing<kPickBins, kPickThreads>(lh, need, suf, out2);
-    const uint32_t b = out2[0];
-    need -= out2[1];
-    inside = lh[b];
+    find_crossing<kPickBins, kPickThreads>(sh.lh, need, sh.suf, sh.out2);
+    const uint32_t b = sh.out2[0];
+    need -= sh.out2[1];
+    inside = sh.lh[b];
     lo += b << shift;
     if (b + 1 < kPickBins) {
       const uint32_t top = lo + ((1u << shift) - 1u);
@@ -1400,31 +1450,31 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   // ---- 3. tau and the last tie to take ----
   uint32_t tau, tie_last, ties, ties_kept;
   if (inside <= kPickRank) {
-    sweep([&](const uint2& en, bool ok) {
+    sweep([&](const uint2& en, bool ok, uint32_t) {
       const uint32_t key = key_of_bits(en.y);
-      if (ok && key >= lo && key <= hi) rank_en[atomicAdd(&sh_count, 1u)] = make_uint2(en.x, key);
+      if (ok && key >= lo && key <= hi) sh.rank_en[atomicAdd(&sh.count, 1u)] = make_uint2(en.x, key);
     });
     __syncthreads();
     uint32_t my_key = 0, my_coord = 0, rank = 0;
     if (t < inside) {
-      my_coord = rank_en[t].x;
-      my_key = rank_en[t].y;
+      my_coord = sh.rank_en[t].x;
+      my_key = sh.rank_en[t].y;
       for (uint32_t q = 0; q < inside; ++q) {
-        const uint2 o = rank_en[q];
+        const uint2 o = sh.rank_en[q];
         rank += (o.y > my_key || (o.y == my_key && o.x < my_coord)) ? 1u : 0u;
       }
-      if (rank == need - 1) { sh_tau = my_key; sh_last = my_coord; }  // the last kept one
+      if (rank == need - 1) { sh.tau = my_key; sh.last = my_coord; }  // the last kept one
     }
     __syncthreads();
-    tau = sh_tau;
+    tau = sh.tau;
     if (t < inside && my_key == tau) {
-      atomicAdd(&sh_ties, 1u);
-      if (my_coord <= sh_last) atomicAdd(&sh_ties_in, 1u);
+      atomicAdd(&sh.ties, 1u);
+      if (my_coord <= sh.last) atomicAdd(&sh.ties_in, 1u);
     }
     __syncthreads();
-    ties = sh_ties;
-    ties_kept = sh_ties_in;
-    tie_last = ties_kept < ties ? sh_last : 0xffffffffu;
+    ties = sh.ties;
+    ties_kept = sh.ties_in;
+    tie_last = ties_kept < ties ? sh.last : 0xffffffffu;
   } else {
     tau = lo;
     ties = inside;
@@ -1432,19 +1482,20 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
     tie_last = 0xffffffffu;
     if (need < inside) {  // the need-th smallest coordinate among the entries equal to tau
       uint32_t c_lo = 0, left = need;
+      constexpr uint32_t kCoordShift = 5;
+      static_assert((kPickChunks * kChunk) >> kCoordShift <= kPickBins && (1u << kCoordShift) <= kPickBins, "two levels");
 #pragma unroll 1
-      for (uint32_t c_shift = 20;; c_shift = c_shift > 11u ? c_shift - 11u : 0u) {
-        for (int b = t; b < kPickBins; b += kPickThreads) lh[b] = 0;
+      for (uint32_t c_shift = kCoordShift;; c_shift = 0) {
+        for (int b = t; b < kPickBins; b += kPickThreads) sh.lh[b] = 0;
         __syncthreads();
-        sweep([&](const uint2& en, bool ok) {
-          const uint32_t rel = (en.x - c_lo) >> c_shift;
-          if (ok && key_of_bits(en.y) == tau && en.x >= c_lo && rel < kPickBins)
-            atomicAdd(&lh[kPickBins - 1 - rel], 1u);  // mirrored: the smallest coordinates on top
+        sweep([&](const uint2& en, bool ok, uint32_t) {
+          const uint32_t rel = (en.x - c_lo) >> c_shift;  // mirrored below: the smallest coordinates on top
+          count_in(ok && key_of_bits(en.y) == tau && en.x >= c_lo && rel < kPickBins, kPickBins - 1 - rel);
         });
         __syncthreads();
-        find_crossing<kPickBins, kPickThreads>(lh, left, suf, out2);
-        c_lo += (kPickBins - 1 - out2[0]) << c_shift;
-        left -= out2[1];
+        find_crossing<kPickBins, kPickThreads>(sh.lh, left, sh.suf, sh.out2);
+        c_lo += (kPickBins - 1 - sh.out2[0]) << c_shift;
+        left -= sh.out2[1];
         __syncthreads();
         if (c_shift == 0) break;
       }
@@ -1454,40 +1505,50 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   // ---- 4. kept entries per chunk; what the counters and the next step's guess need ----
   const uint32_t b0 = tau >> kL0Shift;
   const uint32_t tau_bucket = windowed && tau >= blo && tau < bhi ? band_bucket(tau - blo, bmul) : 0xffffffffu;
-  sweep([&](const uint2& en, bool ok) {
+  uint32_t n_from0 = 0, n_from1 = 0, n_window = 0, n_same = 0;  // this wavefront's
+  sweep([&](const uint2& en, bool ok, uint32_t q0) {
     const uint32_t key = key_of_bits(en.y), bucket = key >> kL0Shift;
-    const uint64_t kept = ballot64(ok && (key > tau || (key == tau && en.x <= tie_last)));
-    const uint64_t from0 = ballot64(ok && bucket >= b0), from1 = ballot64(ok && bucket + 1 >= b0);
-    const bool in_window = ok && windowed && key >= blo && key < bhi;
-    const uint64_t window = ballot64(in_window), same = ballot64(in_window && band_bucket(key - blo, bmul) == tau_bucket);
-    if (lane == 0) {
-      if (from0) atomicAdd(&sh_from0, popc64(from0));
-      if (from1) atomicAdd(&sh_from1, popc64(from1));
-      if (window) atomicAdd(&sh_window, popc64(window));
-      if (same) atomicAdd(&sh_bucket, popc64(same));
+    uint64_t kept = ballot64(ok && (key > tau || (key == tau && en.x <= tie_last)));
+    if constexpr (!LISTED) {  // (a list holds them all)
+      n_from0 += popc64(ballot64(ok && bucket >= b0));
+      n_from1 += popc64(ballot64(ok && bucket + 1 >= b0));
     }
-    uint64_t left = kept;
-    const uint32_t c = en.x / kChunk;
-    while (left) {  // (a wavefront's 64 elements lie in a few chunks)
-      const uint32_t c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(left));
-      const uint64_t here = ballot64(c == c0) & left;
-      if (lane == 0) atomicAdd(&chunk_cnt[c0], popc64(here));
-      left &= ~here;
+    if (windowed) {  // uniform
+      const bool in_window = ok && key >= blo && key < bhi;
+      n_window += popc64(ballot64(in_window));
+      n_same += popc64(ballot64(in_window && band_bucket(key - blo, bmul) == tau_bucket));
+    }
+    if constexpr (LISTED) {
+      const uint32_t c = en.x / kChunk;
+      while (kept) {  // (a wavefront's 64 entries lie in a few chunks)
+        const uint32_t c0 = __builtin_amdgcn_readlane(c, __builtin_ctzll(kept));
+        const uint64_t here = ballot64(c == c0) & kept;
+        if (lane == 0) atomicAdd(&sh.chunk_cnt[c0], popc64(here));
+        kept &= ~here;
+      }
+    } else if (kept && lane == 0) {
+      atomicAdd(&sh.chunk_cnt[q0 / kChunk], popc64(kept));
     }
   });
+  if (lane == 0) {
+    if (n_from0) atomicAdd(&sh.from0, n_from0);
+    if (n_from1) atomicAdd(&sh.from1, n_from1);
+    if (n_window) atomicAdd(&sh.window, n_window);
+    if (n_same) atomicAdd(&sh.bucket, n_same);
+  }
   __syncthreads();
   if (t < geo.num_chunks) {
     uint32_t before = 0;
-    for (uint32_t u = 0; u < t; ++u) before += chunk_cnt[u];
-    ws.chunk_rec[sc.chunk_base + t] = make_uint4(chunk_cnt[t], 0u, before, 0u);
+    for (uint32_t u = 0; u < t; ++u) before += sh.chunk_cnt[u];
+    ws.chunk_rec[sc.chunk_base + t] = make_uint4(sh.chunk_cnt[t], 0u, before, 0u);
   }
   if (t != 0) return;
-  const uint32_t total = sh_from0;  // entries from the threshold's bucket upwards (a list holds them all)
+  const uint32_t total = sh.from0;  // (from the row itself) entries from the threshold's bucket upwards
   const bool fits = total <= opt.cap && !opt.force_dense;
   rowp->fast = kFastPick;
   rowp->level1_done = 1;
-  rowp->mode = listed ? kModeCand : kModeDense;
-  rowp->n_src = listed ? n_cand : 0u;
+  rowp->mode = LISTED ? kModeCand : kModeDense;
+  rowp->n_src = LISTED ? n_cand : 0u;
   rowp->tau_prev = tau_before;
   rowp->tau = tau;
   rowp->r = ties_kept;
@@ -1498,26 +1559,26 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   ws.tau[row] = tau;
   ws.count_gt[row] = k - ties_kept;
   uint32_t* cn = ws.counters + row * kCountersPerRow;
-  cn[0] = listed ? 0u : (fits ? 1u : 4u);
-  cn[1] = listed ? n_cand : (fits ? total : 0u);
+  cn[0] = LISTED ? 0u : (fits ? 1u : 4u);
+  cn[1] = LISTED ? n_cand : (fits ? total : 0u);
   cn[2] = ties;
   cn[3] = ties_kept;
-  const uint32_t in_window = sh_window;
+  const uint32_t in_window = sh.window;
   uint32_t miss = 0;
   if (!windowed || opt.force_dense) miss = 1;
   else if (n_cand > opt.cap) miss = 2;
   else if (in_window > opt.band_cap) miss = 3;
   else if (tau >= bhi) miss = 4;
   else if (tau < blo) miss = 5;
-  else if (sh_bucket > kBoundaryCap) miss = 6;
+  else if (sh.bucket > kBoundaryCap) miss = 6;
   cn[4] = miss ? 0u : in_window;
   cn[5] = miss;
   // Guess and window for the next step, as the other routes set them; from a list nothing is known below its lower
   // end, and the bucket below the guess it was made with is taken to hold at most as many entries as all above it.
   uint32_t valid = 0, guess = 0;
   if (opt.predict && !opt.force_dense) {
-    const uint32_t at_hand = listed ? n_cand : total;
-    const uint32_t bound = listed ? (b0 > bg ? n_cand : 2u * n_cand) : sh_from1;
+    const uint32_t at_hand = LISTED ? n_cand : total;
+    const uint32_t bound = LISTED ? (b0 > bg ? n_cand : 2u * n_cand) : sh.from1;
     if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
     else if (at_hand <= opt.cap / 2) { valid = 1; guess = b0; }
   }
@@ -1527,6 +1588,19 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
     noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
             static_cast<float>(in_window);
   set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, k, opt);
+}
+
+__global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
+                                                             TopkOptions opt, uint32_t use_guess) {
+  __shared__ PickShared sh;
+  const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
+  const TopkRow* rp = ws.rows + sc.seg;
+  const PickRow r{rp->cursor /* a short row's list is kept as one run */, rp->cand_from, rp->b_guess, rp->band_valid,
+                  rp->band_lo, rp->band_hi, rp->band_mul, rp->tau, rp->tau_prev};
+  const bool pred = use_guess && r.cand_from != 0;
+  const bool listed = pred && !opt.force_dense && r.n_cand >= geo.k && r.n_cand <= opt.cap;
+  if (listed) pick_row<true>(sh, e, geo, ws, opt, sc, r, pred);  // uniform
+  else pick_row<false>(sh, e, geo, ws, opt, sc, r, pred);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1550,8 +1624,8 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
   const float* er = e + static_cast<int64_t>(row) * geo.ld;
   constexpr uint32_t kQuads = kSample / 4;
   constexpr int kPer = kQuads / kPickThreads;
-  static_assert(kQuads % kPickThreads == 0 && kSample <= kPickChunks * kChunk, "whole quads, of a row that is longer");
-  const uint32_t whole_quads = geo.d / 4;  // (rows of more than kPickChunks chunks: more than kQuads)
+  static_assert(kQuads % kPickThreads == 0, "whole quads");
+  const uint32_t whole_quads = geo.d / 4;  // at least kQuads: the host asks for no sample of a shorter row
   const uint32_t taken = kSample;
   float4 x[kPer];
 #pragma unroll
@@ -2548,12 +2622,13 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const dim3 grid_rows(G, geo.n), wg(kWG);
   const uint32_t use_guess = first_pass_may_predict || whole ? 1u : 0u;
   const dim3 grid_chunks(geo.num_chunks, geo.n);
-  // Short rows are selected by a workgroup each.  A longer row's list, and a row that has to be read again, are too
-  // much for one compute unit's share of the bandwidth.
-  const bool pick = geo.num_chunks <= kPickChunks;
+  // Short rows are selected by a workgroup each (where the line lies: see there), unless no row of this step has a guess.
+  const bool pick = geo.num_chunks <= kPickChunks && use_guess;
   TopkOptions opt = options;
   if (pick && opt.band) opt.band = kBandWindow;
-  if (whole && !pick) {  // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample)
+  // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample; 4 rows of 65536,
+  // k = 655: the whole call 66 us by the general kernels without a guess, 34.4 with it and one workgroup per row)
+  if (whole && geo.d >= kSample) {
     launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws);
     COMPAMS_CHECK_LAUNCH();
   }

@@ -58,3 +58,40 @@ def test_the_two_selections_meet_at_sixteen_chunks(d):
     c = p.gpu.compams_state("counters").cpu().numpy()
     assert (c[:, 0] == 0).all() and (c[:, 4] > 0).all() and (c[:, 5] == 0).all(), c
     p.close()
+
+
+@pytest.mark.parametrize("option,value", [(B.OPT_PREDICT, 0), (B.OPT_FORCE_DENSE, 1), (B.OPT_BAND, 0)])
+@pytest.mark.parametrize("kind", ["normal", "equal"])
+def test_short_rows_with_options(kind, option, value):
+    """Without a guess the general kernels take the row, in between steps that one workgroup per row has taken."""
+    n, d, k = 3, 5 * 4096 + 8, 300
+    rng = np.random.default_rng(option + value)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    for t in range(9):
+        if t in (3, 6):
+            p.gpu.set_option(option, value if t == 3 else 1 - value)
+        p.step(values(kind, rng, n, d), 1e-3, label=f"{kind} option {option} step {t}", with_e=t in (4, 8))
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
+@pytest.mark.parametrize("listed", [True, False])
+@pytest.mark.parametrize("ties", [255, 256, 257, 4000])
+def test_ties_around_what_is_ranked(ties, listed):
+    """The entries left in the threshold's bucket are ranked up to 256 of them; more are equal keys, cut at a coordinate.
+    From the list, and from a row whose list does not fit."""
+    n, d = 2, 16 * 4096
+    k = 100 + ties // 2
+    rng = np.random.default_rng(ties)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    if not listed:
+        p.gpu.set_option(B.OPT_CANDIDATE_CAP, 1)
+    for t in range(4):
+        g = (rng.standard_normal((n, d)) * 1e-3).astype(np.float32)
+        for row in g:
+            at = rng.choice(d, size=100 + ties, replace=False)
+            row[at[:100]] = 64.0 + 4.0 * t
+            row[at[100:]] = 16.0
+        p.step(g, 1e-3, label=f"{ties} ties step {t}", with_e=t == 3)
+    assert all(p.exact.values()), p.exact
+    p.close()
