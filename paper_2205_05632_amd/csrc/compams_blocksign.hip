@@ -362,8 +362,17 @@ __global__ __launch_bounds__(kWG) void k_bs_finalize(Geometry geo, BlocksignWork
   ws.scales[t] = block_scale(word, sp, static_cast<double>(ws.offsets[b + 1] - ws.offsets[b]));
 }
 
-// Rows whose last workgroup forms the scales: few workgroups to draw a ticket, few blocks for one workgroup.
+// Rows whose last workgroup forms the scales have few workgroups that draw its ticket, and few blocks for one workgroup.
 constexpr uint32_t kBsScalesChunks = 64, kBsScalesBlocks = 64;
+// What it saves is the launch of k_bs_finalize, 1.5 us, or 4.5 us where a block has several sets of digits.  What it costs
+// grows with the rows' length and with the whole grid, because every workgroup waits for its own atomics before it
+// ends.  Measured (us gained; rows x chunks), one set of digits: 256 x 6 +0.1, 128 x 8 +0.6, 16 x 12 -0.4, 4 x 32 +0.2, 8 x 24
+// +0.8, 4 x 64 -0.9, 16 x 64 -7; several: 256 x 16 +1.0, 32 x 24 +0.8, 16 x 32 -0.3, 8 x 64 -0.4, 16 x 64 -3.8.
+inline bool scales_in_first_pass(const Geometry& geo, const BlocksignWorkspace& ws) {
+  if (geo.num_chunks > kBsScalesChunks || geo.num_blocks > kBsScalesBlocks) return false;
+  const bool several = ws.acc_replicas > 1;
+  return geo.num_chunks <= (several ? 16u : 8u) || geo.n * geo.num_chunks <= (several ? 512u : 128u);
+}
 
 // The scales of a row's blocks by one workgroup, from digits that other workgroups of the same launch have added to (with
 // device-scope atomics): read at that scope, all of them at once, and added up in LDS over the sets of a block.
@@ -500,9 +509,8 @@ __device__ __forceinline__ void bs_lean_chunk(uint32_t c, uint32_t row, const fl
   window_to_digits(A.sum, A.eh, dg);
 }
 
-// SCALES: the workgroup of a row that finishes last also turns the row's sums into scales.  A short row's few workgroups
-// hardly queue for the ticket, and the launch that this saves is a quarter of a small model's step (4 rows of 65536,
-// blocks of 4096: 13.9 -> 12.6 us a pass); of thousands of workgroups each would wait for its own atomics before it ends.
+// SCALES: the workgroup of a row that finishes last also turns the row's sums into scales (4 rows of 65536, blocks of 4096:
+// 13.9 -> 12.6 us a step; where the line lies: scales_in_first_pass).
 template <bool PEND, bool SCALES>
 __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
                                                   BlocksignWorkspace ws) {
@@ -889,7 +897,7 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
                           float* e, float* theta, float* m, float* v, float* vhat, bool residual_pending,
                           bool workers_only, hipStream_t stream, Launcher* L) {
   const dim3 grid_chunks(geo.num_chunks, geo.n), wg(kWG);
-  const bool scales = geo.num_chunks <= kBsScalesChunks && geo.num_blocks <= kBsScalesBlocks;
+  const bool scales = scales_in_first_pass(geo, ws);
   auto* first = residual_pending ? (scales ? k_bs_lean<true, true> : k_bs_lean<true, false>)
                                  : (scales ? k_bs_lean<false, true> : k_bs_lean<false, false>);
   launch(L, kSlotBsPass1, first, grid_chunks, wg, stream, g, e, geo, ws);

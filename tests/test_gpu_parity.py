@@ -725,10 +725,14 @@ def test_every_count_of_cached_state_arrays_gives_the_same_bytes(case, cached):
 
 
 @pytest.mark.parametrize("n,d,blocks", [(3, 64 * 4096, 64), (2, 64 * 4096 + 4, 64), (2, 64 * 4096, 65), (5, 9001, 1), (1, 37, 37),
-                                        (33, 4096, 3), (2, 250_001, 2)])
+                                        (33, 4096, 3), (2, 250_001, 2),
+                                        # one set of digits: up to 8 chunks, else 128 workgroups; several: 16, else 512
+                                        (2, 64 * 4096, 64), (17, 8 * 4096, 8), (15, 8 * 4096 + 5, 9), (14, 9 * 4096, 9),
+                                        (33, 16 * 4096, 2), (8, 64 * 4096, 2), (9, 64 * 4096 - 7, 2), (31, 17 * 4096, 1)])
 def test_blocksign_scales_of_short_rows(n, d, blocks):
-    """Up to 64 chunks and 64 blocks the row's last workgroup forms the scales, beyond either a launch of its own: the
-    same sums, cleared for the next step, with entries that miss the register windows and a block that is not finite."""
+    """Of short rows in small grids the row's last workgroup forms the scales, else a launch of its own (never the
+    former beyond 64 chunks or blocks): the same sums, cleared for the next step, with entries that miss the register
+    windows and a block that is not finite."""
     rng = np.random.default_rng(d + blocks)
     cuts = np.sort(rng.choice(np.arange(1, d), size=blocks - 1, replace=False))
     off = np.concatenate([[0], cuts, [d]]).astype(np.int64)
@@ -741,3 +745,27 @@ def test_blocksign_scales_of_short_rows(n, d, blocks):
             p.step(g, 1e-3, label=f"short row {d} x {blocks} step {t}", with_e=t == 3)
     assert all(p.exact.values()), p.exact
     p.close()
+
+
+def blocksign_step_us(n, chunks, blocks):
+    d = chunks * 4096
+    c = B.Compams(n, d, torch.zeros(d), compressor=B.BLOCKSIGN,
+                  block_offsets=np.linspace(0, d, blocks + 1).astype(np.int64))
+    g = torch.randn((n, c.ld), device=c.device)
+    times = []
+    for _ in range(9):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(40):
+            c.compams_step(g, 1e-3)
+        end.record()
+        torch.cuda.synchronize()
+        times.append(begin.elapsed_time(end) / 40 * 1e3)
+    c.close()
+    return sorted(times)[4]
+
+
+def test_forming_the_scales_in_the_first_pass_is_not_the_slower_way():
+    """64 rows of 64 and of 65 chunks, a block per chunk: the longer ones always have a launch of its own for the scales.  With the
+    row's last workgroup forming them the shorter ones took 68 us against 53."""
+    assert blocksign_step_us(64, 64, 64) < 1.12 * blocksign_step_us(64, 65, 65)
