@@ -419,7 +419,7 @@ static void set_geometry(compams_ctx* ctx) {
   geo.k = is_topk(c.compressor) ? static_cast<uint32_t>(c.k) : 0;
   geo.num_blocks = c.compressor == COMPAMS_BLOCKSIGN ? static_cast<uint32_t>(c.num_blocks) : 0;
   geo.words = ctx->lay.words;
-  geo.count_cpw = count_chunks_per_row_block(ctx->lay.num_chunks);
+  geo.count_cpw = count_chunks_per_row_block(geo.n, geo.num_chunks);
 }
 
 // What compams_init checks of a configuration before it looks at the workspace.

@@ -38,16 +38,22 @@ constexpr uint32_t kMicroFlag = 0x80000000u;  // WgSlot.seg of a first-pass work
 
 // The band and the counting kernel split a row's chunks into at most kMaxCountBlocks contiguous blocks of count_cpw
 // chunks (four wavefronts, eight chunks at a time: a multiple of 32).  d < 2^31 gives at most 2^19 chunks.  Rows of up
-// to 1024 chunks have blocks of 8, two chunks to a wavefront: their blocks of 32 leave most of the chip idle (4 rows of
-// 300007: the counting kernel 18.1 -> 10.1 us; 16 rows of 1 M: the band kernel 14.6 -> 12.6 us).
+// to 1024 chunks have blocks of 8, two chunks to a wavefront, while there are fewer than kShortChunks chunks in all rows: blocks
+// of 32 leave most of the chip idle then (4 rows of 300007: the counting kernel 18.1 -> 10.1 us; 16 rows of 1 M: the band
+// kernel 14.6 -> 12.6 us).  In larger grids the row's histogram, which every block of the band kernel reads, outweighs
+// that; where rows miss their window and have to be counted, the shorter blocks still gain.  Measured (us, blocks of 32 / of 8;
+// band kernel, counting kernel of rows that miss): 16 x 640 chunks 15.6 / 15.6, 13.5 / 8.9; 64 x 245 15.2 / 17.7, 20.0 / 10.8; 64 x
+// 512 17.4 / 26.9, 26.1 / 15.9; 64 x 1024 23.9 / 42.8, 22.3 / 16.1; long rows, 4 x 2048: 16.1 / 18.4, 14.8 / 9.2.
 constexpr uint32_t kMaxCountBlocks = 256;
 constexpr uint32_t kMaxCountCpw = 2048;
+constexpr uint32_t kShortChunks = 32768;
 inline uint32_t count_chunks_per_block(uint32_t num_chunks) {
   const uint32_t m = (num_chunks + 32 * kMaxCountBlocks - 1) / (32 * kMaxCountBlocks);
   return 32 * (m ? m : 1);
 }
-inline uint32_t count_chunks_per_row_block(uint32_t num_chunks) {
-  return num_chunks <= 4 * kMaxCountBlocks ? 8 : count_chunks_per_block(num_chunks);
+inline uint32_t count_chunks_per_row_block(uint32_t n, uint32_t num_chunks) {
+  const bool few = static_cast<uint64_t>(n) * num_chunks < kShortChunks;
+  return num_chunks <= 4 * kMaxCountBlocks && few ? 8 : count_chunks_per_block(num_chunks);
 }
 // Chunks that a wavefront takes at a time of a block of cpw: two or eight.
 __host__ __device__ __forceinline__ uint32_t chunks_per_wave(uint32_t cpw) { return cpw < 32 ? cpw / 4 : 8; }
