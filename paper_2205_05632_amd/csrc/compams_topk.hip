@@ -2172,11 +2172,12 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
 // ---------------------------------------------------------------------------------------------
 // Kernel 5: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds what is
 // to be known of worker i of the tile.
-//   Selecting: every wavefront takes a quarter of the tile's workers.  Where a worker's entries of the chunk go in its
+//   Selecting: the wavefronts share out the tile's workers.  Where a worker's entries of the chunk go in its
 //              list follows from the tables (entries above the threshold in earlier chunks, plus the ties taken there:
 //              in coordinate order until r are in); its candidates of the chunk are gone through 64 to a slot, kSlots
 //              slots requested while the ones before are worked on.  The selected (coordinate, value) pairs are
-//              written to the list and kept in LDS.
+//              written to the list and kept in LDS.  What a slot needs of its worker is taken out of the worker's lane when
+//              the walk reaches it (64 x 520 chunks, k = d / 20, crowded: 582 -> 561 us a step).
 //   Adding:    one barrier later the first wavefront (or, where some worker has many entries, every
 //              wavefront for its own quarter of the chunk's coordinates) adds the workers' entries into an LDS tile of
 //              the summed gradient, one worker after the other: the fp32 sum has exactly the order i = 0 .. n-1, and
@@ -2192,16 +2193,28 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
 // 722 -> 685, 16 x 1 M 28 -> 18.5, 4 x 65536 10.7 -> 8.5, the server's half 87 -> 80.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kTileWorkers = 16;
-constexpr int kSlots = 8;            // slots of 64 entries requested together
 constexpr uint32_t kSolo = 128;      // up to so many selected entries of every worker one wavefront adds them all
 constexpr uint32_t kKept = 2048;     // selected entries of a tile kept in LDS, shared out evenly among its workers
 
-// Wavefronts per chunk.  Grids of many chunks have four, each with a quarter of the workers, then of the coordinates.
-// A grid that leaves a compute unit one or two workgroups has sixteen: its time is the chain of the most crowded
-// chunk's slots, not their number (16 workers x 1 M coordinates, 245 chunks, up to 590 selected entries per worker and
-// chunk: 27.2 us with four, 18.5 with sixteen; 4 x 65536: 9.3 and 8.5).
-constexpr int kFinalMany = 4, kFinalFew = 16;
-inline bool few_chunks(uint32_t workgroups) { return workgroups <= 512; }
+// Wavefronts per chunk.  A chunk's time is the chain of its slots, which more wavefronts share; a grid that fills the chip
+// anyway pays for the room they take.  How a row's selection is spread is not known beforehand: evenly, or crowded into the
+// few chunks of the layers with large gradients.  Whole steps in us, with sixteen / eight / four, selections spread evenly; in a
+// tenth of the row:
+//   16 x 245 chunks, k = d / 100   70 / - / 72; 80 / - / 95
+//   16 x 300, k = d / 100          88 / 82 / 83; 90 / 93 / 105     64 x 300, k = d / 20    323 / 291 / 306; 351 / 457 / 622
+//   16 x 520, k = d / 100          133 / 121 / 122; 122 / 124 / 136
+//   64 x 1024, k = d / 100         715 / 673 / 661; 703 / 693 / 740  64 x 1024, k = d / 20   909 / 838 / 818; 913 / 1003 / 1206
+//   1 x 1024, k = d / 20           85 / 73 / 71; 83 / 80 / 83
+// So a row has sixteen up to 512 chunks, where crowded selections gain more than even ones lose, eight up to 768, and beyond that
+// four, or eight where every row keeps more than a hundred entries of a chunk.  Inside every block the selection is spread
+// evenly by what it is (16 layers, 64 x 300, one entry in twenty: 380 / 332 / -; 64 x 768: - / 734 / 713).
+constexpr int kFinalMany = 4, kFinalSome = 8, kFinalFew = 16;
+inline int final_wavefronts(uint32_t workgroups, const Geometry& geo, bool uniform) {
+  if (uniform) return workgroups <= 256 ? kFinalFew : workgroups <= 640 ? kFinalSome : kFinalMany;
+  if (workgroups <= 512) return kFinalFew;
+  const bool large = geo.n >= 4 && static_cast<uint64_t>(geo.k) * kChunk >= static_cast<uint64_t>(geo.d) * 100;
+  return workgroups <= 768 || large ? kFinalSome : kFinalMany;
+}
 
 // ROLE: kWholeStep does all of it; kWorkerHalf writes the lists and stops (the workers' lines of Algorithm 2: the
 // lists are the messages); kServerHalf adds up lists that were put into the workspace (the server's lines; where a
@@ -2259,11 +2272,13 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
 // merges them and drops the hint).
 // CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
 template <int ROLE, bool UNI, int NC, int NW, bool CLEAR = false>
-__global__ __launch_bounds__(NW * 64) void k_topk_final(
+__global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_final(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
     const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
   static_assert(UNI || ROLE != kServerHalf, "the server's half works on whole rows");
+  static_assert(NW == kWaves || ROLE != kServerHalf, "it knows the offsets of quarters");
   constexpr uint32_t kPart = kChunk / NW;  // coordinates of a wavefront's part of the chunk
+  constexpr int kSlots = NW == kFinalFew ? 4 : 8;  // slots of 64 entries requested together (their code is fetched for each)
   static_assert(kTileWorkers % NW == 0 && NW % kWaves == 0 && NW <= 16, "workers and quarters are shared out evenly");
   __shared__ float4 gs4[ROLE == kWorkerHalf ? 1 : kChunk / 4];
   __shared__ float kept_val[ROLE == kWholeStep ? kKept : 1];
@@ -2399,6 +2414,22 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
       if (lane < NW)
 #pragma unroll
         for (uint32_t i = wave; i < kTileWorkers; i += NW) sh_part[i][lane] = 0;
+      // What the slots of the present worker need, the same in every lane: taken out of its lane once.
+      uint32_t tau_i = 0, tie_i = 0, at_i = 0, first_i = 0, eq_i = 0, r_i = 0, in_parts = 0;
+      bool partial_i = false;
+      auto enter = [&] {
+        tau_i = __builtin_amdgcn_readlane(tau, now.i);
+        tie_i = __builtin_amdgcn_readlane(tie, now.i);
+        first_i = __builtin_amdgcn_readlane(at, now.i);
+        at_i = first_i;
+        partial_i = (partial_mask >> now.i) & 1u;
+        if (partial_i) {
+          eq_i = __builtin_amdgcn_readlane(eq, now.i);
+          r_i = __builtin_amdgcn_readlane(r, now.i);
+        }
+        in_parts = 0;
+      };
+      if (now.i < kTileWorkers) enter();
 #pragma unroll 1
       while (now.i < kTileWorkers) {
         Slots nxt;
@@ -2408,14 +2439,12 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
           if (now.i < kTileWorkers) {  // wave-uniform
             const uint2 en = cur.en[s];
             const uint32_t key = key_of_bits(en.y);
-            const uint32_t tau_i = __builtin_amdgcn_readlane(tau, now.i), tie_i = __builtin_amdgcn_readlane(tie, now.i);
             const bool ok = now.t + lane < now.n;
             bool is_tie = ok && key == tau_i && en.x <= tie_i;
-            if ((partial_mask >> now.i) & 1u) {  // wave-uniform
+            if (partial_i) {
               const uint64_t ties = ballot64(is_tie);
-              const uint32_t eq_i = __builtin_amdgcn_readlane(eq, now.i), r_i = __builtin_amdgcn_readlane(r, now.i);
               is_tie = is_tie && eq_i + count_below(ties) < r_i;
-              if (lane == now.i) eq += popc64(ties);
+              eq_i += popc64(ties);
             }
             const bool sel = is_tie || (ok && key > tau_i);
             const uint64_t taken = ballot64(sel);
@@ -2426,8 +2455,8 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
               const uint64_t set = ballot64((en.x & bit) != 0);
               in_part &= (lane & (bit / kPart)) ? set : ~set;
             }
-            if (lane < NW) sh_part[now.i][lane] += popc64(in_part);
-            const uint32_t pos = __builtin_amdgcn_readlane(at, now.i) + count_below(taken);
+            in_parts += popc64(in_part);
+            const uint32_t pos = at_i + count_below(taken);
             if (sel && pos < f.k_loc) {  // (always, when the counts are consistent)
               const size_t l = f.list0 + (i0 + now.i) * f.list_stride + pos;
               ws.idx[l] = static_cast<int32_t>(f.coord_base + en.x);
@@ -2436,14 +2465,20 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
               if (CLEAR) const_cast<float*>(e)[static_cast<int64_t>(i0 + now.i) * geo.ld + f.coord_base + en.x] = 0.0f;
             }
             if (ROLE == kWholeStep) {
-              const uint32_t kept = pos - __builtin_amdgcn_readlane(at_first, now.i);
+              const uint32_t kept = pos - first_i;
               if (sel && kept < share) {
                 kept_val[now.i * share + kept] = __uint_as_float(en.y);
                 kept_at[now.i * share + kept] = static_cast<uint16_t>(en.x - c_lo);
               }
             }
-            if (lane == now.i) at += popc64(taken);
-            next_slot(now, cnt);
+            at_i += popc64(taken);
+            now.t += 64;
+            if (now.t >= now.n) {  // the worker's last slot
+              if (lane == now.i) at = at_i;
+              if (lane < NW) sh_part[now.i][lane] = in_parts;
+              next_worker(now, cnt);
+              if (now.i < kTileWorkers) enter();
+            }
           }
         cur = nxt;
       }
@@ -2505,9 +2540,7 @@ __global__ __launch_bounds__(NW * 64) void k_topk_final(
       const uint32_t i_lane = have ? i0 + lane : i0;
       uint32_t first = 0, cnt = 0;  // the worker's entries of the part: from entry `first` of its list on
       if (ROLE == kServerHalf) {
-        // (offsets are known per quarter: with more wavefronts each skips the entries of its quarter that are others')
-        const uint32_t* so = ws.sel_off_srv + static_cast<size_t>(i_lane) * (geo.num_chunks * kWaves + 1) + c * kWaves +
-                             wave / (NW / kWaves);
+        const uint32_t* so = ws.sel_off_srv + static_cast<size_t>(i_lane) * (geo.num_chunks * kWaves + 1) + c * kWaves + wave;
         first = so[0];
         const uint32_t hi = so[1] < f.k_loc ? so[1] : f.k_loc;
         cnt = have && hi > first ? hi - first : 0u;
@@ -2613,6 +2646,34 @@ __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e,
     if (err__ != hipSuccess) return err__;        \
   } while (0)
 
+namespace {
+
+// The last kernel with NW wavefronts per chunk.
+template <int ROLE, bool UNI, int NW, bool CLEAR, typename... Args>
+void launch_final_of(int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
+  const dim3 grid(workgroups), wg(NW * 64);
+  if constexpr (ROLE == kWorkerHalf) {  // (no state)
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR>, grid, wg, stream, args...);
+  } else if constexpr (CLEAR && NW == kFinalFew) {  // (so short that its whole state stays in the memory-side cache)
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR>, grid, wg, stream, args...);
+  } else {
+#define COMPAMS_FINAL(NC) k_topk_final<ROLE, UNI, NC, NW, CLEAR>
+    COMPAMS_LAUNCH_BY_CACHED(cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL, grid, wg, stream, args...);
+#undef COMPAMS_FINAL
+  }
+}
+
+template <int ROLE, bool UNI, bool CLEAR, typename... Args>
+void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
+  switch (final_wavefronts(workgroups, geo, !UNI)) {
+    case kFinalFew: launch_final_of<ROLE, UNI, kFinalFew, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
+    case kFinalSome: launch_final_of<ROLE, UNI, kFinalSome, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
+    default: launch_final_of<ROLE, UNI, kFinalMany, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
+  }
+}
+
+}  // namespace
+
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& options, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
                      bool first_pass_may_predict, bool clear_pending, bool workers_only, bool whole, hipStream_t stream,
@@ -2663,38 +2724,15 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     launch(L, kSlotCount, k_topk_count<true>, dim3(count_blocks, geo.n), wg, stream, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
-  const dim3 grid_f(geo.num_chunks);
   const TopkFlat none{};
-  const bool few = few_chunks(geo.num_chunks);
-  if (whole) {
-#define COMPAMS_FINAL_CLEAR(NC) k_topk_final<kWholeStep, true, NC, kFinalMany, true>
-    if (few)  // (so short that its whole state stays in the memory-side cache)
-      launch(L, kSlotTopkFinal, k_topk_final<kWholeStep, true, 4, kFinalFew, true>, grid_f, dim3(kFinalFew * 64), stream, theta,
-             m, v, vhat, e, geo, ws, opt, ap, none);
-    else
-      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_CLEAR, grid_f, wg, stream, theta, m, v,
-                               vhat, e, geo, ws, opt, ap, none);
-#undef COMPAMS_FINAL_CLEAR
-    COMPAMS_CHECK_LAUNCH();
-    return hipSuccess;
-  }
-  const dim3 wg_few(kFinalFew * 64);
-#define COMPAMS_FINAL_WHOLE_ROW(NC) k_topk_final<kWholeStep, true, NC, kFinalMany>
-#define COMPAMS_FINAL_WHOLE_ROW_FEW(NC) k_topk_final<kWholeStep, true, NC, kFinalFew>
-  if (role == kWorkerHalf && few)
-    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, true, 0, kFinalFew>, grid_f, wg_few, stream, theta, m, v, vhat, e,
-           geo, ws, opt, ap, none);
+  if (whole)
+    launch_final<kWholeStep, true, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
+                                         none);
   else if (role == kWorkerHalf)
-    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, true, 0, kFinalMany>, grid_f, wg, stream, theta, m, v, vhat, e, geo,
-           ws, opt, ap, none);
-  else if (few)
-    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_WHOLE_ROW_FEW, grid_f, wg_few, stream, theta,
-                             m, v, vhat, e, geo, ws, opt, ap, none);
+    launch_final<kWorkerHalf, true, false>(geo, 0, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap, none);
   else
-    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_WHOLE_ROW, grid_f, wg, stream, theta, m, v,
-                             vhat, e, geo, ws, opt, ap, none);
-#undef COMPAMS_FINAL_WHOLE_ROW_FEW
-#undef COMPAMS_FINAL_WHOLE_ROW
+    launch_final<kWholeStep, true, false>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
+                                          none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -2728,24 +2766,12 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
     launch(L, kSlotCount, k_topk_count<false>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
-  if (workers_only) {
-    const float* residuals = e;
-    launch(L, kSlotTopkFinal, k_topk_final<kWorkerHalf, false, 0, kFinalMany>, dim3(flat.wg_final), wg, stream, theta, m, v,
-           vhat, residuals, geo, ws, opt, ap, flat);
-  } else {
-    const float* residuals = e;
-    const dim3 grid_f(flat.wg_final), wg_few(kFinalFew * 64);
-#define COMPAMS_FINAL_BLOCKS(NC) k_topk_final<kWholeStep, false, NC, kFinalMany>
-#define COMPAMS_FINAL_BLOCKS_FEW(NC) k_topk_final<kWholeStep, false, NC, kFinalFew>
-    if (few_chunks(flat.wg_final))
-      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_BLOCKS_FEW, grid_f, wg_few, stream, theta, m,
-                               v, vhat, residuals, geo, ws, opt, ap, flat);
-    else
-      COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_BLOCKS, grid_f, wg, stream, theta, m, v,
-                               vhat, residuals, geo, ws, opt, ap, flat);
-#undef COMPAMS_FINAL_BLOCKS_FEW
-#undef COMPAMS_FINAL_BLOCKS
-  }
+  const float* residuals = e;
+  if (workers_only)
+    launch_final<kWorkerHalf, false, false>(geo, 0, L, flat.wg_final, stream, theta, m, v, vhat, residuals, geo, ws, opt, ap, flat);
+  else
+    launch_final<kWholeStep, false, false>(geo, ap.cached_arrays, L, flat.wg_final, stream, theta, m, v, vhat, residuals, geo, ws,
+                                           opt, ap, flat);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -2755,12 +2781,9 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
 hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
-  const dim3 grid_f(geo.num_chunks), wg(kWG);
   const TopkFlat none{};
-#define COMPAMS_FINAL_SERVER(NC) k_topk_final<kServerHalf, true, NC, kFinalMany>
-  COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL_SERVER, grid_f, wg, stream, theta, m, v, vhat,
-                           no_e, geo, ws, opt, ap, none);
-#undef COMPAMS_FINAL_SERVER
+  launch_final_of<kServerHalf, true, kFinalMany, false>(ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
+                                                        ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }

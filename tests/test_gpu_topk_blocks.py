@@ -258,3 +258,18 @@ def test_invalid_block_configurations_are_refused():
         B.Compams(2, 100, t, compressor=B.TOPK_BLOCKS, block_offsets=[0, 48, 96], block_k=[1, 1])    # not up to d
     with pytest.raises(B.CompamsError):
         B.Compams(2, 100, t, compressor=B.TOPK_BLOCKS, block_offsets=[0, 48, 100])                   # no counts
+
+
+@pytest.mark.parametrize("chunks,per_thousand", [(256, 50), (257, 50), (640, 10), (641, 10)])
+def test_wavefronts_per_chunk_of_the_last_kernel(chunks, per_thousand):
+    """Sixteen wavefronts per chunk up to 256 chunks over all blocks, eight up to 640, then four; more than a tile of workers."""
+    n, d = (17 if chunks < 300 else 3), chunks * 4096
+    rng = np.random.default_rng(chunks)
+    sizes = np.array([1, 3, chunks // 3, chunks - 4 - chunks // 3]) * 4096
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    kb = np.maximum(1, sizes * per_thousand // 1000).astype(np.int64)
+    p = BlockPair(n, d, off, kb, np.zeros(d, dtype=np.float32))
+    for t in range(3):
+        p.step(rng.standard_normal((n, d), dtype=np.float32))
+        p.compare(f"step {t}", with_e=t == 2)
+    p.close()
