@@ -1342,7 +1342,7 @@ struct PickRow {
 template <bool LISTED>
 __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict__ e, const Geometry& geo,
                                          const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc,
-                                         const PickRow& in_row, bool pred) {
+                                         const PickRow& in_row, bool pred, const uint2 (&first)[kPickQuad]) {
   const uint32_t row = sc.seg, t = threadIdx.x, lane = lane_id();
   const uint32_t k = geo.k;
   TopkRow* rowp = ws.rows + row;
@@ -1373,7 +1373,12 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
     }
   };
   Trip held;  // the first trip stays in registers
-  load(0, held);
+  if constexpr (LISTED) {
+#pragma unroll
+    for (uint32_t u = 0; u < kPickQuad; ++u) held.en[u] = first[u];
+  } else {
+    load(0, held);
+  }
   // visit(element, whether it exists, first element of the trip) for every element, whole wavefronts at a time
   auto sweep = [&](auto&& visit) {
     constexpr uint32_t kAhead = 4;  // trips requested together
@@ -1597,10 +1602,18 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   const TopkRow* rp = ws.rows + sc.seg;
   const PickRow r{rp->cursor /* a short row's list is kept as one run */, rp->cand_from, rp->b_guess, rp->band_valid,
                   rp->band_lo, rp->band_hi, rp->band_mul, rp->tau, rp->tau_prev};
+  // The list's first trip is requested with it (what the list does not hold is not looked at).
+  const uint2* candr = ws.cand + sc.cand_base;
+  uint2 first[kPickQuad];
+#pragma unroll
+  for (uint32_t u = 0; u < kPickQuad; ++u) {
+    const uint32_t q = u * kPickThreads + threadIdx.x;
+    first[u] = q < opt.cap ? candr[q] : make_uint2(0u, 0u);
+  }
   const bool pred = use_guess && r.cand_from != 0;
   const bool listed = pred && !opt.force_dense && r.n_cand >= geo.k && r.n_cand <= opt.cap;
-  if (listed) pick_row<true>(sh, e, geo, ws, opt, sc, r, pred);  // uniform
-  else pick_row<false>(sh, e, geo, ws, opt, sc, r, pred);
+  if (listed) pick_row<true>(sh, e, geo, ws, opt, sc, r, pred, first);  // uniform
+  else pick_row<false>(sh, e, geo, ws, opt, sc, r, pred, first);
 }
 
 // ---------------------------------------------------------------------------------------------
