@@ -593,7 +593,6 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 // another.  The level-0 histogram is taken afterwards, from the candidate list (k_topk_level0).
 // ---------------------------------------------------------------------------------------------
 constexpr int kLeanRounds = kRounds / kWaves;  // rounds of a chunk per wavefront
-constexpr uint32_t kQuarterCoords = kChunk / kWaves;
 constexpr int kStageQ = 512;                   // staged candidates per wavefront (of at most 1024 coordinates)
 
 // UNI: grid (chunks, rows).  Otherwise (top-k inside every block) the launch is flat over map_first: a workgroup
@@ -1246,7 +1245,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       rowp->r = ties_kept;
       rowp->ties = n_ties;
       rowp->tie_last = ties_after ? last_coord : 0xffffffffu;
-      rowp->bnd_kept = n_kept;
       ws.tau[row] = tau;
       ws.count_gt[row] = k - ties_kept;
       uint32_t* cn = ws.counters + row * kCountersPerRow;
@@ -1621,14 +1619,16 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
 // the row, one workgroup per row.  (What bounds it are the cache lines that one compute unit asks for: 8192 single
 // coordinates take 37 us, in quads 12.7, 4096 in quads 7.7.)
 // The guess is the bucket above which one and a half times the share k / d of the sample lies, plus three deviations of
-// that count and a few entries for small counts: the list then holds k entries or more but for one row in hundreds, and
-// less than the capacity of 8 k + 65536.  It decides only whether the row is read again.  No window is known: the
-// general kernels select, and are told so here.
+// that count and three entries for small counts: the list then holds k entries or more but for one row in hundreds.  A row
+// whose list would not fit by what the sample holds from that bucket upwards (few magnitudes; three of 4096 are more than
+// 65536 entries from 90 M coordinates on) gets no guess: the list would be written and counted for nothing.  It decides only
+// whether the row is read again.  (Eight entries instead of three, and no look at what fits: 34 M coordinates, k = 1000, 362
+// us a call, now 338; 60 M, k = 100000, 580, now 523.)  No window is known: the general kernels select, and are told so here.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kSample = 4096;
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __restrict__ g, const float* __restrict__ e,
-                                                               Geometry geo, TopkWorkspace ws) {
+                                                               Geometry geo, TopkWorkspace ws, TopkOptions opt) {
   __shared__ uint32_t lh[kNB0];
   __shared__ uint32_t suf[kPickThreads + 1];
   __shared__ uint32_t out2[2];
@@ -1639,7 +1639,11 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
   constexpr int kPer = kQuads / kPickThreads;
   static_assert(kQuads % kPickThreads == 0, "whole quads");
   const uint32_t whole_quads = geo.d / 4;  // at least kQuads: the host asks for no sample of a shorter row
-  const uint32_t taken = kSample;
+  if (row == 0 && t == 0) ws.flags[0] = 1;
+  const float each = static_cast<float>(geo.d) / static_cast<float>(kSample);  // coordinates that a sampled one stands for
+  const float share = static_cast<float>(geo.k) / each;
+  const float want = 1.5f * share + 3.0f * sqrtf(share) + 3.0f;
+  if (want >= static_cast<float>(kSample) || want * each > static_cast<float>(opt.cap)) return;  // uniform
   float4 x[kPer];
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
@@ -1658,16 +1662,10 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
     atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].w)) >> kL0Shift], 1u);
   }
   __syncthreads();
-  const float share = static_cast<float>(taken) * (static_cast<float>(geo.k) / static_cast<float>(geo.d));
-  const float want = 1.5f * share + 3.0f * sqrtf(share) + 8.0f;
-  const bool use = want < static_cast<float>(taken);
-  if (row == 0 && t == 0) ws.flags[0] = 1;
-  if (use) {  // uniform
-    find_crossing<kNB0, kPickThreads>(lh, static_cast<uint32_t>(want), suf, out2);
-    if (t == 0) {
-      ws.rows[row].b_guess = out2[0];
-      ws.rows[row].cand_from = (out2[0] << kL0Shift) + 1u;
-    }
+  find_crossing<kNB0, kPickThreads>(lh, static_cast<uint32_t>(want), suf, out2);
+  if (t == 0 && static_cast<float>(out2[1] + lh[out2[0]]) * each <= static_cast<float>(opt.cap)) {
+    ws.rows[row].b_guess = out2[0];
+    ws.rows[row].cand_from = (out2[0] << kL0Shift) + 1u;
   }
 }
 
@@ -2703,7 +2701,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample; 4 rows of 65536,
   // k = 655: the whole call 66 us by the general kernels without a guess, 34.4 with it and one workgroup per row)
   if (whole && geo.d >= kSample) {
-    launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws);
+    launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   if (clear_pending)
