@@ -219,7 +219,6 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.flat.wg_sweep = static_cast<uint32_t>(n * wg_sweep);
     L.flat.wg_count = static_cast<uint32_t>(n * wg_count);
     L.flat.wg_final = static_cast<uint32_t>(chunks);
-    L.flat.band_stride = bcaps;
     L.flat.blocks = static_cast<uint32_t>(M);
     L.flat.chunk_stride = static_cast<uint32_t>(chunks);
     L.flat.seloff_stride = static_cast<uint32_t>(chunks * kWaves + M);

@@ -133,10 +133,10 @@ struct TopkRow {
   uint32_t tau_prev;       // the threshold key of the step before (0: none)
   uint32_t above;          // entries at or above band_hi (a list kept as one run; else in the runs' cursor lines)
   uint32_t bnd_n;          // entries of the threshold's bucket gathered so far (k_topk_band); zero between launches
-  uint32_t bnd_kept;       // fast: how many of them are kept; their coordinates, ascending, are in bnd_sel
   uint32_t ticket_band;    // "last workgroup" counter of k_topk_band; zero between launches
   float noise;             // not taken by k_topk_band: what its window's population says of the threshold's scatter (0:
                            // there was no window)
+  uint32_t known_from;     // general route: see set_next_band()
   uint32_t pad[26];
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
@@ -326,7 +326,7 @@ struct TopkFlat {
   uint32_t wg_first, wg_level0, wg_sweep, wg_count, wg_final;
   // from worker i's segment of a block to worker i + 1's: segment index, chunk tables, list offsets, candidates
   uint32_t blocks, chunk_stride, seloff_stride;
-  uint64_t cand_stride, band_stride;
+  uint64_t cand_stride;
 };
 hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                             const TopkFlat& flat, const float* g, float* e, float* theta, float* m, float* v,

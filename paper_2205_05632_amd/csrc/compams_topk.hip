@@ -853,6 +853,13 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
 // the bucket guess the next first pass will use; the window must lie at or above it so that every band entry is
 // also a candidate.
 // ---------------------------------------------------------------------------------------------
+// A step's list held n entries, every key from list_from upwards; the guess for the next step may lie below that, where
+// nothing is known, and is taken to add at most as many again.  Where even that would not leave room to spare, the key
+// that a list without a window should start at: the present list's first (0: the guess's own).
+__device__ __forceinline__ uint32_t known_from(uint32_t guess, uint32_t list_from, uint32_t n, uint32_t cap) {
+  return (guess << kL0Shift) < list_from && n > cap / 4 ? list_from : 0u;
+}
+
 __device__ __forceinline__ float default_band_noise(uint32_t k) { return 1.5f / sqrtf(static_cast<float>(k)); }
 
 __device__ __forceinline__ bool normal_key(uint32_t key) { return key >= 0x00800000u && key < 0x7f000000u; }
@@ -862,9 +869,10 @@ __device__ __forceinline__ bool normal_key(uint32_t key) { return key >= 0x00800
 // list and costs the general kernels' sweeps (50 us), not two more reads of every row (470 us).  (Without the limit the
 // wide windows of a run's first steps make lists so long that the next step is given no guess.)
 
+// known_from: where no window follows, the next list starts there if that is above the guess's first key (see known_from()).
 __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint32_t tau_prev, uint32_t tau_prev2,
-                                              uint32_t guess_valid, uint32_t guess, float noise, uint32_t k,
-                                              const TopkOptions& opt) {
+                                              uint32_t guess_valid, uint32_t guess, uint32_t known_from, float noise,
+                                              uint32_t k, const TopkOptions& opt) {
   uint32_t valid = 0, lo = 0, hi = 0;
   uint32_t from = guess << kL0Shift;  // the first key that the next first pass lists
   float delta_set = 0.0f;
@@ -897,6 +905,7 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
     const uint32_t margin = __float_as_uint(centre * (1.0f - delta - fminf(0.5f * delta, 0.02f)));
     if (valid && margin > from) from = margin;
   }
+  if (!valid && known_from > from) from = known_from;
   rowp->cand_from = guess_valid ? from + 1u : 0u;
   // Buckets of the window's histogram: the population of the last window (noise is 8 w sqrt(k) / B) says how many
   // entries this one will hold; beyond 16 to a bucket of the few it gets the many.
@@ -998,6 +1007,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       total_above += ws.xcur[(static_cast<size_t>(sc.cursor_set) * kSubLists + s) * kCursorPitch + kCursorAboveWord];
   }
   const uint32_t blo = rowp->band_lo, bhi = rowp->band_hi, bmul = rowp->band_mul, bg = rowp->b_guess;
+  const uint32_t list_from = rowp->cand_from - 1u;  // (with a candidate list)
   const uint32_t tau_before = rowp->tau, tau_before2 = rowp->tau_prev;  // the last two threshold keys (asked for
                                                                        // here: the last workgroup needs them)
   const ListRuns cand = runs_from_cursors(ws, rowp, sc.cursor_set, opt.cap);
@@ -1164,7 +1174,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   // ---- 3. the problem-wide part, by whichever of its workgroups finishes last ----
   if (!last_group_of_row(&rowp->ticket_band, sc.groups, &sh_flag)) return;
   for (uint32_t b = t; b < buckets; b += kWG) bh_used[b] = 0;  // every workgroup has read it
-  uint32_t n_kept = 0;
   if (inside) {
     // the gathered entries (written by other workgroups with device-scope stores: read at that scope)
     const uint2* bnd = ws.bnd + static_cast<size_t>(row) * kBoundaryCap;
@@ -1223,7 +1232,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     }
     __syncthreads();
     const uint32_t n_ties = suf[0];
-    n_kept = need;
     uint32_t* sel = ws.bnd_sel + static_cast<size_t>(row) * kBoundaryCap;
     if (t < kBoundaryCap) sel[t] = b_rank[t];
     if (t < sc.groups) {
@@ -1255,8 +1263,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
       cn[4] = band.total;
       cn[5] = 0;
       // Guess for the next step, as the general route sets it but from what is known here: the candidate list held
-      // cand.total entries at or above bucket bg, so that many bound the entries from any bucket >= bg upwards;
-      // of the bucket below bg nothing is known, and it is taken to hold at most as many again.
+      // cand.total entries, every key from a key of bucket bg or above upwards.  Below that nothing is known: the bucket
+      // below bg is taken to hold at most as many again, what bg itself holds below the list is left to known_from().
       const uint32_t b0 = tau >> kL0Shift;  // >= bg
       uint32_t valid = 0, guess = 0;
       if (opt.predict) {
@@ -1265,7 +1273,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         else if (cand.total <= opt.cap / 2) { valid = 1; guess = b0; }
       }
       rowp->b_guess = guess;
-      set_next_band(rowp, tau, tau_prev, tau_before2, valid, guess, noise, k, opt);
+      set_next_band(rowp, tau, tau_prev, tau_before2, valid, guess, known_from(guess, list_from, cand.total, opt.cap), noise, k,
+                    opt);
     }
   } else if (t == 0) {
     rowp->fast = kFastNot;
@@ -1577,7 +1586,7 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
   cn[4] = miss ? 0u : in_window;
   cn[5] = miss;
   // Guess and window for the next step, as the other routes set them; from a list nothing is known below its lower
-  // end, and the bucket below the guess it was made with is taken to hold at most as many entries as all above it.
+  // end: the bucket below the guess it was made with is taken to hold at most as many entries as all above it.
   uint32_t valid = 0, guess = 0;
   if (opt.predict && !opt.force_dense) {
     const uint32_t at_hand = LISTED ? n_cand : total;
@@ -1590,7 +1599,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
   if (miss == 0 && in_window && normal_key(tau))
     noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
             static_cast<float>(in_window);
-  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, noise, k, opt);
+  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, LISTED ? known_from(guess, cand_lo, n_cand, opt.cap) : 0u,
+                noise, k, opt);
 }
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
@@ -1773,14 +1783,15 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
     rowp->level1_done = 0;
     // Guess for the next step: one bucket below this step's threshold bucket if the list that guess would
     // have produced now fits with room to spare, else the bucket itself, else no guess.  From a list, nothing
-    // is known about the buckets below the guess it was made with: the bucket below is then taken to hold at
-    // most as many entries as all the buckets above it together.
+    // is known below its first key: the bucket below the guess it was made with is then taken to hold at most as many
+    // entries as all the buckets above it together, what that guess's bucket holds below the list is left to known_from().
     uint32_t valid = 0, guess = 0;
     if (opt.predict && !opt.force_dense) {
       const uint32_t below = bstar ? ((listed && bstar == bg) ? total : lh[bstar - 1]) : 0;
       if (bstar && total + below <= opt.cap / 2) { valid = 1; guess = bstar - 1; }
       else if (total <= opt.cap / 2) { valid = 1; guess = bstar; }
     }
+    rowp->known_from = listed ? known_from(guess, rowp->cand_from - 1u, runs.total, opt.cap) : 0u;
     rowp->cand_from = valid ? (guess << kL0Shift) + 1u : 0u;
     rowp->b_guess = guess;
     uint32_t* cn = ws.counters + row * kCountersPerRow;
@@ -1947,7 +1958,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level2(const float* __restrict__ e
     cn[3] = r;
     cn[4] = 0;
     // the guess was set when the threshold bucket was found (first kernel of this route, an earlier launch)
-    set_next_band(rowp, tau, tau_prev, tau_prev2, rowp->cand_from != 0 ? 1u : 0u, rowp->b_guess,
+    set_next_band(rowp, tau, tau_prev, tau_prev2, rowp->cand_from != 0 ? 1u : 0u, rowp->b_guess, rowp->known_from,
                   rowp->noise > 0.0f ? rowp->noise : default_band_noise(geo.k), geo.k, opt);
   }
 }

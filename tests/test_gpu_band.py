@@ -213,3 +213,29 @@ def test_windows_of_many_and_of_few_buckets(n, d, k):
         assert (used > 32768).any(), used
     assert all(p.exact.values()), p.exact
     p.close()
+
+
+@pytest.mark.parametrize("d", [10 * 4096, 30 * 4096])
+def test_a_list_without_a_window_keeps_to_what_is_known_to_fit(d):
+    """A step's list says nothing of the keys below its first one.  When no window follows, and entries have crowded in
+    right below, the next list starts where this one did: rows selected by one workgroup and by the band kernel."""
+    n, k = 2, 2000
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d, np.float32), B.TOPK, k=k)
+    p.gpu.set_option(B.OPT_CANDIDATE_CAP, 4800)
+    used = []
+    for t in range(8):
+        x = rng.uniform(0.001, 0.01, size=(n, d)).astype(np.float32)
+        for row in x:
+            at = rng.choice(d, size=8100, replace=False)
+            row[at[:600]] = rng.uniform(1.07, 2.0, size=600)
+            row[at[600:2100]] = rng.uniform(1.03, 1.07, size=1500)   # the threshold is among these
+            if t >= 5:                                               # ... and these lie a bucket of a sixteenth below
+                row[at[2100:]] = rng.uniform(0.97, 0.999, size=6000)
+        if t == 5:
+            p.gpu.set_option(B.OPT_BAND, 0)
+        p.step((x - p.cpu.get("e")).astype(np.float32), 1e-3, label=f"step {t}", with_e=False)
+        torch.cuda.synchronize()
+        used.append(p.gpu.compams_state("counters").cpu().numpy()[:, [0, 1, 5]].tolist())
+    assert all(c[0] == 0 for step in used[3:] for c in step), used
+    p.close()
