@@ -167,8 +167,12 @@ enum {
 enum {
   COMPAMS_CNT_DENSE_READS = 0, /* how many times the step read the whole row of corrected gradients back
                                   (0: candidates came out of the first pass; 1: the candidate list had to be made
-                                  from the stored row; 4: no candidate list) */
-  COMPAMS_CNT_CANDIDATES = 1,  /* entries in the candidate list, 0 if none was used */
+                                  from the stored row; 4: no candidate list).  Rows of up to 65536 coordinates
+                                  that are selected without the first pass's list: 1 if a list of the entries
+                                  from the threshold's bucket upwards would have fitted, else 4; no list is made of
+                                  them and the row is read more or less often than that */
+  COMPAMS_CNT_CANDIDATES = 1,  /* entries in the candidate list (of those rows: that such a list would have), 0 if none
+                                  was used (would have fitted) */
   COMPAMS_CNT_TIES = 2,        /* coordinates whose key equals the threshold key */
   COMPAMS_CNT_TIES_TAKEN = 3,  /* how many of those were selected */
   COMPAMS_CNT_BAND = 4,        /* entries in the band list if the threshold key was found there (the selection then

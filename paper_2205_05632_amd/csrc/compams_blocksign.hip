@@ -376,6 +376,9 @@ inline bool scales_in_first_pass(const Geometry& geo, const BlocksignWorkspace& 
 
 // The scales of a row's blocks by one workgroup, from digits that other workgroups of the same launch have added to (with
 // device-scope atomics): read at that scope, all of them at once, and added up in LDS over the sets of a block.
+// It writes ws.scales, which the row's workgroups read through the scalar path in the same launch (the previous step's
+// means).  They have all read it by then: the sums that a wavefront adds to the digits are formed from those means, and
+// it waits for its own additions before the row's ticket is drawn.  Nothing reads the means again after that.
 __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, const BlocksignWorkspace& ws) {
   __shared__ unsigned long long sums[kBsScalesBlocks * kLimbs];
   const uint32_t t = threadIdx.x, M = geo.num_blocks, R = ws.acc_replicas;

@@ -97,9 +97,10 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_a
 
 // A table entry at a wave-uniform index, read through the scalar path: the tables read this way (block offsets,
 // chunk-to-block map, the previous step's means and list offsets, a row's carried-over guess) are not
-// written by the kernel that reads them, and a scalar load has its own counter, so waiting for it does not mean
-// waiting for the vector loads that are in flight (a vector load here stalled the stream once per chunk); what
-// it returns sits in scalar registers.
+// written by the kernel that reads them while anybody may still read them, and a scalar load has its own counter, so
+// waiting for it does not mean waiting for the vector loads that are in flight (a vector load here stalled the stream
+// once per chunk); what it returns sits in scalar registers.  (The one table written in the launch that reads it: the
+// block means of a short row, by its last workgroup, see row_scales.)
 typedef const __attribute__((address_space(4))) uint32_t* ScalarTable;
 __device__ __forceinline__ uint32_t table_u32(const uint32_t* p, uint32_t i) {
   return reinterpret_cast<ScalarTable>(reinterpret_cast<uintptr_t>(p))[i];
