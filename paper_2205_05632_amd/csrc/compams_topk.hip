@@ -2670,7 +2670,8 @@ __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e,
 
 namespace {
 
-// The last kernel with NW wavefronts per chunk.
+// The last kernel with NW wavefronts per chunk.  (Grids of sixteen always keep all four state arrays cached, unless the
+// context's option says otherwise.)
 template <int ROLE, bool UNI, int NW, bool CLEAR, typename... Args>
 void launch_final_of(int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
   const dim3 grid(workgroups), wg(NW * 64);
