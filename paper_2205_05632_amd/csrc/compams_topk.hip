@@ -1360,8 +1360,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
   const uint32_t tau_before = in_row.tau, tau_before2 = in_row.tau_prev;
   const bool windowed = pred && opt.band && in_row.band_valid != 0;
   const uint32_t count = LISTED ? n_cand : geo.d;
-  // A trip takes kPickQuad elements of every thread: entries of the list 1024 apart, or a quad of the row's coordinates (a
-  // trip is then a chunk).
+  // A trip takes kPickQuad elements of every thread: entries of the list 1024 apart, or (from the second trip on) a quad of the
+  // row's coordinates; over the row it is a chunk.
   struct Trip { uint2 en[kPickQuad]; };
   constexpr uint32_t kTripElements = kPickQuad * kPickThreads;
   static_assert(kTripElements == kChunk, "a trip over the row is a chunk");
@@ -1379,19 +1379,20 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
       to.en[3] = make_uint2(j + 3, __float_as_uint(x.w));
     }
   };
-  Trip held;  // the first trip stays in registers
-  if constexpr (LISTED) {
+  // The first trip stays in registers, elements 1024 apart also of the row: a row of a few hundred coordinates is then one
+  // element of a thread (8 x 5 coordinates: 17.5 us a step as quads, 16.5 so; 8 x 100 20.8 / 19.4).
+  Trip held;
 #pragma unroll
-    for (uint32_t u = 0; u < kPickQuad; ++u) held.en[u] = first[u];
-  } else {
-    load(0, held);
+  for (uint32_t u = 0; u < kPickQuad; ++u) {
+    const uint32_t q = u * kPickThreads + t;
+    held.en[u] = LISTED ? first[u] : q < count ? make_uint2(q, __float_as_uint(er[q])) : make_uint2(0u, 0u);
   }
   // visit(element, whether it exists, first element of the trip) for every element, whole wavefronts at a time
   auto sweep = [&](auto&& visit) {
     constexpr uint32_t kAhead = 4;  // trips requested together
 #pragma unroll
     for (uint32_t u = 0; u < kPickQuad; ++u)
-      if (!LISTED || u * kPickThreads < count) visit(held.en[u], number(0, u) < count, 0u);  // uniform
+      if (u * kPickThreads < count) visit(held.en[u], u * kPickThreads + t < count, 0u);  // uniform
 #pragma unroll 1
     for (uint32_t q0 = kTripElements; q0 < count; q0 += kAhead * kTripElements) {
       Trip trip[kAhead];
@@ -1610,13 +1611,15 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
   const TopkRow* rp = ws.rows + sc.seg;
   const PickRow r{rp->cursor /* a short row's list is kept as one run */, rp->cand_from, rp->b_guess, rp->band_valid,
                   rp->band_lo, rp->band_hi, rp->band_mul, rp->tau, rp->tau_prev};
-  // The list's first trip is requested with it (what the list does not hold is not looked at).
+  // The list's first trip is requested with it (what the list does not hold is not looked at).  Every thread loads, the same
+  // entry again where there is none: behind a condition the compiler masked the sign inside it, and the four loads waited
+  // for each other (4 x 65536, k = 655: 24.8 us a step so, 24.3 as here).
   const uint2* candr = ws.cand + sc.cand_base;
   uint2 first[kPickQuad];
 #pragma unroll
   for (uint32_t u = 0; u < kPickQuad; ++u) {
     const uint32_t q = u * kPickThreads + threadIdx.x;
-    first[u] = q < opt.cap ? candr[q] : make_uint2(0u, 0u);
+    first[u] = candr[q < opt.cap ? q : 0u];
   }
   const bool pred = use_guess && r.cand_from != 0;
   const bool listed = pred && !opt.force_dense && r.n_cand >= geo.k && r.n_cand <= opt.cap;
