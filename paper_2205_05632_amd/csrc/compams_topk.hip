@@ -2318,7 +2318,9 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
   const uint32_t c_len = f.d_loc - c_lo < kChunk ? f.d_loc - c_lo : kChunk;
   const uint32_t q_lo = c_lo + wave * kPart;                              // this wavefront's part of it
   if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = 0;  // the general kernels have run
-  if (ROLE != kServerHalf && c == 0)  // the next step's first pass allocates its candidate lists from the start
+  // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
+  const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
+  if (ROLE != kServerHalf && c == 0 && i_first == 0)  // the next step's first pass allocates its candidate lists from the start
     for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {
       ws.rows[f.row0 + i * f.row_stride].cursor = 0;
       ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
@@ -2356,7 +2358,7 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
   struct Slots { uint2 en[kSlots]; };
 
 #pragma unroll 1
-  for (uint32_t i0 = 0; i0 < geo.n; i0 += kTileWorkers) {
+  for (uint32_t i0 = i_first; i0 < geo.n; i0 += kTileWorkers) {
     if (!listed) {  // uniform
       // ---- selecting: this wavefront's workers are those at lanes wave, wave + NW, ... ----
       const bool have = lane < kTileWorkers && (lane & (NW - 1)) == wave && i0 + lane < geo.n;
@@ -2525,7 +2527,7 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
 #pragma unroll
       for (int w = 1; w <= kWaves; ++w) so[w] = f.k_loc;
     }
-    if (ROLE == kWorkerHalf) continue;
+    if (ROLE == kWorkerHalf) return;
     if (!listed) __syncthreads();
 
     // ---- adding ----
@@ -2676,10 +2678,13 @@ namespace {
 // The last kernel with NW wavefronts per chunk.  (Grids of sixteen always keep all four state arrays cached, unless the
 // context's option says otherwise.)
 template <int ROLE, bool UNI, int NW, bool CLEAR, typename... Args>
-void launch_final_of(int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
+void launch_final_of(uint32_t n, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
   const dim3 grid(workgroups), wg(NW * 64);
-  if constexpr (ROLE == kWorkerHalf) {  // (no state)
-    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR>, grid, wg, stream, args...);
+  if constexpr (ROLE == kWorkerHalf) {
+    // No state, and no order among the workers: a workgroup per tile of them.  With all tiles in one workgroup a few chunks
+    // leave the chip idle (50000 coordinates in seven blocks: the half of 300 workers 128 us / 76 as here, of 64 52 / 45).
+    const dim3 grid_tiles(workgroups, (n + kTileWorkers - 1) / kTileWorkers);
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR>, grid_tiles, wg, stream, args...);
   } else if constexpr (CLEAR && NW == kFinalFew) {  // (so short that its whole state stays in the memory-side cache)
     launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR>, grid, wg, stream, args...);
   } else {
@@ -2692,9 +2697,9 @@ void launch_final_of(int cached_arrays, Launcher* L, uint32_t workgroups, hipStr
 template <int ROLE, bool UNI, bool CLEAR, typename... Args>
 void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
   switch (final_wavefronts(workgroups, geo, !UNI)) {
-    case kFinalFew: launch_final_of<ROLE, UNI, kFinalFew, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
-    case kFinalSome: launch_final_of<ROLE, UNI, kFinalSome, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
-    default: launch_final_of<ROLE, UNI, kFinalMany, CLEAR>(cached_arrays, L, workgroups, stream, args...); break;
+    case kFinalFew: launch_final_of<ROLE, UNI, kFinalFew, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
+    case kFinalSome: launch_final_of<ROLE, UNI, kFinalSome, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
+    default: launch_final_of<ROLE, UNI, kFinalMany, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
   }
 }
 
@@ -2808,7 +2813,7 @@ hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const 
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
   const TopkFlat none{};
-  launch_final_of<kServerHalf, true, kFinalMany, false>(ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
+  launch_final_of<kServerHalf, true, kFinalMany, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
                                                         ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;

@@ -93,3 +93,58 @@ def test_the_identity_compressor_has_no_halves():
     with pytest.raises(B.CompamsError):
         c.compams_worker_step(torch.zeros((2, c.ld), device=c.device))
     c.close()
+
+
+@pytest.mark.parametrize("n", [1, 16, 17, 33])
+def test_workers_half_of_block_topk_over_tiles_of_workers(n):
+    """The workers' half has a workgroup per chunk and tile of sixteen workers: lists, values, residuals and the counters
+    that the next step starts from, bit for bit."""
+    rng = np.random.default_rng(n)
+    off = np.array([0, 20, 1044, 5140, 5144, 20000, 36388], dtype=np.int64)
+    kb = np.array([1, 1024, 41, 4, 3000, 100], dtype=np.int64)
+    d = int(off[-1])
+    theta0 = np.zeros(d, dtype=np.float32)
+    gpu = B.Compams(n, d, torch.from_numpy(theta0), compressor=B.TOPK_BLOCKS, block_offsets=off, block_k=kb)
+    cpu = O.Oracle(n, d, theta0, compressor=O.TOPK_BLOCKS, block_offsets=off, block_k=kb)
+    for t in range(4):
+        g = rng.standard_normal((n, d), dtype=np.float32) * np.float32(8.0 if t == 3 else 1.0)
+        gp = torch.zeros((n, gpu.ld), dtype=torch.float32)
+        gp[:, :d] = torch.from_numpy(g)
+        gpu.compams_worker_step(gp.to(gpu.device))
+        cpu.step(g, 1e-3)
+        torch.cuda.synchronize()
+        assert np.array_equal(gpu.compams_state("last_idx").cpu().numpy(), cpu.get("idx")), f"step {t}: lists"
+        assert bits_equal(gpu.compams_state("last_val").cpu().numpy(), cpu.get("val")), f"step {t}: values"
+    assert bits_equal(np.ascontiguousarray(gpu.compams_state("e").cpu().numpy()), cpu.get("e")), "residuals"
+    assert bits_equal(gpu.compams_state("theta").cpu().numpy(), theta0)
+    gpu.close()
+    cpu.close()
+
+
+def test_workers_half_does_not_go_through_the_tiles_one_after_the_other():
+    """300 workers in few chunks: the half alone is far from the whole step, which also adds every list (with all tiles of
+    workers in one workgroup 128 of 201 us or worse; with a workgroup per tile 76)."""
+    n, d = 300, 50000
+    off = np.array([0, 400, 1200, 4000, 8000, 16000, 32000, d], dtype=np.int64)
+    kb = np.diff(off) // 100
+    ctx = B.Compams(n, d, torch.zeros(d), compressor=B.TOPK_BLOCKS, block_offsets=off, block_k=kb)
+    g = [torch.randn((n, ctx.ld), device=ctx.device) for _ in range(3)]
+
+    def us(call):
+        for i in range(9):
+            call(g[i % 3])
+        times = []
+        for _ in range(7):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for i in range(20):
+                call(g[i % 3])
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end) / 20 * 1e3)
+        return sorted(times)[3]
+
+    whole = us(lambda x: ctx.compams_step(x, 1e-3))
+    half = us(ctx.compams_worker_step)
+    assert half < 0.55 * whole, (half, whole)
+    ctx.close()
