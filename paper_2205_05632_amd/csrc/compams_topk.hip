@@ -2246,8 +2246,8 @@ inline int final_wavefronts(uint32_t workgroups, const Geometry& geo, bool unifo
 // quarter's slice of each list starts was found by the unpacking).
 enum : int { kWholeStep = 0, kWorkerHalf = 1, kServerHalf = 2 };
 
-// UNI: one selection problem per worker over its whole row, one workgroup per chunk of the row.  !UNI (whole step
-// only): top-k inside every block; a workgroup takes one chunk of one block (flat launch over map_final) and goes
+// UNI: one selection problem per worker over its whole row, one workgroup per chunk of the row.  !UNI (not in
+// the server's half): top-k inside every block; a workgroup takes one chunk of one block (flat launch over map_final) and goes
 // through the workers' segments of that block, which lie a fixed stride apart in every table.
 struct FinalCtx {
   uint32_t c;                     // chunk of the problem
