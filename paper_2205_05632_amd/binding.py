@@ -104,15 +104,19 @@ def _current_stream_handle() -> int:
     return torch.cuda.current_stream().cuda_stream
 
 
+_CUDA = torch.device("cuda")
+_CUDA_AT = tuple(torch.device("cuda", i) for i in range(128))  # (an index of torch's has seven bits)
+
+
 def _on_stream(device: torch.device, call, *args) -> int:
     """call(*args, handle of `device`'s current stream) with `device` current.  A step of a small model takes about
     10 us: the device is switched only if another one is current, and the stream's handle is asked for without the
     Python object around it (4 us less than a torch.cuda.device block and torch.cuda.current_stream()).  Another
     device than a GPU is refused as that block refuses it: its index is None too, and the call would be handed pointers
-    into host memory."""
-    if device.type != "cuda":
-        raise ValueError(f"Expected a cuda device, but got: {device}")
+    into host memory.  (Compared with a device: device.type makes a string, 0.2 us of a small call's 5.)"""
     index = device.index
+    if device != (_CUDA if index is None else _CUDA_AT[index]):
+        raise ValueError(f"Expected a cuda device, but got: {device}")
     if index is None or index == torch._C._cuda_getDevice():
         return call(*args, torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     with torch.cuda.device(device):

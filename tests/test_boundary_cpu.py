@@ -208,7 +208,7 @@ class _Tensor:
         return 64
 
 
-@pytest.mark.parametrize("device", ["cpu", "meta"])
+@pytest.mark.parametrize("device", ["cpu", "meta", "cpu:0", "meta:3"])
 def test_residual_outside_a_gpu_is_refused_before_the_call(monkeypatch, device):
     """The pointers of such a tensor would reach the kernels: nothing on the C side can tell them from device ones."""
     called = []
