@@ -21,6 +21,15 @@ constexpr int kWaves = kWG / 64;
 constexpr int kChunk = 4096;             // coordinates per chunk
 constexpr int kRounds = kChunk / 256;    // rounds per chunk
 
+// Which part of memory a die works on.  Consecutive workgroups run on the eight dies (XCDs) in turn, and the memory
+// channels follow each other through every span of eight 4 KB pages.  Where the workgroups of a die always take the same page
+// of a span, each channel is asked by one die only: a first pass's traffic (two arrays read, one written, 2.1 GB) streams at
+// 6.75 TB/s so, at 6.2 with a workgroup per 16 KB in address order, at 6.05 with pages that change from group to group (pages
+// of 1 and 2 KB do as well, 512 B 6.6, 256 B 5.9).  A page is a quarter of a chunk: one wavefront's part of the dense passes.
+constexpr uint32_t kPageCoords = 1024;
+constexpr uint32_t kDies = 8;
+constexpr uint32_t kSpanCoords = kDies * kPageCoords;  // two chunks
+
 // Radix levels over the 31-bit magnitude key (fp32 bit pattern without the sign):
 // level 0 = bits 30..19 (the exponent and 4 mantissa bits), level 1 = bits 18..9, level 2 = bits 8..0.
 constexpr int kL0Shift = 19;

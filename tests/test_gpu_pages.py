@@ -1,0 +1,43 @@
+"""The dense passes in pages (a die's workgroups take the same 4 KB page of every 32 KB span) at the sizes where the walk
+could miss or repeat something: one page more or less than a span, a group of spans or a group of workgroups; rows whose
+sign words start on 32 bytes (pages) and rows whose do not (address order); magnitudes that leave a quarter's window.
+Everything is compared with the oracle bit for bit, as every operation is fixed."""
+import numpy as np
+import pytest
+
+from paper_2205_05632_amd import binding as B
+
+from parity import Pair
+
+pytestmark = pytest.mark.gpu
+PAGE, SPAN, GROUP = 1024, 8192, 32768
+
+
+def values(rng, n, d, kind):
+    g = rng.standard_normal((n, d)).astype(np.float32)
+    if kind == "zeros":            # whole quarters of zeros, single ones elsewhere
+        g[:, : d // 2] = 0.0
+        g[rng.random((n, d)) < 0.1] = 0.0
+    elif kind == "wide":           # far below a window of 22 exponents, denormals among them
+        g *= (2.0 ** rng.integers(-140, 3, (n, d))).astype(np.float32)
+    elif kind == "special":
+        g[:, d // 3] = np.inf
+        g[:, d // 2] = -np.inf
+        g[n // 2, (2 * d) // 3] = np.nan
+    elif kind == "ends":           # every quarter's largest magnitude just below a power of two, the others 2^-21 of it
+        g = np.where(np.arange(d) % PAGE == 0, np.float32(2.0 - 2.0 ** -23), np.float32(2.0 ** -21)) * np.sign(g + 0.5)
+    return g.astype(np.float32)
+
+
+def run(p, n, d, kind, steps=3, with_e=True):
+    rng = np.random.default_rng(d + n)
+    for t in range(steps):
+        p.step(values(rng, n, d, kind), 1e-3, label=f"{n} x {d} {kind} step {t}", with_e=with_e or t == steps - 1)
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
+@pytest.mark.parametrize("d", [1, 255, 1027, SPAN, GROUP - 1, GROUP, GROUP + 1, 3 * GROUP + SPAN + 5])
+def test_identity_sizes(n, d):
+    run(Pair(n, d, np.ones(d, np.float32), B.NONE), n, d, "plain", with_e=False)
