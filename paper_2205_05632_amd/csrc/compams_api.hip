@@ -575,6 +575,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
     b.ticket = reinterpret_cast<uint32_t*>(w + lay.ticket);
     b.scales = reinterpret_cast<float*>(w + lay.scales);
     b.bits = reinterpret_cast<uint32_t*>(w + lay.bits);
+    b.paged = geo.words % 8 == 0 || geo.n == 1 ? 1u : 0u;
     std::vector<uint32_t> off32, cb;
     try {
       off32.resize(static_cast<size_t>(cfg->num_blocks) + 1);

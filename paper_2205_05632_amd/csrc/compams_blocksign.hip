@@ -48,14 +48,37 @@ __device__ __forceinline__ Fixed to_fixed(uint32_t bits) {
   return f;
 }
 
+// Sum / largest over the wavefront, the same in every lane: neighbours, quads and halves of each row of 16 lanes, then the rows'
+// last lanes into the rows after them (data-parallel moves: three vector instructions a step, where a step through the LDS
+// crossbar waits for it).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t moved(uint32_t v) {  // 0 where nothing arrives
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t moved64(uint64_t v) {
+  return (static_cast<uint64_t>(moved<CTRL, ROWS>(static_cast<uint32_t>(v >> 32))) << 32) |
+         moved<CTRL, ROWS>(static_cast<uint32_t>(v));
+}
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
-    const uint32_t lo = __shfl_xor(static_cast<uint32_t>(v), s, 64);
-    const uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), s, 64);
-    v += (static_cast<uint64_t>(hi) << 32) | lo;
-  }
-  return v;
+  v += moved64<0xB1, 0xF>(v);   // lanes ^ 1
+  v += moved64<0x4E, 0xF>(v);   // lanes ^ 2
+  v += moved64<0x141, 0xF>(v);  // mirrored in each half row
+  v += moved64<0x140, 0xF>(v);  // mirrored in each row
+  v += moved64<0x142, 0xA>(v);  // row 0 into 1, row 2 into 3
+  v += moved64<0x143, 0xC>(v);  // rows 0 and 1 into 2 and 3
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(v), 63);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(v >> 32), 63);
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max(v, moved<0xB1, 0xF>(v));
+  v = max(v, moved<0x4E, 0xF>(v));
+  v = max(v, moved<0x141, 0xF>(v));
+  v = max(v, moved<0x140, 0xF>(v));
+  v = max(v, moved<0x142, 0xA>(v));
+  v = max(v, moved<0x143, 0xC>(v));
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 __device__ __forceinline__ void atomic_add_u64(uint64_t* p, uint64_t v) {
@@ -65,7 +88,7 @@ __device__ __forceinline__ void atomic_add_u64(uint64_t* p, uint64_t v) {
 // Register accumulator of a lane: an fp64 sum over a window of kWinSpan binary exponents, placed by the
 // wavefront (wave-uniform) so that it ends at the largest magnitude of the coordinates it is about to add.
 // Every |x| in the window is an integer below 2^(24 + kWinSpan - 1) = 2^45 times the window's quantum
-// 2^(lowest exponent - 150), so the fp64 sum of up to kWinAdds = 2^8 of them (a lane adds 16) is below 2^53
+// 2^(lowest exponent - 150), so the fp64 sum of up to kWinAdds = 2^6 of them (a lane adds 16) is below 2^51
 // quanta: every addition is exact and their order does not matter.  The sum then becomes an integer again, is
 // added over the wavefront and goes to the global digits.  Entries below the window (more than 2^21 below the
 // largest magnitude: rare) and non-finite ones go straight to the global digits and flags.
@@ -74,8 +97,8 @@ __device__ __forceinline__ void atomic_add_u64(uint64_t* p, uint64_t v) {
 // (One window of 22 exponents replaced two of 17: per entry one compare, one select, one conversion and one
 // addition instead of twice that and a second range test.)
 constexpr uint32_t kWinSpan = 22;
-constexpr uint32_t kWinAdds = 256;
-static_assert(24 + kWinSpan - 1 + 8 <= 53, "a window's sum must stay an exact integer in fp64");
+constexpr uint32_t kWinAdds = 64;
+static_assert(24 + kWinSpan - 1 + 6 < 52, "a window's sum must stay an exact integer in fp64, and 2^52 more than it");
 
 struct WaveAcc {
   double sum;       // sum of the window
@@ -88,12 +111,11 @@ __device__ __forceinline__ void acc_reset(WaveAcc& A) {
   A.sum = 0.0; A.eh = 1; A.klo = 0; A.kspan = 0;
 }
 
-// Places the window so that it ends `headroom` exponents above the largest finite magnitude key kmax_key
-// seen so far (wave-uniform).  Its top exponent is at most 254: infinities and NaNs are never inside.
-__device__ __forceinline__ void acc_place(WaveAcc& A, uint32_t kmax_key, uint32_t headroom) {
+// Places the window so that it ends at the largest finite magnitude key kmax_key (wave-uniform).  Its top exponent is at
+// most 254: infinities and NaNs are never inside.
+__device__ __forceinline__ void acc_place(WaveAcc& A, uint32_t kmax_key) {
   uint32_t top = kmax_key >> 23;
   top = top ? top : 1u;
-  top = top + headroom > 254u ? 254u : top + headroom;
   A.eh = top >= kWinSpan ? top - (kWinSpan - 1u) : 1u;
   A.klo = A.eh == 1u ? 0u : A.eh << 23;
   A.kspan = ((A.eh + kWinSpan) << 23) - A.klo;
@@ -103,8 +125,11 @@ __device__ __forceinline__ void acc_place(WaveAcc& A, uint32_t kmax_key, uint32_
 // lane 0, into the digits: bit position e_low - 1 above 2^-149, i.e. digit (e_low - 1) / 32 and up.
 // In line: once per wavefront, and a call would pass its arguments through scratch memory.
 __device__ __forceinline__ void window_to_digits(double sum, uint32_t e_low, uint64_t* digits) {
-  const uint64_t mine = static_cast<uint64_t>(ldexp(sum, 150 - static_cast<int>(e_low)));  // exact, below 2^53
-  const uint64_t all = wave_sum_u64(mine);                                                 // below 2^59
+  // times 2^(150 - e_low), exactly an integer below 2^52, which 2^52 more shows in the mantissa
+  const double scale = __longlong_as_double(static_cast<long long>(1023u + 150u - e_low) << 52);
+  const uint64_t mine = static_cast<uint64_t>(__double_as_longlong(__builtin_fma(sum, scale, 4503599627370496.0))) &
+                        0xfffffffffffffull;
+  const uint64_t all = wave_sum_u64(mine);  // below 2^58
   if (lane_id() == 0 && all) {
     const uint32_t sh = e_low - 1u, w = sh >> 5, s = sh & 31u;
     const uint64_t low = all << s, high = s ? all >> (64u - s) : 0ull;
@@ -184,36 +209,8 @@ __device__ __forceinline__ double fixed192_to_double(uint64_t w0, uint64_t w1, u
 // ---------------------------------------------------------------------------------------------
 // Pass 1: x = e + g -> e, the sign words of x and the exact block sums.
 // ---------------------------------------------------------------------------------------------
-constexpr int kBsBatch = 4;
 constexpr int kQuarter = kRounds / kWaves;  // rounds of a chunk per wavefront when a workgroup takes one chunk
-static_assert(kQuarter == kBsBatch, "a wavefront's quarter of a chunk is one batch of loads");
 static_assert(kQuarter * 4 <= static_cast<int>(kWinAdds), "additions per lane into one window");
-
-struct BsBatch {
-  float4 g[kBsBatch], e[kBsBatch];
-};
-
-template <bool FULL>
-__device__ __forceinline__ void bs_load_batch_t(BsBatch& B, const float* __restrict__ gr, const float* __restrict__ er,
-                                                uint32_t c, int r0, uint32_t d) {
-  const uint32_t lane = lane_id();
-#pragma unroll
-  for (int u = 0; u < kBsBatch; ++u) {
-    const uint32_t j = c * kChunk + (r0 + u) * 256 + lane * 4;
-    if (FULL) {
-      B.g[u] = load_stream4(gr + j);
-      B.e[u] = load_stream4(er + j);
-    } else {
-      B.g[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      B.e[u] = B.g[u];
-      if (j < d) {
-        B.g[u] = load_stream4(gr + j);
-        B.e[u] = load_stream4(er + j);
-      }
-    }
-  }
-}
-
 
 // One round (256 coordinates from j0 on) that straddles block boundaries.  The blocks that meet the round are
 // the same for every lane, so they are gone through one after the other (from block b, the block of the round's
@@ -221,9 +218,9 @@ __device__ __forceinline__ void bs_load_batch_t(BsBatch& B, const float* __restr
 // after x has been formed and stored the magnitudes of its coordinates are summed in a register window and go
 // to its digits like any other partial sum.  A block with at most 8 coordinates in the round adds them one by
 // one instead (a layout of one-coordinate blocks would otherwise make 256 trips through the wavefront-wide
-// sum).  Rare -- a few rounds per row in layouts worth the name -- and out of line.
+// sum).  Rare: a few rounds per row in layouts worth the name.
 template <bool PEND>
-__device__ __noinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0, uint32_t d, uint32_t b,
+__device__ __forceinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0, uint32_t d, uint32_t b,
                                               const uint32_t* __restrict__ off, const float* __restrict__ mur,
                                               float* __restrict__ er, uint32_t* __restrict__ bitr, uint32_t words,
                                               uint64_t* accr, size_t blk_digits, uint32_t replica, uint32_t* specr) {
@@ -273,14 +270,9 @@ __device__ __noinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0,
         const uint32_t key = bits[s] & 0x7fffffffu;
         if (in[s] && key < 0x7f800000u && key > kmax) kmax = key;
       }
-#pragma unroll
-      for (int s = 32; s >= 1; s >>= 1) {
-        const uint32_t o = __shfl_xor(kmax, s, 64);
-        kmax = o > kmax ? o : kmax;
-      }
       WaveAcc A;
       acc_reset(A);
-      acc_place(A, uniform_u32(kmax), 0);
+      acc_place(A, wave_max_u32(kmax));
       acc_add4(A, bits, in, dg + static_cast<size_t>(replica) * kLimbs, specr + bb);
       window_to_digits(A.sum, A.eh, dg + static_cast<size_t>(replica) * kLimbs);
     }
@@ -418,18 +410,22 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 }
 
 // ---------------------------------------------------------------------------------------------
-// First pass for general block layouts as a grid of short workgroups: a workgroup takes ONE chunk and ends,
-// wavefront w takes rounds 4w .. 4w+3 of it (plain streaming kernels of this shape move the same traffic at
-// 6.1-6.4 TB/s on MI355X, workgroups that walk many chunks at 5.4-5.7 TB/s).  A quarter that lies inside one
-// block -- all but a few per row -- is summed in a register window placed by the quarter's own largest
-// magnitude and goes to the block's digits with at most three atomics per wavefront; a quarter that straddles
-// block boundaries goes out of line through the blocks it meets.  The pending residual update of the previous
-// step is applied to e as it is read.
+// First pass for general block layouts as a grid of short workgroups: a wavefront takes a quarter of a chunk and ends, its
+// workgroup the same page of four spans (page_quarter; or the four quarters of a chunk where the sign words do not allow
+// it).  Bound by memory (12 bytes of a worker's coordinate) and by the instructions in between: 8 x 124439808 coordinates, blocks
+// of 4096, 1995 us a workgroup per chunk with eight of them on a compute unit, 1845 in pages with five; 16 x 11181642,
+// layers, 342 either way.  A quarter that lies inside one block -- all but a few per row -- is summed in a register window
+// placed by the quarter's own largest magnitude and goes to the block's digits with at most three atomics; a quarter that
+// meets block ends or the row's end goes through the blocks it meets, round by round.  The pending residual update of the
+// previous step is applied to e as it is read.
 // ---------------------------------------------------------------------------------------------
 template <bool PEND>
-__device__ __forceinline__ void bs_lean_chunk(uint32_t c, uint32_t row, const float* __restrict__ g, float* __restrict__ e,
-                                              const Geometry& geo, const BlocksignWorkspace& ws) {
-  const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
+__device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, const float* __restrict__ g,
+                                                float* __restrict__ e, const Geometry& geo, const BlocksignWorkspace& ws) {
+  const uint32_t lane = lane_id();
+  const uint32_t wave = uniform_u32(threadIdx.x >> 6);
+  const Quarter quarter = ws.paged ? page_quarter(group, wave) : Quarter{group, wave};
+  const uint32_t c = quarter.chunk;
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   float* er = e + static_cast<int64_t>(row) * geo.ld;
   const uint32_t* __restrict__ off = ws.offsets;
@@ -439,76 +435,91 @@ __device__ __forceinline__ void bs_lean_chunk(uint32_t c, uint32_t row, const fl
   uint64_t* accr = ws.acc + static_cast<size_t>(row) * geo.num_blocks * blk_digits;
   uint32_t* specr = ws.special + static_cast<size_t>(row) * geo.num_blocks;
   const uint32_t d = geo.d;
-  const uint32_t q0 = c * kChunk + wave * (kQuarter * 256);  // first coordinate of this wavefront's quarter
-  if (q0 >= d) return;                                       // wave-uniform; no barrier in here
-  const bool full = (c + 1) * static_cast<uint64_t>(kChunk) <= d;
-  BsBatch cur;
-  if (full) bs_load_batch_t<true>(cur, gr, er, c, wave * kQuarter, d);
-  else bs_load_batch_t<false>(cur, gr, er, c, wave * kQuarter, d);
+  const uint32_t q0 = c * kChunk + quarter.part * (kQuarter * 256);  // first coordinate of this wavefront's quarter
+  if (q0 >= d) return;                                               // wave-uniform; no barrier in here
+  // The quarter's loads go out before it is known whether it is a whole one (nothing is read beyond the row).
+  float4 gq[kQuarter], eq[kQuarter];
+#pragma unroll
+  for (int u = 0; u < kQuarter; ++u) {
+    const uint32_t j = q0 + u * 256 + lane * 4;
+    gq[u] = eq[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < d) {
+      gq[u] = load_stream4(gr + j);
+      eq[u] = load_stream4(er + j);
+    }
+  }
   uint32_t b = table_u32(ws.chunk_block, c);
   while (table_u32(off, b + 1) <= q0) ++b;  // block of the quarter's first coordinate
-  const uint32_t q_end = q0 + kQuarter * 256 < d ? q0 + kQuarter * 256 : d;
-  if (table_u32(off, b + 1) < q_end) {  // the quarter straddles block boundaries (a scalar condition)
-#pragma unroll  // (a run-time index into the batch would put it into scratch memory)
-    for (int u = 0; u < kQuarter; ++u) {
-      const uint32_t j0 = q0 + u * 256;
+  // a large block receives the sums of thousands of wavefronts: they go to one of several sets of digits (atomics to one
+  // address are performed one after the other), which the finalize kernel adds up
+  const uint32_t replica = group % ws.acc_replicas;
+  if (table_u32(off, b + 1) < q0 + kQuarter * 256) {  // the quarter meets block ends or the row's end (a scalar condition)
+    // (asked for again, round by round: the batch at a run-time index would lie in scratch memory, and a call for every round
+    // costs all quarters its registers)
+#pragma unroll 1
+    for (uint32_t u = 0; u < static_cast<uint32_t>(kQuarter); ++u) {
+      const uint32_t j0 = q0 + u * 256, j = j0 + lane * 4;
       if (j0 >= d) break;
       while (table_u32(off, b + 1) <= j0) ++b;
-      straddling_round<PEND>(cur.g[u], cur.e[u], j0, d, b, off, mur, er, bitr, geo.words, accr, blk_digits,
-                             c % ws.acc_replicas, specr);
+      float4 g4 = make_float4(0.f, 0.f, 0.f, 0.f), e4 = g4;
+      if (j < d) {
+        g4 = load_stream4(gr + j);
+        e4 = load_stream4(er + j);
+      }
+      straddling_round<PEND>(g4, e4, j0, d, b, off, mur, er, bitr, geo.words, accr, blk_digits, replica, specr);
     }
     return;
   }
   const float mu_b = PEND ? table_f32(mur, b) : 0.0f;
   uint32_t bits[kQuarter][4];
-  uint32_t kmax = 0;
+  uint32_t kmax = 0, kmin = 0xffffffffu, my_word = 0;
 #pragma unroll
   for (int u = 0; u < kQuarter; ++u) {
-    const uint32_t j0 = q0 + u * 256;
-    const uint32_t j = j0 + lane * 4;
-    const bool ok[4] = {full || j < d, full || j + 1 < d, full || j + 2 < d, full || j + 3 < d};
-    float ev[4] = {cur.e[u].x, cur.e[u].y, cur.e[u].z, cur.e[u].w};
-    const float gv[4] = {cur.g[u].x, cur.g[u].y, cur.g[u].z, cur.g[u].w};
-    if (PEND) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (ok[s]) ev[s] = ev[s] - (ev[s] < 0.0f ? -mu_b : mu_b);
-    }
+    float ev[4] = {eq[u].x, eq[u].y, eq[u].z, eq[u].w};
+    const float gv[4] = {gq[u].x, gq[u].y, gq[u].z, gq[u].w};
     float xv[4];
     uint32_t nib = 0;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      xv[s] = ok[s] ? ev[s] + gv[s] : ev[s];  // columns at and beyond d keep their contents
-      nib |= (ok[s] && xv[s] < 0.0f ? 1u : 0u) << s;
-    }
-    if (ok[0]) store_stream4(er + j, make_float4(xv[0], xv[1], xv[2], xv[3]));
-    if (full || j0 < d) {  // wave-uniform
-      const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
-      const uint32_t widx = (j0 >> 5) + (lane >> 3);
-      if ((lane & 7u) == 0 && (full || widx < geo.words)) bitr[widx] = word;
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      bits[u][s] = ok[s] ? __float_as_uint(xv[s]) : 0u;  // a coordinate beyond d adds nothing
+      if (PEND) ev[s] = ev[s] - (ev[s] < 0.0f ? -mu_b : mu_b);
+      xv[s] = ev[s] + gv[s];
+      nib |= (xv[s] < 0.0f ? 1u : 0u) << s;
+      bits[u][s] = __float_as_uint(xv[s]);
       const uint32_t key = bits[u][s] & 0x7fffffffu;
-      if (key < 0x7f800000u && key > kmax) kmax = key;
+      kmax = max(kmax, key);
+      kmin = min(kmin, key);
     }
+    store_stream4(er + q0 + u * 256 + lane * 4, make_float4(xv[0], xv[1], xv[2], xv[3]));
+    // every eight lanes hold a word of the round; lane u of them keeps that of round u for one store of the quarter's 128 bytes
+    const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
+    my_word = (lane & 7u) == static_cast<uint32_t>(u) ? word : my_word;
   }
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) {
-    const uint32_t o = __shfl_xor(kmax, s, 64);
-    kmax = o > kmax ? o : kmax;
-  }
+  if ((lane & 7u) < static_cast<uint32_t>(kQuarter)) bitr[(q0 >> 5) + (lane & 7u) * 8u + (lane >> 3)] = my_word;
+  kmax = wave_max_u32(kmax);
+  uint64_t* dg = accr + static_cast<size_t>(b) * blk_digits + static_cast<size_t>(replica) * kLimbs;
   // the window ends at the quarter's largest magnitude: 16 additions per lane, exact
   WaveAcc A;
   acc_reset(A);
-  acc_place(A, uniform_u32(kmax), 0);
-  // a large block receives the sums of thousands of wavefronts: they go to one of several sets of digits, chosen
-  // by the chunk (atomics to one address are performed one after the other), which the finalize kernel adds up
-  uint64_t* dg = accr + static_cast<size_t>(b) * blk_digits + static_cast<size_t>(c % ws.acc_replicas) * kLimbs;
-  const bool all[4] = {true, true, true, true};
+  acc_place(A, kmax);
+  if (kmax < 0x7f800000u && ballot64(kmin < A.klo) == 0) {  // wave-uniform: every magnitude lies inside it
 #pragma unroll
-  for (int u = 0; u < kQuarter; ++u) acc_add4(A, bits[u], all, dg, specr + b);
+    for (int u = 0; u < kQuarter; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) A.sum += static_cast<double>(__builtin_fabsf(__uint_as_float(bits[u][s])));  // exactly
+  } else {  // zeros, magnitudes far below the largest one, infinities, NaNs
+    uint32_t finite = 0;
+#pragma unroll
+    for (int u = 0; u < kQuarter; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t key = bits[u][s] & 0x7fffffffu;
+        finite = key < 0x7f800000u ? max(finite, key) : finite;
+      }
+    acc_place(A, wave_max_u32(finite));
+    const bool all[4] = {true, true, true, true};
+#pragma unroll
+    for (int u = 0; u < kQuarter; ++u) acc_add4(A, bits[u], all, dg, specr + b);
+  }
   window_to_digits(A.sum, A.eh, dg);
 }
 
@@ -517,7 +528,7 @@ __device__ __forceinline__ void bs_lean_chunk(uint32_t c, uint32_t row, const fl
 template <bool PEND, bool SCALES>
 __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
                                                   BlocksignWorkspace ws) {
-  bs_lean_chunk<PEND>(blockIdx.x, blockIdx.y, g, e, geo, ws);
+  bs_lean_quarter<PEND>(blockIdx.x, blockIdx.y, g, e, geo, ws);
   if constexpr (SCALES) {
     __shared__ uint32_t sh_last;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wavefront's atomics have been performed
@@ -539,14 +550,14 @@ __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, fl
 // and wrote the sign words once more: 16 x 11.2 M coordinates took 276 us, this 232).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWG) void k_bs_pass2(float* __restrict__ e, Geometry geo, BlocksignWorkspace ws) {
-  const uint32_t c = blockIdx.x, row = blockIdx.y;
-  const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
+  const Quarter quarter = page_quarter(blockIdx.x, uniform_u32(threadIdx.x >> 6));
+  const uint32_t c = quarter.chunk, row = blockIdx.y, lane = lane_id();
   float* er = e + static_cast<int64_t>(row) * geo.ld;
   const uint32_t* __restrict__ off = ws.offsets;
   const float* __restrict__ mur = ws.scales + static_cast<size_t>(row) * geo.num_blocks;
   const uint32_t d = geo.d;
-  const uint32_t q0 = c * kChunk + wave * (kQuarter * 256);  // first coordinate of this wavefront's quarter
-  if (q0 >= d) return;                                       // wave-uniform; no barrier in this kernel
+  const uint32_t q0 = c * kChunk + quarter.part * (kQuarter * 256);  // first coordinate of this wavefront's quarter
+  if (q0 >= d) return;                                               // wave-uniform; no barrier in this kernel
   float4 xb[kQuarter];
 #pragma unroll
   for (int u = 0; u < kQuarter; ++u) {
@@ -782,7 +793,7 @@ __global__ __launch_bounds__(bs_server_split(NC) * 64) __attribute__((amdgpu_wav
 // ---------------------------------------------------------------------------------------------
 // C = identity (full-precision distributed AMSGrad): gbar = mean of the n gradients in worker order.
 // Bound by memory: n rows and the four state arrays.  A wavefront takes one round (1 KB of every array), a workgroup
-// the same kilobyte of its die's page in four spans: n + 4 streams through the same addresses are
+// the same kilobyte of its die's page in four spans (see page_quarter): n + 4 streams through the same addresses are
 // 13 % faster so than a workgroup per 4 KB in address order.  Sixteen rows are requested at once (16 x 11.2 M, state from
 // HBM / cached: plain order, eight rows 195 / 155 us; pages, eight rows 174 / 151; pages, sixteen 171 / 149).
 // ---------------------------------------------------------------------------------------------
@@ -906,11 +917,11 @@ __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, flo
 hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, const AmsParams& ap, const float* g,
                           float* e, float* theta, float* m, float* v, float* vhat, bool residual_pending,
                           bool workers_only, hipStream_t stream, Launcher* L) {
-  const dim3 grid_chunks(geo.num_chunks, geo.n), wg(kWG);
+  const dim3 grid_chunks(ws.paged ? page_groups(geo.num_chunks) : geo.num_chunks, geo.n), wg(kWG);
   const bool scales = scales_in_first_pass(geo, ws);
   auto* first = residual_pending ? (scales ? k_bs_lean<true, true> : k_bs_lean<true, false>)
                                  : (scales ? k_bs_lean<false, true> : k_bs_lean<false, false>);
-  launch(L, kSlotBsPass1, first, grid_chunks, wg, stream, g, e, geo, ws);
+  launch_lds(L, kSlotBsPass1, first, grid_chunks, wg, kStreamLds, stream, g, e, geo, ws);
   COMPAMS_CHECK_LAUNCH();
   if (!scales) {
     const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
@@ -938,7 +949,7 @@ hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& 
 }
 
 hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspace& ws, float* e, hipStream_t stream) {
-  hipLaunchKernelGGL(k_bs_pass2, dim3(geo.num_chunks, geo.n), dim3(kWG), 0, stream, e, geo, ws);
+  hipLaunchKernelGGL(k_bs_pass2, dim3(page_groups(geo.num_chunks), geo.n), dim3(kWG), kStreamLds, stream, e, geo, ws);
   return hipGetLastError();
 }
 

@@ -29,6 +29,24 @@ constexpr int kRounds = kChunk / 256;    // rounds per chunk
 constexpr uint32_t kPageCoords = 1024;
 constexpr uint32_t kDies = 8;
 constexpr uint32_t kSpanCoords = kDies * kPageCoords;  // two chunks
+constexpr uint32_t kSpansPerGroup = kWaves;            // spans that eight consecutive workgroups share, a wavefront each
+
+// The quarter of a chunk that a wavefront of a dense pass takes, the workgroup being number `group` of the row's
+// page_groups(): page `group` % 8 of one of the four spans.
+struct Quarter {
+  uint32_t chunk, part;
+};
+__device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave) {
+  const uint32_t page = group % kDies, span = group / kDies * kSpansPerGroup + wave;
+  return {span * (kSpanCoords / kChunk) + page / kWaves, page % kWaves};
+}
+// A dense pass asks for this much LDS that it has no use for: five workgroups per compute unit are enough to keep the memory
+// busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with five, 317 with
+// four, 373 with three).
+constexpr size_t kStreamLds = 32768;
+inline uint32_t page_groups(uint32_t num_chunks) { return (num_chunks + kDies - 1) / kDies * kDies; }
+static_assert(kPageCoords * kWaves == kChunk, "a page is a wavefront's quarter of a chunk");
+static_assert(kSpansPerGroup * kSpanCoords == kDies * kChunk, "eight workgroups take eight chunks");
 
 // Radix levels over the 31-bit magnitude key (fp32 bit pattern without the sign):
 // level 0 = bits 30..19 (the exponent and 4 mantissa bits), level 1 = bits 18..9, level 2 = bits 8..0.
@@ -267,6 +285,9 @@ struct BlocksignWorkspace {
                         // the sum of a (row, block) is the sum of its replicas
   uint32_t acc_replicas;
   uint32_t* special;    // n * M : bit 0 = an infinity was seen, bit 1 = a NaN was seen
+  uint32_t paged;       // the first pass takes the rows in pages: the rows' sign words start on 32 bytes.  (Where they do not,
+                        // two dies write the sector that two pages share, by halves: 16 x 11181642, layers, first pass and
+                        // server 426 us in pages, 424 in address order; 8 x 124439808, blocks of 4096 2520 / 2620)
   uint32_t* ticket;     // n : "last workgroup of the row" counters of the first pass; zero between launches
   float* scales;        // n * M
   uint32_t* bits;       // n * words
@@ -374,11 +395,16 @@ void launcher_begin(Launcher* L, int slot, hipStream_t stream);
 void launcher_end(Launcher* L, int slot, hipStream_t stream);
 
 template <typename... KArgs, typename... Args>
+inline void launch_lds(Launcher* L, int slot, void (*kernel)(KArgs...), const dim3& grid, const dim3& block, size_t lds,
+                       hipStream_t stream, Args... args) {
+  if (L) launcher_begin(L, slot, stream);
+  hipLaunchKernelGGL(kernel, grid, block, lds, stream, static_cast<KArgs>(args)...);
+  if (L) launcher_end(L, slot, stream);
+}
+template <typename... KArgs, typename... Args>
 inline void launch(Launcher* L, int slot, void (*kernel)(KArgs...), const dim3& grid, const dim3& block,
                    hipStream_t stream, Args... args) {
-  if (L) launcher_begin(L, slot, stream);
-  hipLaunchKernelGGL(kernel, grid, block, 0, stream, static_cast<KArgs>(args)...);
-  if (L) launcher_end(L, slot, stream);
+  launch_lds(L, slot, kernel, grid, block, 0, stream, args...);
 }
 
 // A kernel template over the number of cached state arrays (0..4), picked at run time.

@@ -37,6 +37,25 @@ def run(p, n, d, kind, steps=3, with_e=True):
     p.close()
 
 
+def offsets(d, size):
+    return np.concatenate([np.arange(0, d, size, dtype=np.int64), [d]])
+
+
+@pytest.mark.parametrize("kind", ["plain", "zeros", "wide", "special", "ends"])
+@pytest.mark.parametrize("n,d,size", [(3, GROUP, 4096), (2, GROUP + PAGE, 1 << 30), (1, 2 * GROUP + 5, 4096),
+                                      (3, SPAN - 32, 1000), (5, GROUP + 1, 1 << 30)])
+def test_blocksign_values(n, d, size, kind):
+    run(Pair(n, d, np.zeros(d, np.float32), B.BLOCKSIGN, block_offsets=offsets(d, size)), n, d, kind)
+
+
+@pytest.mark.parametrize("n,d,size", [(2, 256, 256), (4, PAGE, 1 << 30), (2, SPAN, 4096), (2, SPAN + PAGE, 300), (2, GROUP - PAGE, 4096),
+                                      (1, GROUP + 3, 1 << 30), (3, 9 * 4096, 1000), (2, 17 * 4096 + 256, 65536),
+                                      (2, 150 * 4096 - 2048, 4096), (2, 150 * 4096 + 3, 100000), (64, 3000, 1000)])
+def test_blocksign_sizes(n, d, size):
+    # the residual stays pending between the steps, and is asked for after the last
+    run(Pair(n, d, np.zeros(d, np.float32), B.BLOCKSIGN, block_offsets=offsets(d, size)), n, d, "plain", with_e=False)
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
 @pytest.mark.parametrize("d", [1, 255, 1027, SPAN, GROUP - 1, GROUP, GROUP + 1, 3 * GROUP + SPAN + 5])
 def test_identity_sizes(n, d):
