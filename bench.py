@@ -266,12 +266,12 @@ def main():
 
     # what the box gives the access pattern of the server's lines (theta, m, v, vhat of the workload's size read and
     # written once, in place, nothing else): each launch follows a copy of 2 GiB of traffic, as a step's server
-    # kernel follows its first pass; with as many of the four arrays kept in the memory-side cache as the library
-    # keeps for this size, and with none and all four beside it
+    # kernel follows its first pass; with as many of the four arrays kept in the memory-side cache as fit it at this
+    # size, and with none and all four beside it
     quads = (w.d + 3) // 4 * 4
     state = [torch.zeros(quads, dtype=torch.float32, device=dev) for _ in range(4)]
     kept = B.compams_cached_state_arrays(w.d)
-    server_ceiling = {"arrays": 4, "elements_each": quads, "bytes_per_launch": 32 * quads, "library_caches": kept}
+    server_ceiling = {"arrays": 4, "elements_each": quads, "bytes_per_launch": 32 * quads, "fit_the_cache": kept}
     for cached in sorted({0, kept, 4}):
         pe = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(12)]
         for a, b in pe:
@@ -356,8 +356,7 @@ def main():
                    "num_blocks": (len(w.block_offsets()) - 1) if w.compressor == "blocksign" else 0,
                    "eps_mode": "out_sqrt" if args.eps_out else "in_sqrt",
                    "predict": not args.no_predict, "force_dense": args.force_dense, "band": not args.no_band,
-                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0
-                   else B.compams_cached_state_arrays(w.d)},
+                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0 else "library's choice"},
         "hbm_gbps": main_res["hbm_gbps"],
         "hbm_frac_of_peak": main_res["hbm_frac_of_peak"],
         "algorithmic_bytes_per_step": main_res["algorithmic_bytes_per_step"],

@@ -206,8 +206,10 @@ enum {
                                     inside; when the threshold does fall inside (verified exactly), one launch
                                     finishes the selection from that short list */
   COMPAMS_OPT_CACHED_ARRAYS = 4  /* every compressor: how many of theta, m, v, vhat (in that order) the server's
-                                    lines read and write with ordinary accesses, the others with streaming ones:
-                                    0..4, or -1 (default) for compams_cached_state_arrays(d) */
+                                    lines write through to the memory-side cache for the next step, the others with
+                                    streaming accesses: 0..4, or -1 (default) for the library's choice:
+                                    compams_cached_state_arrays(d) with the identity compressor and where the
+                                    gradients and residuals fit that cache as well, else 0 */
 };
 int compams_set_option(compams_ctx* ctx, int option, int64_t value);
 
@@ -294,10 +296,9 @@ int compams_server_step(compams_ctx* ctx, const uint32_t* messages, int64_t stri
  * beside the step's figures, and the known-size kernel that hardware counters are calibrated against. */
 int compams_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
 
-/* How many of theta, m, v, vhat (in that order) the kernels that apply the server's lines of Algorithm 2 read and
- * write with ordinary accesses for a problem of d coordinates, so that they stay in the memory-side cache from
- * one step to the next; the others are streamed past it.  As many as fit a fixed share of that cache together:
- * 0..4 (4 for every small d).  Pure, host-only; COMPAMS_INVALID_ARG for d < 1. */
+/* How many of theta, m, v, vhat (in that order) can stay in the memory-side cache from one step to the next, for a
+ * problem of d coordinates: as many as fit a fixed share of that cache together, 0..4 (4 for every small d).  What a
+ * step makes of it: COMPAMS_OPT_CACHED_ARRAYS.  Pure, host-only; COMPAMS_INVALID_ARG for d < 1. */
 int compams_cached_state_arrays(int64_t d);
 
 /* A second measured ceiling, for the server's lines of Algorithm 2 (theta, m, v, vhat each read once and
@@ -306,8 +307,8 @@ int compams_cached_state_arrays(int64_t d);
  * per lane and access - the access pattern of those lines without their arithmetic and without the look-ups
  * that precede them.  What the box gives this pattern bounds the kernels that apply those lines.
  *   arrays: HOST array of n_arrays DEVICE pointers (16-byte aligned, distinct, count elements each, modified).
- *   count: multiple of 4.  cached_arrays (0..4): the first that many arrays are accessed with ordinary loads
- *   and stores, the others with non-temporal ones (see compams_cached_state_arrays).
+ *   count: multiple of 4.  cached_arrays (0..4): the first that many arrays are written through to the memory-side
+ *   cache, the others with non-temporal stores (see compams_cached_state_arrays).
  * Only enqueues on hip_stream.  COMPAMS_INVALID_ARG / COMPAMS_BAD_ALIGNMENT as for compams_copy. */
 int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int cached_arrays, void* hip_stream);
 

@@ -346,7 +346,7 @@ def compams_step_static(n: int, d: int, k: int, theta, m, v, vhat, e, g, lr: flo
 
 
 def compams_cached_state_arrays(d: int) -> int:
-    """How many of theta, m, v, vhat the server kernels keep in the memory-side cache for a problem of d coordinates."""
+    """How many of theta, m, v, vhat the memory-side cache can keep from step to step for a problem of d coordinates."""
     count = lib().compams_cached_state_arrays(d)
     if count < 0:
         _check(count, "compams_cached_state_arrays")
@@ -356,7 +356,7 @@ def compams_cached_state_arrays(d: int) -> int:
 def compams_inplace_probe(arrays, cached_arrays: int):
     """x += 1 on up to four separately allocated fp32 arrays of one size, in the access pattern of the server's
     lines of Algorithm 2 (the measured ceiling for the kernels that apply them); the first cached_arrays of them
-    with ordinary accesses, the others with streaming ones."""
+    written through to the memory-side cache, the others with streaming accesses."""
     count = arrays[0].numel()
     assert all(a.numel() == count and a.dtype == torch.float32 and a.is_cuda and a.is_contiguous() for a in arrays)
     ptrs = (ctypes.c_void_p * len(arrays))(*[a.data_ptr() for a in arrays])

@@ -595,10 +595,9 @@ __global__ __launch_bounds__(kWG) void k_bs_pass2(float* __restrict__ e, Geometr
 // ---------------------------------------------------------------------------------------------
 constexpr int kBsWorkers = 8;  // workers whose sign words and scales are requested together (rounds that meet block ends)
 
-// Wavefronts per chunk.  With the whole state cached a wavefront takes two rounds and asks for everything it
-// needs at once; with state that streams from HBM four rounds, the next one's state requested while one is
-// updated (ResNet-18 shape, all cached: 61 against 66 us; GPT-2 shape, all streamed: 666 against 685 us).
-constexpr int bs_server_split(int cached_arrays) { return cached_arrays == 4 ? 8 : 4; }
+// Wavefronts per chunk: a wavefront takes two rounds and asks for everything it needs at once.  (Four rounds, the next one's
+// state requested while one is updated: 16 x 11.2 M 68 -> 75 us, 8 x 25.6 M 145 -> 151, 8 x 60 M 334 -> 336, 8 x 124.4 M 690 -> 686.)
+constexpr int kBsServerWaves = 8;
 
 // Sums of a share of KQ rounds that lies inside block b and inside the row: sum[r][s] for the lane's four
 // coordinates of round r.  A worker's sign words of the share are KQ * 8 consecutive words, which a group of
@@ -610,7 +609,7 @@ __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometr
                                               uint32_t b, uint32_t q0, uint32_t lane) {
   constexpr int kShareWords = KQ * 8;           // sign words of one worker for the share
   constexpr int kPerLoad = 64 / kShareWords;    // workers whose words one load of the wavefront brings in
-  constexpr int kTrip = KQ == 2 ? 16 : 8;       // workers per trip: kTrip / kPerLoad loads, kTrip scales
+  constexpr int kTrip = 16;                     // workers per trip: kTrip / kPerLoad loads, kTrip scales
   static_assert(kShareWords * kPerLoad == 64 && kTrip % kPerLoad == 0, "lanes of a load: worker by word");
 #pragma unroll
   for (int r = 0; r < KQ; ++r)
@@ -647,7 +646,7 @@ __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometr
 }
 
 template <int NC>  // how many of theta, m, v, vhat are cached, the others streamed (see the top-k final kernel)
-__global__ __launch_bounds__(bs_server_split(NC) * 64) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_bs_amsgrad(
+__global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_bs_amsgrad(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat, Geometry geo,
     BlocksignWorkspace ws, AmsParams p) {
   const uint32_t* __restrict__ off = ws.offsets;
@@ -658,57 +657,32 @@ __global__ __launch_bounds__(bs_server_split(NC) * 64) __attribute__((amdgpu_wav
   const uint32_t c = blockIdx.x, part = wave;
   if (c >= geo.num_chunks) return;
   uint32_t b = table_u32(ws.chunk_block, c);
-  constexpr int kQ = kRounds / bs_server_split(NC);  // rounds of a wavefront's share of the chunk
+  constexpr int kQ = kRounds / kBsServerWaves;  // rounds of a wavefront's share of the chunk
   const uint32_t q0 = c * kChunk + part * (kQ * 256);
   if (q0 >= d) return;
   while (table_u32(off, b + 1) <= q0) ++b;  // block of the share's first coordinate
   if (q0 + kQ * 256 <= d && table_u32(off, b + 1) >= q0 + kQ * 256) {
     // the whole share lies inside one block (all but a few per row in layouts worth the name)
-    const uint32_t j = q0 + lane * 4;
     float sum[kQ][4];
-    if constexpr (kQ == 2) {  // the state of both rounds and the sign words are requested together
-      float4 th[kQ], mm[kQ], vv[kQ], vh[kQ];
+    // the state of all its rounds and the sign words are requested together
+    float4 th[kQ], mm[kQ], vv[kQ], vh[kQ];
 #pragma unroll
-      for (int r = 0; r < kQ; ++r) {
-        th[r] = load_state4<(NC > 0)>(theta + j + r * 256); mm[r] = load_state4<(NC > 1)>(m + j + r * 256);
-        vv[r] = load_state4<(NC > 2)>(v + j + r * 256); vh[r] = load_state4<(NC > 3)>(vhat + j + r * 256);
-      }
-      bs_share_sums<kQ>(sum, geo, ws, b, q0, lane);
+    for (int r = 0; r < kQ; ++r) {
+      th[r] = load_state4(theta + q0 + r * 256, lane * 4); mm[r] = load_state4(m + q0 + r * 256, lane * 4);
+      vv[r] = load_state4(v + q0 + r * 256, lane * 4); vh[r] = load_state4(vhat + q0 + r * 256, lane * 4);
+    }
+    bs_share_sums<kQ>(sum, geo, ws, b, q0, lane);
 #pragma unroll
-      for (int r = 0; r < kQ; ++r) {
-        const uint32_t jr = j + r * 256;
-        ams_update(sum[r][0] / p.nf, th[r].x, mm[r].x, vv[r].x, vh[r].x, p);
-        ams_update(sum[r][1] / p.nf, th[r].y, mm[r].y, vv[r].y, vh[r].y, p);
-        ams_update(sum[r][2] / p.nf, th[r].z, mm[r].z, vv[r].z, vh[r].z, p);
-        ams_update(sum[r][3] / p.nf, th[r].w, mm[r].w, vv[r].w, vh[r].w, p);
-        store_state4<(NC > 0)>(theta + jr, th[r]);
-        store_state4<(NC > 1)>(m + jr, mm[r]);
-        store_state4<(NC > 2)>(v + jr, vv[r]);
-        store_state4<(NC > 3)>(vhat + jr, vh[r]);
-      }
-    } else {  // the first round's state with the sign words, each next round's while one is updated
-      float4 th = load_state4<(NC > 0)>(theta + j), mm = load_state4<(NC > 1)>(m + j);
-      float4 vv = load_state4<(NC > 2)>(v + j), vh = load_state4<(NC > 3)>(vhat + j);
-      bs_share_sums<kQ>(sum, geo, ws, b, q0, lane);
-#pragma unroll
-      for (int r = 0; r < kQ; ++r) {
-        __builtin_amdgcn_sched_barrier(0);  // (else all rounds' loads are moved up front: 82 registers)
-        const uint32_t jr = j + r * 256;
-        float4 th2 = th, mm2 = mm, vv2 = vv, vh2 = vh;
-        if (r + 1 < kQ) {
-          th2 = load_state4<(NC > 0)>(theta + jr + 256); mm2 = load_state4<(NC > 1)>(m + jr + 256);
-          vv2 = load_state4<(NC > 2)>(v + jr + 256); vh2 = load_state4<(NC > 3)>(vhat + jr + 256);
-        }
-        ams_update(sum[r][0] / p.nf, th.x, mm.x, vv.x, vh.x, p);
-        ams_update(sum[r][1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
-        ams_update(sum[r][2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
-        ams_update(sum[r][3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-        store_state4<(NC > 0)>(theta + jr, th);
-        store_state4<(NC > 1)>(m + jr, mm);
-        store_state4<(NC > 2)>(v + jr, vv);
-        store_state4<(NC > 3)>(vhat + jr, vh);
-        th = th2; mm = mm2; vv = vv2; vh = vh2;
-      }
+    for (int r = 0; r < kQ; ++r) {
+      const uint32_t jr = q0 + r * 256;
+      ams_update(sum[r][0] / p.nf, th[r].x, mm[r].x, vv[r].x, vh[r].x, p);
+      ams_update(sum[r][1] / p.nf, th[r].y, mm[r].y, vv[r].y, vh[r].y, p);
+      ams_update(sum[r][2] / p.nf, th[r].z, mm[r].z, vv[r].z, vh[r].z, p);
+      ams_update(sum[r][3] / p.nf, th[r].w, mm[r].w, vv[r].w, vh[r].w, p);
+      store_state4<(NC > 0)>(theta + jr, lane * 4, th[r]);
+      store_state4<(NC > 1)>(m + jr, lane * 4, mm[r]);
+      store_state4<(NC > 2)>(v + jr, lane * 4, vv[r]);
+      store_state4<(NC > 3)>(vhat + jr, lane * 4, vh[r]);
     }
     return;
   }
@@ -722,8 +696,8 @@ __global__ __launch_bounds__(bs_server_split(NC) * 64) __attribute__((amdgpu_wav
     // the optimizer state of this round is requested first; the sign/scale loop runs while it travels
     float4 th = make_float4(0.f, 0.f, 0.f, 0.f), mm = th, vv = th, vh = th;
     if (ok[3]) {
-      th = load_state4<(NC > 0)>(theta + j); mm = load_state4<(NC > 1)>(m + j);
-      vv = load_state4<(NC > 2)>(v + j); vh = load_state4<(NC > 3)>(vhat + j);
+      th = load_state4(theta + j0, lane * 4); mm = load_state4(m + j0, lane * 4);
+      vv = load_state4(v + j0, lane * 4); vh = load_state4(vhat + j0, lane * 4);
     }
     while (table_u32(off, b + 1) <= j0) ++b;
     const uint32_t j_end = (j0 + 256 < d) ? j0 + 256 : d;
@@ -775,10 +749,10 @@ __global__ __launch_bounds__(bs_server_split(NC) * 64) __attribute__((amdgpu_wav
       ams_update(sum[1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(sum[2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(sum[3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4<(NC > 0)>(theta + j, th);
-      store_state4<(NC > 1)>(m + j, mm);
-      store_state4<(NC > 2)>(v + j, vv);
-      store_state4<(NC > 3)>(vhat + j, vh);
+      store_state4<(NC > 0)>(theta + j0, lane * 4, th);
+      store_state4<(NC > 1)>(m + j0, lane * 4, mm);
+      store_state4<(NC > 2)>(v + j0, lane * 4, vv);
+      store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
     } else {
       for (int s = 0; s < 4; ++s)
         if (ok[s]) {
@@ -804,14 +778,15 @@ __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ 
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   // workgroups 32 s .. 32 s + 31 share the four spans from 4 s on: die b % 8 has page b % 8, round (b / 8) % 4 of it
   const uint32_t b = blockIdx.x;
-  const uint32_t j = ((b >> 5) * kWaves + wave) * kSpanCoords + (b & 7u) * kPageCoords + ((b >> 3) & 3u) * 256 + lane * 4;
+  const uint32_t j0 = ((b >> 5) * kWaves + wave) * kSpanCoords + (b & 7u) * kPageCoords + ((b >> 3) & 3u) * 256;
+  const uint32_t j = j0 + lane * 4;
   if (j >= geo.d) return;
   const bool whole = j + 3 < geo.d;
   // the optimizer state is requested first; the workers' gradients follow sixteen rows at a time, loads together
   float4 th = make_float4(0.f, 0.f, 0.f, 0.f), mm = th, vv = th, vh = th;
   if (whole) {
-    th = load_state4<(NC > 0)>(theta + j); mm = load_state4<(NC > 1)>(m + j);
-    vv = load_state4<(NC > 2)>(v + j); vh = load_state4<(NC > 3)>(vhat + j);
+    th = load_state4(theta + j0, lane * 4); mm = load_state4(m + j0, lane * 4);
+    vv = load_state4(v + j0, lane * 4); vh = load_state4(vhat + j0, lane * 4);
   }
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
   constexpr int kRows = 16;
@@ -835,10 +810,10 @@ __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ 
     ams_update(sum[1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
     ams_update(sum[2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
     ams_update(sum[3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-    store_state4<(NC > 0)>(theta + j, th);
-    store_state4<(NC > 1)>(m + j, mm);
-    store_state4<(NC > 2)>(v + j, vv);
-    store_state4<(NC > 3)>(vhat + j, vh);
+    store_state4<(NC > 0)>(theta + j0, lane * 4, th);
+    store_state4<(NC > 1)>(m + j0, lane * 4, mm);
+    store_state4<(NC > 2)>(v + j0, lane * 4, vv);
+    store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
   } else {
     for (uint32_t s = 0; s < 4 && j + s < geo.d; ++s) {
       float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
@@ -879,29 +854,30 @@ template <int A, int NC>
 __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, float* a2, float* a3, size_t count) {
   constexpr int kR = kChunk / (kWG * 4);
   float4 x[kR][4];
-  const size_t j0 = static_cast<size_t>(blockIdx.x) * kChunk + threadIdx.x * 4;
+  const size_t j0 = static_cast<size_t>(blockIdx.x) * kChunk;
+  const uint32_t at = threadIdx.x * 4;
 #pragma unroll
   for (int r = 0; r < kR; ++r) {
     const size_t j = j0 + r * kWG * 4;
-    if (j + 3 < count) {
-      x[r][0] = load_state4<(NC > 0)>(a0 + j);
-      if (A > 1) x[r][1] = load_state4<(NC > 1)>(a1 + j);
-      if (A > 2) x[r][2] = load_state4<(NC > 2)>(a2 + j);
-      if (A > 3) x[r][3] = load_state4<(NC > 3)>(a3 + j);
+    if (j + at + 3 < count) {
+      x[r][0] = load_state4(a0 + j, at);
+      if (A > 1) x[r][1] = load_state4(a1 + j, at);
+      if (A > 2) x[r][2] = load_state4(a2 + j, at);
+      if (A > 3) x[r][3] = load_state4(a3 + j, at);
     }
   }
 #pragma unroll
   for (int r = 0; r < kR; ++r) {
     const size_t j = j0 + r * kWG * 4;
-    if (j + 3 < count) {
+    if (j + at + 3 < count) {
 #pragma unroll
       for (int a = 0; a < A; ++a) {
         x[r][a].x += 1.0f; x[r][a].y += 1.0f; x[r][a].z += 1.0f; x[r][a].w += 1.0f;
       }
-      store_state4<(NC > 0)>(a0 + j, x[r][0]);
-      if (A > 1) store_state4<(NC > 1)>(a1 + j, x[r][1]);
-      if (A > 2) store_state4<(NC > 2)>(a2 + j, x[r][2]);
-      if (A > 3) store_state4<(NC > 3)>(a3 + j, x[r][3]);
+      store_state4<(NC > 0)>(a0 + j, at, x[r][0]);
+      if (A > 1) store_state4<(NC > 1)>(a1 + j, at, x[r][1]);
+      if (A > 2) store_state4<(NC > 2)>(a2 + j, at, x[r][2]);
+      if (A > 3) store_state4<(NC > 3)>(a3 + j, at, x[r][3]);
     }
   }
 }
@@ -939,7 +915,7 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
 // The server's lines from the sign words and scales that sit in the workspace.
 hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& ws, const AmsParams& ap, float* theta,
                                  float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
-  const dim3 grid(geo.num_chunks), wg(bs_server_split(ap.cached_arrays) * 64);  // a workgroup per chunk
+  const dim3 grid(geo.num_chunks), wg(kBsServerWaves * 64);  // a workgroup per chunk
 #define COMPAMS_BS_AMSGRAD(NC) k_bs_amsgrad<NC>
   COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, geo, ws,
                            ap);

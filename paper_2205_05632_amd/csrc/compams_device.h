@@ -68,6 +68,7 @@ __device__ __forceinline__ uint32_t or_over_8_lanes(uint32_t w) {
 
 // 128-bit streaming (non-temporal) access for data that is touched once per step.
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 load_stream4(const float* p) {
   const f4v v = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(p));
   return make_float4(v.x, v.y, v.z, v.w);
@@ -78,22 +79,29 @@ __device__ __forceinline__ void store_stream4(float* p, const float4& x) {
   __builtin_nontemporal_store(v, reinterpret_cast<f4v*>(p));
 }
 
-// theta, m, v, vhat are touched once per step.  CACHED: an ordinary access, which leaves the line in the memory-side
-// cache for the next step; else a streaming one.
-template <bool CACHED>
-__device__ __forceinline__ float4 load_state4(const float* p) {
-  if constexpr (CACHED) return *reinterpret_cast<const float4*>(p);
-  else return load_stream4(p);
-}
-template <bool CACHED>
-__device__ __forceinline__ void store_state4(float* p, const float4& x) {
-  if constexpr (CACHED) *reinterpret_cast<float4*>(p) = x;
-  else store_stream4(p, x);
-}
-
 // A value that is the same in every lane, moved to a scalar register: conditions on it become scalar branches
 // and it can be an operand of every lane's arithmetic without a register per lane.
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// theta, m, v, vhat are touched once per step: read with streaming accesses.  CACHED: written through to the memory-side cache,
+// where the next step may find them; else written with streaming accesses too.  (Ordinary stores left dirty lines in the
+// dies' L2 as well: 16 x 1 M, top-k, 87.7 us a step, as here 85.0; identity, 16 x 11.2 M, 184 / 171.  Which is taken when:
+// step_cached_arrays.)
+// base is the same in every lane, at the lane's offset from it.
+__device__ __forceinline__ float4 load_state4(const float* base, uint32_t at) { return load_stream4(base + at); }
+template <bool CACHED>
+__device__ __forceinline__ void store_state4(float* base, uint32_t at, const float4& x) {
+  if constexpr (CACHED) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    const uint64_t q = (static_cast<uint64_t>(uniform_u32(static_cast<uint32_t>(p >> 32))) << 32) | uniform_u32(static_cast<uint32_t>(p));
+    const __amdgpu_buffer_rsrc_t view = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(q), 0, 0xffffffffu, 0x00020000);
+    u4v v;
+    v.x = __float_as_uint(x.x); v.y = __float_as_uint(x.y); v.z = __float_as_uint(x.z); v.w = __float_as_uint(x.w);
+    __builtin_amdgcn_raw_buffer_store_b128(v, view, at * 4u, 0, /*device-scope policy*/ 16);
+  } else {
+    store_stream4(base + at, x);
+  }
+}
 
 // A table entry at a wave-uniform index, read through the scalar path: the tables read this way (block offsets,
 // chunk-to-block map, the previous step's means and list offsets, a row's carried-over guess) are not

@@ -297,18 +297,25 @@ constexpr int kLimbs = 10;  // 10 digits of 32 bits cover 2^-149 .. 2^171
 struct AmsParams {
   float beta1, beta2, one_minus_beta1, one_minus_beta2, eps, lr, nf;
   int eps_out;  // 1: epsilon outside the square root
-  int cached_arrays;  // how many of theta, m, v, vhat (in that order) fit the memory-side cache together from one
-                      // step to the next: those are read and written with ordinary accesses, the others with
-                      // streaming ones (measured, final kernel of the top-k step: ResNet-18, 4 x 45 MB, all four
-                      // cached 70 against 87 us; ResNet-50, 4 x 102 MB, none 174, one 147, two 144, three 175 us;
-                      // GPT-2, 4 x 498 MB, none is best)
+  int cached_arrays;  // how many of theta, m, v, vhat (in that order) are written through to the memory-side cache for the
+                      // next step, the others streamed past it (see step_cached_arrays)
 };
 
-// The memory-side cache holds 256 MB; what the first pass streams through in between costs some of it.
+// How many of the four state arrays the memory-side cache (256 MB) holds together, with room for what else passes through.
+constexpr int64_t kCacheBudget = int64_t(212) << 20;
 inline int cached_state_arrays(int64_t d) {
-  const int64_t budget = int64_t(212) << 20, each = d * 4;
-  const int64_t fit = budget / each;
+  const int64_t fit = kCacheBudget / (d * 4);
   return fit > 4 ? 4 : static_cast<int>(fit);
+}
+
+// How many a step keeps there.  Between two steps lie a forward and a backward pass, so state that was left in the cache is
+// found there again only by a small model; of any other its dirty lines are written out in the way of the kernels that follow.
+// Top-k and block-sign keep it where the gradients and residuals would fit as well.  Measured (us a step; three contexts in
+// turn, state from HBM / one context's steps one after the other): 16 x 11.2 M, top-k kept 524 / 472, streamed 502 / 476;
+// block-sign 433 / 412, 408 / 412; 8 x 25.6 M, top-k, two of four kept 633 / 587, streamed 610 / 607; 16 x 1 M 85.0 kept, 87.3
+// streamed.  The identity compressor reads the gradients in the same pass: 172 / 167 kept, 173 / 175 streamed: what fits is kept.
+inline int step_cached_arrays(int64_t n, int64_t d, bool identity) {
+  return identity || (2 * n + 4) * 4 * d <= kCacheBudget ? cached_state_arrays(d) : 0;
 }
 
 // Moment and parameter lines of Algorithm 2 for one coordinate: every product, sum, square root and

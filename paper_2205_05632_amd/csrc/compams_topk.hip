@@ -2292,8 +2292,8 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
   return f;
 }
 
-// NC: how many of theta, m, v, vhat (in that order) are read and written with ordinary accesses, the others with
-// streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
+// NC: how many of theta, m, v, vhat (in that order) are written through to the memory-side cache, the others with
+// streaming accesses (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
 // CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
 template <int ROLE, bool UNI, int NC, int NW, bool CLEAR = false>
@@ -2631,17 +2631,18 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
     const uint32_t t = wave * (kPart / 4) + r * 64 + lane;
     const uint32_t j = j_lane + r * 256;
     if (j + 3 < d_end) {
-      float4 th = load_state4<(NC > 0)>(theta + j), mm = load_state4<(NC > 1)>(m + j);
-      float4 vv = load_state4<(NC > 2)>(v + j), vh = load_state4<(NC > 3)>(vhat + j);
+      const uint32_t j0 = f.base + wave * kPart + r * 256;  // the same in every lane
+      float4 th = load_state4(theta + j0, lane * 4), mm = load_state4(m + j0, lane * 4);
+      float4 vv = load_state4(v + j0, lane * 4), vh = load_state4(vhat + j0, lane * 4);
       const float4 s = gs4[t];
       ams_update(s.x / p.nf, th.x, mm.x, vv.x, vh.x, p);
       ams_update(s.y / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(s.z / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(s.w / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4<(NC > 0)>(theta + j, th);
-      store_state4<(NC > 1)>(m + j, mm);
-      store_state4<(NC > 2)>(v + j, vv);
-      store_state4<(NC > 3)>(vhat + j, vh);
+      store_state4<(NC > 0)>(theta + j0, lane * 4, th);
+      store_state4<(NC > 1)>(m + j0, lane * 4, mm);
+      store_state4<(NC > 2)>(v + j0, lane * 4, vv);
+      store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
     } else {
       for (uint32_t s = 0; s < 4 && j + s < d_end; ++s) {
         float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
