@@ -208,8 +208,8 @@ enum {
   COMPAMS_OPT_CACHED_ARRAYS = 4  /* every compressor: how many of theta, m, v, vhat (in that order) the server's
                                     lines write through to the memory-side cache for the next step, the others with
                                     streaming accesses: 0..4, or -1 (default) for the library's choice:
-                                    compams_cached_state_arrays(d) with the identity compressor and where the
-                                    gradients and residuals fit that cache as well, else 0 */
+                                    compams_cached_state_arrays(d) with the identity compressor, with block-sign
+                                    only where gradients and residuals fit that cache as well, else 0 */
 };
 int compams_set_option(compams_ctx* ctx, int option, int64_t value);
 

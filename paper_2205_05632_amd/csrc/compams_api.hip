@@ -65,7 +65,7 @@ struct Layout {
   // block-sign
   size_t offsets, chunk_block, acc, special, ticket, scales, bits;
   uint32_t acc_replicas;
-  uint32_t cap_alloc, band_alloc, num_chunks, words;
+  uint32_t cap_alloc, band_alloc, num_chunks, words, desc_parts;
   // top-k inside every block
   uint64_t k_total;
   size_t num_micro;  // selection problems taken by single wavefronts (top-k per block)
@@ -178,8 +178,9 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.blk = take(n * kMaxCountBlocks * 8);
     L.blk_prefix = take(n * kMaxCountBlocks * 8);
     L.sel_off = take(n * offsets * 4);
-    L.desc = take(n * nc * 8);
-    L.desc2 = take(context || measure ? n * nc * 8 : 0);
+    L.desc_parts = context && paged_first_pass(n, L.num_chunks) ? kWaves : 1;
+    L.desc = take(n * nc * L.desc_parts * 8);
+    L.desc2 = take(context || measure ? n * nc * L.desc_parts * 8 : 0);
     L.bnd = take(n * kBoundaryCap * 8);
     L.bnd_sel = take(n * kBoundaryCap * 4);
     L.cand = take(n * cap * 8);
@@ -236,6 +237,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.blk = take(S * kMaxCountBlocks * 8);
     L.blk_prefix = take(S * kMaxCountBlocks * 8);
     L.sel_off = take(n * (chunks * kWaves + M) * 4);
+    L.desc_parts = 1;
     L.desc = take(n * chunks * 8);
     L.desc2 = take(n * chunks * 8);
     L.bnd = take(S * kBoundaryCap * 8);
@@ -385,6 +387,7 @@ static void bind_topk_workspace(compams_ctx* ctx, char* w) {
   t.wire_total = reinterpret_cast<uint32_t*>(w + lay.wire_total);
   t.wire_tile_off = reinterpret_cast<uint32_t*>(w + lay.wire_tile_off);
   t.wire_tile_sum = reinterpret_cast<uint32_t*>(w + lay.wire_tile_sum);
+  t.desc_parts = lay.desc_parts;
   t.desc = reinterpret_cast<uint2*>(w + lay.desc);
   t.desc2 = reinterpret_cast<uint2*>(w + lay.desc2);
   t.cand = reinterpret_cast<uint2*>(w + lay.cand);
@@ -575,7 +578,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
     b.ticket = reinterpret_cast<uint32_t*>(w + lay.ticket);
     b.scales = reinterpret_cast<float*>(w + lay.scales);
     b.bits = reinterpret_cast<uint32_t*>(w + lay.bits);
-    b.paged = geo.words % 8 == 0 || geo.n == 1 ? 1u : 0u;
+    b.paged = static_cast<uint64_t>(geo.n) * geo.num_chunks >= kBsPagedChunks ? 1u : 0u;
     std::vector<uint32_t> off32, cb;
     try {
       off32.resize(static_cast<size_t>(cfg->num_blocks) + 1);
@@ -615,8 +618,8 @@ static AmsParams ams_params(const compams_config& c, float lr, int cached_overri
   ap.lr = lr;
   ap.nf = static_cast<float>(c.n);
   ap.eps_out = c.eps_mode == COMPAMS_EPS_OUT_SQRT;
-  ap.cached_arrays =
-      cached_override >= 0 ? cached_override : step_cached_arrays(c.n, c.d, c.compressor == COMPAMS_NONE);
+  const int keep = c.compressor == COMPAMS_NONE ? kKeepFitting : c.compressor == COMPAMS_BLOCKSIGN ? kKeepSmall : kKeepNothing;
+  ap.cached_arrays = cached_override >= 0 ? cached_override : step_cached_arrays(c.n, c.d, keep);
   return ap;
 }
 

@@ -411,8 +411,8 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 
 // ---------------------------------------------------------------------------------------------
 // First pass for general block layouts as a grid of short workgroups: a wavefront takes a quarter of a chunk and ends, its
-// workgroup the same page of four spans (page_quarter; or the four quarters of a chunk where the sign words do not allow
-// it).  Bound by memory (12 bytes of a worker's coordinate) and by the instructions in between: 8 x 124439808 coordinates, blocks
+// workgroup the same page of four spans (page_quarter), in smaller problems the four quarters of a chunk (kBsPagedChunks).
+// Bound by memory (12 bytes of a worker's coordinate) and by the instructions in between: 8 x 124439808 coordinates, blocks
 // of 4096, 1995 us a workgroup per chunk with eight of them on a compute unit, 1845 in pages with five; 16 x 11181642,
 // layers, 342 either way.  A quarter that lies inside one block -- all but a few per row -- is summed in a register window
 // placed by the quarter's own largest magnitude and goes to the block's digits with at most three atomics; a quarter that

@@ -84,9 +84,8 @@ __device__ __forceinline__ void store_stream4(float* p, const float4& x) {
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // theta, m, v, vhat are touched once per step: read with streaming accesses.  CACHED: written through to the memory-side cache,
-// where the next step may find them; else written with streaming accesses too.  (Ordinary stores left dirty lines in the
-// dies' L2 as well: 16 x 1 M, top-k, 87.7 us a step, as here 85.0; identity, 16 x 11.2 M, 184 / 171.  Which is taken when:
-// step_cached_arrays.)
+// where the next step may find them (ordinary stores leave dirty lines in the dies' L2 as well: identity, 16 x 11.2 M, 184 us a
+// step, 171 as here); else written with streaming accesses too.  Which is taken when: step_cached_arrays.
 // base is the same in every lane, at the lane's offset from it.
 __device__ __forceinline__ float4 load_state4(const float* base, uint32_t at) { return load_stream4(base + at); }
 template <bool CACHED>

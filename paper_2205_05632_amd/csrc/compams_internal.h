@@ -85,8 +85,8 @@ inline uint32_t count_chunks_per_row_block(uint32_t n, uint32_t num_chunks) {
 // Chunks that a wavefront takes at a time of a block of cpw: two or eight.
 __host__ __device__ __forceinline__ uint32_t chunks_per_wave(uint32_t cpw) { return cpw < 32 ? cpw / 4 : 8; }
 
-// The candidate list of a selection problem is kept as kSubLists runs, chunk c of the problem appending to run
-// c % kSubLists, each run with a cursor in a 128-byte line of its own.  Atomics to one address are performed one
+// The candidate list of a selection problem is kept as kSubLists runs, workgroup w of its first pass appending to run
+// w % kSubLists, each run with a cursor in a 128-byte line of its own.  Atomics to one address are performed one
 // after the other (about 3 ns apart on MI355X); a chunk's allocation every 8 ns through a single cursor queued long
 // enough to cost the first pass 9 of 352 us, and cursors that share a line were little better.
 constexpr uint32_t kSubLists = 8;
@@ -96,6 +96,18 @@ constexpr uint32_t kCursorPitch = 32;  // words between the cursors of a problem
 // would overflow for nothing.
 constexpr uint32_t kSubListMinChunks = 64;
 constexpr uint32_t kNoCursorSet = 0xffffffffu;
+// So many chunks in all rows (one selection per row, rows of several runs) have their first pass in pages, with a segment of
+// the lists for every quarter of a chunk.  First pass (us; k = d / 100, chunks in order / pages), and the whole step: 8 x 2730
+// chunks 170 / 172; 16 x 2730 339 / 339, 502 / 507; 64 x 733 375 / 363, 508 / 502; 8 x 6240 398 / 388; 16 x 6240 827 / 781, 1322
+// / 1286; k = d / 1000, 8 x 3907 245 / 237; 8 x 30381 1945 / 1828; but 2 x 6240 99.7 / 99.7.
+constexpr uint32_t kPagedChunks = 45056;
+// Block-sign, which keeps no lists, from so many on (first pass, chunks in order / pages): 16 x 733 chunks 96.7 / 99.2; 8 x 2730
+// 169 / 172; 2 x 12208 186.5 / 184; 8 x 3907 247 / 239; 8 x 5128 314 / 313; 16 x 2730 332 / 333; 64 x 733 368 / 355; 8 x 7325
+// 466 / 443; 8 x 30381 1948 / 1844.
+constexpr uint32_t kBsPagedChunks = 24576;
+inline bool paged_first_pass(uint64_t n, uint32_t num_chunks) {
+  return num_chunks >= kSubListMinChunks && n * num_chunks >= kPagedChunks;
+}
 
 constexpr uint32_t kCountersPerRow = 8;  // == COMPAMS_COUNTERS_PER_ROW of the public header
 
@@ -252,9 +264,10 @@ struct TopkWorkspace {
   uint32_t* wire_total;    // n : words of the gap stream of the message being packed or unpacked
   uint32_t* wire_tile_off; // n * ceil(k / kWireTile) : where each tile of gaps starts in its stream
   uint32_t* wire_tile_sum; // n * ceil(k / kWireTile) : coordinates before each tile, while unpacking
-  uint2* desc;          // n * num_chunks : (offset, count) of the chunk's segment in the candidate list
-  uint2* desc2;         // n * num_chunks : offset of the chunk's segment in the band list; entries at or above the
-                        //                  band | entries in the band << 13 | kBandChunkOverflow
+  uint32_t desc_parts;  // segments of a chunk: one, or (rows whose first pass goes in pages) one for every quarter
+  uint2* desc;          // n * num_chunks * desc_parts : (offset, count) of the segment in the candidate list
+  uint2* desc2;         // n * num_chunks * desc_parts : offset of the segment in the band list; entries at or above the
+                        //                               band | entries in the band << 13
   uint2* band;          // n * band_cap   : (coordinate, fp32 bits) of the entries inside the band
   uint32_t* bhist;      // band_buckets(k) per problem : how many band entries fall into each bucket; zero between steps
   uint2* bnd;           // n * kBoundaryCap : the entries of the bucket that holds the threshold key
@@ -285,9 +298,7 @@ struct BlocksignWorkspace {
                         // the sum of a (row, block) is the sum of its replicas
   uint32_t acc_replicas;
   uint32_t* special;    // n * M : bit 0 = an infinity was seen, bit 1 = a NaN was seen
-  uint32_t paged;       // the first pass takes the rows in pages: the rows' sign words start on 32 bytes.  (Where they do not,
-                        // two dies write the sector that two pages share, by halves: 16 x 11181642, layers, first pass and
-                        // server 426 us in pages, 424 in address order; 8 x 124439808, blocks of 4096 2520 / 2620)
+  uint32_t paged;       // the first pass takes the rows in pages (kBsPagedChunks)
   uint32_t* ticket;     // n : "last workgroup of the row" counters of the first pass; zero between launches
   float* scales;        // n * M
   uint32_t* bits;       // n * words
@@ -310,12 +321,15 @@ inline int cached_state_arrays(int64_t d) {
 
 // How many a step keeps there.  Between two steps lie a forward and a backward pass, so state that was left in the cache is
 // found there again only by a small model; of any other its dirty lines are written out in the way of the kernels that follow.
-// Top-k and block-sign keep it where the gradients and residuals would fit as well.  Measured (us a step; three contexts in
-// turn, state from HBM / one context's steps one after the other): 16 x 11.2 M, top-k kept 524 / 472, streamed 502 / 476;
-// block-sign 433 / 412, 408 / 412; 8 x 25.6 M, top-k, two of four kept 633 / 587, streamed 610 / 607; 16 x 1 M 85.0 kept, 87.3
-// streamed.  The identity compressor reads the gradients in the same pass: 172 / 167 kept, 173 / 175 streamed: what fits is kept.
-inline int step_cached_arrays(int64_t n, int64_t d, bool identity) {
-  return identity || (2 * n + 4) * 4 * d <= kCacheBudget ? cached_state_arrays(d) : 0;
+// Measured (us a step; three contexts in turn, state from HBM / one context's steps one after the other): top-k, 16 x 11.2 M,
+// kept 524 / 472, streamed 502 / 476; 8 x 25.6 M, two of four kept 633 / 587, streamed 610 / 607; 4 x 65536 kept 24.8, streamed
+// 24.5: never kept.  Block-sign, 16 x 11.2 M, 433 / 412, 408 / 412; 4 x 65536 11.9 kept, 12.05 streamed: kept where gradients
+// and residuals would fit as well.  The identity compressor reads the gradients in the same pass: 172 / 167 kept, 173 / 175
+// streamed: what fits is kept.
+enum : int { kKeepNothing = 0, kKeepSmall = 1, kKeepFitting = 2 };
+inline int step_cached_arrays(int64_t n, int64_t d, int keep) {
+  const bool keeps = keep == kKeepFitting || (keep == kKeepSmall && (2 * n + 4) * 4 * d <= kCacheBudget);
+  return keeps ? cached_state_arrays(d) : 0;
 }
 
 // Moment and parameter lines of Algorithm 2 for one coordinate: every product, sum, square root and

@@ -135,7 +135,8 @@ __device__ __forceinline__ uint32_t segment_request(TopkRow* rowp, uint32_t cnt)
 // (already stored) corrected gradients again.
 __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, uint32_t cnt,
                                               const float* __restrict__ er, uint32_t d, uint32_t c,
-                                              uint32_t thr_bucket, uint2* candr, uint32_t cap, uint2* descr) {
+                                              uint32_t thr_bucket, uint2* candr, uint32_t cap, uint2* descr,
+                                              uint32_t parts) {
   const uint32_t lane = lane_id();
   uint32_t off = 0;
   if (cnt) {
@@ -167,14 +168,17 @@ __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, 
       }
     }
   }
-  if (lane == 0) descr[c] = make_uint2(off, cnt);
+  if (lane < parts) {  // (parts of it one behind the other, where a chunk has several segments)
+    const uint32_t share = (cnt + parts - 1) / parts, at = share * lane < cnt ? share * lane : cnt;
+    descr[c * parts + lane] = make_uint2(off + at, cnt - at < share ? cnt - at : share);
+  }
 }
 
 __device__ __forceinline__ void flush_chunk(const uint2* stage, uint32_t cnt, const float* __restrict__ er, uint32_t d,
                                             uint32_t c, uint32_t thr_bucket, TopkRow* rowp, uint2* candr,
-                                            uint32_t cap, uint2* descr) {
+                                            uint32_t cap, uint2* descr, uint32_t parts) {
   const uint32_t raw = segment_request(rowp, cnt);
-  segment_write(raw, stage, cnt, er, d, c, thr_bucket, candr, cap, descr);
+  segment_write(raw, stage, cnt, er, d, c, thr_bucket, candr, cap, descr, parts);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -591,14 +595,19 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 // the entries at or above it are staged per wavefront in coordinate order, the chunk's segment of the candidate
 // list is allocated with one atomic for the whole workgroup, and the four quarters are written behind one
 // another.  The level-0 histogram is taken afterwards, from the candidate list (k_topk_level0).
+// In large problems (paged_first_pass) the workgroup takes the same page of four spans instead, a quarter of four different
+// chunks (page_quarter): one allocation still, but a segment of the lists for every quarter.  (Measured on the way: fewer
+// instructions between the loads and the stores, and stores as soon as a round's loads have come, made it slower, 8 x 30381
+// chunks 1828 -> 1899 us; all stores behind a barrier 1866; four workgroups per compute unit instead of five 1820, eight 1843.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kLeanRounds = kRounds / kWaves;  // rounds of a chunk per wavefront
 constexpr int kStageQ = 512;                   // staged candidates per wavefront (of at most 1024 coordinates)
+constexpr size_t kLeanLds = 14000;              // asked for on top of that: five workgroups per compute unit, see kStreamLds
 
 // UNI: grid (chunks, rows).  Otherwise (top-k inside every block) the launch is flat over map_first: a workgroup
 // per chunk of every segment in address order, and at the end the workgroups whose wavefronts take one micro
 // problem each; coordinates below are the segment's own, the lists hold coordinates of the worker's row.
-template <bool PEND, bool UNI>
+template <bool PEND, bool UNI, bool PAGED>
 __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
                                                     TopkWorkspace ws, TopkOptions opt, uint32_t use_guess) {
   __shared__ uint2 stage_all[kWaves * kStageQ];
@@ -617,12 +626,13 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     }
   }
   const SegCtx sc = seg_ctx<UNI, kClassFirst>(geo, opt, ws);
-  const uint32_t c = sc.group, row = sc.seg;
+  const Quarter quarter = PAGED ? page_quarter(sc.group, wave) : Quarter{sc.group, wave};
+  const uint32_t c = quarter.chunk, row = sc.seg;
   const float* gr = g + sc.elem_off;
   float* er = e + sc.elem_off;
   TopkRow* rowp = ws.rows + row;
   const uint32_t d = geo.d;
-  const uint32_t q0 = c * kChunk + wave * (kLeanRounds * 256);  // first coordinate of this wavefront's quarter
+  const uint32_t q0 = c * kChunk + quarter.part * (kLeanRounds * 256);  // first coordinate of this wavefront's quarter
   const bool full = (c + 1) * static_cast<uint64_t>(kChunk) <= d;
   // The chunk's loads go out before anything else is asked for: nothing below decides their addresses.
   float4 gv[kLeanRounds], ev[kLeanRounds];
@@ -650,8 +660,10 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
   uint32_t prev_lo = 0, prev_hi = 0;
   if constexpr (PEND) {
     const uint32_t* prev_off = ws.sel_off + sc.seloff_base;
-    prev_lo = table_u32(prev_off, c * kWaves + wave);
-    prev_hi = table_u32(prev_off, c * kWaves + wave + 1);
+    if (!PAGED || q0 < d) {  // (eight workgroups take eight chunks, also where the row ends before)
+      prev_lo = table_u32(prev_off, c * kWaves + quarter.part);
+      prev_hi = table_u32(prev_off, c * kWaves + quarter.part + 1);
+    }
   }
   const bool pred = use_guess && rw[0] != 0;  // workgroup-uniform
   // the band [blo, bhi) of keys: empty (no key is >= 0xffffffff) unless the row carries one
@@ -747,10 +759,10 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     btotal += tb;
     atotal += sh_above[w];
   }
-  // the run this chunk appends to, its share of the capacities and its cursors (candidates in the low half of a
+  // the run this workgroup appends to, its share of the capacities and its cursors (candidates in the low half of a
   // 64-bit word, band entries in the high half: one atomic advances both)
   const bool runs = sc.cursor_set != kNoCursorSet;  // workgroup-uniform
-  const uint32_t run = runs ? c % kSubLists : 0u;
+  const uint32_t run = runs ? sc.group % kSubLists : 0u;
   const uint32_t run_cap = runs ? opt.cap / kSubLists : opt.cap;
   const uint32_t run_base = run * run_cap;
   const uint32_t brun_cap = runs ? opt.band_cap / kSubLists : opt.band_cap;
@@ -763,12 +775,19 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     const uint32_t off = static_cast<uint32_t>(old), boff = static_cast<uint32_t>(old >> 32);
     sh_off = off;
     sh_boff = boff;
-    ws.desc[sc.chunk_base + c] = make_uint2(run_base + off, total);
-    if (banded) ws.desc2[sc.chunk_base + c] = make_uint2(brun_base + boff, atotal | (btotal << 13));
+    if constexpr (!PAGED) {
+      ws.desc[sc.chunk_base + c] = make_uint2(run_base + off, total);
+      if (banded) ws.desc2[sc.chunk_base + c] = make_uint2(brun_base + boff, atotal | (btotal << 13));
+    }
     if (atotal) atomicAdd(runs ? cur + kCursorAboveWord : &rowp->above, atotal);  // nobody waits for it
   }
   __syncthreads();
   const uint32_t off = sh_off, boff = sh_boff;
+  if (PAGED && lane == 0 && c < geo.num_chunks) {  // a quarter has a segment of its own
+    const size_t at = (sc.chunk_base + c) * kWaves + quarter.part;
+    ws.desc[at] = make_uint2(run_base + off + before, cnt);
+    if (banded) ws.desc2[at] = make_uint2(brun_base + boff + bbefore, above_w | (band_w << 13));
+  }
   if (off + total > run_cap) return;  // the list has overflowed and will not be used (nor will the band)
   const bool band_fits = boff + btotal <= brun_cap;  // else the band has overflowed and will not be used
   uint2* dst = ws.cand + sc.cand_base + run_base + off + before;
@@ -945,6 +964,37 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
   return L;
 }
 
+// How a wavefront that takes `group` (two or eight) chunks at a time shares its lanes out among their segments, `parts` (one
+// or four) to a chunk: every segment has the same number of lanes, which take its entries in turn, so that the segments of all
+// the chunks are requested together however short they are.
+struct SegmentLanes {
+  uint32_t lanes;    // lanes per segment
+  uint32_t segment;  // the lane's, counted from the group's first
+  uint32_t chunk;    // ... and its chunk
+  uint32_t sub;      // the lane's number among those of the segment
+  bool first;        // it is the first lane of its chunk
+};
+__device__ __forceinline__ SegmentLanes segment_lanes(uint32_t group, uint32_t parts) {
+  const uint32_t lane = lane_id(), per_chunk = 64u / group;
+  SegmentLanes s;
+  s.lanes = per_chunk / parts;
+  s.segment = lane / s.lanes;
+  s.chunk = lane / per_chunk;
+  s.sub = lane % s.lanes;
+  s.first = lane % per_chunk == 0;
+  return s;
+}
+// Sum over the lanes of a chunk: 8 or 32 consecutive ones.
+__device__ __forceinline__ uint32_t chunk_sum(uint32_t v, uint32_t group) {
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
+  if (group < 8) {  // uniform
+    v += __shfl_xor(v, 8, 64);
+    v += __shfl_xor(v, 16, 64);
+  }
+  return v;
+}
+
 // ---------------------------------------------------------------------------------------------
 // The selection in one launch, for problems whose threshold key falls inside the band the first pass was given.
 // Same geometry as the counting kernel: a workgroup owns a contiguous block of geo.count_cpw chunks.
@@ -981,15 +1031,17 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   TopkRow* rowp = ws.rows + row;
   uint32_t* bh = ws.bhist + sc.bhist_base;
   const uint32_t wave = uniform_u32(t >> 6), lane = lane_id();
-  constexpr int kGroup = 8;  // chunks a wavefront takes at a time: descriptors with one load, entries together
+  // A wavefront takes up to eight chunks at a time, the lanes shared out among their segments (SegmentLanes).
   // Everything that can be asked for before anything is known goes out together (a workgroup's work is a chain
   // of round trips otherwise): the control block and the cursors, the bucket histogram, the counts above the
   // band, the first descriptors.
-  const uint2* d2 = ws.desc2 + sc.chunk_base;
-  const uint32_t group = chunks_per_wave(cpw);  // <= kGroup
+  const uint32_t parts = ws.desc_parts;
+  const uint2* d2 = ws.desc2 + sc.chunk_base * parts;
+  const uint32_t group = chunks_per_wave(cpw);
   const uint32_t c_first = start + wave * group;
+  const SegmentLanes sl = segment_lanes(group, parts);
   uint2 ds = make_uint2(0, 0);
-  if (opt.band && lane < group && c_first + lane < end) ds = d2[c_first + lane];  // (no such table without a band)
+  if (opt.band && c_first + sl.chunk < end) ds = d2[c_first * parts + sl.segment];  // (no such table without a band)
   // (thread t's buckets are consecutive: 8 of the few, 32 of the many, of which the first 8 lie where the few do and the
   // others are asked for below, with the band entries)
   constexpr uint32_t kQuadsFew = kBandBucketsFew / kWG / 4, kQuadsMany = kBandBucketsMany / kWG / 4;
@@ -1046,24 +1098,27 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   }
   // the band entries of this wavefront's first chunks: requested before the histogram is looked at
   const uint2* bandr = ws.band + sc.band_base;
-  uint32_t off[kGroup], cnt[kGroup];
-  uint2 a[kGroup];
-  auto request = [&](const uint2& d) {
-    uint32_t cnt_l = (d.y >> 13) & 0x1fffu;
-    if (d.x > opt.band_cap) cnt_l = 0;  // segments always lie inside the list; never read outside it
-    else if (cnt_l > opt.band_cap - d.x) cnt_l = opt.band_cap - d.x;
+  constexpr int kAhead = 8;  // entries of a lane requested together
+  uint2 a[kAhead];
+  uint32_t cnt = 0;  // entries of the lane's segment
+  auto take = [&] {
+    cnt = (ds.y >> 13) & 0x1fffu;
+    if (ds.x > opt.band_cap) cnt = 0;  // segments always lie inside the list; never read outside it
+    else if (cnt > opt.band_cap - ds.x) cnt = opt.band_cap - ds.x;
+  };
+  auto request = [&](uint32_t q0) {
 #pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
-      off[u] = __builtin_amdgcn_readlane(d.x, u);
-      cnt[u] = __builtin_amdgcn_readlane(cnt_l, u);
-      a[u] = lane < cnt[u] ? bandr[off[u] + lane] : make_uint2(0, 0);
+    for (int u = 0; u < kAhead; ++u) {
+      const uint32_t q = q0 + u * sl.lanes + sl.sub;
+      a[u] = q < cnt ? bandr[ds.x + q] : make_uint2(0, 0);
     }
   };
   if (many) {  // uniform
 #pragma unroll
     for (uint32_t i = kQuadsFew; i < kQuadsMany; ++i) x[i] = bh4[((i / kQuadsFew + rot) & 3u) * (kBandBucketsFew / 4) + i % kQuadsFew];
   }
-  request(ds);
+  take();
+  request(0);
   // ---- 1. the bucket of the threshold key: the thread whose buckets the count from the top crosses finds it ----
   bool inside = total_above < k && k - total_above <= band.total;  // uniform
   const uint32_t miss = total_above >= k ? 4u : (inside ? 6u : 5u);  // the threshold lies above / below the band; or (6) ...
@@ -1121,32 +1176,29 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     for (uint32_t c0 = c_first; c0 < end; c0 += kWaves * group) {
       if (c0 != c_first) {  // wave-uniform
         ds = make_uint2(0, 0);
-        if (lane < group && c0 + lane < end) ds = d2[c0 + lane];
-        request(ds);
+        if (c0 + sl.chunk < end) ds = d2[c0 * parts + sl.segment];
+        take();
+        request(0);
       }
-      uint32_t gt[kGroup];  // wave-uniform
+      uint32_t gt = sl.sub == 0 ? ds.y & 0x1fffu : 0u;  // this lane's part of the chunk's count
+      for (uint32_t q0 = 0; ballot64(q0 < cnt) != 0; q0 += kAhead * sl.lanes) {
+        if (q0) request(q0);
 #pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        gt[u] = 0;
-        for (uint32_t q = 0; q < cnt[u]; q += 64) {  // one trip unless the chunk holds more than 64 band entries
-          const uint2 en = q == 0 ? a[u] : (q + lane < cnt[u] ? bandr[off[u] + q + lane] : make_uint2(0, 0));
-          const bool ok = q + lane < cnt[u];
-          const uint32_t bucket = band_bucket(key_of_bits(en.y) - blo, bmul);
-          gt[u] += popc64(ballot64(ok && bucket > bstar));
+        for (int u = 0; u < kAhead; ++u) {
+          const bool ok = q0 + u * sl.lanes + sl.sub < cnt;
+          const uint32_t bucket = band_bucket(key_of_bits(a[u].y) - blo, bmul);
+          gt += ok && bucket > bstar ? 1u : 0u;
           if (ok && bucket == bstar) {
             const uint32_t slot = atomicAdd(&rowp->bnd_n, 1u);
             if (slot < kBoundaryCap) {  // always: the histogram counted these entries
-              __hip_atomic_store(&bnd[slot].x, en.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              __hip_atomic_store(&bnd[slot].y, en.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(&bnd[slot].x, a[u].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(&bnd[slot].y, a[u].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
           }
         }
       }
-      uint32_t mine = 0;
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u)
-        if (lane == static_cast<uint32_t>(u)) mine = gt[u];
-      if (lane < group && c0 + lane < end) l_gt[c0 - start + lane] = (ds.y & 0x1fffu) + mine;
+      gt = chunk_sum(gt, group);
+      if (sl.first && c0 + sl.chunk < end) l_gt[c0 - start + sl.chunk] = gt;
     }
     __syncthreads();
     // exclusive prefixes within the block: thread t takes `per` consecutive chunks
@@ -1850,7 +1902,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e
     if (ok && (key >> kL0Shift) == bstar) atomicAdd(&lh[(key >> kL1Shift) & (kNB1 - 1)], 1u);
   };
   if (mode == kModeNeedB) {
-    uint2* descr = ws.desc + sc.chunk_base;
+    uint2* descr = ws.desc + sc.chunk_base * ws.desc_parts;
     const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
     uint2* stage = stage_all + wave * kStage;
     const uint32_t stride = sc.groups * kWaves;
@@ -1873,7 +1925,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e
         stage_round(stage, cnt, j, bits, flag);
       }
       // fits by construction: the level-0 histogram counted exactly these entries
-      flush_chunk(stage, cnt, er, geo.d, c, bstar, rowp, candr, opt.cap, descr);
+      flush_chunk(stage, cnt, er, geo.d, c, bstar, rowp, candr, opt.cap, descr, ws.desc_parts);
     }
   } else if (mode == kModeCand) {
     const ListRuns runs = runs_of_row(rowp, opt.cap);
@@ -2046,7 +2098,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
   const uint32_t mode = rowp->mode, tau = rowp->tau;
   const float* er = e + sc.elem_off;
   const uint2* candr = ws.cand + sc.cand_base;
-  const uint2* descr = ws.desc + sc.chunk_base;
+  const uint2* descr = ws.desc + sc.chunk_base * ws.desc_parts;
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   if (mode == kModeDense) {
     for (uint32_t c = start + wave; c < end; c += kWaves) {
@@ -2061,58 +2113,35 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
       if (lane == 0) { l_gt[c - start] = gt; l_eq[c - start] = eq; }
     }
   } else {
-    // A wavefront takes kGroup consecutive chunks at a time: their descriptors come with one load, the first
-    // 128 entries of every segment with independent loads (two round trips for the whole group).
-    constexpr int kGroup = 8;
-    const uint32_t group = chunks_per_wave(cpw);  // <= kGroup
+    // A wavefront takes up to eight consecutive chunks at a time, the lanes shared out among their segments: the
+    // descriptors come with one load, then kAhead entries of every lane together.
+    constexpr int kAhead = 16;
+    const uint32_t group = chunks_per_wave(cpw), parts = ws.desc_parts;
+    const SegmentLanes sl = segment_lanes(group, parts);
     for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
       uint2 ds = make_uint2(0, 0);
-      if (lane < group && c0 + lane < end) ds = descr[c0 + lane];
+      if (c0 + sl.chunk < end) ds = descr[c0 * parts + sl.segment];
       if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
       else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
-      uint32_t off[kGroup], cnt[kGroup];
-      uint2 a[kGroup], b[kGroup];
+      uint32_t gt = 0, eq = 0;  // of this lane's entries
+      for (uint32_t q0 = 0; ballot64(q0 < ds.y) != 0; q0 += kAhead * sl.lanes) {
+        uint32_t bits[kAhead];
 #pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        off[u] = __builtin_amdgcn_readlane(ds.x, u);
-        cnt[u] = __builtin_amdgcn_readlane(ds.y, u);
-        a[u] = lane < cnt[u] ? candr[off[u] + lane] : make_uint2(0, 0);
-        b[u] = lane + 64 < cnt[u] ? candr[off[u] + lane + 64] : make_uint2(0, 0);
-      }
-      uint32_t gt[kGroup], eq[kGroup];  // wave-uniform
-      uint32_t longest = 0;
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const uint32_t ka = key_of_bits(a[u].y), kb = key_of_bits(b[u].y);
-        gt[u] = popc64(ballot64(lane < cnt[u] && ka > tau)) + popc64(ballot64(lane + 64 < cnt[u] && kb > tau));
-        eq[u] = popc64(ballot64(lane < cnt[u] && ka == tau)) + popc64(ballot64(lane + 64 < cnt[u] && kb == tau));
-        longest = cnt[u] > longest ? cnt[u] : longest;
-      }
-      // long segments: the next 128 entries of every segment of the group per trip, all loads in flight together
-      // (a trip per segment instead would make a group of long segments a chain of several dozen round trips)
-      for (uint32_t t = 128; t < longest; t += 128) {
-        uint32_t ka[kGroup], kb[kGroup];
-#pragma unroll
-        for (int u = 0; u < kGroup; ++u) {
-          ka[u] = kb[u] = 0;
-          if (t < cnt[u]) {  // wave-uniform
-            if (t + lane < cnt[u]) ka[u] = key_of_bits(candr[off[u] + t + lane].y);
-            if (t + 64 + lane < cnt[u]) kb[u] = key_of_bits(candr[off[u] + t + 64 + lane].y);
-          }
+        for (int u = 0; u < kAhead; ++u) {
+          const uint32_t q = q0 + u * sl.lanes + sl.sub;
+          bits[u] = q < ds.y ? candr[ds.x + q].y : 0u;
         }
 #pragma unroll
-        for (int u = 0; u < kGroup; ++u)
-          if (t < cnt[u]) {
-            const bool oa = t + lane < cnt[u], ob = t + 64 + lane < cnt[u];
-            gt[u] += popc64(ballot64(oa && ka[u] > tau)) + popc64(ballot64(ob && kb[u] > tau));
-            eq[u] += popc64(ballot64(oa && ka[u] == tau)) + popc64(ballot64(ob && kb[u] == tau));
-          }
+        for (int u = 0; u < kAhead; ++u) {
+          const bool ok = q0 + u * sl.lanes + sl.sub < ds.y;
+          const uint32_t key = key_of_bits(bits[u]);
+          gt += ok && key > tau ? 1u : 0u;
+          eq += ok && key == tau ? 1u : 0u;
+        }
       }
-      uint32_t my_gt = 0, my_eq = 0;
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u)
-        if (lane == static_cast<uint32_t>(u)) { my_gt = gt[u]; my_eq = eq[u]; }
-      if (lane < group && c0 + lane < end) { l_gt[c0 - start + lane] = my_gt; l_eq[c0 - start + lane] = my_eq; }
+      gt = chunk_sum(gt, group);
+      eq = chunk_sum(eq, group);
+      if (sl.first && c0 + sl.chunk < end) { l_gt[c0 - start + sl.chunk] = gt; l_eq[c0 - start + sl.chunk] = eq; }
     }
   }
   __syncthreads();
@@ -2296,7 +2325,8 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
 // streaming accesses (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
 // CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
-template <int ROLE, bool UNI, int NC, int NW, bool CLEAR = false>
+// QUARTERS: a chunk has a segment of the candidate list for every quarter, else one.
+template <int ROLE, bool UNI, int NC, int NW, bool CLEAR, bool QUARTERS>
 __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_final(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
     const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
@@ -2369,7 +2399,15 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
                     "words read below");
       const uint4 ra = reinterpret_cast<const uint4*>(ws.rows + rowi)[2];
       const uint2 rb = reinterpret_cast<const uint2*>(ws.rows + rowi)[6];
-      const uint2 ds = ws.desc[f.chunk0 + i_lane * f.chunk_stride + c];
+      const size_t chunk_i = f.chunk0 + i_lane * f.chunk_stride + c;
+      uint4 da, db = make_uint4(0, 0, 0, 0);  // the chunk's segments of the candidate list: one, or one for every quarter
+      if constexpr (QUARTERS) {
+        da = reinterpret_cast<const uint4*>(ws.desc)[2 * chunk_i];
+        db = reinterpret_cast<const uint4*>(ws.desc)[2 * chunk_i + 1];
+      } else {
+        const uint2 ds = ws.desc[chunk_i];
+        da = make_uint4(ds.x, ds.y, 0, 0);
+      }
       const uint4 rec = ws.chunk_rec[f.chunk0 + i_lane * f.chunk_stride + c];
       uint2 pre = make_uint2(0, 0);
       if (my_block) pre = ws.blk_prefix[static_cast<size_t>(rowi) * kMaxCountBlocks + my_block];
@@ -2377,10 +2415,13 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
       const bool dense = ra.x != kFastBand && ra.y == kModeDense;
       const bool partial = have && !fast && ra.w != rb.x;  // some of the row's ties are left out
       const uint32_t tau = ra.z, r = ra.w, tie = fast ? rb.y : 0xffffffffu;
-      const uint32_t off = ds.x;  // of the chunk's segment in the candidate list
-      uint32_t cnt = ds.y;
-      if (off > f.cap) cnt = 0;  // segments always lie inside the list; never read outside it
-      else if (cnt > f.cap - off) cnt = f.cap - off;
+      auto inside = [&](uint32_t off, uint32_t n) {  // segments always lie inside the list; never read outside it
+        return off > f.cap ? 0u : n > f.cap - off ? f.cap - off : n;
+      };
+      // the segments as one list: entry q lies at q + shift, where the segment it is in says how far the list is shifted
+      const uint32_t end0 = inside(da.x, da.y), end1 = end0 + inside(da.z, da.w), end2 = end1 + inside(db.x, db.y);
+      const uint32_t shift0 = da.x, shift1 = da.z - end0, shift2 = db.x - end1, shift3 = db.z - end2;
+      uint32_t cnt = end2 + inside(db.z, db.w);
       if (dense) cnt = c_len;    // no list: the chunk's coordinates themselves
       if (!have) cnt = 0;
       const uint32_t dense_mask = static_cast<uint32_t>(ballot64(dense));
@@ -2394,8 +2435,15 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
             if (q < w.n) {
               if ((dense_mask >> w.i) & 1u)
                 to.en[s] = make_uint2(c_lo + q, __float_as_uint((e + static_cast<int64_t>(i) * geo.ld + f.coord_base + c_lo)[q]));
-              else
-                to.en[s] = (ws.cand + f.cand0 + i * f.cand_stride + __builtin_amdgcn_readlane(off, w.i))[q];
+              else {
+                uint32_t at = __builtin_amdgcn_readlane(shift0, w.i);
+                if constexpr (QUARTERS) {
+                  at = q < static_cast<uint32_t>(__builtin_amdgcn_readlane(end0, w.i)) ? at : __builtin_amdgcn_readlane(shift1, w.i);
+                  at = q < static_cast<uint32_t>(__builtin_amdgcn_readlane(end1, w.i)) ? at : __builtin_amdgcn_readlane(shift2, w.i);
+                  at = q < static_cast<uint32_t>(__builtin_amdgcn_readlane(end2, w.i)) ? at : __builtin_amdgcn_readlane(shift3, w.i);
+                }
+                to.en[s] = (ws.cand + f.cand0 + i * f.cand_stride)[q + at];
+              }
             }
             next_slot(w, cnt);
           }
@@ -2676,31 +2724,30 @@ __global__ __launch_bounds__(kWG) void k_topk_apply_clear(float* __restrict__ e,
 
 namespace {
 
-// The last kernel with NW wavefronts per chunk.  (Grids of sixteen always keep all four state arrays cached, unless the
-// context's option says otherwise.)
-template <int ROLE, bool UNI, int NW, bool CLEAR, typename... Args>
+// The last kernel with NW wavefronts per chunk.
+template <int ROLE, bool UNI, int NW, bool CLEAR, bool QUARTERS, typename... Args>
 void launch_final_of(uint32_t n, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
   const dim3 grid(workgroups), wg(NW * 64);
   if constexpr (ROLE == kWorkerHalf) {
     // No state, and no order among the workers: a workgroup per tile of them.  With all tiles in one workgroup a few chunks
     // leave the chip idle (50000 coordinates in seven blocks: the half of 300 workers 128 us / 76 as here, of 64 52 / 45).
     const dim3 grid_tiles(workgroups, (n + kTileWorkers - 1) / kTileWorkers);
-    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR>, grid_tiles, wg, stream, args...);
-  } else if constexpr (CLEAR && NW == kFinalFew) {  // (so short that its whole state stays in the memory-side cache)
-    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR>, grid, wg, stream, args...);
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid_tiles, wg, stream, args...);
+  } else if constexpr (CLEAR) {  // (a call that stands for itself has no option)
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
   } else {
-#define COMPAMS_FINAL(NC) k_topk_final<ROLE, UNI, NC, NW, CLEAR>
+#define COMPAMS_FINAL(NC) k_topk_final<ROLE, UNI, NC, NW, CLEAR, QUARTERS>
     COMPAMS_LAUNCH_BY_CACHED(cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL, grid, wg, stream, args...);
 #undef COMPAMS_FINAL
   }
 }
 
-template <int ROLE, bool UNI, bool CLEAR, typename... Args>
+template <int ROLE, bool UNI, bool CLEAR, bool QUARTERS = false, typename... Args>
 void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
   switch (final_wavefronts(workgroups, geo, !UNI)) {
-    case kFinalFew: launch_final_of<ROLE, UNI, kFinalFew, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
-    case kFinalSome: launch_final_of<ROLE, UNI, kFinalSome, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
-    default: launch_final_of<ROLE, UNI, kFinalMany, CLEAR>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
+    case kFinalFew: launch_final_of<ROLE, UNI, kFinalFew, CLEAR, QUARTERS>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
+    case kFinalSome: launch_final_of<ROLE, UNI, kFinalSome, CLEAR, QUARTERS>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
+    default: launch_final_of<ROLE, UNI, kFinalMany, CLEAR, QUARTERS>(geo.n, cached_arrays, L, workgroups, stream, args...); break;
   }
 }
 
@@ -2714,7 +2761,9 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const uint32_t G = groups_per_row(geo.n, geo.num_chunks);
   const dim3 grid_rows(G, geo.n), wg(kWG);
   const uint32_t use_guess = first_pass_may_predict || whole ? 1u : 0u;
-  const dim3 grid_chunks(geo.num_chunks, geo.n);
+  const bool paged = ws.desc_parts > 1;
+  const dim3 grid_first(paged ? page_groups(geo.num_chunks) : geo.num_chunks, geo.n);
+  const size_t lds_first = paged ? kLeanLds : 0;
   // Short rows are selected by a workgroup each (where the line lies: see there), unless no row of this step has a guess.
   const bool pick = geo.num_chunks <= kPickChunks && use_guess;
   TopkOptions opt = options;
@@ -2725,10 +2774,9 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
-  if (clear_pending)
-    launch(L, kSlotPassA, k_topk_lean<true, true>, grid_chunks, wg, stream, g, e, geo, ws, opt, use_guess);
-  else
-    launch(L, kSlotPassA, k_topk_lean<false, true>, grid_chunks, wg, stream, g, e, geo, ws, opt, use_guess);
+  auto* first = clear_pending ? (paged ? k_topk_lean<true, true, true> : k_topk_lean<true, true, false>)
+                              : (paged ? k_topk_lean<false, true, true> : k_topk_lean<false, true, false>);
+  launch_lds(L, kSlotPassA, first, grid_first, wg, lds_first, stream, g, e, geo, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (pick) {
     launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, e, geo, ws, opt, use_guess);
@@ -2760,8 +2808,13 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   if (whole)
     launch_final<kWholeStep, true, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
                                          none);
+  else if (role == kWorkerHalf && paged)
+    launch_final<kWorkerHalf, true, false, true>(geo, 0, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap, none);
   else if (role == kWorkerHalf)
     launch_final<kWorkerHalf, true, false>(geo, 0, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap, none);
+  else if (paged)
+    launch_final<kWholeStep, true, false, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt,
+                                                ap, none);
   else
     launch_final<kWholeStep, true, false>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
                                           none);
@@ -2778,9 +2831,9 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   const dim3 wg(kWG);
   const uint32_t use_guess = first_pass_may_predict ? 1u : 0u;
   if (clear_pending)
-    launch(L, kSlotPassA, k_topk_lean<true, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
+    launch(L, kSlotPassA, k_topk_lean<true, false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
   else
-    launch(L, kSlotPassA, k_topk_lean<false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
+    launch(L, kSlotPassA, k_topk_lean<false, false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (flat.wg_count) {
     launch(L, kSlotBand, k_topk_band<false>, dim3(flat.wg_count), wg, stream, geo, ws, opt, use_guess);
@@ -2814,7 +2867,7 @@ hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const 
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
   const TopkFlat none{};
-  launch_final_of<kServerHalf, true, kFinalMany, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
+  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
                                                         ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;

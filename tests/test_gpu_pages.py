@@ -1,6 +1,6 @@
 """The dense passes in pages (a die's workgroups take the same 4 KB page of every 32 KB span) at the sizes where the walk
-could miss or repeat something: one page more or less than a span, a group of spans or a group of workgroups; rows whose
-sign words start on 32 bytes (pages) and rows whose do not (address order); magnitudes that leave a quarter's window.
+could miss or repeat something: one page more or less than a span, a group of spans or a group of workgroups; and the
+first passes of block-sign on magnitudes that leave a quarter's window, in pages (large problems) and in address order.
 Everything is compared with the oracle bit for bit, as every operation is fixed."""
 import numpy as np
 import pytest
@@ -60,3 +60,38 @@ def test_blocksign_sizes(n, d, size):
 @pytest.mark.parametrize("d", [1, 255, 1027, SPAN, GROUP - 1, GROUP, GROUP + 1, 3 * GROUP + SPAN + 5])
 def test_identity_sizes(n, d):
     run(Pair(n, d, np.ones(d, np.float32), B.NONE), n, d, "plain", with_e=False)
+
+
+# Block-sign goes in pages from 24576 chunks in all rows on.
+@pytest.mark.parametrize("n,d,size", [(1600, 16 * 4096 - 3100, 4096), (1100, 23 * 4096 + 1, 100000)])
+def test_blocksign_in_pages(n, d, size):
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d, np.float32), B.BLOCKSIGN, block_offsets=offsets(d, size))
+    base = values(rng, 2, d, "plain")
+    odd = [values(rng, 2, d, kind) for kind in ("zeros", "wide", "special", "ends")]
+    for t in range(3):
+        g = np.stack([np.roll(base[(t + i) % 2], 37 * i + 1001 * t) for i in range(n)])
+        for i, o in enumerate(odd):
+            g[7 * i + t] = o[t % 2]
+        p.step(g, 1e-3, label=f"{n} x {d} step {t}", with_e=(t == 2))
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
+# Top-k goes in pages from 45056 chunks in all rows on: tests of whole rows with as many rows as that takes, of a length at
+# which the last span, the last chunk and the last quarter are cut.
+@pytest.mark.parametrize("n,d,k", [(700, 65 * 4096 - 3100, 400), (640, 71 * 4096 + 1, 9000)])
+def test_topk_in_pages(n, d, k):
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d, np.float32), B.TOPK, k=k)
+    scale = np.repeat(10.0 ** rng.uniform(-2, 0, d // 5000 + 1), 5000)[:d].astype(np.float32)
+    base = rng.standard_normal((2, d)).astype(np.float32)
+    for t in range(4):  # (rows are shifted copies: every row its own selection without drawing all of them)
+        g = np.stack([np.roll(base[(t + i) % 2], 37 * i + 1001 * t) for i in range(n)]) * scale
+        if t == 2:
+            g[1] = 1.0                      # equal magnitudes: ties, a list that overflows, the general kernels
+            g[2] *= 8.0                     # a threshold far above its window
+            g[3, : d // 2] = 0.0
+        p.step(g, 1e-3, label=f"{n} x {d} step {t}", with_e=(t == 3))
+    assert all(p.exact.values()), p.exact
+    p.close()
