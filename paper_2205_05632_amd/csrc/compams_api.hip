@@ -618,8 +618,7 @@ static AmsParams ams_params(const compams_config& c, float lr, int cached_overri
   ap.lr = lr;
   ap.nf = static_cast<float>(c.n);
   ap.eps_out = c.eps_mode == COMPAMS_EPS_OUT_SQRT;
-  const int keep = c.compressor == COMPAMS_NONE ? kKeepFitting : c.compressor == COMPAMS_BLOCKSIGN ? kKeepSmall : kKeepNothing;
-  ap.cached_arrays = cached_override >= 0 ? cached_override : step_cached_arrays(c.n, c.d, keep);
+  ap.cached_arrays = cached_override >= 0 ? cached_override : step_cached_arrays(c.d, c.compressor == COMPAMS_NONE);
   return ap;
 }
 

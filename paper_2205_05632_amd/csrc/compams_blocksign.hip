@@ -668,8 +668,8 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
     float4 th[kQ], mm[kQ], vv[kQ], vh[kQ];
 #pragma unroll
     for (int r = 0; r < kQ; ++r) {
-      th[r] = load_state4(theta + q0 + r * 256, lane * 4); mm[r] = load_state4(m + q0 + r * 256, lane * 4);
-      vv[r] = load_state4(v + q0 + r * 256, lane * 4); vh[r] = load_state4(vhat + q0 + r * 256, lane * 4);
+      th[r] = load_state4<(NC > 0)>(theta + q0 + r * 256, lane * 4); mm[r] = load_state4<(NC > 1)>(m + q0 + r * 256, lane * 4);
+      vv[r] = load_state4<(NC > 2)>(v + q0 + r * 256, lane * 4); vh[r] = load_state4<(NC > 3)>(vhat + q0 + r * 256, lane * 4);
     }
     bs_share_sums<kQ>(sum, geo, ws, b, q0, lane);
 #pragma unroll
@@ -679,10 +679,10 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
       ams_update(sum[r][1] / p.nf, th[r].y, mm[r].y, vv[r].y, vh[r].y, p);
       ams_update(sum[r][2] / p.nf, th[r].z, mm[r].z, vv[r].z, vh[r].z, p);
       ams_update(sum[r][3] / p.nf, th[r].w, mm[r].w, vv[r].w, vh[r].w, p);
-      store_state4<(NC > 0)>(theta + jr, lane * 4, th[r]);
-      store_state4<(NC > 1)>(m + jr, lane * 4, mm[r]);
-      store_state4<(NC > 2)>(v + jr, lane * 4, vv[r]);
-      store_state4<(NC > 3)>(vhat + jr, lane * 4, vh[r]);
+      store_state4(theta + jr, lane * 4, th[r]);
+      store_state4(m + jr, lane * 4, mm[r]);
+      store_state4(v + jr, lane * 4, vv[r]);
+      store_state4(vhat + jr, lane * 4, vh[r]);
     }
     return;
   }
@@ -696,8 +696,8 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
     // the optimizer state of this round is requested first; the sign/scale loop runs while it travels
     float4 th = make_float4(0.f, 0.f, 0.f, 0.f), mm = th, vv = th, vh = th;
     if (ok[3]) {
-      th = load_state4(theta + j0, lane * 4); mm = load_state4(m + j0, lane * 4);
-      vv = load_state4(v + j0, lane * 4); vh = load_state4(vhat + j0, lane * 4);
+      th = load_state4<(NC > 0)>(theta + j0, lane * 4); mm = load_state4<(NC > 1)>(m + j0, lane * 4);
+      vv = load_state4<(NC > 2)>(v + j0, lane * 4); vh = load_state4<(NC > 3)>(vhat + j0, lane * 4);
     }
     while (table_u32(off, b + 1) <= j0) ++b;
     const uint32_t j_end = (j0 + 256 < d) ? j0 + 256 : d;
@@ -749,10 +749,10 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
       ams_update(sum[1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(sum[2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(sum[3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4<(NC > 0)>(theta + j0, lane * 4, th);
-      store_state4<(NC > 1)>(m + j0, lane * 4, mm);
-      store_state4<(NC > 2)>(v + j0, lane * 4, vv);
-      store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
+      store_state4(theta + j0, lane * 4, th);
+      store_state4(m + j0, lane * 4, mm);
+      store_state4(v + j0, lane * 4, vv);
+      store_state4(vhat + j0, lane * 4, vh);
     } else {
       for (int s = 0; s < 4; ++s)
         if (ok[s]) {
@@ -785,8 +785,8 @@ __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ 
   // the optimizer state is requested first; the workers' gradients follow sixteen rows at a time, loads together
   float4 th = make_float4(0.f, 0.f, 0.f, 0.f), mm = th, vv = th, vh = th;
   if (whole) {
-    th = load_state4(theta + j0, lane * 4); mm = load_state4(m + j0, lane * 4);
-    vv = load_state4(v + j0, lane * 4); vh = load_state4(vhat + j0, lane * 4);
+    th = load_state4<false>(theta + j0, lane * 4); mm = load_state4<false>(m + j0, lane * 4);
+    vv = load_state4<false>(v + j0, lane * 4); vh = load_state4<false>(vhat + j0, lane * 4);
   }
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
   constexpr int kRows = 16;
@@ -810,10 +810,10 @@ __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ 
     ams_update(sum[1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
     ams_update(sum[2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
     ams_update(sum[3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-    store_state4<(NC > 0)>(theta + j0, lane * 4, th);
-    store_state4<(NC > 1)>(m + j0, lane * 4, mm);
-    store_state4<(NC > 2)>(v + j0, lane * 4, vv);
-    store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
+    store_through4<(NC > 0)>(theta + j0, lane * 4, th);
+    store_through4<(NC > 1)>(m + j0, lane * 4, mm);
+    store_through4<(NC > 2)>(v + j0, lane * 4, vv);
+    store_through4<(NC > 3)>(vhat + j0, lane * 4, vh);
   } else {
     for (uint32_t s = 0; s < 4 && j + s < geo.d; ++s) {
       float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
@@ -860,10 +860,10 @@ __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, flo
   for (int r = 0; r < kR; ++r) {
     const size_t j = j0 + r * kWG * 4;
     if (j + at + 3 < count) {
-      x[r][0] = load_state4(a0 + j, at);
-      if (A > 1) x[r][1] = load_state4(a1 + j, at);
-      if (A > 2) x[r][2] = load_state4(a2 + j, at);
-      if (A > 3) x[r][3] = load_state4(a3 + j, at);
+      x[r][0] = load_state4<(NC > 0)>(a0 + j, at);
+      if (A > 1) x[r][1] = load_state4<(NC > 1)>(a1 + j, at);
+      if (A > 2) x[r][2] = load_state4<(NC > 2)>(a2 + j, at);
+      if (A > 3) x[r][3] = load_state4<(NC > 3)>(a3 + j, at);
     }
   }
 #pragma unroll
@@ -874,10 +874,10 @@ __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, flo
       for (int a = 0; a < A; ++a) {
         x[r][a].x += 1.0f; x[r][a].y += 1.0f; x[r][a].z += 1.0f; x[r][a].w += 1.0f;
       }
-      store_state4<(NC > 0)>(a0 + j, at, x[r][0]);
-      if (A > 1) store_state4<(NC > 1)>(a1 + j, at, x[r][1]);
-      if (A > 2) store_state4<(NC > 2)>(a2 + j, at, x[r][2]);
-      if (A > 3) store_state4<(NC > 3)>(a3 + j, at, x[r][3]);
+      store_state4(a0 + j, at, x[r][0]);
+      if (A > 1) store_state4(a1 + j, at, x[r][1]);
+      if (A > 2) store_state4(a2 + j, at, x[r][2]);
+      if (A > 3) store_state4(a3 + j, at, x[r][3]);
     }
   }
 }

@@ -83,13 +83,18 @@ __device__ __forceinline__ void store_stream4(float* p, const float4& x) {
 // and it can be an operand of every lane's arithmetic without a register per lane.
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// theta, m, v, vhat are touched once per step: read with streaming accesses.  CACHED: written through to the memory-side cache,
-// where the next step may find them (ordinary stores leave dirty lines in the dies' L2 as well: identity, 16 x 11.2 M, 184 us a
-// step, 171 as here); else written with streaming accesses too.  Which is taken when: step_cached_arrays.
-// base is the same in every lane, at the lane's offset from it.
-__device__ __forceinline__ float4 load_state4(const float* base, uint32_t at) { return load_stream4(base + at); }
+// theta, m, v, vhat are touched once per step.  CACHED: read with
+// ordinary accesses, which leave them in the memory-side cache for the next step, else with streaming ones; written with
+// streaming accesses (ordinary stores leave dirty lines that are written out in the way of the kernels that follow).
 template <bool CACHED>
-__device__ __forceinline__ void store_state4(float* base, uint32_t at, const float4& x) {
+__device__ __forceinline__ float4 load_state4(const float* base, uint32_t at) {
+  if constexpr (CACHED) return *reinterpret_cast<const float4*>(base + at);
+  else return load_stream4(base + at);
+}
+__device__ __forceinline__ void store_state4(float* base, uint32_t at, const float4& x) { store_stream4(base + at, x); }
+// A store that leaves them there itself, for the kernel that reads the gradients in the same pass.  base: the same in every lane.
+template <bool CACHED>
+__device__ __forceinline__ void store_through4(float* base, uint32_t at, const float4& x) {
   if constexpr (CACHED) {
     const uint64_t p = reinterpret_cast<uint64_t>(base);
     const uint64_t q = (static_cast<uint64_t>(uniform_u32(static_cast<uint32_t>(p >> 32))) << 32) | uniform_u32(static_cast<uint32_t>(p));

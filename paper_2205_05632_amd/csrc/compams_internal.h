@@ -308,8 +308,8 @@ constexpr int kLimbs = 10;  // 10 digits of 32 bits cover 2^-149 .. 2^171
 struct AmsParams {
   float beta1, beta2, one_minus_beta1, one_minus_beta2, eps, lr, nf;
   int eps_out;  // 1: epsilon outside the square root
-  int cached_arrays;  // how many of theta, m, v, vhat (in that order) are written through to the memory-side cache for the
-                      // next step, the others streamed past it (see step_cached_arrays)
+  int cached_arrays;  // how many of theta, m, v, vhat (in that order) are left in the memory-side cache for the next step, the
+                      // others streamed past it (see step_cached_arrays)
 };
 
 // How many of the four state arrays the memory-side cache (256 MB) holds together, with room for what else passes through.
@@ -319,17 +319,16 @@ inline int cached_state_arrays(int64_t d) {
   return fit > 4 ? 4 : static_cast<int>(fit);
 }
 
-// How many a step keeps there.  Between two steps lie a forward and a backward pass, so state that was left in the cache is
-// found there again only by a small model; of any other its dirty lines are written out in the way of the kernels that follow.
-// Measured (us a step; three contexts in turn, state from HBM / one context's steps one after the other): top-k, 16 x 11.2 M,
-// kept 524 / 472, streamed 502 / 476; 8 x 25.6 M, two of four kept 633 / 587, streamed 610 / 607; 4 x 65536 kept 24.8, streamed
-// 24.5: never kept.  Block-sign, 16 x 11.2 M, 433 / 412, 408 / 412; 4 x 65536 11.9 kept, 12.05 streamed: kept where gradients
-// and residuals would fit as well.  The identity compressor reads the gradients in the same pass: 172 / 167 kept, 173 / 175
-// streamed: what fits is kept.
-enum : int { kKeepNothing = 0, kKeepSmall = 1, kKeepFitting = 2 };
-inline int step_cached_arrays(int64_t n, int64_t d, int keep) {
-  const bool keeps = keep == kKeepFitting || (keep == kKeepSmall && (2 * n + 4) * 4 * d <= kCacheBudget);
-  return keeps ? cached_state_arrays(d) : 0;
+// How many a step keeps there.  Between two steps lie a forward and a backward pass, so only a small model's state is found
+// there again; a larger one's lines only get in the way of what follows.  The identity compressor, which reads the gradients
+// in the same pass, writes through what fits (16 x 11.2 M, three contexts in turn / one context's steps one after the other:
+// 172 / 167 us, streamed 173 / 175).  Top-k and block-sign read all four with ordinary accesses or all with streaming ones
+// (three contexts in turn; us a step, ordinary / streaming): per layer 4 x 1 M 52.6 / 54.8, 8 x 3 M 99 / 103, 8 x 5 M 146 /
+// 150, 8 x 8 M 226 / 220; top-k 8 x 3 M 92.4 / 93.8, 8 x 6 M 161 / 159; 16 x 11.2 M 525 / 502 (one context alone 473 / 476), 8 x 25.6 M
+// 633 / 610; block-sign 8 x 3 M 77.4 / 79.3, 8 x 6 M 136.9 / 139.0, 16 x 11.2 M 428 / 408.
+constexpr int64_t kOrdinaryState = 5500000;  // coordinates
+inline int step_cached_arrays(int64_t d, bool identity) {
+  return identity ? cached_state_arrays(d) : d <= kOrdinaryState ? 4 : 0;
 }
 
 // Moment and parameter lines of Algorithm 2 for one coordinate: every product, sum, square root and

@@ -2321,8 +2321,7 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
   return f;
 }
 
-// NC: how many of theta, m, v, vhat (in that order) are written through to the memory-side cache, the others with
-// streaming accesses (a template parameter: as a run-time choice between otherwise identical branches the compiler
+// NC: how many of theta, m, v, vhat (in that order) are read with ordinary accesses, the others with streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
 // CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
 // QUARTERS: a chunk has a segment of the candidate list for every quarter, else one.
@@ -2679,18 +2678,17 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
     const uint32_t t = wave * (kPart / 4) + r * 64 + lane;
     const uint32_t j = j_lane + r * 256;
     if (j + 3 < d_end) {
-      const uint32_t j0 = f.base + wave * kPart + r * 256;  // the same in every lane
-      float4 th = load_state4(theta + j0, lane * 4), mm = load_state4(m + j0, lane * 4);
-      float4 vv = load_state4(v + j0, lane * 4), vh = load_state4(vhat + j0, lane * 4);
+      float4 th = load_state4<(NC > 0)>(theta, j), mm = load_state4<(NC > 1)>(m, j);
+      float4 vv = load_state4<(NC > 2)>(v, j), vh = load_state4<(NC > 3)>(vhat, j);
       const float4 s = gs4[t];
       ams_update(s.x / p.nf, th.x, mm.x, vv.x, vh.x, p);
       ams_update(s.y / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(s.z / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(s.w / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4<(NC > 0)>(theta + j0, lane * 4, th);
-      store_state4<(NC > 1)>(m + j0, lane * 4, mm);
-      store_state4<(NC > 2)>(v + j0, lane * 4, vv);
-      store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
+      store_state4(theta, j, th);
+      store_state4(m, j, mm);
+      store_state4(v, j, vv);
+      store_state4(vhat, j, vh);
     } else {
       for (uint32_t s = 0; s < 4 && j + s < d_end; ++s) {
         float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
@@ -2733,8 +2731,9 @@ void launch_final_of(uint32_t n, int cached_arrays, Launcher* L, uint32_t workgr
     // leave the chip idle (50000 coordinates in seven blocks: the half of 300 workers 128 us / 76 as here, of 64 52 / 45).
     const dim3 grid_tiles(workgroups, (n + kTileWorkers - 1) / kTileWorkers);
     launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid_tiles, wg, stream, args...);
-  } else if constexpr (CLEAR) {  // (a call that stands for itself has no option)
-    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
+  } else if constexpr (CLEAR) {  // (a call that stands for itself has no option: four or none)
+    if (cached_arrays) launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
+    else launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
   } else {
 #define COMPAMS_FINAL(NC) k_topk_final<ROLE, UNI, NC, NW, CLEAR, QUARTERS>
     COMPAMS_LAUNCH_BY_CACHED(cached_arrays, L, kSlotTopkFinal, COMPAMS_FINAL, grid, wg, stream, args...);
