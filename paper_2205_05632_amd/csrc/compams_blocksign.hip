@@ -547,10 +547,12 @@ __global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, fl
 // ---------------------------------------------------------------------------------------------
 // The residual  e = x - sign(x) * mu  on its own: when the caller asks for e while the update is still pending.  A grid
 // of short workgroups as the first pass (HBM-bound: 8 bytes per worker-coordinate; workgroups that walked many chunks,
-// and wrote the sign words once more: 16 x 11.2 M coordinates took 276 us, this 232).
+// and wrote the sign words once more: 16 x 11.2 M coordinates took 276 us, this 232, in pages 216; 8 x 600000, address
+// order 7.7, pages 8.8: as the first pass, see kBsPagedChunks).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWG) void k_bs_pass2(float* __restrict__ e, Geometry geo, BlocksignWorkspace ws) {
-  const Quarter quarter = page_quarter(blockIdx.x, uniform_u32(threadIdx.x >> 6));
+  const uint32_t wave = uniform_u32(threadIdx.x >> 6);
+  const Quarter quarter = ws.paged ? page_quarter(blockIdx.x, wave) : Quarter{blockIdx.x, wave};
   const uint32_t c = quarter.chunk, row = blockIdx.y, lane = lane_id();
   float* er = e + static_cast<int64_t>(row) * geo.ld;
   const uint32_t* __restrict__ off = ws.offsets;
@@ -925,7 +927,8 @@ hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& 
 }
 
 hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspace& ws, float* e, hipStream_t stream) {
-  hipLaunchKernelGGL(k_bs_pass2, dim3(page_groups(geo.num_chunks), geo.n), dim3(kWG), kStreamLds, stream, e, geo, ws);
+  const uint32_t groups = ws.paged ? page_groups(geo.num_chunks) : geo.num_chunks;
+  hipLaunchKernelGGL(k_bs_pass2, dim3(groups, geo.n), dim3(kWG), ws.paged ? kStreamLds : 0, stream, e, geo, ws);
   return hipGetLastError();
 }
 
