@@ -87,8 +87,11 @@ class Run:
             self.ctx.set_option(B.OPT_FORCE_DENSE, 1)
         if not band and self.comp in (B.TOPK, B.TOPK_BLOCKS):
             self.ctx.set_option(B.OPT_BAND, 0)
-        if cached_arrays >= 0:
-            self.ctx.set_option(B.OPT_CACHED_ARRAYS, cached_arrays)
+        # These steps follow each other with nothing in between: what fits the memory-side cache is found there by the next one,
+        # and the context is told to leave it there.  (By default the state of a larger model is streamed past that cache, because a
+        # training program's forward and backward pass lie in between.)
+        kept = cached_arrays if cached_arrays >= 0 else B.compams_cached_state_arrays(w.d)
+        self.ctx.set_option(B.OPT_CACHED_ARRAYS, kept)
         total = warmup + steps
         scale = W.coordinate_scale(w, self.dev)
         nbuf = total if grad_buffers <= 0 else min(total, grad_buffers)
@@ -205,7 +208,7 @@ def main():
                     help="ablation: every selection by the general kernels (no window carried over for the threshold key)")
     ap.add_argument("--cached-arrays", type=int, default=-1,
                     help="ablation: how many of theta, m, v, vhat the server kernels keep in the memory-side cache "
-                         "(0..4; default: the library's choice by size)")
+                         "(0..4; default: as many as fit it)")
     ap.add_argument("--grad-buffers", type=int, default=0,
                     help="how many distinct gradient buffers to cycle through (0: one per step)")
     ap.add_argument("--settle-each-step", action="store_true",
@@ -356,7 +359,8 @@ def main():
                    "num_blocks": (len(w.block_offsets()) - 1) if w.compressor == "blocksign" else 0,
                    "eps_mode": "out_sqrt" if args.eps_out else "in_sqrt",
                    "predict": not args.no_predict, "force_dense": args.force_dense, "band": not args.no_band,
-                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0 else "library's choice"},
+                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0
+                   else B.compams_cached_state_arrays(w.d)},
         "hbm_gbps": main_res["hbm_gbps"],
         "hbm_frac_of_peak": main_res["hbm_frac_of_peak"],
         "algorithmic_bytes_per_step": main_res["algorithmic_bytes_per_step"],

@@ -40,9 +40,9 @@ __device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave) {
   const uint32_t page = group % kDies, span = group / kDies * kSpansPerGroup + wave;
   return {span * (kSpanCoords / kChunk) + page / kWaves, page % kWaves};
 }
-// A dense pass asks for this much LDS that it has no use for: five workgroups per compute unit are enough to keep the memory
-// busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with five, 317 with
-// four, 373 with three).
+// A dense pass asks for this much LDS that it has no use for: four or five workgroups per compute unit are enough to keep the
+// memory busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with five, 317
+// with four, 373 with three).
 constexpr size_t kStreamLds = 32768;
 inline uint32_t page_groups(uint32_t num_chunks) { return (num_chunks + kDies - 1) / kDies * kDies; }
 static_assert(kPageCoords * kWaves == kChunk, "a page is a wavefront's quarter of a chunk");
