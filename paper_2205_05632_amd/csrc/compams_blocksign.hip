@@ -218,7 +218,7 @@ static_assert(kQuarter * 4 <= static_cast<int>(kWinAdds), "additions per lane in
 // after x has been formed and stored the magnitudes of its coordinates are summed in a register window and go
 // to its digits like any other partial sum.  A block with at most 8 coordinates in the round adds them one by
 // one instead (a layout of one-coordinate blocks would otherwise make 256 trips through the wavefront-wide
-// sum).  Rare: a few rounds per row in layouts worth the name.
+// sum).  Rare where the blocks are layers; with blocks of less than 1024 coordinates every round comes here.
 template <bool PEND>
 __device__ __forceinline__ void straddling_round(float4 g4, float4 e4, uint32_t j0, uint32_t d, uint32_t b,
                                               const uint32_t* __restrict__ off, const float* __restrict__ mur,
@@ -277,6 +277,66 @@ __device__ __forceinline__ void straddling_round(float4 g4, float4 e4, uint32_t 
       window_to_digits(A.sum, A.eh, dg + static_cast<size_t>(replica) * kLimbs);
     }
   }
+}
+
+// A quarter of a chunk, from coordinate q0 on, that lies inside one block; WHOLE: and inside the row.
+template <bool PEND, bool WHOLE>
+__device__ __forceinline__ void quarter_in_block(const float4 (&gq)[kQuarter], const float4 (&eq)[kQuarter], uint32_t q0,
+                                                 uint32_t d, float mu_b, float* __restrict__ er, uint32_t* __restrict__ bitr,
+                                                 uint32_t words, uint64_t* dg, uint32_t* specb) {
+  const uint32_t lane = lane_id();
+  uint32_t bits[kQuarter][4];
+  uint32_t kmax = 0, kmin = 0xffffffffu, my_word = 0;
+#pragma unroll
+  for (int u = 0; u < kQuarter; ++u) {
+    const uint32_t j = q0 + u * 256 + lane * 4;
+    const bool ok[4] = {WHOLE || j < d, WHOLE || j + 1 < d, WHOLE || j + 2 < d, WHOLE || j + 3 < d};
+    float ev[4] = {eq[u].x, eq[u].y, eq[u].z, eq[u].w};
+    const float gv[4] = {gq[u].x, gq[u].y, gq[u].z, gq[u].w};
+    float xv[4];
+    uint32_t nib = 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (PEND && ok[s]) ev[s] = ev[s] - (ev[s] < 0.0f ? -mu_b : mu_b);
+      xv[s] = ok[s] ? ev[s] + gv[s] : ev[s];  // columns at and beyond d keep their contents
+      nib |= (ok[s] && xv[s] < 0.0f ? 1u : 0u) << s;
+      bits[u][s] = ok[s] ? __float_as_uint(xv[s]) : 0u;  // and add nothing
+      const uint32_t key = bits[u][s] & 0x7fffffffu;
+      kmax = max(kmax, key);
+      kmin = min(kmin, key);
+    }
+    if (ok[0]) store_stream4(er + q0 + u * 256 + lane * 4, make_float4(xv[0], xv[1], xv[2], xv[3]));
+    // every eight lanes hold a word of the round; lane u of them keeps that of round u for one store of the quarter's 128 bytes
+    const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
+    my_word = (lane & 7u) == static_cast<uint32_t>(u) ? word : my_word;
+  }
+  const uint32_t widx = (q0 >> 5) + (lane & 7u) * 8u + (lane >> 3);
+  if ((lane & 7u) < static_cast<uint32_t>(kQuarter) && (WHOLE || widx < words)) bitr[widx] = my_word;
+  kmax = wave_max_u32(kmax);
+  // the window ends at the quarter's largest magnitude: 16 additions per lane, exact
+  WaveAcc A;
+  acc_reset(A);
+  acc_place(A, kmax);
+  if (kmax < 0x7f800000u && ballot64(kmin < A.klo) == 0) {  // wave-uniform: every magnitude lies inside it
+#pragma unroll
+    for (int u = 0; u < kQuarter; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) A.sum += static_cast<double>(__builtin_fabsf(__uint_as_float(bits[u][s])));  // exactly
+  } else {  // zeros, magnitudes far below the largest one, infinities, NaNs
+    uint32_t finite = 0;
+#pragma unroll
+    for (int u = 0; u < kQuarter; ++u)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t key = bits[u][s] & 0x7fffffffu;
+        finite = key < 0x7f800000u ? max(finite, key) : finite;
+      }
+    acc_place(A, wave_max_u32(finite));
+    const bool all[4] = {true, true, true, true};
+#pragma unroll
+    for (int u = 0; u < kQuarter; ++u) acc_add4(A, bits[u], all, dg, specb);
+  }
+  window_to_digits(A.sum, A.eh, dg);
 }
 
 // A block's scale from the digits of its exact sum (still carried in 64-bit words), its flags and its length: the digits
@@ -416,8 +476,12 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 // of 4096, 1995 us a workgroup per chunk with eight of them on a compute unit, 1845 in pages with five; 16 x 11181642,
 // layers, 342 either way.  A quarter that lies inside one block -- all but a few per row -- is summed in a register window
 // placed by the quarter's own largest magnitude and goes to the block's digits with at most three atomics; a quarter that
-// meets block ends or the row's end goes through the blocks it meets, round by round.  The pending residual update of the
-// previous step is applied to e as it is read.
+// meets block ends goes through the blocks it meets, round by round.  Either way it works from the one batch of loads in its
+// registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 683 / 496
+// us, of 1000 671 / 517; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
+// round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5).  Up to 96 registers cost nothing: five
+// workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous step is applied to e as
+// it is read.
 // ---------------------------------------------------------------------------------------------
 template <bool PEND>
 __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, const float* __restrict__ g,
@@ -437,7 +501,7 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
   const uint32_t d = geo.d;
   const uint32_t q0 = c * kChunk + quarter.part * (kQuarter * 256);  // first coordinate of this wavefront's quarter
   if (q0 >= d) return;                                               // wave-uniform; no barrier in here
-  // The quarter's loads go out before it is known whether it is a whole one (nothing is read beyond the row).
+  // The quarter's loads go out before it is known whether it is a whole one (nothing is read beyond the padded row).
   float4 gq[kQuarter], eq[kQuarter];
 #pragma unroll
   for (int u = 0; u < kQuarter; ++u) {
@@ -453,80 +517,28 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
   // a large block receives the sums of thousands of wavefronts: they go to one of several sets of digits (atomics to one
   // address are performed one after the other), which the finalize kernel adds up
   const uint32_t replica = group % ws.acc_replicas;
-  if (table_u32(off, b + 1) < q0 + kQuarter * 256) {  // the quarter meets block ends or the row's end (a scalar condition)
-    // (asked for again, round by round: the batch at a run-time index would lie in scratch memory, and a call for every round
-    // costs all quarters its registers)
+  const bool cut = q0 + kQuarter * 256 > d;  // by the row's end
+  if (table_u32(off, b + 1) < (cut ? d : q0 + kQuarter * 256)) {  // the quarter meets block ends (a scalar condition)
+    // (the rounds move up: the batch at a run-time index would lie in scratch memory)
 #pragma unroll 1
-    for (uint32_t u = 0; u < static_cast<uint32_t>(kQuarter); ++u) {
-      const uint32_t j0 = q0 + u * 256, j = j0 + lane * 4;
-      if (j0 >= d) break;
+    for (uint32_t j0 = q0; j0 < q0 + kQuarter * 256 && j0 < d; j0 += 256) {
       while (table_u32(off, b + 1) <= j0) ++b;
-      float4 g4 = make_float4(0.f, 0.f, 0.f, 0.f), e4 = g4;
-      if (j < d) {
-        g4 = load_stream4(gr + j);
-        e4 = load_stream4(er + j);
-      }
-      straddling_round<PEND>(g4, e4, j0, d, b, off, mur, er, bitr, geo.words, accr, blk_digits, replica, specr);
+      straddling_round<PEND>(gq[0], eq[0], j0, d, b, off, mur, er, bitr, geo.words, accr, blk_digits, replica, specr);
+#pragma unroll
+      for (int u = 0; u + 1 < kQuarter; ++u) { gq[u] = gq[u + 1]; eq[u] = eq[u + 1]; }
     }
     return;
   }
-  const float mu_b = PEND ? table_f32(mur, b) : 0.0f;
-  uint32_t bits[kQuarter][4];
-  uint32_t kmax = 0, kmin = 0xffffffffu, my_word = 0;
-#pragma unroll
-  for (int u = 0; u < kQuarter; ++u) {
-    float ev[4] = {eq[u].x, eq[u].y, eq[u].z, eq[u].w};
-    const float gv[4] = {gq[u].x, gq[u].y, gq[u].z, gq[u].w};
-    float xv[4];
-    uint32_t nib = 0;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (PEND) ev[s] = ev[s] - (ev[s] < 0.0f ? -mu_b : mu_b);
-      xv[s] = ev[s] + gv[s];
-      nib |= (xv[s] < 0.0f ? 1u : 0u) << s;
-      bits[u][s] = __float_as_uint(xv[s]);
-      const uint32_t key = bits[u][s] & 0x7fffffffu;
-      kmax = max(kmax, key);
-      kmin = min(kmin, key);
-    }
-    store_stream4(er + q0 + u * 256 + lane * 4, make_float4(xv[0], xv[1], xv[2], xv[3]));
-    // every eight lanes hold a word of the round; lane u of them keeps that of round u for one store of the quarter's 128 bytes
-    const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
-    my_word = (lane & 7u) == static_cast<uint32_t>(u) ? word : my_word;
-  }
-  if ((lane & 7u) < static_cast<uint32_t>(kQuarter)) bitr[(q0 >> 5) + (lane & 7u) * 8u + (lane >> 3)] = my_word;
-  kmax = wave_max_u32(kmax);
   uint64_t* dg = accr + static_cast<size_t>(b) * blk_digits + static_cast<size_t>(replica) * kLimbs;
-  // the window ends at the quarter's largest magnitude: 16 additions per lane, exact
-  WaveAcc A;
-  acc_reset(A);
-  acc_place(A, kmax);
-  if (kmax < 0x7f800000u && ballot64(kmin < A.klo) == 0) {  // wave-uniform: every magnitude lies inside it
-#pragma unroll
-    for (int u = 0; u < kQuarter; ++u)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) A.sum += static_cast<double>(__builtin_fabsf(__uint_as_float(bits[u][s])));  // exactly
-  } else {  // zeros, magnitudes far below the largest one, infinities, NaNs
-    uint32_t finite = 0;
-#pragma unroll
-    for (int u = 0; u < kQuarter; ++u)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const uint32_t key = bits[u][s] & 0x7fffffffu;
-        finite = key < 0x7f800000u ? max(finite, key) : finite;
-      }
-    acc_place(A, wave_max_u32(finite));
-    const bool all[4] = {true, true, true, true};
-#pragma unroll
-    for (int u = 0; u < kQuarter; ++u) acc_add4(A, bits[u], all, dg, specr + b);
-  }
-  window_to_digits(A.sum, A.eh, dg);
+  const float mu_b = PEND ? table_f32(mur, b) : 0.0f;
+  if (cut) quarter_in_block<PEND, false>(gq, eq, q0, d, mu_b, er, bitr, geo.words, dg, specr + b);
+  else quarter_in_block<PEND, true>(gq, eq, q0, d, mu_b, er, bitr, geo.words, dg, specr + b);
 }
 
 // SCALES: the workgroup of a row that finishes last also turns the row's sums into scales (4 rows of 65536, blocks of 4096:
 // 13.9 -> 12.6 us a step; where the line lies: scales_in_first_pass).
 template <bool PEND, bool SCALES>
-__global__ __launch_bounds__(kWG) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
+__global__ __launch_bounds__(kWG, 5) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
                                                   BlocksignWorkspace ws) {
   bs_lean_quarter<PEND>(blockIdx.x, blockIdx.y, g, e, geo, ws);
   if constexpr (SCALES) {
