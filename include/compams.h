@@ -196,8 +196,8 @@ enum {
   COMPAMS_OPT_CANDIDATE_CAP = 0, /* candidate-list capacity per worker, 0 .. the capacity the workspace was sized
                                     for (min(d, 8k + 65536)); a list that would not fit is not built.  Rows of 64
                                     chunks (262144 coordinates) and more keep the list as eight runs of an eighth
-                                    of the capacity each, filled by every eighth chunk of the row: a run that would
-                                    not fit counts as a list that would not fit */
+                                    of the capacity each, filled by the row's workgroups in turn: a run that would not
+                                    fit counts as a list that would not fit */
   COMPAMS_OPT_PREDICT = 1,       /* 1 (default): the first pass of a step already writes the candidate list, using
                                     the previous step's threshold bucket as a guess that is verified afterwards */
   COMPAMS_OPT_FORCE_DENSE = 2,   /* 1: never build a candidate list; every selection pass reads the whole row */

@@ -85,10 +85,11 @@ inline uint32_t count_chunks_per_row_block(uint32_t n, uint32_t num_chunks) {
 // Chunks that a wavefront takes at a time of a block of cpw: two or eight.
 __host__ __device__ __forceinline__ uint32_t chunks_per_wave(uint32_t cpw) { return cpw < 32 ? cpw / 4 : 8; }
 
-// The candidate list of a selection problem is kept as kSubLists runs, workgroup w of its first pass appending to run
-// w % kSubLists, each run with a cursor in a 128-byte line of its own.  Atomics to one address are performed one
-// after the other (about 3 ns apart on MI355X); a chunk's allocation every 8 ns through a single cursor queued long
-// enough to cost the first pass 9 of 352 us, and cursors that share a line were little better.
+// The candidate list of a selection problem is kept as kSubLists runs, which the workgroups of its first pass append to in
+// turn (in pages in another turn from one eight of them to the next), each run with a cursor in a 128-byte line of its own.
+// Atomics to one address are performed one after the other (about 3 ns apart on MI355X); a chunk's allocation every 8 ns
+// through a single cursor queued long enough to cost the first pass 9 of 352 us, and cursors that share a line were little
+// better.
 constexpr uint32_t kSubLists = 8;
 constexpr uint32_t kCursorPitch = 32;  // words between the cursors of a problem
 // A problem (row or block) of fewer chunks than this keeps its list as one run: its allocations are few, and

@@ -4,6 +4,7 @@ first passes of block-sign on magnitudes that leave a quarter's window, in pages
 Everything is compared with the oracle bit for bit, as every operation is fixed."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2205_05632_amd import binding as B
 
@@ -95,3 +96,23 @@ def test_topk_in_pages(n, d, k):
         p.step(g, 1e-3, label=f"{n} x {d} step {t}", with_e=(t == 3))
     assert all(p.exact.values()), p.exact
     p.close()
+
+
+# Large entries side by side in every row of a matrix whose width is a multiple of the span, so that all of them lie in the same
+# pages: the lists hold them all the same, and no row is read again once its window has settled.
+@pytest.mark.parametrize("n,d,k,width", [(8, 5700 * 4096 - 100, 230000, SPAN), (8, 5700 * 4096 - 100, 230000, GROUP),
+                                         (64, 733 * 4096 - 100, 250000, SPAN)])
+def test_large_columns_in_one_page(n, d, k, width):
+    ctx = B.Compams(n, d, torch.zeros(d, device="cuda"), compressor=B.TOPK, k=k)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    scale = torch.where(torch.arange(d, device="cuda") % width < PAGE, 1.0, 1e-3)
+    g = torch.zeros((n, ctx.ld), device="cuda")
+    for t in range(12):
+        for i in range(n):
+            g[i, :d].normal_(generator=gen).mul_(scale)
+        ctx.compams_step(g, 1e-3)
+        if t >= 6:
+            counters = ctx.compams_state("counters").cpu().numpy()
+            assert not (counters[:, 5] == 2).any(), (t, counters[:, 5])  # no candidate list overflowed
+            assert not counters[:, 0].any(), (t, counters[:, 0])         # no row was read again
+    ctx.close()
