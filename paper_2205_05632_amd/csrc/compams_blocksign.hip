@@ -479,16 +479,17 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 // meets block ends goes through the blocks it meets, round by round.  Either way it works from the one batch of loads in its
 // registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 683 / 496
 // us, of 1000 671 / 517; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
-// round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5).  Up to 96 registers cost nothing: five
-// workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous step is applied to e as
+// round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5; not in pages, where one quarter more or less
+// round by round is nothing and the second form in the kernel's code cost 8 x 124439808 1910 -> 1934 us).  Up to 96 registers
+// cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous step is applied to e as
 // it is read.
 // ---------------------------------------------------------------------------------------------
-template <bool PEND>
+template <bool PEND, bool PAGED>
 __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, const float* __restrict__ g,
                                                 float* __restrict__ e, const Geometry& geo, const BlocksignWorkspace& ws) {
   const uint32_t lane = lane_id();
   const uint32_t wave = uniform_u32(threadIdx.x >> 6);
-  const Quarter quarter = ws.paged ? page_quarter(group, wave) : Quarter{group, wave};
+  const Quarter quarter = PAGED ? page_quarter(group, wave) : Quarter{group, wave};
   const uint32_t c = quarter.chunk;
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   float* er = e + static_cast<int64_t>(row) * geo.ld;
@@ -517,9 +518,10 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
   // a large block receives the sums of thousands of wavefronts: they go to one of several sets of digits (atomics to one
   // address are performed one after the other), which the finalize kernel adds up
   const uint32_t replica = group % ws.acc_replicas;
-  const bool cut = q0 + kQuarter * 256 > d;  // by the row's end
-  if (table_u32(off, b + 1) < (cut ? d : q0 + kQuarter * 256)) {  // the quarter meets block ends (a scalar condition)
-    // (the rounds move up: the batch at a run-time index would lie in scratch memory)
+  const bool cut = !PAGED && q0 + kQuarter * 256 > d;  // by the row's end
+  if (table_u32(off, b + 1) < (cut ? d : q0 + kQuarter * 256)) {  // a scalar condition
+    // The quarter meets block ends, or, in pages, the row's end.  (The rounds move up: the batch at a run-time index would lie in
+    // scratch memory.)
 #pragma unroll 1
     for (uint32_t j0 = q0; j0 < q0 + kQuarter * 256 && j0 < d; j0 += 256) {
       while (table_u32(off, b + 1) <= j0) ++b;
@@ -537,10 +539,10 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
 
 // SCALES: the workgroup of a row that finishes last also turns the row's sums into scales (4 rows of 65536, blocks of 4096:
 // 13.9 -> 12.6 us a step; where the line lies: scales_in_first_pass).
-template <bool PEND, bool SCALES>
+template <bool PEND, bool SCALES, bool PAGED>
 __global__ __launch_bounds__(kWG, 5) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
                                                   BlocksignWorkspace ws) {
-  bs_lean_quarter<PEND>(blockIdx.x, blockIdx.y, g, e, geo, ws);
+  bs_lean_quarter<PEND, PAGED>(blockIdx.x, blockIdx.y, g, e, geo, ws);
   if constexpr (SCALES) {
     __shared__ uint32_t sh_last;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // this wavefront's atomics have been performed
@@ -909,8 +911,10 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
                           bool workers_only, hipStream_t stream, Launcher* L) {
   const dim3 grid_chunks(ws.paged ? page_groups(geo.num_chunks) : geo.num_chunks, geo.n), wg(kWG);
   const bool scales = scales_in_first_pass(geo, ws);
-  auto* first = residual_pending ? (scales ? k_bs_lean<true, true> : k_bs_lean<true, false>)
-                                 : (scales ? k_bs_lean<false, true> : k_bs_lean<false, false>);
+  auto* first = ws.paged ? (residual_pending ? (scales ? k_bs_lean<true, true, true> : k_bs_lean<true, false, true>)
+                                             : (scales ? k_bs_lean<false, true, true> : k_bs_lean<false, false, true>))
+                         : (residual_pending ? (scales ? k_bs_lean<true, true, false> : k_bs_lean<true, false, false>)
+                                             : (scales ? k_bs_lean<false, true, false> : k_bs_lean<false, false, false>));
   launch_lds(L, kSlotBsPass1, first, grid_chunks, wg, kStreamLds, stream, g, e, geo, ws);
   COMPAMS_CHECK_LAUNCH();
   if (!scales) {
