@@ -388,6 +388,7 @@ static void bind_topk_workspace(compams_ctx* ctx, char* w) {
   t.wire_tile_off = reinterpret_cast<uint32_t*>(w + lay.wire_tile_off);
   t.wire_tile_sum = reinterpret_cast<uint32_t*>(w + lay.wire_tile_sum);
   t.desc_parts = lay.desc_parts;
+  t.page_turn = (kDies << 16) / static_cast<uint32_t>(ctx->cfg.n);  // the dies change places seven times over the rows
   t.desc = reinterpret_cast<uint2*>(w + lay.desc);
   t.desc2 = reinterpret_cast<uint2*>(w + lay.desc2);
   t.cand = reinterpret_cast<uint2*>(w + lay.cand);

@@ -32,12 +32,12 @@ constexpr uint32_t kSpanCoords = kDies * kPageCoords;  // two chunks
 constexpr uint32_t kSpansPerGroup = kWaves;            // spans that eight consecutive workgroups share, a wavefront each
 
 // The quarter of a chunk that a wavefront of a dense pass takes, the workgroup being number `group` of the row's
-// page_groups(): page `group` % 8 of one of the four spans.
+// page_groups(): page (`group` + `turn`) % 8 of one of the four spans.
 struct Quarter {
   uint32_t chunk, part;
 };
-__device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave) {
-  const uint32_t page = group % kDies, span = group / kDies * kSpansPerGroup + wave;
+__device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave, uint32_t turn = 0) {
+  const uint32_t page = (group + turn) % kDies, span = group / kDies * kSpansPerGroup + wave;
   return {span * (kSpanCoords / kChunk) + page / kWaves, page % kWaves};
 }
 // A dense pass asks for this much LDS that it has no use for: four or five workgroups per compute unit are enough to keep the
@@ -265,6 +265,7 @@ struct TopkWorkspace {
   uint32_t* wire_total;    // n : words of the gap stream of the message being packed or unpacked
   uint32_t* wire_tile_off; // n * ceil(k / kWireTile) : where each tile of gaps starts in its stream
   uint32_t* wire_tile_sum; // n * ceil(k / kWireTile) : coordinates before each tile, while unpacking
+  uint32_t page_turn;   // first pass in pages: row i starts its dies' pages (i * page_turn) >> 16 further on
   uint32_t desc_parts;  // segments of a chunk: one, or (rows whose first pass goes in pages) one for every quarter
   uint2* desc;          // n * num_chunks * desc_parts : (offset, count) of the segment in the candidate list
   uint2* desc2;         // n * num_chunks * desc_parts : offset of the segment in the band list; entries at or above the

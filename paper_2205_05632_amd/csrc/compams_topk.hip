@@ -596,7 +596,11 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 // list is allocated with one atomic for the whole workgroup, and the four quarters are written behind one
 // another.  The level-0 histogram is taken afterwards, from the candidate list (k_topk_level0).
 // In large problems (paged_first_pass) the workgroup takes the same page of four spans instead, a quarter of four different
-// chunks (page_quarter): one allocation still, but a segment of the lists for every quarter.  (Measured on the way: fewer
+// chunks (page_quarter): one allocation still, but a segment of the lists for every quarter.  Which page a die takes changes
+// seven times over the rows: a crowded page (a matrix as wide as the span or a multiple, its large columns side by side) takes
+// its die longer, and as one die's page in every row it held up the whole pass (8 x 25570000, k 5 %, 1024 large columns of
+// 32768: 441 us in chunks, 598 with the pages as they are in every row, 407 so; 64 x 3002268, k 8 %: 412, 574, 413; without
+// such columns 16 x 25570000 755 / 755, 64 x 3002268 356 / 363).  (Measured on the way: fewer
 // instructions between the loads and the stores, and stores as soon as a round's loads have come, made it slower, 8 x 30381
 // chunks 1828 -> 1899 us; all stores behind a barrier 1866; four workgroups per compute unit instead of five 1820, eight 1843.)
 // ---------------------------------------------------------------------------------------------
@@ -626,7 +630,7 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, 
     }
   }
   const SegCtx sc = seg_ctx<UNI, kClassFirst>(geo, opt, ws);
-  const Quarter quarter = PAGED ? page_quarter(sc.group, wave) : Quarter{sc.group, wave};
+  const Quarter quarter = PAGED ? page_quarter(sc.group, wave, (sc.seg * ws.page_turn) >> 16) : Quarter{sc.group, wave};
   const uint32_t c = quarter.chunk, row = sc.seg;
   const float* gr = g + sc.elem_off;
   float* er = e + sc.elem_off;
