@@ -102,6 +102,7 @@ constexpr uint32_t kNoCursorSet = 0xffffffffu;
 // chunks 170 / 172; 16 x 2730 339 / 339, 502 / 507; 64 x 733 375 / 363, 508 / 502; 8 x 6240 398 / 388; 16 x 6240 827 / 781, 1322
 // / 1286; k = d / 1000, 8 x 3907 245 / 237; 8 x 30381 1945 / 1828; but 2 x 6240 99.7 / 99.7.
 constexpr uint32_t kPagedChunks = 45056;
+static_assert(kPagedChunks >= kShortChunks, "rows in pages have blocks of 32 chunks and more: eight chunks to a wavefront");
 // Block-sign, which keeps no lists, from so many on (first pass, chunks in order / pages): 16 x 733 chunks 96.7 / 99.2; 8 x 2730
 // 169 / 172; 2 x 12208 186.5 / 184; 8 x 3907 247 / 239; 8 x 5128 314 / 313; 16 x 2730 332 / 333; 64 x 733 368 / 355; 8 x 7325
 // 466 / 443; 8 x 30381 1948 / 1844.

@@ -1021,7 +1021,7 @@ __device__ __forceinline__ uint32_t chunk_sum(uint32_t v, uint32_t group) {
 //      the kept ones, ascending, let the last kernel add them to the positions of the chunks after them.
 //      It also sets the guess and the band for the next step and clears the histogram.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI>
+template <bool UNI, bool QUARTERS>
 __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace ws, TopkOptions opt, uint32_t use_guess) {
   __shared__ uint32_t suf[kWG / 64];
   __shared__ uint32_t out3[3];
@@ -1039,17 +1039,24 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   TopkRow* rowp = ws.rows + row;
   uint32_t* bh = ws.bhist + sc.bhist_base;
   const uint32_t wave = uniform_u32(t >> 6), lane = lane_id();
-  // A wavefront takes up to eight chunks at a time, the lanes shared out among their segments (SegmentLanes).
+  // A wavefront takes up to eight chunks at a time: all its lanes the entries of one after the other, or, where a chunk has a
+  // segment for every quarter, the lanes shared out among the segments (SegmentLanes).  (Shared out also where there is one
+  // segment to a chunk, this kernel took, us: blocks of 12 x 60000 13.8 -> 15.5, 16 x 733 chunks 13.8 -> 15.9.)
   // Everything that can be asked for before anything is known goes out together (a workgroup's work is a chain
   // of round trips otherwise): the control block and the cursors, the bucket histogram, the counts above the
   // band, the first descriptors.
-  const uint32_t parts = ws.desc_parts;
-  const uint2* d2 = ws.desc2 + sc.chunk_base * parts;
+  constexpr int kGroup = 8;  // chunks a wavefront takes at a time, at most
+  constexpr uint32_t kParts = QUARTERS ? kWaves : 1;
+  const uint2* d2 = ws.desc2 + sc.chunk_base * kParts;
   const uint32_t group = chunks_per_wave(cpw);
   const uint32_t c_first = start + wave * group;
-  const SegmentLanes sl = segment_lanes(group, parts);
+  const SegmentLanes sl = segment_lanes(kGroup, kParts);  // (quarters: group is eight)
+  auto descriptor = [&](uint32_t c0) {
+    const bool mine = QUARTERS ? c0 + sl.chunk < end : lane < group && c0 + lane < end;
+    return mine ? d2[c0 * kParts + (QUARTERS ? sl.segment : lane)] : make_uint2(0, 0);
+  };
   uint2 ds = make_uint2(0, 0);
-  if (opt.band && c_first + sl.chunk < end) ds = d2[c_first * parts + sl.segment];  // (no such table without a band)
+  if (opt.band) ds = descriptor(c_first);  // (no such table without a band)
   // (thread t's buckets are consecutive: 8 of the few, 32 of the many, of which the first 8 lie where the few do and the
   // others are asked for below, with the band entries)
   constexpr uint32_t kQuadsFew = kBandBucketsFew / kWG / 4, kQuadsMany = kBandBucketsMany / kWG / 4;
@@ -1106,27 +1113,36 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   }
   // the band entries of this wavefront's first chunks: requested before the histogram is looked at
   const uint2* bandr = ws.band + sc.band_base;
-  constexpr int kAhead = 8;  // entries of a lane requested together
-  uint2 a[kAhead];
+  uint2 a[kGroup];   // the first 64 entries of every chunk's segment, or (quarters) a lane's first entries of its segment
   uint32_t cnt = 0;  // entries of the lane's segment
+  uint32_t chunk_off[kGroup], chunk_cnt[kGroup];  // one segment to a chunk: wave-uniform
+  auto request = [&](uint32_t q0) {
+    if constexpr (QUARTERS) {
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        const uint32_t q = q0 + u * sl.lanes + sl.sub;
+        a[u] = q < cnt ? bandr[ds.x + q] : make_uint2(0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        chunk_off[u] = __builtin_amdgcn_readlane(ds.x, u);
+        chunk_cnt[u] = __builtin_amdgcn_readlane(cnt, u);
+        a[u] = lane < chunk_cnt[u] ? bandr[chunk_off[u] + lane] : make_uint2(0, 0);
+      }
+    }
+  };
   auto take = [&] {
     cnt = (ds.y >> 13) & 0x1fffu;
     if (ds.x > opt.band_cap) cnt = 0;  // segments always lie inside the list; never read outside it
     else if (cnt > opt.band_cap - ds.x) cnt = opt.band_cap - ds.x;
-  };
-  auto request = [&](uint32_t q0) {
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const uint32_t q = q0 + u * sl.lanes + sl.sub;
-      a[u] = q < cnt ? bandr[ds.x + q] : make_uint2(0, 0);
-    }
+    request(0);
   };
   if (many) {  // uniform
 #pragma unroll
     for (uint32_t i = kQuadsFew; i < kQuadsMany; ++i) x[i] = bh4[((i / kQuadsFew + rot) & 3u) * (kBandBucketsFew / 4) + i % kQuadsFew];
   }
   take();
-  request(0);
   // ---- 1. the bucket of the threshold key: the thread whose buckets the count from the top crosses finds it ----
   bool inside = total_above < k && k - total_above <= band.total;  // uniform
   const uint32_t miss = total_above >= k ? 4u : (inside ? 6u : 5u);  // the threshold lies above / below the band; or (6) ...
@@ -1183,30 +1199,47 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     uint2* bnd = ws.bnd + static_cast<size_t>(row) * kBoundaryCap;
     for (uint32_t c0 = c_first; c0 < end; c0 += kWaves * group) {
       if (c0 != c_first) {  // wave-uniform
-        ds = make_uint2(0, 0);
-        if (c0 + sl.chunk < end) ds = d2[c0 * parts + sl.segment];
+        ds = descriptor(c0);
         take();
-        request(0);
       }
-      uint32_t gt = sl.sub == 0 ? ds.y & 0x1fffu : 0u;  // this lane's part of the chunk's count
-      for (uint32_t q0 = 0; ballot64(q0 < cnt) != 0; q0 += kAhead * sl.lanes) {
-        if (q0) request(q0);
+      auto gather = [&](bool at, const uint2& en) {
+        if (!at) return;
+        const uint32_t slot = atomicAdd(&rowp->bnd_n, 1u);
+        if (slot < kBoundaryCap) {  // always: the histogram counted these entries
+          __hip_atomic_store(&bnd[slot].x, en.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(&bnd[slot].y, en.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      };
+      if constexpr (QUARTERS) {
+        uint32_t gt = sl.sub == 0 ? ds.y & 0x1fffu : 0u;  // this lane's part of the chunk's count
+        for (uint32_t q0 = 0; ballot64(q0 < cnt) != 0; q0 += kGroup * sl.lanes) {
+          if (q0) request(q0);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-          const bool ok = q0 + u * sl.lanes + sl.sub < cnt;
-          const uint32_t bucket = band_bucket(key_of_bits(a[u].y) - blo, bmul);
-          gt += ok && bucket > bstar ? 1u : 0u;
-          if (ok && bucket == bstar) {
-            const uint32_t slot = atomicAdd(&rowp->bnd_n, 1u);
-            if (slot < kBoundaryCap) {  // always: the histogram counted these entries
-              __hip_atomic_store(&bnd[slot].x, a[u].x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              __hip_atomic_store(&bnd[slot].y, a[u].y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+          for (int u = 0; u < kGroup; ++u) {
+            const bool ok = q0 + u * sl.lanes + sl.sub < cnt;
+            const uint32_t bucket = band_bucket(key_of_bits(a[u].y) - blo, bmul);
+            gt += ok && bucket > bstar ? 1u : 0u;
+            gather(ok && bucket == bstar, a[u]);
           }
         }
+        gt = chunk_sum(gt, group);
+        if (sl.first && c0 + sl.chunk < end) l_gt[c0 - start + sl.chunk] = gt;
+      } else {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) {
+          uint32_t gt = 0;  // wave-uniform
+          for (uint32_t q = 0; q < chunk_cnt[u]; q += 64) {  // one trip unless the chunk holds more than 64 band entries
+            const bool ok = q + lane < chunk_cnt[u];
+            const uint2 en = q == 0 ? a[u] : (ok ? bandr[chunk_off[u] + q + lane] : make_uint2(0, 0));
+            const uint32_t bucket = band_bucket(key_of_bits(en.y) - blo, bmul);
+            gt += popc64(ballot64(ok && bucket > bstar));
+            gather(ok && bucket == bstar, en);
+          }
+          if (lane == static_cast<uint32_t>(u)) mine = gt;
+        }
+        if (lane < group && c0 + lane < end) l_gt[c0 - start + lane] = (ds.y & 0x1fffu) + mine;
       }
-      gt = chunk_sum(gt, group);
-      if (sl.first && c0 + sl.chunk < end) l_gt[c0 - start + sl.chunk] = gt;
     }
     __syncthreads();
     // exclusive prefixes within the block: thread t takes `per` consecutive chunks
@@ -2793,7 +2826,8 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     // otherwise, so it runs in every step (about a microsecond when it has nothing to do) but one that stands for itself
     const uint32_t count_blocks = (geo.num_chunks + geo.count_cpw - 1) / geo.count_cpw;  // <= kMaxCountBlocks
     if (!whole) {
-      launch(L, kSlotBand, k_topk_band<true>, dim3(count_blocks, geo.n), wg, stream, geo, ws, opt, use_guess);
+      launch(L, kSlotBand, paged ? k_topk_band<true, true> : k_topk_band<true, false>, dim3(count_blocks, geo.n), wg, stream, geo,
+             ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
     {
@@ -2843,7 +2877,7 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
     launch(L, kSlotPassA, k_topk_lean<false, false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (flat.wg_count) {
-    launch(L, kSlotBand, k_topk_band<false>, dim3(flat.wg_count), wg, stream, geo, ws, opt, use_guess);
+    launch(L, kSlotBand, k_topk_band<false, false>, dim3(flat.wg_count), wg, stream, geo, ws, opt, use_guess);
     COMPAMS_CHECK_LAUNCH();
   }
   if (flat.wg_level0) {
