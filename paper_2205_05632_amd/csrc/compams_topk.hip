@@ -972,7 +972,7 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
   return L;
 }
 
-// How a wavefront that takes `group` (two or eight) chunks at a time shares its lanes out among their segments, `parts` (one
+// How a wavefront that takes up to `chunks` (1 .. 8) chunks at a time shares its lanes out among their segments, `parts` (one
 // or four) to a chunk: every segment has the same number of lanes, which take its entries in turn, so that the segments of all
 // the chunks are requested together however short they are.
 struct SegmentLanes {
@@ -980,26 +980,25 @@ struct SegmentLanes {
   uint32_t segment;  // the lane's, counted from the group's first
   uint32_t chunk;    // ... and its chunk
   uint32_t sub;      // the lane's number among those of the segment
+  uint32_t share;    // lanes per chunk
   bool first;        // it is the first lane of its chunk
 };
-__device__ __forceinline__ SegmentLanes segment_lanes(uint32_t group, uint32_t parts) {
-  const uint32_t lane = lane_id(), per_chunk = 64u / group;
+__device__ __forceinline__ SegmentLanes segment_lanes(uint32_t chunks, uint32_t parts) {
+  // (powers of two: shifts, as what follows waits for the result before it can ask for anything)
+  const uint32_t lane = lane_id(), chunk_shift = chunks > 1u ? __builtin_clz(chunks - 1u) - 26u : 6u;
+  const uint32_t shift = parts > 1u ? chunk_shift - 2u : chunk_shift;
   SegmentLanes s;
-  s.lanes = per_chunk / parts;
-  s.segment = lane / s.lanes;
-  s.chunk = lane / per_chunk;
-  s.sub = lane % s.lanes;
-  s.first = lane % per_chunk == 0;
+  s.lanes = 1u << shift;
+  s.segment = lane >> shift;
+  s.chunk = lane >> chunk_shift;
+  s.sub = lane & (s.lanes - 1u);
+  s.share = 1u << chunk_shift;
+  s.first = (lane & (s.share - 1u)) == 0;
   return s;
 }
-// Sum over the lanes of a chunk: 8 or 32 consecutive ones.
-__device__ __forceinline__ uint32_t chunk_sum(uint32_t v, uint32_t group) {
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
-  if (group < 8) {  // uniform
-    v += __shfl_xor(v, 8, 64);
-    v += __shfl_xor(v, 16, 64);
-  }
+// Sum over the lanes of a chunk.
+__device__ __forceinline__ uint32_t chunk_sum(uint32_t v, const SegmentLanes& s) {
+  for (uint32_t o = 1; o < s.share; o <<= 1) v += __shfl_xor(v, o, 64);  // uniform
   return v;
 }
 
@@ -1222,7 +1221,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
             gather(ok && bucket == bstar, a[u]);
           }
         }
-        gt = chunk_sum(gt, group);
+        gt = chunk_sum(gt, sl);
         if (sl.first && c0 + sl.chunk < end) l_gt[c0 - start + sl.chunk] = gt;
       } else {
         uint32_t mine = 0;
@@ -2122,7 +2121,7 @@ __device__ __forceinline__ void for_each_round(uint32_t mode, const float* __res
 // the block, and per block the two totals.  The last kernel turns these into positions in the worker's
 // list (a sum over at most kMaxCountBlocks block totals), so no workgroup waits for or follows another.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI>
+template <bool UNI, bool QUARTERS>
 __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
                                                      TopkOptions opt) {
   if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
@@ -2139,7 +2138,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
   const uint32_t mode = rowp->mode, tau = rowp->tau;
   const float* er = e + sc.elem_off;
   const uint2* candr = ws.cand + sc.cand_base;
-  const uint2* descr = ws.desc + sc.chunk_base * ws.desc_parts;
+  const uint2* descr = ws.desc + sc.chunk_base * (QUARTERS ? kWaves : 1);
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   if (mode == kModeDense) {
     for (uint32_t c = start + wave; c < end; c += kWaves) {
@@ -2153,15 +2152,62 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
       });
       if (lane == 0) { l_gt[c - start] = gt; l_eq[c - start] = eq; }
     }
+  } else if constexpr (QUARTERS) {
+    // A wavefront takes eight consecutive chunks at a time, sixteen lanes for every quarter of a chunk: the first 32 entries of
+    // all quarters together, then, chunk by chunk, what any of its quarters holds beyond.  (Two lanes to a quarter, all quarters at
+    // once, ask for every line of the list several times, and go through a crowded quarter in a chain of 32 trips.  us, rows in
+    // chunks / in pages with two lanes / with sixteen: 8 x 25570000, k 1 % 18.3 / 24.3 / 18.7, 10 % 65 / 102 / 48, 5 % in 1024 large
+    // columns of 32768 41 / 168 / 48; 8 x 124439808, 0.1 % 36.6 / 30.9 / 27.0; 64 x 3002268, 1 % 12.5 / 22.4 / 16.8.)
+    constexpr int kGroup = 8;
+    constexpr uint32_t kLanes = 64 / kWaves, kFirst = 2 * kLanes, kAhead = 8;
+    const uint32_t part = lane / kLanes, sub = lane % kLanes;
+    for (uint32_t c0 = start + wave * kGroup; c0 < end; c0 += kWaves * kGroup) {
+      uint2 all = make_uint2(0, 0);  // lane l: segment l % 32
+      if (c0 + lane % 32 / kWaves < end) all = descr[c0 * kWaves + lane % 32];
+      if (all.x > opt.cap) all.y = 0;  // segments always lie inside the list; never read outside it
+      else if (all.y > opt.cap - all.x) all.y = opt.cap - all.x;
+      uint2 ds[kGroup];
+      uint32_t first[kGroup], second[kGroup];
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) ds[u] = make_uint2(__shfl(all.x, u * kWaves + part, 64), __shfl(all.y, u * kWaves + part, 64));
+#pragma unroll
+      for (int u = 0; u < kGroup; ++u) {
+        first[u] = sub < ds[u].y ? candr[ds[u].x + sub].y : 0u;
+        second[u] = sub + kLanes < ds[u].y ? candr[ds[u].x + sub + kLanes].y : 0u;
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kGroup; ++u) {
+        uint32_t gt = 0, eq = 0;  // wave-uniform
+        auto add = [&](bool ok, uint32_t bits) {
+          const uint32_t key = key_of_bits(bits);
+          gt += popc64(ballot64(ok && key > tau));
+          eq += popc64(ballot64(ok && key == tau));
+        };
+        add(sub < ds[u].y, first[u]);
+        add(sub + kLanes < ds[u].y, second[u]);
+        for (uint32_t q0 = kFirst; ballot64(q0 < ds[u].y) != 0; q0 += kAhead * kLanes) {
+          uint32_t bits[kAhead];
+#pragma unroll
+          for (uint32_t w = 0; w < kAhead; ++w) {
+            const uint32_t q = q0 + w * kLanes + sub;
+            bits[w] = q < ds[u].y ? candr[ds[u].x + q].y : 0u;
+          }
+#pragma unroll
+          for (uint32_t w = 0; w < kAhead; ++w) add(q0 + w * kLanes + sub < ds[u].y, bits[w]);
+        }
+        if (lane == 0 && c0 + u < end) { l_gt[c0 + u - start] = gt; l_eq[c0 + u - start] = eq; }
+      }
+    }
   } else {
     // A wavefront takes up to eight consecutive chunks at a time, the lanes shared out among their segments: the
-    // descriptors come with one load, then kAhead entries of every lane together.
+    // descriptors come with one load, then kAhead entries of every lane together.  Where fewer chunks are there than it could
+    // take, each has more lanes (blocks of 12 x 60000, one coordinate in 20: 9.1 us, eight lanes to a chunk in any case 14.0).
     constexpr int kAhead = 16;
-    const uint32_t group = chunks_per_wave(cpw), parts = ws.desc_parts;
-    const SegmentLanes sl = segment_lanes(group, parts);
+    const uint32_t group = chunks_per_wave(cpw);
+    const SegmentLanes sl = segment_lanes(end - start < group ? end - start : group, 1u);
     for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
       uint2 ds = make_uint2(0, 0);
-      if (c0 + sl.chunk < end) ds = descr[c0 * parts + sl.segment];
+      if (c0 + sl.chunk < end) ds = descr[c0 + sl.chunk];
       if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
       else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
       uint32_t gt = 0, eq = 0;  // of this lane's entries
@@ -2180,8 +2226,8 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
           eq += ok && key == tau ? 1u : 0u;
         }
       }
-      gt = chunk_sum(gt, group);
-      eq = chunk_sum(eq, group);
+      gt = chunk_sum(gt, sl);
+      eq = chunk_sum(eq, sl);
       if (sl.first && c0 + sl.chunk < end) { l_gt[c0 - start + sl.chunk] = gt; l_eq[c0 - start + sl.chunk] = eq; }
     }
   }
@@ -2842,7 +2888,8 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     COMPAMS_CHECK_LAUNCH();
     launch(L, kSlotLevel2, k_topk_level2<true>, grid_rows, wg, stream, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotCount, k_topk_count<true>, dim3(count_blocks, geo.n), wg, stream, e, geo, ws, opt);
+    launch(L, kSlotCount, paged ? k_topk_count<true, true> : k_topk_count<true, false>, dim3(count_blocks, geo.n), wg, stream, e, geo,
+           ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   const TopkFlat none{};
@@ -2889,7 +2936,7 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
     COMPAMS_CHECK_LAUNCH();
     launch(L, kSlotLevel2, k_topk_level2<false>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotCount, k_topk_count<false>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt);
+    launch(L, kSlotCount, k_topk_count<false, false>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   const float* residuals = e;

@@ -116,3 +116,26 @@ def test_large_columns_in_one_page(n, d, k, width):
             assert not (counters[:, 5] == 2).any(), (t, counters[:, 5])  # no candidate list overflowed
             assert not counters[:, 0].any(), (t, counters[:, 0])         # no row was read again
     ctx.close()
+
+
+# The general kernels alone (no window; then no list at all) on rows in pages, with large entries crowded into one quarter of every
+# eighth chunk, and with few in any.
+@pytest.mark.parametrize("n,d,k,columns", [(700, 65 * 4096 - 3100, 12000, PAGE), (640, 71 * 4096 + 1, 300, 0)])
+def test_general_route_in_pages(n, d, k, columns):
+    rng = np.random.default_rng(d)
+    p = Pair(n, d, np.zeros(d, np.float32), B.TOPK, k=k)
+    p.gpu.set_option(B.OPT_BAND, 0)
+    base = rng.standard_normal((2, d)).astype(np.float32)
+    scale = np.where(np.arange(d) % GROUP < columns, 1.0, 1e-2).astype(np.float32)
+    for t in range(4):
+        g = np.stack([np.roll(base[(t + i) % 2], 37 * i + 1001 * t) for i in range(n)]) * scale
+        g[1] = 1.0  # ties, and a list that overflows
+        if t == 3:
+            p.gpu.set_option(B.OPT_FORCE_DENSE, 1)
+        p.step(g, 1e-3, label=f"{n} x {d} step {t}", with_e=(t == 3))
+        counters = p.gpu.compams_state("counters").cpu().numpy()
+        assert not counters[:, 4].any()
+        if t in (1, 2):
+            assert (counters[2:, 0] == 0).all()  # selected from the lists
+    assert all(p.exact.values()), p.exact
+    p.close()
