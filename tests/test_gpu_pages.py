@@ -9,6 +9,7 @@ import torch
 from paper_2205_05632_amd import binding as B
 
 from parity import Pair
+from test_gpu_split import run_split
 
 pytestmark = pytest.mark.gpu
 PAGE, SPAN, GROUP = 1024, 8192, 32768
@@ -139,3 +140,7 @@ def test_general_route_in_pages(n, d, k, columns):
             assert (counters[2:, 0] == 0).all()  # selected from the lists
     assert all(p.exact.values()), p.exact
     p.close()
+
+
+def test_halves_in_pages():
+    run_split(640, 71 * 4096 + 1, B.TOPK, 3, k=9000)
