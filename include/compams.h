@@ -208,8 +208,8 @@ enum {
   COMPAMS_OPT_CACHED_ARRAYS = 4  /* every compressor: how many of theta, m, v, vhat (in that order) the server's
                                     lines leave in the memory-side cache for the next step, the others with
                                     streaming accesses: 0..4, or -1 (default) for the library's choice:
-                                    compams_cached_state_arrays(d) with the identity compressor, else four up to
-                                    5.5 M coordinates and none beyond */
+                                    compams_cached_state_arrays(d) with the identity compressor, else four while
+                                    (n + 32) * d is at most 231 M, and none beyond */
 };
 int compams_set_option(compams_ctx* ctx, int option, int64_t value);
 
@@ -307,8 +307,8 @@ int compams_cached_state_arrays(int64_t d);
  * per lane and access - the access pattern of those lines without their arithmetic and without the look-ups
  * that precede them.  What the box gives this pattern bounds the kernels that apply those lines.
  *   arrays: HOST array of n_arrays DEVICE pointers (16-byte aligned, distinct, count elements each, modified).
- *   count: multiple of 4.  cached_arrays (0..4): the first that many arrays are read with ordinary loads, the
- *   others with non-temporal ones; all are written with non-temporal stores (see compams_cached_state_arrays).
+ *   count: multiple of 4.  cached_arrays (0..4): the first that many arrays are accessed with ordinary loads
+ *   and stores, the others with non-temporal ones (see compams_cached_state_arrays).
  * Only enqueues on hip_stream.  COMPAMS_INVALID_ARG / COMPAMS_BAD_ALIGNMENT as for compams_copy. */
 int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int cached_arrays, void* hip_stream);
 

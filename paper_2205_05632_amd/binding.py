@@ -356,7 +356,7 @@ def compams_cached_state_arrays(d: int) -> int:
 def compams_inplace_probe(arrays, cached_arrays: int):
     """x += 1 on up to four separately allocated fp32 arrays of one size, in the access pattern of the server's
     lines of Algorithm 2 (the measured ceiling for the kernels that apply them); the first cached_arrays of them
-    read with ordinary accesses, the others with streaming ones."""
+    with ordinary accesses, the others with streaming ones."""
     count = arrays[0].numel()
     assert all(a.numel() == count and a.dtype == torch.float32 and a.is_cuda and a.is_contiguous() for a in arrays)
     ptrs = (ctypes.c_void_p * len(arrays))(*[a.data_ptr() for a in arrays])

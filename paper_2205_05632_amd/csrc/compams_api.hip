@@ -619,7 +619,7 @@ static AmsParams ams_params(const compams_config& c, float lr, int cached_overri
   ap.lr = lr;
   ap.nf = static_cast<float>(c.n);
   ap.eps_out = c.eps_mode == COMPAMS_EPS_OUT_SQRT;
-  ap.cached_arrays = cached_override >= 0 ? cached_override : step_cached_arrays(c.d, c.compressor == COMPAMS_NONE);
+  ap.cached_arrays = cached_override >= 0 ? cached_override : step_cached_arrays(c.n, c.d, c.compressor == COMPAMS_NONE);
   return ap;
 }
 

@@ -695,10 +695,10 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
       ams_update(sum[r][1] / p.nf, th[r].y, mm[r].y, vv[r].y, vh[r].y, p);
       ams_update(sum[r][2] / p.nf, th[r].z, mm[r].z, vv[r].z, vh[r].z, p);
       ams_update(sum[r][3] / p.nf, th[r].w, mm[r].w, vv[r].w, vh[r].w, p);
-      store_state4(theta + jr, lane * 4, th[r]);
-      store_state4(m + jr, lane * 4, mm[r]);
-      store_state4(v + jr, lane * 4, vv[r]);
-      store_state4(vhat + jr, lane * 4, vh[r]);
+      store_state4<(NC > 0)>(theta + jr, lane * 4, th[r]);
+      store_state4<(NC > 1)>(m + jr, lane * 4, mm[r]);
+      store_state4<(NC > 2)>(v + jr, lane * 4, vv[r]);
+      store_state4<(NC > 3)>(vhat + jr, lane * 4, vh[r]);
     }
     return;
   }
@@ -765,10 +765,10 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
       ams_update(sum[1] / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(sum[2] / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(sum[3] / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4(theta + j0, lane * 4, th);
-      store_state4(m + j0, lane * 4, mm);
-      store_state4(v + j0, lane * 4, vv);
-      store_state4(vhat + j0, lane * 4, vh);
+      store_state4<(NC > 0)>(theta + j0, lane * 4, th);
+      store_state4<(NC > 1)>(m + j0, lane * 4, mm);
+      store_state4<(NC > 2)>(v + j0, lane * 4, vv);
+      store_state4<(NC > 3)>(vhat + j0, lane * 4, vh);
     } else {
       for (int s = 0; s < 4; ++s)
         if (ok[s]) {
@@ -890,10 +890,10 @@ __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, flo
       for (int a = 0; a < A; ++a) {
         x[r][a].x += 1.0f; x[r][a].y += 1.0f; x[r][a].z += 1.0f; x[r][a].w += 1.0f;
       }
-      store_state4(a0 + j, at, x[r][0]);
-      if (A > 1) store_state4(a1 + j, at, x[r][1]);
-      if (A > 2) store_state4(a2 + j, at, x[r][2]);
-      if (A > 3) store_state4(a3 + j, at, x[r][3]);
+      store_state4<(NC > 0)>(a0 + j, at, x[r][0]);
+      if (A > 1) store_state4<(NC > 1)>(a1 + j, at, x[r][1]);
+      if (A > 2) store_state4<(NC > 2)>(a2 + j, at, x[r][2]);
+      if (A > 3) store_state4<(NC > 3)>(a3 + j, at, x[r][3]);
     }
   }
 }

@@ -322,16 +322,24 @@ inline int cached_state_arrays(int64_t d) {
   return fit > 4 ? 4 : static_cast<int>(fit);
 }
 
-// How many a step keeps there.  Between two steps lie a forward and a backward pass, so only a small model's state is found
-// there again; a larger one's lines only get in the way of what follows.  The identity compressor, which reads the gradients
-// in the same pass, writes through what fits (16 x 11.2 M, three contexts in turn / one context's steps one after the other:
-// 172 / 167 us, streamed 173 / 175).  Top-k and block-sign read all four with ordinary accesses or all with streaming ones
-// (three contexts in turn; us a step, ordinary / streaming): per layer 4 x 1 M 52.6 / 54.8, 8 x 3 M 99 / 103, 8 x 5 M 146 /
-// 150, 8 x 8 M 226 / 220; top-k 8 x 3 M 92.4 / 93.8, 8 x 6 M 161 / 159; 16 x 11.2 M 525 / 502 (one context alone 473 / 476), 8 x 25.6 M
-// 633 / 610; block-sign 8 x 3 M 77.4 / 79.3, 8 x 6 M 136.9 / 139.0, 16 x 11.2 M 428 / 408.
-constexpr int64_t kOrdinaryState = 5500000;  // coordinates
-inline int step_cached_arrays(int64_t d, bool identity) {
-  return identity ? cached_state_arrays(d) : d <= kOrdinaryState ? 4 : 0;
+// How many a step keeps there.  The identity compressor, which reads the gradients in the same pass, writes through what fits (16 x
+// 11.2 M, three contexts in turn / one context's steps one after the other: 172 / 167 us, streamed 173 / 175).  Top-k and
+// block-sign read and write all four with ordinary accesses or all with streaming ones.  Ordinary accesses are the faster ones
+// where one context's steps follow each other with nothing in between, at every size that fits the cache at all (us, ordinary /
+// streaming: top-k 8 x 8 M 189 / 199, 16 x 11.2 M 432 / 450; block-sign 8 x 8 M 165 / 173, 1 x 12 M 87 / 98).  Where something
+// else comes in between, as in a training program, they are so only while the state is small: the lines of a larger one are gone
+// when the next step asks for them, and are written out in the way of what follows.  Three contexts in turn, ordinary /
+// streaming, k = d / 100 (the line lies at (n + 32) d = 231 M, 7 M coordinates of one worker, 4.8 M of sixteen):
+//   top-k       1 x 6 M 73.1 / 75.2, 1 x 8 M 96.7 / 93.8; 4 x 6 M 110.5 / 111.8, 4 x 7 M 130.7 / 125.4; 8 x 5.5 M 153.4 / 155.0,
+//               8 x 7 M 192 / 186; 16 x 4.5 M 206 / 205, 16 x 5.5 M 255 / 251; 64 x 2 M 363 / 366, 64 x 3.5 M 575 / 568
+//   block-sign  1 x 6.5 M 57.1 / 58.3, 1 x 8 M 71.7 / 67.6; 8 x 6 M 129.8 / 131.7, 8 x 7 M 155.2 / 153.3; 16 x 4.5 M 171.6 / 172.9,
+//               16 x 5.5 M 207.1 / 206.7, 16 x 8 M 305 / 296; 64 x 2.5 M 343 / 342
+//   per layer   2 x 6 M 93.9 / 98.5, 8 x 5.5 M 165.6 / 167.1, 16 x 5 M 244 / 240
+// With 512 MB of other traffic before every step, which is not counted, neither is ahead by more than 5 % from 6 M on (16 x 11 M:
+// block-sign 412 / 404, top-k 475 / 474; 8 x 8 M: 178.9 / 177.9, 222 / 218).
+constexpr int64_t kOrdinaryState = 231000000;
+inline int step_cached_arrays(int64_t n, int64_t d, bool identity) {
+  return identity ? cached_state_arrays(d) : (n + 32) * d <= kOrdinaryState ? 4 : 0;
 }
 
 // Moment and parameter lines of Algorithm 2 for one coordinate: every product, sum, square root and

@@ -2408,7 +2408,8 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
   return f;
 }
 
-// NC: how many of theta, m, v, vhat (in that order) are read with ordinary accesses, the others with streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
+// NC: how many of theta, m, v, vhat (in that order) are read and written with ordinary accesses, the others with
+// streaming ones (a template parameter: as a run-time choice between otherwise identical branches the compiler
 // merges them and drops the hint).
 // CLEAR: the residual at the selected coordinates becomes zero at once (nothing is left to a next step).
 // QUARTERS: a chunk has a segment of the candidate list for every quarter, else one.
@@ -2772,10 +2773,10 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
       ams_update(s.y / p.nf, th.y, mm.y, vv.y, vh.y, p);
       ams_update(s.z / p.nf, th.z, mm.z, vv.z, vh.z, p);
       ams_update(s.w / p.nf, th.w, mm.w, vv.w, vh.w, p);
-      store_state4(theta, j, th);
-      store_state4(m, j, mm);
-      store_state4(v, j, vv);
-      store_state4(vhat, j, vh);
+      store_state4<(NC > 0)>(theta, j, th);
+      store_state4<(NC > 1)>(m, j, mm);
+      store_state4<(NC > 2)>(v, j, vv);
+      store_state4<(NC > 3)>(vhat, j, vh);
     } else {
       for (uint32_t s = 0; s < 4 && j + s < d_end; ++s) {
         float th = theta[j + s], mm = m[j + s], vv = v[j + s], vh = vhat[j + s];
@@ -2818,6 +2819,8 @@ void launch_final_of(uint32_t n, int cached_arrays, Launcher* L, uint32_t workgr
     // leave the chip idle (50000 coordinates in seven blocks: the half of 300 workers 128 us / 76 as here, of 64 52 / 45).
     const dim3 grid_tiles(workgroups, (n + kTileWorkers - 1) / kTileWorkers);
     launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid_tiles, wg, stream, args...);
+  } else if constexpr (CLEAR && NW == kFinalFew) {  // (so short that its whole state stays in the memory-side cache)
+    launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
   } else if constexpr (CLEAR) {  // (a call that stands for itself has no option: four or none)
     if (cached_arrays) launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
     else launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
