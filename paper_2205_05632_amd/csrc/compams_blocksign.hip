@@ -784,10 +784,11 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
 // C = identity (full-precision distributed AMSGrad): gbar = mean of the n gradients in worker order.
 // Bound by memory: n rows and the four state arrays.  A wavefront takes one round (1 KB of every array), a workgroup
 // the same kilobyte of its die's page in four spans (see page_quarter): n + 4 streams through the same addresses are
-// 13 % faster so than a workgroup per 4 KB in address order.  Sixteen rows are requested at once (16 x 11.2 M, state from
-// HBM / cached: plain order, eight rows 195 / 155 us; pages, eight rows 174 / 151; pages, sixteen 171 / 149).
+// 13 % faster so than a workgroup per 4 KB in address order (16 x 11.2 M, state from HBM / cached: plain order, eight rows
+// 195 / 155 us; pages, eight rows 174 / 151; pages, sixteen 171 / 149), and no slower anywhere: 8 x 300000 7.2 / 7.4, 16 x 300000
+// 11.0 / 11.3, 16 x 3 M 51.7 / 52.3.  ROWS: how many rows are requested at once (identity_rows).
 // ---------------------------------------------------------------------------------------------
-template <int NC>  // how many of theta, m, v, vhat are cached (the others are streamed)
+template <int NC, uint32_t ROWS>  // NC: how many of theta, m, v, vhat are cached (the others are streamed)
 __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ g, float* __restrict__ theta,
                                                        float* __restrict__ m, float* __restrict__ v,
                                                        float* __restrict__ vhat, Geometry geo, AmsParams p) {
@@ -798,23 +799,22 @@ __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ 
   const uint32_t j = j0 + lane * 4;
   if (j >= geo.d) return;
   const bool whole = j + 3 < geo.d;
-  // the optimizer state is requested first; the workers' gradients follow sixteen rows at a time, loads together
+  // the optimizer state is requested first; the workers' gradients follow ROWS rows at a time, loads together
   float4 th = make_float4(0.f, 0.f, 0.f, 0.f), mm = th, vv = th, vh = th;
   if (whole) {
     th = load_state4<false>(theta + j0, lane * 4); mm = load_state4<false>(m + j0, lane * 4);
     vv = load_state4<false>(v + j0, lane * 4); vh = load_state4<false>(vhat + j0, lane * 4);
   }
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
-  constexpr int kRows = 16;
-  for (uint32_t i0 = 0; i0 < geo.n; i0 += kRows) {
-    float4 gv[kRows];
+  for (uint32_t i0 = 0; i0 < geo.n; i0 += ROWS) {
+    float4 gv[ROWS];
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) {
+    for (uint32_t u = 0; u < ROWS; ++u) {
       gv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (i0 + u < geo.n) gv[u] = load_stream4(g + static_cast<int64_t>(i0 + u) * geo.ld + j);  // uniform condition
     }
 #pragma unroll
-    for (int u = 0; u < kRows; ++u)
+    for (uint32_t u = 0; u < ROWS; ++u)
       if (i0 + u < geo.n) {
         // x = e + g with e identically zero
         sum[0] = sum[0] + (0.0f + gv[u].x); sum[1] = sum[1] + (0.0f + gv[u].y);
@@ -948,14 +948,31 @@ hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspac
   return hipGetLastError();
 }
 
+// Rows that the identity compressor's kernel requests at once: sixteen in large problems, eight in smaller ones and wherever there
+// are no more than eight (but for one and two workers of a large one: the longer form has fewer wavefronts in flight, as the pages
+// like it).  us a step, three contexts in turn / one alone, sixteen and eight: 8 x 4 M 44.0 41.3 / 43.4 40.6; 16 x 4 M 64.6 60.8 /
+// 64.2 60.5; 4 x 6 M 48.0 44.6 / 46.1 42.5; 8 x 12 M 130.5 129.5 / 123.4 112.7; 4 x 20 M 161.8 163.5 / 151.7 143.2; but 16 x 8 M 129.2
+// 128.8 / 122.1 118.2; 24 x 8 M 166.8 170.0; 16 x 12 M 189.5 192.0; 32 x 16 M 418.6 431.2; 1 x 12 M 71.0 72.9; 2 x 16 M 104.4 107.3.
+static uint32_t identity_rows(const Geometry& geo) {
+  constexpr uint32_t kFewCoords = 7000000;
+  return geo.d <= kFewCoords || (geo.n > 2 && geo.n <= 8) ? 8 : 16;
+}
+
 hipError_t none_step(const Geometry& geo, const AmsParams& ap, const float* g, float* theta, float* m, float* v,
                      float* vhat, hipStream_t stream, Launcher* L) {
   const uint32_t per_group = kWaves * kSpanCoords;  // coordinates of 32 workgroups
   const dim3 grid((geo.d + per_group - 1) / per_group * 32), wg(kWG);
-#define COMPAMS_NONE_AMSGRAD(NC) k_none_amsgrad<NC>
-  COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotNoneAms, COMPAMS_NONE_AMSGRAD, grid, wg, stream, g, theta, m, v, vhat,
-                           geo, ap);
-#undef COMPAMS_NONE_AMSGRAD
+#define COMPAMS_NONE_AMSGRAD_16(NC) k_none_amsgrad<NC, 16>
+#define COMPAMS_NONE_AMSGRAD_8(NC) k_none_amsgrad<NC, 8>
+  if (identity_rows(geo) == 16) {
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotNoneAms, COMPAMS_NONE_AMSGRAD_16, grid, wg, stream, g, theta, m, v, vhat,
+                             geo, ap);
+  } else {
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotNoneAms, COMPAMS_NONE_AMSGRAD_8, grid, wg, stream, g, theta, m, v, vhat,
+                             geo, ap);
+  }
+#undef COMPAMS_NONE_AMSGRAD_16
+#undef COMPAMS_NONE_AMSGRAD_8
   return hipGetLastError();
 }
 

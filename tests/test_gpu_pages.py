@@ -64,6 +64,19 @@ def test_identity_sizes(n, d):
     run(Pair(n, d, np.ones(d, np.float32), B.NONE), n, d, "plain", with_e=False)
 
 
+# Sixteen rows at once beyond 7 M coordinates unless there are three to eight.
+@pytest.mark.parametrize("n,d", [(1, 7_000_001), (2, 7_000_001), (3, 7_000_001), (8, 7_000_001), (9, 7_000_001), (9, 7_000_000),
+                                 (16, 7_000_003), (17, 7_000_003), (33, 7_000_002)])
+def test_identity_forms(n, d):
+    rng = np.random.default_rng(n)
+    p = Pair(n, d, np.ones(d, np.float32), B.NONE)
+    base = rng.standard_normal(d).astype(np.float32)
+    for t in range(2):
+        p.step(np.stack([np.roll(base, 1001 * t + 37 * i) for i in range(n)]), 1e-3, label=f"{n} x {d} step {t}")
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
 # Block-sign goes in pages from 24576 chunks in all rows on.
 @pytest.mark.parametrize("n,d,size", [(1600, 16 * 4096 - 3100, 4096), (1100, 23 * 4096 + 1, 100000)])
 def test_blocksign_in_pages(n, d, size):
