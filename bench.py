@@ -10,9 +10,12 @@ The default workload is the one the headline metric is quoted on: n = 16 workers
 (ResNet-18-shaped), top-k with k/d = 1 %.  Gradients are seeded synthetic data (a distinct pre-generated
 buffer per step, so the residuals evolve as they would in training).
 
-`value` is the headline workload's.  The line also carries, under "workloads", a short run (10 timed steps after
-12, a distinct gradient buffer per step) of every other workload of the build and, under "eps_out", the headline
-workload with epsilon outside the square root: figures for the record, none of them enters `value`.
+`value` is the headline workload's, with every option as the library sets it.  The line also carries, under "workloads", a
+short run (10 timed steps after 12, a distinct gradient buffer per step) of every other workload of the build and, under
+"eps_out", the headline workload with epsilon outside the square root: figures for the record, none of them enters `value`.
+These steps follow each other with nothing in between, so that a state that fits the memory-side cache could be found there
+by the next step, while the library streams the state of larger models past it: "state_kept" (and "ms_per_step_state_kept"
+of the other workloads) is the same short run with COMPAMS_OPT_CACHED_ARRAYS set to as many arrays as fit.
 """
 import argparse
 import json
@@ -87,11 +90,8 @@ class Run:
             self.ctx.set_option(B.OPT_FORCE_DENSE, 1)
         if not band and self.comp in (B.TOPK, B.TOPK_BLOCKS):
             self.ctx.set_option(B.OPT_BAND, 0)
-        # These steps follow each other with nothing in between: what fits the memory-side cache is found there by the next one,
-        # and the context is told to leave it there.  (By default the state of a larger model is streamed past that cache, because a
-        # training program's forward and backward pass lie in between.)
-        kept = cached_arrays if cached_arrays >= 0 else B.compams_cached_state_arrays(w.d)
-        self.ctx.set_option(B.OPT_CACHED_ARRAYS, kept)
+        if cached_arrays >= 0:
+            self.ctx.set_option(B.OPT_CACHED_ARRAYS, cached_arrays)
         total = warmup + steps
         scale = W.coordinate_scale(w, self.dev)
         nbuf = total if grad_buffers <= 0 else min(total, grad_buffers)
@@ -165,11 +165,11 @@ class Run:
 BRIEF_STEPS, BRIEF_WARMUP = 10, 12
 
 
-def brief(name, eps_mode=None, stride=4):
+def brief(name, eps_mode=None, stride=4, cached_arrays=-1):
     """The short run of a workload for the record: 10 timed steps after 12, a distinct gradient buffer per step (the
     selection settles on its steady-state route within about ten steps of a smoothly drifting threshold; a handful
     of buffers in rotation would make the threshold jump back and forth instead)."""
-    r = Run(name, steps=BRIEF_STEPS, warmup=BRIEF_WARMUP, grad_buffers=0, eps_mode=eps_mode)
+    r = Run(name, steps=BRIEF_STEPS, warmup=BRIEF_WARMUP, grad_buffers=0, eps_mode=eps_mode, cached_arrays=cached_arrays)
     m = r.timed(event_mode=2, stride=stride)
     c = r.counters()
     out = {"ms_per_step": m["ms_per_step"], "steps_per_s": m["steps_per_s"], "hbm_frac_of_peak": m["hbm_frac_of_peak"],
@@ -208,7 +208,7 @@ def main():
                     help="ablation: every selection by the general kernels (no window carried over for the threshold key)")
     ap.add_argument("--cached-arrays", type=int, default=-1,
                     help="ablation: how many of theta, m, v, vhat the server kernels keep in the memory-side cache "
-                         "(0..4; default: as many as fit it)")
+                         "(0..4; default: the library's choice by size)")
     ap.add_argument("--grad-buffers", type=int, default=0,
                     help="how many distinct gradient buffers to cycle through (0: one per step)")
     ap.add_argument("--settle-each-step", action="store_true",
@@ -324,15 +324,26 @@ def main():
     run.close()
     del grads, run, ctx
 
-    others, eps_out = None, None
+    def with_state_kept(name):
+        """The short run with as many state arrays kept as fit the cache, or None where that is none of them (and for the
+        identity compressor, which keeps them by itself)."""
+        fit = B.compams_cached_state_arrays(W.get(name).d)
+        if fit == 0 or W.get(name).compressor == "none":
+            return None
+        return dict(brief(name, stride=args.event_stride, cached_arrays=fit), cached_state_arrays=fit)
+
+    others, eps_out, state_kept = None, None, None
     if not args.no_others:
         eps_out = brief(args.workload, eps_mode=B.EPS_IN_SQRT if args.eps_out else B.EPS_OUT_SQRT,
                         stride=args.event_stride)
         eps_out["eps_mode"] = "in_sqrt" if args.eps_out else "out_sqrt"
+        state_kept = with_state_kept(args.workload)
         others = {}
         for name in OTHER_WORKLOADS:
             if name != args.workload:
                 others[name] = brief(name, stride=args.event_stride)
+                kept = with_state_kept(name)
+                others[name]["ms_per_step_state_kept"] = kept["ms_per_step"] if kept else None
 
     cpu = None
     if host is not None:
@@ -359,8 +370,7 @@ def main():
                    "num_blocks": (len(w.block_offsets()) - 1) if w.compressor == "blocksign" else 0,
                    "eps_mode": "out_sqrt" if args.eps_out else "in_sqrt",
                    "predict": not args.no_predict, "force_dense": args.force_dense, "band": not args.no_band,
-                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0
-                   else B.compams_cached_state_arrays(w.d)},
+                   "cached_state_arrays": args.cached_arrays if args.cached_arrays >= 0 else "library default"},
         "hbm_gbps": main_res["hbm_gbps"],
         "hbm_frac_of_peak": main_res["hbm_frac_of_peak"],
         "algorithmic_bytes_per_step": main_res["algorithmic_bytes_per_step"],
@@ -374,6 +384,7 @@ def main():
         "wire": wire,
         "cpu_baseline": cpu,
         "eps_out": eps_out,
+        "state_kept": state_kept,
         "workloads": others,
     }
     print(json.dumps(out))
