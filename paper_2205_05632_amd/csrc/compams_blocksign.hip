@@ -481,8 +481,8 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 // us, of 1000 671 / 517; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
 // round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5; not in pages, where one quarter more or less
 // round by round is nothing and the second form in the kernel's code cost 8 x 124439808 1910 -> 1934 us).  Up to 96 registers
-// cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous step is applied to e as
-// it is read.
+// cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous
+// step is applied to e as it is read.
 // ---------------------------------------------------------------------------------------------
 template <bool PEND, bool PAGED>
 __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, const float* __restrict__ g,

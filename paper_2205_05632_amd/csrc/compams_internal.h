@@ -42,7 +42,8 @@ __device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave, u
 }
 // A dense pass asks for this much LDS that it has no use for: four or five workgroups per compute unit are enough to keep the
 // memory busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with five, 317
-// with four, 373 with three).
+// with four, 373 with three).  Block-sign's first pass does so in chunk order as well (a step, with / without: 8 x 12 M 269.5 /
+// 271.9 us, 4 x 12 M 174.1 / 175.5; the same below 3 M).
 constexpr size_t kStreamLds = 32768;
 inline uint32_t page_groups(uint32_t num_chunks) { return (num_chunks + kDies - 1) / kDies * kDies; }
 static_assert(kPageCoords * kWaves == kChunk, "a page is a wavefront's quarter of a chunk");
@@ -98,9 +99,10 @@ constexpr uint32_t kCursorPitch = 32;  // words between the cursors of a problem
 constexpr uint32_t kSubListMinChunks = 64;
 constexpr uint32_t kNoCursorSet = 0xffffffffu;
 // So many chunks in all rows (one selection per row, rows of several runs) have their first pass in pages, with a segment of
-// the lists for every quarter of a chunk.  First pass (us; k = d / 100, chunks in order / pages), and the whole step: 8 x 2730
-// chunks 170 / 172; 16 x 2730 339 / 339, 502 / 507; 64 x 733 375 / 363, 508 / 502; 8 x 6240 398 / 388; 16 x 6240 827 / 781, 1322
-// / 1286; k = d / 1000, 8 x 3907 245 / 237; 8 x 30381 1945 / 1828; but 2 x 6240 99.7 / 99.7.
+// the lists for every quarter of a chunk.  First pass (us; k = d / 100, chunks in order / pages): 8 x 2730 chunks 170 / 172; 2 x 6240
+// 99.7 / 99.7; 16 x 2730 339 / 339; 8 x 6240 406 / 385; 16 x 6240 818 / 755; k = d / 1000, 8 x 3907 245 / 237, 8 x 30381 1977 / 1837.
+// The whole step, three contexts in turn: 64 x 733 465 / 467, 64 x 977 619 / 615, 32 x 1465 477 / 478, 24 x 1954 484 / 476, 16 x
+// 2930 494 / 490, 3 x 17090 823 / 815.
 constexpr uint32_t kPagedChunks = 45056;
 static_assert(kPagedChunks >= kShortChunks, "rows in pages have blocks of 32 chunks and more: eight chunks to a wavefront");
 // Block-sign, which keeps no lists, from so many on (first pass, chunks in order / pages): 16 x 733 chunks 96.7 / 99.2; 8 x 2730
@@ -266,8 +268,6 @@ struct TopkWorkspace {
   uint32_t* wire_total;    // n : words of the gap stream of the message being packed or unpacked
   uint32_t* wire_tile_off; // n * ceil(k / kWireTile) : where each tile of gaps starts in its stream
   uint32_t* wire_tile_sum; // n * ceil(k / kWireTile) : coordinates before each tile, while unpacking
-  uint32_t page_turn;   // first pass in pages: row i starts its dies' pages (i * page_turn) >> 16 further on
-  uint32_t desc_parts;  // segments of a chunk: one, or (rows whose first pass goes in pages) one for every quarter
   uint2* desc;          // n * num_chunks * desc_parts : (offset, count) of the segment in the candidate list
   uint2* desc2;         // n * num_chunks * desc_parts : offset of the segment in the band list; entries at or above the
                         //                               band | entries in the band << 13
@@ -292,6 +292,8 @@ struct TopkWorkspace {
   const WgSlot* map_final;  // .seg = block (worker 0's segment of it), .group = chunk of the block
   uint32_t* sel_off_srv;    // n * (4 * chunks of a whole row + 1) : list offsets per quarter of a chunk, for the
                             //                                   server's lines run from lists
+  uint32_t page_turn;   // first pass in pages: row i starts its dies' pages (i * page_turn) >> 16 further on
+  uint32_t desc_parts;  // segments of a chunk: one, or (rows whose first pass goes in pages) one for every quarter
 };
 
 struct BlocksignWorkspace {

@@ -2958,8 +2958,8 @@ hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const 
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
   const TopkFlat none{};
-  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, no_e, geo,
-                                                        ws, opt, ap, none);
+  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat,
+                                                               no_e, geo, ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }

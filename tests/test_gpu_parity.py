@@ -314,10 +314,10 @@ def test_blocksign_deferred_residual(n, d, offsets):
 @pytest.mark.parametrize("cached", [0, 3, 4])
 @pytest.mark.parametrize("n", [1, 8, 9, 17, 40])
 def test_blocksign_server_kernel_shares(n, cached):
-    """The server kernel gives a wavefront a share of a chunk's rounds (two with the whole state cached, else
-    four) and fetches each worker's sign words of the share once, eight or sixteen workers per trip; shares that
-    meet a block's or the row's end go round by round.  Worker counts around the trip sizes, block ends on and
-    off the shares' and the sign words' boundaries, a last chunk that is partial, both share sizes."""
+    """The server kernel gives a wavefront a share of two of a chunk's rounds and fetches each worker's sign words of
+    the share once, sixteen workers per trip; shares that meet a block's or the row's end go round by round, eight
+    workers at a time.  Worker counts around the trip sizes, block ends on and off the shares' and the sign words'
+    boundaries, a last chunk that is partial, the state accessed in every way (none, some, all arrays kept cached)."""
     d = 5 * 4096 + 777
     rng = np.random.default_rng(n * 10 + cached)
     off = np.array([0, 512, 1024 + 32, 4096, 2 * 4096 + 1, 3 * 4096 + 1024, 4 * 4096 + 2048 - 5, d], dtype=np.int64)
