@@ -477,8 +477,8 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 // layers, 342 either way.  A quarter that lies inside one block -- all but a few per row -- is summed in a register window
 // placed by the quarter's own largest magnitude and goes to the block's digits with at most three atomics; a quarter that
 // meets block ends goes through the blocks it meets, round by round.  Either way it works from the one batch of loads in its
-// registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 683 / 496
-// us, of 1000 671 / 517; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
+// registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 634 / 469
+// us, of 1000 654 / 499; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
 // round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5; not in pages, where one quarter more or less
 // round by round is nothing and the second form in the kernel's code cost 8 x 124439808 1910 -> 1934 us).  Up to 96 registers
 // cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous
