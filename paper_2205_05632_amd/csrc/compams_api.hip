@@ -143,12 +143,12 @@ std::vector<BlockShape> block_shapes(const compams_config* c) {
   return v;
 }
 
-// What a layout is for: a context's workspace, the tables of compams_step_static() (which has no window to carry over
-// and no messages to pack), or the size by which that call decides what it takes.  The last is a measure of its own,
+// What a layout is for: a context's workspace, the tables of compams_step_static() (which has no messages to pack, and a band list of
+// static_band entries), or the size by which that call decides what it takes.  The last is a measure of its own,
 // so that what the call takes does not change with the tables.
 enum LayoutFor { kForContext, kForStatic, kStaticMeasure };
 
-Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
+Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uint32_t static_band = 0) {
   Layout L;
   std::memset(&L, 0, sizeof L);
   const size_t n = static_cast<size_t>(c->n), d = static_cast<size_t>(c->d);
@@ -164,6 +164,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.cap_alloc = static_cast<uint32_t>(cap);
     const bool context = purpose == kForContext, measure = purpose == kStaticMeasure;
     L.band_alloc = context ? band_capacity(k, L.cap_alloc) : 0;
+    if (purpose == kForStatic) L.band_alloc = static_band;
     const size_t offsets = measure ? nc + 1 : nc * kWaves + 1;
     L.rows = take(n * sizeof(TopkRow));
     L.flags = take(64);
@@ -180,7 +181,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext) {
     L.sel_off = take(n * offsets * 4);
     L.desc_parts = context && paged_first_pass(n, L.num_chunks) ? kWaves : 1;
     L.desc = take(n * nc * L.desc_parts * 8);
-    L.desc2 = take(context || measure ? n * nc * L.desc_parts * 8 : 0);
+    L.desc2 = take(context || measure || L.band_alloc ? n * nc * L.desc_parts * 8 : 0);
     L.bnd = take(n * kBoundaryCap * 8);
     L.bnd_sel = take(n * kBoundaryCap * 4);
     L.cand = take(n * cap * 8);
@@ -978,6 +979,11 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   try {
     if (make_layout(cfg, kStaticMeasure).total > most) return COMPAMS_WORKSPACE_TOO_SMALL;
     ctx.lay = make_layout(cfg, kForStatic);
+    // A band list of what room there is, up to four times what is kept and 8192 entries: a sampled window is wide.
+    const size_t room = most - std::min<size_t>(most, ctx.lay.total + 1024 + static_cast<size_t>(cfg->n) * ctx.lay.num_chunks * 8);
+    const uint32_t band = static_cast<uint32_t>(std::min<size_t>(
+        {4 * static_cast<size_t>(cfg->k) + 8192, kBandMaxEntries, ctx.lay.cap_alloc, room / (8 * static_cast<size_t>(cfg->n))}));
+    if (band) ctx.lay = make_layout(cfg, kForStatic, band);
   } catch (...) {
     return COMPAMS_HIP_ERROR;
   }
@@ -989,7 +995,7 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   ctx.cfg.workspace_bytes = COMPAMS_STATIC_SCRATCH_BYTES;
   set_geometry(&ctx);
   bind_topk_workspace(&ctx, w);
-  ctx.tkopt.band = kBandOff;
+  ctx.tkopt.band = ctx.lay.band_alloc ? kBandLists : kBandOff;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Layout& lay = ctx.lay;
   const AmsParams ap = ams_params(ctx.cfg, lr, -1);
@@ -997,7 +1003,7 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   auto ok = [&](hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; };
   // the array keeps what the last call left: control blocks, counters, cursors and histograms start at zero (a fill
   // kernel, so that the call can be recorded into a graph); the tables behind them are written before they are read
-  ok(fill_u32(reinterpret_cast<uint32_t*>(w), lay.chunk_rec / 4, 0u, stream));
+  if (ctx.geo.d < kSample) ok(fill_u32(reinterpret_cast<uint32_t*>(w), lay.chunk_rec / 4, 0u, stream));  // else with the sample
   // what the workers send is written where the caller wants it
   if (idx_out) ctx.tk.idx = idx_out;
   if (val_out) ctx.tk.val = val_out;

@@ -380,6 +380,8 @@ struct Launcher;  // host-side helper that brackets launches with events (compam
 // Host-side launch entry points, one per compressor (defined next to their kernels).
 // whole: a step that stands for itself (fresh control blocks, no guess, nothing pending): the residual's zeros are
 // written at once.
+// It clears the tables from the control blocks up to the chunk records itself where rows have kSample coordinates or more.
+constexpr uint32_t kSample = 4096;
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& opt, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
                      bool first_pass_may_predict, bool clear_pending, bool workers_only, bool whole, hipStream_t stream,

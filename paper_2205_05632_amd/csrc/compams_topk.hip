@@ -51,6 +51,8 @@
 // varies from run to run but nothing that is output depends on it.  No floating-point atomics are used
 // anywhere.
 
+#include <algorithm>
+
 #include "compams_device.h"
 #include "compams_internal.h"
 
@@ -230,8 +232,9 @@ __device__ __forceinline__ uint32_t load_agent(const AgentView& v, uint32_t word
 // h: NB bucket counts in LDS.  Returns through out2 the largest s with sum_{b >= s} h[b] >= need and the
 // count strictly above it.  Requires 1 <= need <= sum h.
 // ---------------------------------------------------------------------------------------------
-template <int NB, int NT = kWG>
-__device__ void find_crossing(const uint32_t* h, uint32_t need, uint32_t* suf /* NT + 1 */, uint32_t* out2) {
+// WANTS of them at once (each returned in two words of out2).
+template <int NB, int NT = kWG, int WANTS = 1>
+__device__ void find_crossings(const uint32_t* h, const uint32_t (&needs)[WANTS], uint32_t* suf /* NT + 1 */, uint32_t* out2) {
   constexpr int PER = NB / NT;
   static_assert(NB % NT == 0 && NT % 64 == 0, "buckets per thread, whole wavefronts");
   const int t = threadIdx.x;
@@ -248,7 +251,7 @@ __device__ void find_crossing(const uint32_t* h, uint32_t need, uint32_t* suf /*
   }
   __syncthreads();  // everybody has read h and whatever suf / out2 held before
   if (lane == 0) suf[wave] = s;  // the wavefront's total
-  if (t == 0) { out2[0] = 0; out2[1] = 0; }
+  if (t < 2 * WANTS) out2[t] = 0;
   __syncthreads();
   uint32_t higher = 0;
 #pragma unroll
@@ -256,19 +259,28 @@ __device__ void find_crossing(const uint32_t* h, uint32_t need, uint32_t* suf /*
     if (static_cast<uint32_t>(w) > wave) higher += suf[w];
   s += higher;                       // entries in this thread's buckets and all buckets above them
   const uint32_t above_mine = s - part;  // entries in the buckets above this thread's
-  if (s >= need && above_mine < need) {  // exactly one thread when 1 <= need <= sum h
-    uint32_t acc = above_mine;
-    for (int i = PER - 1; i >= 0; --i) {
-      const uint32_t hb = h[t * PER + i];
-      if (acc + hb >= need) {
-        out2[0] = t * PER + i;
-        out2[1] = acc;
-        break;
+#pragma unroll
+  for (int w = 0; w < WANTS; ++w) {
+    const uint32_t need = needs[w];
+    if (s >= need && above_mine < need) {  // exactly one thread when 1 <= need <= sum h
+      uint32_t acc = above_mine;
+      for (int i = PER - 1; i >= 0; --i) {
+        const uint32_t hb = h[t * PER + i];
+        if (acc + hb >= need) {
+          out2[2 * w] = t * PER + i;
+          out2[2 * w + 1] = acc;
+          break;
+        }
+        acc += hb;
       }
-      acc += hb;
     }
   }
   __syncthreads();
+}
+template <int NB, int NT = kWG>
+__device__ __forceinline__ void find_crossing(const uint32_t* h, uint32_t need, uint32_t* suf, uint32_t* out2) {
+  const uint32_t needs[1] = {need};
+  find_crossings<NB, NT, 1>(h, needs, suf, out2);
 }
 
 // Copy a row's global histogram into LDS and clear it for the next step.
@@ -1728,50 +1740,89 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
 // whose list would not fit by what the sample holds from that bucket upwards (few magnitudes; three of 4096 are more than
 // 65536 entries from 90 M coordinates on) gets no guess: the list would be written and counted for nothing.  It decides only
 // whether the row is read again.  (Eight entries instead of three, and no look at what fits: 34 M coordinates, k = 1000, 362
-// us a call, now 338; 60 M, k = 100000, 580, now 523.)  No window is known: the general kernels select, and are told so here.
+// us a call, now 338; 60 M, k = 100000, 580, now 523.)  
 // ---------------------------------------------------------------------------------------------
-constexpr uint32_t kSample = 4096;
+// The same sample gives the window of keys in which the threshold is expected, where the first pass is to keep band lists: from the
+// bucket above which the expected count plus three deviations lies to the one above which the expected count less three
+// deviations does, if the band list would hold what the sample says lies in it.  The band kernel then selects, as in a step that
+// carries its window over, and the four general ones (30 us of the call for 4 x 300007, k = 3000) return at once.  Fewer than
+// kWindowSample of the sample's entries above the threshold say too little: the window is two octaves wide and more, its entries'
+// lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (us a call, 24 drawn shapes each,
+// without a window / from 8 entries on / always, geometric means of the gain: 1.04, 1.06, 1.05; always: 4 x 1634958, k = 2524,
+// 70.9 -> 74.0; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 -> 43.9.)
+// The launch also clears the tables that the call expects at zero, which took a launch of its own, 2 us: a workgroup its row's control block,
+// further workgroups what follows the flags.
+constexpr uint32_t kWindowSample = 8;
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __restrict__ g, const float* __restrict__ e,
                                                                Geometry geo, TopkWorkspace ws, TopkOptions opt) {
   __shared__ uint32_t lh[kNB0];
   __shared__ uint32_t suf[kPickThreads + 1];
-  __shared__ uint32_t out2[2];
+  __shared__ uint32_t out2[6];
   const uint32_t row = blockIdx.x, t = threadIdx.x;
+  if (row >= geo.n) {  // clears, 16 bytes a thread
+    uint4* p = reinterpret_cast<uint4*>(ws.counters);
+    const uint32_t quads = static_cast<uint32_t>(reinterpret_cast<uint4*>(ws.chunk_rec) - p);
+    for (uint32_t q = (row - geo.n) * kPickThreads + t; q < quads; q += (gridDim.x - geo.n) * kPickThreads) p[q] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  // the control block as the first pass reads it; nothing else in it but zeros
+  uint32_t cand_from = 0, guess = 0, valid = 0, band_lo = 0, band_hi = 0, band_mul = 0;
+  if (row == 0 && t == 0) ws.flags[0] = opt.band == kBandLists ? 0u : 1u;  // without a band kernel the general ones are told here
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   const float* er = e + static_cast<int64_t>(row) * geo.ld;
   constexpr uint32_t kQuads = kSample / 4;
   constexpr int kPer = kQuads / kPickThreads;
   static_assert(kQuads % kPickThreads == 0, "whole quads");
   const uint32_t whole_quads = geo.d / 4;  // at least kQuads: the host asks for no sample of a shorter row
-  if (row == 0 && t == 0) ws.flags[0] = 1;
   const float each = static_cast<float>(geo.d) / static_cast<float>(kSample);  // coordinates that a sampled one stands for
   const float share = static_cast<float>(geo.k) / each;
   const float want = 1.5f * share + 3.0f * sqrtf(share) + 3.0f;
-  if (want >= static_cast<float>(kSample) || want * each > static_cast<float>(opt.cap)) return;  // uniform
-  float4 x[kPer];
+  if (want < static_cast<float>(kSample) && want * each <= static_cast<float>(opt.cap)) {  // uniform
+    float4 x[kPer];
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const uint32_t q = u * kPickThreads + t;
-    const uint32_t j = 4u * static_cast<uint32_t>((static_cast<uint64_t>(q) * whole_quads) / kQuads);  // (a shift)
-    const float4 ev = *reinterpret_cast<const float4*>(er + j), gv = *reinterpret_cast<const float4*>(gr + j);
-    x[u] = make_float4(ev.x + gv.x, ev.y + gv.y, ev.z + gv.z, ev.w + gv.w);
-  }
-  for (int b = t; b < kNB0; b += kPickThreads) lh[b] = 0;
-  __syncthreads();
+    for (int u = 0; u < kPer; ++u) {
+      const uint32_t q = u * kPickThreads + t;
+      const uint32_t j = 4u * static_cast<uint32_t>((static_cast<uint64_t>(q) * whole_quads) / kQuads);  // (a shift)
+      const float4 ev = *reinterpret_cast<const float4*>(er + j), gv = *reinterpret_cast<const float4*>(gr + j);
+      x[u] = make_float4(ev.x + gv.x, ev.y + gv.y, ev.z + gv.z, ev.w + gv.w);
+    }
+    for (int b = t; b < kNB0; b += kPickThreads) lh[b] = 0;
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].x)) >> kL0Shift], 1u);
-    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].y)) >> kL0Shift], 1u);
-    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].z)) >> kL0Shift], 1u);
-    atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].w)) >> kL0Shift], 1u);
+    for (int u = 0; u < kPer; ++u) {
+      atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].x)) >> kL0Shift], 1u);
+      atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].y)) >> kL0Shift], 1u);
+      atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].z)) >> kL0Shift], 1u);
+      atomicAdd(&lh[key_of_bits(__float_as_uint(x[u].w)) >> kL0Shift], 1u);
+    }
+    __syncthreads();
+    // (three crossings; no band list: the first one)
+    const float off = 3.0f * sqrtf(share) + 2.0f;
+    const uint32_t needs[3] = {static_cast<uint32_t>(want), static_cast<uint32_t>(fminf(want, share + off)),
+                               static_cast<uint32_t>(fmaxf(share - off, 1.0f))};
+    find_crossings<kNB0, kPickThreads, 3>(lh, needs, suf, out2);
+    if (static_cast<float>(out2[1] + lh[out2[0]]) * each <= static_cast<float>(opt.cap)) {  // uniform
+      guess = out2[0];
+      cand_from = (guess << kL0Shift) + 1u;
+    }
+    if (cand_from && opt.band == kBandLists) {  // uniform
+      const uint32_t lo = out2[2], from_lo = out2[3] + lh[lo];
+      const uint32_t hi = out2[4] + 1, above = out2[5];
+      band_lo = lo << kL0Shift;
+      band_hi = hi << kL0Shift;
+      const float inside = static_cast<float>(from_lo - above) * each;
+      const bool many = band_buckets(geo.k) == kBandBucketsMany && inside > 16.0f * kBandBucketsFew;
+      if (lo > 15 && hi < 0xff0u && 1.25f * inside <= static_cast<float>(opt.band_cap)) valid = many ? kBandMany : kBandFew;
+      band_mul = band_multiplier_dev(band_hi - band_lo, many ? kBandBucketsMany : kBandBucketsFew);
+    }
   }
-  __syncthreads();
-  find_crossing<kNB0, kPickThreads>(lh, static_cast<uint32_t>(want), suf, out2);
-  if (t == 0 && static_cast<float>(out2[1] + lh[out2[0]]) * each <= static_cast<float>(opt.cap)) {
-    ws.rows[row].b_guess = out2[0];
-    ws.rows[row].cand_from = (out2[0] << kL0Shift) + 1u;
-  }
+  static_assert(offsetof(TopkRow, cand_from) == 0 && offsetof(TopkRow, b_guess) == 4 && offsetof(TopkRow, band_valid) == 16 &&
+                offsetof(TopkRow, band_lo) == 20 && offsetof(TopkRow, band_hi) == 24 && offsetof(TopkRow, band_mul) == 28,
+                "words written below");
+  if (t < sizeof(TopkRow) / 4)
+    reinterpret_cast<uint32_t*>(ws.rows + row)[t] =
+        t == 0 ? cand_from : t == 1 ? guess : t == 4 ? valid : t == 5 ? band_lo : t == 6 ? band_hi : t == 7 ? band_mul : 0u;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2842,6 +2893,8 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 
 }  // namespace
 
+constexpr size_t kClearBytes = 32768;  // a workgroup of the sampling launch clears
+
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& options, const AmsParams& ap,
                      const float* g, float* e, float* theta, float* m, float* v, float* vhat,
                      bool first_pass_may_predict, bool clear_pending, bool workers_only, bool whole, hipStream_t stream,
@@ -2857,10 +2910,13 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const bool pick = geo.num_chunks <= kPickChunks && use_guess;
   TopkOptions opt = options;
   if (pick && opt.band) opt.band = kBandWindow;
+  if (whole && static_cast<uint64_t>(geo.k) * kSample < static_cast<uint64_t>(geo.d) * kWindowSample) opt.band = kBandOff;
   // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample; 4 rows of 65536,
   // k = 655: the whole call 66 us by the general kernels without a guess, 34.4 with it and one workgroup per row)
   if (whole && geo.d >= kSample) {
-    launch(L, kSlotPick, k_topk_sample, dim3(geo.n), dim3(kPickThreads), stream, g, e, geo, ws, opt);
+    const size_t bytes = reinterpret_cast<const char*>(ws.chunk_rec) - reinterpret_cast<const char*>(ws.counters);
+    const uint32_t clearing = static_cast<uint32_t>(std::min<size_t>((bytes + kClearBytes - 1) / kClearBytes, 256));
+    launch(L, kSlotPick, k_topk_sample, dim3(geo.n + clearing), dim3(kPickThreads), stream, g, e, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   auto* first = clear_pending ? (paged ? k_topk_lean<true, true, true> : k_topk_lean<true, true, false>)
@@ -2872,9 +2928,9 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     COMPAMS_CHECK_LAUNCH();
   } else {
     // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
-    // otherwise, so it runs in every step (about a microsecond when it has nothing to do) but one that stands for itself
+    // otherwise, so it runs in every step (about a microsecond when it has nothing to do)
     const uint32_t count_blocks = (geo.num_chunks + geo.count_cpw - 1) / geo.count_cpw;  // <= kMaxCountBlocks
-    if (!whole) {
+    if (!whole || opt.band) {
       launch(L, kSlotBand, paged ? k_topk_band<true, true> : k_topk_band<true, false>, dim3(count_blocks, geo.n), wg, stream, geo,
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
