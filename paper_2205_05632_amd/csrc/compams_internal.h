@@ -149,6 +149,13 @@ enum : uint32_t {
   kFastPick = 2   // k_topk_pick: chunk records hold prefixes over the whole row, there are no further tables
 };
 
+// What is still to be set for the next step's first pass.
+enum : uint32_t {
+  kNextSet = 0,    // nothing: there is a guess and a window, or none
+  kNextNone = 1,   // that there is no guess
+  kNextGuess = 2   // guess and window
+};
+
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
 struct TopkRow {
   uint32_t cand_from;   // 0, or one more than the first key that the next first pass lists as a candidate
@@ -179,8 +186,11 @@ struct TopkRow {
   uint32_t ticket_band;    // "last workgroup" counter of k_topk_band; zero between launches
   float noise;             // not taken by k_topk_band: what its window's population says of the threshold's scatter (0:
                            // there was no window)
-  uint32_t known_from;     // general route: see set_next_band()
-  uint32_t pad[26];
+  uint32_t known_from;     // see set_next_band()
+  uint32_t next;           // kNext*: what the last kernel is to make of the next step's window (selected in one launch), from ...
+  uint32_t next_prev2;     // ... the threshold key two steps before, and the window's population and a key in it
+  uint32_t next_population, next_ref;
+  uint32_t pad[22];
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
 

@@ -956,6 +956,30 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
   rowp->band_mul = valid ? band_multiplier_dev(hi - lo, many ? kBandBucketsMany : kBandBucketsFew) : 0u;
 }
 
+// The kernels that select in one launch end in one workgroup's chain, of which the above (divisions and roots, one after the other)
+// was 1 to 1.5 us: they leave what it needs in the control block, and a wavefront of the last kernel goes through it beside
+// the others' work (a step of 4 x 65536, k = 655: 24.3 us, with that and the ranking of k_topk_pick 23.2; 16 x 1 M 70.4, now 69.6).
+// population: entries of the window that was looked at (0: none), ref: a key in it.
+__device__ __forceinline__ void leave_next(TopkRow* rowp, uint32_t valid, uint32_t guess, uint32_t known, uint32_t tau_prev2,
+                                           uint32_t population, uint32_t ref) {
+  rowp->b_guess = guess;
+  rowp->next = valid ? kNextGuess : kNextNone;
+  rowp->known_from = known;
+  rowp->next_prev2 = tau_prev2;
+  rowp->next_population = population;
+  rowp->next_ref = ref;
+}
+__device__ __forceinline__ void set_next(TopkRow* rowp, uint32_t k, const TopkOptions& opt) {
+  const uint32_t next = rowp->next, lo = rowp->band_lo, hi = rowp->band_hi, population = rowp->next_population;
+  if (next == kNextSet) return;
+  rowp->next = kNextSet;
+  const float noise = population ? 8.0f * ((__uint_as_float(hi) - __uint_as_float(lo)) / __uint_as_float(rowp->next_ref)) *
+                                       sqrtf(static_cast<float>(k)) / static_cast<float>(population)
+                                 : default_band_noise(k);
+  set_next_band(rowp, rowp->tau, rowp->tau_prev, rowp->next_prev2, next == kNextGuess ? 1u : 0u, rowp->b_guess, rowp->known_from,
+                noise, k, opt);
+}
+
 // The runs of a problem's band list, from the high halves of the cursors the first pass advanced.
 __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& ws, const TopkRow* rowp,
                                                            uint32_t cursor_set, uint32_t cap) {
@@ -1030,7 +1054,7 @@ __device__ __forceinline__ uint32_t chunk_sum(uint32_t v, const SegmentLanes& s)
 //      ascending): the first k - (entries above the bucket) of them are kept, the last of those holds tau;
 //      an entry anywhere is kept iff key > tau, or key == tau and coordinate <= tie_last.  The coordinates of
 //      the kept ones, ascending, let the last kernel add them to the positions of the chunks after them.
-//      It also sets the guess and the band for the next step and clears the histogram.
+//      It also leaves what the next step's guess and band follow from (leave_next) and clears the histogram.
 // ---------------------------------------------------------------------------------------------
 template <bool UNI, bool QUARTERS>
 __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace ws, TopkOptions opt, uint32_t use_guess) {
@@ -1097,10 +1121,11 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   uint32_t* bh_used = many ? bh : bh + rot * kBandBucketsFew;
   const uint32_t per_quads = many ? kQuadsMany : kQuadsFew;  // uniform
   // What the window's population says of the threshold's scatter, also where this route is not taken.
-  float noise = 0.0f;
-  if (banded && bhi > blo && band.total)
-    noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(blo)) * sqrtf(static_cast<float>(k)) /
-            static_cast<float>(band.total);
+  auto noise = [&] {
+    return banded && bhi > blo && band.total ? 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(blo)) *
+                                                   sqrtf(static_cast<float>(k)) / static_cast<float>(band.total)
+                                             : 0.0f;
+  };
   if (!(banded && cand.fits && band.fits && bhi > blo)) {
     // Not this route.  The first pass may still have counted (lists that did not fit): one workgroup clears the
     // problem's histogram and counters; nobody of this launch makes use of them.
@@ -1109,7 +1134,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         for (uint32_t b = t; b < buckets; b += kWG) bh_used[b] = 0;
       if (t == 0) {
         rowp->fast = kFastNot;
-        rowp->noise = noise;
+        rowp->noise = noise();
         rowp->above = 0;
         if (sc.cursor_set != kNoCursorSet)
           for (uint32_t s = 0; s < kSubLists; ++s)
@@ -1376,13 +1401,11 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
         else if (cand.total <= opt.cap / 2) { valid = 1; guess = b0; }
       }
-      rowp->b_guess = guess;
-      set_next_band(rowp, tau, tau_prev, tau_before2, valid, guess, known_from(guess, list_from, cand.total, opt.cap), noise, k,
-                    opt);
+      leave_next(rowp, valid, guess, known_from(guess, list_from, cand.total, opt.cap), tau_before2, band.total, blo);
     }
   } else if (t == 0) {
     rowp->fast = kFastNot;
-    rowp->noise = noise;
+    rowp->noise = noise();
     uint32_t* cn = ws.counters + row * kCountersPerRow;
     cn[4] = 0;
     cn[5] = miss;  // (6): ... its bucket holds more entries than are ranked here
@@ -1415,10 +1438,11 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 //      one before found: from a list, buckets of a thousandth of an octave from the list's lower end upwards, so that
 //      the first one usually leaves a handful of entries (key bits from the top, as for a row, would put a list's keys
 //      into a few buckets, on which the LDS atomics queue).
-//   3. At most kPickRank entries left: they are ranked by (key descending, coordinate ascending).  More can only be
-//      equal keys: the last tie to take is found by the same histograms over the coordinates.
-//   4. Per chunk the entries kept, and their prefix over the row, for the last kernel; guess and window for the next
-//      step as the other routes set them.
+//   3. At most kPickRank entries left: they are ranked by (key descending, coordinate ascending), up to 64 of them by every
+//      wavefront for itself, without a barrier in between (4 rows of 65536: 2.7 us of the kernel's 9.7, now 1.8).  More can
+//      only be equal keys: the last tie to take is found by the same histograms over the coordinates.
+//   4. Per chunk the entries kept, and their prefix over the row, for the last kernel; what the next step's guess and window
+//      follow from (leave_next).
 // Where the line lies (whole step in us, 4 rows, the general kernels / this one): k = d / 100 16 chunks 30.6 / 24.6, 32
 // chunks 30.8 / 28.6, 48 chunks 31.1 / 33.7; k = d / 10 16 chunks 39.5 / 39.1, 20 chunks 40.1 / 42.9.  What bounds it is one compute
 // unit's instructions, about 20 us for a sweep over 65536 coordinates.  A row whose list did not hold (a selection of half
@@ -1572,26 +1596,44 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
       if (ok && key >= lo && key <= hi) sh.rank_en[atomicAdd(&sh.count, 1u)] = make_uint2(en.x, key);
     });
     __syncthreads();
-    uint32_t my_key = 0, my_coord = 0, rank = 0;
-    if (t < inside) {
-      my_coord = sh.rank_en[t].x;
-      my_key = sh.rank_en[t].y;
-      for (uint32_t q = 0; q < inside; ++q) {
-        const uint2 o = sh.rank_en[q];
-        rank += (o.y > my_key || (o.y == my_key && o.x < my_coord)) ? 1u : 0u;
+    uint32_t last;
+    if (inside <= 64) {  // every wavefront ranks them for itself: no more barriers (they took a third of the ranking)
+      const bool have = lane < inside;
+      const uint2 mine = have ? sh.rank_en[lane] : make_uint2(0u, 0u);
+      uint32_t rank = have ? 0u : 64u;
+      for (uint32_t q = 0; q < inside; ++q) {  // uniform
+        const uint32_t coord = __builtin_amdgcn_readlane(mine.x, q), key = __builtin_amdgcn_readlane(mine.y, q);
+        rank += (key > mine.y || (key == mine.y && coord < mine.x)) ? 1u : 0u;
       }
-      if (rank == need - 1) { sh.tau = my_key; sh.last = my_coord; }  // the last kept one
+      const uint32_t at = __builtin_ctzll(ballot64(rank == need - 1));  // the last kept one
+      tau = __builtin_amdgcn_readlane(mine.y, at);
+      last = __builtin_amdgcn_readlane(mine.x, at);
+      const bool tie = have && mine.y == tau;
+      ties = popc64(ballot64(tie));
+      ties_kept = popc64(ballot64(tie && mine.x <= last));
+    } else {
+      uint32_t my_key = 0, my_coord = 0, rank = 0;
+      if (t < inside) {
+        my_coord = sh.rank_en[t].x;
+        my_key = sh.rank_en[t].y;
+        for (uint32_t q = 0; q < inside; ++q) {
+          const uint2 o = sh.rank_en[q];
+          rank += (o.y > my_key || (o.y == my_key && o.x < my_coord)) ? 1u : 0u;
+        }
+        if (rank == need - 1) { sh.tau = my_key; sh.last = my_coord; }  // the last kept one
+      }
+      __syncthreads();
+      tau = sh.tau;
+      last = sh.last;
+      if (t < inside && my_key == tau) {
+        atomicAdd(&sh.ties, 1u);
+        if (my_coord <= last) atomicAdd(&sh.ties_in, 1u);
+      }
+      __syncthreads();
+      ties = sh.ties;
+      ties_kept = sh.ties_in;
     }
-    __syncthreads();
-    tau = sh.tau;
-    if (t < inside && my_key == tau) {
-      atomicAdd(&sh.ties, 1u);
-      if (my_coord <= sh.last) atomicAdd(&sh.ties_in, 1u);
-    }
-    __syncthreads();
-    ties = sh.ties;
-    ties_kept = sh.ties_in;
-    tie_last = ties_kept < ties ? sh.last : 0xffffffffu;
+    tie_last = ties_kept < ties ? last : 0xffffffffu;
   } else {
     tau = lo;
     ties = inside;
@@ -1699,13 +1741,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
     if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
     else if (at_hand <= opt.cap / 2) { valid = 1; guess = b0; }
   }
-  rowp->b_guess = guess;
-  float noise = default_band_noise(k);
-  if (miss == 0 && in_window && normal_key(tau))
-    noise = 8.0f * ((__uint_as_float(bhi) - __uint_as_float(blo)) / __uint_as_float(tau)) * sqrtf(static_cast<float>(k)) /
-            static_cast<float>(in_window);
-  set_next_band(rowp, tau, tau_before, tau_before2, valid, guess, LISTED ? known_from(guess, cand_lo, n_cand, opt.cap) : 0u,
-                noise, k, opt);
+  leave_next(rowp, valid, guess, LISTED ? known_from(guess, cand_lo, n_cand, opt.cap) : 0u, tau_before2,
+             miss == 0 && normal_key(tau) ? in_window : 0u, tau);
 }
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
@@ -2488,10 +2525,12 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
   if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = 0;  // the general kernels have run
   // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
   const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
-  if (ROLE != kServerHalf && c == 0 && i_first == 0)  // the next step's first pass allocates its candidate lists from the start
-    for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {
-      ws.rows[f.row0 + i * f.row_stride].cursor = 0;
-      ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
+  if (ROLE != kServerHalf && c == 0 && i_first == 0 && wave == NW - 1)  // (it has workers of its own only from NW on)
+    for (uint32_t i = lane; i < geo.n; i += 64) {
+      TopkRow* rowp = ws.rows + f.row0 + i * f.row_stride;
+      rowp->cursor = 0;  // the next step's first pass allocates its candidate lists from the start
+      rowp->cursor_band = 0;
+      if (!CLEAR) set_next(rowp, f.k_loc, opt);
     }
   if (ROLE != kWorkerHalf) {  // (before the tile's barrier: other wavefronts may add here)
 #pragma unroll

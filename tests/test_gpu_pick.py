@@ -95,3 +95,24 @@ def test_ties_around_what_is_ranked(ties, listed):
         p.step(g, 1e-3, label=f"{ties} ties step {t}", with_e=t == 3)
     assert all(p.exact.values()), p.exact
     p.close()
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("left", [1, 2, 63, 64, 65, 255, 256, 257])
+def test_entries_left_to_rank(left, ties):
+    """Up to 64 are ranked by every wavefront for itself, up to 256 by the workgroup, beyond that there is one more histogram."""
+    n, d, above = 2, 5000, 100
+    rng = np.random.default_rng(left)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=above + (left + 1) // 2)
+    for t in range(5):
+        g = (rng.standard_normal((n, d)) * 1e-6).astype(np.float32)
+        for i in range(n):
+            where = rng.permutation(d)[: above + left]
+            g[i, where[:above]] = 10.0 + rng.random(above)
+            step = np.zeros(left) if ties else np.arange(left)
+            g[i, where[above:]] = np.float32(1.0) + step.astype(np.float32) * np.float32(2.0 ** -23)
+        # what is kept leaves the residual, what is left out comes back: the sign turns it over and the next gradient replaces it
+        e = p.cpu.get("e") if t else np.zeros((n, d), dtype=np.float32)
+        p.step(g - e, 1e-3, label=f"{left} left, step {t}", with_e=t == 4)
+    assert all(p.exact.values()), p.exact
+    p.close()
