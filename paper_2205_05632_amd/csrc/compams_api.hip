@@ -49,7 +49,8 @@ void launcher_end(Launcher* L, int slot, hipStream_t stream) {
 namespace {
 
 const char* const kSlotNames[kNumSlots] = {
-    "topk_pass_a", "topk_band", "topk_pick", "topk_level0", "topk_level1", "topk_level2", "topk_count", "topk_final",
+    "topk_pass_a", "topk_band", "topk_pick", "topk_general", "topk_level0", "topk_level1", "topk_level2",
+    "topk_count", "topk_final",
     "bs_pass1", "bs_finalize", "bs_pass2", "bs_amsgrad", "none_amsgrad", "wire_encode", "wire_decode"};
 
 static_assert(kCountersPerRow == COMPAMS_COUNTERS_PER_ROW, "the kernels' stride of the counters is the header's");
@@ -167,7 +168,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     if (purpose == kForStatic) L.band_alloc = static_band;
     const size_t offsets = measure ? nc + 1 : nc * kWaves + 1;
     L.rows = take(n * sizeof(TopkRow));
-    L.flags = take(64);
+    L.flags = take(256);
     L.counters = take(n * COMPAMS_COUNTERS_PER_ROW * 4);
     L.hist0 = take(n * kNB0 * 4);
     L.hist1 = take(n * kNB1 * 4);
@@ -184,7 +185,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     L.desc2 = take(context || measure || L.band_alloc ? n * nc * L.desc_parts * 8 : 0);
     L.bnd = take(n * kBoundaryCap * 8);
     L.bnd_sel = take(n * kBoundaryCap * 4);
-    L.cand = take(n * cap * 8);
+    L.cand = take(n * (measure ? cap : cand_pitch(L.cap_alloc)) * 8);
     L.band = take(n * (measure ? std::min<size_t>({k + 4096, kBandMaxEntries, cap}) : static_cast<size_t>(L.band_alloc)) * 8);
     L.idx = take(n * k * 4);
     L.val = take(n * k * 4);
@@ -205,7 +206,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
            big = 0;
     uint32_t cap_max = 0, band_max = 0;
     for (const BlockShape& b : shapes) {
-      k += b.k; chunks += b.nc; caps += b.cap; cap_max = std::max(cap_max, b.cap);
+      k += b.k; chunks += b.nc; caps += cand_pitch(b.cap); cap_max = std::max(cap_max, b.cap);
       bhists += b.micro ? 0 : band_buckets(b.k);
       bcaps += b.band_cap; band_max = std::max(band_max, b.band_cap);
       wg_first += b.groups_first; wg_level0 += b.groups_level0; wg_sweep += b.groups_sweep; wg_count += b.count_blocks;
@@ -226,7 +227,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     L.flat.seloff_stride = static_cast<uint32_t>(chunks * kWaves + M);
     L.flat.cand_stride = caps;
     L.rows = take(S * sizeof(TopkRow));
-    L.flags = take(64);
+    L.flags = take(256);
     L.counters = take(S * COMPAMS_COUNTERS_PER_ROW * 4);
     L.hist0 = take(S * kNB0 * 4);
     L.hist1 = take(S * kNB1 * 4);
@@ -510,7 +511,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
         const std::vector<BlockShape> shapes = block_shapes(cfg);
         const size_t M = shapes.size();
         uint64_t chunks = 0, caps = 0, bcaps = 0, bhists = 0;
-        for (const BlockShape& b : shapes) { chunks += b.nc; caps += b.cap; bcaps += b.band_cap; bhists += b.micro ? 0 : band_buckets(b.k); }
+        for (const BlockShape& b : shapes) { chunks += b.nc; caps += cand_pitch(b.cap); bcaps += b.band_cap; bhists += b.micro ? 0 : band_buckets(b.k); }
         uint32_t cursor_sets = 0;
         segs.resize(static_cast<size_t>(cfg->n) * M);
         for (int64_t i = 0; i < cfg->n; ++i) {
@@ -541,7 +542,7 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
             for (uint32_t q = 0; q < sh.count_blocks; ++q) m_count.push_back(WgSlot{si, q});
             if (i == 0)
               for (uint32_t q = 0; q < sh.nc; ++q) m_final.push_back(WgSlot{si, q});
-            c_at += sh.nc; cap_at += sh.cap; k_at += sh.k; band_at += sh.band_cap;
+            c_at += sh.nc; cap_at += cand_pitch(sh.cap); k_at += sh.k; band_at += sh.band_cap;
             bhist_at += sh.micro ? 0 : band_buckets(sh.k);
           }
         }

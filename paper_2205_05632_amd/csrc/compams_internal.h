@@ -156,6 +156,10 @@ enum : uint32_t {
   kNextGuess = 2   // guess and window
 };
 
+constexpr uint32_t kQueueWord = 32;  // (a cache line apart from what everybody reads)
+// The part of the general route that a problem is at: the parts before it are done.
+enum : uint32_t { kPhaseLevel0 = 0, kPhaseLevel1 = 1, kPhaseLevel2 = 2, kPhaseCount = 3 };
+
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
 struct TopkRow {
   uint32_t cand_from;   // 0, or one more than the first key that the next first pass lists as a candidate
@@ -190,9 +194,14 @@ struct TopkRow {
   uint32_t next;           // kNext*: what the last kernel is to make of the next step's window (selected in one launch), from ...
   uint32_t next_prev2;     // ... the threshold key two steps before, and the window's population and a key in it
   uint32_t next_population, next_ref;
-  uint32_t pad[22];
+  uint32_t phase;          // kPhase*: how far k_topk_general is with a problem left to it
+  uint32_t listed;         // with it: the candidate list held (0 also where nobody has looked)
+  uint32_t pad[20];
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
+
+// Entries from one problem's candidate list to the next one's: whole cache lines.
+__host__ __device__ __forceinline__ uint64_t cand_pitch(uint32_t cap) { return (static_cast<uint64_t>(cap) + 15) / 16 * 16; }
 
 // Bucket of a key inside a band of `span` keys starting at lo: floor(rel * buckets / span) for rel = key - lo,
 // computed as the high word of rel * mul with mul = floor(2^32 * buckets / span); a band of at most `buckets`
@@ -285,7 +294,7 @@ struct TopkWorkspace {
   uint32_t* bhist;      // band_buckets(k) per problem : how many band entries fall into each bucket; zero between steps
   uint2* bnd;           // n * kBoundaryCap : the entries of the bucket that holds the threshold key
   uint32_t* bnd_sel;    // n * kBoundaryCap : coordinates of the kept ones among them, ascending
-  uint32_t* flags;      // [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared
+  uint32_t* flags;      // [kQueueWord]: tasks drawn by k_topk_general.  [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared
                         //      by the step's last kernel): the general kernels return at once otherwise
   uint2* cand;          // n * cap_alloc  : (coordinate, fp32 bits)
   int32_t* idx;         // n * k
@@ -380,7 +389,8 @@ struct Geometry {
 
 // Kernel slots for optional timing.
 enum KernelSlot {
-  kSlotPassA = 0, kSlotBand, kSlotPick, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount, kSlotTopkFinal,
+  kSlotPassA = 0, kSlotBand, kSlotPick, kSlotGeneral, kSlotLevel0, kSlotLevel1, kSlotLevel2, kSlotCount,
+  kSlotTopkFinal,
   kSlotBsPass1, kSlotBsFinal, kSlotBsPass2, kSlotBsAms,
   kSlotNoneAms, kSlotWireEncode, kSlotWireDecode, kNumSlots
 };

@@ -5,8 +5,8 @@
 // (fp32 pattern without the sign; ties to the lower coordinate) are written out as ascending
 // (coordinate, value) lists, and the residual at those coordinates becomes zero.
 //
-// Kernels of a step.  In the steady state three of them do the work (first pass, band, final); the four
-// general ones in between return at once for every row whose threshold the band kernel has found:
+// Kernels of a step.  In the steady state three of them do the work (first pass, band, final); the general
+// ones in between return at once for every row whose threshold the band kernel has found:
 //   first pass     x = e + g -> e as a grid of short workgroups, one chunk each.  When the previous step's
 //                  threshold bucket is carried over as a guess, the same pass writes the candidate list: the
 //                  entries at or above the guessed bucket, a segment per chunk.  When the last two thresholds
@@ -20,7 +20,7 @@
 //                  gives tau, the ties to keep (by coordinate) and the next step's guess and band.
 //   pick           rows of at most 16 chunks, in every step that may have a guess: the whole selection by one workgroup
 //                  per row, in place of the band kernel and the general ones.
-//   The general route (12 + 10 + 9 key bits and a zero sign bit), for every other row:
+//   The general route (12 + 10 + 9 key bits and a zero sign bit), for every other row, in four launches or in one:
 //   level 0        histogram of the 12-bit threshold buckets, from the candidate list when the guess held (the
 //                  list then holds at least k entries), else from the row itself; for a listed row also the
 //                  level-1 histograms of the three buckets from the guess upwards, among which the threshold
@@ -52,6 +52,7 @@
 // anywhere.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "compams_device.h"
 #include "compams_internal.h"
@@ -106,6 +107,22 @@ __device__ __forceinline__ RoundRank rank_round(const bool flag[4]) {
   return rr;
 }
 
+// Stores that other workgroups of the same launch read (see last_group_of_row).
+__device__ __forceinline__ void store_agent(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(uint2* p, uint2 v) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), static_cast<uint64_t>(v.x) | (static_cast<uint64_t>(v.y) << 32),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What the parts of the general route hand on: SAME: to the same launch, else to the next one.
+template <bool SAME, typename T>
+__device__ __forceinline__ void hand_on(T* p, T v) {
+  if constexpr (SAME) store_agent(p, v);
+  else *p = v;
+}
+
 // Candidate entries of the chunk a wavefront is walking are first staged in LDS (kStage entries per
 // wavefront) so that the chunk's segment can be allocated with one atomic once its size is known and
 // then written with coalesced stores.  A chunk with more candidates than that is re-read instead.
@@ -135,6 +152,7 @@ __device__ __forceinline__ uint32_t segment_request(TopkRow* rowp, uint32_t cnt)
 
 // Write the chunk's segment: from the staging area if everything fitted there, else by reading the chunk's
 // (already stored) corrected gradients again.
+template <bool SAME>
 __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, uint32_t cnt,
                                               const float* __restrict__ er, uint32_t d, uint32_t c,
                                               uint32_t thr_bucket, uint2* candr, uint32_t cap, uint2* descr,
@@ -145,7 +163,7 @@ __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, 
     off = first_lane(raw);
     if (off + cnt <= cap) {  // otherwise the row's list has overflowed and will not be used
       if (cnt <= static_cast<uint32_t>(kStage)) {
-        for (uint32_t q = lane; q < cnt; q += 64) candr[off + q] = stage[q];
+        for (uint32_t q = lane; q < cnt; q += 64) hand_on<SAME>(candr + off + q, stage[q]);
       } else {
         uint32_t at = off;
         for (int r = 0; r < kRounds; ++r) {
@@ -162,7 +180,7 @@ __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, 
 #pragma unroll
           for (int s = 0; s < 4; ++s)
             if (flag[s]) {
-              if (pos < off + cnt) candr[pos] = make_uint2(j + s, bits[s]);
+              if (pos < off + cnt) hand_on<SAME>(candr + pos, make_uint2(j + s, bits[s]));
               ++pos;
             }
           at += rr.total;
@@ -172,15 +190,16 @@ __device__ __forceinline__ void segment_write(uint32_t raw, const uint2* stage, 
   }
   if (lane < parts) {  // (parts of it one behind the other, where a chunk has several segments)
     const uint32_t share = (cnt + parts - 1) / parts, at = share * lane < cnt ? share * lane : cnt;
-    descr[c * parts + lane] = make_uint2(off + at, cnt - at < share ? cnt - at : share);
+    hand_on<SAME>(descr + c * parts + lane, make_uint2(off + at, cnt - at < share ? cnt - at : share));
   }
 }
 
+template <bool SAME>
 __device__ __forceinline__ void flush_chunk(const uint2* stage, uint32_t cnt, const float* __restrict__ er, uint32_t d,
                                             uint32_t c, uint32_t thr_bucket, TopkRow* rowp, uint2* candr,
                                             uint32_t cap, uint2* descr, uint32_t parts) {
   const uint32_t raw = segment_request(rowp, cnt);
-  segment_write(raw, stage, cnt, er, d, c, thr_bucket, candr, cap, descr, parts);
+  segment_write<SAME>(raw, stage, cnt, er, d, c, thr_bucket, candr, cap, descr, parts);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -225,6 +244,10 @@ __device__ __forceinline__ AgentView agent_view(const uint32_t* p, uint32_t word
 }
 __device__ __forceinline__ uint32_t load_agent(const AgentView& v, uint32_t word) {
   return __builtin_amdgcn_raw_buffer_load_b32(v.rsrc, word * 4u, 0, /*device-scope policy*/ 16);
+}
+
+__device__ __forceinline__ uint2 load_agent2(const AgentView& v, uint32_t pair) {
+  return make_uint2(load_agent(v, 2 * pair), load_agent(v, 2 * pair + 1));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -302,13 +325,13 @@ __device__ __forceinline__ void take_hist(uint32_t* gh, uint32_t* h) {
 
 // bstar and need are passed in (not re-read from the control block): the caller may have written them a
 // moment ago, and a line of the control block read earlier by this compute unit may still sit in its L1.
-template <int NT = kWG>
+template <bool SAME, int NT = kWG>
 __device__ __forceinline__ void resolve_level1(TopkRow* rp, uint32_t bstar, uint32_t need, const uint32_t* h,
                                                uint32_t* suf, uint32_t* out2) {
   find_crossing<kNB1, NT>(h, need, suf, out2);
   if (threadIdx.x == 0) {
-    rp->prefix1 = (bstar << (kL0Shift - kL1Shift)) | out2[0];
-    rp->need = need - out2[1];
+    hand_on<SAME>(&rp->prefix1, (bstar << (kL0Shift - kL1Shift)) | out2[0]);
+    hand_on<SAME>(&rp->need, need - out2[1]);
     rp->level1_done = 1;
   }
 }
@@ -476,24 +499,27 @@ __device__ __forceinline__ SegCtx seg_ctx_of(uint32_t seg, uint32_t group, uint3
   return c;
 }
 
+// The context of workgroup `group` of the row `seg`, `groups` of them.
+__device__ __forceinline__ SegCtx row_ctx(uint32_t seg, uint32_t group, uint32_t groups, const Geometry& geo, const TopkOptions& opt) {
+  SegCtx c;
+  c.seg = seg;
+  c.group = group;
+  c.groups = groups;
+  c.elem_off = static_cast<int64_t>(c.seg) * geo.ld;
+  c.coord_base = 0;
+  c.chunk_base = static_cast<size_t>(c.seg) * geo.num_chunks;
+  c.seloff_base = static_cast<size_t>(c.seg) * (geo.num_chunks * kWaves + 1);
+  c.cand_base = static_cast<size_t>(c.seg) * cand_pitch(opt.cap);
+  c.list_base = static_cast<size_t>(c.seg) * geo.k;
+  c.band_base = static_cast<size_t>(c.seg) * opt.band_cap;
+  c.bhist_base = static_cast<size_t>(c.seg) * band_buckets(geo.k);
+  c.cursor_set = geo.num_chunks >= kSubListMinChunks ? c.seg : kNoCursorSet;  // short rows keep one run
+  return c;
+}
+
 template <bool UNI, int CLASS>
 __device__ __forceinline__ SegCtx seg_ctx(Geometry& geo, TopkOptions& opt, const TopkWorkspace& ws) {
-  if (UNI) {
-    SegCtx c;
-    c.seg = blockIdx.y;
-    c.group = blockIdx.x;
-    c.groups = gridDim.x;
-    c.elem_off = static_cast<int64_t>(c.seg) * geo.ld;
-    c.coord_base = 0;
-    c.chunk_base = static_cast<size_t>(c.seg) * geo.num_chunks;
-    c.seloff_base = static_cast<size_t>(c.seg) * (geo.num_chunks * kWaves + 1);
-    c.cand_base = static_cast<size_t>(c.seg) * opt.cap;
-    c.list_base = static_cast<size_t>(c.seg) * geo.k;
-    c.band_base = static_cast<size_t>(c.seg) * opt.band_cap;
-    c.bhist_base = static_cast<size_t>(c.seg) * band_buckets(geo.k);
-    c.cursor_set = geo.num_chunks >= kSubListMinChunks ? c.seg : kNoCursorSet;  // short rows keep one run
-    return c;
-  }
+  if (UNI) return row_ctx(blockIdx.y, blockIdx.x, gridDim.x, geo, opt);
   // (the records come through the vector path: through the scalar one the first pass was 1-2 % slower)
   const WgSlot slot = (CLASS == kClassFirst ? ws.map_first
                        : CLASS == kClassLevel0 ? ws.map_level0
@@ -504,6 +530,32 @@ __device__ __forceinline__ SegCtx seg_ctx(Geometry& geo, TopkOptions& opt, const
                     : CLASS == kClassLevel0 ? sg.groups_level0
                     : CLASS == kClassSweep ? sg.groups_sweep : sg.count_blocks,
                     sg, geo, opt);
+}
+
+constexpr uint32_t kRowWord(size_t offset) { return static_cast<uint32_t>(offset / 4); }
+
+// How the parts of the general route hand things on: SAME: inside one launch, at device scope; else from launch to launch, with
+// ordinary accesses (at device scope the four launches took 5 us more).
+template <bool SAME>
+struct Handed {  // words from p on, `words` of them
+  const uint32_t* p;
+  AgentView view;
+  __device__ __forceinline__ Handed(const void* from, uint32_t words) : p(static_cast<const uint32_t*>(from)) {
+    if constexpr (SAME) view = agent_view(p, words);
+  }
+  __device__ __forceinline__ uint32_t word(uint32_t at) const {
+    if constexpr (SAME) return load_agent(view, at);
+    else return p[at];
+  }
+  __device__ __forceinline__ uint2 pair(uint32_t at) const {
+    if constexpr (SAME) return load_agent2(view, at);
+    else return reinterpret_cast<const uint2*>(p)[at];
+  }
+};
+
+template <bool SAME>
+__device__ __forceinline__ Handed<SAME> handed_row(const TopkRow* rowp) {
+  return Handed<SAME>(rowp, sizeof(TopkRow) / 4);
 }
 
 // The runs of a problem's candidate list (one, or kSubLists for a row of the one-selection-per-row form).
@@ -543,15 +595,18 @@ __device__ __forceinline__ ListRuns runs_from_cursors(const TopkWorkspace& ws, c
 }
 
 // As level 0 recorded them for the later sweeps.
-__device__ __forceinline__ ListRuns runs_of_row(const TopkRow* rowp, uint32_t cap) {
+template <bool SAME>
+__device__ __forceinline__ ListRuns runs_of_row(const Handed<SAME>& row, uint32_t cap) {
   ListRuns L;
-  L.lists = rowp->n_lists;
+  L.lists = row.word(kRowWord(offsetof(TopkRow, n_lists)));
   L.pitch = cap / kSubLists;
   L.total = 0;
   L.fits = true;
 #pragma unroll
+  for (uint32_t s = 0; s < kSubLists; ++s) L.n[s] = row.word(kRowWord(offsetof(TopkRow, n_sub)) + s);
+#pragma unroll
   for (uint32_t s = 0; s < kSubLists; ++s) {
-    L.n[s] = s < L.lists ? rowp->n_sub[s] : 0u;
+    L.n[s] = s < L.lists ? L.n[s] : 0u;
     L.total += L.n[s];
   }
   return L;
@@ -1142,7 +1197,9 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         uint32_t* cn = ws.counters + row * kCountersPerRow;
         cn[4] = 0;
         cn[5] = !banded ? 1u : (!cand.fits ? 2u : 3u);  // no band was set; the candidate list / the band list overflowed
-        ws.flags[0] = 1;  // work for the general kernels
+        rowp->phase = kPhaseLevel0;
+        rowp->listed = use_guess && rowp->cand_from != 0 && cand.total >= k && cand.fits && !opt.force_dense ? 1u : 0u;
+        ws.flags[0] = 1;  // work for the general kernel
       }
     }
     return;
@@ -1409,7 +1466,9 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     uint32_t* cn = ws.counters + row * kCountersPerRow;
     cn[4] = 0;
     cn[5] = miss;  // (6): ... its bucket holds more entries than are ranked here
-    ws.flags[0] = 1;  // work for the general kernels
+    rowp->phase = kPhaseLevel0;
+    rowp->listed = cand.total >= k ? 1u : 0u;  // (banded, and the list fits)
+    ws.flags[0] = 1;  // work for the general kernel
   }
   if (t == 0) {
     rowp->above = 0;
@@ -1805,6 +1864,7 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
   }
   // the control block as the first pass reads it; nothing else in it but zeros
   uint32_t cand_from = 0, guess = 0, valid = 0, band_lo = 0, band_hi = 0, band_mul = 0;
+  if (row == 0 && t == 0) ws.flags[kQueueWord] = 0;
   if (row == 0 && t == 0) ws.flags[0] = opt.band == kBandLists ? 0u : 1u;  // without a band kernel the general ones are told here
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   const float* er = e + static_cast<int64_t>(row) * geo.ld;
@@ -1871,24 +1931,53 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
 // workgroup of the row finds the threshold bucket, decides the route of the remaining kernels and leaves the
 // guess for the next step.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI>
-__global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                      TopkOptions opt, uint32_t use_guess) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
-  __shared__ uint32_t lh[kNB0];
-  __shared__ uint32_t lh1[kTracked * kNB1];
-  __shared__ uint32_t suf[kWG + 1];
-  __shared__ uint32_t out2[2];
-  __shared__ uint32_t sh_flag, sh_l1, sh_bstar, sh_need;
-  const SegCtx sc = seg_ctx<UNI, kClassLevel0>(geo, opt, ws);
+// What the four parts of the general route keep in LDS, besides what they share.
+struct GeneralShared {
+  uint32_t suf[kWG + 1];
+  uint32_t scratch[kWG / 64 + 1];
+  uint32_t out2[2];
+  uint32_t flag, l1, bstar, need;
+};
+struct Level0Shared { uint32_t lh[kNB0], lh1[kTracked * kNB1]; };
+struct Level1Shared { uint32_t lh[kNB1]; uint2 stage[kWaves * kStage]; };
+struct Level2Shared { uint32_t lh[kNB2]; };
+struct CountShared { uint32_t gt[kMaxCountCpw], eq[kMaxCountCpw]; };
+
+// A part of a problem is done: the next one may begin.  By the thread that has written what the next one reads, with device-scope
+// stores.
+__device__ __forceinline__ void problem_at(TopkRow* rowp, uint32_t phase) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  store_agent(&rowp->phase, phase);
+}
+
+// (unrolled by hand: before it is in line, the compiler does not know how many threads there are, and in loops level 0 took 1.6 us more)
+template <uint32_t NB>
+__device__ __forceinline__ void clear_bins(uint32_t* bins) {
+  static_assert(NB % kWG == 0, "bins per thread");
+#pragma unroll
+  for (uint32_t i = 0; i < NB / kWG; ++i) bins[i * kWG + threadIdx.x] = 0;
+}
+template <uint32_t NB>
+__device__ __forceinline__ void flush_bins(const uint32_t* bins, uint32_t* to) {
+#pragma unroll
+  for (uint32_t i = 0; i < NB / kWG; ++i) {
+    const uint32_t h = bins[i * kWG + threadIdx.x];
+    if (h) atomicAdd(&to[i * kWG + threadIdx.x], h);
+  }
+}
+
+template <bool SAME>
+__device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
+                                               const TopkOptions& opt, const SegCtx& sc, uint32_t use_guess) {
+  uint32_t (&lh)[kNB0] = lds.lh;
+  uint32_t (&lh1)[kTracked * kNB1] = lds.lh1;
   const uint32_t row = sc.seg;
   TopkRow* rowp = ws.rows + row;
-  if (rowp->fast) return;  // the threshold was found in the band (k_topk_band); same for the whole row
   const uint32_t bg = rowp->b_guess;
   const ListRuns runs = runs_from_cursors(ws, rowp, sc.cursor_set, opt.cap);  // written by the previous launch
   const bool listed = use_guess && rowp->cand_from != 0 && runs.total >= geo.k && runs.fits && !opt.force_dense;
-  for (int b = threadIdx.x; b < kNB0; b += kWG) lh[b] = 0;
-  for (uint32_t b = threadIdx.x; b < kTracked * kNB1; b += kWG) lh1[b] = 0;
+  clear_bins<kNB0>(lh);
+  clear_bins<kTracked * kNB1>(lh1);
   __syncthreads();
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   if (listed) {
@@ -1923,35 +2012,29 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
   }
   __syncthreads();
   uint32_t* gh = ws.hist0 + static_cast<size_t>(row) * kNB0;
-  for (int b = threadIdx.x; b < kNB0; b += kWG) {
-    const uint32_t h = lh[b];
-    if (h) atomicAdd(&gh[b], h);
-  }
+  flush_bins<kNB0>(lh, gh);
   uint32_t* gh1 = ws.hist1x + static_cast<size_t>(row) * kTracked * kNB1;
   if (listed)
-    for (uint32_t b = threadIdx.x; b < kTracked * kNB1; b += kWG) {
-      const uint32_t h = lh1[b];
-      if (h) atomicAdd(&gh1[b], h);
-    }
+    flush_bins<kTracked * kNB1>(lh1, gh1);
   // ---- row-wide part, by whichever workgroup of the row finishes last ----
-  if (!last_group_of_row(&rowp->ticket[0], sc.groups, &sh_flag)) return;
+  if (!last_group_of_row(&rowp->ticket[0], sc.groups, &sh.flag)) return;
   take_hist<kNB0>(gh, lh);
-  find_crossing<kNB0>(lh, geo.k, suf, out2);
+  find_crossing<kNB0>(lh, geo.k, sh.suf, sh.out2);
   if (threadIdx.x == 0) {
-    const uint32_t bstar = out2[0], above = out2[1];
+    const uint32_t bstar = sh.out2[0], above = sh.out2[1];
     const uint32_t total = above + lh[bstar];  // entries with bucket >= bstar
     uint32_t mode, n_src, reads;
     if (listed) { mode = kModeCand; n_src = runs.total; reads = 0; }  // bstar >= bg: the list holds the k largest keys
     else if (total <= opt.cap && !opt.force_dense) { mode = kModeNeedB; n_src = total; reads = 1; }
     else { mode = kModeDense; n_src = 0; reads = 4; }
-    rowp->mode = mode;
+    hand_on<SAME>(&rowp->mode, mode);
     rowp->n_src = n_src;
     // the list's runs for the sweeps that follow: as the first pass left them, or the one run that the second
     // read of the row is about to write; the cursors go back to zero for that read and for the next step
-    rowp->n_lists = listed ? runs.lists : 1u;
+    hand_on<SAME>(&rowp->n_lists, listed ? runs.lists : 1u);
 #pragma unroll
-    for (uint32_t s = 0; s < kSubLists; ++s) rowp->n_sub[s] = listed ? runs.n[s] : (s == 0 ? n_src : 0u);
-    rowp->cursor = 0;
+    for (uint32_t s = 0; s < kSubLists; ++s) hand_on<SAME>(&rowp->n_sub[s], listed ? runs.n[s] : (s == 0 ? n_src : 0u));
+    hand_on<SAME>(&rowp->cursor, 0u);
     rowp->cursor_band = 0;
     if (sc.cursor_set != kNoCursorSet) {
 #pragma unroll
@@ -1961,8 +2044,8 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
         cur[1] = 0;
       }
     }
-    rowp->bstar = bstar;
-    rowp->need = geo.k - above;
+    hand_on<SAME>(&rowp->bstar, bstar);
+    hand_on<SAME>(&rowp->need, geo.k - above);
     rowp->level1_done = 0;
     // Guess for the next step: one bucket below this step's threshold bucket if the list that guess would
     // have produced now fits with room to spare, else the bucket itself, else no guess.  From a list, nothing
@@ -1974,20 +2057,27 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
       if (bstar && total + below <= opt.cap / 2) { valid = 1; guess = bstar - 1; }
       else if (total <= opt.cap / 2) { valid = 1; guess = bstar; }
     }
-    rowp->known_from = listed ? known_from(guess, rowp->cand_from - 1u, runs.total, opt.cap) : 0u;
-    rowp->cand_from = valid ? (guess << kL0Shift) + 1u : 0u;
-    rowp->b_guess = guess;
+    hand_on<SAME>(&rowp->known_from, listed ? known_from(guess, rowp->cand_from - 1u, runs.total, opt.cap) : 0u);
+    hand_on<SAME>(&rowp->cand_from, valid ? (guess << kL0Shift) + 1u : 0u);
+    hand_on<SAME>(&rowp->b_guess, guess);
     uint32_t* cn = ws.counters + row * kCountersPerRow;
     cn[0] = reads;
     cn[1] = n_src;
-    sh_l1 = (listed && bstar - bg < kTracked) ? 1u + (bstar - bg) : 0u;
-    sh_bstar = bstar;
-    sh_need = geo.k - above;
+    sh.l1 = (listed && bstar - bg < kTracked) ? 1u + (bstar - bg) : 0u;
+    sh.bstar = bstar;
+    sh.need = geo.k - above;
   }
   __syncthreads();
   if (listed) {
-    const uint32_t which = sh_l1;  // 0: level 1 not available; 1 + t: histogram of bucket guess + t
-    if (which) {
+    const uint32_t which = sh.l1;  // 0: level 1 not available; 1 + t: histogram of bucket guess + t
+    if (!which && SAME) {  // (rare: the threshold has risen by three buckets) this workgroup sweeps the list for it
+      clear_bins<kNB1>(lh);
+      __syncthreads();
+      sweep_list(ws.cand + sc.cand_base, runs, threadIdx.x, kWG, [&](uint32_t bits) {
+        const uint32_t key = key_of_bits(bits);
+        if ((key >> kL0Shift) == sh.bstar) atomicAdd(&lh[(key >> kL1Shift) & (kNB1 - 1)], 1u);
+      });
+    } else if (which) {
       const AgentView view = agent_view(gh1 + (which - 1) * kNB1, kNB1);
       uint32_t x[kNB1 / kWG];
 #pragma unroll
@@ -1995,33 +2085,29 @@ __global__ __launch_bounds__(kWG) void k_topk_level0(const float* __restrict__ e
 #pragma unroll
       for (int i = 0; i < kNB1 / kWG; ++i) lh[i * kWG + threadIdx.x] = x[i];
     }
-    for (uint32_t b = threadIdx.x; b < kTracked * kNB1; b += kWG) gh1[b] = 0;
+    clear_bins<kTracked * kNB1>(gh1);
     __syncthreads();
-    if (which) resolve_level1(rowp, sh_bstar, sh_need, lh, suf, out2);
+    if (which || SAME) resolve_level1<SAME>(rowp, sh.bstar, sh.need, lh, sh.suf, sh.out2);
   }
+  if (SAME && threadIdx.x == 0) problem_at(rowp, listed ? kPhaseLevel2 : kPhaseLevel1);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 2: level 1 for rows that could not resolve it in the first pass.
+// Level 1 for rows that could not resolve it in the first pass.
 //   kModeNeedB: one more read of the row; writes the candidate list (bucket >= bstar) and the histogram.
 //   kModeCand : the list exists (the threshold bucket was above the tracked ones): sweep it.
 //   kModeDense: no list: histogram from the row itself.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI>
-__global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                      TopkOptions opt) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
-  __shared__ uint32_t lh[kNB1];
-  __shared__ uint2 stage_all[kWaves * kStage];
-  __shared__ uint32_t suf[kWG + 1];
-  __shared__ uint32_t out2[2];
-  __shared__ uint32_t sh_flag;
-  const SegCtx sc = seg_ctx<UNI, kClassSweep>(geo, opt, ws);
+template <bool SAME>
+__device__ __forceinline__ void general_level1(GeneralShared& sh, Level1Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
+                                               const TopkOptions& opt, const SegCtx& sc) {
+  uint32_t (&lh)[kNB1] = lds.lh;
   const uint32_t row = sc.seg;
   TopkRow* rowp = ws.rows + row;
-  if (rowp->fast || rowp->level1_done) return;
-  const uint32_t mode = rowp->mode, bstar = rowp->bstar, need = rowp->need;
-  for (int b = threadIdx.x; b < kNB1; b += kWG) lh[b] = 0;
+  const Handed<SAME> view = handed_row<SAME>(rowp);
+  const uint32_t mode = view.word(kRowWord(offsetof(TopkRow, mode)));
+  const uint32_t bstar = view.word(kRowWord(offsetof(TopkRow, bstar))), need = view.word(kRowWord(offsetof(TopkRow, need)));
+  clear_bins<kNB1>(lh);
   __syncthreads();
   const float* er = e + sc.elem_off;
   uint2* candr = ws.cand + sc.cand_base;
@@ -2032,7 +2118,7 @@ __global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e
   if (mode == kModeNeedB) {
     uint2* descr = ws.desc + sc.chunk_base * ws.desc_parts;
     const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
-    uint2* stage = stage_all + wave * kStage;
+    uint2* stage = lds.stage + wave * kStage;
     const uint32_t stride = sc.groups * kWaves;
     for (uint32_t c = sc.group * kWaves + wave; c < geo.num_chunks; c += stride) {
       const uint32_t base = c * kChunk + lane * 4;
@@ -2053,10 +2139,10 @@ __global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e
         stage_round(stage, cnt, j, bits, flag);
       }
       // fits by construction: the level-0 histogram counted exactly these entries
-      flush_chunk(stage, cnt, er, geo.d, c, bstar, rowp, candr, opt.cap, descr, ws.desc_parts);
+      flush_chunk<SAME>(stage, cnt, er, geo.d, c, bstar, rowp, candr, opt.cap, descr, ws.desc_parts);
     }
   } else if (mode == kModeCand) {
-    const ListRuns runs = runs_of_row(rowp, opt.cap);
+    const ListRuns runs = runs_of_row(view, opt.cap);
     sweep_list(candr, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) { visit(bits, true); });
   } else {
     const uint32_t step = sc.groups * kWG * 4;
@@ -2070,32 +2156,26 @@ __global__ __launch_bounds__(kWG) void k_topk_level1(const float* __restrict__ e
   }
   __syncthreads();
   uint32_t* gh = ws.hist1 + static_cast<size_t>(row) * kNB1;
-  for (int b = threadIdx.x; b < kNB1; b += kWG) {
-    const uint32_t h = lh[b];
-    if (h) atomicAdd(&gh[b], h);
-  }
-  if (!last_group_of_row(&rowp->ticket[1], sc.groups, &sh_flag)) return;
+  flush_bins<kNB1>(lh, gh);
+  if (!last_group_of_row(&rowp->ticket[1], sc.groups, &sh.flag)) return;
   take_hist<kNB1>(gh, lh);
-  resolve_level1(rowp, bstar, need, lh, suf, out2);
+  resolve_level1<SAME>(rowp, bstar, need, lh, sh.suf, sh.out2);
+  if (SAME && threadIdx.x == 0) problem_at(rowp, kPhaseLevel2);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 3: level 2 (last 9 key bits) over the entries that match bits 30..9 of the threshold key.
+// Level 2 (last 9 key bits) over the entries that match bits 30..9 of the threshold key.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI>
-__global__ __launch_bounds__(kWG) void k_topk_level2(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                      TopkOptions opt) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
-  __shared__ uint32_t lh[kNB2];
-  __shared__ uint32_t suf[kWG + 1];
-  __shared__ uint32_t out2[2];
-  __shared__ uint32_t sh_flag;
-  const SegCtx sc = seg_ctx<UNI, kClassSweep>(geo, opt, ws);
+template <bool SAME>
+__device__ __forceinline__ void general_level2(GeneralShared& sh, Level2Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
+                                               const TopkOptions& opt, const SegCtx& sc) {
+  uint32_t (&lh)[kNB2] = lds.lh;
   const uint32_t row = sc.seg;
   TopkRow* rowp = ws.rows + row;
-  if (rowp->fast) return;
-  const uint32_t mode = rowp->mode, want = rowp->prefix1, need = rowp->need;
-  for (int b = threadIdx.x; b < kNB2; b += kWG) lh[b] = 0;
+  const Handed<SAME> view = handed_row<SAME>(rowp);
+  const uint32_t mode = view.word(kRowWord(offsetof(TopkRow, mode)));
+  const uint32_t want = view.word(kRowWord(offsetof(TopkRow, prefix1))), need = view.word(kRowWord(offsetof(TopkRow, need)));
+  clear_bins<kNB2>(lh);
   __syncthreads();
   auto visit = [&](uint32_t bits, bool ok) {
     const uint32_t key = key_of_bits(bits);
@@ -2113,25 +2193,22 @@ __global__ __launch_bounds__(kWG) void k_topk_level2(const float* __restrict__ e
     }
   } else {
     const uint2* candr = ws.cand + sc.cand_base;
-    const ListRuns runs = runs_of_row(rowp, opt.cap);
+    const ListRuns runs = runs_of_row(view, opt.cap);
     sweep_list(candr, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) { visit(bits, true); });
   }
   __syncthreads();
   uint32_t* gh = ws.hist2 + static_cast<size_t>(row) * kNB2;
-  for (int b = threadIdx.x; b < kNB2; b += kWG) {
-    const uint32_t h = lh[b];
-    if (h) atomicAdd(&gh[b], h);
-  }
-  if (!last_group_of_row(&rowp->ticket[2], sc.groups, &sh_flag)) return;
+  flush_bins<kNB2>(lh, gh);
+  if (!last_group_of_row(&rowp->ticket[2], sc.groups, &sh.flag)) return;
   take_hist<kNB2>(gh, lh);
-  find_crossing<kNB2>(lh, need, suf, out2);
+  find_crossing<kNB2>(lh, need, sh.suf, sh.out2);
   if (threadIdx.x == 0) {
-    const uint32_t s = out2[0], above = out2[1];
+    const uint32_t s = sh.out2[0], above = sh.out2[1];
     const uint32_t tau = (want << kL1Shift) | s;
     const uint32_t r = need - above, ties = lh[s];
     const uint32_t tau_prev = rowp->tau, tau_prev2 = rowp->tau_prev;
     rowp->tau_prev = tau_prev;
-    rowp->tau = tau;
+    hand_on<SAME>(&rowp->tau, tau);
     rowp->r = r;
     rowp->ties = ties;
     ws.tau[row] = tau;
@@ -2140,8 +2217,10 @@ __global__ __launch_bounds__(kWG) void k_topk_level2(const float* __restrict__ e
     cn[2] = ties;
     cn[3] = r;
     cn[4] = 0;
-    // the guess was set when the threshold bucket was found (first kernel of this route, an earlier launch)
-    set_next_band(rowp, tau, tau_prev, tau_prev2, rowp->cand_from != 0 ? 1u : 0u, rowp->b_guess, rowp->known_from,
+    if (SAME) problem_at(rowp, kPhaseCount);
+    // the guess was set when the threshold bucket was found
+    set_next_band(rowp, tau, tau_prev, tau_prev2, view.word(kRowWord(offsetof(TopkRow, cand_from))) != 0 ? 1u : 0u,
+                  view.word(kRowWord(offsetof(TopkRow, b_guess))), view.word(kRowWord(offsetof(TopkRow, known_from))),
                   rowp->noise > 0.0f ? rowp->noise : default_band_noise(geo.k), geo.k, opt);
   }
 }
@@ -2204,29 +2283,27 @@ __device__ __forceinline__ void for_each_round(uint32_t mode, const float* __res
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 4: per chunk, how many keys lie above tau and how many equal it.  A workgroup owns a contiguous
+// Counting: per chunk, how many keys lie above tau and how many equal it.  A workgroup owns a contiguous
 // block of geo.count_cpw chunks; it leaves, per chunk, the two counts and their exclusive prefixes within
 // the block, and per block the two totals.  The last kernel turns these into positions in the worker's
 // list (a sum over at most kMaxCountBlocks block totals), so no workgroup waits for or follows another.
 // ---------------------------------------------------------------------------------------------
-template <bool UNI, bool QUARTERS>
-__global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                     TopkOptions opt) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
-  __shared__ uint32_t l_gt[kMaxCountCpw], l_eq[kMaxCountCpw];
-  __shared__ uint32_t scratch[kWG / 64 + 1];
-  const SegCtx sc = seg_ctx<UNI, kClassCount>(geo, opt, ws);
+template <bool QUARTERS, bool SAME>
+__device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
+                                               const TopkOptions& opt, const SegCtx& sc) {
   const uint32_t row = sc.seg;
   const uint32_t cpw = geo.count_cpw;
   const uint32_t start = sc.group * cpw;
   if (start >= geo.num_chunks) return;  // uniform; the grid has exactly the blocks that exist
   const uint32_t end = start + cpw < geo.num_chunks ? start + cpw : geo.num_chunks;
   const TopkRow* rowp = ws.rows + row;
-  if (rowp->fast) return;
-  const uint32_t mode = rowp->mode, tau = rowp->tau;
+  const Handed<SAME> view = handed_row<SAME>(rowp);
+  const uint32_t mode = view.word(kRowWord(offsetof(TopkRow, mode))), tau = view.word(kRowWord(offsetof(TopkRow, tau)));
   const float* er = e + sc.elem_off;
   const uint2* candr = ws.cand + sc.cand_base;
-  const uint2* descr = ws.desc + sc.chunk_base * (QUARTERS ? kWaves : 1);
+  // (a chunk's descriptors may have been written in this launch)
+  constexpr uint32_t kParts = QUARTERS ? kWaves : 1;
+  const Handed<SAME> descr(ws.desc + sc.chunk_base * kParts, 2 * geo.num_chunks * kParts);
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   if (mode == kModeDense) {
     for (uint32_t c = start + wave; c < end; c += kWaves) {
@@ -2238,7 +2315,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
           eq += popc64(ballot64(en.ok[s] && key == tau));
         }
       });
-      if (lane == 0) { l_gt[c - start] = gt; l_eq[c - start] = eq; }
+      if (lane == 0) { lds.gt[c - start] = gt; lds.eq[c - start] = eq; }
     }
   } else if constexpr (QUARTERS) {
     // A wavefront takes eight consecutive chunks at a time, sixteen lanes for every quarter of a chunk: the first 32 entries of
@@ -2251,7 +2328,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
     const uint32_t part = lane / kLanes, sub = lane % kLanes;
     for (uint32_t c0 = start + wave * kGroup; c0 < end; c0 += kWaves * kGroup) {
       uint2 all = make_uint2(0, 0);  // lane l: segment l % 32
-      if (c0 + lane % 32 / kWaves < end) all = descr[c0 * kWaves + lane % 32];
+      if (c0 + lane % 32 / kWaves < end) all = descr.pair(c0 * kWaves + lane % 32);
       if (all.x > opt.cap) all.y = 0;  // segments always lie inside the list; never read outside it
       else if (all.y > opt.cap - all.x) all.y = opt.cap - all.x;
       uint2 ds[kGroup];
@@ -2283,7 +2360,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
 #pragma unroll
           for (uint32_t w = 0; w < kAhead; ++w) add(q0 + w * kLanes + sub < ds[u].y, bits[w]);
         }
-        if (lane == 0 && c0 + u < end) { l_gt[c0 + u - start] = gt; l_eq[c0 + u - start] = eq; }
+        if (lane == 0 && c0 + u < end) { lds.gt[c0 + u - start] = gt; lds.eq[c0 + u - start] = eq; }
       }
     }
   } else {
@@ -2295,7 +2372,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
     const SegmentLanes sl = segment_lanes(end - start < group ? end - start : group, 1u);
     for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
       uint2 ds = make_uint2(0, 0);
-      if (c0 + sl.chunk < end) ds = descr[c0 + sl.chunk];
+      if (c0 + sl.chunk < end) ds = descr.pair(c0 + sl.chunk);
       if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
       else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
       uint32_t gt = 0, eq = 0;  // of this lane's entries
@@ -2316,7 +2393,7 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
       }
       gt = chunk_sum(gt, sl);
       eq = chunk_sum(eq, sl);
-      if (sl.first && c0 + sl.chunk < end) { l_gt[c0 - start + sl.chunk] = gt; l_eq[c0 - start + sl.chunk] = eq; }
+      if (sl.first && c0 + sl.chunk < end) { lds.gt[c0 - start + sl.chunk] = gt; lds.eq[c0 - start + sl.chunk] = eq; }
     }
   }
   __syncthreads();
@@ -2326,19 +2403,121 @@ __global__ __launch_bounds__(kWG) void k_topk_count(const float* __restrict__ e,
   const uint32_t first = threadIdx.x * per;
   uint32_t sum_gt = 0, sum_eq = 0;
   for (uint32_t i = 0; i < per; ++i)
-    if (first + i < len) { sum_gt += l_gt[first + i]; sum_eq += l_eq[first + i]; }
+    if (first + i < len) { sum_gt += lds.gt[first + i]; sum_eq += lds.eq[first + i]; }
   uint32_t tot_gt, tot_eq;
-  uint32_t pre_gt = block_excl_scan<kWG>(sum_gt, scratch, &tot_gt);
-  uint32_t pre_eq = block_excl_scan<kWG>(sum_eq, scratch, &tot_eq);
+  uint32_t pre_gt = block_excl_scan<kWG>(sum_gt, sh.scratch, &tot_gt);
+  uint32_t pre_eq = block_excl_scan<kWG>(sum_eq, sh.scratch, &tot_eq);
   uint4* rec = ws.chunk_rec + sc.chunk_base + start;
   for (uint32_t i = 0; i < per; ++i)
     if (first + i < len) {
-      const uint32_t gt = l_gt[first + i], eq = l_eq[first + i];
+      const uint32_t gt = lds.gt[first + i], eq = lds.eq[first + i];
       rec[first + i] = make_uint4(gt, eq, pre_gt, pre_eq);
       pre_gt += gt;
       pre_eq += eq;
     }
   if (threadIdx.x == 0) ws.blk[static_cast<size_t>(row) * kMaxCountBlocks + sc.group] = make_uint2(tot_gt, tot_eq);
+}
+
+// A part of the general route as a launch of its own.
+template <bool UNI, bool QUARTERS, int PART>
+__global__ __launch_bounds__(kWG) void k_topk_part(const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt,
+                                                   uint32_t use_guess) {
+  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
+  __shared__ GeneralShared sh;
+  __shared__ std::conditional_t<PART == 0, Level0Shared, std::conditional_t<PART == 1, Level1Shared,
+                                std::conditional_t<PART == 2, Level2Shared, CountShared>>> lds;
+  const SegCtx sc = seg_ctx<UNI, PART == 0 ? kClassLevel0 : PART == 3 ? kClassCount : kClassSweep>(geo, opt, ws);
+  const TopkRow* rowp = ws.rows + sc.seg;
+  if (rowp->fast) return;                              // the same for the whole problem
+  if (PART == 1 && rowp->level1_done) return;  // level 0 has resolved it
+  if constexpr (PART == 0) general_level0<false>(sh, lds, e, geo, ws, opt, sc, use_guess);
+  else if constexpr (PART == 1) general_level1<false>(sh, lds, e, geo, ws, opt, sc);
+  else if constexpr (PART == 2) general_level2<false>(sh, lds, e, geo, ws, opt, sc);
+  else general_count<QUARTERS, false>(sh, lds, e, geo, ws, opt, sc);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at once then, where
+// four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 64.7).  The four parts are cut into
+// tasks, all of level 0's first, then all of level 1's and so on, and a workgroup draws its tasks from one queue in that order, a
+// share of a part at a time (at most as many shares as there are workgroups).  A task waits until its problem's part before is
+// done.  The wait always ends: what it waits for was drawn earlier, by workgroups that are running, and a task waits only for parts
+// before its own; level 0 waits for nothing.  So it does not matter how many workgroups run at a time, or in what order they start.
+// What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row); a list that level 1
+// writes is read with ordinary loads, as nobody has looked at it before and no two problems' lists share a cache line.
+// Where it is taken: see general_in_one().
+// ---------------------------------------------------------------------------------------------
+struct GeneralTasks {
+  uint32_t groups[4];  // (a selection per row) workgroups per row, for each part
+  uint32_t total[4];   // tasks of each part
+};
+
+template <bool UNI>
+__global__ __launch_bounds__(kWG, 4) void k_topk_general(const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
+                                                      TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
+  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
+  __shared__ GeneralShared sh;
+  __shared__ union {
+    Level0Shared level0;
+    Level1Shared level1;
+    Level2Shared level2;
+    CountShared count;
+  } lds;
+  __shared__ uint32_t sh_share, sh_phase;
+  // (out of the arguments at once: looked up by a number, each look-up waited for memory)
+  const uint32_t t0 = tasks.total[0], t1 = tasks.total[1], t2 = tasks.total[2], t3 = tasks.total[3];
+  const uint32_t g0 = tasks.groups[0], g1 = tasks.groups[1], g2 = tasks.groups[2], g3 = tasks.groups[3];
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) sh_share = __hip_atomic_fetch_add(ws.flags + kQueueWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    uint32_t share = uniform_u32(sh_share), part = 0, total = t0, groups = g0, shares = t0 < gridDim.x ? t0 : gridDim.x;
+    auto next_part = [&](uint32_t tasks_of, uint32_t groups_of) {
+      if (share < shares) return;
+      share -= shares;
+      ++part;
+      total = tasks_of;
+      groups = groups_of;
+      shares = total < gridDim.x ? total : gridDim.x;
+    };
+    next_part(t1, g1);
+    if (part == 1) next_part(t2, g2);
+    if (part == 2) next_part(t3, g3);
+    if (share >= shares) return;
+    for (uint32_t q = share; q < total; q += shares) {
+      Geometry geo = geo_all;
+      TopkOptions opt = opt_all;
+      SegCtx sc;
+      if constexpr (UNI) {
+        sc = row_ctx(q / groups, q % groups, groups, geo, opt);
+      } else {
+        const WgSlot slot = (part == 0 ? ws.map_level0 : part == 3 ? ws.map_count : ws.map_sweep)[q];
+        const Seg sg = ws.segs[slot.seg];
+        sc = seg_ctx_of(slot.seg, slot.group, part == 0 ? sg.groups_level0 : part == 3 ? sg.count_blocks : sg.groups_sweep, sg, geo, opt);
+      }
+      TopkRow* rowp = ws.rows + sc.seg;
+      // (both written by an earlier launch, the same for the whole problem)
+      if (rowp->fast) continue;                // found by k_topk_band
+      if (part == 1 && rowp->listed) continue;  // resolved by level 0
+      if (part) {
+        if (threadIdx.x == 0) {
+          uint32_t at;
+          while ((at = load_agent(&rowp->phase)) < part) __builtin_amdgcn_s_sleep(2);
+          sh_phase = at;
+        }
+        __syncthreads();
+        if (part == 1 && sh_phase > part) {  // level 0 has resolved it
+          __syncthreads();
+          continue;
+        }
+      }
+      if (part == 0) general_level0<true>(sh, lds.level0, e, geo, ws, opt, sc, use_guess);
+      else if (part == 1) general_level1<true>(sh, lds.level1, e, geo, ws, opt, sc);
+      else if (part == 2) general_level2<true>(sh, lds.level2, e, geo, ws, opt, sc);
+      else general_count<false, true>(sh, lds.count, e, geo, ws, opt, sc);
+      __syncthreads();  // the next task takes the same LDS
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2399,7 +2578,7 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// Kernel 5: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds what is
+// The last kernel: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds what is
 // to be known of worker i of the tile.
 //   Selecting: the wavefronts share out the tile's workers.  Where a worker's entries of the chunk go in its
 //              list follows from the tables (entries above the threshold in earlier chunks, plus the ties taken there:
@@ -2476,7 +2655,7 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
     f.row0 = 0; f.row_stride = 1;
     f.chunk0 = 0; f.chunk_stride = geo.num_chunks;
     f.seloff0 = 0; f.seloff_stride = geo.num_chunks * kWaves + 1;
-    f.cand0 = 0; f.cand_stride = opt.cap;
+    f.cand0 = 0; f.cand_stride = cand_pitch(opt.cap);
     f.list0 = 0; f.list_stride = geo.k;
   } else {
     const WgSlot slot = ws.map_final[blockIdx.x];
@@ -2522,7 +2701,7 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
   const uint32_t c_lo = c * kChunk;                                       // the chunk, in coordinates of the problem
   const uint32_t c_len = f.d_loc - c_lo < kChunk ? f.d_loc - c_lo : kChunk;
   const uint32_t q_lo = c_lo + wave * kPart;                              // this wavefront's part of it
-  if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = 0;  // the general kernels have run
+  if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = ws.flags[kQueueWord] = 0;  // the general kernel has run
   // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
   const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
   if (ROLE != kServerHalf && c == 0 && i_first == 0 && wave == NW - 1)  // (it has workers of its own only from NW on)
@@ -2932,6 +3111,23 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 
 }  // namespace
 
+// Whether the general route is one launch: where a window gives the band kernel its chance, and the step is short enough for three
+// launches to count.  What it saves a step whose rows all keep to their windows is 5 us; a step in which every row misses pays for the
+// queue and the waits, the more the larger it is, and dense sweeps stream better from a full grid.  us a step, four launches / one:
+// windows kept 16 x 1 M 69.6 / 64.7, 4 x 300007 (the call without a workspace) 47.4 / 41.0; every row missing (thresholds that jump
+// tenfold; one magnitude only) 4 x 300000 40.5 / 37.2, 1 x 3 M 59.9 / 58.9, 193 / 201, 16 x 1 M 85.2 / 91.4, 234 / 239, 16 x 4 M 208 /
+// 231, 774 / 817.
+constexpr uint64_t kOneLaunchChunks = 4096;
+static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, uint64_t chunks) {
+  return use_guess && opt.band && chunks <= kOneLaunchChunks;
+}
+static_assert(kOneLaunchChunks < kPagedChunks, "k_topk_general counts chunks of one segment");
+// (16 x 1 M, every row missing, 512 / 768 / 1024: 99.8 / 105.8 / 110.8 us: more of them draw and wait)
+static uint32_t general_workgroups(const GeneralTasks& tasks) {
+  constexpr uint32_t kMost = 512;
+  return std::min(kMost, *std::max_element(tasks.total, tasks.total + 4));
+}
+
 constexpr size_t kClearBytes = 32768;  // a workgroup of the sampling launch clears
 
 hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOptions& options, const AmsParams& ap,
@@ -2940,7 +3136,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
                      Launcher* L) {
   const int role = workers_only ? kWorkerHalf : kWholeStep;
   const uint32_t G = groups_per_row(geo.n, geo.num_chunks);
-  const dim3 grid_rows(G, geo.n), wg(kWG);
+  const dim3 wg(kWG);
   const uint32_t use_guess = first_pass_may_predict || whole ? 1u : 0u;
   const bool paged = ws.desc_parts > 1;
   const dim3 grid_first(paged ? page_groups(geo.num_chunks) : geo.num_chunks, geo.n);
@@ -2974,21 +3170,25 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
-    {
-      // about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
-      // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
-      uint32_t g0 = (512 + geo.n - 1) / geo.n;
-      g0 = g0 > G ? G : g0;
-      launch(L, kSlotLevel0, k_topk_level0<true>, dim3(g0, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+    // level 0 by about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
+    // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
+    const uint32_t g0 = std::min((512 + geo.n - 1) / geo.n, G);
+    GeneralTasks tasks{{g0, G, G, count_blocks}, {}};
+    for (int part = 0; part < 4; ++part) tasks.total[part] = tasks.groups[part] * geo.n;
+    if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * geo.num_chunks)) {
+      launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, e, geo, ws, opt, use_guess, tasks);
+      COMPAMS_CHECK_LAUNCH();
+    } else {
+      launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotLevel2, k_topk_part<true, false, 2>, dim3(G, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotCount, paged ? k_topk_part<true, true, 3> : k_topk_part<true, false, 3>, dim3(count_blocks, geo.n), wg, stream, e, geo,
+             ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
     }
-    COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotLevel1, k_topk_level1<true>, grid_rows, wg, stream, e, geo, ws, opt);
-    COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotLevel2, k_topk_level2<true>, grid_rows, wg, stream, e, geo, ws, opt);
-    COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotCount, paged ? k_topk_count<true, true> : k_topk_count<true, false>, dim3(count_blocks, geo.n), wg, stream, e, geo,
-           ws, opt);
-    COMPAMS_CHECK_LAUNCH();
   }
   const TopkFlat none{};
   if (whole)
@@ -3025,17 +3225,21 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
     launch(L, kSlotBand, k_topk_band<false, false>, dim3(flat.wg_count), wg, stream, geo, ws, opt, use_guess);
     COMPAMS_CHECK_LAUNCH();
   }
-  if (flat.wg_level0) {
-    launch(L, kSlotLevel0, k_topk_level0<false>, dim3(flat.wg_level0), wg, stream, e, geo, ws, opt, use_guess);
-    COMPAMS_CHECK_LAUNCH();
-  }
   if (flat.wg_sweep) {  // none if every block is a micro problem
-    launch(L, kSlotLevel1, k_topk_level1<false>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt);
-    COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotLevel2, k_topk_level2<false>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt);
-    COMPAMS_CHECK_LAUNCH();
-    launch(L, kSlotCount, k_topk_count<false, false>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt);
-    COMPAMS_CHECK_LAUNCH();
+    const GeneralTasks tasks{{}, {flat.wg_level0, flat.wg_sweep, flat.wg_sweep, flat.wg_count}};
+    if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * flat.chunk_stride)) {
+      launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, e, geo, ws, opt, use_guess, tasks);
+      COMPAMS_CHECK_LAUNCH();
+    } else {
+      launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotLevel1, k_topk_part<false, false, 1>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotLevel2, k_topk_part<false, false, 2>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+      launch(L, kSlotCount, k_topk_part<false, false, 3>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt, use_guess);
+      COMPAMS_CHECK_LAUNCH();
+    }
   }
   const float* residuals = e;
   if (workers_only)

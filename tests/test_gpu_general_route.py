@@ -1,0 +1,82 @@
+"""The general route in one launch and in four, on both sides of the line (4096 chunks in all rows): steps in which all, some or none
+of the rows miss their window, with lists and without, whole rows and blocks, bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2205_05632_amd import binding as B
+
+from parity import Pair
+from test_gpu_topk_blocks import BlockPair, make_blocks
+
+pytestmark = pytest.mark.gpu
+CHUNK = 4096
+
+
+def gradients(kind, base, t, n, d):
+    g = np.stack([np.roll(base, 1013 * t + 41 * i) for i in range(n)])
+    if kind == "jump":        # up and down tenfold: lists that overflow, lists with too few entries
+        g *= np.float32(10.0 ** (t % 2))
+    elif kind == "some":      # every third row, by a little: listed, but outside its window, and more than three buckets up
+        g[t % 3::3] *= np.float32(1.0 + 0.3 * (t % 4))
+    elif kind == "levels":    # few magnitudes: the threshold's bucket holds most of the row
+        g = np.round(g * 2) / 2
+    elif kind == "equal":     # one magnitude: no list fits
+        g = np.where(g < 0, np.float32(-1), np.float32(1))
+    return np.ascontiguousarray(g, dtype=np.float32)
+
+
+@pytest.mark.parametrize("kind", ["steady", "jump", "some", "levels", "equal"])
+@pytest.mark.parametrize("n,d,k", [(3, 17 * CHUNK + 1, 700), (2, 64 * CHUNK, 2000), (64, 64 * CHUNK, 2600), (17, 241 * CHUNK, 9000),
+                                   (1, 1000 * CHUNK - 5, 40000)])
+def test_whole_rows(n, d, k, kind):
+    rng = np.random.default_rng(d + n)
+    base = rng.standard_normal(d).astype(np.float32)
+    p = Pair(n, d, rng.standard_normal(d).astype(np.float32), B.TOPK, k=k)
+    steps, missed, counters = 7, 0, None
+    for t in range(steps):
+        p.step(gradients(kind, base, t, n, d), 1e-3, label=f"{kind} {n} x {d} step {t}", with_e=t == steps - 1, check=t % 2 == 0 or n < 10)
+        counters = p.gpu.compams_state("counters").cpu().numpy()
+        missed += int((counters[:, 5] != 0).sum()) if t > 2 else 0
+    p.compare(f"{kind} {n} x {d}")
+    assert missed > 0 or kind in ("steady", "some"), "no row took the general route"
+    assert all(p.exact.values()), p.exact
+    p.close()
+
+
+@pytest.mark.parametrize("kind", ["steady", "jump", "some", "levels"])
+@pytest.mark.parametrize("n,d,blocks", [(3, 70000, 9), (8, 400000, 30), (40, 103 * CHUNK, 6)])
+def test_blocks(n, d, blocks, kind):
+    rng = np.random.default_rng(d)
+    off, kb = make_blocks(d, blocks, rng)
+    base = rng.standard_normal(d).astype(np.float32)
+    p = BlockPair(n, d, off, kb, np.zeros(d, dtype=np.float32))
+    for t in range(6):
+        p.step(gradients(kind, base, t, n, d))
+        if t % 2:
+            p.compare(f"{kind} {n} x {d} step {t}", with_e=t == 5)
+
+
+def test_two_streams_at_a_time():
+    """Two contexts whose rows all miss, on two streams at once: neither's tasks wait for the other's."""
+    n, d, k = 4, 80 * CHUNK, 3000
+    rng = np.random.default_rng(5)
+    base = rng.standard_normal(d).astype(np.float32)
+    theta = rng.standard_normal(d).astype(np.float32)
+    pairs = [Pair(n, d, theta, B.TOPK, k=k) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in pairs]
+    grads = [[torch.zeros((n, p.gpu.ld), device="cuda") for _ in range(2)] for p in pairs]
+    for c, pair_grads in enumerate(grads):
+        for t, g in enumerate(pair_grads):
+            g[:, :d] = torch.from_numpy(gradients("jump", base, t + c, n, d)).cuda()
+    torch.cuda.synchronize()
+    for t in range(8):
+        for p, s, g in zip(pairs, streams, grads):
+            with torch.cuda.stream(s):
+                p.gpu.compams_step(g[t % 2], 1e-3)
+    torch.cuda.synchronize()
+    for c, p in enumerate(pairs):
+        for t in range(8):
+            p.cpu.step(gradients("jump", base, t % 2 + c, n, d), 1e-3)
+        p.compare(f"context {c}")
+        p.close()
