@@ -2,7 +2,10 @@
 
 `python -m paper_2205_05632_amd.build` compiles every source under csrc/ with hipcc and links
 paper_2205_05632_amd/libcompams.so.  Floating-point contraction is off so that every fp32 operation of
-the optimizer update rounds once, and packed-fp32 instruction selection is disabled.
+the optimizer update rounds once, and packed-fp32 instruction selection is disabled.  A kernel's first plain arguments arrive in
+scalar registers (up to the first structure, 14 words), where the first loads of a short kernel would wait for them: the
+kernels of small steps have what those loads need in front (4 x 65536: block-sign 11.8 -> 11.3 us a step, top-k 23.0 -> 22.7), the
+first pass and the last kernel of top-k have the structure in front (16 x 1 M: 65.6 us with the others' order, 65.3 so).
 """
 import os
 import subprocess
@@ -18,6 +21,7 @@ SOURCES = ["compams_api.hip", "compams_topk.hip", "compams_blocksign.hip", "comp
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-warning-option"]
 
 

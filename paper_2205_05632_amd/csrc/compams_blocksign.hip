@@ -540,8 +540,11 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
 // SCALES: the workgroup of a row that finishes last also turns the row's sums into scales (4 rows of 65536, blocks of 4096:
 // 13.9 -> 12.6 us a step; where the line lies: scales_in_first_pass).
 template <bool PEND, bool SCALES, bool PAGED>
-__global__ __launch_bounds__(kWG, 5) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
-                                                  BlocksignWorkspace ws) {
+__global__ __launch_bounds__(kWG, 5) void k_bs_lean(const float* __restrict__ g, float* __restrict__ e, int64_t ld, uint32_t d,
+                                                     uint32_t num_blocks, uint32_t* chunk_block, uint32_t* offsets, float* scales,
+                                                     Geometry geo, BlocksignWorkspace ws) {
+  geo.ld = ld; geo.d = d; geo.num_blocks = num_blocks;
+  ws.chunk_block = chunk_block; ws.offsets = offsets; ws.scales = scales;
   bs_lean_quarter<PEND, PAGED>(blockIdx.x, blockIdx.y, g, e, geo, ws);
   if constexpr (SCALES) {
     __shared__ uint32_t sh_last;
@@ -663,8 +666,10 @@ __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometr
 
 template <int NC>  // how many of theta, m, v, vhat are cached, the others streamed (see the top-k final kernel)
 __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_bs_amsgrad(
-    float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat, Geometry geo,
-    BlocksignWorkspace ws, AmsParams p) {
+    float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat, uint32_t* chunk_block,
+    uint32_t* offsets, uint32_t d_row, uint32_t num_chunks, Geometry geo, BlocksignWorkspace ws, AmsParams p) {
+  geo.d = d_row; geo.num_chunks = num_chunks;
+  ws.chunk_block = chunk_block; ws.offsets = offsets;
   const uint32_t* __restrict__ off = ws.offsets;
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   const uint32_t d = geo.d;
@@ -915,7 +920,8 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
                                              : (scales ? k_bs_lean<false, true, true> : k_bs_lean<false, false, true>))
                          : (residual_pending ? (scales ? k_bs_lean<true, true, false> : k_bs_lean<true, false, false>)
                                              : (scales ? k_bs_lean<false, true, false> : k_bs_lean<false, false, false>));
-  launch_lds(L, kSlotBsPass1, first, grid_chunks, wg, kStreamLds, stream, g, e, geo, ws);
+  launch_lds(L, kSlotBsPass1, first, grid_chunks, wg, kStreamLds, stream, g, e, geo.ld, geo.d, geo.num_blocks, ws.chunk_block,
+             ws.offsets, ws.scales, geo, ws);
   COMPAMS_CHECK_LAUNCH();
   if (!scales) {
     const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
@@ -935,8 +941,8 @@ hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& 
                                  float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const dim3 grid(geo.num_chunks), wg(kBsServerWaves * 64);  // a workgroup per chunk
 #define COMPAMS_BS_AMSGRAD(NC) k_bs_amsgrad<NC>
-  COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, geo, ws,
-                           ap);
+  COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, ws.chunk_block,
+                           ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
 #undef COMPAMS_BS_AMSGRAD
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;

@@ -443,6 +443,8 @@ hipError_t fill_rows_f32(float* p, uint32_t n, int64_t ld, uint32_t d, float val
 hipError_t stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 hipError_t inplace_probe(float* const* arrays, int n_arrays, size_t count, int cached_arrays, hipStream_t stream);
 
+// Kernels of short steps take what their first loads need as leading plain arguments, which arrive in scalar registers; the structures
+// that follow hold the same values.
 // Launch with optional timing: when the slot is being timed, the launch is bracketed by a pair of events on
 // the same stream.  (Events attached to the dispatch itself give the same durations but slow the step down
 // by more than the bracketing does; measured on MI355X.)

@@ -679,7 +679,7 @@ constexpr size_t kLeanLds = 14000;              // asked for on top of that: fiv
 // per chunk of every segment in address order, and at the end the workgroups whose wavefronts take one micro
 // problem each; coordinates below are the segment's own, the lists hold coordinates of the worker's row.
 template <bool PEND, bool UNI, bool PAGED>
-__global__ __launch_bounds__(kWG) void k_topk_lean(const float* __restrict__ g, float* __restrict__ e, Geometry geo,
+__global__ __launch_bounds__(kWG) void k_topk_lean(Geometry geo, const float* __restrict__ g, float* __restrict__ e,
                                                     TopkWorkspace ws, TopkOptions opt, uint32_t use_guess) {
   __shared__ uint2 stage_all[kWaves * kStageQ];
   __shared__ uint32_t bm_all[PEND ? kWaves * 32 : 1];
@@ -1804,8 +1804,11 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
              miss == 0 && normal_key(tau) ? in_window : 0u, tau);
 }
 
-__global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restrict__ e, Geometry geo, TopkWorkspace ws,
-                                                             TopkOptions opt, uint32_t use_guess) {
+__global__ __launch_bounds__(kPickThreads) void k_topk_pick(TopkRow* rows, uint2* cand, const float* __restrict__ e,
+                                                             int64_t ld, uint32_t d, uint32_t k, uint32_t cap, uint32_t num_chunks,
+                                                             uint32_t use_guess, Geometry geo, TopkWorkspace ws, TopkOptions opt) {
+  geo.ld = ld; geo.d = d; geo.k = k; geo.num_chunks = num_chunks; opt.cap = cap;
+  ws.rows = rows; ws.cand = cand;
   __shared__ PickShared sh;
   const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
   const TopkRow* rp = ws.rows + sc.seg;
@@ -1851,7 +1854,9 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(const float* __restr
 constexpr uint32_t kWindowSample = 8;
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __restrict__ g, const float* __restrict__ e,
-                                                               Geometry geo, TopkWorkspace ws, TopkOptions opt) {
+                                                               int64_t ld, uint32_t d, uint32_t n, uint32_t k, uint32_t cap,
+                                                               TopkRow* rows, Geometry geo, TopkWorkspace ws, TopkOptions opt) {
+  geo.ld = ld; geo.d = d; geo.n = n; geo.k = k; opt.cap = cap; ws.rows = rows;
   __shared__ uint32_t lh[kNB0];
   __shared__ uint32_t suf[kPickThreads + 1];
   __shared__ uint32_t out2[6];
@@ -2420,9 +2425,9 @@ __device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& ld
 
 // A part of the general route as a launch of its own.
 template <bool UNI, bool QUARTERS, int PART>
-__global__ __launch_bounds__(kWG) void k_topk_part(const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt,
+__global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt,
                                                    uint32_t use_guess) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
+  if (table_u32(flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
   __shared__ GeneralShared sh;
   __shared__ std::conditional_t<PART == 0, Level0Shared, std::conditional_t<PART == 1, Level1Shared,
                                 std::conditional_t<PART == 2, Level2Shared, CountShared>>> lds;
@@ -2453,9 +2458,9 @@ struct GeneralTasks {
 };
 
 template <bool UNI>
-__global__ __launch_bounds__(kWG, 4) void k_topk_general(const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
+__global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
                                                       TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
-  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
+  if (table_u32(flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
   __shared__ GeneralShared sh;
   __shared__ union {
     Level0Shared level0;
@@ -2682,8 +2687,8 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
 // QUARTERS: a chunk has a segment of the candidate list for every quarter, else one.
 template <int ROLE, bool UNI, int NC, int NW, bool CLEAR, bool QUARTERS>
 __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_final(
-    float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
-    const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
+    Geometry geo, float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat,
+    const float* __restrict__ e, TopkWorkspace ws, TopkOptions opt, AmsParams p, TopkFlat flat) {
   static_assert(UNI || ROLE != kServerHalf, "the server's half works on whole rows");
   static_assert(NW == kWaves || ROLE != kServerHalf, "it knows the offsets of quarters");
   constexpr uint32_t kPart = kChunk / NW;  // coordinates of a wavefront's part of the chunk
@@ -3151,15 +3156,17 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   if (whole && geo.d >= kSample) {
     const size_t bytes = reinterpret_cast<const char*>(ws.chunk_rec) - reinterpret_cast<const char*>(ws.counters);
     const uint32_t clearing = static_cast<uint32_t>(std::min<size_t>((bytes + kClearBytes - 1) / kClearBytes, 256));
-    launch(L, kSlotPick, k_topk_sample, dim3(geo.n + clearing), dim3(kPickThreads), stream, g, e, geo, ws, opt);
+    launch(L, kSlotPick, k_topk_sample, dim3(geo.n + clearing), dim3(kPickThreads), stream, g, e, geo.ld, geo.d, geo.n, geo.k, opt.cap, ws.rows, geo,
+           ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   auto* first = clear_pending ? (paged ? k_topk_lean<true, true, true> : k_topk_lean<true, true, false>)
                               : (paged ? k_topk_lean<false, true, true> : k_topk_lean<false, true, false>);
-  launch_lds(L, kSlotPassA, first, grid_first, wg, lds_first, stream, g, e, geo, ws, opt, use_guess);
+  launch_lds(L, kSlotPassA, first, grid_first, wg, lds_first, stream, geo, g, e, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (pick) {
-    launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, e, geo, ws, opt, use_guess);
+    launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, ws.rows, ws.cand, e, geo.ld, geo.d, geo.k, opt.cap,
+           geo.num_chunks, use_guess, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   } else {
     // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
@@ -3176,33 +3183,33 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
     GeneralTasks tasks{{g0, G, G, count_blocks}, {}};
     for (int part = 0; part < 4; ++part) tasks.total[part] = tasks.groups[part] * geo.n;
     if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * geo.num_chunks)) {
-      launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, e, geo, ws, opt, use_guess, tasks);
+      launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
-      launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel2, k_topk_part<true, false, 2>, dim3(G, geo.n), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel2, k_topk_part<true, false, 2>, dim3(G, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotCount, paged ? k_topk_part<true, true, 3> : k_topk_part<true, false, 3>, dim3(count_blocks, geo.n), wg, stream, e, geo,
+      launch(L, kSlotCount, paged ? k_topk_part<true, true, 3> : k_topk_part<true, false, 3>, dim3(count_blocks, geo.n), wg, stream, ws.flags, e, geo,
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
   }
   const TopkFlat none{};
   if (whole)
-    launch_final<kWholeStep, true, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
+    launch_final<kWholeStep, true, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat, e, ws, opt, ap,
                                          none);
   else if (role == kWorkerHalf && paged)
-    launch_final<kWorkerHalf, true, false, true>(geo, 0, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap, none);
+    launch_final<kWorkerHalf, true, false, true>(geo, 0, L, geo.num_chunks, stream, geo, theta, m, v, vhat, e, ws, opt, ap, none);
   else if (role == kWorkerHalf)
-    launch_final<kWorkerHalf, true, false>(geo, 0, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap, none);
+    launch_final<kWorkerHalf, true, false>(geo, 0, L, geo.num_chunks, stream, geo, theta, m, v, vhat, e, ws, opt, ap, none);
   else if (paged)
-    launch_final<kWholeStep, true, false, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt,
+    launch_final<kWholeStep, true, false, true>(geo, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat, e, ws, opt,
                                                 ap, none);
   else
-    launch_final<kWholeStep, true, false>(geo, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat, e, geo, ws, opt, ap,
+    launch_final<kWholeStep, true, false>(geo, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat, e, ws, opt, ap,
                                           none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
@@ -3217,9 +3224,9 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   const dim3 wg(kWG);
   const uint32_t use_guess = first_pass_may_predict ? 1u : 0u;
   if (clear_pending)
-    launch(L, kSlotPassA, k_topk_lean<true, false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
+    launch(L, kSlotPassA, k_topk_lean<true, false, false>, dim3(flat.wg_first), wg, stream, geo, g, e, ws, opt, use_guess);
   else
-    launch(L, kSlotPassA, k_topk_lean<false, false, false>, dim3(flat.wg_first), wg, stream, g, e, geo, ws, opt, use_guess);
+    launch(L, kSlotPassA, k_topk_lean<false, false, false>, dim3(flat.wg_first), wg, stream, geo, g, e, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (flat.wg_count) {
     launch(L, kSlotBand, k_topk_band<false, false>, dim3(flat.wg_count), wg, stream, geo, ws, opt, use_guess);
@@ -3228,24 +3235,24 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   if (flat.wg_sweep) {  // none if every block is a micro problem
     const GeneralTasks tasks{{}, {flat.wg_level0, flat.wg_sweep, flat.wg_sweep, flat.wg_count}};
     if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * flat.chunk_stride)) {
-      launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, e, geo, ws, opt, use_guess, tasks);
+      launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
-      launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel1, k_topk_part<false, false, 1>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel1, k_topk_part<false, false, 1>, dim3(flat.wg_sweep), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel2, k_topk_part<false, false, 2>, dim3(flat.wg_sweep), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel2, k_topk_part<false, false, 2>, dim3(flat.wg_sweep), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotCount, k_topk_part<false, false, 3>, dim3(flat.wg_count), wg, stream, e, geo, ws, opt, use_guess);
+      launch(L, kSlotCount, k_topk_part<false, false, 3>, dim3(flat.wg_count), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
   }
   const float* residuals = e;
   if (workers_only)
-    launch_final<kWorkerHalf, false, false>(geo, 0, L, flat.wg_final, stream, theta, m, v, vhat, residuals, geo, ws, opt, ap, flat);
+    launch_final<kWorkerHalf, false, false>(geo, 0, L, flat.wg_final, stream, geo, theta, m, v, vhat, residuals, ws, opt, ap, flat);
   else
-    launch_final<kWholeStep, false, false>(geo, ap.cached_arrays, L, flat.wg_final, stream, theta, m, v, vhat, residuals, geo, ws,
+    launch_final<kWholeStep, false, false>(geo, ap.cached_arrays, L, flat.wg_final, stream, geo, theta, m, v, vhat, residuals, ws,
                                            opt, ap, flat);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
@@ -3257,8 +3264,7 @@ hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const 
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
   const TopkFlat none{};
-  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, theta, m, v, vhat,
-                                                               no_e, geo, ws, opt, ap, none);
+  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat, no_e, ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }
