@@ -256,12 +256,13 @@ struct LaneGaps {
   uint32_t gap[4];
   uint32_t n;
 };
+// start: where the tile starts in the stream.
 __device__ __forceinline__ LaneGaps lane_gaps(const uint32_t* __restrict__ msg, uint32_t k, uint32_t tiles, uint32_t t,
-                                              const uint32_t* __restrict__ tile_off_row) {
+                                              uint32_t start) {
   const uint32_t lane = lane_id();
   const uint32_t cnt = tile_count(k, t);
   const uint32_t b = clamp_width(width_byte(msg, t));
-  const uint32_t* tile = msg + 3 + ((tiles + 3u) >> 2) + tile_off_row[t];
+  const uint32_t* tile = msg + 3 + ((tiles + 3u) >> 2) + start;
   const uint32_t nw = tile_words(cnt, b);
   LaneGaps g;
   g.n = 0;
@@ -292,12 +293,74 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_sums(const uint32_t* __restri
   const uint32_t t = blockIdx.x * kWaves + wave;
   if (t >= tiles) return;  // wave-uniform; no barrier below
   const uint32_t* msg = messages + static_cast<int64_t>(row) * stride;
-  const LaneGaps g = lane_gaps(msg, k, tiles, t, tile_off + static_cast<size_t>(row) * tiles);
+  const LaneGaps g = lane_gaps(msg, k, tiles, t, tile_off[static_cast<size_t>(row) * tiles + t]);
   uint32_t sum = g.n;
 #pragma unroll
   for (int s = 0; s < 4; ++s) sum += g.gap[s];
   sum = wave_total(sum);
   if (lane_id() == 0) tile_sum[static_cast<size_t>(row) * tiles + t] = sum;
+}
+
+// Both at once for rows of up to kDirectTiles tiles: every workgroup goes through the row's widths itself, four of them (a word) to a
+// thread, for what lies before its own four tiles; the first one leaves status and total.  What it saves is a launch of one
+// workgroup per row (a step in two halves, us, with that launch / so: 16 x 1 M, k = 10000 89.4 / 88.0; 16 x 11181642, k = 111816
+// 485.6 / 483.5; 64 x 1 M 208.8 / 207.6; 8 x 25 M, k = 262144, 1024 tiles, 620.4 / 617.6).
+__global__ __launch_bounds__(kWG) void k_wire_measure_topk(const uint32_t* __restrict__ messages, int64_t stride, uint32_t k,
+                                                            uint32_t tiles, uint32_t* __restrict__ tile_off,
+                                                            uint32_t* __restrict__ totals, uint32_t* __restrict__ status,
+                                                            uint32_t* __restrict__ tile_sum) {
+  static_assert(kDirectTiles <= 4 * kWG && kWaves == 4, "a word of widths to a thread, and to a workgroup's tiles");
+  __shared__ uint32_t part[3][kWaves];
+  const uint32_t row = blockIdx.y, wave = threadIdx.x >> 6, word = threadIdx.x;
+  const uint32_t* msg = messages + static_cast<int64_t>(row) * stride;
+  // words of a tile, and whether its width is one
+  auto tile = [&](uint32_t widths, uint32_t t, bool& bad) {
+    const uint32_t b = (widths >> (8u * (t & 3u))) & 0xffu;
+    bad |= t < tiles && (b < 1u || b > 31u);
+    return t < tiles ? tile_words(tile_count(k, t), clamp_width(b)) : 0u;
+  };
+  uint32_t total = 0;
+  bool bad = false;
+  if (4 * word < tiles) {
+    const uint32_t widths = msg[3 + word];
+#pragma unroll
+    for (uint32_t s = 0; s < 4; ++s) total += tile(widths, 4 * word + s, bad);
+  }
+  uint32_t before = word < blockIdx.x ? total : 0u;
+  before = wave_total(before);
+  total = wave_total(total);
+  const bool wave_bad = ballot64(bad) != 0;
+  if (lane_id() == 0) {
+    part[0][wave] = before;
+    part[1][wave] = total;
+    part[2][wave] = wave_bad ? 1u : 0u;
+  }
+  __syncthreads();
+  before = total = 0;
+  uint32_t any = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    before += part[0][w];
+    total += part[1][w];
+    any |= part[2][w];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    status[row] = any | (msg[0] != 1u || msg[1] != k || msg[2] != kWireTile ? 1u : 0u);
+    totals[row] = total;
+  }
+  const uint32_t t = blockIdx.x * kWaves + wave;
+  if (t >= tiles) return;  // wave-uniform; no barrier below
+  const uint32_t widths = msg[3 + blockIdx.x];
+  for (uint32_t s = 0; s < wave; ++s) before += tile(widths, blockIdx.x * kWaves + s, bad);
+  const LaneGaps g = lane_gaps(msg, k, tiles, t, before);
+  uint32_t sum = g.n;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) sum += g.gap[s];
+  sum = wave_total(sum);
+  if (lane_id() == 0) {
+    tile_off[static_cast<size_t>(row) * tiles + t] = before;
+    tile_sum[static_cast<size_t>(row) * tiles + t] = sum;
+  }
 }
 
 // DIRECT: tile_sum holds the coordinates each tile covers, not yet summed.  quarter_off (OFFSETS): where the slice of
@@ -327,7 +390,7 @@ __global__ __launch_bounds__(kWG) void k_wire_unpack_topk(const uint32_t* __rest
   if constexpr (DIRECT) tile_before = tile_sums_direct(tile_sum + static_cast<size_t>(row) * tiles, tiles, blockIdx.x * kWaves).before;
   else tile_before = t < tiles ? tile_sum[static_cast<size_t>(row) * tiles + t] : 0u;
   if (t < tiles) {  // wave-uniform
-    const LaneGaps g = lane_gaps(msg, k, tiles, t, tile_off + static_cast<size_t>(row) * tiles);
+    const LaneGaps g = lane_gaps(msg, k, tiles, t, tile_off[static_cast<size_t>(row) * tiles + t]);
     uint32_t mine = g.n;
 #pragma unroll
     for (int s = 0; s < 4; ++s) mine += g.gap[s];
@@ -465,14 +528,18 @@ hipError_t wire_decode_topk(const Geometry& geo, const TopkWorkspace& ws, const 
   const uint32_t tiles = (geo.k + kWireTile - 1) / kWireTile;
   const dim3 grid((tiles + kWaves - 1) / kWaves, geo.n), wg(kWG);
   uint32_t* none = nullptr;
-  launch(L, kSlotWireDecode, k_wire_check_topk, dim3(geo.n), wg, stream, messages, stride, geo.k, tiles,
-         ws.wire_tile_off, ws.wire_total, status);
-  COMPAMS_CHECK_LAUNCH();
-  launch(L, kSlotWireDecode, k_wire_tile_sums, grid, wg, stream, messages, stride, geo.k, tiles, ws.wire_tile_off,
-         ws.wire_tile_sum);
-  COMPAMS_CHECK_LAUNCH();
   const bool direct = tiles <= kDirectTiles;
-  if (!direct) {
+  if (direct) {
+    launch(L, kSlotWireDecode, k_wire_measure_topk, grid, wg, stream, messages, stride, geo.k, tiles, ws.wire_tile_off, ws.wire_total,
+           status, ws.wire_tile_sum);
+    COMPAMS_CHECK_LAUNCH();
+  } else {
+    launch(L, kSlotWireDecode, k_wire_check_topk, dim3(geo.n), wg, stream, messages, stride, geo.k, tiles,
+           ws.wire_tile_off, ws.wire_total, status);
+    COMPAMS_CHECK_LAUNCH();
+    launch(L, kSlotWireDecode, k_wire_tile_sums, grid, wg, stream, messages, stride, geo.k, tiles, ws.wire_tile_off,
+           ws.wire_tile_sum);
+    COMPAMS_CHECK_LAUNCH();
     launch(L, kSlotWireDecode, k_wire_tile_scan, dim3(geo.n), wg, stream, ws.wire_tile_sum, tiles, none);
     COMPAMS_CHECK_LAUNCH();
   }

@@ -157,3 +157,25 @@ def test_tile_sums_with_and_without_a_launch_of_their_own(k):
         assert torch.equal(getattr(a, s), getattr(b, s)), s
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("k", [700, 256 * 300, 256 * 1024, 256 * 1024 + 300])
+@pytest.mark.parametrize("width", [0, 32, 255])
+def test_a_malformed_width_anywhere_is_flagged(k, width):
+    """Up to 1024 tiles every workgroup goes through all of a row's widths, beyond that one does."""
+    n, d, tiles = 3, 600_000, (k + 255) // 256
+    rng = np.random.default_rng(k)
+    c = B.Compams(n, d, torch.zeros(d), compressor=B.TOPK, k=k)
+    g = torch.zeros((n, c.ld))
+    g[:, :d] = torch.from_numpy(rng.standard_normal((n, d)).astype(np.float32))
+    c.compams_step(g.to(c.device), 1e-3)
+    messages, words = c.compams_encode()
+    for t in sorted({0, 1, 2, min(4, tiles - 1), tiles // 2, tiles - 1}):
+        bad = messages.clone()
+        bad.view(torch.uint8).view(n, -1)[1, 4 * 3 + t] = width
+        idx, val, status = c.compams_decode(bad, words)
+        torch.cuda.synchronize()
+        st = status.cpu().numpy()
+        assert st[0] == 0 and st[1] & 1 and st[2] == 0, (t, st)
+        assert torch.equal(idx[::2], c.compams_state("last_idx")[::2]) and torch.equal(val[::2], c.compams_state("last_val")[::2])
+    c.close()
