@@ -588,12 +588,17 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
       cb.resize(lay.num_chunks);
     } catch (...) { free_ctx(ctx); return COMPAMS_HIP_ERROR; }
     for (int64_t i = 0; i <= cfg->num_blocks; ++i) off32[static_cast<size_t>(i)] = static_cast<uint32_t>(cfg->block_offsets[i]);
-    uint32_t blk = 0;
+    uint32_t blk = 0, most = 0;
+    bool inside = true;  // every chunk begins with a block
     for (uint32_t c = 0; c < lay.num_chunks; ++c) {
       const uint32_t j = c * static_cast<uint32_t>(kChunk);
       while (off32[blk + 1] <= j) ++blk;
       cb[c] = blk;
+      inside = inside && off32[blk] == j;
+      if (c) most = std::max(most, blk - cb[c - 1]);
     }
+    most = std::max(most, static_cast<uint32_t>(cfg->num_blocks) - blk);
+    b.chunk_blocks = inside ? most : 0u;
     ok(fill_u32(reinterpret_cast<uint32_t*>(w), lay.total / 4, 0u, s0));
     ok(hipStreamSynchronize(s0));
     ok(hipMemcpy(b.offsets, off32.data(), off32.size() * 4, hipMemcpyHostToDevice));

@@ -11,8 +11,8 @@
 // the result unique.  Inside a lane the additions run in fp64 over windows of exponents narrow enough that
 // no addition rounds.  The sum is rounded once to double, divided by d_B in double and rounded to fp32.
 //
-// Pass 1 forms x (stored in place of e), its sign words and the sums, a small kernel turns sums into
-// scales, and the server kernel adds the n workers' +-mu in worker order before the AMSGrad update.  The
+// Pass 1 forms x (stored in place of e), its sign words and the sums, a small kernel (or the last workgroup of a short row, or
+// the server kernel where no block reaches beyond a chunk) turns sums into scales, and the server kernel adds the n workers' +-mu in worker order before the AMSGrad update.  The
 // residual e = x - sign(x) * mu is applied by the next step's pass 1 as it reads e (or by the stand-alone
 // residual kernel when e is asked for).
 
@@ -617,15 +617,28 @@ constexpr int kBsWorkers = 8;  // workers whose sign words and scales are reques
 // Wavefronts per chunk: a wavefront takes two rounds and asks for everything it needs at once.  (Four rounds, the next one's
 // state requested while one is updated: 16 x 11.2 M 68 -> 75 us, 8 x 25.6 M 145 -> 151, 8 x 60 M 334 -> 336, 8 x 124.4 M 690 -> 686.)
 constexpr int kBsServerWaves = 8;
+constexpr uint32_t kBsServerScales = kBsServerWaves * 64;  // scales that a workgroup's threads form at most
+
+// Whether the server kernel of a whole step forms them: wherever every block lies inside one chunk, which is then the only one to look
+// at its digits, and there is a thread for every worker and block.  It saves the launch of k_bs_finalize, or the chain of the row's
+// last workgroup in the first pass, and costs a workgroup one thread's conversion of a sum.  Measured (us a step, scales in the first
+// pass or by a launch / in the server kernel; rows x chunks / block): 4 x 1 / 4096 9.7 / 9.3, 4 x 16 / 4096 10.8 / 10.8, 4 x 16 / 256
+// 16.0 / 14.3, 8 x 64 / 4096 15.3 / 13.8, 64 x 64 / 4096 52.3 / 50.0, 16 x 256 / 4096 47.4 / 45.7, 16 x 1024 / 4096 152.0 / 152.0, / 256
+// 188.1 / 182.8, 8 x 6000 / 4096 498.5 / 494.3, / 256 579 / 563.  (Held to seven wavefronts per SIMD, as the kernel without them, it
+// spilled nine registers: 4 x 16 / 4096 11.6, 16 x 1024 / 4096 156, 8 x 6000 / 4096 504.)
+inline bool scales_in_server(const Geometry& geo, const BlocksignWorkspace& ws) {
+  return ws.chunk_blocks && static_cast<uint64_t>(geo.n) * ws.chunk_blocks <= kBsServerScales;
+}
 
 // Sums of a share of KQ rounds that lies inside block b and inside the row: sum[r][s] for the lane's four
 // coordinates of round r.  A worker's sign words of the share are KQ * 8 consecutive words, which a group of
 // lanes requests once, several workers per load; a round then takes its word out of the holder's register.
 // (Asked for round by round, 32 bytes at a time with the state's traffic in between, the lines were fetched
 // 3.4 times over.)  One scale per worker serves all rounds.  Worker order, as everywhere.
-template <int KQ>
+// scale(i): worker i's scale of the block.
+template <int KQ, typename Scale>
 __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometry& geo, const BlocksignWorkspace& ws,
-                                              uint32_t b, uint32_t q0, uint32_t lane) {
+                                              uint32_t q0, uint32_t lane, Scale&& scale) {
   constexpr int kShareWords = KQ * 8;           // sign words of one worker for the share
   constexpr int kPerLoad = 64 / kShareWords;    // workers whose words one load of the wavefront brings in
   constexpr int kTrip = 16;                     // workers per trip: kTrip / kPerLoad loads, kTrip scales
@@ -646,7 +659,7 @@ __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometr
     float mu[kTrip];
 #pragma unroll
     for (int u = 0; u < kTrip; ++u)
-      mu[u] = i0 + u < geo.n ? table_f32(ws.scales + static_cast<size_t>(i0 + u) * geo.num_blocks, b) : 0.0f;
+      mu[u] = i0 + u < geo.n ? scale(i0 + u) : 0.0f;
 #pragma unroll
     for (int u = 0; u < kTrip; ++u) {
       if (i0 + u < geo.n) {  // wave-uniform
@@ -664,8 +677,11 @@ __device__ __forceinline__ void bs_share_sums(float (&sum)[KQ][4], const Geometr
   }
 }
 
-template <int NC>  // how many of theta, m, v, vhat are cached, the others streamed (see the top-k final kernel)
-__global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_bs_amsgrad(
+// NC: how many of theta, m, v, vhat are cached, the others streamed (see the top-k final kernel).
+// SCALES: every block lies inside one chunk, and the workgroup forms its chunk's scales from the first pass's digits, a
+// thread per worker and block, while its state travels; see scales_in_server().
+template <int NC, bool SCALES>
+__global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_per_eu(SCALES ? 5 : 7, 8))) void k_bs_amsgrad(
     float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v, float* __restrict__ vhat, uint32_t* chunk_block,
     uint32_t* offsets, uint32_t d_row, uint32_t num_chunks, Geometry geo, BlocksignWorkspace ws, AmsParams p) {
   geo.d = d_row; geo.num_chunks = num_chunks;
@@ -678,6 +694,33 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
   const uint32_t c = blockIdx.x, part = wave;
   if (c >= geo.num_chunks) return;
   uint32_t b = table_u32(ws.chunk_block, c);
+  __shared__ float mus[SCALES ? kBsServerScales : 1];
+  const uint32_t b_first = b;
+  uint32_t nb = 1;  // (SCALES) blocks of the chunk
+  if constexpr (SCALES) {
+    nb = (c + 1 < geo.num_chunks ? table_u32(ws.chunk_block, c + 1) : geo.num_blocks) - b;
+    const uint32_t t = threadIdx.x;
+    if (t < geo.n * nb) {
+      const uint32_t bb = b + t % nb;
+      const size_t at = static_cast<size_t>(t / nb) * geo.num_blocks + bb;
+      uint64_t* dg = ws.acc + at * kLimbs;
+      uint64_t word[kLimbs];
+#pragma unroll
+      for (int i = 0; i < kLimbs; ++i) word[i] = dg[i];
+      const uint32_t sp = ws.special[at];
+      const float mu = block_scale(word, sp, static_cast<double>(off[bb + 1] - off[bb]));
+      mus[t] = mu;
+      ws.scales[at] = mu;
+#pragma unroll
+      for (int i = 0; i < kLimbs; ++i) dg[i] = 0;  // for the next step (nobody else looks at them)
+      ws.special[at] = 0;
+    }
+    __syncthreads();
+  }
+  auto scale = [&](uint32_t i, uint32_t block) {
+    if constexpr (SCALES) return mus[i * nb + (block - b_first)];
+    else return table_f32(ws.scales + static_cast<size_t>(i) * geo.num_blocks, block);
+  };
   constexpr int kQ = kRounds / kBsServerWaves;  // rounds of a wavefront's share of the chunk
   const uint32_t q0 = c * kChunk + part * (kQ * 256);
   if (q0 >= d) return;
@@ -692,7 +735,7 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
       th[r] = load_state4<(NC > 0)>(theta + q0 + r * 256, lane * 4); mm[r] = load_state4<(NC > 1)>(m + q0 + r * 256, lane * 4);
       vv[r] = load_state4<(NC > 2)>(v + q0 + r * 256, lane * 4); vh[r] = load_state4<(NC > 3)>(vhat + q0 + r * 256, lane * 4);
     }
-    bs_share_sums<kQ>(sum, geo, ws, b, q0, lane);
+    bs_share_sums<kQ>(sum, geo, ws, q0, lane, [&](uint32_t i) { return scale(i, b); });
 #pragma unroll
     for (int r = 0; r < kQ; ++r) {
       const uint32_t jr = q0 + r * 256;
@@ -741,7 +784,7 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
           mu[u] = 0.0f;
           if (i < geo.n) {
             if (ok[0]) word[u] = ws.bits[static_cast<size_t>(i) * geo.words + widx];
-            mu[u] = table_f32(ws.scales + static_cast<size_t>(i) * geo.num_blocks, b);
+            mu[u] = scale(i, b);
           }
         }
 #pragma unroll
@@ -756,11 +799,10 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
     } else {
       for (uint32_t i = 0; i < geo.n; ++i) {
         const uint32_t word = ok[0] ? ws.bits[static_cast<size_t>(i) * geo.words + widx] : 0u;
-        const float* mur = ws.scales + static_cast<size_t>(i) * geo.num_blocks;
         const uint32_t nib = (word >> sh) & 15u;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const float mu = mur[bb[s]];
+          const float mu = SCALES ? scale(i, bb[s]) : ws.scales[static_cast<size_t>(i) * geo.num_blocks + bb[s]];
           sum[s] = sum[s] + (((nib >> s) & 1u) ? -mu : mu);
         }
       }
@@ -911,11 +953,31 @@ __global__ __launch_bounds__(kWG) void k_inplace_probe(float* a0, float* a1, flo
     if (err__ != hipSuccess) return err__;        \
   } while (0)
 
+// The server kernel; scales: that forms the scales as well.
+static hipError_t server_lines(bool scales, const Geometry& geo, const BlocksignWorkspace& ws, const AmsParams& ap, float* theta,
+                                 float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
+  const dim3 grid(geo.num_chunks), wg(kBsServerWaves * 64);  // a workgroup per chunk
+#define COMPAMS_BS_AMSGRAD(NC) k_bs_amsgrad<NC, false>
+#define COMPAMS_BS_AMSGRAD_SCALES(NC) k_bs_amsgrad<NC, true>
+  if (scales) {
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD_SCALES, grid, wg, stream, theta, m, v, vhat, ws.chunk_block,
+                             ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
+  } else {
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, ws.chunk_block, ws.offsets,
+                             geo.d, geo.num_chunks, geo, ws, ap);
+  }
+#undef COMPAMS_BS_AMSGRAD
+#undef COMPAMS_BS_AMSGRAD_SCALES
+  COMPAMS_CHECK_LAUNCH();
+  return hipSuccess;
+}
+
 hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, const AmsParams& ap, const float* g,
                           float* e, float* theta, float* m, float* v, float* vhat, bool residual_pending,
                           bool workers_only, hipStream_t stream, Launcher* L) {
   const dim3 grid_chunks(ws.paged ? page_groups(geo.num_chunks) : geo.num_chunks, geo.n), wg(kWG);
-  const bool scales = scales_in_first_pass(geo, ws);
+  const bool in_server = !workers_only && scales_in_server(geo, ws);
+  const bool scales = !in_server && scales_in_first_pass(geo, ws);
   auto* first = ws.paged ? (residual_pending ? (scales ? k_bs_lean<true, true, true> : k_bs_lean<true, false, true>)
                                              : (scales ? k_bs_lean<false, true, true> : k_bs_lean<false, false, true>))
                          : (residual_pending ? (scales ? k_bs_lean<true, true, false> : k_bs_lean<true, false, false>)
@@ -923,7 +985,7 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
   launch_lds(L, kSlotBsPass1, first, grid_chunks, wg, kStreamLds, stream, g, e, geo.ld, geo.d, geo.num_blocks, ws.chunk_block,
              ws.offsets, ws.scales, geo, ws);
   COMPAMS_CHECK_LAUNCH();
-  if (!scales) {
+  if (!scales && !in_server) {
     const size_t total = static_cast<size_t>(geo.n) * geo.num_blocks;
     const size_t per_group = ws.acc_replicas == 1 ? kWG : kWaves;  // (row, block) pairs per workgroup
     launch(L, kSlotBsFinal, k_bs_finalize, dim3(static_cast<uint32_t>((total + per_group - 1) / per_group)), wg, stream,
@@ -933,19 +995,13 @@ hipError_t blocksign_step(const Geometry& geo, const BlocksignWorkspace& ws, con
   // The residual e = x - sign(x) * mu is left to the next step's first pass (or to blocksign_apply_residual when
   // e is asked for).
   if (workers_only) return hipSuccess;
-  return blocksign_server_step(geo, ws, ap, theta, m, v, vhat, stream, L);
+  return server_lines(in_server, geo, ws, ap, theta, m, v, vhat, stream, L);
 }
 
 // The server's lines from the sign words and scales that sit in the workspace.
 hipError_t blocksign_server_step(const Geometry& geo, const BlocksignWorkspace& ws, const AmsParams& ap, float* theta,
                                  float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
-  const dim3 grid(geo.num_chunks), wg(kBsServerWaves * 64);  // a workgroup per chunk
-#define COMPAMS_BS_AMSGRAD(NC) k_bs_amsgrad<NC>
-  COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, ws.chunk_block,
-                           ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
-#undef COMPAMS_BS_AMSGRAD
-  COMPAMS_CHECK_LAUNCH();
-  return hipSuccess;
+  return server_lines(false, geo, ws, ap, theta, m, v, vhat, stream, L);
 }
 
 hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspace& ws, float* e, hipStream_t stream) {

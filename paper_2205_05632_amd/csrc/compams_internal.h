@@ -326,6 +326,7 @@ struct BlocksignWorkspace {
   uint32_t* ticket;     // n : "last workgroup of the row" counters of the first pass; zero between launches
   float* scales;        // n * M
   uint32_t* bits;       // n * words
+  uint32_t chunk_blocks;  // where every block lies inside one chunk: the most that a chunk has, else 0
 };
 constexpr int kLimbs = 10;  // 10 digits of 32 bits cover 2^-149 .. 2^171
 
