@@ -185,7 +185,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     L.desc2 = take(context || measure || L.band_alloc ? n * nc * L.desc_parts * 8 : 0);
     L.bnd = take(n * kBoundaryCap * 8);
     L.bnd_sel = take(n * kBoundaryCap * 4);
-    L.cand = take(n * (measure ? cap : cand_pitch(L.cap_alloc)) * 8);
+    L.cand = take(n * (measure ? cap : row_cand_pitch(L.cap_alloc, L.num_chunks)) * 8);
     L.band = take(n * (measure ? std::min<size_t>({k + 4096, kBandMaxEntries, cap}) : static_cast<size_t>(L.band_alloc)) * 8);
     L.idx = take(n * k * 4);
     L.val = take(n * k * 4);

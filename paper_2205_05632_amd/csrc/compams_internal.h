@@ -200,8 +200,13 @@ struct TopkRow {
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
 
-// Entries from one problem's candidate list to the next one's: whole cache lines.
+// Entries from one problem's candidate list to the next one's: whole cache lines, where the general route may be one launch (blocks;
+// rows of more chunks than k_topk_pick takes).
+constexpr uint32_t kPickChunks = 16;
 __host__ __device__ __forceinline__ uint64_t cand_pitch(uint32_t cap) { return (static_cast<uint64_t>(cap) + 15) / 16 * 16; }
+__host__ __device__ __forceinline__ uint64_t row_cand_pitch(uint32_t cap, uint32_t num_chunks) {
+  return num_chunks > kPickChunks ? cand_pitch(cap) : cap;
+}
 
 // Bucket of a key inside a band of `span` keys starting at lo: floor(rel * buckets / span) for rel = key - lo,
 // computed as the high word of rel * mul with mul = floor(2^32 * buckets / span); a band of at most `buckets`

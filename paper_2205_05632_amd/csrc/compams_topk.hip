@@ -509,7 +509,7 @@ __device__ __forceinline__ SegCtx row_ctx(uint32_t seg, uint32_t group, uint32_t
   c.coord_base = 0;
   c.chunk_base = static_cast<size_t>(c.seg) * geo.num_chunks;
   c.seloff_base = static_cast<size_t>(c.seg) * (geo.num_chunks * kWaves + 1);
-  c.cand_base = static_cast<size_t>(c.seg) * cand_pitch(opt.cap);
+  c.cand_base = static_cast<size_t>(c.seg) * row_cand_pitch(opt.cap, geo.num_chunks);
   c.list_base = static_cast<size_t>(c.seg) * geo.k;
   c.band_base = static_cast<size_t>(c.seg) * opt.band_cap;
   c.bhist_base = static_cast<size_t>(c.seg) * band_buckets(geo.k);
@@ -661,7 +661,7 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 // none: x = e + g (pending zeros honoured) is stored, and when the row carries a guess for the threshold bucket
 // the entries at or above it are staged per wavefront in coordinate order, the chunk's segment of the candidate
 // list is allocated with one atomic for the whole workgroup, and the four quarters are written behind one
-// another.  The level-0 histogram is taken afterwards, from the candidate list (k_topk_level0).
+// another.  The level-0 histogram is taken afterwards, from the candidate list (general_level0).
 // In large problems (paged_first_pass) the workgroup takes the same page of four spans instead, a quarter of four different
 // chunks (page_quarter): one allocation still, but a segment of the lists for every quarter.  Which page a die takes changes
 // seven times over the rows: a crowded page (a matrix as wide as the span or a multiple, its large columns side by side) takes
@@ -1512,7 +1512,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 // counted as on the band route.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPickThreads = 1024;
-constexpr uint32_t kPickChunks = 16;
 constexpr int kPickBins = 2048;
 constexpr uint32_t kPickQuad = 4;    // elements of a thread per trip
 constexpr uint32_t kPickRank = 256;  // (ranked by comparing all with all: a thousand of them take 27 us, one more sweep less)
@@ -1839,16 +1838,16 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(TopkRow* rows, uint2
 // whose list would not fit by what the sample holds from that bucket upwards (few magnitudes; three of 4096 are more than
 // 65536 entries from 90 M coordinates on) gets no guess: the list would be written and counted for nothing.  It decides only
 // whether the row is read again.  (Eight entries instead of three, and no look at what fits: 34 M coordinates, k = 1000, 362
-// us a call, now 338; 60 M, k = 100000, 580, now 523.)  
+// us a call, now 338; 60 M, k = 100000, 580, now 523.)
 // ---------------------------------------------------------------------------------------------
 // The same sample gives the window of keys in which the threshold is expected, where the first pass is to keep band lists: from the
 // bucket above which the expected count plus three deviations lies to the one above which the expected count less three
 // deviations does, if the band list would hold what the sample says lies in it.  The band kernel then selects, as in a step that
 // carries its window over, and the four general ones (30 us of the call for 4 x 300007, k = 3000) return at once.  Fewer than
 // kWindowSample of the sample's entries above the threshold say too little: the window is two octaves wide and more, its entries'
-// lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (us a call, 24 drawn shapes each,
-// without a window / from 8 entries on / always, geometric means of the gain: 1.04, 1.06, 1.05; always: 4 x 1634958, k = 2524,
-// 70.9 -> 74.0; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 -> 43.9.)
+// lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (Two sets of 24 drawn shapes, times
+// faster than without a window, in the mean: from 8 entries on 1.06 and 1.06, from 16 on 1.05 and 1.04, always 1.05; always: 4 x
+// 1634958, k = 2524, 70.9 -> 74.0 us; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 -> 43.9.)
 // The launch also clears the tables that the call expects at zero, which took a launch of its own, 2 us: a workgroup its row's control block,
 // further workgroups what follows the flags.
 constexpr uint32_t kWindowSample = 8;
@@ -2443,7 +2442,7 @@ __global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const 
 
 // ---------------------------------------------------------------------------------------------
 // The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at once then, where
-// four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 64.7).  The four parts are cut into
+// four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 65.1).  The four parts are cut into
 // tasks, all of level 0's first, then all of level 1's and so on, and a workgroup draws its tasks from one queue in that order, a
 // share of a part at a time (at most as many shares as there are workgroups).  A task waits until its problem's part before is
 // done.  The wait always ends: what it waits for was drawn earlier, by workgroups that are running, and a task waits only for parts
@@ -2660,7 +2659,7 @@ __device__ __forceinline__ FinalCtx final_ctx(const Geometry& geo, const TopkWor
     f.row0 = 0; f.row_stride = 1;
     f.chunk0 = 0; f.chunk_stride = geo.num_chunks;
     f.seloff0 = 0; f.seloff_stride = geo.num_chunks * kWaves + 1;
-    f.cand0 = 0; f.cand_stride = cand_pitch(opt.cap);
+    f.cand0 = 0; f.cand_stride = row_cand_pitch(opt.cap, geo.num_chunks);
     f.list0 = 0; f.list_stride = geo.k;
   } else {
     const WgSlot slot = ws.map_final[blockIdx.x];
@@ -3119,7 +3118,7 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 // Whether the general route is one launch: where a window gives the band kernel its chance, and the step is short enough for three
 // launches to count.  What it saves a step whose rows all keep to their windows is 5 us; a step in which every row misses pays for the
 // queue and the waits, the more the larger it is, and dense sweeps stream better from a full grid.  us a step, four launches / one:
-// windows kept 16 x 1 M 69.6 / 64.7, 4 x 300007 (the call without a workspace) 47.4 / 41.0; every row missing (thresholds that jump
+// windows kept 16 x 1 M 69.6 / 65.1, 4 x 300007 (the call without a workspace) 47.4 / 41.0; every row missing (thresholds that jump
 // tenfold; one magnitude only) 4 x 300000 40.5 / 37.2, 1 x 3 M 59.9 / 58.9, 193 / 201, 16 x 1 M 85.2 / 91.4, 234 / 239, 16 x 4 M 208 /
 // 231, 774 / 817.
 constexpr uint64_t kOneLaunchChunks = 4096;

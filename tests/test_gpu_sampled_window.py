@@ -54,3 +54,22 @@ def test_sampled_window(n, d, k, kind):
             a, b = np.ascontiguousarray(x.cpu().numpy()), cpu.get(name)
             assert np.array_equal(np.isnan(a), np.isnan(b)) and bits_equal(a[~np.isnan(a)], b[~np.isnan(b)]), (t, name)
     cpu.close()
+
+
+@pytest.mark.parametrize("most,d,k", [(680, 1, 1), (54, 65536, 655), (54, 65537, 655), (39, 300007, 3000)])
+def test_what_the_call_admits(most, d, k):
+    """The most rows it has ever taken of these shapes, and one more: the band list is made of the room that is left."""
+    rng = np.random.default_rng(d)
+    for n, want in ((most, 0), (most + 1, 3)):
+        ld = B.padded_ld(d)
+        theta, m, v, vhat = (torch.zeros(d, device="cuda") for _ in range(4))
+        e, g = torch.zeros((n, ld), device="cuda"), torch.zeros((n, ld), device="cuda")
+        g[:, :d] = torch.from_numpy(rng.standard_normal(d).astype(np.float32)).cuda()
+        idx = torch.zeros((n, k), dtype=torch.int32, device="cuda")
+        status = B.compams_step_static(n, d, k, theta, m, v, vhat, e, g, 1e-3, idx_out=idx)
+        torch.cuda.synchronize()
+        assert B.compams_strerror(status) == ("ok" if want == 0 else "workspace too small"), (n, status)
+        if want == 0:
+            x = g[0, :d].abs()
+            keep = torch.sort(torch.topk(x, k).indices).values.to(torch.int32)
+            assert torch.equal(idx, keep.expand(n, k))
