@@ -180,7 +180,9 @@ enum {
   COMPAMS_CNT_BAND_MISS = 5,   /* why not: 0 = it was; 1 = the step had no window to offer (first steps, options, blocks of
                                   at most 1024 coordinates); 2 = the candidate list did not fit; 3 = the band list did
                                   not fit; 4 / 5 = the threshold key lay above / below the window; 6 = its bucket held
-                                  more than 64 entries (many equal or nearly equal magnitudes) */
+                                  more than 64 entries (many equal or nearly equal magnitudes); 7 = the selection was
+                                  given up because something else wrote the workspace during the step: its results are
+                                  wrong */
   COMPAMS_COUNTERS_PER_ROW = 8 /* 6, 7 are reserved and read 0 */
 };
 
@@ -333,7 +335,8 @@ int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int 
  * bit for bit what the four calls above give.  Nothing is carried from one call to the next (the threshold guess comes
  * from a sample of every row), so it is the slower way to step.
  * All calls on one device share that device's array: calls that overlap in time on one device (two streams, two
- * threads) race; calls on one stream, or otherwise ordered, do not. */
+ * threads) race - every one of them ends, after some seconds at worst, with undefined results; calls on one stream, or
+ * otherwise ordered, do not. */
 #define COMPAMS_STATIC_SCRATCH_BYTES (32u << 20)
 int compams_step_static(const compams_config* cfg, const float* g, float lr, int32_t* idx_out, float* val_out,
                         void* hip_stream);

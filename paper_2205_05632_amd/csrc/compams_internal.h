@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "compams_tasks.h"
+
 namespace compams {
 
 // ---------------------------------------------------------------------------------------------
@@ -157,8 +159,7 @@ enum : uint32_t {
 };
 
 constexpr uint32_t kQueueWord = 32;  // (a cache line apart from what everybody reads)
-// The part of the general route that a problem is at: the parts before it are done.
-enum : uint32_t { kPhaseLevel0 = 0, kPhaseLevel1 = 1, kPhaseLevel2 = 2, kPhaseCount = 3 };
+constexpr uint32_t kMissGaveUp = 7;  // COMPAMS_CNT_BAND_MISS of a problem that k_topk_general has given up waiting for
 
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
 struct TopkRow {
@@ -195,8 +196,7 @@ struct TopkRow {
   uint32_t next_prev2;     // ... the threshold key two steps before, and the window's population and a key in it
   uint32_t next_population, next_ref;
   uint32_t phase;          // kPhase*: how far k_topk_general is with a problem left to it
-  uint32_t listed;         // with it: the candidate list held (0 also where nobody has looked)
-  uint32_t pad[20];
+  uint32_t pad[21];
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
 

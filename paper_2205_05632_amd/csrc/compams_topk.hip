@@ -1198,7 +1198,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         cn[4] = 0;
         cn[5] = !banded ? 1u : (!cand.fits ? 2u : 3u);  // no band was set; the candidate list / the band list overflowed
         rowp->phase = kPhaseLevel0;
-        rowp->listed = use_guess && rowp->cand_from != 0 && cand.total >= k && cand.fits && !opt.force_dense ? 1u : 0u;
         ws.flags[0] = 1;  // work for the general kernel
       }
     }
@@ -1467,7 +1466,6 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
     cn[4] = 0;
     cn[5] = miss;  // (6): ... its bucket holds more entries than are ranked here
     rowp->phase = kPhaseLevel0;
-    rowp->listed = cand.total >= k ? 1u : 0u;  // (banded, and the list fits)
     ws.flags[0] = 1;  // work for the general kernel
   }
   if (t == 0) {
@@ -2093,7 +2091,7 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
     __syncthreads();
     if (which || SAME) resolve_level1<SAME>(rowp, sh.bstar, sh.need, lh, sh.suf, sh.out2);
   }
-  if (SAME && threadIdx.x == 0) problem_at(rowp, listed ? kPhaseLevel2 : kPhaseLevel1);
+  if (SAME && threadIdx.x == 0) problem_at(rowp, phase_after_level0(listed));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2444,18 +2442,15 @@ __global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const 
 // The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at once then, where
 // four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 65.1).  The four parts are cut into
 // tasks, all of level 0's first, then all of level 1's and so on, and a workgroup draws its tasks from one queue in that order, a
-// share of a part at a time (at most as many shares as there are workgroups).  A task waits until its problem's part before is
-// done.  The wait always ends: what it waits for was drawn earlier, by workgroups that are running, and a task waits only for parts
-// before its own; level 0 waits for nothing.  So it does not matter how many workgroups run at a time, or in what order they start.
+// share of a part at a time (share_of).  A task waits until its problem's part before is done (wait_for_part; level 1's also where level 0
+// has resolved it and nothing is left to do: nobody has to know beforehand).  The wait ends: what it waits for was drawn earlier, by
+// workgroups that are running, and a task waits only for parts before its own; level 0 waits for nothing.  So it does not matter how
+// many workgroups run at a time, or in what order they start.  Only a control block that somebody else writes meanwhile can keep a
+// phase from coming; the wait is bounded for that.
 // What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row); a list that level 1
 // writes is read with ordinary loads, as nobody has looked at it before and no two problems' lists share a cache line.
 // Where it is taken: see general_in_one().
 // ---------------------------------------------------------------------------------------------
-struct GeneralTasks {
-  uint32_t groups[4];  // (a selection per row) workgroups per row, for each part
-  uint32_t total[4];   // tasks of each part
-};
-
 template <bool UNI>
 __global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
                                                       TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
@@ -2467,28 +2462,18 @@ __global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, 
     Level2Shared level2;
     CountShared count;
   } lds;
-  __shared__ uint32_t sh_share, sh_phase;
+  __shared__ uint32_t sh_drawn, sh_phase;
   // (out of the arguments at once: looked up by a number, each look-up waited for memory)
   const uint32_t t0 = tasks.total[0], t1 = tasks.total[1], t2 = tasks.total[2], t3 = tasks.total[3];
   const uint32_t g0 = tasks.groups[0], g1 = tasks.groups[1], g2 = tasks.groups[2], g3 = tasks.groups[3];
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) sh_share = __hip_atomic_fetch_add(ws.flags + kQueueWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) sh_drawn = __hip_atomic_fetch_add(ws.flags + kQueueWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    uint32_t share = uniform_u32(sh_share), part = 0, total = t0, groups = g0, shares = t0 < gridDim.x ? t0 : gridDim.x;
-    auto next_part = [&](uint32_t tasks_of, uint32_t groups_of) {
-      if (share < shares) return;
-      share -= shares;
-      ++part;
-      total = tasks_of;
-      groups = groups_of;
-      shares = total < gridDim.x ? total : gridDim.x;
-    };
-    next_part(t1, g1);
-    if (part == 1) next_part(t2, g2);
-    if (part == 2) next_part(t3, g3);
-    if (share >= shares) return;
-    for (uint32_t q = share; q < total; q += shares) {
+    TaskShare share;
+    if (!share_of(uniform_u32(sh_drawn), gridDim.x, t0, t1, t2, t3, share)) return;
+    const uint32_t part = share.part, groups = part == 0 ? g0 : part == 1 ? g1 : part == 2 ? g2 : g3;
+    for (uint32_t q = share.first; q < share.total; q += share.stride) {
       Geometry geo = geo_all;
       TopkOptions opt = opt_all;
       SegCtx sc;
@@ -2500,17 +2485,23 @@ __global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, 
         sc = seg_ctx_of(slot.seg, slot.group, part == 0 ? sg.groups_level0 : part == 3 ? sg.count_blocks : sg.groups_sweep, sg, geo, opt);
       }
       TopkRow* rowp = ws.rows + sc.seg;
-      // (both written by an earlier launch, the same for the whole problem)
-      if (rowp->fast) continue;                // found by k_topk_band
-      if (part == 1 && rowp->listed) continue;  // resolved by level 0
+      if (rowp->fast) continue;  // found by k_topk_band (an earlier launch: the same for the whole problem)
       if (part) {
         if (threadIdx.x == 0) {
-          uint32_t at;
-          while ((at = load_agent(&rowp->phase)) < part) __builtin_amdgcn_s_sleep(2);
-          sh_phase = at;
+          bool again = false;
+          sh_phase = wait_for_part(part, kMostLooks, [&] {
+            if (again) __builtin_amdgcn_s_sleep(2);
+            again = true;
+            return load_agent(&rowp->phase);
+          });
         }
         __syncthreads();
-        if (part == 1 && sh_phase > part) {  // level 0 has resolved it
+        const TaskTurn turn = turn_of(part, uniform_u32(sh_phase));
+        if (turn == kTurnStop) {
+          if (threadIdx.x == 0) ws.counters[sc.seg * kCountersPerRow + 5] = kMissGaveUp;
+          return;
+        }
+        if (turn == kTurnSkip) {
           __syncthreads();
           continue;
         }
