@@ -612,13 +612,26 @@ __device__ __forceinline__ ListRuns runs_of_row(const Handed<SAME>& row, uint32_
   return L;
 }
 
+// read(bits_of) with the entries of a problem's candidate list, as an earlier launch has left them.  A list that this launch has
+// written (SAME; level 1, kModeNeedB) is read at device scope: segments lie behind one another, so that workgroups of
+// several dies write parts of one line, and the line in the reader's own die may be from before.
+template <bool SAME, typename F>
+__device__ __forceinline__ void with_list(const uint2* __restrict__ candr, uint32_t cap, uint32_t mode, F&& read) {
+  if (SAME && mode == kModeNeedB) {  // uniform
+    const AgentView view = agent_view(reinterpret_cast<const uint32_t*>(candr), 2 * cap);
+    read([=](uint32_t q) { return load_agent(view, 2 * q + 1); });
+  } else {
+    read([=](uint32_t q) { return candr[q].y; });
+  }
+}
+
 // A sweep over a problem's candidate list by `threads` threads, of which the caller is number `first`: visit(bits)
-// for the entries first, first + threads, ... of every run.  The loads of a trip are requested together -- four
-// entries of a list kept as one run, one entry of each of the kSubLists runs otherwise -- because a thread's trips
-// are a chain of round trips (run after run, the sweep of level 2 took 10.4 us instead of 7).
-template <typename F>
-__device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, const ListRuns& R, uint32_t first,
-                                           uint32_t threads, F&& visit) {
+// for the entries first, first + threads, ... of every run; bits_of(q) is the value of the list's entry q.  The loads of a
+// trip are requested together -- four entries of a list kept as one run, one entry of each of the kSubLists runs
+// otherwise -- because a thread's trips are a chain of round trips (run after run, the sweep of level 2 took 10.4 us
+// instead of 7).
+template <typename Bits, typename F>
+__device__ __forceinline__ void sweep_list(Bits&& bits_of, const ListRuns& R, uint32_t first, uint32_t threads, F&& visit) {
   if (R.lists == 1) {  // uniform
     const uint32_t len = R.n[0];
     for (uint32_t q = first; q < len; q += 4 * threads) {
@@ -627,7 +640,7 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         ok[w] = q + w * threads < len;
-        bits[w] = ok[w] ? candr[q + w * threads].y : 0u;
+        bits[w] = ok[w] ? bits_of(q + w * threads) : 0u;
       }
 #pragma unroll
       for (int w = 0; w < 4; ++w)
@@ -644,7 +657,7 @@ __device__ __forceinline__ void sweep_list(const uint2* __restrict__ candr, cons
 #pragma unroll
     for (uint32_t s = 0; s < kSubLists; ++s) {
       ok[s] = q < R.n[s];
-      bits[s] = ok[s] ? candr[static_cast<size_t>(s) * R.pitch + q].y : 0u;
+      bits[s] = ok[s] ? bits_of(s * R.pitch + q) : 0u;  // (below cap)
     }
 #pragma unroll
     for (uint32_t s = 0; s < kSubLists; ++s)
@@ -1983,7 +1996,8 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
   __syncthreads();
   const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = lane_id();
   if (listed) {
-    sweep_list(ws.cand + sc.cand_base, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) {
+    const uint2* candr = ws.cand + sc.cand_base;
+    sweep_list([=](uint32_t q) { return candr[q].y; }, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) {
       const uint32_t key = key_of_bits(bits);
       const uint32_t bucket = key >> kL0Shift;
       atomicAdd(&lh[bucket], 1u);
@@ -2075,7 +2089,8 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
     if (!which && SAME) {  // (rare: the threshold has risen by three buckets) this workgroup sweeps the list for it
       clear_bins<kNB1>(lh);
       __syncthreads();
-      sweep_list(ws.cand + sc.cand_base, runs, threadIdx.x, kWG, [&](uint32_t bits) {
+      const uint2* candr = ws.cand + sc.cand_base;
+      sweep_list([=](uint32_t q) { return candr[q].y; }, runs, threadIdx.x, kWG, [&](uint32_t bits) {
         const uint32_t key = key_of_bits(bits);
         if ((key >> kL0Shift) == sh.bstar) atomicAdd(&lh[(key >> kL1Shift) & (kNB1 - 1)], 1u);
       });
@@ -2145,7 +2160,9 @@ __device__ __forceinline__ void general_level1(GeneralShared& sh, Level1Shared& 
     }
   } else if (mode == kModeCand) {
     const ListRuns runs = runs_of_row(view, opt.cap);
-    sweep_list(candr, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) { visit(bits, true); });
+    const uint2* list = candr;
+    sweep_list([=](uint32_t q) { return list[q].y; }, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG,
+               [&](uint32_t bits) { visit(bits, true); });
   } else {
     const uint32_t step = sc.groups * kWG * 4;
     for (uint32_t j = (sc.group * kWG + threadIdx.x) * 4; j < geo.d; j += step) {
@@ -2194,9 +2211,10 @@ __device__ __forceinline__ void general_level2(GeneralShared& sh, Level2Shared& 
       visit(__float_as_uint(x.w), j + 3 < geo.d);
     }
   } else {
-    const uint2* candr = ws.cand + sc.cand_base;
     const ListRuns runs = runs_of_row(view, opt.cap);
-    sweep_list(candr, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) { visit(bits, true); });
+    with_list<SAME>(ws.cand + sc.cand_base, opt.cap, mode, [&](auto bits_of) {
+      sweep_list(bits_of, runs, sc.group * kWG + threadIdx.x, sc.groups * kWG, [&](uint32_t bits) { visit(bits, true); });
+    });
   }
   __syncthreads();
   uint32_t* gh = ws.hist2 + static_cast<size_t>(row) * kNB2;
@@ -2372,31 +2390,33 @@ __device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& ld
     constexpr int kAhead = 16;
     const uint32_t group = chunks_per_wave(cpw);
     const SegmentLanes sl = segment_lanes(end - start < group ? end - start : group, 1u);
-    for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
-      uint2 ds = make_uint2(0, 0);
-      if (c0 + sl.chunk < end) ds = descr.pair(c0 + sl.chunk);
-      if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
-      else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
-      uint32_t gt = 0, eq = 0;  // of this lane's entries
-      for (uint32_t q0 = 0; ballot64(q0 < ds.y) != 0; q0 += kAhead * sl.lanes) {
-        uint32_t bits[kAhead];
+    with_list<SAME>(candr, opt.cap, mode, [&](auto bits_of) {
+      for (uint32_t c0 = start + wave * group; c0 < end; c0 += kWaves * group) {
+        uint2 ds = make_uint2(0, 0);
+        if (c0 + sl.chunk < end) ds = descr.pair(c0 + sl.chunk);
+        if (ds.x > opt.cap) ds.y = 0;  // segments always lie inside the list; never read outside it
+        else if (ds.y > opt.cap - ds.x) ds.y = opt.cap - ds.x;
+        uint32_t gt = 0, eq = 0;  // of this lane's entries
+        for (uint32_t q0 = 0; ballot64(q0 < ds.y) != 0; q0 += kAhead * sl.lanes) {
+          uint32_t bits[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-          const uint32_t q = q0 + u * sl.lanes + sl.sub;
-          bits[u] = q < ds.y ? candr[ds.x + q].y : 0u;
-        }
+          for (int u = 0; u < kAhead; ++u) {
+            const uint32_t q = q0 + u * sl.lanes + sl.sub;
+            bits[u] = q < ds.y ? bits_of(ds.x + q) : 0u;
+          }
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-          const bool ok = q0 + u * sl.lanes + sl.sub < ds.y;
-          const uint32_t key = key_of_bits(bits[u]);
-          gt += ok && key > tau ? 1u : 0u;
-          eq += ok && key == tau ? 1u : 0u;
+          for (int u = 0; u < kAhead; ++u) {
+            const bool ok = q0 + u * sl.lanes + sl.sub < ds.y;
+            const uint32_t key = key_of_bits(bits[u]);
+            gt += ok && key > tau ? 1u : 0u;
+            eq += ok && key == tau ? 1u : 0u;
+          }
         }
+        gt = chunk_sum(gt, sl);
+        eq = chunk_sum(eq, sl);
+        if (sl.first && c0 + sl.chunk < end) { lds.gt[c0 - start + sl.chunk] = gt; lds.eq[c0 - start + sl.chunk] = eq; }
       }
-      gt = chunk_sum(gt, sl);
-      eq = chunk_sum(eq, sl);
-      if (sl.first && c0 + sl.chunk < end) { lds.gt[c0 - start + sl.chunk] = gt; lds.eq[c0 - start + sl.chunk] = eq; }
-    }
+    });
   }
   __syncthreads();
   // exclusive prefixes within the block: thread t takes `per` consecutive chunks
@@ -2447,8 +2467,8 @@ __global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const 
 // workgroups that are running, and a task waits only for parts before its own; level 0 waits for nothing.  So it does not matter how
 // many workgroups run at a time, or in what order they start.  Only a control block that somebody else writes meanwhile can keep a
 // phase from coming; the wait is bounded for that.
-// What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row); a list that level 1
-// writes is read with ordinary loads, as nobody has looked at it before and no two problems' lists share a cache line.
+// What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row), the list that level 1
+// writes included (with_list).
 // Where it is taken: see general_in_one().
 // ---------------------------------------------------------------------------------------------
 template <bool UNI>

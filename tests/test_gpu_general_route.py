@@ -57,6 +57,28 @@ def test_blocks(n, d, blocks, kind):
             p.compare(f"{kind} {n} x {d} step {t}", with_e=t == 5)
 
 
+@pytest.mark.parametrize("blocks", [0, 3])
+@pytest.mark.parametrize("n,d", [(4, 80 * CHUNK), (1, 257 * CHUNK - 3), (16, 20 * CHUNK + 1)])
+def test_lists_made_again(n, d, blocks):
+    """The corrected gradients themselves shrink and grow tenfold.  Where they have shrunk no list holds: level 1 makes them all again
+    from the rows, about one entry to a chunk, so that many workgroups write parts of one line of the list that the next parts read."""
+    rng = np.random.default_rng(d)
+    off = np.array([d * b // blocks // 4 * 4 for b in range(blocks)] + [d], dtype=np.int64) if blocks else None
+    kept = d // CHUNK
+    if blocks:
+        p = BlockPair(n, d, off, np.full(blocks, max(1, kept // blocks), dtype=np.int64), np.zeros(d, dtype=np.float32))
+    else:
+        p = Pair(n, d, np.zeros(d), B.TOPK, k=kept)
+    for t in range(6):
+        x = rng.standard_normal((n, d)).astype(np.float32) * np.float32(10.0 ** -(t % 2))
+        p.step(x - p.cpu.get("e") if t else x, 1e-3)
+        counters = p.gpu.compams_state("counters").cpu().numpy().reshape(-1, 8)
+        p.compare(f"{n} x {d} step {t}", with_e=t == 5)
+        if t > 1 and t % 2:
+            assert (counters[:, 0] == 1).all() and (counters[:, 5] != 0).all(), (t, counters)
+    p.close()
+
+
 def test_two_streams_at_a_time():
     """Two contexts whose rows all miss, on two streams at once: neither's tasks wait for the other's."""
     n, d, k = 4, 80 * CHUNK, 3000
