@@ -2086,15 +2086,7 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
   __syncthreads();
   if (listed) {
     const uint32_t which = sh.l1;  // 0: level 1 not available; 1 + t: histogram of bucket guess + t
-    if (!which && SAME) {  // (rare: the threshold has risen by three buckets) this workgroup sweeps the list for it
-      clear_bins<kNB1>(lh);
-      __syncthreads();
-      const uint2* candr = ws.cand + sc.cand_base;
-      sweep_list([=](uint32_t q) { return candr[q].y; }, runs, threadIdx.x, kWG, [&](uint32_t bits) {
-        const uint32_t key = key_of_bits(bits);
-        if ((key >> kL0Shift) == sh.bstar) atomicAdd(&lh[(key >> kL1Shift) & (kNB1 - 1)], 1u);
-      });
-    } else if (which) {
+    if (which) {
       const AgentView view = agent_view(gh1 + (which - 1) * kNB1, kNB1);
       uint32_t x[kNB1 / kWG];
 #pragma unroll
@@ -2104,9 +2096,9 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
     }
     clear_bins<kTracked * kNB1>(gh1);
     __syncthreads();
-    if (which || SAME) resolve_level1<SAME>(rowp, sh.bstar, sh.need, lh, sh.suf, sh.out2);
+    if (which) resolve_level1<SAME>(rowp, sh.bstar, sh.need, lh, sh.suf, sh.out2);
   }
-  if (SAME && threadIdx.x == 0) problem_at(rowp, phase_after_level0(listed));
+  if (SAME && threadIdx.x == 0) problem_at(rowp, phase_after_level0(sh.l1 != 0));
 }
 
 // ---------------------------------------------------------------------------------------------

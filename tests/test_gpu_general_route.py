@@ -11,6 +11,7 @@ from test_gpu_topk_blocks import BlockPair, make_blocks
 
 pytestmark = pytest.mark.gpu
 CHUNK = 4096
+GENERAL = ("topk_general", "topk_level0", "topk_level1", "topk_level2", "topk_count")
 
 
 def gradients(kind, base, t, n, d):
@@ -77,6 +78,37 @@ def test_lists_made_again(n, d, blocks):
         if t > 1 and t % 2:
             assert (counters[:, 0] == 1).all() and (counters[:, 5] != 0).all(), (t, counters)
     p.close()
+
+
+def test_threshold_that_rises():
+    """The corrected gradients grow by 30 %: the list holds, but the threshold's bucket lies above the ones that level 0 keeps histograms
+    of.  All workgroups sweep the list for it, in one launch (51 us) as in four (52); by one workgroup alone it took 277."""
+    n, d, k = 1, 1000 * CHUNK - 5, 200_000
+    rng = np.random.default_rng(3)
+    pairs = {band: Pair(n, d, np.zeros(d), B.TOPK, k=k) for band in (1, 0)}
+    pairs[0].gpu.set_option(B.OPT_BAND, 0)  # four launches
+    us = {1: [], 0: []}
+    scale, buckets = np.float32(1), 0
+    for t in range(16):
+        rises = t % 4 == 3
+        if rises:
+            scale *= np.float32(1.3)
+        x = rng.standard_normal((n, d)).astype(np.float32) * scale
+        for band, p in pairs.items():
+            p.gpu.profile_enable(1)
+            p.step(x - p.cpu.get("e") if t else x, 1e-3, label=f"step {t}", with_e=False)
+            times = p.gpu.profile_read()
+            p.gpu.profile_enable(0)
+            if rises:
+                c = p.gpu.compams_state("counters").cpu().numpy().reshape(-1, 8)
+                assert c[0, 0] == 0 and c[0, 5] == (4 if band else 1), c
+                us[band].append(sum(ms for name, (ms, _) in times.items() if name in GENERAL) * 1e3)
+        tau = int(pairs[1].gpu.compams_state("last_threshold").cpu().numpy().view(np.uint32)[0]) >> 19
+        assert not rises or tau >= buckets + 3, (tau, buckets)  # (the guess lies a bucket below the last threshold's, or at it)
+        buckets = tau
+    assert min(us[1]) < 1.5 * min(us[0]), us
+    for p in pairs.values():
+        p.close()
 
 
 def test_two_streams_at_a_time():
