@@ -168,7 +168,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     if (purpose == kForStatic) L.band_alloc = static_band;
     const size_t offsets = measure ? nc + 1 : nc * kWaves + 1;
     L.rows = take(n * sizeof(TopkRow));
-    L.flags = take(256);
+    L.flags = take(measure ? 256 : kFlagBytes);
     L.counters = take(n * COMPAMS_COUNTERS_PER_ROW * 4);
     L.hist0 = take(n * kNB0 * 4);
     L.hist1 = take(n * kNB1 * 4);
@@ -227,7 +227,7 @@ Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uin
     L.flat.seloff_stride = static_cast<uint32_t>(chunks * kWaves + M);
     L.flat.cand_stride = caps;
     L.rows = take(S * sizeof(TopkRow));
-    L.flags = take(256);
+    L.flags = take(kFlagBytes);
     L.counters = take(S * COMPAMS_COUNTERS_PER_ROW * 4);
     L.hist0 = take(S * kNB0 * 4);
     L.hist1 = take(S * kNB1 * 4);

@@ -158,7 +158,10 @@ enum : uint32_t {
   kNextGuess = 2   // guess and window
 };
 
-constexpr uint32_t kQueueWord = 32;  // (a cache line apart from what everybody reads)
+// Words of TopkWorkspace::flags: the queues of k_topk_general lie a cache line apart from one another and from what everybody reads.
+constexpr uint32_t kQueuePitch = 32;
+__host__ __device__ __forceinline__ uint32_t queue_word(uint32_t queue) { return (1 + queue) * kQueuePitch; }
+constexpr size_t kFlagBytes = (1 + kQueues) * kQueuePitch * 4;
 constexpr uint32_t kMissGaveUp = 7;  // COMPAMS_CNT_BAND_MISS of a problem that k_topk_general has given up waiting for
 
 // Per-row control block of the top-k selection (device memory, written by single workgroups).
@@ -299,7 +302,7 @@ struct TopkWorkspace {
   uint32_t* bhist;      // band_buckets(k) per problem : how many band entries fall into each bucket; zero between steps
   uint2* bnd;           // n * kBoundaryCap : the entries of the bucket that holds the threshold key
   uint32_t* bnd_sel;    // n * kBoundaryCap : coordinates of the kept ones among them, ascending
-  uint32_t* flags;      // [kQueueWord]: tasks drawn by k_topk_general.  [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared
+  uint32_t* flags;      // [queue_word(q)]: shares drawn by k_topk_general.  [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared
                         //      by the step's last kernel): the general kernels return at once otherwise
   uint2* cand;          // n * cap_alloc  : (coordinate, fp32 bits)
   int32_t* idx;         // n * k

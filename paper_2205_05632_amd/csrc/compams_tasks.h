@@ -14,30 +14,38 @@ struct GeneralTasks {
   uint32_t total[kGeneralParts];   // tasks of each part
 };
 
-// Tasks first, first + stride, ... below total of a part.
-struct TaskShare {
-  uint32_t part, first, stride, total;
+// Tasks first .. end - 1 of a part.
+struct TaskRange {
+  uint32_t first, end;
 };
 
-// What draw number `drawn` stands for: every part is cut into as many shares as there are workgroups (or tasks, if they are fewer),
-// all of one part's before the next one's.  False: nothing is left.  total: tasks of the parts.
-__host__ __device__ inline bool share_of(uint32_t drawn, uint32_t workgroups, uint32_t total0, uint32_t total1, uint32_t total2,
-                                         uint32_t total3, TaskShare& s) {
-  s.part = kPhaseLevel0;
-  s.first = drawn;
-  s.total = total0;
-  s.stride = total0 < workgroups ? total0 : workgroups;
-  auto next_part = [&](uint32_t total) {
-    if (s.first < s.stride) return;
-    s.first -= s.stride;
-    ++s.part;
-    s.total = total;
-    s.stride = total < workgroups ? total : workgroups;
-  };
-  next_part(total1);
-  if (s.part == kPhaseLevel1) next_part(total2);
-  if (s.part == kPhaseLevel2) next_part(total3);
-  return s.first < s.stride;
+// Every part is cut into as many shares as there are workgroups.  Consecutive tasks: a share is then much the same problem in every
+// part.  (A part has 4096 tasks at most.)
+__host__ __device__ inline TaskRange tasks_of(uint32_t share, uint32_t shares, uint32_t total) {
+  return TaskRange{share * total / shares, (share + 1) * total / shares};
+}
+
+// Shares are drawn from kQueues counters, as many shares from each as there are workgroups that begin with it: draws from one counter
+// follow one another 13 ns apart.  (512 of them: the last workgroup began 8 us after the launch.)
+constexpr uint32_t kQueues = 16;
+__host__ __device__ inline uint32_t queue_shares(uint32_t queue, uint32_t shares) { return (shares + kQueues - 1 - queue) / kQueues; }
+
+// The next share for a workgroup: its first one from its own queue; further ones, after level 0's tasks of that, only if there are
+// queues with some left, so that all shares belong to workgroups that are running before anybody waits.  left(): the queues with some
+// left, a bit each; draw(q): how many were drawn from q before.  Returns `shares` if there is none.
+template <typename Left, typename Draw>
+__host__ __device__ inline uint32_t next_share(uint32_t workgroup, bool first, uint32_t shares, Left&& left, Draw&& draw) {
+  uint32_t q = workgroup % kQueues;
+  for (;;) {
+    if (!first) {
+      const uint32_t some = left();
+      if (!some) return shares;
+      q = static_cast<uint32_t>(__builtin_ctz(some));
+    }
+    first = false;
+    const uint32_t drawn = draw(q);
+    if (drawn < queue_shares(q, shares)) return drawn * kQueues + q;
+  }
 }
 
 // The phase in which level 0 leaves a problem.  resolved: it has done level 1's work as well.

@@ -1879,7 +1879,7 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
   }
   // the control block as the first pass reads it; nothing else in it but zeros
   uint32_t cand_from = 0, guess = 0, valid = 0, band_lo = 0, band_hi = 0, band_mul = 0;
-  if (row == 0 && t == 0) ws.flags[kQueueWord] = 0;
+  if (row == 0 && t < kQueues) ws.flags[queue_word(t)] = 0;
   if (row == 0 && t == 0) ws.flags[0] = opt.band == kBandLists ? 0u : 1u;  // without a band kernel the general ones are told here
   const float* gr = g + static_cast<int64_t>(row) * geo.ld;
   const float* er = e + static_cast<int64_t>(row) * geo.ld;
@@ -2453,16 +2453,22 @@ __global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const 
 // ---------------------------------------------------------------------------------------------
 // The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at once then, where
 // four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 65.1).  The four parts are cut into
-// tasks, all of level 0's first, then all of level 1's and so on, and a workgroup draws its tasks from one queue in that order, a
-// share of a part at a time (share_of).  A task waits until its problem's part before is done (wait_for_part; level 1's also where level 0
-// has resolved it and nothing is left to do: nobody has to know beforehand).  The wait ends: what it waits for was drawn earlier, by
-// workgroups that are running, and a task waits only for parts before its own; level 0 waits for nothing.  So it does not matter how
-// many workgroups run at a time, or in what order they start.  Only a control block that somebody else writes meanwhile can keep a
-// phase from coming; the wait is bounded for that.
+// tasks and every part into as many shares as there are workgroups.  A workgroup draws a share (next_share), takes level 0's tasks of
+// it, draws again if there are shares that nobody has taken, and goes through the tasks of its shares in the parts that follow.  A task
+// waits until its problem's part before is done (wait_for_part; level 1's also where level 0 has resolved it and nothing is left to
+// do: nobody has to know beforehand).  The wait ends: a workgroup waits only when all shares belong to workgroups that are running,
+// and only for parts before its task's; level 0 waits for nothing.  So it does not matter how many workgroups run at a time, or in
+// what order they start.  Only a control block that somebody else writes meanwhile can keep a phase from coming; the wait is
+// bounded for that.
+// What bounds it is a chain for every part: the wait, the list or row, the histogram's atomics, the ticket, the last workgroup's
+// crossing, about 6 us.  (Every share of every part drawn from one counter, and two tasks of level 1 and 2 to a workgroup: 16 x 1 M, all
+// thresholds rising by 15 % a step, 113 us a step; so 96, four launches 92.)
 // What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row), the list that level 1
 // writes included (with_list).
 // Where it is taken: see general_in_one().
 // ---------------------------------------------------------------------------------------------
+constexpr uint32_t kGeneralMost = 512;  // workgroups at most
+
 template <bool UNI>
 __global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
                                                       TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
@@ -2475,54 +2481,89 @@ __global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, 
     CountShared count;
   } lds;
   __shared__ uint32_t sh_drawn, sh_phase;
+  __shared__ uint16_t sh_share[kGeneralMost];  // the shares that this workgroup holds
   // (out of the arguments at once: looked up by a number, each look-up waited for memory)
   const uint32_t t0 = tasks.total[0], t1 = tasks.total[1], t2 = tasks.total[2], t3 = tasks.total[3];
   const uint32_t g0 = tasks.groups[0], g1 = tasks.groups[1], g2 = tasks.groups[2], g3 = tasks.groups[3];
-  for (;;) {
-    __syncthreads();
-    if (threadIdx.x == 0) sh_drawn = __hip_atomic_fetch_add(ws.flags + kQueueWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    TaskShare share;
-    if (!share_of(uniform_u32(sh_drawn), gridDim.x, t0, t1, t2, t3, share)) return;
-    const uint32_t part = share.part, groups = part == 0 ? g0 : part == 1 ? g1 : part == 2 ? g2 : g3;
-    for (uint32_t q = share.first; q < share.total; q += share.stride) {
-      Geometry geo = geo_all;
-      TopkOptions opt = opt_all;
-      SegCtx sc;
-      if constexpr (UNI) {
-        sc = row_ctx(q / groups, q % groups, groups, geo, opt);
-      } else {
-        const WgSlot slot = (part == 0 ? ws.map_level0 : part == 3 ? ws.map_count : ws.map_sweep)[q];
-        const Seg sg = ws.segs[slot.seg];
-        sc = seg_ctx_of(slot.seg, slot.group, part == 0 ? sg.groups_level0 : part == 3 ? sg.count_blocks : sg.groups_sweep, sg, geo, opt);
-      }
-      TopkRow* rowp = ws.rows + sc.seg;
-      if (rowp->fast) continue;  // found by k_topk_band (an earlier launch: the same for the whole problem)
-      if (part) {
-        if (threadIdx.x == 0) {
-          bool again = false;
-          sh_phase = wait_for_part(part, kMostLooks, [&] {
-            if (again) __builtin_amdgcn_s_sleep(2);
-            again = true;
-            return load_agent(&rowp->phase);
-          });
+  uint32_t held = 0;
+  uint32_t seg = ~0u, fast = 0, at = 0;  // the problem looked at last: found by k_topk_band; its phase, as far as seen
+  for (uint32_t part = 0; part < kGeneralParts; ++part) {
+    const uint32_t total = part == 0 ? t0 : part == 1 ? t1 : part == 2 ? t2 : t3;
+    const uint32_t groups = part == 0 ? g0 : part == 1 ? g1 : part == 2 ? g2 : g3;
+    for (uint32_t i = 0; part == 0 || i < held; ++i) {
+      uint32_t share;
+      if (part == 0) {
+        if (threadIdx.x < 64) {  // (a wavefront: a lane per queue)
+          const uint32_t lane = lane_id();
+          const uint32_t next = held == gridDim.x ? gridDim.x : next_share(
+              blockIdx.x, i == 0, gridDim.x,
+              [&] {
+                const uint32_t q = lane % kQueues;
+                return static_cast<uint32_t>(ballot64(lane < kQueues && load_agent(ws.flags + queue_word(q)) <
+                                                                            queue_shares(q, gridDim.x)));
+              },
+              [&](uint32_t q) {
+                uint32_t drawn = 0;
+                if (lane == 0)
+                  drawn = __hip_atomic_fetch_add(ws.flags + queue_word(q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return first_lane(drawn);
+              });
+          if (lane == 0) sh_drawn = next;
         }
         __syncthreads();
-        const TaskTurn turn = turn_of(part, uniform_u32(sh_phase));
+        share = uniform_u32(sh_drawn);
+        if (threadIdx.x == 0 && share < gridDim.x) sh_share[held] = static_cast<uint16_t>(share);
+        __syncthreads();
+        if (share >= gridDim.x) break;  // none is left
+        ++held;
+      } else {
+        share = uniform_u32(sh_share[i]);
+      }
+      const TaskRange range = tasks_of(share, gridDim.x, total);
+      for (uint32_t q = range.first; q < range.end; ++q) {
+        Geometry geo = geo_all;
+        TopkOptions opt = opt_all;
+        SegCtx sc;
+        if constexpr (UNI) {
+          sc = row_ctx(q / groups, q % groups, groups, geo, opt);
+        } else {
+          const WgSlot slot = (part == 0 ? ws.map_level0 : part == 3 ? ws.map_count : ws.map_sweep)[q];
+          const Seg sg = ws.segs[slot.seg];
+          sc = seg_ctx_of(slot.seg, slot.group, part == 0 ? sg.groups_level0 : part == 3 ? sg.count_blocks : sg.groups_sweep, sg, geo,
+                          opt);
+        }
+        TopkRow* rowp = ws.rows + sc.seg;
+        if (sc.seg != seg) {
+          seg = sc.seg;
+          fast = rowp->fast;  // (written by an earlier launch: the same for the whole problem)
+          at = 0;
+        }
+        if (fast) continue;
+        if (at < part) {
+          if (threadIdx.x == 0) {
+            bool again = false;
+            sh_phase = wait_for_part(part, kMostLooks, [&] {
+              if (again) __builtin_amdgcn_s_sleep(2);
+              again = true;
+              return load_agent(&rowp->phase);
+            });
+          }
+          __syncthreads();
+          at = uniform_u32(sh_phase);
+          __syncthreads();
+        }
+        const TaskTurn turn = turn_of(part, at);
         if (turn == kTurnStop) {
           if (threadIdx.x == 0) ws.counters[sc.seg * kCountersPerRow + 5] = kMissGaveUp;
           return;
         }
-        if (turn == kTurnSkip) {
-          __syncthreads();
-          continue;
-        }
+        if (turn == kTurnSkip) continue;
+        if (part == 0) general_level0<true>(sh, lds.level0, e, geo, ws, opt, sc, use_guess);
+        else if (part == 1) general_level1<true>(sh, lds.level1, e, geo, ws, opt, sc);
+        else if (part == 2) general_level2<true>(sh, lds.level2, e, geo, ws, opt, sc);
+        else general_count<false, true>(sh, lds.count, e, geo, ws, opt, sc);
+        __syncthreads();  // the next task takes the same LDS
       }
-      if (part == 0) general_level0<true>(sh, lds.level0, e, geo, ws, opt, sc, use_guess);
-      else if (part == 1) general_level1<true>(sh, lds.level1, e, geo, ws, opt, sc);
-      else if (part == 2) general_level2<true>(sh, lds.level2, e, geo, ws, opt, sc);
-      else general_count<false, true>(sh, lds.count, e, geo, ws, opt, sc);
-      __syncthreads();  // the next task takes the same LDS
     }
   }
 }
@@ -2708,7 +2749,8 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
   const uint32_t c_lo = c * kChunk;                                       // the chunk, in coordinates of the problem
   const uint32_t c_len = f.d_loc - c_lo < kChunk ? f.d_loc - c_lo : kChunk;
   const uint32_t q_lo = c_lo + wave * kPart;                              // this wavefront's part of it
-  if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x == 0) ws.flags[0] = ws.flags[kQueueWord] = 0;  // the general kernel has run
+  if (ROLE != kServerHalf && blockIdx.x == 0 && threadIdx.x < 1 + kQueues)  // the general kernel has run
+    ws.flags[threadIdx.x < kQueues ? queue_word(threadIdx.x) : 0] = 0;
   // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
   const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
   if (ROLE != kServerHalf && c == 0 && i_first == 0 && wave == NW - 1)  // (it has workers of its own only from NW on)
@@ -3119,20 +3161,22 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 }  // namespace
 
 // Whether the general route is one launch: where a window gives the band kernel its chance, and the step is short enough for three
-// launches to count.  What it saves a step whose rows all keep to their windows is 5 us; a step in which every row misses pays for the
-// queue and the waits, the more the larger it is, and dense sweeps stream better from a full grid.  us a step, four launches / one:
-// windows kept 16 x 1 M 69.6 / 65.1, 4 x 300007 (the call without a workspace) 47.4 / 41.0; every row missing (thresholds that jump
-// tenfold; one magnitude only) 4 x 300000 40.5 / 37.2, 1 x 3 M 59.9 / 58.9, 193 / 201, 16 x 1 M 85.2 / 91.4, 234 / 239, 16 x 4 M 208 /
-// 231, 774 / 817.
+// launches to count.  us a step, four launches / one, two dozen steps into a run; windows mostly kept (a fifth to a third of the rows
+// miss), thresholds that rise by 15 % a step, that jump tenfold, one magnitude only (the last three: most or all rows miss):
+// 4 x 300007 40.9 / 37.3, 49.5 / 51.4, 46.9 / 46.3, 127.6 / 130.0; 8 x 1 M 58.4 / 55.2, 72.7 / 77.3, 73.3 / 74.4, 183.2 / 184.9; 16 x 1 M
+// 74.5 / 71.6, 92.4 / 95.8, 95.0 / 95.0, 246.6 / 250.2; 64 x 250007 87.5 / 82.7, 104.6 / 105.2, 107.1 / 106.1, 344.6 / 347.2; 1 x 16 M
+// 167.3 / 163.1, 197.0 / 189.0, 222.2 / 219.2, 707.3 / 709.4; 8 x 12 blocks of 60000 54.5 / 49.6, 64.5 / 60.5, 72.7 / 70.5, 148.7 / 151.6.
+// Beyond the line the launches are less than three per cent of a step.
 constexpr uint64_t kOneLaunchChunks = 4096;
 static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, uint64_t chunks) {
   return use_guess && opt.band && chunks <= kOneLaunchChunks;
 }
 static_assert(kOneLaunchChunks < kPagedChunks, "k_topk_general counts chunks of one segment");
-// (16 x 1 M, every row missing, 512 / 768 / 1024: 99.8 / 105.8 / 110.8 us: more of them draw and wait)
+static_assert((kOneLaunchChunks + 1) * kGeneralMost < (1ull << 32), "tasks_of: a task has a chunk at least");
+// (kGeneralMost = 256 / 512 / 1024: 16 x 1 M, rising thresholds 98 / 96 / 108 us a step, one magnitude 279 / 249 / 249; 1 x 16 M 185 / 191 / 207,
+// 723 / 709 / 720)
 static uint32_t general_workgroups(const GeneralTasks& tasks) {
-  constexpr uint32_t kMost = 512;
-  return std::min(kMost, *std::max_element(tasks.total, tasks.total + 4));
+  return std::min(kGeneralMost, *std::max_element(tasks.total, tasks.total + 4));
 }
 
 constexpr size_t kClearBytes = 32768;  // a workgroup of the sampling launch clears
@@ -3179,15 +3223,17 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
-    // level 0 by about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
-    // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
-    const uint32_t g0 = std::min((512 + geo.n - 1) / geo.n, G);
-    GeneralTasks tasks{{g0, G, G, count_blocks}, {}};
-    for (int part = 0; part < 4; ++part) tasks.total[part] = tasks.groups[part] * geo.n;
     if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * geo.num_chunks)) {
+      // a task of every part to a workgroup: the second one's clearing, flushing and ticket would follow the first one's
+      const uint32_t g1 = std::max(1u, std::min(kGeneralMost / geo.n, G));
+      GeneralTasks tasks{{g1, g1, g1, count_blocks}, {}};
+      for (uint32_t part = 0; part < kGeneralParts; ++part) tasks.total[part] = tasks.groups[part] * geo.n;
       launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
+      // level 0 by about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
+      // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
+      const uint32_t g0 = std::min((512 + geo.n - 1) / geo.n, G);
       launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
       launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);

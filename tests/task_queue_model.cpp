@@ -21,7 +21,7 @@ struct Problem {
 
 int main(int, char** argv) {
   const uint32_t seed = std::atoi(argv[1]), workgroups = std::atoi(argv[2]), n = std::atoi(argv[3]);
-  const bool disturb = std::atoi(argv[4]) != 0;
+  const bool disturb = std::atoi(argv[4]) != 0, late = seed % 2;
   std::mt19937 rng(seed);
   std::vector<Problem> problems(n);
   for (Problem& p : problems) { p.fast = rng() % 3 == 0; p.resolved = rng() % 2 == 0; }
@@ -30,40 +30,61 @@ int main(int, char** argv) {
     tasks.groups[part] = 1 + rng() % 9;
     tasks.total[part] = tasks.groups[part] * n;
   }
-  std::atomic<uint32_t> queue{0}, wrong{0}, gave_up{0}, ended{0};
-  auto workgroup = [&] {
-    for (;;) {
-      TaskShare s;
-      if (!share_of(queue.fetch_add(1), workgroups, tasks.total[0], tasks.total[1], tasks.total[2], tasks.total[3], s)) return;
-      for (uint32_t q = s.first; q < s.total; q += s.stride) {
-        Problem& p = problems[q / tasks.groups[s.part]];
-        if (p.fast) continue;
-        if (s.part) {
-          const uint32_t at = wait_for_part(s.part, disturb ? 2000u : kMostLooks, [&] {
-            std::this_thread::yield();
-            return p.phase.load();
-          });
-          const TaskTurn turn = turn_of(s.part, at);
+  std::atomic<uint32_t> queues[kQueues]{}, wrong{0}, gave_up{0}, ended{0};
+  auto workgroup = [&](uint32_t w) {
+    std::vector<uint32_t> held;
+    for (uint32_t part = 0; part < kGeneralParts; ++part) {
+      for (uint32_t i = 0; part == 0 || i < held.size(); ++i) {
+        if (part == 0) {
+          if (held.size() == workgroups) break;
+          auto left = [&] {
+            uint32_t some = 0;
+            for (uint32_t queue = 0; queue < kQueues; ++queue) some |= (queues[queue] < queue_shares(queue, workgroups) ? 1u : 0u) << queue;
+            return some;
+          };
+          const uint32_t share = next_share(w, i == 0, workgroups, left, [&](uint32_t queue) { return queues[queue].fetch_add(1); });
+          if (share >= workgroups) break;
+          held.push_back(share);
+        }
+        const TaskRange range = tasks_of(held[i], workgroups, tasks.total[part]);
+        for (uint32_t q = range.first; q < range.end; ++q) {
+          Problem& p = problems[q / tasks.groups[part]];
+          if (p.fast) continue;
+          uint32_t at = 0;
+          if (part)
+            at = wait_for_part(part, disturb ? 2000u : kMostLooks, [&] {
+              std::this_thread::yield();
+              return p.phase.load();
+            });
+          const TaskTurn turn = turn_of(part, at);
           if (turn == kTurnStop) { ++gave_up; return; }
           if (turn == kTurnSkip) {
-            if (!p.resolved) ++wrong;
+            if (!p.resolved && !disturb) ++wrong;
             continue;
           }
-          const uint32_t before = s.part - 1 - (s.part == kPhaseLevel2 && p.resolved ? 1u : 0u);
-          if (p.done[before] < tasks.groups[before]) ++wrong;
+          if (part && !disturb) {
+            const uint32_t before = part - 1 - (part == kPhaseLevel2 && p.resolved ? 1u : 0u);
+            if (p.done[before] < tasks.groups[before]) ++wrong;
+          }
+          ++p.begun[part];
+          if (q % 5 == seed % 5) std::this_thread::yield();
+          if (++p.done[part] == tasks.groups[part] && part < kPhaseCount)
+            p.phase = part == kPhaseLevel0 ? phase_after_level0(p.resolved) : part + 1;
         }
-        ++p.begun[s.part];
-        if (q % 5 == seed % 5) std::this_thread::yield();
-        if (++p.done[s.part] == tasks.groups[s.part] && s.part < kPhaseCount)
-          p.phase = s.part == kPhaseLevel0 ? phase_after_level0(p.resolved) : s.part + 1;
       }
     }
   };
   std::vector<std::thread> threads;
-  for (uint32_t w = 0; w < workgroups; ++w) threads.emplace_back([&] { workgroup(); ++ended; });
+  // (late: every second workgroup finds no place to run until another one has ended)
+  for (uint32_t w = 0; w < workgroups; ++w)
+    threads.emplace_back([&, w] {
+      while (late && w % 2 && !ended) std::this_thread::yield();
+      workgroup(w);
+      ++ended;
+    });
   for (int i = 0; disturb && i < 50 && ended < workgroups; ++i) {
     for (Problem& p : problems) p.phase = kPhaseLevel0;
-    queue = 0;
+    for (auto& queue : queues) queue = 0;
     std::this_thread::yield();
   }
   for (std::thread& t : threads) t.join();
@@ -72,5 +93,5 @@ int main(int, char** argv) {
       for (uint32_t part = 0; part < kGeneralParts; ++part)
         if (p.begun[part] != (p.fast || (part == kPhaseLevel1 && p.resolved) ? 0u : tasks.groups[part])) ++wrong;
   std::printf("wrong %u gave_up %u\n", wrong.load(), gave_up.load());
-  return !disturb && (wrong || gave_up) ? 1 : 0;
+  return wrong || (!disturb && gave_up) ? 1 : 0;
 }
