@@ -1027,10 +1027,25 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
 // The kernels that select in one launch end in one workgroup's chain, of which the above (divisions and roots, one after the other)
 // was 1 to 1.5 us: they leave what it needs in the control block, and a wavefront of the last kernel goes through it beside
 // the others' work (a step of 4 x 65536, k = 655: 24.3 us, with that and the ranking of k_topk_pick 23.2; 16 x 1 M 70.4, now 69.6).
-// population: entries of the window that was looked at (0: none), ref: a key in it.
-__device__ __forceinline__ void leave_next(TopkRow* rowp, uint32_t valid, uint32_t guess, uint32_t known, uint32_t tau_prev2,
-                                           uint32_t population, uint32_t ref) {
+// Only where there is a lane for every row: more of them keep that wavefront's compute unit busy, 1.4 us for every 64, while in the
+// selecting kernel every row has a workgroup of its own (us, all rows in the selecting kernel / in the last one: a step of 32 x 600000
+// 75.4 / 74.6, 24 x 300000 49.5 / 48.9, 64 x 100000 59.7 / 59.1, 64 x 4096 43.4 / 43.7, 300 x 4096 134.7 / 140.8, 4000 x 4096 1547 / 1640; the
+// workers' half 300 x 4096 27.2 / 33.8, 4000 x 4096 120 / 218).
+// population: entries of the window lo .. hi that was looked at (0: none), ref: a key in it.
+__device__ __forceinline__ bool window_later(uint32_t n) { return n <= 64; }
+__device__ __forceinline__ float population_noise(uint32_t population, uint32_t lo, uint32_t hi, uint32_t ref, uint32_t k) {
+  return population ? 8.0f * ((__uint_as_float(hi) - __uint_as_float(lo)) / __uint_as_float(ref)) * sqrtf(static_cast<float>(k)) /
+                          static_cast<float>(population)
+                    : default_band_noise(k);
+}
+__device__ __forceinline__ void leave_next(TopkRow* rowp, uint32_t n, uint32_t k, const TopkOptions& opt, uint32_t valid, uint32_t guess,
+                                           uint32_t known, uint32_t tau, uint32_t tau_prev, uint32_t tau_prev2, uint32_t population,
+                                           uint32_t lo, uint32_t hi, uint32_t ref) {
   rowp->b_guess = guess;
+  if (!window_later(n)) {
+    set_next_band(rowp, tau, tau_prev, tau_prev2, valid, guess, known, population_noise(population, lo, hi, ref, k), k, opt);
+    return;
+  }
   rowp->next = valid ? kNextGuess : kNextNone;
   rowp->known_from = known;
   rowp->next_prev2 = tau_prev2;
@@ -1041,11 +1056,8 @@ __device__ __forceinline__ void set_next(TopkRow* rowp, uint32_t k, const TopkOp
   const uint32_t next = rowp->next, lo = rowp->band_lo, hi = rowp->band_hi, population = rowp->next_population;
   if (next == kNextSet) return;
   rowp->next = kNextSet;
-  const float noise = population ? 8.0f * ((__uint_as_float(hi) - __uint_as_float(lo)) / __uint_as_float(rowp->next_ref)) *
-                                       sqrtf(static_cast<float>(k)) / static_cast<float>(population)
-                                 : default_band_noise(k);
   set_next_band(rowp, rowp->tau, rowp->tau_prev, rowp->next_prev2, next == kNextGuess ? 1u : 0u, rowp->b_guess, rowp->known_from,
-                noise, k, opt);
+                population_noise(population, lo, hi, rowp->next_ref, k), k, opt);
 }
 
 // The runs of a problem's band list, from the high halves of the cursors the first pass advanced.
@@ -1470,7 +1482,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
         if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
         else if (cand.total <= opt.cap / 2) { valid = 1; guess = b0; }
       }
-      leave_next(rowp, valid, guess, known_from(guess, list_from, cand.total, opt.cap), tau_before2, band.total, blo);
+      leave_next(rowp, geo.n, k, opt, valid, guess, known_from(guess, list_from, cand.total, opt.cap), tau, tau_prev, tau_before2,
+                 band.total, blo, bhi, blo);
     }
   } else if (t == 0) {
     rowp->fast = kFastNot;
@@ -1810,8 +1823,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
     if (b0 && bound <= opt.cap / 2) { valid = 1; guess = b0 - 1; }
     else if (at_hand <= opt.cap / 2) { valid = 1; guess = b0; }
   }
-  leave_next(rowp, valid, guess, LISTED ? known_from(guess, cand_lo, n_cand, opt.cap) : 0u, tau_before2,
-             miss == 0 && normal_key(tau) ? in_window : 0u, tau);
+  leave_next(rowp, geo.n, k, opt, valid, guess, LISTED ? known_from(guess, cand_lo, n_cand, opt.cap) : 0u, tau, tau_before, tau_before2,
+             miss == 0 && normal_key(tau) ? in_window : 0u, blo, bhi, tau);
 }
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_pick(TopkRow* rows, uint2* cand, const float* __restrict__ e,
@@ -2753,13 +2766,14 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
     ws.flags[threadIdx.x < kQueues ? queue_word(threadIdx.x) : 0] = 0;
   // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
   const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
-  if (ROLE != kServerHalf && c == 0 && i_first == 0 && wave == NW - 1)  // (it has workers of its own only from NW on)
-    for (uint32_t i = lane; i < geo.n; i += 64) {
-      TopkRow* rowp = ws.rows + f.row0 + i * f.row_stride;
-      rowp->cursor = 0;  // the next step's first pass allocates its candidate lists from the start
-      rowp->cursor_band = 0;
-      if (!CLEAR) set_next(rowp, f.k_loc, opt);
+  if (ROLE != kServerHalf && c == 0 && i_first == 0) {
+    for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {  // the next step's first pass allocates its candidate lists from the start
+      ws.rows[f.row0 + i * f.row_stride].cursor = 0;
+      ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
     }
+    if (!CLEAR && window_later(geo.n) && wave == NW - 1 && lane < geo.n)  // (it has workers of its own only from NW on)
+      set_next(ws.rows + f.row0 + lane * f.row_stride, f.k_loc, opt);
+  }
   if (ROLE != kWorkerHalf) {  // (before the tile's barrier: other wavefronts may add here)
 #pragma unroll
     for (uint32_t r = 0; r < kPart / 256; ++r)
