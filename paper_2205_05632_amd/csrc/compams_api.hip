@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -142,6 +143,13 @@ std::vector<BlockShape> block_shapes(const compams_config* c) {
     if (s.micro) s.groups_first = s.groups_level0 = s.groups_sweep = s.count_blocks = 0;
   }
   return v;
+}
+
+// What a window from a sample of kSample of d coordinates holds: three deviations and two sampled entries on either side of the expected
+// count, and what the buckets of a sixteenth of an octave at its ends add to that, three tenths of k each on normal values.
+double sampled_window(int64_t d, int64_t k) {
+  const double each = static_cast<double>(d) / kSample, share = static_cast<double>(k) / each;
+  return (6.0 * std::sqrt(share) + 4.0 + 0.6 * share) * each;
 }
 
 // What a layout is for: a context's workspace, the tables of compams_step_static() (which has no messages to pack, and a band list of
@@ -985,10 +993,14 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   try {
     if (make_layout(cfg, kStaticMeasure).total > most) return COMPAMS_WORKSPACE_TOO_SMALL;
     ctx.lay = make_layout(cfg, kForStatic);
-    // A band list of what room there is, up to four times what is kept and 8192 entries: a sampled window is wide.
+    // A band list of what room there is, up to the candidate list's length, or none where a sampled window would hardly fit: a row whose
+    // window does not fit costs the call the band kernel and the general route as well (8 x 2893126, k = 5860, a list of 4 k + 8192: two
+    // calls out of three, 122 us where the others took 105; 4 x 6 M, k = 87891, which leaves room for 150000 entries, 162 us with windows,
+    // 144 without).
     const size_t room = most - std::min<size_t>(most, ctx.lay.total + 1024 + static_cast<size_t>(cfg->n) * ctx.lay.num_chunks * 8);
-    const uint32_t band = static_cast<uint32_t>(std::min<size_t>(
-        {4 * static_cast<size_t>(cfg->k) + 8192, kBandMaxEntries, ctx.lay.cap_alloc, room / (8 * static_cast<size_t>(cfg->n))}));
+    uint32_t band = static_cast<uint32_t>(std::min<size_t>(
+        {kBandMaxEntries, ctx.lay.cap_alloc, room / (8 * static_cast<size_t>(cfg->n))}));
+    if (band < 1.5 * sampled_window(cfg->d, cfg->k)) band = 0;
     if (band) ctx.lay = make_layout(cfg, kForStatic, band);
   } catch (...) {
     return COMPAMS_HIP_ERROR;

@@ -1867,14 +1867,23 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(TopkRow* rows, uint2
 // The same sample gives the window of keys in which the threshold is expected, where the first pass is to keep band lists: from the
 // bucket above which the expected count plus three deviations lies to the one above which the expected count less three
 // deviations does, if the band list would hold what the sample says lies in it.  The band kernel then selects, as in a step that
-// carries its window over, and the four general ones (30 us of the call for 4 x 300007, k = 3000) return at once.  Fewer than
-// kWindowSample of the sample's entries above the threshold say too little: the window is two octaves wide and more, its entries'
-// lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (Two sets of 24 drawn shapes, times
-// faster than without a window, in the mean: from 8 entries on 1.06 and 1.06, from 16 on 1.05 and 1.04, always 1.05; always: 4 x
-// 1634958, k = 2524, 70.9 -> 74.0 us; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 -> 43.9.)
+// carries its window over, and the general route (30 us of the call for 4 x 300007, k = 3000, in four launches) returns at once.
+// Fewer of the sample's entries above the threshold than sample_gives_window() asks for say too little: the window is two octaves wide
+// and more, its entries' lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (Two sets of 24
+// drawn shapes, times faster than without a window, in the mean: from 8 entries on 1.06 and 1.06, from 16 on 1.05 and 1.04, always
+// 1.05; always: 4 x 1634958, k = 2524, 70.9 -> 74.0 us; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 ->
+// 43.9.)  In long rows a wide window's entries meet on the histogram's crowded end: us a call without / with a window, unit normal and
+// heavy-tailed values, 12 entries above the threshold: 4 x 1.8 M 71.8 / 67.9, 71.1 / 69.3; 4 x 2.6 M 80.2 / 77.4, 89.7 / 81.9; 4 x 2.9 M
+// 85.0 / 83.9, 84.1 / 91.8; 8 x 1.8 M 89.6 / 83.8, 88.1 / 84.5; 8 x 2.1 M 91.6 / 94.0, 95.9 / 96.8; 8 x 2.9 M 107.4 / 117.1, 107.6 / 130.9; 40
+// entries, where it is narrower: 4 x 2.9 M 87.0 / 78.9, 8 x 2.9 M 111.4 / 109.0.
 // The launch also clears the tables that the call expects at zero, which took a launch of its own, 2 us: a workgroup its row's control block,
 // further workgroups what follows the flags.
-constexpr uint32_t kWindowSample = 8;
+// (And where nearly all is kept, the sample does not say from where on.)
+inline bool sample_gives_window(const Geometry& geo) {
+  const uint64_t entries = geo.num_chunks <= 640 && static_cast<uint64_t>(geo.n) * geo.num_chunks <= 4096 ? 8 : 32;
+  const uint64_t k = geo.k, d = geo.d;
+  return k * kSample >= d * entries && 8 * k <= 5 * d;
+}
 
 __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __restrict__ g, const float* __restrict__ e,
                                                                int64_t ld, uint32_t d, uint32_t n, uint32_t k, uint32_t cap,
@@ -3210,7 +3219,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   const bool pick = geo.num_chunks <= kPickChunks && use_guess;
   TopkOptions opt = options;
   if (pick && opt.band) opt.band = kBandWindow;
-  if (whole && static_cast<uint64_t>(geo.k) * kSample < static_cast<uint64_t>(geo.d) * kWindowSample) opt.band = kBandOff;
+  if (whole && !sample_gives_window(geo)) opt.band = kBandOff;
   // (4 rows of 300007, k = 3000: level 0 to count 49 us without a guess, with it 38 and 8 for the sample; 4 rows of 65536,
   // k = 655: the whole call 66 us by the general kernels without a guess, 34.4 with it and one workgroup per row)
   if (whole && geo.d >= kSample) {
