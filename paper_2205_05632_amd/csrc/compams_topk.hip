@@ -3190,9 +3190,14 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 // 74.5 / 71.6, 92.4 / 95.8, 95.0 / 95.0, 246.6 / 250.2; 64 x 250007 87.5 / 82.7, 104.6 / 105.2, 107.1 / 106.1, 344.6 / 347.2; 1 x 16 M
 // 167.3 / 163.1, 197.0 / 189.0, 222.2 / 219.2, 707.3 / 709.4; 8 x 12 blocks of 60000 54.5 / 49.6, 64.5 / 60.5, 72.7 / 70.5, 148.7 / 151.6.
 // Beyond the line the launches are less than three per cent of a step.
+// Steps of a run that keep much: from two fifths of a row on a list seldom holds and the route is taken in every step (k = d / 2.7, d /
+// 2.3, d / 1.5: 4 x 1 M 97.1 / 94.7, 112.8 / 111.6, 137.8 / 143.3; 1 x 4 M 120.5 / 118.7, 137.6 / 136.1, 163.1 / 168.6; 4 x 4 M 206.8 / 211.1,
+// 236.2 / 248.2, 276.9 / 339.4; 16 x 1 M, d / 1.5, 231.4 / 302.4), and long lists are swept better by a full grid: a million entries of all
+// rows (k = d / 8: 8 x 1 M 91.9 / 90.1, 16 x 1 M 125.1 / 128.1, 64 x 200000 153.8 / 157.5, 200 x 70000 288.4 / 303.6).
 constexpr uint64_t kOneLaunchChunks = 4096;
-static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, uint64_t chunks) {
-  return use_guess && opt.band && chunks <= kOneLaunchChunks;
+static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, const Geometry& geo, uint64_t chunks, bool whole) {
+  const uint64_t k = geo.k, d = geo.d, n = geo.n;
+  return use_guess && opt.band && chunks <= kOneLaunchChunks && (whole || (5 * k <= 2 * d && n * k <= 1u << 20));
 }
 static_assert(kOneLaunchChunks < kPagedChunks, "k_topk_general counts chunks of one segment");
 static_assert((kOneLaunchChunks + 1) * kGeneralMost < (1ull << 32), "tasks_of: a task has a chunk at least");
@@ -3246,7 +3251,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
-    if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * geo.num_chunks)) {
+    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * geo.num_chunks, whole)) {
       // a task of every part to a workgroup: the second one's clearing, flushing and ticket would follow the first one's
       const uint32_t g1 = std::max(1u, std::min(kGeneralMost / geo.n, G));
       GeneralTasks tasks{{g1, g1, g1, count_blocks}, {}};
@@ -3305,7 +3310,7 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   }
   if (flat.wg_sweep) {  // none if every block is a micro problem
     const GeneralTasks tasks{{}, {flat.wg_level0, flat.wg_sweep, flat.wg_sweep, flat.wg_count}};
-    if (general_in_one(use_guess, opt, static_cast<uint64_t>(geo.n) * flat.chunk_stride)) {
+    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * flat.chunk_stride, false)) {
       launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {

@@ -111,6 +111,24 @@ def test_threshold_that_rises():
         p.close()
 
 
+@pytest.mark.parametrize("n,d,k,one", [
+    (2, 80 * CHUNK, 32 * CHUNK, True), (2, 80 * CHUNK, 32 * CHUNK + 1, False),   # two fifths of a row
+    (16, 80 * CHUNK, 16 * CHUNK, True), (16, 80 * CHUNK, 16 * CHUNK + 1, False),  # 2^20 entries of all rows
+    (64, 64 * CHUNK, 2600, True), (64, 64 * CHUNK + 1, 2600, False)])             # 4096 chunks
+def test_which_form(n, d, k, one):
+    """Steps that keep much take the route every time, and its four launches: 16 x 1 M, k = d / 2, 201 us, in one launch 248."""
+    rng = np.random.default_rng(k)
+    p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    base = rng.standard_normal(d).astype(np.float32)
+    for t in range(4):
+        p.gpu.profile_enable(1)
+        p.step(gradients("some", base, t, n, d), 1e-3, label=f"step {t}", with_e=False)
+        used = {name for name, (_, launches) in p.gpu.profile_read().items() if launches}
+        p.gpu.profile_enable(0)
+        assert ("topk_general" in used) == (one and t > 0) and ("topk_level0" in used) == (not one or t == 0), (t, used)
+    p.close()
+
+
 def test_two_streams_at_a_time():
     """Two contexts whose rows all miss, on two streams at once: neither's tasks wait for the other's."""
     n, d, k = 4, 80 * CHUNK, 3000
