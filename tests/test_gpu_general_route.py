@@ -14,6 +14,24 @@ CHUNK = 4096
 GENERAL = ("topk_general", "topk_level0", "topk_level1", "topk_level2", "topk_count")
 
 
+def went(p):
+    """Per problem: whether it took the general route in the last step, and whether from the list that the first pass had made."""
+    counters = p.gpu.compams_state("counters").cpu().numpy().reshape(-1, 8)
+    missed = counters[:, 5] != 0
+    return missed, missed & (counters[:, 0] == 0)
+
+
+def provoked(kind, steps, alone=False):
+    """Whether the steps (from the third on, where there are windows) took the ways that the kind of gradient is there for."""
+    if kind == "steady":
+        return not any(missed.any() for missed, _ in steps)
+    if kind == "some":  # in one step rows inside their windows and rows outside whose lists held (one row: one after the other)
+        return any(listed.any() and (alone or not missed.all()) for missed, listed in steps)
+    if kind == "jump":  # all of them, and lists that did not hold
+        return any((missed & ~listed).all() for missed, listed in steps)
+    return any(missed.any() for missed, _ in steps)
+
+
 def gradients(kind, base, t, n, d):
     g = np.stack([np.roll(base, 1013 * t + 41 * i) for i in range(n)])
     if kind == "jump":        # up and down tenfold: lists that overflow, lists with too few entries
@@ -34,13 +52,12 @@ def test_whole_rows(n, d, k, kind):
     rng = np.random.default_rng(d + n)
     base = rng.standard_normal(d).astype(np.float32)
     p = Pair(n, d, rng.standard_normal(d).astype(np.float32), B.TOPK, k=k)
-    steps, missed, counters = 7, 0, None
+    steps, seen = 7, []
     for t in range(steps):
         p.step(gradients(kind, base, t, n, d), 1e-3, label=f"{kind} {n} x {d} step {t}", with_e=t == steps - 1, check=t % 2 == 0 or n < 10)
-        counters = p.gpu.compams_state("counters").cpu().numpy()
-        missed += int((counters[:, 5] != 0).sum()) if t > 2 else 0
+        seen.append(went(p))
     p.compare(f"{kind} {n} x {d}")
-    assert missed > 0 or kind in ("steady", "some"), "no row took the general route"
+    assert provoked(kind, seen[2:], alone=n == 1), seen
     assert all(p.exact.values()), p.exact
     p.close()
 
@@ -52,10 +69,13 @@ def test_blocks(n, d, blocks, kind):
     off, kb = make_blocks(d, blocks, rng)
     base = rng.standard_normal(d).astype(np.float32)
     p = BlockPair(n, d, off, kb, np.zeros(d, dtype=np.float32))
+    seen = []
     for t in range(6):
         p.step(gradients(kind, base, t, n, d))
+        seen.append(went(p))
         if t % 2:
             p.compare(f"{kind} {n} x {d} step {t}", with_e=t == 5)
+    assert provoked(kind, seen[2:]), seen
 
 
 @pytest.mark.parametrize("blocks", [0, 3])
@@ -130,7 +150,7 @@ def test_which_form(n, d, k, one):
 
 
 def test_two_streams_at_a_time():
-    """Two contexts whose rows all miss, on two streams at once: neither's tasks wait for the other's."""
+    """Two contexts whose rows all miss in every second step at least, on two streams at once: neither's tasks wait for the other's."""
     n, d, k = 4, 80 * CHUNK, 3000
     rng = np.random.default_rng(5)
     base = rng.standard_normal(d).astype(np.float32)
@@ -142,12 +162,16 @@ def test_two_streams_at_a_time():
         for t, g in enumerate(pair_grads):
             g[:, :d] = torch.from_numpy(gradients("jump", base, t + c, n, d)).cuda()
     torch.cuda.synchronize()
+    counters = [[], []]
     for t in range(8):
-        for p, s, g in zip(pairs, streams, grads):
+        for p, s, g, seen in zip(pairs, streams, grads, counters):
             with torch.cuda.stream(s):
                 p.gpu.compams_step(g[t % 2], 1e-3)
+                seen.append(p.gpu.compams_state("counters").clone())
     torch.cuda.synchronize()
     for c, p in enumerate(pairs):
+        missed = [(m[:, 5] != 0).all().item() for m in counters[c][2:]]
+        assert sum(missed) >= 3, missed
         for t in range(8):
             p.cpu.step(gradients("jump", base, t % 2 + c, n, d), 1e-3)
         p.compare(f"context {c}")
