@@ -3,9 +3,11 @@
 `python -m paper_2205_05632_amd.build` compiles every source under csrc/ with hipcc and links
 paper_2205_05632_amd/libcompams.so.  Floating-point contraction is off so that every fp32 operation of
 the optimizer update rounds once, and packed-fp32 instruction selection is disabled.  A kernel's first plain arguments arrive in
-scalar registers (up to the first structure, 14 words), where the first loads of a short kernel would wait for them: the
-kernels of small steps have what those loads need in front (4 x 65536: block-sign 11.8 -> 11.3 us a step, top-k 23.0 -> 22.7), the
-first pass and the last kernel of top-k have the structure in front (16 x 1 M: 65.6 us with the others' order, 65.3 so).
+scalar registers (up to the first structure, 14 words), where the first loads of a short kernel would wait for them.  The block-sign
+kernels of small steps have what those loads need in front (4 x 65536: 11.9 -> 11.5 us a step), and so have the packing kernels and the
+call without a workspace (64 x 300000 in two halves 108.2 -> 107.5, 4 x 300007 43.95 -> 43.8).  The top-k kernels of a context's step have a
+structure in front, which switches it off: with plain arguments the one that selects short rows cost a step 0.2 us (4 x 65536: 23.3 ->
+23.5), the four of the general route 0.3 (64 x 300000: 90.05 -> 90.35).
 """
 import os
 import subprocess

@@ -1827,11 +1827,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
              miss == 0 && normal_key(tau) ? in_window : 0u, blo, bhi, tau);
 }
 
-__global__ __launch_bounds__(kPickThreads) void k_topk_pick(TopkRow* rows, uint2* cand, const float* __restrict__ e,
-                                                             int64_t ld, uint32_t d, uint32_t k, uint32_t cap, uint32_t num_chunks,
-                                                             uint32_t use_guess, Geometry geo, TopkWorkspace ws, TopkOptions opt) {
-  geo.ld = ld; geo.d = d; geo.k = k; geo.num_chunks = num_chunks; opt.cap = cap;
-  ws.rows = rows; ws.cand = cand;
+__global__ __launch_bounds__(kPickThreads) void k_topk_pick(Geometry geo, const float* __restrict__ e, TopkWorkspace ws, TopkOptions opt,
+                                                             uint32_t use_guess) {
   __shared__ PickShared sh;
   const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
   const TopkRow* rp = ws.rows + sc.seg;
@@ -2456,9 +2453,9 @@ __device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& ld
 
 // A part of the general route as a launch of its own.
 template <bool UNI, bool QUARTERS, int PART>
-__global__ __launch_bounds__(kWG) void k_topk_part(const uint32_t* flags, const float* __restrict__ e, Geometry geo, TopkWorkspace ws, TopkOptions opt,
+__global__ __launch_bounds__(kWG) void k_topk_part(Geometry geo, const float* __restrict__ e, TopkWorkspace ws, TopkOptions opt,
                                                    uint32_t use_guess) {
-  if (table_u32(flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
+  if (table_u32(ws.flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
   __shared__ GeneralShared sh;
   __shared__ std::conditional_t<PART == 0, Level0Shared, std::conditional_t<PART == 1, Level1Shared,
                                 std::conditional_t<PART == 2, Level2Shared, CountShared>>> lds;
@@ -3239,8 +3236,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   launch_lds(L, kSlotPassA, first, grid_first, wg, lds_first, stream, geo, g, e, ws, opt, use_guess);
   COMPAMS_CHECK_LAUNCH();
   if (pick) {
-    launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, ws.rows, ws.cand, e, geo.ld, geo.d, geo.k, opt.cap,
-           geo.num_chunks, use_guess, geo, ws, opt);
+    launch(L, kSlotPick, k_topk_pick, dim3(1, geo.n), dim3(kPickThreads), stream, geo, e, ws, opt, use_guess);
     COMPAMS_CHECK_LAUNCH();
   } else {
     // the selection in one launch for the rows whose threshold lies in the band; it clears the rows' "fast" mark
@@ -3262,13 +3258,13 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
       // level 0 by about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
       // lists are short (measured on the headline workload: 37 us with 128 workgroups per row, 23 us with 32)
       const uint32_t g0 = std::min((512 + geo.n - 1) / geo.n, G);
-      launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel0, k_topk_part<true, false, 0>, dim3(g0, geo.n), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel1, k_topk_part<true, false, 1>, dim3(G, geo.n), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel2, k_topk_part<true, false, 2>, dim3(G, geo.n), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel2, k_topk_part<true, false, 2>, dim3(G, geo.n), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotCount, paged ? k_topk_part<true, true, 3> : k_topk_part<true, false, 3>, dim3(count_blocks, geo.n), wg, stream, ws.flags, e, geo,
+      launch(L, kSlotCount, paged ? k_topk_part<true, true, 3> : k_topk_part<true, false, 3>, dim3(count_blocks, geo.n), wg, stream, geo, e,
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
@@ -3314,13 +3310,13 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
       launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
-      launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel1, k_topk_part<false, false, 1>, dim3(flat.wg_sweep), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel1, k_topk_part<false, false, 1>, dim3(flat.wg_sweep), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotLevel2, k_topk_part<false, false, 2>, dim3(flat.wg_sweep), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotLevel2, k_topk_part<false, false, 2>, dim3(flat.wg_sweep), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
-      launch(L, kSlotCount, k_topk_part<false, false, 3>, dim3(flat.wg_count), wg, stream, ws.flags, e, geo, ws, opt, use_guess);
+      launch(L, kSlotCount, k_topk_part<false, false, 3>, dim3(flat.wg_count), wg, stream, geo, e, ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
   }
