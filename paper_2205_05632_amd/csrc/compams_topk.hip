@@ -2486,10 +2486,12 @@ __global__ __launch_bounds__(kWG) void k_topk_part(Geometry geo, const float* __
 // writes included (with_list).
 // Where it is taken: see general_in_one().
 // ---------------------------------------------------------------------------------------------
-constexpr uint32_t kGeneralMost = 512;  // workgroups at most
+// Workgroups at most: two to a compute unit, so that there is room for 137 vector registers (128 of them: 12 bytes spilled, steps that miss
+// 0.3 to 1 us longer).
+constexpr uint32_t kGeneralMost = 512;
 
 template <bool UNI>
-__global__ __launch_bounds__(kWG, 4) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
+__global__ __launch_bounds__(kWG, 3) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
                                                       TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
   if (table_u32(flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
   __shared__ GeneralShared sh;
