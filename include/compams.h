@@ -335,8 +335,8 @@ int compams_inplace_probe(float* const* arrays, int n_arrays, size_t count, int 
  * bit for bit what the four calls above give.  Nothing is carried from one call to the next (the threshold guess comes
  * from a sample of every row), so it is the slower way to step.
  * All calls on one device share that device's array: calls that overlap in time on one device (two streams, two
- * threads) race - every one of them ends, after some seconds at worst, with undefined results; calls on one stream, or
- * otherwise ordered, do not. */
+ * threads) race, with undefined results (no kernel waits for what another call has taken away for longer than some
+ * seconds); calls on one stream, or otherwise ordered, do not. */
 #define COMPAMS_STATIC_SCRATCH_BYTES (32u << 20)
 int compams_step_static(const compams_config* cfg, const float* g, float lr, int32_t* idx_out, float* val_out,
                         void* hip_stream);

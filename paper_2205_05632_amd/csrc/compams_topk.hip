@@ -17,9 +17,10 @@
 //   band           if the threshold key does lie in the band (decided exactly from the counts): per chunk the
 //                  entries kept for certain, their prefixes inside blocks of chunks and the block totals; the
 //                  few entries of the threshold's bucket are ranked by the last workgroup of the row, which
-//                  gives tau, the ties to keep (by coordinate) and the next step's guess and band.
+//                  gives tau, the ties to keep (by coordinate) and the next step's guess, and the next step's band or,
+//                  up to 64 rows, what it follows from (final).
 //   pick           rows of at most 16 chunks, in every step that may have a guess: the whole selection by one workgroup
-//                  per row, in place of the band kernel and the general ones.
+//                  per row, in place of the band kernel and the general route.
 //   The general route (12 + 10 + 9 key bits and a zero sign bit), for every other row, in four launches or in one:
 //   level 0        histogram of the 12-bit threshold buckets, from the candidate list when the guess held (the
 //                  list then holds at least k entries), else from the row itself; for a listed row also the
@@ -35,12 +36,13 @@
 //                  chunks and the totals of every block.
 //   final          per chunk of coordinates: the position of each worker's entries in its list follows from
 //                  the block totals and prefixes; the selected entries are written there, then added in
-//                  worker order into an LDS tile of the averaged gradient, then AMSGrad.
+//                  worker order into an LDS tile of the averaged gradient, then AMSGrad.  Up to 64 rows a wavefront sets the
+//                  next step's band of the rows that band or pick has selected.
 // With top-k inside every block (one selection problem per worker and block) the same launches go over all
 // problems at once through tables of workgroup slots; problems of at most 1024 coordinates are solved by one
 // wavefront inside the first pass.
 // A step without a state of its own (the step whose tables lie in a static array) has no guess to carry over: a kernel
-// before the first pass takes one from a sample of every row.
+// before the first pass takes one, and mostly a band, from a sample of every row.
 // Zeroing the residual at the selected coordinates is not done by scattered stores: the next step's
 // first pass treats the coordinates in the previous lists as zero while it forms x (and a small kernel
 // applies the zeros when the caller asks for e).
@@ -1513,7 +1515,7 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 
 // ---------------------------------------------------------------------------------------------
 // The whole selection of a short row (at most kPickChunks chunks) by one workgroup: it takes the place of the band
-// kernel and of the four general ones, whose launches and row-wide steps cost a short row more than its bytes (4 rows
+// kernel and of the general route's four, whose launches and row-wide steps cost a short row more than its bytes (4 rows
 // of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass 31.0 -> 24.2).
 //   1. Elements: the candidate list if the guess held, else the row's stored values, chunk after chunk.  The first trip of
 //      four per thread stays in registers; what goes beyond is read again in every sweep, four trips requested together.
