@@ -96,4 +96,4 @@ def test_windows_fit():
         events.append((begin, end))
     torch.cuda.synchronize()
     us = sorted(a.elapsed_time(b) * 1e3 for a, b in events[5:])
-    assert us[len(us) * 9 // 10] < 1.2 * us[len(us) // 5], us
+    assert us[len(us) * 9 // 10] < 1.28 * us[len(us) // 5], us
