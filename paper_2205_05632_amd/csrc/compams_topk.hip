@@ -3196,9 +3196,11 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 // 236.2 / 248.2, 276.9 / 339.4; 16 x 1 M, d / 1.5, 231.4 / 302.4), and long lists are swept better by a full grid: a million entries of all
 // rows (k = d / 8: 8 x 1 M 91.9 / 90.1, 16 x 1 M 125.1 / 128.1, 64 x 200000 153.8 / 157.5, 200 x 70000 288.4 / 303.6).
 constexpr uint64_t kOneLaunchChunks = 4096;
-static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, const Geometry& geo, uint64_t chunks, bool whole) {
-  const uint64_t k = geo.k, d = geo.d, n = geo.n;
-  return use_guess && opt.band && chunks <= kOneLaunchChunks && (whole || (5 * k <= 2 * d && n * k <= 1u << 20));
+// room: entries that a worker's lists hold (a list that the caller's option keeps short is left like a row of which much is kept: 16 x 1 M,
+// k = 10000, a list of 20000 146.1 / 155.0).
+static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, const Geometry& geo, uint64_t chunks, uint64_t room, bool whole) {
+  const uint64_t k = geo.k, n = geo.n;
+  return use_guess && opt.band && chunks <= kOneLaunchChunks && (whole || (5 * k <= 2 * room && n * k <= 1u << 20));
 }
 static_assert(kOneLaunchChunks < kPagedChunks, "k_topk_general counts chunks of one segment");
 static_assert((kOneLaunchChunks + 1) * kGeneralMost < (1ull << 32), "tasks_of: a task has a chunk at least");
@@ -3251,7 +3253,7 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
              ws, opt, use_guess);
       COMPAMS_CHECK_LAUNCH();
     }
-    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * geo.num_chunks, whole)) {
+    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * geo.num_chunks, opt.cap, whole)) {
       // a task of every part to a workgroup: the second one's clearing, flushing and ticket would follow the first one's
       const uint32_t g1 = std::max(1u, std::min(kGeneralMost / geo.n, G));
       GeneralTasks tasks{{g1, g1, g1, count_blocks}, {}};
@@ -3310,7 +3312,7 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   }
   if (flat.wg_sweep) {  // none if every block is a micro problem
     const GeneralTasks tasks{{}, {flat.wg_level0, flat.wg_sweep, flat.wg_sweep, flat.wg_count}};
-    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * flat.chunk_stride, false)) {
+    if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * flat.chunk_stride, geo.d, false)) {
       launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {

@@ -3,7 +3,7 @@
 This module holds none of the method's arithmetic.  It only says how large the
 flattened parameter vector is, where the layer tensors start, and how the
 per-worker gradients (the inputs of one optimizer step) are drawn.  Both the GPU
-library's callers and the CPU checker are fed from here, with the same bytes.
+library's callers and the CPU oracle are fed from here, with the same bytes.
 
 The paper trains a CNN, LeNet-5, an LSTM and ResNet-18 on MNIST, CIFAR-10 and
 IMDB (Section 5.1, Appendix A).  None of those datasets is used here: a step's

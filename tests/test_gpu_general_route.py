@@ -131,14 +131,17 @@ def test_threshold_that_rises():
         p.close()
 
 
-@pytest.mark.parametrize("n,d,k,one", [
-    (2, 80 * CHUNK, 32 * CHUNK, True), (2, 80 * CHUNK, 32 * CHUNK + 1, False),   # two fifths of a row
-    (16, 80 * CHUNK, 16 * CHUNK, True), (16, 80 * CHUNK, 16 * CHUNK + 1, False),  # 2^20 entries of all rows
-    (64, 64 * CHUNK, 2600, True), (64, 64 * CHUNK + 1, 2600, False)])             # 4096 chunks
-def test_which_form(n, d, k, one):
+@pytest.mark.parametrize("n,d,k,one,cap", [
+    (2, 80 * CHUNK, 32 * CHUNK, True, 0), (2, 80 * CHUNK, 32 * CHUNK + 1, False, 0),    # two fifths of a row
+    (16, 80 * CHUNK, 16 * CHUNK, True, 0), (16, 80 * CHUNK, 16 * CHUNK + 1, False, 0),  # 2^20 entries of all rows
+    (64, 64 * CHUNK, 2600, True, 0), (64, 64 * CHUNK + 1, 2600, False, 0),              # 4096 chunks
+    (4, 80 * CHUNK, 2000, True, 5000), (4, 80 * CHUNK, 2000, False, 4999)])             # two fifths of a list
+def test_which_form(n, d, k, one, cap):
     """Steps that keep much take the route every time, and its four launches: 16 x 1 M, k = d / 2, 201 us, in one launch 248."""
     rng = np.random.default_rng(k)
     p = Pair(n, d, np.zeros(d), B.TOPK, k=k)
+    if cap:
+        p.gpu.set_option(B.OPT_CANDIDATE_CAP, cap)
     base = rng.standard_normal(d).astype(np.float32)
     for t in range(4):
         p.gpu.profile_enable(1)
