@@ -36,7 +36,7 @@
 //                  chunks and the totals of every block.
 //   final          per chunk of coordinates: the position of each worker's entries in its list follows from
 //                  the block totals and prefixes; the selected entries are written there, then added in
-//                  worker order into an LDS tile of the averaged gradient, then AMSGrad.  Up to 64 rows a wavefront sets the
+//                  worker order into an LDS tile of the averaged gradient, then AMSGrad.  Up to 64 rows it also sets the
 //                  next step's band of the rows that band or pick has selected.
 // With top-k inside every block (one selection problem per worker and block) the same launches go over all
 // problems at once through tables of workgroup slots; problems of at most 1024 coordinates are solved by one
@@ -1027,14 +1027,16 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
 }
 
 // The kernels that select in one launch end in one workgroup's chain, of which the above (divisions and roots, one after the other)
-// was 1 to 1.5 us: they leave what it needs in the control block, and a wavefront of the last kernel goes through it beside
-// the others' work (a step of 4 x 65536, k = 655: 24.3 us, with that and the ranking of k_topk_pick 23.2; 16 x 1 M 70.4, now 69.6).
-// Only where there is a lane for every row: more of them keep that wavefront's compute unit busy, 1.4 us for every 64, while in the
+// was 1 to 1.5 us: they leave what it needs in the control block, and a workgroup of the last kernel goes through it beside
+// the others' work, one more than there are chunks (a step of 4 x 65536, k = 655: 24.3 us, with that and the ranking of k_topk_pick 23.2;
+// 16 x 1 M 70.4, now 69.6).  Top-k inside blocks: a wavefront of every problem's first chunk; in whole rows that kept the first chunk
+// 0.4 us longer, in every step (4 x 65536 23.26 us a step, now 23.13).
+// Only where there is a lane of a wavefront for every row: more of them keep its compute unit busy, 1.4 us for every 64, while in the
 // selecting kernel every row has a workgroup of its own (us, all rows in the selecting kernel / in the last one: a step of 32 x 600000
 // 75.4 / 74.6, 24 x 300000 49.5 / 48.9, 64 x 100000 59.7 / 59.1, 64 x 4096 43.4 / 43.7, 300 x 4096 134.7 / 140.8, 4000 x 4096 1547 / 1640; the
 // workers' half 300 x 4096 27.2 / 33.8, 4000 x 4096 120 / 218).
 // population: entries of the window lo .. hi that was looked at (0: none), ref: a key in it.
-__device__ __forceinline__ bool window_later(uint32_t n) { return n <= 64; }
+__host__ __device__ __forceinline__ bool window_later(uint32_t n) { return n <= 64; }
 __device__ __forceinline__ float population_noise(uint32_t population, uint32_t lo, uint32_t hi, uint32_t ref, uint32_t k) {
   return population ? 8.0f * ((__uint_as_float(hi) - __uint_as_float(lo)) / __uint_as_float(ref)) * sqrtf(static_cast<float>(k)) /
                           static_cast<float>(population)
@@ -2776,12 +2778,16 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
     ws.flags[threadIdx.x < kQueues ? queue_word(threadIdx.x) : 0] = 0;
   // The workers' half has a workgroup per tile of workers, the others one that goes through all tiles.
   const uint32_t i_first = ROLE == kWorkerHalf ? blockIdx.y * kTileWorkers : 0u;
+  if (UNI && !CLEAR && ROLE != kServerHalf && c == geo.num_chunks) {  // the workgroup beyond the chunks
+    if (i_first == 0 && threadIdx.x < geo.n) set_next(ws.rows + threadIdx.x, f.k_loc, opt);
+    return;
+  }
   if (ROLE != kServerHalf && c == 0 && i_first == 0) {
     for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {  // the next step's first pass allocates its candidate lists from the start
       ws.rows[f.row0 + i * f.row_stride].cursor = 0;
       ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
     }
-    if (!CLEAR && window_later(geo.n) && wave == NW - 1 && lane < geo.n)  // (it has workers of its own only from NW on)
+    if (!UNI && !CLEAR && window_later(geo.n) && wave == NW - 1 && lane < geo.n)  // (it has workers of its own only from NW on)
       set_next(ws.rows + f.row0 + lane * f.row_stride, f.k_loc, opt);
   }
   if (ROLE != kWorkerHalf) {  // (before the tile's barrier: other wavefronts may add here)
@@ -3155,11 +3161,12 @@ namespace {
 // The last kernel with NW wavefronts per chunk.
 template <int ROLE, bool UNI, int NW, bool CLEAR, bool QUARTERS, typename... Args>
 void launch_final_of(uint32_t n, int cached_arrays, Launcher* L, uint32_t workgroups, hipStream_t stream, Args... args) {
-  const dim3 grid(workgroups), wg(NW * 64);
+  const uint32_t more = UNI && !CLEAR && ROLE != kServerHalf && window_later(n) ? 1 : 0;  // for the next step's windows
+  const dim3 grid(workgroups + more), wg(NW * 64);
   if constexpr (ROLE == kWorkerHalf) {
     // No state, and no order among the workers: a workgroup per tile of them.  With all tiles in one workgroup a few chunks
     // leave the chip idle (50000 coordinates in seven blocks: the half of 300 workers 128 us / 76 as here, of 64 52 / 45).
-    const dim3 grid_tiles(workgroups, (n + kTileWorkers - 1) / kTileWorkers);
+    const dim3 grid_tiles(workgroups + more, (n + kTileWorkers - 1) / kTileWorkers);
     launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 0, NW, CLEAR, QUARTERS>, grid_tiles, wg, stream, args...);
   } else if constexpr (CLEAR && NW == kFinalFew) {  // (so short that its whole state stays in the memory-side cache)
     launch(L, kSlotTopkFinal, k_topk_final<ROLE, UNI, 4, NW, CLEAR, QUARTERS>, grid, wg, stream, args...);
