@@ -61,9 +61,9 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct Layout {
   size_t total;
   // top-k
-  size_t rows, flags, counters, hist0, hist1, hist1x, hist2, bhist, xcur, chunk_rec, blk, blk_prefix, sel_off, desc, desc2, bnd, bnd_sel, cand, band,
-      idx, val, tau, count_gt, wire_total, wire_tile_off, wire_tile_sum, sel_off_srv, segs, map_first, map_level0, map_sweep,
-      map_count, map_final, micro_list;
+  size_t rows, flags, counters, hist0, hist1, hist1x, hist2, bhist, xcur, chunk_rec, blk, blk_prefix, sel_off, desc, desc2, bnd,
+      bnd_sel, cand, band, idx, val, tau, count_gt, wire_total, wire_tile_off, wire_tile_sum, sel_off_srv, segs, map_first,
+      map_level0, map_sweep, map_count, map_final, micro_list;
   // block-sign
   size_t offsets, chunk_block, acc, special, ticket, scales, bits;
   uint32_t acc_replicas;
@@ -145,16 +145,17 @@ std::vector<BlockShape> block_shapes(const compams_config* c) {
   return v;
 }
 
-// What a window from a sample of kSample of d coordinates holds: three deviations and two sampled entries on either side of the expected
-// count, and what the buckets of a sixteenth of an octave at its ends add to that, three tenths of k each on normal values.
+// What a window from a sample of kSample of d coordinates holds: three deviations and two sampled entries on either side
+// of the expected count, and what the buckets of a sixteenth of an octave at its ends add to that, three tenths of k each
+// on normal values.
 double sampled_window(int64_t d, int64_t k) {
   const double each = static_cast<double>(d) / kSample, share = static_cast<double>(k) / each;
   return (6.0 * std::sqrt(share) + 4.0 + 0.6 * share) * each;
 }
 
-// What a layout is for: a context's workspace, the tables of compams_step_static() (which has no messages to pack, and a band list of
-// static_band entries), or the size by which that call decides what it takes.  The last is a measure of its own,
-// so that what the call takes does not change with the tables.
+// What a layout is for: a context's workspace, the tables of compams_step_static() (which has no messages to pack, and a
+// band list of static_band entries), or the size by which that call decides what it takes.  The last is a measure of its
+// own, so that what the call takes does not change with the tables.
 enum LayoutFor { kForContext, kForStatic, kStaticMeasure };
 
 Layout make_layout(const compams_config* c, LayoutFor purpose = kForContext, uint32_t static_band = 0) {
@@ -519,7 +520,10 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
         const std::vector<BlockShape> shapes = block_shapes(cfg);
         const size_t M = shapes.size();
         uint64_t chunks = 0, caps = 0, bcaps = 0, bhists = 0;
-        for (const BlockShape& b : shapes) { chunks += b.nc; caps += cand_pitch(b.cap); bcaps += b.band_cap; bhists += b.micro ? 0 : band_buckets(b.k); }
+        for (const BlockShape& b : shapes) {
+          chunks += b.nc; caps += cand_pitch(b.cap); bcaps += b.band_cap;
+          bhists += b.micro ? 0 : band_buckets(b.k);
+        }
         uint32_t cursor_sets = 0;
         segs.resize(static_cast<size_t>(cfg->n) * M);
         for (int64_t i = 0; i < cfg->n; ++i) {
@@ -568,8 +572,8 @@ int compams_init(const compams_config* cfg, compams_ctx** out) {
       ok(hipMemcpy(w + lay.map_count, m_count.data(), m_count.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       ok(hipMemcpy(w + lay.map_final, m_final.data(), m_final.size() * sizeof(WgSlot), hipMemcpyHostToDevice));
       if (!micro.empty()) ok(hipMemcpy(w + lay.micro_list, micro.data(), micro.size() * 4, hipMemcpyHostToDevice));
-      if (m_first.size() != lay.flat.wg_first || m_level0.size() != lay.flat.wg_level0 || m_sweep.size() != lay.flat.wg_sweep || m_count.size() != lay.flat.wg_count ||
-          m_final.size() != lay.flat.wg_final || micro.size() != lay.num_micro)
+      if (m_first.size() != lay.flat.wg_first || m_level0.size() != lay.flat.wg_level0 || m_sweep.size() != lay.flat.wg_sweep ||
+          m_count.size() != lay.flat.wg_count || m_final.size() != lay.flat.wg_final || micro.size() != lay.num_micro)
         ok(hipErrorInvalidValue);  // the tables and the launch sizes come from the same shapes
       t.segs = reinterpret_cast<const Seg*>(w + lay.segs);
       t.map_first = reinterpret_cast<const WgSlot*>(w + lay.map_first);
@@ -993,10 +997,10 @@ int compams_step_static(const compams_config* cfg, const float* g, float lr, int
   try {
     if (make_layout(cfg, kStaticMeasure).total > most) return COMPAMS_WORKSPACE_TOO_SMALL;
     ctx.lay = make_layout(cfg, kForStatic);
-    // A band list of what room there is, up to the candidate list's length, or none where a sampled window would hardly fit: a row whose
-    // window does not fit costs the call the band kernel and the general route as well (8 x 2893126, k = 5860, a list of 4 k + 8192: two
-    // calls out of three, 122 us where the others took 105; 4 x 6 M, k = 87891, which leaves room for 150000 entries, 162 us with windows,
-    // 144 without).
+    // A band list of what room there is, up to the candidate list's length, or none where a sampled window would hardly
+    // fit: a row whose window does not fit costs the call the band kernel and the general route as well (8 x 2893126, k =
+    // 5860, a list of 4 k + 8192: two calls out of three, 122 us where the others took 105; 4 x 6 M, k = 87891, which
+    // leaves room for 150000 entries, 162 us with windows, 144 without).
     const size_t room = most - std::min<size_t>(most, ctx.lay.total + 1024 + static_cast<size_t>(cfg->n) * ctx.lay.num_chunks * 8);
     uint32_t band = static_cast<uint32_t>(std::min<size_t>(
         {kBandMaxEntries, ctx.lay.cap_alloc, room / (8 * static_cast<size_t>(cfg->n))}));

@@ -11,10 +11,10 @@
 // the result unique.  Inside a lane the additions run in fp64 over windows of exponents narrow enough that
 // no addition rounds.  The sum is rounded once to double, divided by d_B in double and rounded to fp32.
 //
-// Pass 1 forms x (stored in place of e), its sign words and the sums, a small kernel (or the last workgroup of a short row, or
-// the server kernel where no block reaches beyond a chunk) turns sums into scales, and the server kernel adds the n workers' +-mu in worker order before the AMSGrad update.  The
-// residual e = x - sign(x) * mu is applied by the next step's pass 1 as it reads e (or by the stand-alone
-// residual kernel when e is asked for).
+// Pass 1 forms x (stored in place of e), its sign words and the sums, a small kernel (or the last workgroup of a short
+// row, or the server kernel where no block reaches beyond a chunk) turns sums into scales, and the server kernel adds the
+// n workers' +-mu in worker order before the AMSGrad update.  The residual e = x - sign(x) * mu is applied by the next
+// step's pass 1 as it reads e (or by the stand-alone residual kernel when e is asked for).
 
 #include <type_traits>
 
@@ -48,9 +48,9 @@ __device__ __forceinline__ Fixed to_fixed(uint32_t bits) {
   return f;
 }
 
-// Sum / largest over the wavefront, the same in every lane: neighbours, quads and halves of each row of 16 lanes, then the rows'
-// last lanes into the rows after them (data-parallel moves: three vector instructions a step, where a step through the LDS
-// crossbar waits for it).
+// Sum / largest over the wavefront, the same in every lane: neighbours, quads and halves of each row of 16 lanes, then
+// the rows' last lanes into the rows after them (data-parallel moves: three vector instructions a step, where a step
+// through the LDS crossbar waits for it).
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t moved(uint32_t v) {  // 0 where nothing arrives
   return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
@@ -306,7 +306,8 @@ __device__ __forceinline__ void quarter_in_block(const float4 (&gq)[kQuarter], c
       kmin = min(kmin, key);
     }
     if (ok[0]) store_stream4(er + q0 + u * 256 + lane * 4, make_float4(xv[0], xv[1], xv[2], xv[3]));
-    // every eight lanes hold a word of the round; lane u of them keeps that of round u for one store of the quarter's 128 bytes
+    // every eight lanes hold a word of the round; lane u of them keeps that of round u for one store of the quarter's 128
+    // bytes
     const uint32_t word = or_over_8_lanes(nib << ((lane & 7u) * 4u));
     my_word = (lane & 7u) == static_cast<uint32_t>(u) ? word : my_word;
   }
@@ -418,8 +419,8 @@ __global__ __launch_bounds__(kWG) void k_bs_finalize(Geometry geo, BlocksignWork
 constexpr uint32_t kBsScalesChunks = 64, kBsScalesBlocks = 64;
 // What it saves is the launch of k_bs_finalize, 1.5 us, or 4.5 us where a block has several sets of digits.  What it costs
 // grows with the rows' length and with the whole grid, because every workgroup waits for its own atomics before it
-// ends.  Measured (us gained; rows x chunks), one set of digits: 256 x 6 +0.1, 128 x 8 +0.6, 16 x 12 -0.4, 4 x 32 +0.2, 8 x 24
-// +0.8, 4 x 64 -0.9, 16 x 64 -7; several: 256 x 16 +1.0, 32 x 24 +0.8, 16 x 32 -0.3, 8 x 64 -0.4, 16 x 64 -3.8.
+// ends.  Measured (us gained; rows x chunks), one set of digits: 256 x 6 +0.1, 128 x 8 +0.6, 16 x 12 -0.4, 4 x 32 +0.2, 8
+// x 24 +0.8, 4 x 64 -0.9, 16 x 64 -7; several: 256 x 16 +1.0, 32 x 24 +0.8, 16 x 32 -0.3, 8 x 64 -0.4, 16 x 64 -3.8.
 inline bool scales_in_first_pass(const Geometry& geo, const BlocksignWorkspace& ws) {
   if (geo.num_chunks > kBsScalesChunks || geo.num_blocks > kBsScalesBlocks) return false;
   const bool several = ws.acc_replicas > 1;
@@ -477,12 +478,12 @@ __device__ __forceinline__ void row_scales(uint32_t row, const Geometry& geo, co
 // layers, 342 either way.  A quarter that lies inside one block -- all but a few per row -- is summed in a register window
 // placed by the quarter's own largest magnitude and goes to the block's digits with at most three atomics; a quarter that
 // meets block ends goes through the blocks it meets, round by round.  Either way it works from the one batch of loads in its
-// registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 634 / 469
-// us, of 1000 654 / 499; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still one sum (else
-// round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5; not in pages, where one quarter more or less
-// round by round is nothing and the second form in the kernel's code cost 8 x 124439808 1910 -> 1934 us).  Up to 96 registers
-// cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending residual update of the previous
-// step is applied to e as it is read.
+// registers (a step with the rounds loaded again, one after the other / from the batch: 16 x 11181642, blocks of 256 634
+// / 469 us, of 1000 654 / 499; 8 x 3 M, blocks of 1000 109 / 87), and where the row ends inside the quarter it is still
+// one sum (else round by round: 8 x 300000, blocks of 4096 20.5 / 17.8; 4 x 60000 13.0 / 11.5; not in pages, where one
+// quarter more or less round by round is nothing and the second form in the kernel's code cost 8 x 124439808 1910 -> 1934
+// us).  Up to 96 registers cost nothing: five workgroups per compute unit are all there are (kStreamLds).  The pending
+// residual update of the previous step is applied to e as it is read.
 // ---------------------------------------------------------------------------------------------
 template <bool PEND, bool PAGED>
 __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, const float* __restrict__ g,
@@ -520,8 +521,8 @@ __device__ __forceinline__ void bs_lean_quarter(uint32_t group, uint32_t row, co
   const uint32_t replica = group % ws.acc_replicas;
   const bool cut = !PAGED && q0 + kQuarter * 256 > d;  // by the row's end
   if (table_u32(off, b + 1) < (cut ? d : q0 + kQuarter * 256)) {  // a scalar condition
-    // The quarter meets block ends, or, in pages, the row's end.  (The rounds move up: the batch at a run-time index would lie in
-    // scratch memory.)
+    // The quarter meets block ends, or, in pages, the row's end.  (The rounds move up: the batch at a run-time index
+    // would lie in scratch memory.)
 #pragma unroll 1
     for (uint32_t j0 = q0; j0 < q0 + kQuarter * 256 && j0 < d; j0 += 256) {
       while (table_u32(off, b + 1) <= j0) ++b;
@@ -615,17 +616,19 @@ __global__ __launch_bounds__(kWG) void k_bs_pass2(float* __restrict__ e, Geometr
 constexpr int kBsWorkers = 8;  // workers whose sign words and scales are requested together (rounds that meet block ends)
 
 // Wavefronts per chunk: a wavefront takes two rounds and asks for everything it needs at once.  (Four rounds, the next one's
-// state requested while one is updated: 16 x 11.2 M 68 -> 75 us, 8 x 25.6 M 145 -> 151, 8 x 60 M 334 -> 336, 8 x 124.4 M 690 -> 686.)
+// state requested while one is updated: 16 x 11.2 M 68 -> 75 us, 8 x 25.6 M 145 -> 151, 8 x 60 M 334 -> 336, 8 x 124.4 M
+// 690 -> 686.)
 constexpr int kBsServerWaves = 8;
 constexpr uint32_t kBsServerScales = kBsServerWaves * 64;  // scales that a workgroup's threads form at most
 
-// Whether the server kernel of a whole step forms them: wherever every block lies inside one chunk, which is then the only one to look
-// at its digits, and there is a thread for every worker and block.  It saves the launch of k_bs_finalize, or the chain of the row's
-// last workgroup in the first pass, and costs a workgroup one thread's conversion of a sum.  Measured (us a step, scales in the first
-// pass or by a launch / in the server kernel; rows x chunks / block): 4 x 1 / 4096 9.7 / 9.3, 4 x 16 / 4096 10.8 / 10.8, 4 x 16 / 256
-// 16.0 / 14.3, 8 x 64 / 4096 15.3 / 13.8, 64 x 64 / 4096 52.3 / 50.0, 16 x 256 / 4096 47.4 / 45.7, 16 x 1024 / 4096 152.0 / 152.0, / 256
-// 188.1 / 182.8, 8 x 6000 / 4096 498.5 / 494.3, / 256 579 / 563.  (Held to seven wavefronts per SIMD, as the kernel without them, it
-// spilled nine registers: 4 x 16 / 4096 11.6, 16 x 1024 / 4096 156, 8 x 6000 / 4096 504.)
+// Whether the server kernel of a whole step forms them: wherever every block lies inside one chunk, which is then the
+// only one to look at its digits, and there is a thread for every worker and block.  It saves the launch of
+// k_bs_finalize, or the chain of the row's last workgroup in the first pass, and costs a workgroup one thread's
+// conversion of a sum.  Measured (us a step, scales in the first pass or by a launch / in the server kernel; rows x
+// chunks / block): 4 x 1 / 4096 9.7 / 9.3, 4 x 16 / 4096 10.8 / 10.8, 4 x 16 / 256 16.0 / 14.3, 8 x 64 / 4096 15.3 /
+// 13.8, 64 x 64 / 4096 52.3 / 50.0, 16 x 256 / 4096 47.4 / 45.7, 16 x 1024 / 4096 152.0 / 152.0, / 256 188.1 / 182.8, 8 x
+// 6000 / 4096 498.5 / 494.3, / 256 579 / 563.  (Held to seven wavefronts per SIMD, as the kernel without them, it spilled
+// nine registers: 4 x 16 / 4096 11.6, 16 x 1024 / 4096 156, 8 x 6000 / 4096 504.)
 inline bool scales_in_server(const Geometry& geo, const BlocksignWorkspace& ws) {
   return ws.chunk_blocks && static_cast<uint64_t>(geo.n) * ws.chunk_blocks <= kBsServerScales;
 }
@@ -832,8 +835,8 @@ __global__ __launch_bounds__(kBsServerWaves * 64) __attribute__((amdgpu_waves_pe
 // Bound by memory: n rows and the four state arrays.  A wavefront takes one round (1 KB of every array), a workgroup
 // the same kilobyte of its die's page in four spans (see page_quarter): n + 4 streams through the same addresses are
 // 13 % faster so than a workgroup per 4 KB in address order (16 x 11.2 M, state from HBM / cached: plain order, eight rows
-// 195 / 155 us; pages, eight rows 174 / 151; pages, sixteen 171 / 149), and no slower anywhere: 8 x 300000 7.2 / 7.4, 16 x 300000
-// 11.0 / 11.3, 16 x 3 M 51.7 / 52.3.  ROWS: how many rows are requested at once (identity_rows).
+// 195 / 155 us; pages, eight rows 174 / 151; pages, sixteen 171 / 149), and no slower anywhere: 8 x 300000 7.2 / 7.4, 16
+// x 300000 11.0 / 11.3, 16 x 3 M 51.7 / 52.3.  ROWS: how many rows are requested at once (identity_rows).
 // ---------------------------------------------------------------------------------------------
 template <int NC, uint32_t ROWS>  // NC: how many of theta, m, v, vhat are cached (the others are streamed)
 __global__ __launch_bounds__(kWG) void k_none_amsgrad(const float* __restrict__ g, float* __restrict__ theta,
@@ -960,11 +963,11 @@ static hipError_t server_lines(bool scales, const Geometry& geo, const Blocksign
 #define COMPAMS_BS_AMSGRAD(NC) k_bs_amsgrad<NC, false>
 #define COMPAMS_BS_AMSGRAD_SCALES(NC) k_bs_amsgrad<NC, true>
   if (scales) {
-    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD_SCALES, grid, wg, stream, theta, m, v, vhat, ws.chunk_block,
-                             ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD_SCALES, grid, wg, stream, theta, m, v, vhat,
+                             ws.chunk_block, ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
   } else {
-    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, ws.chunk_block, ws.offsets,
-                             geo.d, geo.num_chunks, geo, ws, ap);
+    COMPAMS_LAUNCH_BY_CACHED(ap.cached_arrays, L, kSlotBsAms, COMPAMS_BS_AMSGRAD, grid, wg, stream, theta, m, v, vhat, ws.chunk_block,
+                             ws.offsets, geo.d, geo.num_chunks, geo, ws, ap);
   }
 #undef COMPAMS_BS_AMSGRAD
 #undef COMPAMS_BS_AMSGRAD_SCALES
@@ -1010,11 +1013,12 @@ hipError_t blocksign_apply_residual(const Geometry& geo, const BlocksignWorkspac
   return hipGetLastError();
 }
 
-// Rows that the identity compressor's kernel requests at once: sixteen in large problems, eight in smaller ones and wherever there
-// are no more than eight (but for one and two workers of a large one: the longer form has fewer wavefronts in flight, as the pages
-// like it).  us a step, three contexts in turn / one alone, sixteen and eight: 8 x 4 M 44.0 41.3 / 43.4 40.6; 16 x 4 M 64.6 60.8 /
-// 64.2 60.5; 4 x 6 M 48.0 44.6 / 46.1 42.5; 8 x 12 M 130.5 129.5 / 123.4 112.7; 4 x 20 M 161.8 163.5 / 151.7 143.2; but 16 x 8 M 129.2
-// 128.8 / 122.1 118.2; 24 x 8 M 166.8 170.0; 16 x 12 M 189.5 192.0; 32 x 16 M 418.6 431.2; 1 x 12 M 71.0 72.9; 2 x 16 M 104.4 107.3.
+// Rows that the identity compressor's kernel requests at once: sixteen in large problems, eight in smaller ones and
+// wherever there are no more than eight (but for one and two workers of a large one: the longer form has fewer wavefronts
+// in flight, as the pages like it).  us a step, three contexts in turn / one alone, sixteen and eight: 8 x 4 M 44.0 41.3
+// / 43.4 40.6; 16 x 4 M 64.6 60.8 / 64.2 60.5; 4 x 6 M 48.0 44.6 / 46.1 42.5; 8 x 12 M 130.5 129.5 / 123.4 112.7; 4 x 20
+// M 161.8 163.5 / 151.7 143.2; but 16 x 8 M 129.2 128.8 / 122.1 118.2; 24 x 8 M 166.8 170.0; 16 x 12 M 189.5 192.0; 32 x
+// 16 M 418.6 431.2; 1 x 12 M 71.0 72.9; 2 x 16 M 104.4 107.3.
 static uint32_t identity_rows(const Geometry& geo) {
   constexpr uint32_t kFewCoords = 7000000;
   return geo.d <= kFewCoords || (geo.n > 2 && geo.n <= 8) ? 8 : 16;

@@ -83,8 +83,8 @@ __device__ __forceinline__ void store_stream4(float* p, const float4& x) {
 // and it can be an operand of every lane's arithmetic without a register per lane.
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// theta, m, v, vhat are touched once per step.  CACHED: by ordinary accesses, which leave the line in the memory-side cache for the
-// next step; else by streaming ones.
+// theta, m, v, vhat are touched once per step.  CACHED: by ordinary accesses, which leave the line in the memory-side
+// cache for the next step; else by streaming ones.
 template <bool CACHED>
 __device__ __forceinline__ float4 load_state4(const float* base, uint32_t at) {
   if constexpr (CACHED) return *reinterpret_cast<const float4*>(base + at);
@@ -95,8 +95,8 @@ __device__ __forceinline__ void store_state4(float* base, uint32_t at, const flo
   if constexpr (CACHED) *reinterpret_cast<float4*>(base + at) = x;
   else store_stream4(base + at, x);
 }
-// A store that leaves the line there and writes it through, for the kernel that reads the gradients in the same pass: no dirty lines
-// to be written out in the way of what follows.  base: the same in every lane.
+// A store that leaves the line there and writes it through, for the kernel that reads the gradients in the same pass: no
+// dirty lines to be written out in the way of what follows.  base: the same in every lane.
 template <bool CACHED>
 __device__ __forceinline__ void store_through4(float* base, uint32_t at, const float4& x) {
   if constexpr (CACHED) {

@@ -24,10 +24,11 @@ constexpr int kChunk = 4096;             // coordinates per chunk
 constexpr int kRounds = kChunk / 256;    // rounds per chunk
 
 // Which part of memory a die works on.  Consecutive workgroups run on the eight dies (XCDs) in turn, and the memory
-// channels follow each other through every span of eight 4 KB pages.  Where the workgroups of a die always take the same page
-// of a span, each channel is asked by one die only: a first pass's traffic (two arrays read, one written, 2.1 GB) streams at
-// 6.75 TB/s so, at 6.2 with a workgroup per 16 KB in address order, at 6.05 with pages that change from group to group (pages
-// of 1 and 2 KB do as well, 512 B 6.6, 256 B 5.9).  A page is a quarter of a chunk: one wavefront's part of the dense passes.
+// channels follow each other through every span of eight 4 KB pages.  Where the workgroups of a die always take the same
+// page of a span, each channel is asked by one die only: a first pass's traffic (two arrays read, one written, 2.1 GB)
+// streams at 6.75 TB/s so, at 6.2 with a workgroup per 16 KB in address order, at 6.05 with pages that change from group
+// to group (pages of 1 and 2 KB do as well, 512 B 6.6, 256 B 5.9).  A page is a quarter of a chunk: one wavefront's part
+// of the dense passes.
 constexpr uint32_t kPageCoords = 1024;
 constexpr uint32_t kDies = 8;
 constexpr uint32_t kSpanCoords = kDies * kPageCoords;  // two chunks
@@ -42,10 +43,10 @@ __device__ __forceinline__ Quarter page_quarter(uint32_t group, uint32_t wave, u
   const uint32_t page = (group + turn) % kDies, span = group / kDies * kSpansPerGroup + wave;
   return {span * (kSpanCoords / kChunk) + page / kWaves, page % kWaves};
 }
-// A dense pass asks for this much LDS that it has no use for: four or five workgroups per compute unit are enough to keep the
-// memory busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with five, 317
-// with four, 373 with three).  Block-sign's first pass does so in chunk order as well (a step, with / without: 8 x 12 M 269.5 /
-// 271.9 us, 4 x 12 M 174.1 / 175.5; the same below 3 M).
+// A dense pass asks for this much LDS that it has no use for: four or five workgroups per compute unit are enough to keep
+// the memory busy, and with eight the channels change between more pages (the traffic above: 330 us with eight, 318 with
+// five, 317 with four, 373 with three).  Block-sign's first pass does so in chunk order as well (a step, with / without:
+// 8 x 12 M 269.5 / 271.9 us, 4 x 12 M 174.1 / 175.5; the same below 3 M).
 constexpr size_t kStreamLds = 32768;
 inline uint32_t page_groups(uint32_t num_chunks) { return (num_chunks + kDies - 1) / kDies * kDies; }
 static_assert(kPageCoords * kWaves == kChunk, "a page is a wavefront's quarter of a chunk");
@@ -68,12 +69,13 @@ constexpr uint32_t kMicroFlag = 0x80000000u;  // WgSlot.seg of a first-pass work
 
 // The band and the counting kernel split a row's chunks into at most kMaxCountBlocks contiguous blocks of count_cpw
 // chunks (four wavefronts, eight chunks at a time: a multiple of 32).  d < 2^31 gives at most 2^19 chunks.  Rows of up
-// to 1024 chunks have blocks of 8, two chunks to a wavefront, while there are fewer than kShortChunks chunks in all rows: blocks
-// of 32 leave most of the chip idle then (4 rows of 300007: the counting kernel 18.1 -> 10.1 us; 16 rows of 1 M: the band
-// kernel 14.6 -> 12.6 us).  In larger grids the row's histogram, which every block of the band kernel reads, outweighs
-// that; where rows miss their window and have to be counted, the shorter blocks still gain.  Measured (us, blocks of 32 / of 8;
-// band kernel, counting kernel of rows that miss): 16 x 640 chunks 15.6 / 15.6, 13.5 / 8.9; 64 x 245 15.2 / 17.7, 20.0 / 10.8; 64 x
-// 512 17.4 / 26.9, 26.1 / 15.9; 64 x 1024 23.9 / 42.8, 22.3 / 16.1; long rows, 4 x 2048: 16.1 / 18.4, 14.8 / 9.2.
+// to 1024 chunks have blocks of 8, two chunks to a wavefront, while there are fewer than kShortChunks chunks in all rows:
+// blocks of 32 leave most of the chip idle then (4 rows of 300007: the counting kernel 18.1 -> 10.1 us; 16 rows of 1 M:
+// the band kernel 14.6 -> 12.6 us).  In larger grids the row's histogram, which every block of the band kernel reads,
+// outweighs that; where rows miss their window and have to be counted, the shorter blocks still gain.  Measured (us,
+// blocks of 32 / of 8; band kernel, counting kernel of rows that miss): 16 x 640 chunks 15.6 / 15.6, 13.5 / 8.9; 64 x 245
+// 15.2 / 17.7, 20.0 / 10.8; 64 x 512 17.4 / 26.9, 26.1 / 15.9; 64 x 1024 23.9 / 42.8, 22.3 / 16.1; long rows, 4 x 2048:
+// 16.1 / 18.4, 14.8 / 9.2.
 constexpr uint32_t kMaxCountBlocks = 256;
 constexpr uint32_t kMaxCountCpw = 2048;
 constexpr uint32_t kShortChunks = 32768;
@@ -101,15 +103,15 @@ constexpr uint32_t kCursorPitch = 32;  // words between the cursors of a problem
 constexpr uint32_t kSubListMinChunks = 64;
 constexpr uint32_t kNoCursorSet = 0xffffffffu;
 // So many chunks in all rows (one selection per row, rows of several runs) have their first pass in pages, with a segment of
-// the lists for every quarter of a chunk.  First pass (us; k = d / 100, chunks in order / pages): 8 x 2730 chunks 170 / 172; 2 x 6240
-// 99.7 / 99.7; 16 x 2730 339 / 339; 8 x 6240 406 / 385; 16 x 6240 818 / 755; k = d / 1000, 8 x 3907 245 / 237, 8 x 30381 1977 / 1837.
-// The whole step, three contexts in turn: 64 x 733 465 / 467, 64 x 977 619 / 615, 32 x 1465 477 / 478, 24 x 1954 484 / 476, 16 x
-// 2930 494 / 490, 3 x 17090 823 / 815.
+// the lists for every quarter of a chunk.  First pass (us; k = d / 100, chunks in order / pages): 8 x 2730 chunks 170 /
+// 172; 2 x 6240 99.7 / 99.7; 16 x 2730 339 / 339; 8 x 6240 406 / 385; 16 x 6240 818 / 755; k = d / 1000, 8 x 3907 245 /
+// 237, 8 x 30381 1977 / 1837. The whole step, three contexts in turn: 64 x 733 465 / 467, 64 x 977 619 / 615, 32 x 1465
+// 477 / 478, 24 x 1954 484 / 476, 16 x 2930 494 / 490, 3 x 17090 823 / 815.
 constexpr uint32_t kPagedChunks = 45056;
 static_assert(kPagedChunks >= kShortChunks, "rows in pages have blocks of 32 chunks and more: eight chunks to a wavefront");
-// Block-sign, which keeps no lists, from so many on (first pass, chunks in order / pages): 16 x 733 chunks 96.7 / 99.2; 8 x 2730
-// 169 / 172; 2 x 12208 186.5 / 184; 8 x 3907 247 / 239; 8 x 5128 314 / 313; 16 x 2730 332 / 333; 64 x 733 368 / 355; 8 x 7325
-// 466 / 443; 8 x 30381 1948 / 1844.
+// Block-sign, which keeps no lists, from so many on (first pass, chunks in order / pages): 16 x 733 chunks 96.7 / 99.2; 8
+// x 2730 169 / 172; 2 x 12208 186.5 / 184; 8 x 3907 247 / 239; 8 x 5128 314 / 313; 16 x 2730 332 / 333; 64 x 733 368 /
+// 355; 8 x 7325 466 / 443; 8 x 30381 1948 / 1844.
 constexpr uint32_t kBsPagedChunks = 24576;
 inline bool paged_first_pass(uint64_t n, uint32_t num_chunks) {
   return num_chunks >= kSubListMinChunks && n * num_chunks >= kPagedChunks;
@@ -158,7 +160,8 @@ enum : uint32_t {
   kNextGuess = 2   // guess and window
 };
 
-// Words of TopkWorkspace::flags: the queues of k_topk_general lie a cache line apart from one another and from what everybody reads.
+// Words of TopkWorkspace::flags: the queues of k_topk_general lie a cache line apart from one another and from what
+// everybody reads.
 constexpr uint32_t kQueuePitch = 32;
 __host__ __device__ __forceinline__ uint32_t queue_word(uint32_t queue) { return (1 + queue) * kQueuePitch; }
 constexpr size_t kFlagBytes = (1 + kQueues) * kQueuePitch * 4;
@@ -203,8 +206,8 @@ struct TopkRow {
 };
 static_assert(sizeof(TopkRow) == 256, "TopkRow layout");
 
-// Entries from one problem's candidate list to the next one's: whole cache lines, where the general route may be one launch (blocks;
-// rows of more chunks than k_topk_pick takes).
+// Entries from one problem's candidate list to the next one's: whole cache lines, where the general route may be one
+// launch (blocks; rows of more chunks than k_topk_pick takes).
 constexpr uint32_t kPickChunks = 16;
 __host__ __device__ __forceinline__ uint64_t cand_pitch(uint32_t cap) { return (static_cast<uint64_t>(cap) + 15) / 16 * 16; }
 __host__ __device__ __forceinline__ uint64_t row_cand_pitch(uint32_t cap, uint32_t num_chunks) {
@@ -302,8 +305,9 @@ struct TopkWorkspace {
   uint32_t* bhist;      // band_buckets(k) per problem : how many band entries fall into each bucket; zero between steps
   uint2* bnd;           // n * kBoundaryCap : the entries of the bucket that holds the threshold key
   uint32_t* bnd_sel;    // n * kBoundaryCap : coordinates of the kept ones among them, ascending
-  uint32_t* flags;      // [queue_word(q)]: shares drawn by k_topk_general.  [0]: some problem of this step was left to the general kernels (set by k_topk_band, cleared
-                        //      by the step's last kernel): the general kernels return at once otherwise
+  uint32_t* flags;      // [queue_word(q)]: shares drawn by k_topk_general.  [0]: some problem of this step was left to the
+                        //      general kernels (set by k_topk_band, cleared by the step's last kernel): they return at once
+                        //      otherwise
   uint2* cand;          // n * cap_alloc  : (coordinate, fp32 bits)
   int32_t* idx;         // n * k
   float* val;           // n * k
@@ -352,21 +356,22 @@ inline int cached_state_arrays(int64_t d) {
   return fit > 4 ? 4 : static_cast<int>(fit);
 }
 
-// How many a step keeps there.  The identity compressor, which reads the gradients in the same pass, writes through what fits (16 x
-// 11.2 M, three contexts in turn / one context's steps one after the other: 172 / 167 us, streamed 173 / 175).  Top-k and
-// block-sign read and write all four with ordinary accesses or all with streaming ones.  Ordinary accesses are the faster ones
-// where one context's steps follow each other with nothing in between, at every size that fits the cache at all (us, ordinary /
-// streaming: top-k 8 x 8 M 189 / 199, 16 x 11.2 M 432 / 450; block-sign 8 x 8 M 165 / 173, 1 x 12 M 87 / 98).  Where something
-// else comes in between, as in a training program, they are so only while the state is small: the lines of a larger one are gone
-// when the next step asks for them, and are written out in the way of what follows.  Three contexts in turn, ordinary /
-// streaming, k = d / 100 (the line lies at (n + 32) d = 231 M, 7 M coordinates of one worker, 4.8 M of sixteen):
+// How many a step keeps there.  The identity compressor, which reads the gradients in the same pass, writes through what
+// fits (16 x 11.2 M, three contexts in turn / one context's steps one after the other: 172 / 167 us, streamed 173 / 175).
+// Top-k and block-sign read and write all four with ordinary accesses or all with streaming ones.  Ordinary accesses are
+// the faster ones where one context's steps follow each other with nothing in between, at every size that fits the cache
+// at all (us, ordinary / streaming: top-k 8 x 8 M 189 / 199, 16 x 11.2 M 432 / 450; block-sign 8 x 8 M 165 / 173, 1 x 12
+// M 87 / 98).  Where something else comes in between, as in a training program, they are so only while the state is
+// small: the lines of a larger one are gone when the next step asks for them, and are written out in the way of what
+// follows.  Three contexts in turn, ordinary / streaming, k = d / 100 (the line lies at (n + 32) d = 231 M, 7 M
+// coordinates of one worker, 4.8 M of sixteen):
 //   top-k       1 x 6 M 73.1 / 75.2, 1 x 8 M 96.7 / 93.8; 4 x 6 M 110.5 / 111.8, 4 x 7 M 130.7 / 125.4; 8 x 5.5 M 153.4 / 155.0,
 //               8 x 7 M 192 / 186; 16 x 4.5 M 206 / 205, 16 x 5.5 M 255 / 251; 64 x 2 M 363 / 366, 64 x 3.5 M 575 / 568
 //   block-sign  1 x 6.5 M 57.1 / 58.3, 1 x 8 M 71.7 / 67.6; 8 x 6 M 129.8 / 131.7, 8 x 7 M 155.2 / 153.3; 16 x 4.5 M 171.6 / 172.9,
 //               16 x 5.5 M 207.1 / 206.7, 16 x 8 M 305 / 296; 64 x 2.5 M 343 / 342
 //   per layer   2 x 6 M 93.9 / 98.5, 8 x 5.5 M 165.6 / 167.1, 16 x 5 M 244 / 240
-// With 512 MB of other traffic before every step, which is not counted, neither is ahead by more than 5 % from 6 M on (16 x 11 M:
-// block-sign 412 / 404, top-k 475 / 474; 8 x 8 M: 178.9 / 177.9, 222 / 218).
+// With 512 MB of other traffic before every step, which is not counted, neither is ahead by more than 5 % from 6 M on (16
+// x 11 M: block-sign 412 / 404, top-k 475 / 474; 8 x 8 M: 178.9 / 177.9, 222 / 218).
 constexpr int64_t kOrdinaryState = 231000000;
 inline int step_cached_arrays(int64_t n, int64_t d, bool identity) {
   return identity ? cached_state_arrays(d) : (n + 32) * d <= kOrdinaryState ? 4 : 0;
@@ -452,8 +457,8 @@ hipError_t fill_rows_f32(float* p, uint32_t n, int64_t ld, uint32_t d, float val
 hipError_t stream_copy(void* dst, const void* src, size_t bytes, hipStream_t stream);
 hipError_t inplace_probe(float* const* arrays, int n_arrays, size_t count, int cached_arrays, hipStream_t stream);
 
-// Kernels of short steps take what their first loads need as leading plain arguments, which arrive in scalar registers; the structures
-// that follow hold the same values.
+// Kernels of short steps take what their first loads need as leading plain arguments, which arrive in scalar registers;
+// the structures that follow hold the same values.
 // Launch with optional timing: when the slot is being timed, the launch is bracketed by a pair of events on
 // the same stream.  (Events attached to the dispatch itself give the same durations but slow the step down
 // by more than the bracketing does; measured on MI355X.)

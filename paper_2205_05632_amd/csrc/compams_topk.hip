@@ -536,8 +536,8 @@ __device__ __forceinline__ SegCtx seg_ctx(Geometry& geo, TopkOptions& opt, const
 
 constexpr uint32_t kRowWord(size_t offset) { return static_cast<uint32_t>(offset / 4); }
 
-// How the parts of the general route hand things on: SAME: inside one launch, at device scope; else from launch to launch, with
-// ordinary accesses (at device scope the four launches took 5 us more).
+// How the parts of the general route hand things on: SAME: inside one launch, at device scope; else from launch to
+// launch, with ordinary accesses (at device scope the four launches took 5 us more).
 template <bool SAME>
 struct Handed {  // words from p on, `words` of them
   const uint32_t* p;
@@ -614,9 +614,9 @@ __device__ __forceinline__ ListRuns runs_of_row(const Handed<SAME>& row, uint32_
   return L;
 }
 
-// read(bits_of) with the entries of a problem's candidate list, as an earlier launch has left them.  A list that this launch has
-// written (SAME; level 1, kModeNeedB) is read at device scope: segments lie behind one another, so that workgroups of
-// several dies write parts of one line, and the line in the reader's own die may be from before.
+// read(bits_of) with the entries of a problem's candidate list, as an earlier launch has left them.  A list that this
+// launch has written (SAME; level 1, kModeNeedB) is read at device scope: segments lie behind one another, so that
+// workgroups of several dies write parts of one line, and the line in the reader's own die may be from before.
 template <bool SAME, typename F>
 __device__ __forceinline__ void with_list(const uint2* __restrict__ candr, uint32_t cap, uint32_t mode, F&& read) {
   if (SAME && mode == kModeNeedB) {  // uniform
@@ -679,12 +679,12 @@ __device__ __forceinline__ void sweep_list(Bits&& bits_of, const ListRuns& R, ui
 // another.  The level-0 histogram is taken afterwards, from the candidate list (general_level0).
 // In large problems (paged_first_pass) the workgroup takes the same page of four spans instead, a quarter of four different
 // chunks (page_quarter): one allocation still, but a segment of the lists for every quarter.  Which page a die takes changes
-// seven times over the rows: a crowded page (a matrix as wide as the span or a multiple, its large columns side by side) takes
-// its die longer, and as one die's page in every row it held up the whole pass (8 x 25570000, k 5 %, 1024 large columns of
-// 32768: 441 us in chunks, 598 with the pages as they are in every row, 407 so; 64 x 3002268, k 8 %: 412, 574, 413; without
-// such columns 16 x 25570000 755 / 755, 64 x 3002268 356 / 363).  (Measured on the way: fewer
-// instructions between the loads and the stores, and stores as soon as a round's loads have come, made it slower, 8 x 30381
-// chunks 1828 -> 1899 us; all stores behind a barrier 1866; four workgroups per compute unit instead of five 1820, eight 1843.)
+// seven times over the rows: a crowded page (a matrix as wide as the span or a multiple, its large columns side by side)
+// takes its die longer, and as one die's page in every row it held up the whole pass (8 x 25570000, k 5 %, 1024 large
+// columns of 32768: 441 us in chunks, 598 with the pages as they are in every row, 407 so; 64 x 3002268, k 8 %: 412, 574,
+// 413; without such columns 16 x 25570000 755 / 755, 64 x 3002268 356 / 363).  (Measured on the way: fewer instructions
+// between the loads and the stores, and stores as soon as a round's loads have come, made it slower, 8 x 30381 chunks
+// 1828 -> 1899 us; all stores behind a barrier 1866; four workgroups per compute unit instead of five 1820, eight 1843.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kLeanRounds = kRounds / kWaves;  // rounds of a chunk per wavefront
 constexpr int kStageQ = 512;                   // staged candidates per wavefront (of at most 1024 coordinates)
@@ -848,9 +848,9 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(Geometry geo, const float* __
   // the run this workgroup appends to, its share of the capacities and its cursors (candidates in the low half of a
   // 64-bit word, band entries in the high half: one atomic advances both)
   const bool runs = sc.cursor_set != kNoCursorSet;  // workgroup-uniform
-  // In pages `group` % 8 alone is the page, so that a matrix whose rows are a multiple of 8192 long and whose large columns lie
-  // side by side would fill one run of eight and be read again in every step (8 x 25570000, 1024 large columns of 8192: 1108 us
-  // a step against 597 with the runs in turn).
+  // In pages `group` % 8 alone is the page, so that a matrix whose rows are a multiple of 8192 long and whose large
+  // columns lie side by side would fill one run of eight and be read again in every step (8 x 25570000, 1024 large
+  // columns of 8192: 1108 us a step against 597 with the runs in turn).
   const uint32_t turn = PAGED ? sc.group / kDies + sc.group / (kDies * kDies) : 0u;
   const uint32_t run = runs ? (sc.group + turn) % kSubLists : 0u;
   const uint32_t run_cap = runs ? opt.cap / kSubLists : opt.cap;
@@ -953,14 +953,13 @@ __global__ __launch_bounds__(kWG) void k_topk_lean(Geometry geo, const float* __
 // (not below d1 / 4), and to be off by at most half of what that took away from d1; changes of opposite signs are
 // scatter about a level, next = 0, unsure by 0.7 of the larger one; a drift that grows is extrapolated flat, next = d1,
 // unsure by 0.4 |d1| + |d1 - d0|.  The centre is tau (1 + next), the half-width
-// 0.4 % + unsure + `noise`, an allowance for the scatter of the k-th largest of a sample from step to step.  With B entries found in a window
-// of relative width w around the threshold, one entry more or fewer above a level moves the k-th largest key by
-// w / B of its value and the count above a level scatters by about sqrt(k): k_topk_band passes 8 w sqrt(k) / B
-// (the extrapolation more than doubles the scatter, and three times the result is allowed for); where no window
-// has been looked at yet, 1.5 / sqrt(k) stands in (as if a fourteenth of the kept entries lay within one per
-// cent of the threshold).  It only decides which route the next step takes, never a result.  guess_valid / guess:
-// the bucket guess the next first pass will use; the window must lie at or above it so that every band entry is
-// also a candidate.
+// 0.4 % + unsure + `noise`, an allowance for the scatter of the k-th largest of a sample from step to step.  With B
+// entries found in a window of relative width w around the threshold, one entry more or fewer above a level moves the
+// k-th largest key by w / B of its value and the count above a level scatters by about sqrt(k): k_topk_band passes 8 w
+// sqrt(k) / B (the extrapolation more than doubles the scatter, and three times the result is allowed for); where no
+// window has been looked at yet, 1.5 / sqrt(k) stands in (as if a fourteenth of the kept entries lay within one per cent
+// of the threshold).  It only decides which route the next step takes, never a result.  guess_valid / guess: the bucket
+// guess the next first pass will use; the window must lie at or above it so that every band entry is also a candidate.
 // ---------------------------------------------------------------------------------------------
 // A step's list held n entries, every key from list_from upwards; the guess for the next step may lie below that, where
 // nothing is known, and is taken to add at most as many again.  Where even that would not leave room to spare, the key
@@ -1026,15 +1025,16 @@ __device__ __forceinline__ void set_next_band(TopkRow* rowp, uint32_t tau, uint3
   rowp->band_mul = valid ? band_multiplier_dev(hi - lo, many ? kBandBucketsMany : kBandBucketsFew) : 0u;
 }
 
-// The kernels that select in one launch end in one workgroup's chain, of which the above (divisions and roots, one after the other)
-// was 1 to 1.5 us: they leave what it needs in the control block, and a workgroup of the last kernel goes through it beside
-// the others' work, one more than there are chunks (a step of 4 x 65536, k = 655: 24.3 us, with that and the ranking of k_topk_pick 23.2;
-// 16 x 1 M 70.4, now 69.6).  Top-k inside blocks: a wavefront of every problem's first chunk; in whole rows that kept the first chunk
-// 0.4 us longer, in every step (4 x 65536 23.26 us a step, now 23.13).
-// Only where there is a lane of a wavefront for every row: more of them keep its compute unit busy, 1.4 us for every 64, while in the
-// selecting kernel every row has a workgroup of its own (us, all rows in the selecting kernel / in the last one: a step of 32 x 600000
-// 75.4 / 74.6, 24 x 300000 49.5 / 48.9, 64 x 100000 59.7 / 59.1, 64 x 4096 43.4 / 43.7, 300 x 4096 134.7 / 140.8, 4000 x 4096 1547 / 1640; the
-// workers' half 300 x 4096 27.2 / 33.8, 4000 x 4096 120 / 218).
+// The kernels that select in one launch end in one workgroup's chain, of which the above (divisions and roots, one after
+// the other) was 1 to 1.5 us: they leave what it needs in the control block, and a workgroup of the last kernel goes
+// through it beside the others' work, one more than there are chunks (a step of 4 x 65536, k = 655: 24.3 us, with that
+// and the ranking of k_topk_pick 23.2; 16 x 1 M 70.4, now 69.6).  Top-k inside blocks: a wavefront of every problem's
+// first chunk; in whole rows that kept the first chunk 0.4 us longer, in every step (4 x 65536 23.26 us a step, now
+// 23.13).
+// Only where there is a lane of a wavefront for every row: more of them keep its compute unit busy, 1.4 us for every 64,
+// while in the selecting kernel every row has a workgroup of its own (us, all rows in the selecting kernel / in the last
+// one: a step of 32 x 600000 75.4 / 74.6, 24 x 300000 49.5 / 48.9, 64 x 100000 59.7 / 59.1, 64 x 4096 43.4 / 43.7, 300 x
+// 4096 134.7 / 140.8, 4000 x 4096 1547 / 1640; the workers' half 300 x 4096 27.2 / 33.8, 4000 x 4096 120 / 218).
 // population: entries of the window lo .. hi that was looked at (0: none), ref: a key in it.
 __host__ __device__ __forceinline__ bool window_later(uint32_t n) { return n <= 64; }
 __device__ __forceinline__ float population_noise(uint32_t population, uint32_t lo, uint32_t hi, uint32_t ref, uint32_t k) {
@@ -1092,9 +1092,9 @@ __device__ __forceinline__ ListRuns band_runs_from_cursors(const TopkWorkspace& 
   return L;
 }
 
-// How a wavefront that takes up to `chunks` (1 .. 8) chunks at a time shares its lanes out among their segments, `parts` (one
-// or four) to a chunk: every segment has the same number of lanes, which take its entries in turn, so that the segments of all
-// the chunks are requested together however short they are.
+// How a wavefront that takes up to `chunks` (1 .. 8) chunks at a time shares its lanes out among their segments, `parts`
+// (one or four) to a chunk: every segment has the same number of lanes, which take its entries in turn, so that the
+// segments of all the chunks are requested together however short they are.
 struct SegmentLanes {
   uint32_t lanes;    // lanes per segment
   uint32_t segment;  // the lane's, counted from the group's first
@@ -1158,12 +1158,12 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
   TopkRow* rowp = ws.rows + row;
   uint32_t* bh = ws.bhist + sc.bhist_base;
   const uint32_t wave = uniform_u32(t >> 6), lane = lane_id();
-  // A wavefront takes up to eight chunks at a time: all its lanes the entries of one after the other, or, where a chunk has a
-  // segment for every quarter, the lanes shared out among the segments (SegmentLanes).  (Shared out also where there is one
-  // segment to a chunk, this kernel took, us: blocks of 12 x 60000 13.8 -> 15.5, 16 x 733 chunks 13.8 -> 15.9.)
-  // Everything that can be asked for before anything is known goes out together (a workgroup's work is a chain
-  // of round trips otherwise): the control block and the cursors, the bucket histogram, the counts above the
-  // band, the first descriptors.
+  // A wavefront takes up to eight chunks at a time: all its lanes the entries of one after the other, or, where a chunk
+  // has a segment for every quarter, the lanes shared out among the segments (SegmentLanes).  (Shared out also where
+  // there is one segment to a chunk, this kernel took, us: blocks of 12 x 60000 13.8 -> 15.5, 16 x 733 chunks 13.8 ->
+  // 15.9.) Everything that can be asked for before anything is known goes out together (a workgroup's work is a chain of
+  // round trips otherwise): the control block and the cursors, the bucket histogram, the counts above the band, the first
+  // descriptors.
   constexpr int kGroup = 8;  // chunks a wavefront takes at a time, at most
   constexpr uint32_t kParts = QUARTERS ? kWaves : 1;
   const uint2* d2 = ws.desc2 + sc.chunk_base * kParts;
@@ -1518,7 +1518,8 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 // ---------------------------------------------------------------------------------------------
 // The whole selection of a short row (at most kPickChunks chunks) by one workgroup: it takes the place of the band
 // kernel and of the general route's four, whose launches and row-wide steps cost a short row more than its bytes (4 rows
-// of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass 31.0 -> 24.2).
+// of 65536 coordinates: band 11.0 us and four launches of 1.3 to 2.6 us that return at once -> 9.9 us; the whole pass
+// 31.0 -> 24.2).
 //   1. Elements: the candidate list if the guess held, else the row's stored values, chunk after chunk.  The first trip of
 //      four per thread stays in registers; what goes beyond is read again in every sweep, four trips requested together.
 //   2. The bucket that holds the k-th largest key, by histograms of kPickBins buckets in LDS, each over the bucket the
@@ -1531,11 +1532,11 @@ __global__ __launch_bounds__(kWG) void k_topk_band(Geometry geo, TopkWorkspace w
 //   4. Per chunk the entries kept, and their prefix over the row, for the last kernel; what the next step's guess and window
 //      follow from (leave_next).
 // Where the line lies (whole step in us, 4 rows, the general kernels / this one): k = d / 100 16 chunks 30.6 / 24.6, 32
-// chunks 30.8 / 28.6, 48 chunks 31.1 / 33.7; k = d / 10 16 chunks 39.5 / 39.1, 20 chunks 40.1 / 42.9.  What bounds it is one compute
-// unit's instructions, about 20 us for a sweep over 65536 coordinates.  A row whose list did not hold (a selection of half
-// the row, magnitudes that are few and equal) still takes it: 4 x 65536, k = 32768 164 / 101, k = 19660 of three
-// magnitudes 198 / 170.  A step of which it is known beforehand that no row has a guess (the first of a context, prediction
-// off) goes to the general kernels: 4 x 65536, k = 655 56 / 95.
+// chunks 30.8 / 28.6, 48 chunks 31.1 / 33.7; k = d / 10 16 chunks 39.5 / 39.1, 20 chunks 40.1 / 42.9.  What bounds it is
+// one compute unit's instructions, about 20 us for a sweep over 65536 coordinates.  A row whose list did not hold (a
+// selection of half the row, magnitudes that are few and equal) still takes it: 4 x 65536, k = 32768 164 / 101, k = 19660
+// of three magnitudes 198 / 170.  A step of which it is known beforehand that no row has a guess (the first of a context,
+// prediction off) goes to the general kernels: 4 x 65536, k = 655 56 / 95.
 // A row's window only narrows what the first pass lists (opt.band = kBandWindow); whether the threshold lay inside is
 // counted as on the band route.
 // ---------------------------------------------------------------------------------------------
@@ -1574,8 +1575,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
   const uint32_t tau_before = in_row.tau, tau_before2 = in_row.tau_prev;
   const bool windowed = pred && opt.band && in_row.band_valid != 0;
   const uint32_t count = LISTED ? n_cand : geo.d;
-  // A trip takes kPickQuad elements of every thread: entries of the list 1024 apart, or (from the second trip on) a quad of the
-  // row's coordinates; over the row it is a chunk.
+  // A trip takes kPickQuad elements of every thread: entries of the list 1024 apart, or (from the second trip on) a quad
+  // of the row's coordinates; over the row it is a chunk.
   struct Trip { uint2 en[kPickQuad]; };
   constexpr uint32_t kTripElements = kPickQuad * kPickThreads;
   static_assert(kTripElements == kChunk, "a trip over the row is a chunk");
@@ -1831,8 +1832,8 @@ __device__ __forceinline__ void pick_row(PickShared& sh, const float* __restrict
              miss == 0 && normal_key(tau) ? in_window : 0u, blo, bhi, tau);
 }
 
-__global__ __launch_bounds__(kPickThreads) void k_topk_pick(Geometry geo, const float* __restrict__ e, TopkWorkspace ws, TopkOptions opt,
-                                                             uint32_t use_guess) {
+__global__ __launch_bounds__(kPickThreads) void k_topk_pick(Geometry geo, const float* __restrict__ e, TopkWorkspace ws,
+                                                             TopkOptions opt, uint32_t use_guess) {
   __shared__ PickShared sh;
   const SegCtx sc = seg_ctx<true, kClassFirst>(geo, opt, ws);  // grid (1, rows)
   const TopkRow* rp = ws.rows + sc.seg;
@@ -1865,20 +1866,21 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_pick(Geometry geo, const 
 // whether the row is read again.  (Eight entries instead of three, and no look at what fits: 34 M coordinates, k = 1000, 362
 // us a call, now 338; 60 M, k = 100000, 580, now 523.)
 // ---------------------------------------------------------------------------------------------
-// The same sample gives the window of keys in which the threshold is expected, where the first pass is to keep band lists: from the
-// bucket above which the expected count plus three deviations lies to the one above which the expected count less three
-// deviations does, if the band list would hold what the sample says lies in it.  The band kernel then selects, as in a step that
-// carries its window over, and the general route (30 us of the call for 4 x 300007, k = 3000, in four launches) returns at once.
-// Fewer of the sample's entries above the threshold than sample_gives_window() asks for say too little: the window is two octaves wide
-// and more, its entries' lists and counts cost the first pass what the selection gains, and half of the calls miss it.  (Two sets of 24
-// drawn shapes, times faster than without a window, in the mean: from 8 entries on 1.06 and 1.06, from 16 on 1.05 and 1.04, always
-// 1.05; always: 4 x 1634958, k = 2524, 70.9 -> 74.0 us; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 ->
-// 43.9.)  In long rows a wide window's entries meet on the histogram's crowded end: us a call without / with a window, unit normal and
-// heavy-tailed values, 12 entries above the threshold: 4 x 1.8 M 71.8 / 67.9, 71.1 / 69.3; 4 x 2.6 M 80.2 / 77.4, 89.7 / 81.9; 4 x 2.9 M
-// 85.0 / 83.9, 84.1 / 91.8; 8 x 1.8 M 89.6 / 83.8, 88.1 / 84.5; 8 x 2.1 M 91.6 / 94.0, 95.9 / 96.8; 8 x 2.9 M 107.4 / 117.1, 107.6 / 130.9; 40
-// entries, where it is narrower: 4 x 2.9 M 87.0 / 78.9, 8 x 2.9 M 111.4 / 109.0.
-// The launch also clears the tables that the call expects at zero, which took a launch of its own, 2 us: a workgroup its row's control block,
-// further workgroups what follows the flags.
+// The same sample gives the window of keys in which the threshold is expected, where the first pass is to keep band
+// lists: from the bucket above which the expected count plus three deviations lies to the one above which the expected
+// count less three deviations does, if the band list would hold what the sample says lies in it.  The band kernel then
+// selects, as in a step that carries its window over, and the general route (30 us of the call for 4 x 300007, k = 3000,
+// in four launches) returns at once. Fewer of the sample's entries above the threshold than sample_gives_window() asks
+// for say too little: the window is two octaves wide and more, its entries' lists and counts cost the first pass what the
+// selection gains, and half of the calls miss it.  (Two sets of 24 drawn shapes, times faster than without a window, in
+// the mean: from 8 entries on 1.06 and 1.06, from 16 on 1.05 and 1.04, always 1.05; always: 4 x 1634958, k = 2524, 70.9
+// -> 74.0 us; 4 x 297708, k = 1050 -- 14 entries -- 50.3 -> 45.4; 4 x 97241, k = 1445 49.8 -> 43.9.)  In long rows a wide
+// window's entries meet on the histogram's crowded end: us a call without / with a window, unit normal and heavy-tailed
+// values, 12 entries above the threshold: 4 x 1.8 M 71.8 / 67.9, 71.1 / 69.3; 4 x 2.6 M 80.2 / 77.4, 89.7 / 81.9; 4 x 2.9
+// M 85.0 / 83.9, 84.1 / 91.8; 8 x 1.8 M 89.6 / 83.8, 88.1 / 84.5; 8 x 2.1 M 91.6 / 94.0, 95.9 / 96.8; 8 x 2.9 M 107.4 /
+// 117.1, 107.6 / 130.9; 40 entries, where it is narrower: 4 x 2.9 M 87.0 / 78.9, 8 x 2.9 M 111.4 / 109.0.
+// The launch also clears the tables that the call expects at zero, which took a launch of its own, 2 us: a workgroup its
+// row's control block, further workgroups what follows the flags.
 // (And where nearly all is kept, the sample does not say from where on.)
 inline bool sample_gives_window(const Geometry& geo) {
   const uint64_t entries = geo.num_chunks <= 640 && static_cast<uint64_t>(geo.n) * geo.num_chunks <= 4096 ? 8 : 32;
@@ -1897,7 +1899,8 @@ __global__ __launch_bounds__(kPickThreads) void k_topk_sample(const float* __res
   if (row >= geo.n) {  // clears, 16 bytes a thread
     uint4* p = reinterpret_cast<uint4*>(ws.counters);
     const uint32_t quads = static_cast<uint32_t>(reinterpret_cast<uint4*>(ws.chunk_rec) - p);
-    for (uint32_t q = (row - geo.n) * kPickThreads + t; q < quads; q += (gridDim.x - geo.n) * kPickThreads) p[q] = make_uint4(0, 0, 0, 0);
+    for (uint32_t q = (row - geo.n) * kPickThreads + t; q < quads; q += (gridDim.x - geo.n) * kPickThreads)
+      p[q] = make_uint4(0, 0, 0, 0);
     return;
   }
   // the control block as the first pass reads it; nothing else in it but zeros
@@ -1981,14 +1984,15 @@ struct Level1Shared { uint32_t lh[kNB1]; uint2 stage[kWaves * kStage]; };
 struct Level2Shared { uint32_t lh[kNB2]; };
 struct CountShared { uint32_t gt[kMaxCountCpw], eq[kMaxCountCpw]; };
 
-// A part of a problem is done: the next one may begin.  By the thread that has written what the next one reads, with device-scope
-// stores.
+// A part of a problem is done: the next one may begin.  By the thread that has written what the next one reads, with
+// device-scope stores.
 __device__ __forceinline__ void problem_at(TopkRow* rowp, uint32_t phase) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   store_agent(&rowp->phase, phase);
 }
 
-// (unrolled by hand: before it is in line, the compiler does not know how many threads there are, and in loops level 0 took 1.6 us more)
+// (unrolled by hand: before it is in line, the compiler does not know how many threads there are, and in loops level 0
+// took 1.6 us more)
 template <uint32_t NB>
 __device__ __forceinline__ void clear_bins(uint32_t* bins) {
   static_assert(NB % kWG == 0, "bins per thread");
@@ -2005,8 +2009,8 @@ __device__ __forceinline__ void flush_bins(const uint32_t* bins, uint32_t* to) {
 }
 
 template <bool SAME>
-__device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
-                                               const TopkOptions& opt, const SegCtx& sc, uint32_t use_guess) {
+__device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& lds, const float* __restrict__ e, const Geometry& geo,
+                                               const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc, uint32_t use_guess) {
   uint32_t (&lh)[kNB0] = lds.lh;
   uint32_t (&lh1)[kTracked * kNB1] = lds.lh1;
   const uint32_t row = sc.seg;
@@ -2131,8 +2135,8 @@ __device__ __forceinline__ void general_level0(GeneralShared& sh, Level0Shared& 
 //   kModeDense: no list: histogram from the row itself.
 // ---------------------------------------------------------------------------------------------
 template <bool SAME>
-__device__ __forceinline__ void general_level1(GeneralShared& sh, Level1Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
-                                               const TopkOptions& opt, const SegCtx& sc) {
+__device__ __forceinline__ void general_level1(GeneralShared& sh, Level1Shared& lds, const float* __restrict__ e, const Geometry& geo,
+                                               const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc) {
   uint32_t (&lh)[kNB1] = lds.lh;
   const uint32_t row = sc.seg;
   TopkRow* rowp = ws.rows + row;
@@ -2201,8 +2205,8 @@ __device__ __forceinline__ void general_level1(GeneralShared& sh, Level1Shared& 
 // Level 2 (last 9 key bits) over the entries that match bits 30..9 of the threshold key.
 // ---------------------------------------------------------------------------------------------
 template <bool SAME>
-__device__ __forceinline__ void general_level2(GeneralShared& sh, Level2Shared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
-                                               const TopkOptions& opt, const SegCtx& sc) {
+__device__ __forceinline__ void general_level2(GeneralShared& sh, Level2Shared& lds, const float* __restrict__ e, const Geometry& geo,
+                                               const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc) {
   uint32_t (&lh)[kNB2] = lds.lh;
   const uint32_t row = sc.seg;
   TopkRow* rowp = ws.rows + row;
@@ -2324,8 +2328,8 @@ __device__ __forceinline__ void for_each_round(uint32_t mode, const float* __res
 // list (a sum over at most kMaxCountBlocks block totals), so no workgroup waits for or follows another.
 // ---------------------------------------------------------------------------------------------
 template <bool QUARTERS, bool SAME>
-__device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& lds, const float* __restrict__ e, const Geometry& geo, const TopkWorkspace& ws,
-                                               const TopkOptions& opt, const SegCtx& sc) {
+__device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& lds, const float* __restrict__ e, const Geometry& geo,
+                                              const TopkWorkspace& ws, const TopkOptions& opt, const SegCtx& sc) {
   const uint32_t row = sc.seg;
   const uint32_t cpw = geo.count_cpw;
   const uint32_t start = sc.group * cpw;
@@ -2353,11 +2357,12 @@ __device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& ld
       if (lane == 0) { lds.gt[c - start] = gt; lds.eq[c - start] = eq; }
     }
   } else if constexpr (QUARTERS) {
-    // A wavefront takes eight consecutive chunks at a time, sixteen lanes for every quarter of a chunk: the first 32 entries of
-    // all quarters together, then, chunk by chunk, what any of its quarters holds beyond.  (Two lanes to a quarter, all quarters at
-    // once, ask for every line of the list several times, and go through a crowded quarter in a chain of 32 trips.  us, rows in
-    // chunks / in pages with two lanes / with sixteen: 8 x 25570000, k 1 % 18.3 / 24.3 / 18.7, 10 % 65 / 102 / 48, 5 % in 1024 large
-    // columns of 32768 41 / 168 / 48; 8 x 124439808, 0.1 % 36.6 / 30.9 / 27.0; 64 x 3002268, 1 % 12.5 / 22.4 / 16.8.)
+    // A wavefront takes eight consecutive chunks at a time, sixteen lanes for every quarter of a chunk: the first 32
+    // entries of all quarters together, then, chunk by chunk, what any of its quarters holds beyond.  (Two lanes to a
+    // quarter, all quarters at once, ask for every line of the list several times, and go through a crowded quarter in a
+    // chain of 32 trips.  us, rows in chunks / in pages with two lanes / with sixteen: 8 x 25570000, k 1 % 18.3 / 24.3 /
+    // 18.7, 10 % 65 / 102 / 48, 5 % in 1024 large columns of 32768 41 / 168 / 48; 8 x 124439808, 0.1 % 36.6 / 30.9 /
+    // 27.0; 64 x 3002268, 1 % 12.5 / 22.4 / 16.8.)
     constexpr int kGroup = 8;
     constexpr uint32_t kLanes = 64 / kWaves, kFirst = 2 * kLanes, kAhead = 8;
     const uint32_t part = lane / kLanes, sub = lane % kLanes;
@@ -2400,8 +2405,9 @@ __device__ __forceinline__ void general_count(GeneralShared& sh, CountShared& ld
     }
   } else {
     // A wavefront takes up to eight consecutive chunks at a time, the lanes shared out among their segments: the
-    // descriptors come with one load, then kAhead entries of every lane together.  Where fewer chunks are there than it could
-    // take, each has more lanes (blocks of 12 x 60000, one coordinate in 20: 9.1 us, eight lanes to a chunk in any case 14.0).
+    // descriptors come with one load, then kAhead entries of every lane together.  Where fewer chunks are there than it
+    // could take, each has more lanes (blocks of 12 x 60000, one coordinate in 20: 9.1 us, eight lanes to a chunk in any
+    // case 14.0).
     constexpr int kAhead = 16;
     const uint32_t group = chunks_per_wave(cpw);
     const SegmentLanes sl = segment_lanes(end - start < group ? end - start : group, 1u);
@@ -2474,29 +2480,30 @@ __global__ __launch_bounds__(kWG) void k_topk_part(Geometry geo, const float* __
 }
 
 // ---------------------------------------------------------------------------------------------
-// The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at once then, where
-// four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 65.1).  The four parts are cut into
-// tasks and every part into as many shares as there are workgroups.  A workgroup draws a share (next_share), takes level 0's tasks of
-// it, draws again if there are shares that nobody has taken, and goes through the tasks of its shares in the parts that follow.  A task
-// waits until its problem's part before is done (wait_for_part; level 1's also where level 0 has resolved it and nothing is left to
-// do: nobody has to know beforehand).  The wait ends: a workgroup waits only when all shares belong to workgroups that are running,
-// and only for parts before its task's; level 0 waits for nothing.  So it does not matter how many workgroups run at a time, or in
-// what order they start.  Only a control block that somebody else writes meanwhile can keep a phase from coming; the wait is
-// bounded for that.
-// What bounds it is a chain for every part: the wait, the list or row, the histogram's atomics, the ticket, the last workgroup's
-// crossing, about 6 us.  (Every share of every part drawn from one counter, and two tasks of level 1 and 2 to a workgroup: 16 x 1 M, all
-// thresholds rising by 15 % a step, 113 us a step; so 96, four launches 92.)
-// What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row), the list that level 1
-// writes included (with_list).
+// The general route in one launch, for the steps in which the band kernel usually leaves nothing to it: it returns at
+// once then, where four launches return one after the other (1.7 us each: 16 x 1 M, k = 10000, 69.6 us a step, so 65.1).
+// The four parts are cut into tasks and every part into as many shares as there are workgroups.  A workgroup draws a
+// share (next_share), takes level 0's tasks of it, draws again if there are shares that nobody has taken, and goes
+// through the tasks of its shares in the parts that follow.  A task waits until its problem's part before is done
+// (wait_for_part; level 1's also where level 0 has resolved it and nothing is left to do: nobody has to know beforehand).
+// The wait ends: a workgroup waits only when all shares belong to workgroups that are running, and only for parts before
+// its task's; level 0 waits for nothing.  So it does not matter how many workgroups run at a time, or in what order they
+// start.  Only a control block that somebody else writes meanwhile can keep a phase from coming; the wait is bounded for
+// that.
+// What bounds it is a chain for every part: the wait, the list or row, the histogram's atomics, the ticket, the last
+// workgroup's crossing, about 6 us.  (Every share of every part drawn from one counter, and two tasks of level 1 and 2 to
+// a workgroup: 16 x 1 M, all thresholds rising by 15 % a step, 113 us a step; so 96, four launches 92.)
+// What one part leaves to the next goes through device-scope stores and loads (no fences: see last_group_of_row), the
+// list that level 1 writes included (with_list).
 // Where it is taken: see general_in_one().
 // ---------------------------------------------------------------------------------------------
-// Workgroups at most: two to a compute unit, so that there is room for 137 vector registers (128 of them: 12 bytes spilled, steps that miss
-// 0.3 to 1 us longer).
+// Workgroups at most: two to a compute unit, so that there is room for 137 vector registers (128 of them: 12 bytes
+// spilled, steps that miss 0.3 to 1 us longer).
 constexpr uint32_t kGeneralMost = 512;
 
 template <bool UNI>
-__global__ __launch_bounds__(kWG, 3) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all, TopkWorkspace ws,
-                                                      TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
+__global__ __launch_bounds__(kWG, 3) void k_topk_general(const uint32_t* flags, const float* __restrict__ e, Geometry geo_all,
+                                                      TopkWorkspace ws, TopkOptions opt_all, uint32_t use_guess, GeneralTasks tasks) {
   if (table_u32(flags, 0) == 0) return;  // every problem of this step was selected by k_topk_band
   __shared__ GeneralShared sh;
   __shared__ union {
@@ -2651,8 +2658,8 @@ __device__ __forceinline__ void emit_chunk(uint32_t mode, const float* __restric
 }
 
 // ---------------------------------------------------------------------------------------------
-// The last kernel: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds what is
-// to be known of worker i of the tile.
+// The last kernel: per chunk of coordinates.  Workers are taken in tiles of kTileWorkers; lane i of a wavefront holds
+// what is to be known of worker i of the tile.
 //   Selecting: the wavefronts share out the tile's workers.  Where a worker's entries of the chunk go in its
 //              list follows from the tables (entries above the threshold in earlier chunks, plus the ties taken there:
 //              in coordinate order until r are in); its candidates of the chunk are gone through 64 to a slot, kSlots
@@ -2679,16 +2686,17 @@ constexpr uint32_t kKept = 2048;     // selected entries of a tile kept in LDS, 
 
 // Wavefronts per chunk.  A chunk's time is the chain of its slots, which more wavefronts share; a grid that fills the chip
 // anyway pays for the room they take.  How a row's selection is spread is not known beforehand: evenly, or crowded into the
-// few chunks of the layers with large gradients.  Whole steps in us, with sixteen / eight / four, selections spread evenly; in a
-// tenth of the row:
+// few chunks of the layers with large gradients.  Whole steps in us, with sixteen / eight / four, selections spread
+// evenly; in a tenth of the row:
 //   16 x 245 chunks, k = d / 100   70 / - / 72; 80 / - / 95
 //   16 x 300, k = d / 100          88 / 82 / 83; 90 / 93 / 105     64 x 300, k = d / 20    323 / 291 / 306; 351 / 457 / 622
 //   16 x 520, k = d / 100          133 / 121 / 122; 122 / 124 / 136
 //   64 x 1024, k = d / 100         715 / 673 / 661; 703 / 693 / 740  64 x 1024, k = d / 20   909 / 838 / 818; 913 / 1003 / 1206
 //   1 x 1024, k = d / 20           85 / 73 / 71; 83 / 80 / 83
-// So a row has sixteen up to 512 chunks, where crowded selections gain more than even ones lose, eight up to 768, and beyond that
-// four, or eight where every row keeps more than a hundred entries of a chunk.  Inside every block the selection is spread
-// evenly by what it is (16 layers, 64 x 300, one entry in twenty: 380 / 332 / -; 64 x 768: - / 734 / 713).
+// So a row has sixteen up to 512 chunks, where crowded selections gain more than even ones lose, eight up to 768, and
+// beyond that four, or eight where every row keeps more than a hundred entries of a chunk.  Inside every block the
+// selection is spread evenly by what it is (16 layers, 64 x 300, one entry in twenty: 380 / 332 / -; 64 x 768: - / 734 /
+// 713).
 constexpr int kFinalMany = 4, kFinalSome = 8, kFinalFew = 16;
 inline int final_wavefronts(uint32_t workgroups, const Geometry& geo, bool uniform) {
   if (uniform) return workgroups <= 256 ? kFinalFew : workgroups <= 640 ? kFinalSome : kFinalMany;
@@ -2703,8 +2711,8 @@ inline int final_wavefronts(uint32_t workgroups, const Geometry& geo, bool unifo
 enum : int { kWholeStep = 0, kWorkerHalf = 1, kServerHalf = 2 };
 
 // UNI: one selection problem per worker over its whole row, one workgroup per chunk of the row.  !UNI (not in
-// the server's half): top-k inside every block; a workgroup takes one chunk of one block (flat launch over map_final) and goes
-// through the workers' segments of that block, which lie a fixed stride apart in every table.
+// the server's half): top-k inside every block; a workgroup takes one chunk of one block (flat launch over map_final) and
+// goes through the workers' segments of that block, which lie a fixed stride apart in every table.
 struct FinalCtx {
   uint32_t c;                     // chunk of the problem
   uint32_t base;                  // first coordinate of the chunk, in coordinates of the worker's row
@@ -2783,7 +2791,8 @@ __global__ __launch_bounds__(NW * 64, NW == kFinalSome ? 6 : 1) void k_topk_fina
     return;
   }
   if (ROLE != kServerHalf && c == 0 && i_first == 0) {
-    for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {  // the next step's first pass allocates its candidate lists from the start
+    // the next step's first pass allocates its candidate lists from the start
+    for (uint32_t i = threadIdx.x; i < geo.n; i += NW * 64) {
       ws.rows[f.row0 + i * f.row_stride].cursor = 0;
       ws.rows[f.row0 + i * f.row_stride].cursor_band = 0;
     }
@@ -3191,28 +3200,31 @@ void launch_final(const Geometry& geo, int cached_arrays, Launcher* L, uint32_t 
 
 }  // namespace
 
-// Whether the general route is one launch: where a window gives the band kernel its chance, and the step is short enough for three
-// launches to count.  us a step, four launches / one, two dozen steps into a run; windows mostly kept (a fifth to a third of the rows
-// miss), thresholds that rise by 15 % a step, that jump tenfold, one magnitude only (the last three: most or all rows miss):
-// 4 x 300007 40.9 / 37.3, 49.5 / 51.4, 46.9 / 46.3, 127.6 / 130.0; 8 x 1 M 58.4 / 55.2, 72.7 / 77.3, 73.3 / 74.4, 183.2 / 184.9; 16 x 1 M
-// 74.5 / 71.6, 92.4 / 95.8, 95.0 / 95.0, 246.6 / 250.2; 64 x 250007 87.5 / 82.7, 104.6 / 105.2, 107.1 / 106.1, 344.6 / 347.2; 1 x 16 M
-// 167.3 / 163.1, 197.0 / 189.0, 222.2 / 219.2, 707.3 / 709.4; 8 x 12 blocks of 60000 54.5 / 49.6, 64.5 / 60.5, 72.7 / 70.5, 148.7 / 151.6.
-// Beyond the line the launches are less than three per cent of a step.
-// Steps of a run that keep much: from two fifths of a row on a list seldom holds and the route is taken in every step (k = d / 2.7, d /
-// 2.3, d / 1.5: 4 x 1 M 97.1 / 94.7, 112.8 / 111.6, 137.8 / 143.3; 1 x 4 M 120.5 / 118.7, 137.6 / 136.1, 163.1 / 168.6; 4 x 4 M 206.8 / 211.1,
-// 236.2 / 248.2, 276.9 / 339.4; 16 x 1 M, d / 1.5, 231.4 / 302.4), and long lists are swept better by a full grid: a million entries of all
-// rows (k = d / 8: 8 x 1 M 91.9 / 90.1, 16 x 1 M 125.1 / 128.1, 64 x 200000 153.8 / 157.5, 200 x 70000 288.4 / 303.6).
+// Whether the general route is one launch: where a window gives the band kernel its chance, and the step is short enough
+// for three launches to count.  us a step, four launches / one, two dozen steps into a run; windows mostly kept (a fifth
+// to a third of the rows miss), thresholds that rise by 15 % a step, that jump tenfold, one magnitude only (the last
+// three: most or all rows miss): 4 x 300007 40.9 / 37.3, 49.5 / 51.4, 46.9 / 46.3, 127.6 / 130.0; 8 x 1 M 58.4 / 55.2,
+// 72.7 / 77.3, 73.3 / 74.4, 183.2 / 184.9; 16 x 1 M 74.5 / 71.6, 92.4 / 95.8, 95.0 / 95.0, 246.6 / 250.2; 64 x 250007
+// 87.5 / 82.7, 104.6 / 105.2, 107.1 / 106.1, 344.6 / 347.2; 1 x 16 M 167.3 / 163.1, 197.0 / 189.0, 222.2 / 219.2, 707.3 /
+// 709.4; 8 x 12 blocks of 60000 54.5 / 49.6, 64.5 / 60.5, 72.7 / 70.5, 148.7 / 151.6. Beyond the line the launches are
+// less than three per cent of a step.
+// Steps of a run that keep much: from two fifths of a row on a list seldom holds and the route is taken in every step (k
+// = d / 2.7, d / 2.3, d / 1.5: 4 x 1 M 97.1 / 94.7, 112.8 / 111.6, 137.8 / 143.3; 1 x 4 M 120.5 / 118.7, 137.6 / 136.1,
+// 163.1 / 168.6; 4 x 4 M 206.8 / 211.1, 236.2 / 248.2, 276.9 / 339.4; 16 x 1 M, d / 1.5, 231.4 / 302.4), and long lists
+// are swept better by a full grid: a million entries of all rows (k = d / 8: 8 x 1 M 91.9 / 90.1, 16 x 1 M 125.1 / 128.1,
+// 64 x 200000 153.8 / 157.5, 200 x 70000 288.4 / 303.6).
 constexpr uint64_t kOneLaunchChunks = 4096;
-// room: entries that a worker's lists hold (a list that the caller's option keeps short is left like a row of which much is kept: 16 x 1 M,
-// k = 10000, a list of 20000 146.1 / 155.0).
-static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, const Geometry& geo, uint64_t chunks, uint64_t room, bool whole) {
+// room: entries that a worker's lists hold (a list that the caller's option keeps short is left like a row of which much
+// is kept: 16 x 1 M, k = 10000, a list of 20000 146.1 / 155.0).
+static bool general_in_one(uint32_t use_guess, const TopkOptions& opt, const Geometry& geo, uint64_t chunks, uint64_t room,
+                           bool whole) {
   const uint64_t k = geo.k, n = geo.n;
   return use_guess && opt.band && chunks <= kOneLaunchChunks && (whole || (5 * k <= 2 * room && n * k <= 1u << 20));
 }
 static_assert(kOneLaunchChunks < kPagedChunks, "k_topk_general counts chunks of one segment");
 static_assert((kOneLaunchChunks + 1) * kGeneralMost < (1ull << 32), "tasks_of: a task has a chunk at least");
-// (kGeneralMost = 256 / 512 / 1024: 16 x 1 M, rising thresholds 98 / 96 / 108 us a step, one magnitude 279 / 249 / 249; 1 x 16 M 185 / 191 / 207,
-// 723 / 709 / 720)
+// (kGeneralMost = 256 / 512 / 1024: 16 x 1 M, rising thresholds 98 / 96 / 108 us a step, one magnitude 279 / 249 / 249; 1
+// x 16 M 185 / 191 / 207, 723 / 709 / 720)
 static uint32_t general_workgroups(const GeneralTasks& tasks) {
   return std::min(kGeneralMost, *std::max_element(tasks.total, tasks.total + 4));
 }
@@ -3240,8 +3252,8 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
   if (whole && geo.d >= kSample) {
     const size_t bytes = reinterpret_cast<const char*>(ws.chunk_rec) - reinterpret_cast<const char*>(ws.counters);
     const uint32_t clearing = static_cast<uint32_t>(std::min<size_t>((bytes + kClearBytes - 1) / kClearBytes, 256));
-    launch(L, kSlotPick, k_topk_sample, dim3(geo.n + clearing), dim3(kPickThreads), stream, g, e, geo.ld, geo.d, geo.n, geo.k, opt.cap, ws.rows, geo,
-           ws, opt);
+    launch(L, kSlotPick, k_topk_sample, dim3(geo.n + clearing), dim3(kPickThreads), stream, g, e, geo.ld, geo.d, geo.n, geo.k,
+           opt.cap, ws.rows, geo, ws, opt);
     COMPAMS_CHECK_LAUNCH();
   }
   auto* first = clear_pending ? (paged ? k_topk_lean<true, true, true> : k_topk_lean<true, true, false>)
@@ -3265,7 +3277,8 @@ hipError_t topk_step(const Geometry& geo, const TopkWorkspace& ws, const TopkOpt
       const uint32_t g1 = std::max(1u, std::min(kGeneralMost / geo.n, G));
       GeneralTasks tasks{{g1, g1, g1, count_blocks}, {}};
       for (uint32_t part = 0; part < kGeneralParts; ++part) tasks.total[part] = tasks.groups[part] * geo.n;
-      launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
+      launch(L, kSlotGeneral, k_topk_general<true>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt,
+             use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
       // level 0 by about two workgroups per compute unit over all rows: each clears and flushes a whole histogram, and the
@@ -3320,7 +3333,8 @@ hipError_t topk_blocks_step(const Geometry& geo, const TopkWorkspace& ws, const 
   if (flat.wg_sweep) {  // none if every block is a micro problem
     const GeneralTasks tasks{{}, {flat.wg_level0, flat.wg_sweep, flat.wg_sweep, flat.wg_count}};
     if (general_in_one(use_guess, opt, geo, static_cast<uint64_t>(geo.n) * flat.chunk_stride, geo.d, false)) {
-      launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt, use_guess, tasks);
+      launch(L, kSlotGeneral, k_topk_general<false>, dim3(general_workgroups(tasks)), wg, stream, ws.flags, e, geo, ws, opt,
+             use_guess, tasks);
       COMPAMS_CHECK_LAUNCH();
     } else {
       launch(L, kSlotLevel0, k_topk_part<false, false, 0>, dim3(flat.wg_level0), wg, stream, geo, e, ws, opt, use_guess);
@@ -3349,7 +3363,8 @@ hipError_t topk_server_step(const Geometry& geo, const TopkWorkspace& ws, const 
                             float* theta, float* m, float* v, float* vhat, hipStream_t stream, Launcher* L) {
   const float* no_e = nullptr;
   const TopkFlat none{};
-  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat, no_e, ws, opt, ap, none);
+  launch_final_of<kServerHalf, true, kFinalMany, false, false>(geo.n, ap.cached_arrays, L, geo.num_chunks, stream, geo, theta, m, v, vhat,
+                                                               no_e, ws, opt, ap, none);
   COMPAMS_CHECK_LAUNCH();
   return hipSuccess;
 }

@@ -89,9 +89,9 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_width(const int32_t* __restri
 // sums over the tiles before its own adds them up itself, four loads per thread at most; the launch between two short
 // kernels that this replaces costs 4.7 us (437 tiles x 16 rows: packing 17.1 -> 13.7 us; unpacking, with the offsets of
 // the quarters no longer found by a launch of their own, 34.3 -> 21.0 us).
-// The work of a row grows with the square of its tiles: longer rows keep the launch.  (The line is one of registers, four loads
-// per thread; the gain fades later.  With the launch / without, packing; unpacking, 16 rows: 437 tiles 15.1 / 12.5; 20.3 / 17.4
-// us, 1024 tiles 22.7 / 21.7; 30.2 / 27.6, 4000 tiles 70.5 / 70.8; 84.8 / 83.9.)
+// The work of a row grows with the square of its tiles: longer rows keep the launch.  (The line is one of registers, four
+// loads per thread; the gain fades later.  With the launch / without, packing; unpacking, 16 rows: 437 tiles 15.1 / 12.5;
+// 20.3 / 17.4 us, 1024 tiles 22.7 / 21.7; 30.2 / 27.6, 4000 tiles 70.5 / 70.8; 84.8 / 83.9.)
 constexpr uint32_t kDirectTiles = 1024;
 
 // What lies before tile t0 + (the wavefront's number) of a row's per-tile amounts, and the row's sum.
@@ -301,10 +301,10 @@ __global__ __launch_bounds__(kWG) void k_wire_tile_sums(const uint32_t* __restri
   if (lane_id() == 0) tile_sum[static_cast<size_t>(row) * tiles + t] = sum;
 }
 
-// Both at once for rows of up to kDirectTiles tiles: every workgroup goes through the row's widths itself, four of them (a word) to a
-// thread, for what lies before its own four tiles; the first one leaves status and total.  What it saves is a launch of one
-// workgroup per row (a step in two halves, us, with that launch / so: 16 x 1 M, k = 10000 89.4 / 88.0; 16 x 11181642, k = 111816
-// 485.6 / 483.5; 64 x 1 M 208.8 / 207.6; 8 x 25 M, k = 262144, 1024 tiles, 620.4 / 617.6).
+// Both at once for rows of up to kDirectTiles tiles: every workgroup goes through the row's widths itself, four of them
+// (a word) to a thread, for what lies before its own four tiles; the first one leaves status and total.  What it saves is
+// a launch of one workgroup per row (a step in two halves, us, with that launch / so: 16 x 1 M, k = 10000 89.4 / 88.0; 16
+// x 11181642, k = 111816 485.6 / 483.5; 64 x 1 M 208.8 / 207.6; 8 x 25 M, k = 262144, 1024 tiles, 620.4 / 617.6).
 __global__ __launch_bounds__(kWG) void k_wire_measure_topk(const uint32_t* __restrict__ messages, int64_t stride, uint32_t k,
                                                             uint32_t tiles, uint32_t* __restrict__ tile_off,
                                                             uint32_t* __restrict__ totals, uint32_t* __restrict__ status,
