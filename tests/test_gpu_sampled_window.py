@@ -30,9 +30,7 @@ def values(rng, kind, n, d):
 
 @pytest.mark.parametrize("kind", ["unit", "layers", "few", "unsampled", "zeros", "huge"])
 @pytest.mark.parametrize("n,d,k", [(2, 65537, 127), (2, 65537, 129), (3, 64 * 4096, 2700), (1, 300007, 6000), (2, 63 * 4096 + 1, 20000),
-                                   (1, 1_000_003, 30000), (1, 640 * 4096, 5300), (1, 640 * 4096 + 1, 5300),  # from here on 32 entries
-                                   (16, 256 * 4096, 2100), (16, 256 * 4096 + 1, 2100),                       # and here, by all rows
-                                   (2, 70000, 43750), (2, 70000, 43751)])                                    # nearly all kept
+                                   (1, 1_000_003, 30000)])
 def test_sampled_window(n, d, k, kind):
     rng = np.random.default_rng(d + k)
     ld = B.padded_ld(d)
@@ -56,6 +54,14 @@ def test_sampled_window(n, d, k, kind):
             a, b = np.ascontiguousarray(x.cpu().numpy()), cpu.get(name)
             assert np.array_equal(np.isnan(a), np.isnan(b)) and bits_equal(a[~np.isnan(a)], b[~np.isnan(b)]), (t, name)
     cpu.close()
+
+
+@pytest.mark.parametrize("kind", ["unit", "layers", "few", "unsampled", "zeros", "huge"])
+@pytest.mark.parametrize("n,d,k", [(1, 640 * 4096, 5300), (1, 640 * 4096 + 1, 5300),    # from here on 32 entries
+                                   (16, 256 * 4096, 2100), (16, 256 * 4096 + 1, 2100),  # and here, by all rows
+                                   (2, 70000, 43750), (2, 70000, 43751)])               # nearly all kept
+def test_where_a_window_is_looked_for(n, d, k, kind):
+    test_sampled_window(n, d, k, kind)
 
 
 @pytest.mark.parametrize("most,d,k", [(680, 1, 1), (54, 65536, 655), (54, 65537, 655), (39, 300007, 3000)])
